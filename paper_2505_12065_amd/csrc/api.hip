@@ -175,140 +175,119 @@ int check_common(const void *corpus, int64_t N, int32_t d, int32_t dtype, const 
     return ANN_OK;
 }
 
-int kp_of(int k) { return k <= 4 ? 4 : 16; }
-
 // ---- flat: launch geometry ---------------------------------------------------------------
 struct FlatPlan {
-    int kp, P, nqg_max;
     int wide_ntg;            // > 0: matrix-core path with this many query-tile groups
+    StreamPlan st;           // else the streaming kernel; with wide_ntg and k > 4: the repair pass
+    int P;                   // slabs of the matrix-core path
     int pstride;             // slabs per query in the partial array
     size_t sample_ofs, thr_ofs;   // byte offsets of the sample lists and thresholds in the workspace
     // k > 4 on the matrix-core path: candidate arrays instead of lists, streaming kernel as repair
     bool emit;
-    int emit_cap;                 // entries of a query's candidate array
     int sample_P;                 // > 0: a sampling pass with this many slabs supplies thresholds
     int sample_skip;              // > 0: the sample is the first sample_skip tiles, which the main pass skips
-    int st_P, st_nqg_max;         // geometry of the repair pass (streaming kernel, lists of 16)
     size_t cnt_ofs, cand_ofs;
     size_t ws_bytes;
 };
 
 constexpr int WIDE_MIN_B = 65;   // smallest batch sent to the matrix-core path
-constexpr int EMIT_CAP = 4096;   // candidate-array entries per query (k > 4), a multiple of 16
+// Smallest corpus sent there, for batches beyond 128 and up to it: below, its tiles of 256 rows x 256 (128) queries do
+// not fill the chip and its sampling pass costs more than it saves.  d = 768 fp16, k = 3, us through the streaming / the
+// matrix-core kernel: N = 64 000: B = 100: 53 / 168, B = 256: 82 / 165, B = 1024: 221 / 436; N = 256 000: 140 / 175,
+// 254 / 207, 740 / 507; N = 1 M: 469 / 413, 797 / 526.
+constexpr int64_t WIDE_MIN_N = 160 * 1024, WIDE_MIN_N_128 = 640 * 1024;
+constexpr int EMIT_CAP = 4096;   // candidate-array entries per query (k > 4)
 constexpr int SAMPLE_STRIDE = 64; // a sampling pass scores every 64th row
 constexpr int64_t SAMPLE_MIN_N = 64 * 1024;
-constexpr int64_t EMIT_MIN_N = 128 * 1024;   // smallest corpus with candidate arrays when the batch streams
 
-FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, bool allow_emit = true) {
-    FlatPlan pl;
-    pl.kp = kp_of(k);
-    pl.wide_ntg = 0;
-    pl.emit = false;
-    pl.emit_cap = 0;
-    pl.sample_P = 0;
-    pl.sample_skip = 0;
-    // k > 4 on a large 16-bit corpus: lists of 16 per lane are slow to maintain (and do not fit the
-    // matrix-core kernel's registers), so the main pass keeps no lists; it appends every score that
-    // reaches a lower bound of the query's k-th best to a per-query candidate array.  The bound is
-    // the k-th best of every 64th row (scored exactly by a short first pass), so about 64 k rows per
-    // query pass it; an array that overflows all the same (heavily tied scores) is repaired by the
-    // streaming kernel with lists of 16, which does no work otherwise.
-    // A batch large enough for the matrix-core kernel, which keeps no lists of 16, takes this path at
-    // any corpus size (a sample of fewer than k rows gives a bound of -inf: every row is a candidate);
-    // a small batch streams, and lists of 16 are fine until the corpus is large.
-    const bool wide_batch = B >= WIDE_MIN_B && d % 32 == 0;
-    if (allow_emit && dtype != ANN_F32 && pl.kp == 16 && (wide_batch || N >= EMIT_MIN_N)) {
-        const FlatPlan st = flat_plan(cus, N, d, dtype, B, k, false);     // repair pass
-        const FlatPlan m4 = flat_plan(cus, N, d, dtype, B, 4, false);     // geometry of sampling and main pass
+// The streaming kernel's geometry.
+StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int k) {
+    StreamPlan pl;
+    pl.K = (k + 3) & ~3;
+    const int steps = (d * elem_bytes(dtype) + 63) / 64;
+    const int fit = (int)((LDS_MAX - 16 * 1024) / (WAVE * 16));        // steps of one group of 16 queries that fit LDS
+    const int n16 = (B + 15) / 16;
+    int nqg = fit / steps;
+    nqg = nqg < 1 ? 1 : nqg > STREAM_NQG_MAX(elem_bytes(dtype)) ? STREAM_NQG_MAX(elem_bytes(dtype)) : nqg;
+    nqg = nqg > n16 ? n16 : nqg;
+    pl.lds_steps = steps < fit ? steps : fit;
+    // as many queries per workgroup as possible read the corpus least often; fewer when the tiles of 16 rows would not
+    // give every compute unit a workgroup of 8 waves
+    const int64_t tiles = (N + 15) / 16;
+    while (nqg > 1 && tiles * ((n16 + nqg - 1) / nqg) < (int64_t)cus * 8) --nqg;
+    pl.G = (n16 + nqg - 1) / nqg;
+    pl.nqg = (n16 + pl.G - 1) / pl.G;
+    pl.waves = stream_waves(elem_bytes(dtype), pl.nqg, pl.lds_steps);
+    int occ = (int)(LDS_MAX / stream_lds_bytes(pl.nqg, pl.lds_steps, pl.waves));
+    const int most = STREAM_WG_PER_CU(elem_bytes(dtype), pl.nqg, pl.waves);   // measured: more than 2 do not help
+    occ = occ < 1 ? 1 : (occ > most ? most : occ);
+    // every wave takes whole 16-row tiles in rounds; size the grid so that the last round
+    // is as full as the others instead of leaving most of the chip idle
+    int64_t cap = (int64_t)cus * occ / pl.G;
+    cap = cap < 1 ? 1 : (cap > P_MAX ? P_MAX : cap);
+    const int64_t rounds = (tiles + cap * pl.waves - 1) / (cap * pl.waves);
+    const int64_t P = (tiles + rounds * pl.waves - 1) / (rounds * pl.waves);
+    pl.P = (int)(P < cap ? P : cap);
+    return pl;
+}
+
+FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k) {
+    FlatPlan pl{};
+    const size_t a16 = 15;
+    pl.st = stream_plan(cus, N, d, dtype, B, k);
+    const bool wide = dtype != ANN_F32 && d % 32 == 0 && B >= WIDE_MIN_B && N >= (B > 128 ? WIDE_MIN_N : WIDE_MIN_N_128);
+    if (!wide) {
+        pl.pstride = pl.st.P;
+        pl.ws_bytes = (size_t)B * pl.st.P * pl.st.K * sizeof(Cand);
+        return pl;
+    }
+    // matrix-core path
+    const int nt = (B + wide_query_tile(B) - 1) / wide_query_tile(B);
+    pl.wide_ntg = nt < 8 ? nt : 8;
+    int P = cus / pl.wide_ntg;
+    if (wide_query_tile(B) == 128) P *= 2;       // 4-wave workgroups, two per compute unit
+    const int64_t mtiles = (N + 255) / 256;
+    if (P > mtiles) P = (int)mtiles;
+    pl.P = P < 1 ? 1 : (P > P_MAX ? P_MAX : P);
+    const int64_t stiles = ((N + SAMPLE_STRIDE - 1) / SAMPLE_STRIDE + 255) / 256;
+    if (k > 4) {
+        // Lists of 16 per lane do not fit beside the accumulators, so the main pass keeps no lists; it appends every
+        // score that reaches a lower bound of the query's k-th best to a per-query candidate array.  The bound is
+        // the k-th best of every 64th row (scored exactly by a short first pass), so about 64 k rows per
+        // query pass it; an array that overflows all the same (heavily tied scores) is repaired by the
+        // streaming kernel, which does no work otherwise.  (A sample of fewer than k rows gives a bound
+        // of -inf: every row is a candidate.)
         pl.emit = true;
-        pl.emit_cap = EMIT_CAP;
-        pl.wide_ntg = m4.wide_ntg;
-        pl.P = m4.P;
-        pl.nqg_max = m4.nqg_max;
-        pl.st_P = st.P;
-        pl.st_nqg_max = st.nqg_max;
-        pl.pstride = st.P;
-        const int64_t nv = (N + SAMPLE_STRIDE - 1) / SAMPLE_STRIDE;
-        if (pl.wide_ntg > 0) {
-            const int64_t stiles = (nv + 255) / 256;
-            pl.sample_P = (int)(stiles < pl.P ? stiles : pl.P);
-        } else {
-            const int64_t swaves = (nv + 15) / 16;                         // one 16-row tile per wave at least
-            const int64_t sblocks = (swaves + 7) / 8;
-            pl.sample_P = (int)(sblocks < pl.P ? sblocks : pl.P);
-        }
-        const size_t a16 = 15;
-        pl.sample_ofs = ((size_t)B * st.P * pl.kp * sizeof(Cand) + a16) & ~a16;
+        pl.pstride = pl.st.P;
+        pl.sample_P = (int)(stiles < pl.P ? stiles : pl.P);
+        pl.sample_ofs = ((size_t)B * pl.st.P * pl.st.K * sizeof(Cand) + a16) & ~a16;
         pl.thr_ofs = pl.sample_ofs + (size_t)B * pl.sample_P * 4 * sizeof(Cand);   // lists of 4 per sample slab
         pl.cnt_ofs = (pl.thr_ofs + (size_t)B * sizeof(float) + a16) & ~a16;
         pl.cand_ofs = (pl.cnt_ofs + (size_t)B * sizeof(int) + a16) & ~a16;
         pl.ws_bytes = pl.cand_ofs + (size_t)B * EMIT_CAP * sizeof(Cand);
         return pl;
     }
-    if (dtype != ANN_F32 && B >= WIDE_MIN_B && pl.kp == 4 && d % 32 == 0) {
-        const int nt = (B + wide_query_tile(B) - 1) / wide_query_tile(B);
-        pl.wide_ntg = nt < 8 ? nt : 8;
-        int P = cus / pl.wide_ntg;
-        if (wide_query_tile(B) == 128) P *= 2;       // 4-wave workgroups, two per compute unit
-        const int64_t mtiles = (N + 255) / 256;
-        if (P > mtiles) P = (int)mtiles;
-        pl.P = P < 1 ? 1 : P;
-        pl.nqg_max = 4;
-        // a corpus of some size: score a sample first, exactly, and start the main pass from the k-th
-        // best scores of that sample (few rows then pass the threshold test at all).  Many tiles per
-        // slab: the sample is the first tile of every slab-to-be, kept as one more slab and skipped by
-        // the main pass; otherwise every 64th row, which the main pass scores again.
-        if (mtiles >= 8 * (int64_t)pl.P) {
-            pl.sample_P = pl.sample_skip = pl.P;
-        } else if (N >= SAMPLE_MIN_N) {
-            const int64_t stiles = ((N + SAMPLE_STRIDE - 1) / SAMPLE_STRIDE + 255) / 256;
-            pl.sample_P = (int)(stiles < pl.P ? stiles : pl.P);
-        }
-    } else if (dtype == ANN_F32) {
-        const int64_t groups = (N + 7) / 8;
-        int64_t P = (groups + 3) / 4;
-        const int64_t cap = (int64_t)cus * 4;
-        pl.P = (int)(P < cap ? P : cap);
-        pl.nqg_max = 0;
-    } else {
-        const int steps = (d + 31) / 32;
-        int nqg_max = (int)((LDS_MAX - 16 * 1024) / ((size_t)steps * WAVE * 16));
-        pl.nqg_max = nqg_max > 4 ? 4 : nqg_max;
-        const int nqg = B > 16 * pl.nqg_max ? pl.nqg_max : (B + 15) / 16;
-        const int wpb = stream_waves(nqg, steps, pl.kp);
-        const size_t lds = stream_lds_bytes(nqg, steps, wpb, pl.kp);
-        int occ = (int)(LDS_MAX / lds);
-        occ = occ < 1 ? 1 : (occ > 2 ? 2 : occ);     // measured: more resident workgroups do not help
-        const int64_t tiles = (N + 15) / 16;
-        const int64_t cap = (int64_t)cus * occ;
-        // every wave takes whole 16-row tiles in rounds; size the grid so that the last round
-        // is as full as the others instead of leaving most of the chip idle
-        const int64_t rounds = (tiles + cap * wpb - 1) / (cap * wpb);
-        int64_t P = (tiles + rounds * wpb - 1) / (rounds * wpb);
-        pl.P = (int)(P < cap ? P : cap);
-    }
-    if (pl.P > P_MAX) pl.P = P_MAX;
-    if (pl.P < 1) pl.P = 1;
+    // a corpus of some size: score a sample first, exactly, and start the main pass from the k-th
+    // best scores of that sample (few rows then pass the threshold test at all).  Many tiles per
+    // slab: the sample is the first tile of every slab-to-be, kept as one more slab and skipped by
+    // the main pass; otherwise every 64th row, which the main pass scores again.
+    if (mtiles >= 8 * (int64_t)pl.P) pl.sample_P = pl.sample_skip = pl.P;
+    else if (N >= SAMPLE_MIN_N) pl.sample_P = (int)(stiles < pl.P ? stiles : pl.P);
     pl.pstride = pl.P + (pl.sample_skip > 0 ? 1 : 0);
-    pl.sample_ofs = (size_t)B * pl.pstride * pl.kp * sizeof(Cand);
+    pl.sample_ofs = (size_t)B * pl.pstride * 4 * sizeof(Cand);
     pl.thr_ofs = pl.sample_ofs + (size_t)B * pl.sample_P * 4 * sizeof(Cand);
     pl.ws_bytes = pl.thr_ofs + (pl.sample_P > 0 ? (size_t)B * sizeof(float) : 0);
     return pl;
 }
 
-// 16-bit corpus, streaming kernel over all B queries in one launch: groups of 16 nqg_max queries are
-// served one after the other inside the kernel (kp 0: candidate-array mode)
-int flat_stream_all(int kp, int nqg_max, int P, const void *X, int64_t N, int d, int dtype, const void *Q, int B,
-                    Cand *partial, StreamOpts o, After after, bool timed_launch, hipStream_t stream) {
-    o.after = after;
-    const int group = 16 * nqg_max;
-    const int nqg = B > group ? nqg_max : (B + 15) / 16;
-    o.passes = B > group ? (B + group - 1) / group : 1;
+// Streaming kernel over all B queries.  `timed`: the kernel code the launch is recorded under, < 0: not recorded.
+int flat_stream_all(const StreamPlan &st, const void *X, int64_t N, int d, int dtype, const void *Q, int B, Cand *partial,
+                    const int *need, int need_above, After after, int timed_as, hipStream_t stream) {
     hipError_t e;
     {
-        TimedScope timed(timed_launch ? ANN_KERNEL_FLAT_STREAM : -1, stream);
-        e = dtype == ANN_F16 ? launch_flat_stream_f16(nqg, kp, X, N, d, Q, B, 0, partial, P, o, stream)
-                             : launch_flat_stream_bf16(nqg, kp, X, N, d, Q, B, 0, partial, P, o, stream);
+        TimedScope timed(timed_as, stream);
+        e = (dtype == ANN_F16 ? launch_flat_stream_f16 : dtype == ANN_BF16 ? launch_flat_stream_bf16 : launch_flat_stream_f32)(
+            st, X, N, d, Q, B, partial, need, need_above, after, stream);
     }
     return check_launch("flat_stream_kernel", e);
 }
@@ -321,53 +300,28 @@ int flat_search_emit(const FlatPlan &pl, const void *X, int64_t N, int d, int dt
     int *cnt = reinterpret_cast<int *>(ws + pl.cnt_ofs);
     Cand *cand = reinterpret_cast<Cand *>(ws + pl.cand_ofs);
     // sampling pass: every 64th row, the best 4 per slab and query
-    if (pl.wide_ntg > 0) {
-        hipError_t e = launch_flat_wide(dtype, 1, X, N, d, Q, B, sample, pl.sample_P, pl.wide_ntg, 0, nullptr, pl.sample_P,
-                                        0, nullptr, SAMPLE_STRIDE, after, stream);
-        if (int rc = check_launch("flat_wide_kernel (sample)", e)) return rc;
-    } else {
-        StreamOpts o;
-        o.row_stride = SAMPLE_STRIDE;
-        if (int rc = flat_stream_all(4, pl.nqg_max, pl.sample_P, X, N, d, dtype, Q, B, sample, o, after, false, stream)) return rc;
-    }
+    hipError_t e = launch_flat_wide(dtype, 1, X, N, d, Q, B, sample, pl.sample_P, pl.wide_ntg, 0, nullptr, pl.sample_P,
+                                    0, nullptr, SAMPLE_STRIDE, after, stream);
+    if (int rc = check_launch("flat_wide_kernel (sample)", e)) return rc;
     if (int rc = check_launch("flat_sample_kth_kernel", launch_flat_sample_kth(sample, pl.sample_P, B, k, thr, nullptr, 0, 0, cnt, stream)))
         return rc;
     // main pass: candidates
-    if (pl.wide_ntg > 0) {
-        hipError_t e;
-        {
-            TimedScope timed(ANN_KERNEL_FLAT_WIDE, stream);
-            e = launch_flat_wide(dtype, 2, X, N, d, Q, B, cand, pl.P, pl.wide_ntg, 0, thr, pl.emit_cap, 0, cnt, 1, after, stream);
-        }
-        if (int rc = check_launch("flat_wide_kernel (candidates)", e)) return rc;
-    } else {
-        StreamOpts o;
-        o.thr = thr;
-        o.count = cnt;
-        o.cap = pl.emit_cap;
-        if (int rc = flat_stream_all(0, pl.nqg_max, pl.P, X, N, d, dtype, Q, B, cand, o, after, true, stream)) return rc;
+    {
+        TimedScope timed(ANN_KERNEL_FLAT_WIDE, stream);
+        e = launch_flat_wide(dtype, 2, X, N, d, Q, B, cand, pl.P, pl.wide_ntg, 0, thr, EMIT_CAP, 0, cnt, 1, after, stream);
     }
+    if (int rc = check_launch("flat_wide_kernel (candidates)", e)) return rc;
     // repair pass: returns at once unless a candidate array overflowed
-    StreamOpts o;
-    o.need = cnt;
-    o.need_above = pl.emit_cap;
-    if (int rc = flat_stream_all(pl.kp, pl.st_nqg_max, pl.st_P, X, N, d, dtype, Q, B, partial, o, after, false, stream)) return rc;
-    return check_launch("flat_merge_kernel",
-                        launch_flat_merge(pl.kp, partial, pl.st_P, B, k, ids, scores, cnt, cand, pl.emit_cap, stream));
+    if (int rc = flat_stream_all(pl.st, X, N, d, dtype, Q, B, partial, cnt, EMIT_CAP, after, -1, stream)) return rc;
+    return check_launch("flat_merge_lists_kernel",
+                        launch_flat_merge_lists(dtype, partial, pl.st.P, pl.st.K, pl.st.slots(), X, N, d, Q, B, k, ids, scores,
+                                                cnt, cand, EMIT_CAP, after, stream));
 }
 
 int flat_search_run(const FlatPlan &pl, const void *X, int64_t N, int d, int dtype, const void *Q, int B, int k,
                     int32_t *ids, float *scores, Cand *partial, After after, hipStream_t stream) {
     if (pl.emit) return flat_search_emit(pl, X, N, d, dtype, Q, B, k, ids, scores, reinterpret_cast<char *>(partial), after, stream);
-    if (dtype == ANN_F32) {
-        hipError_t e;
-        {
-            TimedScope timed(ANN_KERNEL_FLAT_F32, stream);
-            e = launch_flat_f32(pl.kp, static_cast<const float *>(X), N, d, static_cast<const float *>(Q), B, partial,
-                                pl.P, after, stream);
-        }
-        if (int rc = check_launch("flat_f32_kernel", e)) return rc;
-    } else if (pl.wide_ntg > 0) {
+    if (pl.wide_ntg > 0) {
         const float *thr0 = nullptr;
         if (pl.sample_P > 0) {
             Cand *sample = reinterpret_cast<Cand *>(reinterpret_cast<char *>(partial) + pl.sample_ofs);
@@ -389,9 +343,16 @@ int flat_search_run(const FlatPlan &pl, const void *X, int64_t N, int d, int dty
         }
         if (int rc = check_launch("flat_wide_kernel", e)) return rc;
     } else {
-        if (int rc = flat_stream_all(pl.kp, pl.nqg_max, pl.P, X, N, d, dtype, Q, B, partial, StreamOpts(), after, true, stream)) return rc;
+        // (recorded by what the caller asked for: fp32, or the batch class whose kernel this is or stands in for)
+        const int code = dtype == ANN_F32 ? ANN_KERNEL_FLAT_F32
+                         : B >= WIDE_MIN_B && d % 32 == 0 ? ANN_KERNEL_FLAT_WIDE : ANN_KERNEL_FLAT_STREAM;
+        if (int rc = flat_stream_all(pl.st, X, N, d, dtype, Q, B, partial, nullptr, 0, after, code, stream)) return rc;
+        if (k > 4)
+            return check_launch("flat_merge_lists_kernel",
+                                launch_flat_merge_lists(dtype, partial, pl.st.P, pl.st.K, pl.st.slots(), X, N, d, Q, B, k, ids,
+                                                        scores, nullptr, nullptr, 0, after, stream));
     }
-    return check_launch("flat_merge_kernel", launch_flat_merge(pl.kp, partial, pl.pstride, B, k, ids, scores, nullptr, nullptr, 0, stream));
+    return check_launch("flat_merge_kernel", launch_flat_merge(partial, pl.pstride, B, k, ids, scores, stream));
 }
 
 }  // namespace
@@ -572,7 +533,6 @@ int ann_flat_search_after_typed(const void *corpus, int64_t N, int32_t d, int32_
     DeviceState *st = nullptr;
     if (int rc = device_state(&st)) return rc;
     const FlatPlan pl = flat_plan(st->cus, N, d, dtype, B, k);
-    if (dtype != ANN_F32 && pl.nqg_max < 1) return fail(ANN_ERR_INVALID, "d = %d too large for LDS", d);
     void *ws = nullptr;
     if (int rc = workspace_for(st, &st->ws, &st->ws_bytes, pl.ws_bytes, &ws)) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -598,7 +558,6 @@ int ann_flat_search_static(const void *corpus, int64_t N, int32_t d, int32_t dty
     DeviceState *st = nullptr;
     if (int rc = device_state(&st)) return rc;
     const FlatPlan pl = flat_plan(st->cus, N, d, dtype, B, k);
-    if (dtype != ANN_F32 && pl.nqg_max < 1) return fail(ANN_ERR_INVALID, "d = %d too large for LDS", d);
     if (pl.ws_bytes > (size_t)ANN_STATIC_WORKSPACE_BYTES)
         return fail(ANN_ERR_INVALID, "this search needs %zu bytes of workspace, the static one holds %d",
                     pl.ws_bytes, ANN_STATIC_WORKSPACE_BYTES);

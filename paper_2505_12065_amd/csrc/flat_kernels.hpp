@@ -2,15 +2,12 @@
 // and the k best per query are kept (Section 2.1 of the paper: exact nearest
 // neighbour retrieval; the score matrix is never written to memory).
 //
-//   flat_stream_kernel  16-bit corpora, up to 64 queries per pass: the corpus is
-//                       streamed from HBM exactly once straight into MFMA operand
-//                       registers; queries sit in LDS in MFMA fragment order.
-//   flat_f32_kernel     fp32 corpora: vector FMA, 8 lanes per row.
-//   flat_merge_kernel   per query: the k best of all slabs' partial lists.
+//   flat_stream_kernel  the corpus is streamed straight into MFMA operand registers, each row once per group
+//                       of up to 64 queries; queries sit in LDS in MFMA fragment order.  All element types.
+//   (flat_merge.hpp     per query: the k best of all slabs' lists)
 //
-// Every kernel keeps, per lane, a sorted register list of the KP >= k best
-// pairs it has seen; lists are merged lane -> wave -> workgroup -> grid under
-// the same total order, so the result does not depend on how rows were split.
+// Every lane keeps a sorted register list of the 4 best pairs it has seen, whatever k is; lists are merged
+// lane -> workgroup -> grid under the same total order, so the result does not depend on how rows were split.
 #pragma once
 
 #include "common.hpp"
@@ -18,98 +15,253 @@
 
 namespace ann {
 
-constexpr int STREAM_UNROLL = 8;   // 16-byte loads a lane keeps in flight (6..24 measured alike)
+constexpr int LANE_KP = 4;                            // entries of a lane's list
+constexpr int STREAM_BATCH = 4;                       // 16-byte loads per batch; two batches per lane in flight
 
-// Corpus rows are the M side of a 16x16x32 MFMA, queries the N side: a lane ends
-// up with one query (lane % 16) and four rows (4*(lane/16) + i) per tile of 16 rows.
-//   X        [N, d] 16-bit           Q  [B, d] 16-bit (queries q0 .. q0+NQG*16 are used)
-//   partial  [B, P, KP] pairs, P = gridDim.x
-//   o        see StreamOpts: row stride of a sampling pass, and (EMIT, for k > 4) no lists at all:
-//            every (score, row) with score >= o.thr[q] is appended to the candidate array
-//            partial[q * o.cap ..) through o.count[q]
-// One pass of the whole workgroup (NWV wavefronts) over its share of the corpus for NQG*16 queries.
-template <class T, int NQG, int KP, bool DFULL, bool EMIT, int NWV>
-__device__ __forceinline__ void flat_stream_pass(const void *__restrict__ X, int64_t N, int d,
-                                                 const void *__restrict__ Q, int B, int q0,
-                                                 Cand *__restrict__ partial, const StreamOpts &o,
-                                                 unsigned char *smem) {
-    const int S = o.row_stride;
-    const int64_t NV = (N + S - 1) / S;               // rows 0, S, 2S, ... are "virtual" rows 0 .. NV-1
-    u4 *qf = reinterpret_cast<u4 *>(smem);            // [NQG][steps][64]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwaves = blockDim.x >> 6;
-    const int steps = (d + 31) >> 5;
-    const int P = gridDim.x;
+// Row r of a 16-row MFMA tile is corpus row 16 tile + tile_row(r): lane group g = lane / 16 then receives the
+// scores of corpus rows g, g + 4, g + 8, g + 12 of the tile, so that neighbouring rows (passages of one document,
+// often close to the same query) go to different lanes' lists.
+__device__ __forceinline__ int tile_row(int r) { return ((r & 3) << 2) | (r >> 2); }
+
+// The K best (a multiple of 4, at most 16) of the 4 LG... entries held by an aligned group of LG lanes (32 or 64),
+// LANE_KP sorted keys each (empty slots: the key of (-inf, EMPTY_ID)), written to out[0 .. K) in order by the group;
+// fewer than K entries: the rest is written empty.  `mem`: LDS scratch of 64 keys that belongs to the group alone
+// (only its own wave touches it: no barrier).
+//   K <= 4: four rounds of "largest head wins and is popped".
+//   K > 4:  rounds cost 40 instructions each, so instead the heads' scores are sorted across the lanes; the
+//           K-th is a bound that some 20 of the entries reach; those are ranked by counting.  (More than 64
+//           reach it only when many scores are equal: then rounds it is.)
+template <int LG>
+__device__ __forceinline__ void group_select(uint64_t (&key)[LANE_KP], int K, uint64_t *mem, Cand *out, bool store) {
+    const int lane = threadIdx.x & (WAVE - 1), sub = lane & (LG - 1);
+    const uint64_t empty = order_key(-INFINITY, EMPTY_ID);
+    auto put = [&](int r, uint64_t k64) {
+        Cand c;
+        order_key_decode(k64, c.s, c.id);
+        out[r] = c;
+    };
+    bool rounds = K <= 4;
+    if (!rounds) {
+        const uint32_t sorted = group_sort_desc<LG>((uint32_t)(key[0] >> 32));
+        uint32_t T = (uint32_t)__builtin_amdgcn_readlane((int)sorted, K - 1);
+        if constexpr (LG == 32) {
+            const uint32_t T1 = (uint32_t)__builtin_amdgcn_readlane((int)sorted, 32 + K - 1);
+            T = lane < 32 ? T : T1;
+        }
+        const uint64_t mine = LG == 64 ? ~0ull : 0xffffffffull << (lane & 32);     // the lanes of this group
+        const uint64_t below = mine & ((1ull << lane) - 1ull);
+        int pos[LANE_KP], c = 0;
+        bool in[LANE_KP];
+#pragma unroll
+        for (int e = 0; e < LANE_KP; ++e) {
+            in[e] = (uint32_t)(key[e] >> 32) >= T && key[e] != empty;
+            const uint64_t m = __builtin_amdgcn_ballot_w64(in[e]);
+            pos[e] = c + __builtin_popcountll(m & below);
+            c += __builtin_popcountll(m & mine);
+        }
+        const int c0 = __builtin_amdgcn_readlane(c, 0), c1 = __builtin_amdgcn_readlane(c, 63);
+        const int cmax = max(c0, c1);
+        if (cmax <= 64) {
+#pragma unroll
+            for (int e = 0; e < LANE_KP; ++e)
+                if (in[e]) mem[pos[e]] = key[e];
+            constexpr int PER = 64 / LG;
+            uint64_t my[PER];
+            int rank[PER];
+#pragma unroll
+            for (int u = 0; u < PER; ++u) { my[u] = mem[sub + u * LG]; rank[u] = 0; }
+            for (int j0 = 0; j0 < cmax; j0 += 4) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const uint64_t o = mem[(j0 + t) & 63];
+#pragma unroll
+                    for (int u = 0; u < PER; ++u) rank[u] += (int)(j0 + t < c) & (int)(o > my[u]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < PER; ++u)
+                if (store && sub + u * LG < c && rank[u] < K) put(rank[u], my[u]);
+            if (store && sub < K && sub >= c) put(sub, empty);
+        } else {
+            rounds = true;
+        }
+    }
+    if (rounds) {
+        for (int r = 0; r < K; ++r) {
+            const uint64_t m = group_max<1, LG>(key[0]);
+            if (key[0] == m) {
+#pragma unroll
+                for (int i = 0; i + 1 < LANE_KP; ++i) key[i] = key[i + 1];
+                key[LANE_KP - 1] = empty;
+            }
+            if (store && sub == 0) put(r, m);
+        }
+    }
+}
+
+// What the streaming kernel works on.
+struct StreamShape {
+    const void *X;      // [N, d]
+    const void *Q;      // [B, d]
+    int64_t N;
+    int d, B;
+};
+
+// MFMA operand of one 64-byte step of a row (or query) that may end inside the step: the chunk is zeroed past the end
+__device__ __forceinline__ u4 mask_tail(u4 x, bool inside) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = inside ? x[i] : 0u;
+    return x;
+}
+
+// Corpus rows are the M side of a 16x16 MFMA, queries the N side: a lane ends up with one query (lane % 16)
+// and four rows per tile of 16 rows (see tile_row).  A step is 64 bytes of a row: 32 16-bit or 16 fp32 columns.
+//   FULL: a row is a whole number of 256-byte batches (else the last batch and step are cut to size).
+//   grid: P slabs x G groups of 16 NQG queries, the groups of a slab side by side on one XCD, so that a slab that
+//         several groups read comes from HBM once.  Tile t belongs to wave t % (P NWV) of the grid.
+//   partial [B, P, K] pairs, K = 4, 8, 12 or 16 (>= k), every list sorted, empty slots (-inf, EMPTY_ID) last.
+//   lds_steps: steps of a query that fit LDS (fewer than all of them only for fp32 rows beyond 2304 columns, where
+//         one group of queries alone is larger than LDS: the rest comes from memory, NQG = 1, not FULL).
+//   need: a group of queries is skipped unless need[q] > need_above for one of them (repair pass behind the
+//         candidate arrays of the matrix-core kernel: usually every group is skipped).
+// Lists of 4 are exact for k <= 4.  For k > 4 a lane may meet more than 4 of the k best rows; the merge then finds 4
+// rows of one lane among the k best and goes over that lane's rows again (flat_merge_lists_kernel).
+//
+// Bound by HBM for up to 64 queries on a large corpus.  Loads come in batches of 4, the next batch always requested
+// before the products of the one before it, across tiles: without that a row of 12 steps (d = 384) paid four
+// latencies a tile.  Lists of 4 for every k replace lists of 16 (3.5 times the time) and, on large corpora, a
+// sampling pass with candidate arrays (three more launches and global atomics); fp32 runs here too, on the matrix
+// cores, at most 32 queries to a workgroup (more do not raise the rate: eight products of 32 clocks per 1 KB of rows).
+// Registers: two workgroups of 8 waves (or one of 16) per compute unit, except fp32 with two groups of queries (128
+// registers of accumulators), which runs one workgroup and is bound by the products.
+template <class T, int NQG, bool FULL, int NWV>
+__global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NWV / 4) void flat_stream_kernel(StreamShape sh, Cand *__restrict__ partial, int P, int G,
+                                                               int K, int lds_steps, const int *__restrict__ need,
+                                                               int need_above, After after) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    u4 *qf = reinterpret_cast<u4 *>(smem);            // [NQG][lds_steps][64]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int rb = sh.d * T::bytes;                   // bytes of a row
+    const int steps = (rb + 63) >> 6;
+    const int B = sh.B;
+    const int64_t N = sh.N;
+    int lb = blockIdx.x;
+    if ((gridDim.x & 7) == 0) lb = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const int slab = lb / G, q0 = (lb % G) * (NQG * 16);
+    if (need) {
+        const int q = q0 + tid;
+        if (!__syncthreads_or(tid < NQG * 16 && q < B && need[q] > need_above)) return;
+    }
+
+    // the rows this wave starts with are requested before the queries are put into LDS
+    const int64_t ntiles = (N + 15) >> 4, tstride = (int64_t)P * NWV;
+    const int kofs = (lane >> 4) * 16;                // this lane's byte offset inside a step
+    int64_t tile = (int64_t)slab * NWV + wave;
+    const char *rp = nullptr;                         // this lane's row of the tile being loaded, kofs included
+    auto row_ptr = [&](int64_t t) {
+        int64_t row = t * 16 + tile_row(lane & 15);
+        row = row < N ? row : N - 1;                  // tail tile: re-read the last row, masked below
+        rp = static_cast<const char *>(sh.X) + (size_t)row * rb + kofs;
+    };
+    int64_t ltile = tile;                             // tile and step of the next batch to load
+    int lstep = 0;
+    if (tile < ntiles) row_ptr(tile);
+    auto load = [&](u4 (&a)[STREAM_BATCH]) {
+#pragma unroll
+        for (int u = 0; u < STREAM_BATCH; ++u) {
+            if constexpr (FULL) a[u] = load_chunk(rp + (lstep + u) * 64);
+            else a[u] = load_chunk(rp + min(min(lstep + u, steps - 1) * 64, rb - 16 - kofs));
+        }
+        lstep += STREAM_BATCH;
+        if (lstep >= steps) {
+            lstep = 0;
+            ltile += tstride;
+            if (ltile < ntiles) row_ptr(ltile);       // (past the end: the last tile once more, never used)
+        }
+    };
+    u4 xa[STREAM_BATCH], xb[STREAM_BATCH];
+    if (tile < ntiles) load(xa);
 
     // queries -> LDS, already in B-operand order: fragment (g, s) holds for lane l
-    // the 8 values k = 32 s + 8 (l / 16) .. of query q0 + 16 g + l % 16
-    for (int idx = tid; idx < NQG * steps * WAVE; idx += blockDim.x) {
-        const int l = idx & 63, s = (idx >> 6) % steps, g = (idx >> 6) / steps;
-        const int q = q0 + g * 16 + (l & 15), kb = s * 32 + (l >> 4) * 8;
+    // the 16 bytes from 64 s + 16 (l / 16) on of query q0 + 16 g + l % 16
+    auto query_chunk = [&](int q, int ofs) {
         u4 v = zero_chunk();
-        if (q < B && kb < d) v = load_chunk(static_cast<const char *>(Q) + ((size_t)q * d + kb) * 2);
-        qf[idx] = v;
-    }
-    __syncthreads();
-
-    TopList<KP> best[NQG];
-    float thr[NQG];
-    float bnd_s[NQG];                                 // continuation: this lane's queries' boundary pairs
-    int bnd_id[NQG];
-    const bool bounded = o.after.s != nullptr;
+        if (q < B && ofs < rb) v = load_chunk(static_cast<const char *>(sh.Q) + (size_t)q * rb + ofs);
+        return v;
+    };
+    for (int i0 = wave; i0 < NQG * lds_steps; i0 += 4 * NWV) {
+        u4 v[4];
 #pragma unroll
-    for (int g = 0; g < NQG; ++g) {
-        const int qb = min(q0 + g * 16 + (lane & 15), B - 1);
-        bnd_s[g] = bounded ? o.after.s[qb] : 0.f;
-        bnd_id[g] = bounded ? o.after.id[qb] : 0;
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + u * NWV, g = i / lds_steps, s = i - g * lds_steps;
+            v[u] = i < NQG * lds_steps ? query_chunk(q0 + g * 16 + (lane & 15), s * 64 + kofs) : zero_chunk();
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + u * NWV;
+            if (i < NQG * lds_steps) qf[i * WAVE + lane] = TileSum<T>::operand(v[u]);
+        }
     }
+
+    TopList<LANE_KP> best[NQG];
+    float thr[NQG];
 #pragma unroll
     for (int g = 0; g < NQG; ++g) {
         best[g].init();
         thr[g] = -INFINITY;
-        if constexpr (EMIT) {                         // fixed thresholds; queries past B never emit
-            const int q = q0 + g * 16 + (lane & 15);
-            thr[g] = q < B ? o.thr[q] : INFINITY;
-        }
     }
+    TileSum<T> part[NQG];
+    auto clear = [&] {
+#pragma unroll
+        for (int g = 0; g < NQG; ++g) part[g].clear();
+    };
+    clear();
+    __syncthreads();
 
-    const int64_t ntiles = (NV + 15) >> 4;
-    const int kofs = (lane >> 4) * 8;                 // this lane's k offset inside a 32-wide step
-    for (int64_t tile = (int64_t)blockIdx.x * nwaves + wave; tile < ntiles; tile += (int64_t)P * nwaves) {
-        int64_t row = tile * 16 + (lane & 15);
-        if (row >= NV) row = NV - 1;                  // tail tile: re-read the last row, masked below
-        const char *rp = static_cast<const char *>(X) + ((size_t)row * S * d + kofs) * 2;
+    int cstep = 0;                                    // step of the batch being multiplied
+    // products of one batch; true when it was the last of its tile
+    auto multiply = [&](u4 (&a)[STREAM_BATCH]) -> bool {
+#pragma unroll
+        for (int u = 0; u < STREAM_BATCH; ++u) {
+            const int s = cstep + u;
+            if (FULL || u == 0 || s < steps) {
+                u4 x = a[u];
+                if constexpr (!FULL) {
+                    if (s * 64 + 64 > rb) x = mask_tail(x, s * 64 + kofs < rb);
+                }
+                x = TileSum<T>::operand(x);
+#pragma unroll
+                for (int g = 0; g < NQG; ++g) {
+                    u4 y;
+                    if (FULL || NQG > 1 || s < lds_steps) y = qf[(g * lds_steps + s) * WAVE + lane];
+                    else y = TileSum<T>::operand(query_chunk(q0 + (lane & 15), s * 64 + kofs));
+                    part[g].step(u, x, y);            // (batches start at even steps)
+                }
+                if constexpr (T::bytes == 4) __builtin_amdgcn_sched_barrier(0);   // (one transposed chunk at a time)
+            }
+        }
+        cstep += STREAM_BATCH;
+        if (cstep < steps) return false;
+        cstep = 0;
+        return true;
+    };
+    auto finish_tile = [&] {
+        const int rbase = (int)(tile * 16) + (lane >> 4);                // rows rbase + 4 i; N < 2^31
+        const int nrows = (int)N;
         f4 acc[NQG];
 #pragma unroll
-        for (int g = 0; g < NQG; ++g) acc[g] = f4{0.f, 0.f, 0.f, 0.f};
-
-        int s = 0;
-        for (; s + STREAM_UNROLL <= steps; s += STREAM_UNROLL) {
-            u4 a[STREAM_UNROLL];
+        for (int g = 0; g < NQG; ++g) acc[g] = part[g].sum();
+        if (after.s) {                                // rows at or before a query's boundary do not take part
 #pragma unroll
-            for (int u = 0; u < STREAM_UNROLL; ++u) {
-                if (DFULL || (s + u) * 32 + kofs < d) a[u] = load_chunk(rp + (size_t)(s + u) * 64);
-                else a[u] = zero_chunk();
+            for (int g = 0; g < NQG; ++g) {           // (the pairs come from the L1: no registers to hold them)
+                int l = lane;
+                asm volatile("" : "+v"(l));           // (nor to hold what their addresses are made of)
+                const int qb = min(q0 + g * 16 + (l & 15), B - 1);
+                const float bs = after.s[qb];
+                const int bid = after.id[qb];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[g][i] = after_boundary(acc[g][i], rbase + 4 * i, bs, bid);
             }
-#pragma unroll
-            for (int u = 0; u < STREAM_UNROLL; ++u)
-#pragma unroll
-                for (int g = 0; g < NQG; ++g)
-                    acc[g] = mfma16<T>(a[u], qf[(g * steps + s + u) * WAVE + lane], acc[g]);
-        }
-        for (; s < steps; ++s) {
-            u4 a = zero_chunk();
-            if (DFULL || s * 32 + kofs < d) a = load_chunk(rp + (size_t)s * 64);
-#pragma unroll
-            for (int g = 0; g < NQG; ++g)
-                acc[g] = mfma16<T>(a, qf[(g * steps + s) * WAVE + lane], acc[g]);
-        }
-
-        const int64_t rbase = tile * 16 + (lane >> 4) * 4;
-        if (bounded) {                                // rows at or before a query's boundary do not take part
-#pragma unroll
-            for (int g = 0; g < NQG; ++g)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[g][i] = after_boundary(acc[g][i], (int)((rbase + i) * S), bnd_s[g], bnd_id[g]);
         }
         static_for<NQG>([&](auto gc) {
             constexpr int g = decltype(gc)::value;
@@ -117,260 +269,65 @@ __device__ __forceinline__ void flat_stream_pass(const void *__restrict__ X, int
             const float m = fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]));
             if (__builtin_amdgcn_ballot_w64(m >= thr[g]) != 0) {        // rare after warm-up
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int64_t r = rbase + i;
-                    if constexpr (EMIT) {
-                        if (r < NV && a[i] >= thr[g]) {
-                            const int q = q0 + g * 16 + (lane & 15);
-                            const int slot = atomicAdd(&o.count[q], 1);
-                            if (slot < o.cap) partial[(size_t)q * o.cap + slot] = Cand{a[i], (int)(r * S)};
-                        }
-                    } else {
-                        const int id = (int)(r * S);
-                        if (r < NV && a[i] >= thr[g] && best[g].admits(a[i], id)) best[g].insert(a[i], id);
-                    }
+                for (int i = 0; i < 4; ++i)
+                    if (rbase + 4 * i < nrows && a[i] >= thr[g]) best[g].insert(a[i], rbase + 4 * i);
+                float t = best[g].s[LANE_KP - 1];
+                if (K <= LANE_KP) {
+                    // the 4th best of any lane that serves the same query bounds the final
+                    // k-th best from below, so it is a safe rejection threshold for all four
+                    uint32_t p, q;
+                    row_pair<16>(__float_as_uint(t), p, q);
+                    t = fmaxf(__uint_as_float(p), __uint_as_float(q));
+                    row_pair<32>(__float_as_uint(t), p, q);
+                    t = fmaxf(__uint_as_float(p), __uint_as_float(q));
                 }
-                if constexpr (!EMIT) {
-                    // the KP-th best of any lane that serves the same query bounds the final
-                    // KP-th best from below, so it is a safe rejection threshold for all four
-                    float t = best[g].s[KP - 1];
-                    t = fmaxf(t, __shfl_xor(t, 16));
-                    t = fmaxf(t, __shfl_xor(t, 32));
-                    thr[g] = fmaxf(thr[g], t);
-                }
+                thr[g] = fmaxf(thr[g], t);
             }
         });
+        clear();
+        tile += tstride;
+    };
+    if (tile < ntiles) {
+        for (;;) {
+            load(xb);
+            __builtin_amdgcn_sched_barrier(0);        // the requests stay ahead of the products
+            if (multiply(xa)) {
+                finish_tile();
+                if (tile >= ntiles) break;
+            }
+            load(xa);
+            __builtin_amdgcn_sched_barrier(0);
+            if (multiply(xb)) {
+                finish_tile();
+                if (tile >= ntiles) break;
+            }
+        }
     }
 
-    if constexpr (EMIT) return;
-    // the four lanes that share a query -> one list per wave and query
+    // every lane's lists -> LDS, then 16 queries at a time: the 4 NWV lists of a query by 4 NWV lanes
+    constexpr int LG = 4 * NWV, QS = LG * LANE_KP + 4;                   // (padded: the writes of 16 queries spread over the banks)
+    static_assert(NWV == 8 || NWV == 16, "a query's lists fill half a wave or a whole one");
+    Cand *wl = reinterpret_cast<Cand *>(smem);
     __syncthreads();                                   // query fragments are dead from here
-    Cand *wl = reinterpret_cast<Cand *>(smem);         // [nwaves][NQG*16][KP]
     static_for<NQG>([&](auto gc) {
         constexpr int g = decltype(gc)::value;
-        TopList<KP> wbest;
-        group_top<KP, KP, 16, 64>(best[g], wbest);
-        if (lane < 16) {
+        Cand *o = wl + (g * 16 + (lane & 15)) * QS + (wave * 4 + (lane >> 4)) * LANE_KP;
 #pragma unroll
-            for (int j = 0; j < KP; ++j)
-                wl[((size_t)wave * NQG * 16 + g * 16 + lane) * KP + j] = Cand{wbest.s[j], wbest.id[j]};
-        }
+        for (int j = 0; j < LANE_KP; ++j) o[j] = Cand{best[g].s[j], best[g].id[j]};
     });
     __syncthreads();
-    // the block's list of a query: its NWV wave lists spread over 4 NWV lanes (4 lanes per wave
-    // list, KP/4 consecutive entries each), 16 queries per pass of the workgroup
-    constexpr int LP = KP / 4, LG = 4 * NWV;
-    static_assert((NWV == 8 || NWV == 16) && KP % 4 == 0, "the final selection splits every wave list four ways");
-    const int sub = tid & (LG - 1), w = sub >> 2, part = sub & 3;
-#pragma unroll
+    const int sub = tid & (LG - 1);
+#pragma unroll 1
     for (int pass = 0; pass < NQG; ++pass) {
         const int qi = pass * 16 + tid / LG;
-        TopList<LP> mine;
+        Cand *in = wl + qi * QS;
+        uint64_t key[LANE_KP];
 #pragma unroll
-        for (int j = 0; j < LP; ++j) {
-            const Cand c = wl[((size_t)w * NQG * 16 + qi) * KP + part * LP + j];
-            mine.s[j] = c.s;
-            mine.id[j] = c.id;
+        for (int j = 0; j < LANE_KP; ++j) {
+            const Cand c = in[sub * LANE_KP + j];
+            key[j] = order_key(c.s, c.id);
         }
-        TopList<KP> fin;
-        group_top<KP, LP, 1, LG>(mine, fin);
-        if (sub == 0 && q0 + qi < B) {
-            Cand *out = partial + ((size_t)(q0 + qi) * P + blockIdx.x) * KP;
-#pragma unroll
-            for (int j = 0; j < KP; ++j) out[j] = Cand{fin.s[j], fin.id[j]};
-        }
-    }
-}
-
-// o.passes consecutive groups of NQG*16 queries starting at q0, one after the other in one launch.
-// With o.need, a group is skipped unless need[q] > need_above for one of its queries (the repair
-// pass behind the candidate arrays: usually every group is skipped).
-template <class T, int NQG, int KP, bool DFULL, bool EMIT, int NWV>
-__global__ __launch_bounds__(NWV * 64) void flat_stream_kernel(const void *__restrict__ X, int64_t N, int d,
-                                                          const void *__restrict__ Q, int B, int q0,
-                                                          Cand *__restrict__ partial, StreamOpts o) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    for (int pass = 0; pass < o.passes; ++pass, q0 += NQG * 16) {
-        if (o.need) {
-            const int q = q0 + (int)threadIdx.x;
-            const int mine = threadIdx.x < NQG * 16 && q < B && o.need[q] > o.need_above;
-            if (!__syncthreads_or(mine)) continue;
-        }
-        if (pass) __syncthreads();                    // the previous pass is done with the LDS
-        flat_stream_pass<T, NQG, KP, DFULL, EMIT, NWV>(X, N, d, Q, B, q0, partial, o, smem);
-    }
-}
-
-// fp32 corpora.  8 lanes share a row (float4 chunks c, c+8, ...), a wave covers 8
-// rows per step, 8 queries per pass live in LDS; lane c of a row group keeps the
-// list of query q0 + c.  gridDim = (P slabs, ceil(B / 8)).
-//   partial [B, P, KP]
-template <int KP>
-__global__ __launch_bounds__(256) void flat_f32_kernel(const float *__restrict__ X, int64_t N, int d,
-                                                       const float *__restrict__ Q, int B,
-                                                       Cand *__restrict__ partial, After after) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    u4 *qs = reinterpret_cast<u4 *>(smem);            // [8][d/4]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwaves = blockDim.x >> 6;
-    const int nch = d >> 2;
-    const int q0 = blockIdx.y * 8;
-    const int P = gridDim.x;
-    for (int idx = tid; idx < 8 * nch; idx += blockDim.x) {
-        const int q = q0 + idx / nch, c = idx % nch;
-        qs[idx] = q < B ? load_chunk(Q + (size_t)q * d + c * 4) : zero_chunk();
-    }
-    __syncthreads();
-
-    TopList<KP> best;
-    best.init();
-    const int r8 = lane >> 3, c8 = lane & 7;
-    const int qb = min(q0 + c8, B - 1);               // continuation: the boundary pair of this lane's query
-    const float bnd_s = after.s ? after.s[qb] : 0.f;
-    const int bnd_id = after.s ? after.id[qb] : 0;
-    const int64_t ngroups = (N + 7) >> 3;
-    for (int64_t grp = (int64_t)blockIdx.x * nwaves + wave; grp < ngroups; grp += (int64_t)P * nwaves) {
-        const int64_t row = grp * 8 + r8;
-        const int64_t rowc = row < N ? row : N - 1;
-        const float *rp = X + (size_t)rowc * d;
-        float acc[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) acc[q] = 0.f;
-        for (int c = c8; c < nch; c += 8) {
-            const u4 x = load_chunk(rp + c * 4);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) acc[q] = dot_chunk<F32>(x, qs[q * nch + c], acc[q]);
-        }
-        float mine = 0.f;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            float v = acc[q];
-            v += __shfl_xor(v, 1);
-            v += __shfl_xor(v, 2);
-            v += __shfl_xor(v, 4);
-            if (q == c8) mine = v;
-        }
-        if (after.s) mine = after_boundary(mine, (int)row, bnd_s, bnd_id);
-        if (row < N && best.admits(mine, (int)row)) best.insert(mine, (int)row);
-    }
-    best.merge_xor(8);
-    best.merge_xor(16);
-    best.merge_xor(32);
-
-    __syncthreads();
-    Cand *wl = reinterpret_cast<Cand *>(smem);         // [nwaves][8][KP]
-    if (lane < 8) {
-#pragma unroll
-        for (int j = 0; j < KP; ++j) wl[((size_t)wave * 8 + lane) * KP + j] = Cand{best.s[j], best.id[j]};
-    }
-    __syncthreads();
-    if (tid < 8 && q0 + tid < B) {
-        TopList<KP> fin;
-        fin.init();
-        for (int w = 0; w < nwaves; ++w)
-            for (int j = 0; j < KP; ++j) {
-                const Cand c = wl[((size_t)w * 8 + tid) * KP + j];
-                if (fin.admits(c.s, c.id)) fin.insert(c.s, c.id);
-            }
-        Cand *out = partial + ((size_t)(q0 + tid) * P + blockIdx.x) * KP;
-#pragma unroll
-        for (int j = 0; j < KP; ++j) out[j] = Cand{fin.s[j], fin.id[j]};
-    }
-}
-
-// One workgroup (1 to 4 wavefronts, by the amount of work) per query: the k best of its
-// P*KP partial pairs, written in order; unused tail slots become id -1 / score -inf.
-// best <- best of itself and in[first], in[first + stride], ...: eight loads in flight per
-// thread, so a short list costs one memory latency instead of one per element
-template <int KP>
-__device__ __forceinline__ void gather_best(const Cand *__restrict__ in, int total, int first, int stride,
-                                            TopList<KP> &best) {
-    for (int e0 = first; e0 < total; e0 += 8 * stride) {
-        Cand c[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int e = e0 + u * stride;
-            c[u] = e < total ? in[e] : Cand{-INFINITY, EMPTY_ID};
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (best.admits(c[u].s, c[u].id)) best.insert(c[u].s, c[u].id);
-    }
-}
-
-// count == null: query q's input is its P lists of KP at partial[q * P * KP ..).  count given: the
-// input is the candidate array of count[q] entries at cand[q * cap ..), unless it overflowed
-// (count[q] > cap): then the P lists, which the repair pass has filled for exactly those queries.
-template <int KP>
-__global__ __launch_bounds__(256) void flat_merge_kernel(const Cand *__restrict__ partial, int P, int k,
-                                                         int32_t *__restrict__ ids, float *__restrict__ scores,
-                                                         const int *__restrict__ count, const Cand *__restrict__ cand,
-                                                         int cap) {
-    __shared__ Cand wl[4 * KP];
-    const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nwaves = blockDim.x >> 6;
-    int total = P * KP;
-    const Cand *in = partial + (size_t)q * P * KP;
-    if (count) {
-        const int n = count[q];                           // uniform for the workgroup
-        if (n <= cap) {
-            total = n;
-            in = cand + (size_t)q * cap;
-        }
-    }
-    TopList<KP> best;
-    best.init();
-    gather_best<KP>(in, total, tid, blockDim.x, best);
-    TopList<KP> wbest;
-    group_top<KP, KP, 1, 64>(best, wbest);
-    if (lane == 0) {
-#pragma unroll
-        for (int j = 0; j < KP; ++j) wl[wave * KP + j] = Cand{wbest.s[j], wbest.id[j]};
-    }
-    __syncthreads();
-    if (wave == 0) {                                  // one entry per lane, at most 4 waves x KP <= 64
-        TopList<1> one;
-        one.init();
-        if (lane < nwaves * KP) { one.s[0] = wl[lane].s; one.id[0] = wl[lane].id; }
-        TopList<KP> fin;
-        group_top<KP, 1, 1, 64>(one, fin);
-        if (lane == 0) {
-#pragma unroll
-            for (int j = 0; j < KP; ++j)
-                if (j < k) {
-                    const bool has = fin.id[j] != EMPTY_ID;
-                    ids[(size_t)q * k + j] = has ? fin.id[j] : -1;
-                    scores[(size_t)q * k + j] = has ? fin.s[j] : -INFINITY;
-                }
-        }
-    }
-}
-
-// One wavefront per query: the k-th best score among Ps sampled lists of KS entries (src[(q Ps + s) KS ..)),
-// -inf when the sample holds fewer than k rows.  The lists come from disjoint rows, so this is the
-// k-th best of a subset of the corpus: a lower bound of the final k-th best score.  With dst, the
-// sample's KS best are also kept, as slab pslot of the query's lists dst[(q pstride + pslot) KS ..)
-// (for a sample whose rows the main pass then skips).  With count, count[q] is set to 0.
-template <int KS, int KO>
-__global__ __launch_bounds__(64) void flat_sample_kth_kernel(const Cand *__restrict__ src, int Ps, int k,
-                                                             float *__restrict__ thr, Cand *__restrict__ dst,
-                                                             int pstride, int pslot, int *__restrict__ count) {
-    const int q = blockIdx.x, lane = threadIdx.x;
-    TopList<KO> best;
-    best.init();
-    gather_best<KO>(src + (size_t)q * Ps * KS, Ps * KS, lane, 64, best);
-    TopList<KO> top;
-    group_top<KO, KO, 1, 64>(best, top);
-    if (lane == 0) {
-        float t = -INFINITY;
-#pragma unroll
-        for (int j = 0; j < KO; ++j)
-            if (j == k - 1 && top.id[j] != EMPTY_ID) t = top.s[j];
-        thr[q] = t;
-        if (count) count[q] = 0;                      // the query's candidate array starts empty
-        if (dst) {
-#pragma unroll
-            for (int j = 0; j < KS; ++j) dst[((size_t)q * pstride + pslot) * KS + j] = Cand{top.s[j], top.id[j]};
-        }
+        group_select<LG>(key, K, reinterpret_cast<uint64_t *>(in), partial + ((size_t)(q0 + qi) * P + slab) * K, q0 + qi < B);
     }
 }
 

@@ -1,52 +1,38 @@
-// fp32 flat kernel, the per-query merge kernel, and the LDS sizing helpers.
-#include "flat_kernels.hpp"
+// The per-query merge kernels of the flat search, and the LDS sizing helpers of its streaming kernel.
+#include "flat_merge.hpp"
 #include "launch.hpp"
 
 namespace ann {
 
-size_t stream_lds_bytes(int nqg, int steps, int waves, int kp) {
-    size_t q = (size_t)nqg * steps * WAVE * 16;
-    size_t m = (size_t)waves * nqg * 16 * kp * sizeof(Cand);
+size_t stream_lds_bytes(int nqg, int lds_steps, int waves) {
+    const size_t q = (size_t)nqg * lds_steps * WAVE * 16;
+    const size_t m = (size_t)nqg * 16 * (4 * waves * LANE_KP + 4) * sizeof(Cand);
     return q > m ? q : m;
 }
 
-int stream_waves(int nqg, int steps, int kp) {
-    return kp != 16 && stream_lds_bytes(nqg, steps, STREAM_THREADS / WAVE, kp) > LDS_MAX / 2 ? 16 : 8;
+int stream_waves(int elem_bytes, int nqg, int lds_steps) {
+    return elem_bytes == 2 && nqg >= 2 && stream_lds_bytes(nqg, lds_steps, 8) > LDS_MAX / 2 ? 16 : 8;
 }
 
-size_t f32_lds_bytes(int d, int waves, int kp) {
-    size_t q = (size_t)8 * d * 4;
-    size_t m = (size_t)waves * 8 * kp * sizeof(Cand);
-    return q > m ? q : m;
-}
-
-namespace {
-template <int KP>
-hipError_t launch_f32(const float *X, int64_t N, int d, const float *Q, int B, Cand *partial, int P, After after,
-                      hipStream_t stream) {
-    static size_t big = 0;
-    const size_t lds = f32_lds_bytes(d, 4, KP);
-    if (hipError_t e = allow_big_lds(reinterpret_cast<const void *>(&flat_f32_kernel<KP>), lds, &big)) return e;
-    hipLaunchKernelGGL((flat_f32_kernel<KP>), dim3(P, (B + 7) / 8), dim3(256), lds, stream, X, N, d, Q, B, partial, after);
+hipError_t launch_flat_merge(const Cand *partial, int P, int B, int k, int32_t *ids, float *scores, hipStream_t stream) {
+    const int threads = P * LANE_KP <= 512 ? 64 : 256;            // one batch of loads per lane where possible
+    hipLaunchKernelGGL(flat_merge_kernel, dim3(B), dim3(threads), 0, stream, partial, P, k, ids, scores);
     return hipGetLastError();
 }
-}  // namespace
 
-hipError_t launch_flat_f32(int kp, const float *X, int64_t N, int d, const float *Q, int B, Cand *partial, int P,
-                           After after, hipStream_t stream) {
-    return kp == 4 ? launch_f32<4>(X, N, d, Q, B, partial, P, after, stream) : launch_f32<16>(X, N, d, Q, B, partial, P, after, stream);
-}
-
-hipError_t launch_flat_merge(int kp, const Cand *partial, int P, int B, int k, int32_t *ids, float *scores,
-                             const int *count, const Cand *cand, int cap, hipStream_t stream) {
-    const int threads = !count && P * kp <= 512 ? 64 : 256;       // one batch of loads per lane where possible
-    if (kp == 4)
-        hipLaunchKernelGGL((flat_merge_kernel<4>), dim3(B), dim3(threads), 0, stream, partial, P, k, ids, scores, count,
-                           cand, cap);
-    else
-        hipLaunchKernelGGL((flat_merge_kernel<16>), dim3(B), dim3(threads), 0, stream, partial, P, k, ids, scores, count,
-                           cand, cap);
-    return hipGetLastError();
+hipError_t launch_flat_merge_lists(int dtype, const Cand *partial, int P, int K, int slots, const void *X, int64_t N, int d,
+                                   const void *Q, int B, int k, int32_t *ids, float *scores, const int *count,
+                                   const Cand *cand, int cap, After after, hipStream_t stream) {
+    const StreamShape sh{X, Q, N, d, B};
+    const int threads = count || P > 64 ? 256 : 64;               // a list per lane where possible
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(B), dim3(threads), 0, stream, partial, P, K, k, ids, scores, count, cand, cap, sh,
+                           slots, after);
+        return hipGetLastError();
+    };
+    if (dtype == 0) return go(flat_merge_lists_kernel<F16>);
+    if (dtype == 1) return go(flat_merge_lists_kernel<BF16>);
+    return go(flat_merge_lists_kernel<F32>);
 }
 
 hipError_t launch_flat_sample_kth(const Cand *src, int Ps, int B, int k, float *thr, Cand *dst, int pstride, int pslot,

@@ -3,9 +3,9 @@
 
 namespace ann {
 
-hipError_t launch_flat_stream_bf16(int nqg, int kp, const void *X, int64_t N, int d, const void *Q, int B, int q0,
-                                  Cand *partial, int P, const StreamOpts &o, hipStream_t stream) {
-    return launch_stream_any<BF16>(nqg, kp, X, N, d, Q, B, q0, partial, P, o, stream);
+hipError_t launch_flat_stream_bf16(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
+                                  const int *need, int need_above, After after, hipStream_t stream) {
+    return launch_stream_any<BF16>(pl, X, N, d, Q, B, partial, need, need_above, after, stream);
 }
 
 }  // namespace ann

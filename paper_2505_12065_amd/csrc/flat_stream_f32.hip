@@ -1,0 +1,11 @@
+// flat_stream_kernel instantiations for fp32 corpora.
+#include "flat_stream_launch.hpp"
+
+namespace ann {
+
+hipError_t launch_flat_stream_f32(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
+                                  const int *need, int need_above, After after, hipStream_t stream) {
+    return launch_stream_any<F32>(pl, X, N, d, Q, B, partial, need, need_above, after, stream);
+}
+
+}  // namespace ann

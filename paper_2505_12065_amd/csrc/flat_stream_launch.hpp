@@ -7,54 +7,42 @@
 
 namespace ann {
 
-template <class T, int NQG, int KP, bool EMIT, int NWV>
-hipError_t launch_stream_waves(const void *X, int64_t N, int d, const void *Q, int B, int q0, Cand *partial, int P,
-                               const StreamOpts &o, hipStream_t stream) {
-    static size_t big[2] = {0, 0};
-    const int steps = (d + 31) / 32;
-    const size_t lds = stream_lds_bytes(NQG, steps, NWV, KP);
-    if ((d % 32) == 0) {
-        if (hipError_t e = allow_big_lds(reinterpret_cast<const void *>(&flat_stream_kernel<T, NQG, KP, true, EMIT, NWV>), lds, &big[0]))
-            return e;
-        hipLaunchKernelGGL((flat_stream_kernel<T, NQG, KP, true, EMIT, NWV>), dim3(P), dim3(NWV * WAVE), lds, stream, X, N, d,
-                           Q, B, q0, partial, o);
-    } else {
-        if (hipError_t e = allow_big_lds(reinterpret_cast<const void *>(&flat_stream_kernel<T, NQG, KP, false, EMIT, NWV>), lds, &big[1]))
-            return e;
-        hipLaunchKernelGGL((flat_stream_kernel<T, NQG, KP, false, EMIT, NWV>), dim3(P), dim3(NWV * WAVE), lds, stream, X, N, d,
-                           Q, B, q0, partial, o);
-    }
+template <class T, int NQG, bool FULL, int NWV>
+hipError_t launch_stream_one(const StreamPlan &pl, const StreamShape &sh, Cand *partial, const int *need, int need_above,
+                             After after, hipStream_t stream) {
+    static size_t big = 0;
+    const size_t lds = stream_lds_bytes(NQG, pl.lds_steps, NWV);
+    if (hipError_t e = allow_big_lds(reinterpret_cast<const void *>(&flat_stream_kernel<T, NQG, FULL, NWV>), lds, &big)) return e;
+    hipLaunchKernelGGL((flat_stream_kernel<T, NQG, FULL, NWV>), dim3(pl.P * pl.G), dim3(NWV * WAVE), lds, stream, sh, partial,
+                       pl.P, pl.G, pl.K, pl.lds_steps, need, need_above, after);
     return hipGetLastError();
 }
 
-template <class T, int NQG, int KP, bool EMIT>
-hipError_t launch_stream(const void *X, int64_t N, int d, const void *Q, int B, int q0, Cand *partial, int P,
-                         const StreamOpts &o, hipStream_t stream) {
-    if constexpr (KP != 16 && NQG >= 2) {            // one query group never fills half the LDS (d <= 4096)
-        if (stream_waves(NQG, (d + 31) / 32, KP) == 16)
-            return launch_stream_waves<T, NQG, KP, EMIT, 16>(X, N, d, Q, B, q0, partial, P, o, stream);
+template <class T, int NQG>
+hipError_t launch_stream_nqg(const StreamPlan &pl, const StreamShape &sh, Cand *partial, const int *need, int need_above,
+                             After after, hipStream_t stream) {
+    const bool full = (sh.d * T::bytes) % (64 * STREAM_BATCH) == 0;
+    if constexpr (T::bytes == 2 && NQG >= 2) {           // (one group of 16 queries never fills half the LDS)
+        if (pl.waves == 16)
+            return full ? launch_stream_one<T, NQG, true, 16>(pl, sh, partial, need, need_above, after, stream)
+                        : launch_stream_one<T, NQG, false, 16>(pl, sh, partial, need, need_above, after, stream);
     }
-    return launch_stream_waves<T, NQG, KP, EMIT, 8>(X, N, d, Q, B, q0, partial, P, o, stream);
+    return full && (NQG > 1 || pl.lds_steps * 64 >= sh.d * T::bytes)
+               ? launch_stream_one<T, NQG, true, 8>(pl, sh, partial, need, need_above, after, stream)
+               : launch_stream_one<T, NQG, false, 8>(pl, sh, partial, need, need_above, after, stream);
 }
 
-template <class T, int KP, bool EMIT>
-hipError_t launch_stream_nqg(int nqg, const void *X, int64_t N, int d, const void *Q, int B, int q0, Cand *partial,
-                             int P, const StreamOpts &o, hipStream_t stream) {
-    switch (nqg) {
-    case 1: return launch_stream<T, 1, KP, EMIT>(X, N, d, Q, B, q0, partial, P, o, stream);
-    case 2: return launch_stream<T, 2, KP, EMIT>(X, N, d, Q, B, q0, partial, P, o, stream);
-    case 3: return launch_stream<T, 3, KP, EMIT>(X, N, d, Q, B, q0, partial, P, o, stream);
-    default: return launch_stream<T, 4, KP, EMIT>(X, N, d, Q, B, q0, partial, P, o, stream);
-    }
-}
-
-// kp: 4 or 16 = list length; 0 = candidate-array mode (o.thr, o.count, o.cap)
 template <class T>
-hipError_t launch_stream_any(int nqg, int kp, const void *X, int64_t N, int d, const void *Q, int B, int q0,
-                             Cand *partial, int P, const StreamOpts &o, hipStream_t stream) {
-    if (kp == 0) return launch_stream_nqg<T, 4, true>(nqg, X, N, d, Q, B, q0, partial, P, o, stream);
-    return kp == 4 ? launch_stream_nqg<T, 4, false>(nqg, X, N, d, Q, B, q0, partial, P, o, stream)
-                   : launch_stream_nqg<T, 16, false>(nqg, X, N, d, Q, B, q0, partial, P, o, stream);
+hipError_t launch_stream_any(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
+                             const int *need, int need_above, After after, hipStream_t stream) {
+    const StreamShape sh{X, Q, N, d, B};
+    if (pl.nqg == 1) return launch_stream_nqg<T, 1>(pl, sh, partial, need, need_above, after, stream);
+    if (pl.nqg == 2) return launch_stream_nqg<T, 2>(pl, sh, partial, need, need_above, after, stream);
+    if constexpr (STREAM_NQG_MAX(T::bytes) > 2) {
+        if (pl.nqg == 3) return launch_stream_nqg<T, 3>(pl, sh, partial, need, need_above, after, stream);
+        return launch_stream_nqg<T, 4>(pl, sh, partial, need, need_above, after, stream);
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace ann

@@ -73,14 +73,6 @@ __device__ __forceinline__ int precedes01(float s, int id, float s2, int id2) {
 // trips through the LDS crossbar.  After the first two steps the four lanes of a quad hold the
 // same bits (a + b and b + a are the same number), so the mirror step adds the same two quad
 // sums in every lane: the result is bit for bit that of a butterfly over lanes ^1, ^2, ^4.
-template <int CTRL>
-__device__ __forceinline__ int dpp_move(int x) {
-    return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false);
-}
-constexpr int DPP_SWAP1 = 0xB1;                           // quad_perm [1,0,3,2]
-constexpr int DPP_SWAP2 = 0x4E;                           // quad_perm [2,3,0,1]
-constexpr int DPP_HALF_MIRROR = 0x141;                    // lane i of each 8 <- lane 7 - i
-constexpr int DPP_MIRROR = 0x140;                         // lane i of each 16 <- lane 15 - i
 __device__ __forceinline__ float group_sum(float x) {
     x += __int_as_float(dpp_move<DPP_SWAP1>(__float_as_int(x)));
     x += __int_as_float(dpp_move<DPP_SWAP2>(__float_as_int(x)));

@@ -10,11 +10,9 @@
 namespace ann {
 
 constexpr size_t LDS_MAX = 160 * 1024;   // LDS of one gfx950 compute unit
-constexpr int STREAM_THREADS = 512;
 // Wavefronts of a flat_stream_kernel workgroup: 8, or 16 when the queries' LDS leaves room for one
-// workgroup per compute unit only (the corpus loads in flight are what keeps HBM busy); lists
-// of 16 need too many registers for that.
-int stream_waves(int nqg, int steps, int kp);
+// workgroup per compute unit only (the corpus loads in flight are what keeps HBM busy).
+int stream_waves(int elem_bytes, int nqg, int lds_steps);
 
 // A kernel that needs more than 64 KB of dynamic LDS has to be told so; `granted` holds
 // the largest size already granted to that kernel.
@@ -25,27 +23,27 @@ inline hipError_t allow_big_lds(const void *kernel, size_t bytes, size_t *grante
     return e;
 }
 
-size_t stream_lds_bytes(int nqg, int steps, int waves, int kp);
-size_t f32_lds_bytes(int d, int waves, int kp);
+constexpr int STREAM_NQG_MAX(int elem_bytes) { return elem_bytes == 2 ? 4 : 2; }   // fp32: eight accumulators a group
+constexpr int STREAM_WG_PER_CU(int elem_bytes, int nqg, int waves) { return waves == 16 || (elem_bytes == 4 && nqg > 1) ? 1 : 2; }
+size_t stream_lds_bytes(int nqg, int lds_steps, int waves);
 
-// Optional behaviour of a flat_stream_kernel launch.
-struct StreamOpts {
-    const int *need = nullptr;   // [B]: a group of queries is skipped unless need[q] > need_above for
-    int need_above = 0;          //      one of them (repair pass behind the candidate arrays)
-    int passes = 1;              // consecutive groups of nqg * 16 queries served by the launch, from q0 on
-    int row_stride = 1;          // S > 1: only rows 0, S, 2S, ... are scored (sampling pass)
-    After after;                 // continuation: per-query boundary pairs, or null pointers
-    const float *thr = nullptr;  // candidate-array mode: [B] lower bounds of the final k-th best score,
-    int *count = nullptr;        //   [B] entry counters (zero on entry; a count past cap means overflow),
-    int cap = 0;                 //   entries per query in the candidate array that `partial` then is
+// Geometry and options of a flat_stream_kernel launch.
+struct StreamPlan {
+    int nqg = 1;                 // groups of 16 queries a workgroup serves, 1 .. STREAM_NQG_MAX
+    int G = 1;                   // workgroups side by side over the queries, ceil(B / (16 nqg))
+    int P = 1;                   // slabs of the corpus
+    int waves = 8;               // wavefronts per workgroup
+    int lds_steps = 1;           // 64-byte steps of a query held in LDS
+    int K = 4;                   // entries of a slab's list: k rounded up to a multiple of 4
+    int slots() const { return P * waves; }
 };
-// nqg in 1..4 query groups of 16 starting at query q0.  kp 4 or 16: lists, partial[B, P, kp].
-// kp 0: candidate-array mode, every (score, row) with score >= o.thr[q] is appended to
-// partial[q o.cap ..) through o.count[q].
-hipError_t launch_flat_stream_f16(int nqg, int kp, const void *X, int64_t N, int d, const void *Q, int B, int q0,
-                                  Cand *partial, int P, const StreamOpts &o, hipStream_t stream);
-hipError_t launch_flat_stream_bf16(int nqg, int kp, const void *X, int64_t N, int d, const void *Q, int B, int q0,
-                                   Cand *partial, int P, const StreamOpts &o, hipStream_t stream);
+// partial[B, P, K]: every slab's best K per query.  need: see the kernel.
+hipError_t launch_flat_stream_f16(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
+                                  const int *need, int need_above, After after, hipStream_t stream);
+hipError_t launch_flat_stream_bf16(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
+                                   const int *need, int need_above, After after, hipStream_t stream);
+hipError_t launch_flat_stream_f32(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
+                                  const int *need, int need_above, After after, hipStream_t stream);
 // Large batches on the matrix cores (16-bit corpora, d % 32 == 0, lists of 4).
 // Query tile is wide_query_tile(B) queries; gridDim = P slabs x NTG query-tile groups;
 // rows [256 tile_begin, N) are scanned; results go to partial[(q pstride + pslot0 + slab) 4 ..).
@@ -61,12 +59,13 @@ hipError_t launch_flat_wide(int dtype, int mode, const void *X, int64_t N, int d
 // with dst, the 4 best of the sample also become slab pslot of dst[B, pstride, 4]; with count, count[q] = 0
 hipError_t launch_flat_sample_kth(const Cand *src, int Ps, int B, int k, float *thr, Cand *dst, int pstride, int pslot,
                                   int *count, hipStream_t stream);
-hipError_t launch_flat_f32(int kp, const float *X, int64_t N, int d, const float *Q, int B, Cand *partial, int P,
-                           After after, hipStream_t stream);
-// count == null: merge the P lists of every query.  count given: query q's input is its candidate
-// array cand[q cap ..) of count[q] entries, or, when that overflowed, its P lists (repair pass).
-hipError_t launch_flat_merge(int kp, const Cand *partial, int P, int B, int k, int32_t *ids, float *scores,
-                             const int *count, const Cand *cand, int cap, hipStream_t stream);
+// k <= 4: merge the P lists of 4 of every query.
+hipError_t launch_flat_merge(const Cand *partial, int P, int B, int k, int32_t *ids, float *scores, hipStream_t stream);
+// k > 4: merge the P lists of K of every query, made by flat_stream_kernel with `slots` = P waves; with count, query q's
+// input is its candidate array cand[q cap ..) of count[q] entries, or, when that overflowed, its lists (repair pass).
+hipError_t launch_flat_merge_lists(int dtype, const Cand *partial, int P, int K, int slots, const void *X, int64_t N, int d,
+                                   const void *Q, int B, int k, int32_t *ids, float *scores, const int *count,
+                                   const Cand *cand, int cap, After after, hipStream_t stream);
 
 constexpr int GRAPH_DENSE_MIN_B = 1280;   // batches beyond this run three graph-search workgroups per compute unit
 constexpr int GRAPH_EF_DOUBLE = 2048;    // candidate lists up to this length are double-buffered in LDS

@@ -149,6 +149,42 @@ def test_flat_continuation_pages(dtype, N, d, B, k):
         assert (got[:, 40:] == -1).all() and (np.sort(got[:, :40], 1) == np.arange(40)).all()
 
 
+@pytest.mark.parametrize("dtype,B", [(torch.float16, 1), (torch.bfloat16, 37), (torch.float32, 20)])
+def test_flat_many_of_the_best_rows_in_one_lane(dtype, B):
+    """k > 4: a lane of the streaming kernel keeps the 4 best of its rows, so rows a whole number of grid strides
+    apart, of which more than 4 belong to the answer, are found by the merge's second look.  (The stride
+    follows from the number of slabs, which the workspace size tells.)"""
+    N, d, k = 450_000, 64, 16
+    slabs = ann.ann_flat_workspace_bytes(N, d, dtype, B, k) // (B * k * 8)
+    stride = 16 * 8 * slabs
+    rows = torch.arange(16 * 7 + 6, N, stride)
+    assert rows.numel() >= 6
+    c = synth.make_corpus(N, d, 8, seed=3, dtype=dtype, zipf_a=None, sigma=0.3)
+    x = c.x.clone()
+    q = synth.make_queries(c, B)
+    scale = 1.0 + torch.arange(rows.numel(), dtype=torch.float32)[:, None] / 64
+    x[rows] = (q[0].float() * scale).to(dtype)
+    ids, sc, (o_ids, o_sc, o_sc64) = flat_both(x, q, k)
+    assert ids[0, :rows.numel()].tolist() == rows.flip(0).tolist()
+    strict, tolerant, n = compare_topk(ids, sc, o_ids, o_sc64, to_np(x), to_np(q), dtype=np_dtype_name(x))
+    assert strict >= n - 2, (strict, n)
+
+
+@pytest.mark.parametrize("N,d,B,k,dtype", [(17, 40, 3, 16, torch.float16), (9000, 64, 2, 5, torch.bfloat16),
+                                            (9000, 64, 70, 16, torch.float16), (300_000, 32, 1, 16, torch.float16),
+                                            (300_000, 36, 33, 9, torch.float32), (200_000, 32, 150, 8, torch.bfloat16)])
+def test_flat_all_rows_tied(N, d, B, k, dtype):
+    """Every row scores the same: each level of the selection sees nothing but ties, and the lowest ids win."""
+    gen = torch.Generator().manual_seed(N)
+    row = torch.randn(1, d, generator=gen).to(dtype)
+    x = row.repeat(N, 1).to(DEV)
+    q = torch.randn(B, d, generator=gen).to(dtype).to(DEV)
+    ids, sc = ann.ann_flat_search_typed(x, q, k)
+    torch.cuda.synchronize()
+    assert (ids.cpu() == torch.arange(k, dtype=torch.int32)[None, :]).all()
+    assert (sc == sc[:, :1]).all()
+
+
 def test_flat_ties_go_to_lower_id():
     c = synth.make_corpus(4000, 128, 4, seed=5, dtype=torch.float16, zipf_a=None, sigma=0.3)
     x = c.x.clone()
