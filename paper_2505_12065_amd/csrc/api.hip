@@ -109,9 +109,6 @@ int workspace_for(DeviceState *st, void **own, size_t *own_bytes, size_t bytes, 
     return ANN_OK;
 }
 
-// words of one query's visited bitset: one bit per node, rounded to 16-byte units
-int64_t visited_words(int64_t N) { return (N + 511) / 512 * 16; }
-
 // ---- optional event timing of the main kernels -----------------------------------------------
 struct TimedLaunch { hipEvent_t a, b; int kernel; };
 bool g_timing = false;
@@ -583,6 +580,24 @@ static int check_graph(const void *corpus, int64_t N, int32_t d, int32_t dtype, 
     return ANN_OK;
 }
 
+// Graphs of at most 32 slots per node.  The visited set needs workspace only where it does not fit LDS.
+static int graph_step_run(DeviceState *st, const void *corpus, int64_t N, int32_t d, int32_t dtype, const int32_t *graph, int32_t R,
+                          int32_t entry, const void *queries, int32_t B, int32_t k, int32_t ef, int32_t *ids, float *scores,
+                          bool counters, NonStall ns, hipStream_t s) {
+    const StepLds L = graph_step_plan(st->cus, N, d, elem_bytes(dtype), B, ef, counters);
+    if (L.total > LDS_MAX) return fail(ANN_ERR_INVALID, "d = %d, ef = %d need %u bytes of LDS", d, ef, L.total);
+    if (L.vis_mode == STEP_VIS_GLOBAL) {
+        ns.words = visited_words(N);
+        void *vis = nullptr;
+        if (int rc = workspace_for(st, &st->vis, &st->vis_bytes, (size_t)B * (size_t)ns.words * 4, &vis)) return rc;
+        ns.visited = static_cast<uint32_t *>(vis);
+        if (int rc = check_launch("zero_words_kernel", launch_zero_words(ns.visited, (size_t)B * (size_t)ns.words, s))) return rc;
+    }
+    TimedScope timed(ANN_KERNEL_GRAPH, s);
+    return check_launch("graph_step_kernel", launch_graph_step(dtype, corpus, N, d, graph, R, entry, queries, B, k, ef, ids, scores,
+                                                               L, counters, ns, s));
+}
+
 int64_t ann_graph_nonstall_workspace_bytes(int64_t N, int32_t B) {
     if (N < 1 || N > INT32_MAX || B < 1) return ANN_ERR_INVALID;
     return (int64_t)B * visited_words(N) * 4;
@@ -617,10 +632,12 @@ int ann_graph_search_nonstall_typed(const void *corpus, int64_t N, int32_t d, in
     ns.words = visited_words(N);
     ns.stats = stats;
     ns.ema = ema;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    if (graph_step_pays(st->cus, d * elem_bytes(dtype), R, B, ef, true, tau))
+        return graph_step_run(st, corpus, N, d, dtype, graph, R, entry, queries, B, k, ef, ids, scores, true, ns, s);
     void *vis = nullptr;
     if (int rc = workspace_for(st, &st->vis, &st->vis_bytes, (size_t)B * (size_t)ns.words * 4, &vis)) return rc;
     ns.visited = static_cast<uint32_t *>(vis);
-    hipStream_t s = static_cast<hipStream_t>(stream);
     if (int rc = check_launch("zero_words_kernel", launch_zero_words(ns.visited, (size_t)B * (size_t)ns.words, s)))
         return rc;
     TimedScope timed(ANN_KERNEL_GRAPH, s);
@@ -636,13 +653,20 @@ static int graph_search_any(const void *corpus, int64_t N, int32_t d, int32_t dt
                             int32_t entry, const int32_t *entries, int32_t n_entries, const void *queries, int32_t B, int32_t k,
                             int32_t ef, int32_t *ids, float *scores, const GraphLds &L, hipStream_t s) {
     std::lock_guard<std::mutex> lock(g_mu);
+    DeviceState *st = nullptr;
+    if (int rc = device_state(&st)) return rc;
+    if (graph_step_pays(st->cus, d * elem_bytes(dtype), R, B, ef, false, INFINITY)) {
+        NonStall ns{};
+        ns.entries = entries;
+        ns.n_entries = n_entries;
+        ns.tau = INFINITY;
+        return graph_step_run(st, corpus, N, d, dtype, graph, R, entry, queries, B, k, ef, ids, scores, false, ns, s);
+    }
     if (ef <= GRAPH_EF_DOUBLE && !L.two_level) {
         TimedScope timed(ANN_KERNEL_GRAPH, s);
         return check_launch("graph_search_kernel", launch_graph_search(dtype, corpus, N, d, graph, R, entry, entries, n_entries,
                                                                        queries, B, k, ef, ids, scores, L, s));
     }
-    DeviceState *st = nullptr;
-    if (int rc = device_state(&st)) return rc;
     NonStall ns{};
     ns.entries = entries;
     ns.n_entries = n_entries;

@@ -154,6 +154,109 @@ __device__ __forceinline__ int group_lower_bound_fast(const float *s, const uint
     return 64 * blk + group_sum(gt);
 }
 
+// <q, x_v> by the 8 lanes of a row group; every lane of the group gets the sum.  The lane's share of the first 128
+// chunks of the query (chunks sub, sub + 8, ...) stays in registers for the whole search (QREG): up to 1024 16-bit
+// dimensions are scored without reading the query from LDS.  All of a lane's 16-byte loads of the row are issued
+// before the first one is used, so a whole expansion costs one memory latency, not one per batch of loads.  Loads
+// and products come in runs of four with one scalar test each (is any of the run's 32 chunks inside the row?); a lane
+// whose chunk lies past the end of the row loads the row's last chunk instead and leaves the product out of the sum
+// (`lim` is re-derived per call on purpose: sixteen loop-invariant lane masks would not fit the scalar registers).
+template <class T, bool QREG>
+struct RowScorer {
+    static constexpr int NX = QREG ? 16 : 8;              // 16-byte loads of a row a lane keeps in flight
+    static constexpr int BLK = NX * LANES_PER_ROW;        // chunks of a row covered by those loads
+    static constexpr int TAIL = 8 * LANES_PER_ROW;        // chunks per round of the loop over the rest of a row
+    typedef u4 Loads[NX];
+    const void *X;
+    const u4 *qs;                                         // the query in LDS
+    int nch, sub;
+    u4 qr[QREG ? 16 : 1];
+
+    __device__ __forceinline__ RowScorer(const void *X_, const u4 *qs_, int nch_, int sub_) : X(X_), qs(qs_), nch(nch_), sub(sub_) {
+        if constexpr (QREG) {
+#pragma unroll
+            for (int u = 0; u < 16; ++u) qr[u] = qs[min(sub + u * LANES_PER_ROW, nch - 1)];
+        }
+    }
+    __device__ __forceinline__ u4 q_chunk(int u) const {
+        if constexpr (QREG) return qr[u];
+        else return qs[min(sub + u * LANES_PER_ROW, nch - 1)];
+    }
+    // (in two halves, so that other work can be put between the loads and their use)
+    __device__ __forceinline__ void issue(int v, Loads &x) const {
+        const char *rp = static_cast<const char *>(X) + (size_t)v * nch * 16;
+        int lim = nch - sub;                              // chunk sub + 8u is in the row iff 8u < lim
+        asm volatile("" : "+v"(lim));
+        const char *rl = rp + sub * 16;
+#pragma unroll
+        for (int g = 0; g < NX / 4; ++g)
+            if ((g + 1) * 4 * LANES_PER_ROW <= nch) {      // the whole run is inside: constant offsets
+#pragma unroll
+                for (int u = 4 * g; u < 4 * g + 4; ++u) x[u] = load_chunk(rl + u * LANES_PER_ROW * 16);
+            } else if (g * 4 * LANES_PER_ROW < nch) {
+#pragma unroll
+                for (int u = 4 * g; u < 4 * g + 4; ++u)
+                    x[u] = load_chunk(rp + (size_t)(sub + min(u * LANES_PER_ROW, lim - 1)) * 16);
+            }
+    }
+    // acc + the products of row v's chunks beyond the first BLK
+    __device__ __forceinline__ f4 rest(int v, Loads &x, f4 acc) const {
+        const char *rp = static_cast<const char *>(X) + (size_t)v * nch * 16;
+        int lim = nch - sub;
+        asm volatile("" : "+v"(lim));
+        for (int cb = BLK; cb < nch; cb += TAIL) {        // longer rows: the query comes from LDS
+            u4 qv[8];
+            lim -= cb == BLK ? BLK : TAIL;
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+                if (cb + g * 4 * LANES_PER_ROW < nch) {
+#pragma unroll
+                    for (int u = 4 * g; u < 4 * g + 4; ++u) {
+                        const int c = cb + sub + min(u * LANES_PER_ROW, lim - 1);
+                        x[u] = load_chunk(rp + (size_t)c * 16);
+                        qv[u] = qs[c];
+                    }
+                }
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+                if (cb + g * 4 * LANES_PER_ROW < nch) {
+#pragma unroll
+                    for (int u = 4 * g; u < 4 * g + 4; ++u) {
+                        f4 t = acc;
+                        dot_chunk4<T>(x[u], qv[u], t);
+                        acc = u * LANES_PER_ROW < lim ? t : acc;
+                    }
+                }
+        }
+        return acc;
+    }
+    __device__ __forceinline__ float dots(int v, Loads &x) const {
+        f4 acc = {0.f, 0.f, 0.f, 0.f};                    // four independent chains, added at the end
+        int lim = nch - sub;
+        asm volatile("" : "+v"(lim));
+#pragma unroll
+        for (int g = 0; g < NX / 4; ++g)
+            if ((g + 1) * 4 * LANES_PER_ROW <= nch) {      // the whole run is inside the row
+#pragma unroll
+                for (int u = 4 * g; u < 4 * g + 4; ++u) dot_chunk4<T>(x[u], q_chunk(u), acc);
+            } else if (g * 4 * LANES_PER_ROW < nch) {
+#pragma unroll
+                for (int u = 4 * g; u < 4 * g + 4; ++u) {
+                    f4 t = acc;
+                    dot_chunk4<T>(x[u], q_chunk(u), t);
+                    acc = u * LANES_PER_ROW < lim ? t : acc;
+                }
+            }
+        if (BLK < nch) acc = rest(v, x, acc);
+        return group_sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
+    }
+    __device__ __forceinline__ float score(int v) const {
+        Loads x;
+        issue(v, x);
+        return dots(v, x);
+    }
+};
+
 // RPT: 32 for graphs with R <= 32 slots per node (one scoring pass per expansion, loops over the
 // scored neighbours fully unrolled: the software-pipelined loop), 0 for wider graphs (the number
 // of slots, rounded up to 32, comes from the layout at run time: the plain loop).
@@ -1227,22 +1330,6 @@ __global__ __launch_bounds__(GRAPH_THREADS, QREG ? 2 : 3) void graph_search_kern
         }
         if (ns.ema) ns.ema[b] = ema;
     }
-}
-
-// out[i] <- table[idx[i]], or -1 where idx[i] is not in [0, M)
-__global__ __launch_bounds__(256) void gather_ids_kernel(const int32_t *__restrict__ table, int64_t M,
-                                                         const int32_t *__restrict__ idx, int64_t n,
-                                                         int32_t *__restrict__ out) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t j = idx[i];
-        out[i] = (j >= 0 && j < M) ? table[j] : -1;
-    }
-}
-
-// words[0 .. n) <- 0, 16 bytes per store (n a multiple of 4)
-__global__ __launch_bounds__(256) void zero_words_kernel(u4 *__restrict__ p, size_t n16) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x)
-        p[i] = zero_chunk();
 }
 
 }  // namespace ann

@@ -102,6 +102,32 @@ struct NonStall {
     float *ema;               // [B] final moving average, may be null
 };
 GraphLds graph_lds_layout(int d, int elem_bytes, int R, int ef);
+
+// words of one query's visited bitset: one bit per node, rounded to 64-byte units
+inline int64_t visited_words(int64_t N) { return (N + 511) / 512 * 16; }
+
+// graph_step_kernel (graphs of at most 32 slots per node): how it runs a call, and its LDS
+constexpr int GRAPH_STEP_MAX_R = 32;
+constexpr int STEP_VIS_LDS = 0, STEP_VIS_CACHE = 1, STEP_VIS_GLOBAL = 2;   // where the visited set is
+struct StepLds {
+    // fixed byte offsets: scores, ids, positions, numbers of a step's neighbours (64 each), control words, then the scratch
+    // of every wave
+    static constexpr uint32_t CS = 0, CI = 256, CP = 512, EV = 768, EW = 1024, FM = 1280, CTL = 1312, MK = 1328,
+                              WAVE0 = 1456, WAVE_BYTES = 576;
+    // byte offsets: list scores and ids (two buffers of ls_bytes each), and for long lists the large part and its bits
+    uint32_t ls, li, ls_bytes, um, ms, mi, vis, q, total;
+    int vis_words, cache_shift, vis_mode;
+    int rows_per_group;                                   // neighbours a row group scores in a step: 1 or 2
+    bool dense;                                           // three workgroups per compute unit, query read from LDS
+    bool long_list;
+};
+// whether a call runs in steps of several expansions (graph_step_kernel) or one by one (graph_search_kernel)
+bool graph_step_pays(int cus, int row_bytes, int R, int B, int ef, bool counters, float tau);
+// counters: the call needs an exact visited set (maturity exit)
+StepLds graph_step_plan(int cus, int64_t N, int d, int elem_bytes, int B, int ef, bool counters);
+hipError_t launch_graph_step(int dtype, const void *X, int64_t N, int d, const int32_t *graph, int R, int entry, const void *Q,
+                             int B, int k, int ef, int32_t *ids, float *scores, const StepLds &L, bool counters,
+                             const NonStall &ns, hipStream_t stream);
 // dtype: ANN_F16 / ANN_BF16 / ANN_F32 codes 0 / 1 / 2
 // entries: null, or device [B, n_entries] per-query entry nodes used instead of `entry`
 hipError_t launch_graph_search(int dtype, const void *X, int64_t N, int d, const int32_t *graph, int R, int entry,

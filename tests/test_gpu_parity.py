@@ -10,7 +10,7 @@ import torch
 import oracle
 import paper_2505_12065_amd as ann
 from paper_2505_12065_amd import synth
-from parity import TOL, compare_topk, explain_divergence, np_dtype_name, recall, to_np
+from parity import TOL, compare_nonstall, compare_topk, explain_divergence, np_dtype_name, recall, to_np
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -530,6 +530,42 @@ def test_graph_batch_larger_than_one_resident_round(N, d, B, dtype):
         torch.cuda.synchronize()
         assert torch.equal(few, ids[:64])
         assert float((few_sc - sc[:64]).abs().max()) < 1e-5
+
+
+@pytest.mark.parametrize("dtype,N,d,R,B,ef,tau", [
+    (torch.float16, 5000, 64, 32, 4, 320, None), (torch.bfloat16, 5000, 520, 31, 1, 512, None),     # one list, few queries
+    (torch.float32, 3000, 36, 1, 513, 192, None), (torch.float16, 3000, 136, 32, 600, 257, None),   # one list, many
+    (torch.float16, 700_001, 8, 8, 513, 192, None),                                                 # ... with the id cache
+    (torch.float32, 4000, 1032, 32, 16, 513, None), (torch.float16, 600, 64, 32, 300, 700, None),   # two-level list
+    (torch.float16, 1_400_000, 8, 32, 2, 700, None),                                                # ... bits in memory
+    (torch.float16, 5000, 64, 16, 22, 96, 0.7), (torch.float16, 3000, 136, 32, 8, 600, 0.8),        # maturity exit
+    (torch.bfloat16, 700_001, 8, 16, 300, 96, 0.7)])                                                # ... bits in memory
+def test_graph_steps_of_several_expansions(dtype, N, d, R, B, ef, tau):
+    """Calls at the edges of the ranges that expand several nodes per step, for every place of the visited set:
+    ids, and with the maturity exit its decisions and counters, against the oracle."""
+    say(f"graph in steps: {dtype} N={N} d={d} R={R} B={B} ef={ef} tau={tau}")
+    gen = torch.Generator().manual_seed(N + ef)
+    if N < 10_000:
+        c = synth.make_corpus(N, d, 8, seed=ef, dtype=dtype, zipf_a=None, sigma=0.4)
+        x, q = c.x, synth.make_queries(c, B)
+        g = synth.ring_union(synth.knn_graph(x, max(1, R - 2)))[:, :R].contiguous()
+        g[:, 0] = (torch.arange(N, dtype=torch.int32) + 1) % N                        # connected, also with one slot
+    else:
+        x = torch.nn.functional.normalize(torch.randn(N, d, generator=gen), dim=1).to(dtype)
+        q = torch.nn.functional.normalize(torch.randn(B, d, generator=gen), dim=1).to(dtype)
+        g = torch.randint(-1, N + 1, (N, R), generator=gen, dtype=torch.int32)
+    xn, qn, gn, name = to_np(x), to_np(q), g.numpy(), np_dtype_name(x)
+    if tau is None:
+        ids, sc = ann.ann_graph_search_typed(x.to(DEV), g.to(DEV), 3, q.to(DEV), 3, ef)
+        torch.cuda.synchronize()
+        o_ids, _, o_sc64, _, _ = oracle.graph_search(xn, gn, 3, qn, 3, ef, dtype=name)
+        strict, tolerant, n = compare_topk(ids.cpu().numpy(), sc.cpu().numpy(), o_ids, o_sc64, xn, qn, dtype=name)
+        assert strict >= n - max(2, n // 100), (strict, n)
+    else:
+        gpu = ann.ann_graph_search_nonstall_typed(x.to(DEV), g.to(DEV), 3, q.to(DEV), 3, ef, tau=tau, window=60)
+        torch.cuda.synchronize()
+        o = oracle.graph_search_nonstall(xn, gn, 3, qn, 3, ef, tau=tau, window=60, dtype=name)
+        compare_nonstall([t.cpu().numpy() for t in gpu], o, xn, gn, qn, name, 3, 3, ef, tau, 60)
 
 
 def test_graph_padding_when_few_nodes_are_reachable():
