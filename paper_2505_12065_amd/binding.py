@@ -88,20 +88,38 @@ def _check(rc: int) -> None:
         raise AnnError(rc, lib().ann_last_error().decode())
 
 
-def _stream(stream) -> int:
+# The stream's handle without a Stream object around it (2.5 us), where this torch has the call for it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or \
+    (lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
+def _stream(stream, index: int) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(index)
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _call(device: torch.device, stream, entry_point, *args) -> None:
+    """entry_point(*args, stream) with `device` current.  (A torch.cuda.device block costs 1.2 us even where it
+    changes nothing, and small searches are bound by what runs here, so it is entered only where it does.)"""
+    index = device.index
+    if torch.cuda.current_device() == index:
+        rc = entry_point(*args, _stream(stream, index))
+    else:
+        with torch.cuda.device(device):
+            rc = entry_point(*args, _stream(stream, index))
+    if rc != ANN_OK:
+        _check(rc)
 
 
 def _outputs(B: int, k: int, device, ids, scores):
     if ids is None:
         ids = torch.empty(B, k, dtype=torch.int32, device=device)
+    elif ids.shape != (B, k) or ids.dtype != torch.int32 or not ids.is_contiguous() or not ids.is_cuda:
+        raise ValueError("ids must be a contiguous int32 [B, k] device tensor")
     if scores is None:
         scores = torch.empty(B, k, dtype=torch.float32, device=device)
-    if ids.shape != (B, k) or ids.dtype != torch.int32 or not ids.is_contiguous() or not ids.is_cuda:
-        raise ValueError("ids must be a contiguous int32 [B, k] device tensor")
-    if scores.shape != (B, k) or scores.dtype != torch.float32 or not scores.is_contiguous() or not scores.is_cuda:
+    elif scores.shape != (B, k) or scores.dtype != torch.float32 or not scores.is_contiguous() or not scores.is_cuda:
         raise ValueError("scores must be a contiguous float32 [B, k] device tensor")
     return ids, scores
 
@@ -130,18 +148,16 @@ def ann_flat_search_typed(corpus: torch.Tensor, queries: torch.Tensor, k: int, *
         raise ValueError("queries must have the corpus' element type and dimension")
     (N, d), B = corpus.shape, queries.shape[0]
     ids, scores = _outputs(B, k, corpus.device, ids, scores)
-    with torch.cuda.device(corpus.device):
-        if after is None:
-            _check(lib().ann_flat_search_typed(corpus.data_ptr(), N, d, _DTYPES[corpus.dtype], queries.data_ptr(), B, k,
-                                               ids.data_ptr(), scores.data_ptr(), _stream(stream)))
-        else:
-            a_s, a_i = after
-            if a_s.dtype != torch.float32 or a_i.dtype != torch.int32 or tuple(a_s.shape) != (B,) or tuple(a_i.shape) != (B,) \
-                    or not (a_s.is_cuda and a_i.is_cuda and a_s.is_contiguous() and a_i.is_contiguous()):
-                raise ValueError("after must be (float32 [B], int32 [B]) contiguous device tensors")
-            _check(lib().ann_flat_search_after_typed(corpus.data_ptr(), N, d, _DTYPES[corpus.dtype], queries.data_ptr(),
-                                                     B, k, a_s.data_ptr(), a_i.data_ptr(), ids.data_ptr(),
-                                                     scores.data_ptr(), _stream(stream)))
+    if after is None:
+        _call(corpus.device, stream, lib().ann_flat_search_typed, corpus.data_ptr(), N, d, _DTYPES[corpus.dtype],
+              queries.data_ptr(), B, k, ids.data_ptr(), scores.data_ptr())
+    else:
+        a_s, a_i = after
+        if a_s.dtype != torch.float32 or a_i.dtype != torch.int32 or tuple(a_s.shape) != (B,) or tuple(a_i.shape) != (B,) \
+                or not (a_s.is_cuda and a_i.is_cuda and a_s.is_contiguous() and a_i.is_contiguous()):
+            raise ValueError("after must be (float32 [B], int32 [B]) contiguous device tensors")
+        _call(corpus.device, stream, lib().ann_flat_search_after_typed, corpus.data_ptr(), N, d, _DTYPES[corpus.dtype],
+              queries.data_ptr(), B, k, a_s.data_ptr(), a_i.data_ptr(), ids.data_ptr(), scores.data_ptr())
     return ids, scores
 
 
@@ -157,9 +173,8 @@ def ann_flat_search_static(corpus: torch.Tensor, queries: torch.Tensor, k: int, 
         raise ValueError("queries must have the corpus' element type and dimension")
     (N, d), B = corpus.shape, queries.shape[0]
     ids, scores = _outputs(B, k, corpus.device, ids, scores)
-    with torch.cuda.device(corpus.device):
-        _check(lib().ann_flat_search_static(corpus.data_ptr(), N, d, _DTYPES[corpus.dtype], queries.data_ptr(), B, k,
-                                            ids.data_ptr(), scores.data_ptr(), _stream(stream)))
+    _call(corpus.device, stream, lib().ann_flat_search_static, corpus.data_ptr(), N, d, _DTYPES[corpus.dtype],
+          queries.data_ptr(), B, k, ids.data_ptr(), scores.data_ptr())
     return ids, scores
 
 
@@ -172,9 +187,8 @@ def ann_flat_search(corpus: torch.Tensor, queries: torch.Tensor, k: int, *, ids=
         raise ValueError("queries must have the corpus' element type and dimension")
     (N, d), B = corpus.shape, queries.shape[0]
     ids, scores = _outputs(B, k, corpus.device, ids, scores)
-    with torch.cuda.device(corpus.device):
-        _check(lib().ann_flat_search(corpus.data_ptr(), N, d, queries.data_ptr(), B, k, ids.data_ptr(),
-                                     scores.data_ptr(), _stream(stream)))
+    _call(corpus.device, stream, lib().ann_flat_search, corpus.data_ptr(), N, d, queries.data_ptr(), B, k, ids.data_ptr(),
+          scores.data_ptr())
     return ids, scores
 
 
@@ -194,10 +208,8 @@ def ann_graph_search_typed(corpus: torch.Tensor, graph: torch.Tensor, entry: int
     (N, d), B = corpus.shape, queries.shape[0]
     _graph(graph, N)
     ids, scores = _outputs(B, k, corpus.device, ids, scores)
-    with torch.cuda.device(corpus.device):
-        _check(lib().ann_graph_search_typed(corpus.data_ptr(), N, d, _DTYPES[corpus.dtype], graph.data_ptr(),
-                                            graph.shape[1], int(entry), queries.data_ptr(), B, k, ef,
-                                            ids.data_ptr(), scores.data_ptr(), _stream(stream)))
+    _call(corpus.device, stream, lib().ann_graph_search_typed, corpus.data_ptr(), N, d, _DTYPES[corpus.dtype],
+          graph.data_ptr(), graph.shape[1], int(entry), queries.data_ptr(), B, k, ef, ids.data_ptr(), scores.data_ptr())
     return ids, scores
 
 
@@ -231,12 +243,9 @@ def ann_graph_search_nonstall_typed(corpus: torch.Tensor, graph: torch.Tensor, e
                 not (engine_ready.is_cuda or engine_ready.is_pinned()):
             raise ValueError("engine_ready must be one int32 on the device or in pinned host memory")
         ready_ptr = engine_ready.data_ptr()
-    with torch.cuda.device(corpus.device):
-        _check(lib().ann_graph_search_nonstall_typed(corpus.data_ptr(), N, d, _DTYPES[corpus.dtype], graph.data_ptr(),
-                                                     graph.shape[1], int(entry), queries.data_ptr(), B, k, ef,
-                                                     entries_ptr, n_entries, float(tau), int(window), ready_ptr, ids.data_ptr(),
-                                                     scores.data_ptr(), stats.data_ptr(), ema.data_ptr(),
-                                                     _stream(stream)))
+    _call(corpus.device, stream, lib().ann_graph_search_nonstall_typed, corpus.data_ptr(), N, d, _DTYPES[corpus.dtype],
+          graph.data_ptr(), graph.shape[1], int(entry), queries.data_ptr(), B, k, ef, entries_ptr, n_entries, float(tau),
+          int(window), ready_ptr, ids.data_ptr(), scores.data_ptr(), stats.data_ptr(), ema.data_ptr())
     return ids, scores, stats, ema
 
 
@@ -260,11 +269,9 @@ def ann_graph_search_multi_typed(corpus: torch.Tensor, graph: torch.Tensor, entr
     if entries.dim() != 2:
         raise ValueError("entries must be [B, E]")
     ids, scores = _outputs(B, k, corpus.device, ids, scores)
-    with torch.cuda.device(corpus.device):
-        _check(lib().ann_graph_search_multi_typed(corpus.data_ptr(), N, d, _DTYPES[corpus.dtype], graph.data_ptr(),
-                                                  graph.shape[1], entries.data_ptr(), entries.shape[1],
-                                                  queries.data_ptr(), B, k, ef, ids.data_ptr(), scores.data_ptr(),
-                                                  _stream(stream)))
+    _call(corpus.device, stream, lib().ann_graph_search_multi_typed, corpus.data_ptr(), N, d, _DTYPES[corpus.dtype],
+          graph.data_ptr(), graph.shape[1], entries.data_ptr(), entries.shape[1], queries.data_ptr(), B, k, ef,
+          ids.data_ptr(), scores.data_ptr())
     return ids, scores
 
 
@@ -280,10 +287,9 @@ def ann_graph_search_entries_typed(corpus: torch.Tensor, graph: torch.Tensor, en
     if _entries(entries, B).dim() != 1:
         raise ValueError("entries must be [B]")
     ids, scores = _outputs(B, k, corpus.device, ids, scores)
-    with torch.cuda.device(corpus.device):
-        _check(lib().ann_graph_search_entries_typed(corpus.data_ptr(), N, d, _DTYPES[corpus.dtype], graph.data_ptr(),
-                                                    graph.shape[1], entries.data_ptr(), queries.data_ptr(), B, k, ef,
-                                                    ids.data_ptr(), scores.data_ptr(), _stream(stream)))
+    _call(corpus.device, stream, lib().ann_graph_search_entries_typed, corpus.data_ptr(), N, d, _DTYPES[corpus.dtype],
+          graph.data_ptr(), graph.shape[1], entries.data_ptr(), queries.data_ptr(), B, k, ef, ids.data_ptr(),
+          scores.data_ptr())
     return ids, scores
 
 
@@ -296,9 +302,8 @@ def ann_gather_ids(table: torch.Tensor, idx: torch.Tensor, *, out=None, stream=N
         out = torch.empty_like(idx)
     if out.dtype != torch.int32 or out.shape != idx.shape or not out.is_contiguous() or not out.is_cuda:
         raise ValueError("out must be a contiguous int32 device tensor shaped like idx")
-    with torch.cuda.device(table.device):
-        _check(lib().ann_gather_ids(table.data_ptr(), table.numel(), idx.data_ptr(), idx.numel(), out.data_ptr(),
-                                    _stream(stream)))
+    _call(table.device, stream, lib().ann_gather_ids, table.data_ptr(), table.numel(), idx.data_ptr(), idx.numel(),
+          out.data_ptr())
     return out
 
 
@@ -314,9 +319,8 @@ def ann_priority_order(R: torch.Tensor, W: torch.Tensor, C: torch.Tensor, Wcur: 
             raise ValueError("R, C must be int32 and W, Wcur float64 contiguous device tensors of one length")
     level = torch.empty(n, dtype=torch.int32, device=R.device)
     order = torch.empty(n, dtype=torch.int32, device=R.device)
-    with torch.cuda.device(R.device):
-        _check(lib().ann_priority_order(R.data_ptr(), W.data_ptr(), C.data_ptr(), Wcur.data_ptr(), n, int(G),
-                                        level.data_ptr(), order.data_ptr(), _stream(stream)))
+    _call(R.device, stream, lib().ann_priority_order, R.data_ptr(), W.data_ptr(), C.data_ptr(), Wcur.data_ptr(), n, int(G),
+          level.data_ptr(), order.data_ptr())
     return level, order
 
 
@@ -357,10 +361,8 @@ def ann_graph_search(corpus: torch.Tensor, graph: torch.Tensor, entry: int, quer
     _matrix(queries, "queries")
     B = queries.shape[0]
     ids, scores = _outputs(B, k, queries.device, ids, scores)
-    with torch.cuda.device(queries.device):
-        _check(lib().ann_graph_search(corpus.data_ptr(), graph.data_ptr(), graph.shape[1], int(entry),
-                                      queries.data_ptr(), B, k, ef, ids.data_ptr(), scores.data_ptr(),
-                                      _stream(stream)))
+    _call(queries.device, stream, lib().ann_graph_search, corpus.data_ptr(), graph.data_ptr(), graph.shape[1], int(entry),
+          queries.data_ptr(), B, k, ef, ids.data_ptr(), scores.data_ptr())
     return ids, scores
 
 
