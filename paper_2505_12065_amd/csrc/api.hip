@@ -96,6 +96,7 @@ int grow(void **buf, size_t *have, size_t bytes) {
 
 // The device buffer a call may use as workspace: the caller's when one was set (never grown: a call
 // that needs more fails), else the library's own, grown on demand.
+
 int workspace_for(DeviceState *st, void **own, size_t *own_bytes, size_t bytes, void **out) {
     if (st->user_ws) {
         if (bytes > st->user_bytes)
@@ -174,28 +175,16 @@ int check_common(const void *corpus, int64_t N, int32_t d, int32_t dtype, const 
 
 // ---- flat: launch geometry ---------------------------------------------------------------
 struct FlatPlan {
-    int wide_ntg;            // > 0: matrix-core path with this many query-tile groups
-    StreamPlan st;           // else the streaming kernel; with wide_ntg and k > 4: the repair pass
-    int P;                   // slabs of the matrix-core path
-    int pstride;             // slabs per query in the partial array
-    size_t sample_ofs, thr_ofs;   // byte offsets of the sample lists and thresholds in the workspace
-    // k > 4 on the matrix-core path: candidate arrays instead of lists, streaming kernel as repair
-    bool emit;
-    int sample_P;                 // > 0: a sampling pass with this many slabs supplies thresholds
-    int sample_skip;              // > 0: the sample is the first sample_skip tiles, which the main pass skips
-    size_t cnt_ofs, cand_ofs;
+    StreamPlan st;           // streaming kernel, unless
+    bool wide;               // the matrix-core kernel takes the call, `part` queries at a time
+    WidePlan w;
+    int part;
     size_t ws_bytes;
 };
 
 constexpr int WIDE_MIN_B = 65;   // smallest batch sent to the matrix-core path
-// Smallest corpus sent there, for batches beyond 128 and up to it: below, its tiles of 256 rows x 256 (128) queries do
-// not fill the chip and its sampling pass costs more than it saves.  d = 768 fp16, k = 3, us through the streaming / the
-// matrix-core kernel: N = 64 000: B = 100: 53 / 168, B = 256: 82 / 165, B = 1024: 221 / 436; N = 256 000: 140 / 175,
-// 254 / 207, 740 / 507; N = 1 M: 469 / 413, 797 / 526.
-constexpr int64_t WIDE_MIN_N = 160 * 1024, WIDE_MIN_N_128 = 640 * 1024;
-constexpr int EMIT_CAP = 4096;   // candidate-array entries per query (k > 4)
-constexpr int SAMPLE_STRIDE = 64; // a sampling pass scores every 64th row
-constexpr int64_t SAMPLE_MIN_N = 64 * 1024;
+// Workspace that the group maxima of one launch may take; more queries run one part after the other.
+constexpr size_t WIDE_WS_MAX = (size_t)1 << 30;
 
 // The streaming kernel's geometry.
 StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int k) {
@@ -228,128 +217,109 @@ StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int k) {
     return pl;
 }
 
-FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k) {
+// Rows per group of the matrix-core kernel, by the time of what follows the products, in us: the maxima are written and
+// read once and the rows of k groups are read again, at some 4 TB/s over all queries; one query alone waits for its
+// maxima (twice, 4096 at a time) and, unless groups are single rows, for its rows (128 at a time, 192 columns at once).
+int wide_group_log(int wmf, int64_t N, int d, int B, int k) {
+    int best = 0;
+    double least = INFINITY;
+    for (int g : {0, 2, 4, 5, 6}) {
+        if ((1 << g) > 16 * wmf) break;
+        const double n = (double)N / (1 << g), rows = (double)k * (1 << g);
+        double us = 8.0 * n * B / 4e6 + 1.6 * n / 4096;
+        if (g > 0) us += rows * d * 2 * B / 4e6 + 3.0 + 1.2 * ceil(rows / 128) * ceil(d / 192.0);
+        if (us < least) { least = us; best = g; }
+    }
+    return best;
+}
+
+int wide_shape(int cus, int64_t N, int B) {
+    auto tiles = [&](int bm, int bn) { return ((N + bm - 1) / bm) * ((B + bn - 1) / bn); };
+    if (B > 128 && tiles(256, 256) >= cus) return WIDE_LARGE;
+    if (B <= 64) return tiles(128, 64) >= cus ? WIDE_THIN : WIDE_TINY;
+    if (B <= 128 && tiles(256, 128) >= cus) return WIDE_TALL;
+    return tiles(128, 128) >= cus * 5 / 8 ? WIDE_SMALL : WIDE_TINY;
+}
+
+// Whether the matrix-core kernel takes a call, or the streaming kernel.  The streaming kernel reads large corpora at the
+// rate of HBM for up to 64 queries (1 M x 768, B = 64: 290 us against 380), but its lists cost every group of 16 queries
+// some 400 clocks a tile of 16 rows, whatever d is, which shows where rows are short or the corpus is in the caches
+// (streaming / matrix-core, us: 1 M x 64, B = 16 44 / 41, B = 64 106 / 46; 250 k x 256, B = 32 34 / 34, B = 64 45 / 35; 64 k x
+// 768, B = 32 30 / 32, B = 64 37 / 32).  Very small corpora are all latency: one-row maxima and one pass over them are as
+// fast as short lists and faster than long ones (4000 x 256, k = 16: 13 / 11).
+bool use_wide(int64_t N, int d, int dtype, int B, int k) {
+    if (dtype == ANN_F32) return false;
+    if (B >= WIDE_MIN_B) return true;
+    if (N <= 6000) return k > 4;
+    if (N <= 32 * 1024) return B > 32;
+    return B * (N <= 128 * 1024 ? 16 : N <= 512 * 1024 ? 8 : d <= 128 ? 4 : 0) >= d;
+}
+
+FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, size_t limit) {
     FlatPlan pl{};
-    const size_t a16 = 15;
     pl.st = stream_plan(cus, N, d, dtype, B, k);
-    const bool wide = dtype != ANN_F32 && d % 32 == 0 && B >= WIDE_MIN_B && N >= (B > 128 ? WIDE_MIN_N : WIDE_MIN_N_128);
-    if (!wide) {
-        pl.pstride = pl.st.P;
-        pl.ws_bytes = (size_t)B * pl.st.P * pl.st.K * sizeof(Cand);
-        return pl;
+    pl.part = B;
+    pl.wide = use_wide(N, d, dtype, B, k);
+    if (pl.wide) {
+        int shape = wide_shape(cus, N, B);
+        wide_geometry(pl.w, shape, cus, N, B);
+        pl.w.gs_log = wide_group_log(pl.w.wmf, N, d, B, k);
+        pl.w.n = pl.w.slots >> pl.w.gs_log;
+        const size_t per = (size_t)pl.w.n * sizeof(float);
+        if (per * (size_t)B > limit) {
+            // (large corpora: groups as large as they come)
+            pl.w.gs_log = pl.w.wmf == 4 ? 6 : pl.w.wmf == 2 ? 5 : 4;
+            pl.w.n = pl.w.slots >> pl.w.gs_log;
+            const size_t fit = limit / ((size_t)pl.w.n * sizeof(float));
+            if (fit < 1) pl.wide = false;
+            else if (fit < (size_t)B) {
+                const int parts = (int)((B + fit - 1) / fit);
+                pl.part = (B + parts - 1) / parts;
+                if (pl.part > 256 && (size_t)((pl.part + 255) & ~255) <= fit) pl.part = (pl.part + 255) & ~255;
+                wide_geometry(pl.w, shape, cus, N, pl.part);
+            }
+        }
+        pl.ws_bytes = (size_t)pl.part * (size_t)pl.w.n * sizeof(float);
     }
-    // matrix-core path
-    const int nt = (B + wide_query_tile(B) - 1) / wide_query_tile(B);
-    pl.wide_ntg = nt < 8 ? nt : 8;
-    int P = cus / pl.wide_ntg;
-    if (wide_query_tile(B) == 128) P *= 2;       // 4-wave workgroups, two per compute unit
-    const int64_t mtiles = (N + 255) / 256;
-    if (P > mtiles) P = (int)mtiles;
-    pl.P = P < 1 ? 1 : (P > P_MAX ? P_MAX : P);
-    const int64_t stiles = ((N + SAMPLE_STRIDE - 1) / SAMPLE_STRIDE + 255) / 256;
-    if (k > 4) {
-        // Lists of 16 per lane do not fit beside the accumulators, so the main pass keeps no lists; it appends every
-        // score that reaches a lower bound of the query's k-th best to a per-query candidate array.  The bound is
-        // the k-th best of every 64th row (scored exactly by a short first pass), so about 64 k rows per
-        // query pass it; an array that overflows all the same (heavily tied scores) is repaired by the
-        // streaming kernel, which does no work otherwise.  (A sample of fewer than k rows gives a bound
-        // of -inf: every row is a candidate.)
-        pl.emit = true;
-        pl.pstride = pl.st.P;
-        pl.sample_P = (int)(stiles < pl.P ? stiles : pl.P);
-        pl.sample_ofs = ((size_t)B * pl.st.P * pl.st.K * sizeof(Cand) + a16) & ~a16;
-        pl.thr_ofs = pl.sample_ofs + (size_t)B * pl.sample_P * 4 * sizeof(Cand);   // lists of 4 per sample slab
-        pl.cnt_ofs = (pl.thr_ofs + (size_t)B * sizeof(float) + a16) & ~a16;
-        pl.cand_ofs = (pl.cnt_ofs + (size_t)B * sizeof(int) + a16) & ~a16;
-        pl.ws_bytes = pl.cand_ofs + (size_t)B * EMIT_CAP * sizeof(Cand);
-        return pl;
-    }
-    // a corpus of some size: score a sample first, exactly, and start the main pass from the k-th
-    // best scores of that sample (few rows then pass the threshold test at all).  Many tiles per
-    // slab: the sample is the first tile of every slab-to-be, kept as one more slab and skipped by
-    // the main pass; otherwise every 64th row, which the main pass scores again.
-    if (mtiles >= 8 * (int64_t)pl.P) pl.sample_P = pl.sample_skip = pl.P;
-    else if (N >= SAMPLE_MIN_N) pl.sample_P = (int)(stiles < pl.P ? stiles : pl.P);
-    pl.pstride = pl.P + (pl.sample_skip > 0 ? 1 : 0);
-    pl.sample_ofs = (size_t)B * pl.pstride * 4 * sizeof(Cand);
-    pl.thr_ofs = pl.sample_ofs + (size_t)B * pl.sample_P * 4 * sizeof(Cand);
-    pl.ws_bytes = pl.thr_ofs + (pl.sample_P > 0 ? (size_t)B * sizeof(float) : 0);
+    if (!pl.wide) pl.ws_bytes = (size_t)B * pl.st.P * pl.st.K * sizeof(Cand);
     return pl;
 }
 
-// Streaming kernel over all B queries.  `timed`: the kernel code the launch is recorded under, < 0: not recorded.
-int flat_stream_all(const StreamPlan &st, const void *X, int64_t N, int d, int dtype, const void *Q, int B, Cand *partial,
-                    const int *need, int need_above, After after, int timed_as, hipStream_t stream) {
+int flat_search_run(const FlatPlan &pl, const void *X, int64_t N, int d, int dtype, const void *Q, int B, int k,
+                    int32_t *ids, float *scores, void *ws, After after, hipStream_t stream) {
+    // (launches are recorded by what the caller asked for: fp32, or the batch class whose kernel this is or stands in for)
+    const int code = dtype == ANN_F32 ? ANN_KERNEL_FLAT_F32
+                     : B >= WIDE_MIN_B && d % 32 == 0 ? ANN_KERNEL_FLAT_WIDE : ANN_KERNEL_FLAT_STREAM;
+    if (pl.wide) {
+        float *maxima = static_cast<float *>(ws);
+        for (int q0 = 0; q0 < B; q0 += pl.part) {
+            const int b = B - q0 < pl.part ? B - q0 : pl.part;
+            const void *q = static_cast<const char *>(Q) + (size_t)q0 * d * 2;
+            const After a{after.s ? after.s + q0 : nullptr, after.id ? after.id + q0 : nullptr};
+            hipError_t e;
+            {
+                TimedScope timed(q0 == 0 ? code : -1, stream);
+                e = launch_flat_wide(pl.w, dtype, X, N, d, q, b, maxima, a, stream);
+            }
+            if (int rc = check_launch("flat_wide_kernel", e)) return rc;
+            e = launch_flat_pick(pl.w, dtype, X, N, d, q, b, k, maxima, ids + (size_t)q0 * k, scores + (size_t)q0 * k, a, stream);
+            if (int rc = check_launch("flat_pick_kernel", e)) return rc;
+        }
+        return ANN_OK;
+    }
+    Cand *partial = static_cast<Cand *>(ws);
     hipError_t e;
     {
-        TimedScope timed(timed_as, stream);
+        TimedScope timed(code, stream);
         e = (dtype == ANN_F16 ? launch_flat_stream_f16 : dtype == ANN_BF16 ? launch_flat_stream_bf16 : launch_flat_stream_f32)(
-            st, X, N, d, Q, B, partial, need, need_above, after, stream);
+            pl.st, X, N, d, Q, B, partial, after, stream);
     }
-    return check_launch("flat_stream_kernel", e);
-}
-
-int flat_search_emit(const FlatPlan &pl, const void *X, int64_t N, int d, int dtype, const void *Q, int B, int k,
-                     int32_t *ids, float *scores, char *ws, After after, hipStream_t stream) {
-    Cand *partial = reinterpret_cast<Cand *>(ws);
-    Cand *sample = reinterpret_cast<Cand *>(ws + pl.sample_ofs);
-    float *thr = reinterpret_cast<float *>(ws + pl.thr_ofs);
-    int *cnt = reinterpret_cast<int *>(ws + pl.cnt_ofs);
-    Cand *cand = reinterpret_cast<Cand *>(ws + pl.cand_ofs);
-    // sampling pass: every 64th row, the best 4 per slab and query
-    hipError_t e = launch_flat_wide(dtype, 1, X, N, d, Q, B, sample, pl.sample_P, pl.wide_ntg, 0, nullptr, pl.sample_P,
-                                    0, nullptr, SAMPLE_STRIDE, after, stream);
-    if (int rc = check_launch("flat_wide_kernel (sample)", e)) return rc;
-    if (int rc = check_launch("flat_sample_kth_kernel", launch_flat_sample_kth(sample, pl.sample_P, B, k, thr, nullptr, 0, 0, cnt, stream)))
-        return rc;
-    // main pass: candidates
-    {
-        TimedScope timed(ANN_KERNEL_FLAT_WIDE, stream);
-        e = launch_flat_wide(dtype, 2, X, N, d, Q, B, cand, pl.P, pl.wide_ntg, 0, thr, EMIT_CAP, 0, cnt, 1, after, stream);
-    }
-    if (int rc = check_launch("flat_wide_kernel (candidates)", e)) return rc;
-    // repair pass: returns at once unless a candidate array overflowed
-    if (int rc = flat_stream_all(pl.st, X, N, d, dtype, Q, B, partial, cnt, EMIT_CAP, after, -1, stream)) return rc;
-    return check_launch("flat_merge_lists_kernel",
-                        launch_flat_merge_lists(dtype, partial, pl.st.P, pl.st.K, pl.st.slots(), X, N, d, Q, B, k, ids, scores,
-                                                cnt, cand, EMIT_CAP, after, stream));
-}
-
-int flat_search_run(const FlatPlan &pl, const void *X, int64_t N, int d, int dtype, const void *Q, int B, int k,
-                    int32_t *ids, float *scores, Cand *partial, After after, hipStream_t stream) {
-    if (pl.emit) return flat_search_emit(pl, X, N, d, dtype, Q, B, k, ids, scores, reinterpret_cast<char *>(partial), after, stream);
-    if (pl.wide_ntg > 0) {
-        const float *thr0 = nullptr;
-        if (pl.sample_P > 0) {
-            Cand *sample = reinterpret_cast<Cand *>(reinterpret_cast<char *>(partial) + pl.sample_ofs);
-            float *thr = reinterpret_cast<float *>(reinterpret_cast<char *>(partial) + pl.thr_ofs);
-            const bool skip = pl.sample_skip > 0;
-            hipError_t e = launch_flat_wide(dtype, 1, X, skip ? (int64_t)pl.sample_skip * 256 : N, d, Q, B, sample, pl.sample_P,
-                                            pl.wide_ntg, 0, nullptr, pl.sample_P, 0, nullptr, skip ? 1 : SAMPLE_STRIDE, after, stream);
-            if (int rc = check_launch("flat_wide_kernel (sample)", e)) return rc;
-            e = launch_flat_sample_kth(sample, pl.sample_P, B, k, thr, skip ? partial : nullptr, pl.pstride, pl.P, nullptr,
-                                       stream);
-            if (int rc = check_launch("flat_sample_kth_kernel", e)) return rc;
-            thr0 = thr;
-        }
-        hipError_t e;
-        {
-            TimedScope timed(ANN_KERNEL_FLAT_WIDE, stream);
-            e = launch_flat_wide(dtype, 0, X, N, d, Q, B, partial, pl.P, pl.wide_ntg, pl.sample_skip, thr0, pl.pstride, 0,
-                                 nullptr, 1, after, stream);
-        }
-        if (int rc = check_launch("flat_wide_kernel", e)) return rc;
-    } else {
-        // (recorded by what the caller asked for: fp32, or the batch class whose kernel this is or stands in for)
-        const int code = dtype == ANN_F32 ? ANN_KERNEL_FLAT_F32
-                         : B >= WIDE_MIN_B && d % 32 == 0 ? ANN_KERNEL_FLAT_WIDE : ANN_KERNEL_FLAT_STREAM;
-        if (int rc = flat_stream_all(pl.st, X, N, d, dtype, Q, B, partial, nullptr, 0, after, code, stream)) return rc;
-        if (k > 4)
-            return check_launch("flat_merge_lists_kernel",
-                                launch_flat_merge_lists(dtype, partial, pl.st.P, pl.st.K, pl.st.slots(), X, N, d, Q, B, k, ids,
-                                                        scores, nullptr, nullptr, 0, after, stream));
-    }
-    return check_launch("flat_merge_kernel", launch_flat_merge(partial, pl.pstride, B, k, ids, scores, stream));
+    if (int rc = check_launch("flat_stream_kernel", e)) return rc;
+    if (k > 4)
+        return check_launch("flat_merge_lists_kernel",
+                            launch_flat_merge_lists(dtype, partial, pl.st.P, pl.st.K, pl.st.slots(), X, N, d, Q, B, k, ids,
+                                                    scores, after, stream));
+    return check_launch("flat_merge_kernel", launch_flat_merge(partial, pl.st.P, B, k, ids, scores, stream));
 }
 
 }  // namespace
@@ -391,7 +361,7 @@ int64_t ann_flat_workspace_bytes(int64_t N, int32_t d, int32_t dtype, int32_t B,
     DeviceState *st = nullptr;
     int cus = 256;
     if (device_state(&st) == ANN_OK) cus = st->cus;
-    return (int64_t)flat_plan(cus, N, d, dtype, B, k).ws_bytes;
+    return (int64_t)flat_plan(cus, N, d, dtype, B, k, WIDE_WS_MAX).ws_bytes;
 }
 
 int ann_timing_enable(int32_t on) {
@@ -529,11 +499,11 @@ int ann_flat_search_after_typed(const void *corpus, int64_t N, int32_t d, int32_
     std::lock_guard<std::mutex> lock(g_mu);
     DeviceState *st = nullptr;
     if (int rc = device_state(&st)) return rc;
-    const FlatPlan pl = flat_plan(st->cus, N, d, dtype, B, k);
+    const FlatPlan pl = flat_plan(st->cus, N, d, dtype, B, k, WIDE_WS_MAX);
     void *ws = nullptr;
     if (int rc = workspace_for(st, &st->ws, &st->ws_bytes, pl.ws_bytes, &ws)) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    return flat_search_run(pl, corpus, N, d, dtype, queries, B, k, ids, scores, static_cast<Cand *>(ws), after, s);
+    return flat_search_run(pl, corpus, N, d, dtype, queries, B, k, ids, scores, ws, after, s);
 }
 
 int ann_flat_search(const void *corpus, int64_t N, int32_t d, const void *queries, int32_t B, int32_t k,
@@ -554,13 +524,19 @@ int ann_flat_search_static(const void *corpus, int64_t N, int32_t d, int32_t dty
     std::lock_guard<std::mutex> lock(g_mu);
     DeviceState *st = nullptr;
     if (int rc = device_state(&st)) return rc;
-    const FlatPlan pl = flat_plan(st->cus, N, d, dtype, B, k);
+    // A search that the array does not hold at once runs in parts of as many queries as it does; a batch of 256 and more
+    // with k > 4 is refused instead, as ann.h says.
+    FlatPlan pl = flat_plan(st->cus, N, d, dtype, B, k, WIDE_WS_MAX);
+    if (pl.ws_bytes > (size_t)ANN_STATIC_WORKSPACE_BYTES && (k <= 4 || B < 256)) {
+        const FlatPlan parts = flat_plan(st->cus, N, d, dtype, B, k, ANN_STATIC_WORKSPACE_BYTES);
+        if (parts.ws_bytes <= (size_t)ANN_STATIC_WORKSPACE_BYTES) pl = parts;
+    }
     if (pl.ws_bytes > (size_t)ANN_STATIC_WORKSPACE_BYTES)
         return fail(ANN_ERR_INVALID, "this search needs %zu bytes of workspace, the static one holds %d",
                     pl.ws_bytes, ANN_STATIC_WORKSPACE_BYTES);
     g_timing_off = true;                                  // event pairs would have to be created
     const int rc = flat_search_run(pl, corpus, N, d, dtype, queries, B, k, ids, scores,
-                                   static_cast<Cand *>(st->scratch_ptr), After(), static_cast<hipStream_t>(stream));
+                                   st->scratch_ptr, After(), static_cast<hipStream_t>(stream));
     g_timing_off = false;
     return rc;
 }

@@ -29,6 +29,13 @@ __device__ __forceinline__ void static_for(F &&f) {
     static_for_impl(static_cast<F &&>(f), std::make_integer_sequence<int, N>{});
 }
 
+// Blocks are dealt to the 8 XCDs (each with its own L2) round-robin.  The number of this block in an order in which every
+// XCD has a run of neighbours: work that shares data is numbered side by side and is then fetched into one L2.
+__device__ __forceinline__ int xcd_block() {
+    const int per = gridDim.x >> 3, more = gridDim.x & 7, xcd = blockIdx.x & 7;
+    return xcd * per + min(xcd, more) + (int)(blockIdx.x >> 3);
+}
+
 struct F16 { static constexpr int bytes = 2; };
 struct BF16 { static constexpr int bytes = 2; };
 struct F32 { static constexpr int bytes = 4; };

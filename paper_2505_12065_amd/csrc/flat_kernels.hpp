@@ -122,8 +122,6 @@ __device__ __forceinline__ u4 mask_tail(u4 x, bool inside) {
 //   partial [B, P, K] pairs, K = 4, 8, 12 or 16 (>= k), every list sorted, empty slots (-inf, EMPTY_ID) last.
 //   lds_steps: steps of a query that fit LDS (fewer than all of them only for fp32 rows beyond 2304 columns, where
 //         one group of queries alone is larger than LDS: the rest comes from memory, NQG = 1, not FULL).
-//   need: a group of queries is skipped unless need[q] > need_above for one of them (repair pass behind the
-//         candidate arrays of the matrix-core kernel: usually every group is skipped).
 // Lists of 4 are exact for k <= 4.  For k > 4 a lane may meet more than 4 of the k best rows; the merge then finds 4
 // rows of one lane among the k best and goes over that lane's rows again (flat_merge_lists_kernel).
 //
@@ -136,8 +134,7 @@ __device__ __forceinline__ u4 mask_tail(u4 x, bool inside) {
 // registers of accumulators), which runs one workgroup and is bound by the products.
 template <class T, int NQG, bool FULL, int NWV>
 __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NWV / 4) void flat_stream_kernel(StreamShape sh, Cand *__restrict__ partial, int P, int G,
-                                                               int K, int lds_steps, const int *__restrict__ need,
-                                                               int need_above, After after) {
+                                                               int K, int lds_steps, After after) {
     extern __shared__ __align__(16) unsigned char smem[];
     u4 *qf = reinterpret_cast<u4 *>(smem);            // [NQG][lds_steps][64]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -145,14 +142,8 @@ __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NW
     const int steps = (rb + 63) >> 6;
     const int B = sh.B;
     const int64_t N = sh.N;
-    int lb = blockIdx.x;
-    if ((gridDim.x & 7) == 0) lb = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const int lb = xcd_block();
     const int slab = lb / G, q0 = (lb % G) * (NQG * 16);
-    if (need) {
-        const int q = q0 + tid;
-        if (!__syncthreads_or(tid < NQG * 16 && q < B && need[q] > need_above)) return;
-    }
-
     // the rows this wave starts with are requested before the queries are put into LDS
     const int64_t ntiles = (N + 15) >> 4, tstride = (int64_t)P * NWV;
     const int kofs = (lane >> 4) * 16;                // this lane's byte offset inside a step

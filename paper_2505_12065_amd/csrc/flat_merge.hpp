@@ -60,8 +60,6 @@ __global__ __launch_bounds__(256) void flat_merge_kernel(const Cand *__restrict_
 }
 
 // k > 4.  One workgroup (1 or 4 wavefronts) per query: the k best of its P sorted lists of K pairs (K = 8, 12, 16).
-// With `count`, query q's input is its candidate array cand[q cap ..) of count[q] pairs instead, unless that
-// overflowed (count[q] > cap): then the lists, which a repair pass has filled for exactly those queries.
 //   1. every lane takes the best head of the lists it looks at; the k-th best of those over the workgroup is a
 //      bound that few entries reach (two sorting networks of 21 steps; lists of up to 2048 slabs cost the same);
 //   2. entries that reach it are gathered in LDS (about k of them; a tie of hundreds: rounds of maxima instead);
@@ -74,9 +72,7 @@ constexpr int MERGE_CAP = 512;
 template <class T>
 __global__ __launch_bounds__(256) void flat_merge_lists_kernel(const Cand *__restrict__ partial, int P, int K, int k,
                                                                int32_t *__restrict__ ids, float *__restrict__ scores,
-                                                               const int *__restrict__ count,
-                                                               const Cand *__restrict__ cand, int cap, StreamShape sh,
-                                                               int slots, After after) {
+                                                               StreamShape sh, int slots, After after) {
     __shared__ uint64_t ck[MERGE_CAP];
     __shared__ uint32_t top[64];
     __shared__ uint64_t fin[16];                      // the k best so far, in order
@@ -85,53 +81,50 @@ __global__ __launch_bounds__(256) void flat_merge_lists_kernel(const Cand *__res
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int NT = blockDim.x, nwaves = NT >> 6;
     const uint64_t empty = order_key(-INFINITY, EMPTY_ID);
-    int nl = P, L = K;                                // lists, entries per list
     const Cand *in = partial + (size_t)q * P * K;
-    if (count) {
-        const int n = count[q];                       // uniform for the workgroup
-        if (n <= cap) {
-            nl = n;
-            L = 1;
-            in = cand + (size_t)q * cap;
-            slots = 0;
-        }
-    }
     if (tid < 16) fin[tid] = empty;
     if (tid == 0) n_c = 0;
     auto key_at = [&](int i, int e) {
-        const Cand c = in[(size_t)i * L + e];
+        const Cand c = in[(size_t)i * K + e];
         return order_key(c.s, c.id);
     };
-    uint32_t m = 0;
-    for (int i0 = tid; i0 < nl; i0 += 4 * NT) {
-        uint64_t h[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) h[u] = key_at(min(i0 + u * NT, nl - 1), 0);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) m = i0 + u * NT < nl ? max(m, (uint32_t)(h[u] >> 32)) : m;
-    }
-    m = group_sort_desc<64>(m);
-    if (nwaves > 1) {
-        if (lane < 16) top[wave * 16 + lane] = m;
+    if (P * K <= NT) {                                // an entry per thread: all of them are ranked
+        if (tid < P * K) ck[tid] = key_at(tid / K, tid % K);
+        if (tid == 0) n_c = P * K;
         __syncthreads();
-        m = group_sort_desc<64>(top[lane]);           // (4 waves: 64 values)
     } else {
-        __syncthreads();                              // fin and n_c are set
-    }
-    const uint32_t bound = (uint32_t)__builtin_amdgcn_readlane((int)m, k - 1);
-    for (int i = tid; i < nl; i += NT)
-        for (int e = 0; e < L; ++e) {
-            const uint64_t h = key_at(i, e);
-            if ((uint32_t)(h >> 32) < bound || h == empty) break;
-            const int at = atomicAdd(&n_c, 1);
-            if (at < MERGE_CAP) ck[at] = h;
+        uint32_t m = 0;
+        for (int i0 = tid; i0 < P; i0 += 4 * NT) {
+            uint64_t h[4];
+    #pragma unroll
+            for (int u = 0; u < 4; ++u) h[u] = key_at(min(i0 + u * NT, P - 1), 0);
+    #pragma unroll
+            for (int u = 0; u < 4; ++u) m = i0 + u * NT < P ? max(m, (uint32_t)(h[u] >> 32)) : m;
         }
+        m = group_sort_desc<64>(m);
+        if (nwaves > 1) {
+            if (lane < 16) top[wave * 16 + lane] = m;
+            __syncthreads();
+            m = group_sort_desc<64>(top[lane]);           // (4 waves: 64 values)
+        } else {
+            __syncthreads();                              // fin and n_c are set
+        }
+        const uint32_t bound = (uint32_t)__builtin_amdgcn_readlane((int)m, k - 1);
+        for (int i = tid; i < P; i += NT)
+            for (int e = 0; e < K; ++e) {
+                const uint64_t h = key_at(i, e);
+                if ((uint32_t)(h >> 32) < bound || h == empty) break;
+                const int at = atomicAdd(&n_c, 1);
+                if (at < MERGE_CAP) ck[at] = h;
+            }
+    }
     __syncthreads();
     const int n = n_c;
     if (n <= MERGE_CAP) {
         for (int i = tid; i < n; i += NT) {
             const uint64_t mine = ck[i];
             int r = 0;
+#pragma unroll 8
             for (int j = 0; j < n; ++j) r += (int)(ck[j] > mine);
             if (r < k) fin[r] = mine;
         }
@@ -140,8 +133,8 @@ __global__ __launch_bounds__(256) void flat_merge_lists_kernel(const Cand *__res
         uint64_t last = ~0ull;
         for (int r = 0; r < k; ++r) {
             uint64_t best = empty;
-            for (int i = tid; i < nl; i += NT)
-                for (int e = 0; e < L; ++e) {
+            for (int i = tid; i < P; i += NT)
+                for (int e = 0; e < K; ++e) {
                     const uint64_t h = key_at(i, e);
                     if (h < last) { best = h > best ? h : best; break; }
                 }
@@ -247,35 +240,6 @@ __global__ __launch_bounds__(256) void flat_merge_lists_kernel(const Cand *__res
         const bool has = id != EMPTY_ID;
         ids[(size_t)q * k + tid] = has ? id : -1;
         scores[(size_t)q * k + tid] = has ? s : -INFINITY;
-    }
-}
-
-// One wavefront per query: the k-th best score among Ps sampled lists of KS entries (src[(q Ps + s) KS ..)),
-// -inf when the sample holds fewer than k rows.  The lists come from disjoint rows, so this is the
-// k-th best of a subset of the corpus: a lower bound of the final k-th best score.  With dst, the
-// sample's KS best are also kept, as slab pslot of the query's lists dst[(q pstride + pslot) KS ..)
-// (for a sample whose rows the main pass then skips).  With count, count[q] is set to 0.
-template <int KS, int KO>
-__global__ __launch_bounds__(64) void flat_sample_kth_kernel(const Cand *__restrict__ src, int Ps, int k,
-                                                             float *__restrict__ thr, Cand *__restrict__ dst,
-                                                             int pstride, int pslot, int *__restrict__ count) {
-    const int q = blockIdx.x, lane = threadIdx.x;
-    TopList<KO> best;
-    best.init();
-    gather_best<KO>(src + (size_t)q * Ps * KS, Ps * KS, lane, 64, best);
-    TopList<KO> top;
-    group_top<KO, KO, 1, 64>(best, top);
-    if (lane == 0) {
-        float t = -INFINITY;
-#pragma unroll
-        for (int j = 0; j < KO; ++j)
-            if (j == k - 1 && top.id[j] != EMPTY_ID) t = top.s[j];
-        thr[q] = t;
-        if (count) count[q] = 0;                      // the query's candidate array starts empty
-        if (dst) {
-#pragma unroll
-            for (int j = 0; j < KS; ++j) dst[((size_t)q * pstride + pslot) * KS + j] = Cand{top.s[j], top.id[j]};
-        }
     }
 }
 

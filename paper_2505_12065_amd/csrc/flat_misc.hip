@@ -21,28 +21,16 @@ hipError_t launch_flat_merge(const Cand *partial, int P, int B, int k, int32_t *
 }
 
 hipError_t launch_flat_merge_lists(int dtype, const Cand *partial, int P, int K, int slots, const void *X, int64_t N, int d,
-                                   const void *Q, int B, int k, int32_t *ids, float *scores, const int *count,
-                                   const Cand *cand, int cap, After after, hipStream_t stream) {
+                                   const void *Q, int B, int k, int32_t *ids, float *scores, After after, hipStream_t stream) {
     const StreamShape sh{X, Q, N, d, B};
-    const int threads = count || P > 64 ? 256 : 64;               // a list per lane where possible
+    const int threads = P > 64 || (P * K > 64 && P * K <= 256) ? 256 : 64;         // an entry or a list per lane where possible
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(B), dim3(threads), 0, stream, partial, P, K, k, ids, scores, count, cand, cap, sh,
-                           slots, after);
+        hipLaunchKernelGGL(kernel, dim3(B), dim3(threads), 0, stream, partial, P, K, k, ids, scores, sh, slots, after);
         return hipGetLastError();
     };
     if (dtype == 0) return go(flat_merge_lists_kernel<F16>);
     if (dtype == 1) return go(flat_merge_lists_kernel<BF16>);
     return go(flat_merge_lists_kernel<F32>);
-}
-
-hipError_t launch_flat_sample_kth(const Cand *src, int Ps, int B, int k, float *thr, Cand *dst, int pstride, int pslot,
-                                  int *count, hipStream_t stream) {
-    if (k <= 4)   // short lists: a fraction of the selection work
-        hipLaunchKernelGGL((flat_sample_kth_kernel<4, 4>), dim3(B), dim3(64), 0, stream, src, Ps, k, thr, dst, pstride, pslot, count);
-    else
-        hipLaunchKernelGGL((flat_sample_kth_kernel<4, 16>), dim3(B), dim3(64), 0, stream, src, Ps, k, thr, dst, pstride, pslot,
-                           count);
-    return hipGetLastError();
 }
 
 // ---- measurement support: what the matrix cores of this device sustain --------------------------

@@ -1,0 +1,215 @@
+// Second half of the exact search on the matrix cores: from the group maxima that flat_wide_kernel leaves, the k best
+// rows of every query.
+#pragma once
+
+#include "flat_kernels.hpp"
+
+namespace ann {
+
+// Corpus row of place `slot` in the order of flat_wide_kernel's lanes: tile, wave row, lane half, accumulator.  The groups
+// are runs of 2^gs_log places, and a group's first place is its lowest row.
+template <int WMF>
+__device__ __forceinline__ int64_t wide_row(int64_t slot) {
+    const int s = (int)(slot & (64 * WMF - 1));
+    const int wm = s / (32 * WMF), lhi = s / (16 * WMF) & 1, i = s / 16 & (WMF - 1), r = s & 15;
+    return (slot & ~(int64_t)(64 * WMF - 1)) + wm * 32 * WMF + i * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
+}
+
+// One workgroup (1, 2 or 4 wavefronts) per query.
+//   1. every thread takes the largest of the maxima it looks at; the k-th largest of those is a bound that few maxima
+//      reach (two sorting networks);
+//   2. those few are gathered in LDS and ranked by counting: the groups with fewer than k larger ones hold the k best
+//      rows, and the k-th best group maximum T is a lower bound of the k-th best score;
+//   3. their rows are scored once more, by the instructions and in the order of flat_wide_kernel, so to the same bits: 32
+//      rows to an MFMA, the query as every one of its columns; the rows that reach T (k, if none tie) are ranked.
+// Groups of one row: their maxima are the scores, step 3 falls away.  Hundreds of maxima that tie with the k-th: the groups
+// are gone through in order, a few at a time, past those that can no longer improve the k best so far.
+// Bound by the latency of three dependent reads (maxima twice, rows) at 8 to 12 us, and beyond about 1000 queries by the
+// bytes of the rows.
+constexpr int PICK_CAP = 512;
+template <class T, int WMF, bool ONE>
+__global__ __launch_bounds__(256) void flat_pick_kernel(const float *__restrict__ maxima, int64_t n, int gs_log, int k,
+                                                        int32_t *__restrict__ ids, float *__restrict__ scores, StreamShape sh,
+                                                        After after) {
+    __shared__ uint64_t ck[PICK_CAP];                 // gathered maxima, then scored rows
+    __shared__ int sel[PICK_CAP];                     // groups to score
+    __shared__ uint32_t top[64];
+    __shared__ uint64_t fin[16], old[16];             // the k best so far, in order
+    __shared__ int n_c, n_sel;
+    __shared__ uint32_t t_min;
+    extern __shared__ __align__(16) unsigned char smem[];
+    u4 *qs = reinterpret_cast<u4 *>(smem);            // the query (groups of more than one row)
+    const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int NT = blockDim.x, nwaves = NT >> 6;
+    const int l32 = lane & 31, lhi = lane >> 5;
+    const uint64_t empty = order_key(-INFINITY, EMPTY_ID);
+    const float *mx = maxima + (size_t)q * n;
+    const int rb = sh.d * T::bytes, nch = rb >> 4;
+    if (tid < 16) fin[tid] = empty;
+    if (tid == 0) { n_c = 0; n_sel = 0; t_min = ~0u; }
+    if (!ONE)
+        for (int c = tid; c < nch; c += NT) qs[c] = load_chunk(static_cast<const char *>(sh.Q) + (size_t)q * rb + c * 16);
+
+    // order-preserving image of a maximum, 0 for a NaN (no row that takes part)
+    auto image = [](float v) { return v == v ? (uint32_t)(order_key(v, 0) >> 32) : 0u; };
+    uint32_t m = 0;
+    const int64_t n4 = n >> 2;                        // (n is a multiple of 4)
+    f4 v[4];                                          // 16 maxima: all of this thread's, if n <= 16 NT
+    auto load_maxima = [&](int64_t i0) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t i = i0 + u * NT;
+            v[u] = *reinterpret_cast<const f4 *>(mx + 4 * (i < n4 ? i : i0));
+        }
+    };
+    for (int64_t i0 = tid; i0 < n4; i0 += 4 * NT) {
+        load_maxima(i0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) m = max(m, image(v[u][c]));
+    }
+    m = group_sort_desc<64>(m);
+    if (nwaves > 1) {
+        if (lane < 16) top[wave * 16 + lane] = m;
+        else if (nwaves == 2 && lane < 32) top[16 + wave * 16 + lane] = 0;
+        __syncthreads();
+        m = group_sort_desc<64>(top[lane]);           // (4 waves: 64 values)
+    } else {
+        __syncthreads();                              // the shared words are set
+    }
+    const uint32_t bound = max(1u, (uint32_t)__builtin_amdgcn_readlane((int)m, k - 1));
+    // 64-bit key of entry e with value image x: what the ranks go by (one row: the row's own key)
+    auto entry_key = [&](uint32_t x, int64_t e) {
+        return ((uint64_t)x << 32) | (uint32_t)~(uint32_t)(ONE ? wide_row<WMF>(e) : e);
+    };
+    for (int64_t i0 = tid; i0 < n4; i0 += 4 * NT) {
+        if (n4 > 4 * NT) load_maxima(i0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t x = image(v[u][c]);
+                if (x >= bound && i0 + u * NT < n4) {
+                    const int at = atomicAdd(&n_c, 1);
+                    if (at < PICK_CAP) ck[at] = entry_key(x, 4 * (i0 + u * NT) + c);
+                }
+            }
+    }
+    __syncthreads();
+    const int found = n_c;
+
+    // fin <- the k best of fin and ck[0 .. c)
+    auto merge = [&](int c) {
+        if (tid < 16) old[tid] = fin[tid];
+        __syncthreads();
+        for (int i = tid; i < c + k; i += NT) {
+            const uint64_t mine = i < c ? ck[i] : old[i - c];
+            int r = i < c ? 0 : i - c;
+            for (int j = 0; j < c; ++j) r += (int)(ck[j] > mine);
+            if (i < c)
+                for (int j = 0; j < k; ++j) r += (int)(old[j] > mine);
+            if (r < k) fin[r] = mine;
+        }
+        __syncthreads();
+    };
+    // the rows of groups sel[0 .. ns) scored and merged, PICK_CAP at a time; t: image that a row has to reach
+    auto score_groups = [&](int ns, uint32_t t) {
+        const int steps = (rb + 31) >> 5;
+        const int64_t rows = (int64_t)ns << gs_log;
+        auto row_of = [&](int64_t e) {
+            e = e < rows ? e : rows - 1;
+            return wide_row<WMF>(((int64_t)sel[e >> gs_log] << gs_log) + (e & ((1 << gs_log) - 1)));
+        };
+        for (int64_t b0 = 0; b0 < rows; b0 += PICK_CAP) {
+            if (tid == 0) n_c = 0;
+            __syncthreads();
+            const uint64_t worst = fin[k - 1];
+            for (int u = wave; u < PICK_CAP / 32 && b0 + u * 32 < rows; u += nwaves) {
+                const int64_t e0 = b0 + u * 32;
+                int64_t row = row_of(e0 + l32);
+                row = row < sh.N ? row : sh.N - 1;
+                const char *rp = static_cast<const char *>(sh.X) + (size_t)row * rb;
+                f16v acc;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+                constexpr int RUN = 12;               // steps whose loads are in flight together
+                for (int s0 = 0; s0 < steps; s0 += RUN) {
+                    u4 x[RUN];
+#pragma unroll
+                    for (int s = 0; s < RUN; ++s) {
+                        x[s] = zero_chunk();
+                        if (s0 + s < steps) x[s] = load_chunk(rp + min(2 * (s0 + s) + lhi, nch - 1) * 16);
+                    }
+#pragma unroll
+                    for (int s = 0; s < RUN; ++s)
+                        if (s0 + s < steps) {
+                            const int ch = 2 * (s0 + s) + lhi;
+                            acc = mfma32<T>(mask_tail(x[s], ch < nch), mask_tail(qs[min(ch, nch - 1)], ch < nch), acc);
+                        }
+                }
+                // every column holds the same 32 sums: lane r < 16 of a half looks after its half's r-th
+                float v = acc[0];
+#pragma unroll
+                for (int r = 1; r < 16; ++r) v = l32 == r ? acc[r] : v;
+                const int64_t e = e0 + 8 * ((l32 & 15) >> 2) + 4 * lhi + (l32 & 3);
+                const int64_t id = row_of(e);
+                if (after.s) v = after_boundary(v, (int)id, after.s[q], after.id[q]);
+                if (l32 < 16 && e < rows && id < sh.N && v == v) {
+                    const uint64_t key = order_key(v, (int)id);
+                    if ((uint32_t)(key >> 32) >= t && key > worst) ck[atomicAdd(&n_c, 1)] = key;
+                }
+            }
+            __syncthreads();
+            merge(n_c);
+        }
+    };
+
+    if (found <= PICK_CAP) {
+        if (ONE) {
+            merge(found);
+        } else {
+            for (int i = tid; i < found; i += NT) {
+                const uint32_t mine = (uint32_t)(ck[i] >> 32);
+                int larger = 0;
+                for (int j = 0; j < found; ++j) larger += (int)((uint32_t)(ck[j] >> 32) > mine);
+                if (larger < k) {
+                    sel[atomicAdd(&n_sel, 1)] = (int)~(uint32_t)ck[i];
+                    atomicMin(&t_min, mine);
+                }
+            }
+            __syncthreads();
+            score_groups(n_sel, found < k ? 0u : t_min);
+        }
+    } else {
+        const int step = ONE ? PICK_CAP : 64;
+        for (int64_t c0 = 0; c0 < n; c0 += step) {
+            __syncthreads();
+            if (tid == 0) { n_c = 0; n_sel = 0; }
+            __syncthreads();
+            const uint64_t worst = fin[k - 1];
+            for (int64_t e = c0 + tid; e < min(c0 + (int64_t)step, n); e += NT) {
+                const uint32_t x = image(mx[e]);
+                const uint64_t best = ((uint64_t)x << 32) | (uint32_t)~(uint32_t)wide_row<WMF>(e << gs_log);
+                if (x >= bound && best > worst) {     // its best row may be better than the k-th so far
+                    if (ONE) ck[atomicAdd(&n_c, 1)] = best;
+                    else sel[atomicAdd(&n_sel, 1)] = (int)e;
+                }
+            }
+            __syncthreads();
+            if (ONE) { if (n_c > 0) merge(n_c); }
+            else if (n_sel > 0) score_groups(n_sel, bound);
+        }
+    }
+
+    if (tid < k) {
+        float s;
+        int id;
+        order_key_decode(fin[tid], s, id);
+        const bool has = id != EMPTY_ID;
+        ids[(size_t)q * k + tid] = has ? id : -1;
+        scores[(size_t)q * k + tid] = has ? s : -INFINITY;
+    }
+}
+
+}  // namespace ann

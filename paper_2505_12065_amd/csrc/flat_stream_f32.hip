@@ -4,8 +4,8 @@
 namespace ann {
 
 hipError_t launch_flat_stream_f32(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
-                                  const int *need, int need_above, After after, hipStream_t stream) {
-    return launch_stream_any<F32>(pl, X, N, d, Q, B, partial, need, need_above, after, stream);
+                                  After after, hipStream_t stream) {
+    return launch_stream_any<F32>(pl, X, N, d, Q, B, partial, after, stream);
 }
 
 }  // namespace ann

@@ -1,50 +1,78 @@
-// flat_wide_kernel instantiations and launcher.
+// flat_wide_kernel and flat_pick_kernel: instantiations and launchers.
 #include "flat_wide_kernel.hpp"
-#include "launch.hpp"
+#include "flat_pick.hpp"
 
 namespace ann {
 namespace {
-template <class T, int WNF, int NWN, int MODE>
-hipError_t launch(const void *X, int64_t N, int d, const void *Q, int B, Cand *partial, int P, int NTG,
-                  int64_t tile_begin, const float *thr_init, int pstride, int pslot0, int *emit_count, int row_stride,
-                  After after, hipStream_t stream) {
+template <class T, class C>
+hipError_t launch(const WidePlan &pl, const void *X, int64_t N, int d, const void *Q, int B, float *maxima, After after,
+                  hipStream_t stream) {
     static size_t big = 0;
-    using C = WideCfg<WNF, NWN>;
-    const size_t lds = C::DYN_LDS_BYTES;
-    if (hipError_t e = allow_big_lds(reinterpret_cast<const void *>(&flat_wide_kernel<T, WNF, NWN, MODE>), lds, &big))
-        return e;
-    hipLaunchKernelGGL((flat_wide_kernel<T, WNF, NWN, MODE>), dim3(P * NTG), dim3(C::THREADS), lds, stream, X, N, d,
-                       Q, B, partial, P, NTG, tile_begin, thr_init, pstride, pslot0, emit_count, row_stride, after);
+    if (hipError_t e = allow_big_lds(reinterpret_cast<const void *>(&flat_wide_kernel<T, C>), C::LDS_BYTES, &big)) return e;
+    hipLaunchKernelGGL((flat_wide_kernel<T, C>), dim3(pl.P * pl.NT), dim3(C::THREADS), C::LDS_BYTES, stream, X, N, d, Q, B,
+                       maxima, pl.n, pl.P, pl.NT, pl.gs_log, after);
     return hipGetLastError();
 }
 
-template <class T, int MODE>
-hipError_t launch_tile(const void *X, int64_t N, int d, const void *Q, int B, Cand *partial, int P, int NTG,
-                       int64_t tile_begin, const float *thr_init, int pstride, int pslot0, int *emit_count, int row_stride,
-                  After after, hipStream_t stream) {
-    return wide_query_tile(B) == 128
-               ? launch<T, 2, 2, MODE>(X, N, d, Q, B, partial, P, NTG, tile_begin, thr_init, pstride, pslot0, emit_count, row_stride, after, stream)
-               : launch<T, 2, 4, MODE>(X, N, d, Q, B, partial, P, NTG, tile_begin, thr_init, pstride, pslot0, emit_count, row_stride, after, stream);
+template <class T>
+hipError_t launch_any(const WidePlan &pl, const void *X, int64_t N, int d, const void *Q, int B, float *maxima, After after,
+                      hipStream_t stream) {
+    switch (pl.shape) {
+    case WIDE_LARGE: return launch<T, WideLarge>(pl, X, N, d, Q, B, maxima, after, stream);
+    case WIDE_TALL: return launch<T, WideTall>(pl, X, N, d, Q, B, maxima, after, stream);
+    case WIDE_SMALL: return launch<T, WideSmall>(pl, X, N, d, Q, B, maxima, after, stream);
+    case WIDE_TINY: return launch<T, WideTiny>(pl, X, N, d, Q, B, maxima, after, stream);
+    default: return launch<T, WideThin>(pl, X, N, d, Q, B, maxima, after, stream);
+    }
+}
+
+template <class T>
+hipError_t pick(const WidePlan &pl, const void *X, int64_t N, int d, const void *Q, int B, int k, const float *maxima,
+                int32_t *ids, float *scores, After after, hipStream_t stream) {
+    const StreamShape sh{X, Q, N, d, B};
+    // a wave for one-row groups of a small corpus; else a wave per 32 rows to score, two at least
+    const bool one = pl.gs_log == 0;
+    const int threads = one && pl.n <= 2048 ? 64 : !one && (k << pl.gs_log) <= 64 && pl.n <= 8192 ? 128 : 256;
+    const size_t lds = one ? 0 : (size_t)d * 2;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(B), dim3(threads), lds, stream, maxima, pl.n, pl.gs_log, k, ids, scores, sh, after);
+        return hipGetLastError();
+    };
+    if (one) return pl.wmf == 4 ? go(flat_pick_kernel<T, 4, true>) : pl.wmf == 2 ? go(flat_pick_kernel<T, 2, true>) : go(flat_pick_kernel<T, 1, true>);
+    return pl.wmf == 4 ? go(flat_pick_kernel<T, 4, false>) : pl.wmf == 2 ? go(flat_pick_kernel<T, 2, false>) : go(flat_pick_kernel<T, 1, false>);
+}
+template <class C>
+void geometry(WidePlan &pl, int cus, int64_t N, int B) {
+    const int64_t tiles = (N + C::BM - 1) / C::BM;
+    pl.wmf = C::WMF;
+    pl.NT = (B + C::BN - 1) / C::BN;
+    const int64_t cap = (int64_t)cus * C::PER_CU / pl.NT;
+    pl.P = (int)(cap < 1 ? 1 : cap < tiles ? cap : tiles);
+    pl.slots = tiles * C::BM;
 }
 }  // namespace
 
-int wide_query_tile(int B) { return B <= 128 ? 128 : 256; }
-
-hipError_t launch_flat_wide(int dtype, int mode, const void *X, int64_t N, int d, const void *Q, int B,
-                            Cand *partial, int P, int NTG, int64_t tile_begin, const float *thr_init, int pstride,
-                            int pslot0, int *emit_count, int row_stride, After after, hipStream_t stream) {
-#define ANN_WIDE_CASE(TYPE, MODE)                                                                                    \
-    return launch_tile<TYPE, MODE>(X, N, d, Q, B, partial, P, NTG, tile_begin, thr_init, pstride, pslot0, emit_count, \
-                                   row_stride, after, stream)
-    if (dtype == 0) {
-        if (mode == WIDE_SELECT) ANN_WIDE_CASE(F16, WIDE_SELECT);
-        if (mode == WIDE_EMIT) ANN_WIDE_CASE(F16, WIDE_EMIT);
-        ANN_WIDE_CASE(F16, WIDE_LISTS);
+void wide_geometry(WidePlan &pl, int shape, int cus, int64_t N, int B) {
+    pl.shape = shape;
+    switch (shape) {
+    case WIDE_LARGE: return geometry<WideLarge>(pl, cus, N, B);
+    case WIDE_TALL: return geometry<WideTall>(pl, cus, N, B);
+    case WIDE_SMALL: return geometry<WideSmall>(pl, cus, N, B);
+    case WIDE_TINY: return geometry<WideTiny>(pl, cus, N, B);
+    default: return geometry<WideThin>(pl, cus, N, B);
     }
-    if (mode == WIDE_SELECT) ANN_WIDE_CASE(BF16, WIDE_SELECT);
-    if (mode == WIDE_EMIT) ANN_WIDE_CASE(BF16, WIDE_EMIT);
-    ANN_WIDE_CASE(BF16, WIDE_LISTS);
-#undef ANN_WIDE_CASE
+}
+
+hipError_t launch_flat_wide(const WidePlan &pl, int dtype, const void *X, int64_t N, int d, const void *Q, int B, float *maxima,
+                            After after, hipStream_t stream) {
+    return dtype == 0 ? launch_any<F16>(pl, X, N, d, Q, B, maxima, after, stream)
+                      : launch_any<BF16>(pl, X, N, d, Q, B, maxima, after, stream);
+}
+
+hipError_t launch_flat_pick(const WidePlan &pl, int dtype, const void *X, int64_t N, int d, const void *Q, int B, int k,
+                            const float *maxima, int32_t *ids, float *scores, After after, hipStream_t stream) {
+    return dtype == 0 ? pick<F16>(pl, X, N, d, Q, B, k, maxima, ids, scores, after, stream)
+                      : pick<BF16>(pl, X, N, d, Q, B, k, maxima, ids, scores, after, stream);
 }
 
 }  // namespace ann

@@ -368,7 +368,6 @@ __global__ __launch_bounds__(GRAPH_THREADS, RPG == 2 ? 1 : QREG ? 2 : 3) void gr
 
     // ---- select: the first SW unexpanded entries of the list, in order, into this wave's sel arrays --------------
     int nsel = 0;
-    bool more = false;                                    // the list may hold unexpanded entries behind those
     auto select = [&] {
         const float *dsc = ls(cur);
         const uint32_t *did = li(cur);
@@ -381,7 +380,6 @@ __global__ __launch_bounds__(GRAPH_THREADS, RPG == 2 ? 1 : QREG ? 2 : 3) void gr
         // 256 entries, read together, from the block of 64 that holds the first unexpanded one on (a second round
         // only when those hold none: rare)
         int nd = 0;
-        more = false;
         for (int base = LONG ? 0 : first & ~63; base < len && nd == 0; base += 256) {
             uint32_t e[4];
             float f[4];
@@ -398,10 +396,8 @@ __global__ __launch_bounds__(GRAPH_THREADS, RPG == 2 ? 1 : QREG ? 2 : 3) void gr
                     const int r = nd + __builtin_popcountll(m & below);
                     if (((m >> lane) & 1) && r < SW) put((LONG ? SW : 0) + r, e[u], f[u], base + 64 * u + lane);
                     nd += __builtin_popcountll(m);
-                    more = base + 64 * u + 64 < len;
                 }
         }
-        more |= nd > SW;
         nsel = min(nd, SW);
         if constexpr (LONG) {
             // M's first SW, of the 128 entries around the first; then the two ordered runs are merged: a lane per
@@ -453,7 +449,7 @@ __global__ __launch_bounds__(GRAPH_THREADS, RPG == 2 ? 1 : QREG ? 2 : 3) void gr
             nsel = min(SW, nsel + nm);
             if (m_more) {
                 nsel = min(nsel, __builtin_amdgcn_readlane(r, SW + nm - 1) + 1);
-                more = true;
+
             }
         }
     };

@@ -37,35 +37,32 @@ struct StreamPlan {
     int K = 4;                   // entries of a slab's list: k rounded up to a multiple of 4
     int slots() const { return P * waves; }
 };
-// partial[B, P, K]: every slab's best K per query.  need: see the kernel.
+// partial[B, P, K]: every slab's best K per query.
 hipError_t launch_flat_stream_f16(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
-                                  const int *need, int need_above, After after, hipStream_t stream);
+                                  After after, hipStream_t stream);
 hipError_t launch_flat_stream_bf16(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
-                                   const int *need, int need_above, After after, hipStream_t stream);
+                                   After after, hipStream_t stream);
 hipError_t launch_flat_stream_f32(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
-                                  const int *need, int need_above, After after, hipStream_t stream);
-// Large batches on the matrix cores (16-bit corpora, d % 32 == 0, lists of 4).
-// Query tile is wide_query_tile(B) queries; gridDim = P slabs x NTG query-tile groups;
-// rows [256 tile_begin, N) are scanned; results go to partial[(q pstride + pslot0 + slab) 4 ..).
-// mode 0: list epilogue, thr_init = optional per-query lower bounds of the final k-th best score;
-// mode 1: threshold-free selection epilogue (sampling pass), rows 0, row_stride, 2 row_stride, ... only;
-// mode 2 (k > 4): every score >= thr_init[q] is appended to the candidate array
-// partial[q pstride ..) through emit_count[q] (zero on entry; counts past pstride mean overflow).
-int wide_query_tile(int B);
-hipError_t launch_flat_wide(int dtype, int mode, const void *X, int64_t N, int d, const void *Q, int B,
-                            Cand *partial, int P, int NTG, int64_t tile_begin, const float *thr_init, int pstride,
-                            int pslot0, int *emit_count, int row_stride, After after, hipStream_t stream);
-// thr[q] = k-th best score among the Ps sampled lists of 4 of query q (-inf if fewer), k <= 16;
-// with dst, the 4 best of the sample also become slab pslot of dst[B, pstride, 4]; with count, count[q] = 0
-hipError_t launch_flat_sample_kth(const Cand *src, int Ps, int B, int k, float *thr, Cand *dst, int pstride, int pslot,
-                                  int *count, hipStream_t stream);
+                                  After after, hipStream_t stream);
+// Large batches on the matrix cores (16-bit corpora).
+constexpr int WIDE_LARGE = 0, WIDE_TALL = 1, WIDE_SMALL = 2, WIDE_THIN = 3, WIDE_TINY = 4;
+struct WidePlan {
+    int shape, wmf;              // workgroup tile (a WideCfg); its row fragments per wave
+    int NT, P;                   // query tiles x slabs of the corpus
+    int gs_log;                  // a maximum stands for 2^gs_log rows
+    int64_t slots, n;            // rows of whole tiles; groups they make
+};
+void wide_geometry(WidePlan &pl, int shape, int cus, int64_t N, int B);
+// maxima [B, pl.n]
+hipError_t launch_flat_wide(const WidePlan &pl, int dtype, const void *X, int64_t N, int d, const void *Q, int B, float *maxima,
+                            After after, hipStream_t stream);
+hipError_t launch_flat_pick(const WidePlan &pl, int dtype, const void *X, int64_t N, int d, const void *Q, int B, int k,
+                            const float *maxima, int32_t *ids, float *scores, After after, hipStream_t stream);
 // k <= 4: merge the P lists of 4 of every query.
 hipError_t launch_flat_merge(const Cand *partial, int P, int B, int k, int32_t *ids, float *scores, hipStream_t stream);
-// k > 4: merge the P lists of K of every query, made by flat_stream_kernel with `slots` = P waves; with count, query q's
-// input is its candidate array cand[q cap ..) of count[q] entries, or, when that overflowed, its lists (repair pass).
+// k > 4: merge the P lists of K of every query, made by flat_stream_kernel with `slots` = P waves.
 hipError_t launch_flat_merge_lists(int dtype, const Cand *partial, int P, int K, int slots, const void *X, int64_t N, int d,
-                                   const void *Q, int B, int k, int32_t *ids, float *scores, const int *count,
-                                   const Cand *cand, int cap, After after, hipStream_t stream);
+                                   const void *Q, int B, int k, int32_t *ids, float *scores, After after, hipStream_t stream);
 
 constexpr int GRAPH_DENSE_MIN_B = 1280;   // batches beyond this run three graph-search workgroups per compute unit
 constexpr int GRAPH_EF_DOUBLE = 2048;    // candidate lists up to this length are double-buffered in LDS

@@ -149,6 +149,42 @@ def test_flat_continuation_pages(dtype, N, d, B, k):
         assert (got[:, 40:] == -1).all() and (np.sort(got[:, :40], 1) == np.arange(40)).all()
 
 
+@pytest.mark.parametrize("dtype,N,d,B,k", [
+    (torch.float16, 65_000, 40, 257, 5),        # tiles of 256 x 256, row end inside a stage, one query in the last tile
+    (torch.bfloat16, 65_537, 32, 128, 1),       # 256 x 128, one stage, one row in the last tile
+    (torch.float16, 10_001, 72, 300, 16),       # 128 x 128
+    (torch.bfloat16, 33_000, 72, 64, 2),        # 128 x 64
+    (torch.float16, 65, 136, 70, 16),           # 64 x 64, one-row groups
+    (torch.bfloat16, 4_097, 8, 1, 9),           # ... one query, the shortest row
+    (torch.float16, 400_000, 8, 65, 1),         # groups of 64
+    (torch.float16, 1_000_000, 32, 512, 3),     # ... in parts, through the static workspace
+])
+def test_flat_group_maxima(dtype, N, d, B, k):
+    """The matrix-core kernel at the edges of its tile shapes and group sizes: two pages against one oracle answer, with
+    scores that are not numbers among the rows; the static entry point gives the same."""
+    say(f"flat group maxima: dtype={dtype} N={N} d={d} B={B} k={k}")
+    c = synth.make_corpus(N, d, 8, seed=N % 83, dtype=dtype, zipf_a=None, sigma=0.4)
+    x = c.x.clone()
+    x[::7, 0] = float("nan")                                         # these rows are never listed
+    q = synth.make_queries(c, B)
+    xd, qd = x.to(DEV), q.to(DEV)
+    first = ann.ann_flat_search_typed(xd, qd, k)
+    second = ann.ann_flat_search_typed(xd, qd, k, after=(first[1][:, -1].contiguous(), first[0][:, -1].contiguous()))
+    out = ann.binding.ann_flat_search_static(xd, qd, k, ids=torch.empty_like(first[0]), scores=torch.empty_like(first[1]))
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], first[0]) and torch.equal(out[1], first[1])
+    keep = torch.arange(N)[torch.arange(N) % 7 != 0]
+    few = slice(0, B, max(1, B // 40))                               # the oracle takes its time
+    xn, qn = to_np(x[keep]), to_np(q[few])
+    o_ids, _, o_sc64 = oracle.flat_search(xn, qn, 2 * k, dtype=np_dtype_name(x))
+    ids = torch.cat([first[0], second[0]], 1)[few].cpu().numpy()
+    assert (ids % 7 != 0).all()
+    got = np.searchsorted(keep.numpy(), ids).astype(np.int32)        # ids among the rows that are kept
+    sc = torch.cat([first[1], second[1]], 1)[few].cpu().numpy()
+    strict, tolerant, n = compare_topk(got, sc, o_ids, o_sc64, xn, qn, dtype=np_dtype_name(x))
+    assert strict >= n - max(1, n // 20), (strict, n)
+
+
 @pytest.mark.parametrize("dtype,B", [(torch.float16, 1), (torch.bfloat16, 37), (torch.float32, 20)])
 def test_flat_many_of_the_best_rows_in_one_lane(dtype, B):
     """k > 4: a lane of the streaming kernel keeps the 4 best of its rows, so rows a whole number of grid strides
