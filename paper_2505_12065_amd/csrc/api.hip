@@ -219,26 +219,32 @@ StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int k) {
 
 // Rows per group of the matrix-core kernel, by the time of what follows the products, in us: the maxima are written and
 // read once and the rows of k groups are read again, at some 4 TB/s over all queries; one query alone waits for its
-// maxima (twice, 4096 at a time) and, unless groups are single rows, for its rows (128 at a time, 192 columns at once).
-int wide_group_log(int wmf, int64_t N, int d, int B, int k) {
+// maxima (twice, 1024 a wave at a time) and, unless groups are single rows, for its rows (32 a wave, 192 columns at once).
+int wide_group_log(int cus, int wmf, int64_t N, int d, int B, int k) {
+    const int waves = B <= cus ? 8 : 4;                   // of a query
     int best = 0;
     double least = INFINITY;
     for (int g : {0, 2, 4, 5, 6}) {
         if ((1 << g) > 16 * wmf) break;
         const double n = (double)N / (1 << g), rows = (double)k * (1 << g);
-        double us = 8.0 * n * B / 4e6 + 1.6 * n / 4096;
-        if (g > 0) us += rows * d * 2 * B / 4e6 + 3.0 + 1.2 * ceil(rows / 128) * ceil(d / 192.0);
+        double us = 8.0 * n * B / 4e6 + 1.6 * n / (1024 * waves);
+        if (g > 0) us += rows * d * 2 * B / 4e6 + 3.0 + 1.2 * ceil(rows / (32 * waves)) * ceil(d / 192.0);
         if (us < least) { least = us; best = g; }
     }
     return best;
 }
 
+// The tile of the matrix-core kernel: the largest of which there are enough for the chip (larger tiles move fewer bytes per
+// product: 300 k x 768, B = 256: 162 us with 256 x 256, 187 with 512 x 128, 220 with 128 x 128; 30 k x 768, B = 256, 118
+// large tiles: 36, 39, 32; 50 k, 196 tiles: 40, 42, 52).  Queries are padded to whole tiles; the 512 x 128 tile runs at
+// 12/13 of the rate of the other large one, so it takes over where it saves more than that (1 M x 768, B = 300: 822 -> 745).
 int wide_shape(int cus, int64_t N, int B) {
-    auto tiles = [&](int bm, int bn) { return ((N + bm - 1) / bm) * ((B + bn - 1) / bn); };
-    if (B > 128 && tiles(256, 256) >= cus) return WIDE_LARGE;
-    if (B <= 64) return tiles(128, 64) >= cus ? WIDE_THIN : WIDE_TINY;
-    if (B <= 128 && tiles(256, 128) >= cus) return WIDE_TALL;
-    return tiles(128, 128) >= cus * 5 / 8 ? WIDE_SMALL : WIDE_TINY;
+    auto enough = [&](int bm, int bn) { return 8 * ((N + bm - 1) / bm) * ((B + bn - 1) / bn) >= 5 * (int64_t)cus; };
+    if (B <= 64) return ((N + 127) / 128) >= cus ? WIDE_THIN : WIDE_TINY;
+    const int64_t cols256 = (B + 255) / 256 * 256, cols128 = (B + 127) / 128 * 128;
+    if (enough(256, 256) && 12 * cols256 <= 13 * cols128) return WIDE_LARGE;
+    if (enough(512, 128)) return WIDE_TALL;
+    return enough(128, 128) ? WIDE_SMALL : WIDE_TINY;
 }
 
 // Whether the matrix-core kernel takes a call, or the streaming kernel.  The streaming kernel reads large corpora at the
@@ -263,7 +269,7 @@ FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, size_t li
     if (pl.wide) {
         int shape = wide_shape(cus, N, B);
         wide_geometry(pl.w, shape, cus, N, B);
-        pl.w.gs_log = wide_group_log(pl.w.wmf, N, d, B, k);
+        pl.w.gs_log = wide_group_log(cus, pl.w.wmf, N, d, B, k);
         pl.w.n = pl.w.slots >> pl.w.gs_log;
         const size_t per = (size_t)pl.w.n * sizeof(float);
         if (per * (size_t)B > limit) {

@@ -137,7 +137,7 @@ __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NW
                                                                int K, int lds_steps, After after) {
     extern __shared__ __align__(16) unsigned char smem[];
     u4 *qf = reinterpret_cast<u4 *>(smem);            // [NQG][lds_steps][64]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rb = sh.d * T::bytes;                   // bytes of a row
     const int steps = (rb + 63) >> 6;
     const int B = sh.B;

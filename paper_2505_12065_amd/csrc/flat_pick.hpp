@@ -15,7 +15,7 @@ __device__ __forceinline__ int64_t wide_row(int64_t slot) {
     return (slot & ~(int64_t)(64 * WMF - 1)) + wm * 32 * WMF + i * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
 }
 
-// One workgroup (1, 2 or 4 wavefronts) per query.
+// One workgroup (1 to 8 wavefronts) per query.
 //   1. every thread takes the largest of the maxima it looks at; the k-th largest of those is a bound that few maxima
 //      reach (two sorting networks);
 //   2. those few are gathered in LDS and ranked by counting: the groups with fewer than k larger ones hold the k best
@@ -28,12 +28,12 @@ __device__ __forceinline__ int64_t wide_row(int64_t slot) {
 // bytes of the rows.
 constexpr int PICK_CAP = 512;
 template <class T, int WMF, bool ONE>
-__global__ __launch_bounds__(256) void flat_pick_kernel(const float *__restrict__ maxima, int64_t n, int gs_log, int k,
+__global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict__ maxima, int64_t n, int gs_log, int k,
                                                         int32_t *__restrict__ ids, float *__restrict__ scores, StreamShape sh,
                                                         After after) {
     __shared__ uint64_t ck[PICK_CAP];                 // gathered maxima, then scored rows
     __shared__ int sel[PICK_CAP];                     // groups to score
-    __shared__ uint32_t top[64];
+    __shared__ uint32_t top[8 * 16];
     __shared__ uint64_t fin[16], old[16];             // the k best so far, in order
     __shared__ int n_c, n_sel;
     __shared__ uint32_t t_min;
@@ -72,9 +72,10 @@ __global__ __launch_bounds__(256) void flat_pick_kernel(const float *__restrict_
     m = group_sort_desc<64>(m);
     if (nwaves > 1) {
         if (lane < 16) top[wave * 16 + lane] = m;
-        else if (nwaves == 2 && lane < 32) top[16 + wave * 16 + lane] = 0;
         __syncthreads();
-        m = group_sort_desc<64>(top[lane]);           // (4 waves: 64 values)
+        m = 0;                                        // (of 8 waves: the larger ones of two lists, still k different maxima)
+        for (int w = lane >> 4; w < nwaves; w += 4) m = max(m, top[w * 16 + (lane & 15)]);
+        m = group_sort_desc<64>(m);
     } else {
         __syncthreads();                              // the shared words are set
     }

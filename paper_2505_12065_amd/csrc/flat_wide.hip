@@ -30,9 +30,11 @@ template <class T>
 hipError_t pick(const WidePlan &pl, const void *X, int64_t N, int d, const void *Q, int B, int k, const float *maxima,
                 int32_t *ids, float *scores, After after, hipStream_t stream) {
     const StreamShape sh{X, Q, N, d, B};
-    // a wave for one-row groups of a small corpus; else a wave per 32 rows to score, two at least
+    // a wave for one-row groups of a small corpus; else a wave per 32 rows to score and per 4096 maxima, two at least;
+    // eight only where every query has a compute unit to itself
     const bool one = pl.gs_log == 0;
-    const int threads = one && pl.n <= 2048 ? 64 : !one && (k << pl.gs_log) <= 64 && pl.n <= 8192 ? 128 : 256;
+    const bool little = (k << pl.gs_log) <= 64 && pl.n <= 8192, much = (k << pl.gs_log) > 128 || pl.n > 8192;
+    const int threads = one && pl.n <= 2048 ? 64 : !one && little ? 128 : much && B <= pl.cus ? 512 : 256;
     const size_t lds = one ? 0 : (size_t)d * 2;
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(B), dim3(threads), lds, stream, maxima, pl.n, pl.gs_log, k, ids, scores, sh, after);
@@ -44,6 +46,7 @@ hipError_t pick(const WidePlan &pl, const void *X, int64_t N, int d, const void 
 template <class C>
 void geometry(WidePlan &pl, int cus, int64_t N, int B) {
     const int64_t tiles = (N + C::BM - 1) / C::BM;
+    pl.cus = cus;
     pl.wmf = C::WMF;
     pl.NT = (B + C::BN - 1) / C::BN;
     const int64_t cap = (int64_t)cus * C::PER_CU / pl.NT;

@@ -1,7 +1,7 @@
 // Exact (flat) retrieval on the matrix cores (Section 2.1 of the paper: exact retrieval; the batch stands for the
 // agent's concurrent requests).  The score matrix S = X Q^T is a dense contraction:
 //
-//   workgroup tile  64 WMF corpus rows x 32 WNF NWN queries, 2 x NWN wavefronts
+//   workgroup tile  32 WMF NWM corpus rows x 32 WNF NWN queries, NWM x NWN wavefronts
 //   wavefront tile  32 WMF rows x 32 WNF queries = WMF x WNF MFMA 32x32x16 accumulators
 //   K loop          32 columns of d (64 bytes of a row) per stage, 3 or 4 LDS stages; every stage is filled by direct
 //                   global->LDS loads issued two or three stages ahead.  One load instruction brings 16 rows x
@@ -25,21 +25,21 @@
 
 namespace ann {
 
-template <int WMF_, int WNF_, int NWN_, int STAGES_, int PER_CU_>
+template <int WMF_, int WNF_, int NWM_, int NWN_, int STAGES_, int PER_CU_>
 struct WideCfg {
-    static constexpr int WMF = WMF_, WNF = WNF_, NWN = NWN_, STAGES = STAGES_, PER_CU = PER_CU_;
-    static constexpr int WAVES = 2 * NWN, THREADS = WAVES * WAVE;
-    static constexpr int BM = 64 * WMF, BN = 32 * WNF * NWN;
+    static constexpr int WMF = WMF_, WNF = WNF_, NWM = NWM_, NWN = NWN_, STAGES = STAGES_, PER_CU = PER_CU_;
+    static constexpr int WAVES = NWM * NWN, THREADS = WAVES * WAVE;
+    static constexpr int BM = 32 * WMF * NWM, BN = 32 * WNF * NWN;
     static constexpr int A_BLK = BM / 16, BLKS = A_BLK + BN / 16;       // 1 KB blocks of a stage: 16 rows x 64 B each
     static constexpr int LPW = BLKS / WAVES;                            // blocks loaded per wave and stage
     static_assert(BLKS % WAVES == 0, "blocks must divide evenly over the waves");
     static constexpr int STAGE_BYTES = BLKS * 1024, LDS_BYTES = STAGES * STAGE_BYTES;
 };
-using WideLarge = WideCfg<4, 2, 4, 4, 1>;                 // 256 x 256, 8 waves
-using WideTall = WideCfg<4, 2, 2, 3, 2>;                  // 256 x 128, 4 waves, two workgroups per compute unit
-using WideSmall = WideCfg<2, 2, 2, 3, 3>;                 // 128 x 128, 4 waves, three
-using WideThin = WideCfg<2, 1, 2, 4, 3>;                  // 128 x 64, 4 waves, three
-using WideTiny = WideCfg<1, 1, 2, 6, 3>;                  // 64 x 64, 4 waves, three
+using WideLarge = WideCfg<4, 2, 2, 4, 4, 1>;              // 256 x 256, 8 waves
+using WideTall = WideCfg<4, 2, 4, 2, 4, 1>;               // 512 x 128, 8 waves
+using WideSmall = WideCfg<2, 2, 2, 2, 3, 3>;              // 128 x 128, 4 waves, three workgroups per compute unit
+using WideThin = WideCfg<2, 1, 2, 2, 4, 3>;               // 128 x 64, 4 waves, three
+using WideTiny = WideCfg<1, 1, 2, 2, 6, 3>;               // 64 x 64, 4 waves, three
 
 #define ANN_GLOBAL_TO_LDS_16(gptr, lptr)                                                          \
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gptr),      \
@@ -71,8 +71,8 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
     constexpr int WMF = C::WMF, WNF = C::WNF, NST = C::STAGES, LPW = C::LPW, BM = C::BM;
     extern __shared__ __align__(16) unsigned char stage_mem[];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave & 1, wn = wave >> 1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % C::NWM, wn = wave / C::NWM;
     const int l32 = lane & 31, lhi = lane >> 5;
     const int rb = d * 2, ksteps = (rb + 63) >> 6;
 
@@ -192,6 +192,9 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
         stage(std::true_type{});
         for (int ks = 1; ks < ksteps; ++ks) stage(std::false_type{});
 
+        int ln = lane;
+        asm volatile("" : "+v"(ln));                      // (nothing of the epilogue is worth a register in the loop above)
+        const int l32 = ln & 31, lhi = ln >> 5;
         const int rbase = (int)(tile * BM) + wm * 32 * WMF + 4 * lhi;     // N < 2^31
         const int nrows = (int)N;
         if ((tile + 1) * BM > N) {

@@ -47,7 +47,7 @@ hipError_t launch_flat_stream_f32(const StreamPlan &pl, const void *X, int64_t N
 // Large batches on the matrix cores (16-bit corpora).
 constexpr int WIDE_LARGE = 0, WIDE_TALL = 1, WIDE_SMALL = 2, WIDE_THIN = 3, WIDE_TINY = 4;
 struct WidePlan {
-    int shape, wmf;              // workgroup tile (a WideCfg); its row fragments per wave
+    int cus, shape, wmf;         // compute units; workgroup tile (a WideCfg); its row fragments per wave
     int NT, P;                   // query tiles x slabs of the corpus
     int gs_log;                  // a maximum stands for 2^gs_log rows
     int64_t slots, n;            // rows of whole tiles; groups they make
