@@ -175,8 +175,9 @@ int check_common(const void *corpus, int64_t N, int32_t d, int32_t dtype, const 
 
 // ---- flat: launch geometry ---------------------------------------------------------------
 struct FlatPlan {
-    StreamPlan st;           // streaming kernel, unless
-    bool wide;               // the matrix-core kernel takes the call, `part` queries at a time
+    StreamPlan st;           // streaming kernel with lists, unless
+    bool wide;               // the matrix-core kernel, or
+    bool maxima;             // the streaming kernel with group maxima takes the call, `part` queries at a time
     WidePlan w;
     int part;
     size_t ws_bytes;
@@ -187,9 +188,10 @@ constexpr int WIDE_MIN_B = 65;   // smallest batch sent to the matrix-core path
 constexpr size_t WIDE_WS_MAX = (size_t)1 << 30;
 
 // The streaming kernel's geometry.
-StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int k) {
+// K: see the kernel; unit: rows that go to a wave together.
+StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int K, int unit) {
     StreamPlan pl;
-    pl.K = (k + 3) & ~3;
+    pl.K = K;
     const int steps = (d * elem_bytes(dtype) + 63) / 64;
     const int fit = (int)((LDS_MAX - 16 * 1024) / (WAVE * 16));        // steps of one group of 16 queries that fit LDS
     const int n16 = (B + 15) / 16;
@@ -199,7 +201,7 @@ StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int k) {
     pl.lds_steps = steps < fit ? steps : fit;
     // as many queries per workgroup as possible read the corpus least often; fewer when the tiles of 16 rows would not
     // give every compute unit a workgroup of 8 waves
-    const int64_t tiles = (N + 15) / 16;
+    const int64_t tiles = (N + unit - 1) / unit;
     while (nqg > 1 && tiles * ((n16 + nqg - 1) / nqg) < (int64_t)cus * 8) --nqg;
     pl.G = (n16 + nqg - 1) / nqg;
     pl.nqg = (n16 + pl.G - 1) / pl.G;
@@ -220,15 +222,15 @@ StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int k) {
 // Rows per group of the matrix-core kernel, by the time of what follows the products, in us: the maxima are written and
 // read once and the rows of k groups are read again, at some 4 TB/s over all queries; one query alone waits for its
 // maxima (twice, 1024 a wave at a time) and, unless groups are single rows, for its rows (32 a wave, 192 columns at once).
-int wide_group_log(int cus, int wmf, int64_t N, int d, int B, int k) {
+int wide_group_log(int cus, int wmf, int64_t N, int row_bytes, int B, int k) {
     const int waves = B <= cus ? 8 : 4;                   // of a query
     int best = 0;
     double least = INFINITY;
     for (int g : {0, 2, 4, 5, 6}) {
-        if ((1 << g) > 16 * wmf) break;
+        if (wmf == 0 ? g < 4 : (1 << g) > 16 * wmf) continue;
         const double n = (double)N / (1 << g), rows = (double)k * (1 << g);
         double us = 8.0 * n * B / 4e6 + 1.6 * n / (1024 * waves);
-        if (g > 0) us += rows * d * 2 * B / 4e6 + 3.0 + 1.2 * ceil(rows / (32 * waves)) * ceil(d / 192.0);
+        if (g > 0) us += rows * row_bytes * B / 4e6 + 3.0 + 1.2 * ceil(rows / (32 * waves)) * ceil(row_bytes / 384.0);
         if (us < least) { least = us; best = g; }
     }
     return best;
@@ -261,15 +263,38 @@ bool use_wide(int64_t N, int d, int dtype, int B, int k) {
     return B * (N <= 128 * 1024 ? 16 : N <= 512 * 1024 ? 8 : d <= 128 ? 4 : 0) >= d;
 }
 
+// fp32 keeps lists for up to 16 queries (HBM-bound on large corpora) and wherever picking costs more than the lists: the rows
+// of k groups (10 k d rows of scoring they are worth) and the launch-bound sizes.  Lists / maxima, us: 250 k x 64, B = 1000
+// 787 / 453; 1 M x 196, B = 100 818 / 666; 64 k x 384, B = 300 194 / 185; 16 k x 384, B = 1000, k = 16 164 / 208.
+bool use_f32_maxima(int64_t N, int d, int B, int k) {
+    return B > 16 && N >= (int64_t)10 * k * d && N * B >= (int64_t)32768 * d;
+}
+
 FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, size_t limit) {
     FlatPlan pl{};
-    pl.st = stream_plan(cus, N, d, dtype, B, k);
+    pl.st = stream_plan(cus, N, d, dtype, B, (k + 3) & ~3, 16);
     pl.part = B;
+    if (dtype == ANN_F32 && use_f32_maxima(N, d, B, k)) {
+        pl.w.cus = cus;
+        pl.w.gs_log = wide_group_log(cus, 0, N, d * 4, B, k);
+        auto groups = [&] { return (((N - 1) >> pl.w.gs_log) + 1 + 3) & ~(int64_t)3; };
+        if ((size_t)groups() * sizeof(float) * (size_t)B > limit) pl.w.gs_log = 6;
+        pl.w.n = groups();
+        const size_t fit = limit / ((size_t)pl.w.n * sizeof(float));
+        if (fit >= 1) {
+            pl.maxima = true;
+            const int64_t parts = (B + (int64_t)fit - 1) / (int64_t)fit;
+            pl.part = (int)((B + parts - 1) / parts);
+            pl.st = stream_plan(cus, N, d, dtype, pl.part, 1 << (pl.w.gs_log - 4), 1 << pl.w.gs_log);
+            pl.ws_bytes = (size_t)pl.part * (size_t)pl.w.n * sizeof(float);
+            return pl;
+        }
+    }
     pl.wide = use_wide(N, d, dtype, B, k);
     if (pl.wide) {
         int shape = wide_shape(cus, N, B);
         wide_geometry(pl.w, shape, cus, N, B);
-        pl.w.gs_log = wide_group_log(cus, pl.w.wmf, N, d, B, k);
+        pl.w.gs_log = wide_group_log(cus, pl.w.wmf, N, d * 2, B, k);
         pl.w.n = pl.w.slots >> pl.w.gs_log;
         const size_t per = (size_t)pl.w.n * sizeof(float);
         if (per * (size_t)B > limit) {
@@ -296,18 +321,23 @@ int flat_search_run(const FlatPlan &pl, const void *X, int64_t N, int d, int dty
     // (launches are recorded by what the caller asked for: fp32, or the batch class whose kernel this is or stands in for)
     const int code = dtype == ANN_F32 ? ANN_KERNEL_FLAT_F32
                      : B >= WIDE_MIN_B && d % 32 == 0 ? ANN_KERNEL_FLAT_WIDE : ANN_KERNEL_FLAT_STREAM;
-    if (pl.wide) {
+    auto stream_kernel = [&](const void *q, int b, Cand *partial, float *maxima, After a) {
+        return (dtype == ANN_F16 ? launch_flat_stream_f16 : dtype == ANN_BF16 ? launch_flat_stream_bf16 : launch_flat_stream_f32)(
+            pl.st, X, N, d, q, b, partial, maxima, pl.w.n, a, stream);
+    };
+    if (pl.wide || pl.maxima) {
         float *maxima = static_cast<float *>(ws);
         for (int q0 = 0; q0 < B; q0 += pl.part) {
             const int b = B - q0 < pl.part ? B - q0 : pl.part;
-            const void *q = static_cast<const char *>(Q) + (size_t)q0 * d * 2;
+            const void *q = static_cast<const char *>(Q) + (size_t)q0 * d * elem_bytes(dtype);
             const After a{after.s ? after.s + q0 : nullptr, after.id ? after.id + q0 : nullptr};
             hipError_t e;
             {
                 TimedScope timed(q0 == 0 ? code : -1, stream);
-                e = launch_flat_wide(pl.w, dtype, X, N, d, q, b, maxima, a, stream);
+                e = pl.wide ? launch_flat_wide(pl.w, dtype, X, N, d, q, b, maxima, a, stream)
+                            : stream_kernel(q, b, nullptr, maxima, a);
             }
-            if (int rc = check_launch("flat_wide_kernel", e)) return rc;
+            if (int rc = check_launch(pl.wide ? "flat_wide_kernel" : "flat_stream_kernel", e)) return rc;
             e = launch_flat_pick(pl.w, dtype, X, N, d, q, b, k, maxima, ids + (size_t)q0 * k, scores + (size_t)q0 * k, a, stream);
             if (int rc = check_launch("flat_pick_kernel", e)) return rc;
         }
@@ -317,8 +347,7 @@ int flat_search_run(const FlatPlan &pl, const void *X, int64_t N, int d, int dty
     hipError_t e;
     {
         TimedScope timed(code, stream);
-        e = (dtype == ANN_F16 ? launch_flat_stream_f16 : dtype == ANN_BF16 ? launch_flat_stream_bf16 : launch_flat_stream_f32)(
-            pl.st, X, N, d, Q, B, partial, after, stream);
+        e = stream_kernel(Q, B, partial, nullptr, after);
     }
     if (int rc = check_launch("flat_stream_kernel", e)) return rc;
     if (k > 4)

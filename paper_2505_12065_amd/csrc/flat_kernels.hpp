@@ -122,6 +122,8 @@ __device__ __forceinline__ u4 mask_tail(u4 x, bool inside) {
 //   partial [B, P, K] pairs, K = 4, 8, 12 or 16 (>= k), every list sorted, empty slots (-inf, EMPTY_ID) last.
 //   lds_steps: steps of a query that fit LDS (fewer than all of them only for fp32 rows beyond 2304 columns, where
 //         one group of queries alone is larger than LDS: the rest comes from memory, NQG = 1, not FULL).
+//   MAX: no lists; maxima[q, u] <- the largest score of rows [16 K u, 16 K (u + 1)) for flat_pick_kernel, n of them a
+//         query (a multiple of 4), K = 1, 2 or 4 tiles to a group.
 // Lists of 4 are exact for k <= 4.  For k > 4 a lane may meet more than 4 of the k best rows; the merge then finds 4
 // rows of one lane among the k best and goes over that lane's rows again (flat_merge_lists_kernel).
 //
@@ -132,9 +134,9 @@ __device__ __forceinline__ u4 mask_tail(u4 x, bool inside) {
 // cores, at most 32 queries to a workgroup (more do not raise the rate: eight products of 32 clocks per 1 KB of rows).
 // Registers: two workgroups of 8 waves (or one of 16) per compute unit, except fp32 with two groups of queries (128
 // registers of accumulators), which runs one workgroup and is bound by the products.
-template <class T, int NQG, bool FULL, int NWV>
+template <class T, int NQG, bool FULL, int NWV, bool MAX>
 __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NWV / 4) void flat_stream_kernel(StreamShape sh, Cand *__restrict__ partial, int P, int G,
-                                                               int K, int lds_steps, After after) {
+                                                               int K, int lds_steps, After after, float *__restrict__ maxima, int64_t n) {
     extern __shared__ __align__(16) unsigned char smem[];
     u4 *qf = reinterpret_cast<u4 *>(smem);            // [NQG][lds_steps][64]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -145,9 +147,12 @@ __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NW
     const int lb = xcd_block();
     const int slab = lb / G, q0 = (lb % G) * (NQG * 16);
     // the rows this wave starts with are requested before the queries are put into LDS
-    const int64_t ntiles = (N + 15) >> 4, tstride = (int64_t)P * NWV;
+    // a wave takes one tile after the other a grid stride apart, or (MAX) K tiles side by side and then a stride
+    const int64_t ntiles = (N + 15) >> 4, tstride = (int64_t)P * NWV * (MAX ? K : 1);
+    const int run = MAX ? K : 1;
+    auto next = [&](int64_t t) { return !MAX || (t & (run - 1)) == run - 1 ? t + tstride - (run - 1) : t + 1; };
     const int kofs = (lane >> 4) * 16;                // this lane's byte offset inside a step
-    int64_t tile = (int64_t)slab * NWV + wave;
+    int64_t tile = ((int64_t)slab * NWV + wave) * run;
     const char *rp = nullptr;                         // this lane's row of the tile being loaded, kofs included
     auto row_ptr = [&](int64_t t) {
         int64_t row = t * 16 + tile_row(lane & 15);
@@ -166,7 +171,7 @@ __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NW
         lstep += STREAM_BATCH;
         if (lstep >= steps) {
             lstep = 0;
-            ltile += tstride;
+            ltile = next(ltile);
             if (ltile < ntiles) row_ptr(ltile);       // (past the end: the last tile once more, never used)
         }
     };
@@ -194,12 +199,12 @@ __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NW
         }
     }
 
-    TopList<LANE_KP> best[NQG];
-    float thr[NQG];
+    TopList<LANE_KP> best[MAX ? 1 : NQG];
+    float thr[NQG];                                   // (MAX: the largest score of the group of rows)
 #pragma unroll
     for (int g = 0; g < NQG; ++g) {
-        best[g].init();
-        thr[g] = -INFINITY;
+        if constexpr (!MAX) best[g].init();
+        thr[g] = MAX ? __builtin_nanf("") : -INFINITY;
     }
     TileSum<T> part[NQG];
     auto clear = [&] {
@@ -254,7 +259,34 @@ __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NW
                 for (int i = 0; i < 4; ++i) acc[g][i] = after_boundary(acc[g][i], rbase + 4 * i, bs, bid);
             }
         }
-        static_for<NQG>([&](auto gc) {
+        if constexpr (MAX) {
+            if (tile * 16 + 16 > N) {                 // rows that do not exist
+#pragma unroll
+                for (int g = 0; g < NQG; ++g)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[g][i] = rbase + 4 * i < nrows ? acc[g][i] : __builtin_nanf("");
+            }
+            const bool last = (tile & (run - 1)) == run - 1 || tile + 1 == ntiles;
+#pragma unroll
+            for (int g = 0; g < NQG; ++g) {
+                thr[g] = fmaxf(thr[g], fmaxf(fmaxf(acc[g][0], acc[g][1]), fmaxf(acc[g][2], acc[g][3])));
+                if (last) {
+                    uint32_t p, q;
+                    row_pair<16>(__float_as_uint(thr[g]), p, q);
+                    float m = fmaxf(__uint_as_float(p), __uint_as_float(q));
+                    row_pair<32>(__float_as_uint(m), p, q);
+                    m = fmaxf(__uint_as_float(p), __uint_as_float(q));
+                    thr[g] = __builtin_nanf("");
+                    const int qi = q0 + g * 16 + lane;
+                    if (lane < 16 && qi < B) {
+                        float *o = maxima + (size_t)qi * n + tile / run;
+                        o[0] = m;
+                        if (tile + 1 == ntiles)       // the row of maxima is filled up to a multiple of 4
+                            for (int64_t e = tile / run + 1; e < n; ++e) maxima[(size_t)qi * n + e] = __builtin_nanf("");
+                    }
+                }
+            }
+        } else static_for<NQG>([&](auto gc) {
             constexpr int g = decltype(gc)::value;
             const f4 a = acc[g];
             const float m = fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]));
@@ -276,7 +308,7 @@ __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NW
             }
         });
         clear();
-        tile += tstride;
+        tile = next(tile);
     };
     if (tile < ntiles) {
         for (;;) {
@@ -295,12 +327,13 @@ __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NW
         }
     }
 
+    if constexpr (MAX) return;
     // every lane's lists -> LDS, then 16 queries at a time: the 4 NWV lists of a query by 4 NWV lanes
     constexpr int LG = 4 * NWV, QS = LG * LANE_KP + 4;                   // (padded: the writes of 16 queries spread over the banks)
     static_assert(NWV == 8 || NWV == 16, "a query's lists fill half a wave or a whole one");
     Cand *wl = reinterpret_cast<Cand *>(smem);
     __syncthreads();                                   // query fragments are dead from here
-    static_for<NQG>([&](auto gc) {
+    if constexpr (!MAX) static_for<NQG>([&](auto gc) {
         constexpr int g = decltype(gc)::value;
         Cand *o = wl + (g * 16 + (lane & 15)) * QS + (wave * 4 + (lane >> 4)) * LANE_KP;
 #pragma unroll

@@ -8,11 +8,14 @@ namespace ann {
 
 // Corpus row of place `slot` in the order of flat_wide_kernel's lanes: tile, wave row, lane half, accumulator.  The groups
 // are runs of 2^gs_log places, and a group's first place is its lowest row.
+// WMF = 0: the order of flat_stream_kernel's maxima, rows as they come.
 template <int WMF>
 __device__ __forceinline__ int64_t wide_row(int64_t slot) {
-    const int s = (int)(slot & (64 * WMF - 1));
-    const int wm = s / (32 * WMF), lhi = s / (16 * WMF) & 1, i = s / 16 & (WMF - 1), r = s & 15;
-    return (slot & ~(int64_t)(64 * WMF - 1)) + wm * 32 * WMF + i * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
+    if constexpr (WMF == 0) return slot;
+    constexpr int W = WMF == 0 ? 1 : WMF;
+    const int s = (int)(slot & (64 * W - 1));
+    const int wm = s / (32 * W), lhi = s / (16 * W) & 1, i = s / 16 & (W - 1), r = s & 15;
+    return (slot & ~(int64_t)(64 * W - 1)) + wm * 32 * W + i * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
 }
 
 // One workgroup (1 to 8 wavefronts) per query.
@@ -20,8 +23,9 @@ __device__ __forceinline__ int64_t wide_row(int64_t slot) {
 //      reach (two sorting networks);
 //   2. those few are gathered in LDS and ranked by counting: the groups with fewer than k larger ones hold the k best
 //      rows, and the k-th best group maximum T is a lower bound of the k-th best score;
-//   3. their rows are scored once more, by the instructions and in the order of flat_wide_kernel, so to the same bits: 32
-//      rows to an MFMA, the query as every one of its columns; the rows that reach T (k, if none tie) are ranked.
+//   3. their rows are scored once more, by the instructions and in the order of the kernel that left the maxima, so to the
+//      same bits: 32 (fp32: 16) rows to an MFMA, the query as every one of its columns; the rows that reach T (k, if none
+//      tie) are ranked.
 // Groups of one row: their maxima are the scores, step 3 falls away.  Hundreds of maxima that tie with the k-th: the groups
 // are gone through in order, a few at a time, past those that can no longer improve the k best so far.
 // Bound by the latency of three dependent reads (maxima twice, rows) at 8 to 12 us, and beyond about 1000 queries by the
@@ -41,7 +45,6 @@ __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict_
     u4 *qs = reinterpret_cast<u4 *>(smem);            // the query (groups of more than one row)
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int NT = blockDim.x, nwaves = NT >> 6;
-    const int l32 = lane & 31, lhi = lane >> 5;
     const uint64_t empty = order_key(-INFINITY, EMPTY_ID);
     const float *mx = maxima + (size_t)q * n;
     const int rb = sh.d * T::bytes, nch = rb >> 4;
@@ -116,7 +119,6 @@ __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict_
     };
     // the rows of groups sel[0 .. ns) scored and merged, PICK_CAP at a time; t: image that a row has to reach
     auto score_groups = [&](int ns, uint32_t t) {
-        const int steps = (rb + 31) >> 5;
         const int64_t rows = (int64_t)ns << gs_log;
         auto row_of = [&](int64_t e) {
             e = e < rows ? e : rows - 1;
@@ -126,37 +128,57 @@ __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict_
             if (tid == 0) n_c = 0;
             __syncthreads();
             const uint64_t worst = fin[k - 1];
-            for (int u = wave; u < PICK_CAP / 32 && b0 + u * 32 < rows; u += nwaves) {
-                const int64_t e0 = b0 + u * 32;
-                int64_t row = row_of(e0 + l32);
+            constexpr int UNIT = T::bytes == 4 ? 16 : 32;                 // rows to an MFMA
+            for (int u = wave; u < PICK_CAP / UNIT && b0 + u * UNIT < rows; u += nwaves) {
+                const int64_t e0 = b0 + u * UNIT;
+                int64_t row = row_of(e0 + (lane & (UNIT - 1)));
                 row = row < sh.N ? row : sh.N - 1;
                 const char *rp = static_cast<const char *>(sh.X) + (size_t)row * rb;
-                f16v acc;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[r] = 0.f;
                 constexpr int RUN = 12;               // steps whose loads are in flight together
-                for (int s0 = 0; s0 < steps; s0 += RUN) {
-                    u4 x[RUN];
+                const int sub = lane / UNIT;          // this lane's chunk of a step
+                constexpr int CHUNKS = WAVE / UNIT;
+                const int steps = (nch + CHUNKS - 1) / CHUNKS;
+                // every column of the result holds the same sums: a lane's first columns look after one each
+                float v;
+                int col, at;                          // this lane's column, and which of the rows it looks after
+                auto run = [&](auto &&product) {
+                    for (int s0 = 0; s0 < steps; s0 += RUN) {
+                        u4 x[RUN];
 #pragma unroll
-                    for (int s = 0; s < RUN; ++s) {
-                        x[s] = zero_chunk();
-                        if (s0 + s < steps) x[s] = load_chunk(rp + min(2 * (s0 + s) + lhi, nch - 1) * 16);
-                    }
-#pragma unroll
-                    for (int s = 0; s < RUN; ++s)
-                        if (s0 + s < steps) {
-                            const int ch = 2 * (s0 + s) + lhi;
-                            acc = mfma32<T>(mask_tail(x[s], ch < nch), mask_tail(qs[min(ch, nch - 1)], ch < nch), acc);
+                        for (int s = 0; s < RUN; ++s) {
+                            x[s] = zero_chunk();
+                            if (s0 + s < steps) x[s] = load_chunk(rp + min(CHUNKS * (s0 + s) + sub, nch - 1) * 16);
                         }
-                }
-                // every column holds the same 32 sums: lane r < 16 of a half looks after its half's r-th
-                float v = acc[0];
 #pragma unroll
-                for (int r = 1; r < 16; ++r) v = l32 == r ? acc[r] : v;
-                const int64_t e = e0 + 8 * ((l32 & 15) >> 2) + 4 * lhi + (l32 & 3);
-                const int64_t id = row_of(e);
+                        for (int s = 0; s < RUN; ++s)
+                            if (s0 + s < steps) {
+                                const int ch = CHUNKS * (s0 + s) + sub;
+                                product(s, mask_tail(x[s], ch < nch), mask_tail(qs[min(ch, nch - 1)], ch < nch));
+                            }
+                    }
+                };
+                if constexpr (T::bytes == 4) {
+                    TileSum<T> part;
+                    part.clear();
+                    run([&](int s, u4 x, u4 y) { part.step(s, TileSum<T>::operand(x), TileSum<T>::operand(y)); });
+                    const f4 sum = part.sum();
+                    col = lane & 15;
+                    v = col == 1 ? sum[1] : col == 2 ? sum[2] : col == 3 ? sum[3] : sum[0];
+                    at = 4 * sub + (col & 3);
+                } else {
+                    f16v acc;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+                    run([&](int, u4 x, u4 y) { acc = mfma32<T>(x, y, acc); });
+                    col = lane & 31;
+                    v = acc[0];
+#pragma unroll
+                    for (int r = 1; r < 16; ++r) v = col == r ? acc[r] : v;
+                    at = 8 * ((col & 15) >> 2) + 4 * sub + (col & 3);
+                }
+                const int64_t e = e0 + at, id = row_of(e);
                 if (after.s) v = after_boundary(v, (int)id, after.s[q], after.id[q]);
-                if (l32 < 16 && e < rows && id < sh.N && v == v) {
+                if (col < UNIT / CHUNKS && e < rows && id < sh.N && v == v) {
                     const uint64_t key = order_key(v, (int)id);
                     if ((uint32_t)(key >> 32) >= t && key > worst) ck[atomicAdd(&n_c, 1)] = key;
                 }

@@ -38,12 +38,12 @@ struct StreamPlan {
     int slots() const { return P * waves; }
 };
 // partial[B, P, K]: every slab's best K per query.
-hipError_t launch_flat_stream_f16(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
-                                  After after, hipStream_t stream);
-hipError_t launch_flat_stream_bf16(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
-                                   After after, hipStream_t stream);
-hipError_t launch_flat_stream_f32(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
-                                  After after, hipStream_t stream);
+hipError_t launch_flat_stream_f16(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial, float *maxima,
+                                  int64_t n, After after, hipStream_t stream);
+hipError_t launch_flat_stream_bf16(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial, float *maxima,
+                                   int64_t n, After after, hipStream_t stream);
+hipError_t launch_flat_stream_f32(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial, float *maxima,
+                                  int64_t n, After after, hipStream_t stream);
 // Large batches on the matrix cores (16-bit corpora).
 constexpr int WIDE_LARGE = 0, WIDE_TALL = 1, WIDE_SMALL = 2, WIDE_THIN = 3, WIDE_TINY = 4;
 struct WidePlan {

@@ -158,9 +158,12 @@ def test_flat_continuation_pages(dtype, N, d, B, k):
     (torch.bfloat16, 4_097, 8, 1, 9),           # ... one query, the shortest row
     (torch.float16, 400_000, 8, 65, 1),         # groups of 64
     (torch.float16, 1_000_000, 32, 512, 3),     # ... in parts, through the static workspace
+    (torch.bfloat16, 400_000, 8, 513, 2),       # ... parts of 257 and 256 queries
+    (torch.float32, 70_001, 36, 40, 3),         # the streaming kernel with maxima, ragged tile
+    (torch.float32, 150_003, 64, 17, 9),        # ... whole steps, one query in the second group
 ])
 def test_flat_group_maxima(dtype, N, d, B, k):
-    """The matrix-core kernel at the edges of its tile shapes and group sizes: two pages against one oracle answer, with
+    """The kernels that leave group maxima, at the edges of their tile shapes and group sizes: two pages against one oracle answer, with
     scores that are not numbers among the rows; the static entry point gives the same."""
     say(f"flat group maxima: dtype={dtype} N={N} d={d} B={B} k={k}")
     c = synth.make_corpus(N, d, 8, seed=N % 83, dtype=dtype, zipf_a=None, sigma=0.4)
