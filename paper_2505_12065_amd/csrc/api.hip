@@ -176,6 +176,7 @@ int check_common(const void *corpus, int64_t N, int32_t d, int32_t dtype, const 
 // ---- flat: launch geometry ---------------------------------------------------------------
 struct FlatPlan {
     StreamPlan st;           // streaming kernel with lists, unless
+    bool direct;             // ... of one slab: no merge
     bool wide;               // the matrix-core kernel, or
     bool maxima;             // the streaming kernel with group maxima takes the call, `part` queries at a time
     WidePlan w;
@@ -290,6 +291,17 @@ FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, size_t li
             return pl;
         }
     }
+    // A corpus of one tile per wave of a workgroup: its lists are the answer, one launch instead of two (128 x 768 fp16, k = 1:
+    // B = 64 13.9 -> 10.8 us, B = 512 12.4 -> 11.1; 64 x 1024, B = 8192, k = 16 23.1 -> 17.3).  Lists of 4 per lane are complete
+    // there whatever k is, since a lane sees four rows; selecting k > 4 from all eight waves costs more than the launch
+    // saves where the other way is group maxima (128 x 1024 bf16, B = 5000, k = 16: 19.3 / 23.3).
+    pl.direct = N <= (k <= 4 || dtype == ANN_F32 ? 128 : 64);
+    if (pl.direct) {
+        pl.st = stream_plan(cus, N, d, dtype, B, (k + 3) & ~3, 16);
+        pl.st.P = 1;
+        pl.ws_bytes = 0;
+        return pl;
+    }
     pl.wide = use_wide(N, d, dtype, B, k);
     if (pl.wide) {
         int shape = wide_shape(cus, N, B);
@@ -321,9 +333,11 @@ int flat_search_run(const FlatPlan &pl, const void *X, int64_t N, int d, int dty
     // (launches are recorded by what the caller asked for: fp32, or the batch class whose kernel this is or stands in for)
     const int code = dtype == ANN_F32 ? ANN_KERNEL_FLAT_F32
                      : B >= WIDE_MIN_B && d % 32 == 0 ? ANN_KERNEL_FLAT_WIDE : ANN_KERNEL_FLAT_STREAM;
+    StreamOut direct;
+    if (pl.direct) direct = StreamOut{ids, scores, k};
     auto stream_kernel = [&](const void *q, int b, Cand *partial, float *maxima, After a) {
         return (dtype == ANN_F16 ? launch_flat_stream_f16 : dtype == ANN_BF16 ? launch_flat_stream_bf16 : launch_flat_stream_f32)(
-            pl.st, X, N, d, q, b, partial, maxima, pl.w.n, a, stream);
+            pl.st, X, N, d, q, b, partial, maxima, pl.w.n, direct, a, stream);
     };
     if (pl.wide || pl.maxima) {
         float *maxima = static_cast<float *>(ws);
@@ -350,6 +364,7 @@ int flat_search_run(const FlatPlan &pl, const void *X, int64_t N, int d, int dty
         e = stream_kernel(Q, B, partial, nullptr, after);
     }
     if (int rc = check_launch("flat_stream_kernel", e)) return rc;
+    if (pl.direct) return ANN_OK;
     if (k > 4)
         return check_launch("flat_merge_lists_kernel",
                             launch_flat_merge_lists(dtype, partial, pl.st.P, pl.st.K, pl.st.slots(), X, N, d, Q, B, k, ids,

@@ -24,22 +24,17 @@ constexpr int STREAM_BATCH = 4;                       // 16-byte loads per batch
 __device__ __forceinline__ int tile_row(int r) { return ((r & 3) << 2) | (r >> 2); }
 
 // The K best (a multiple of 4, at most 16) of the 4 LG... entries held by an aligned group of LG lanes (32 or 64),
-// LANE_KP sorted keys each (empty slots: the key of (-inf, EMPTY_ID)), written to out[0 .. K) in order by the group;
-// fewer than K entries: the rest is written empty.  `mem`: LDS scratch of 64 keys that belongs to the group alone
+// LANE_KP sorted keys each (empty slots: the key of (-inf, EMPTY_ID)): put(r, key) for r = 0 .. K - 1, once by some lane of
+// the group if `store`; fewer than K entries: the rest is empty.  `mem`: LDS scratch of 64 keys that belongs to the group alone
 // (only its own wave touches it: no barrier).
 //   K <= 4: four rounds of "largest head wins and is popped".
 //   K > 4:  rounds cost 40 instructions each, so instead the heads' scores are sorted across the lanes; the
 //           K-th is a bound that some 20 of the entries reach; those are ranked by counting.  (More than 64
 //           reach it only when many scores are equal: then rounds it is.)
-template <int LG>
-__device__ __forceinline__ void group_select(uint64_t (&key)[LANE_KP], int K, uint64_t *mem, Cand *out, bool store) {
+template <int LG, class Put>
+__device__ __forceinline__ void group_select(uint64_t (&key)[LANE_KP], int K, uint64_t *mem, Put &&put, bool store) {
     const int lane = threadIdx.x & (WAVE - 1), sub = lane & (LG - 1);
     const uint64_t empty = order_key(-INFINITY, EMPTY_ID);
-    auto put = [&](int r, uint64_t k64) {
-        Cand c;
-        order_key_decode(k64, c.s, c.id);
-        out[r] = c;
-    };
     bool rounds = K <= 4;
     if (!rounds) {
         const uint32_t sorted = group_sort_desc<LG>((uint32_t)(key[0] >> 32));
@@ -136,7 +131,8 @@ __device__ __forceinline__ u4 mask_tail(u4 x, bool inside) {
 // registers of accumulators), which runs one workgroup and is bound by the products.
 template <class T, int NQG, bool FULL, int NWV, bool MAX>
 __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NWV / 4) void flat_stream_kernel(StreamShape sh, Cand *__restrict__ partial, int P, int G,
-                                                               int K, int lds_steps, After after, float *__restrict__ maxima, int64_t n) {
+                                                               int K, int lds_steps, After after, float *__restrict__ maxima, int64_t n,
+                                                               StreamOut out) {
     extern __shared__ __align__(16) unsigned char smem[];
     u4 *qf = reinterpret_cast<u4 *>(smem);            // [NQG][lds_steps][64]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -351,7 +347,19 @@ __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NW
             const Cand c = in[sub * LANE_KP + j];
             key[j] = order_key(c.s, c.id);
         }
-        group_select<LG>(key, K, reinterpret_cast<uint64_t *>(in), partial + ((size_t)(q0 + qi) * P + slab) * K, q0 + qi < B);
+        const size_t q = q0 + qi;
+        auto put = [&](int r, uint64_t k64) {
+            Cand c;
+            order_key_decode(k64, c.s, c.id);
+            if (!out.ids) {
+                partial[(q * P + slab) * K + r] = c;
+            } else if (r < out.k) {                   // the only slab: this list is the answer
+                const bool has = c.id != EMPTY_ID;
+                out.ids[q * out.k + r] = has ? c.id : -1;
+                out.scores[q * out.k + r] = has ? c.s : -INFINITY;
+            }
+        };
+        group_select<LG>(key, K, reinterpret_cast<uint64_t *>(in), put, (int)q < B);
     }
 }
 

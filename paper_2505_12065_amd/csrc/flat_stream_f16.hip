@@ -4,8 +4,8 @@
 namespace ann {
 
 hipError_t launch_flat_stream_f16(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial, float *maxima, int64_t n,
-                                  After after, hipStream_t stream) {
-    return launch_stream_any<F16>(pl, X, N, d, Q, B, partial, maxima, n, after, stream);
+                                  StreamOut out, After after, hipStream_t stream) {
+    return launch_stream_any<F16>(pl, X, N, d, Q, B, partial, maxima, n, out, after, stream);
 }
 
 }  // namespace ann

@@ -37,13 +37,20 @@ struct StreamPlan {
     int K = 4;                   // entries of a slab's list: k rounded up to a multiple of 4
     int slots() const { return P * waves; }
 };
-// partial[B, P, K]: every slab's best K per query.
-hipError_t launch_flat_stream_f16(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial, float *maxima,
-                                  int64_t n, After after, hipStream_t stream);
-hipError_t launch_flat_stream_bf16(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial, float *maxima,
-                                   int64_t n, After after, hipStream_t stream);
-hipError_t launch_flat_stream_f32(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial, float *maxima,
-                                  int64_t n, After after, hipStream_t stream);
+// Where a single slab's lists go instead of to `partial`: the answer itself (ids null: they do not).
+struct StreamOut {
+    int32_t *ids = nullptr;
+    float *scores = nullptr;
+    int k = 0;
+};
+
+// partial[B, P, K]: every slab's best K per query; or maxima [B, n]: see the kernel; or, one slab only, `out`.
+hipError_t launch_flat_stream_f16(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
+                                  float *maxima, int64_t n, StreamOut out, After after, hipStream_t stream);
+hipError_t launch_flat_stream_bf16(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
+                                  float *maxima, int64_t n, StreamOut out, After after, hipStream_t stream);
+hipError_t launch_flat_stream_f32(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
+                                  float *maxima, int64_t n, StreamOut out, After after, hipStream_t stream);
 // Large batches on the matrix cores (16-bit corpora).
 constexpr int WIDE_LARGE = 0, WIDE_TALL = 1, WIDE_SMALL = 2, WIDE_THIN = 3, WIDE_TINY = 4;
 struct WidePlan {

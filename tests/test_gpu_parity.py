@@ -188,6 +188,27 @@ def test_flat_group_maxima(dtype, N, d, B, k):
     assert strict >= n - max(1, n // 20), (strict, n)
 
 
+@pytest.mark.parametrize("dtype,k", [(torch.float16, 4), (torch.float16, 5), (torch.bfloat16, 16), (torch.float32, 16), (torch.float32, 1)])
+@pytest.mark.parametrize("N", [16, 63, 64, 65, 127, 128, 129])
+def test_flat_corpus_of_one_workgroup(dtype, N, k):
+    """Around the sizes where one workgroup's lists are the answer: two pages, the second one running out where 2 k > N."""
+    say(f"flat one workgroup: dtype={dtype} N={N} k={k}")
+    c = synth.make_corpus(N, 96, 4, seed=N, dtype=dtype, zipf_a=None, sigma=0.3)
+    for B in (1, 75):
+        q = synth.make_queries(c, B)
+        xd, qd = c.x.to(DEV), q.to(DEV)
+        first = ann.ann_flat_search_typed(xd, qd, k)
+        second = ann.ann_flat_search_typed(xd, qd, k, after=(first[1][:, -1].contiguous(), first[0][:, -1].contiguous()))
+        torch.cuda.synchronize()
+        m = min(N, 2 * k)
+        ids, sc = torch.cat([first[0], second[0]], 1), torch.cat([first[1], second[1]], 1)
+        assert (ids[:, m:] == -1).all() and torch.isneginf(sc[:, m:]).all()
+        o_ids, _, o_sc64 = oracle.flat_search(to_np(c.x), to_np(q), m, dtype=np_dtype_name(c.x))
+        strict, tolerant, n = compare_topk(ids[:, :m].cpu().numpy(), sc[:, :m].cpu().numpy(), o_ids, o_sc64, to_np(c.x), to_np(q),
+                                           dtype=np_dtype_name(c.x))
+        assert strict >= n - max(1, n // 20), (B, strict, n)
+
+
 @pytest.mark.parametrize("dtype,B", [(torch.float16, 1), (torch.bfloat16, 37), (torch.float32, 20)])
 def test_flat_many_of_the_best_rows_in_one_lane(dtype, B):
     """k > 4: a lane of the streaming kernel keeps the 4 best of its rows, so rows a whole number of grid strides
