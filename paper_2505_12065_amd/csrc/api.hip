@@ -1,6 +1,6 @@
 // libann.so — host side of the C ABI declared in include/ann.h: argument checks,
-// launch geometry, the per-device workspace and the corpus registry.  All compute
-// runs in the kernels reached through launch.hpp.
+// the per-device workspace and the corpus registry.  What a call launches is decided
+// in plan.hpp; all compute runs in the kernels reached through launch.hpp.
 #include <hip/hip_runtime.h>
 
 #include <cstdarg>
@@ -29,8 +29,6 @@ int fail(int code, const char *fmt, ...) {
     g_last_error = buf;
     return code;
 }
-
-constexpr int P_MAX = 2048;
 
 }  // namespace
 
@@ -153,8 +151,6 @@ int check_launch(const char *what, hipError_t e) {
     return ANN_OK;
 }
 
-int elem_bytes(int dtype) { return dtype == ANN_F32 ? 4 : 2; }
-
 int check_common(const void *corpus, int64_t N, int32_t d, int32_t dtype, const void *queries, int32_t B,
                  int32_t k, const void *ids, const void *scores) {
     if (dtype != ANN_F16 && dtype != ANN_BF16 && dtype != ANN_F32)
@@ -171,161 +167,6 @@ int check_common(const void *corpus, int64_t N, int32_t d, int32_t dtype, const 
     if ((reinterpret_cast<uintptr_t>(ids) | reinterpret_cast<uintptr_t>(scores)) & 3)
         return fail(ANN_ERR_ALIGNMENT, "ids and scores must be 4-byte aligned");
     return ANN_OK;
-}
-
-// ---- flat: launch geometry ---------------------------------------------------------------
-struct FlatPlan {
-    StreamPlan st;           // streaming kernel with lists, unless
-    bool direct;             // ... of one slab: no merge
-    bool wide;               // the matrix-core kernel, or
-    bool maxima;             // the streaming kernel with group maxima takes the call, `part` queries at a time
-    WidePlan w;
-    int part;
-    size_t ws_bytes;
-};
-
-constexpr int WIDE_MIN_B = 65;   // smallest batch sent to the matrix-core path
-// Workspace that the group maxima of one launch may take; more queries run one part after the other.
-constexpr size_t WIDE_WS_MAX = (size_t)1 << 30;
-
-// The streaming kernel's geometry.
-// K: see the kernel; unit: rows that go to a wave together.
-StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int K, int unit) {
-    StreamPlan pl;
-    pl.K = K;
-    const int steps = (d * elem_bytes(dtype) + 63) / 64;
-    const int fit = (int)((LDS_MAX - 16 * 1024) / (WAVE * 16));        // steps of one group of 16 queries that fit LDS
-    const int n16 = (B + 15) / 16;
-    int nqg = fit / steps;
-    nqg = nqg < 1 ? 1 : nqg > STREAM_NQG_MAX(elem_bytes(dtype)) ? STREAM_NQG_MAX(elem_bytes(dtype)) : nqg;
-    nqg = nqg > n16 ? n16 : nqg;
-    pl.lds_steps = steps < fit ? steps : fit;
-    // as many queries per workgroup as possible read the corpus least often; fewer when the tiles of 16 rows would not
-    // give every compute unit a workgroup of 8 waves
-    const int64_t tiles = (N + unit - 1) / unit;
-    while (nqg > 1 && tiles * ((n16 + nqg - 1) / nqg) < (int64_t)cus * 8) --nqg;
-    pl.G = (n16 + nqg - 1) / nqg;
-    pl.nqg = (n16 + pl.G - 1) / pl.G;
-    pl.waves = stream_waves(elem_bytes(dtype), pl.nqg, pl.lds_steps);
-    int occ = (int)(LDS_MAX / stream_lds_bytes(pl.nqg, pl.lds_steps, pl.waves));
-    const int most = STREAM_WG_PER_CU(elem_bytes(dtype), pl.nqg, pl.waves);   // measured: more than 2 do not help
-    occ = occ < 1 ? 1 : (occ > most ? most : occ);
-    // every wave takes whole 16-row tiles in rounds; size the grid so that the last round
-    // is as full as the others instead of leaving most of the chip idle
-    int64_t cap = (int64_t)cus * occ / pl.G;
-    cap = cap < 1 ? 1 : (cap > P_MAX ? P_MAX : cap);
-    const int64_t rounds = (tiles + cap * pl.waves - 1) / (cap * pl.waves);
-    const int64_t P = (tiles + rounds * pl.waves - 1) / (rounds * pl.waves);
-    pl.P = (int)(P < cap ? P : cap);
-    return pl;
-}
-
-// Rows per group of the matrix-core kernel, by the time of what follows the products, in us: the maxima are written and
-// read once and the rows of k groups are read again, at some 4 TB/s over all queries; one query alone waits for its
-// maxima (twice, 1024 a wave at a time) and, unless groups are single rows, for its rows (32 a wave, 192 columns at once).
-int wide_group_log(int cus, int wmf, int64_t N, int row_bytes, int B, int k) {
-    const int waves = B <= cus ? 8 : 4;                   // of a query
-    int best = 0;
-    double least = INFINITY;
-    for (int g : {0, 2, 4, 5, 6}) {
-        if (wmf == 0 ? g < 4 : (1 << g) > 16 * wmf) continue;
-        const double n = (double)N / (1 << g), rows = (double)k * (1 << g);
-        double us = 8.0 * n * B / 4e6 + 1.6 * n / (1024 * waves);
-        if (g > 0) us += rows * row_bytes * B / 4e6 + 3.0 + 1.2 * ceil(rows / (32 * waves)) * ceil(row_bytes / 384.0);
-        if (us < least) { least = us; best = g; }
-    }
-    return best;
-}
-
-// The tile of the matrix-core kernel: the largest of which there are enough for the chip (larger tiles move fewer bytes per
-// product: 300 k x 768, B = 256: 162 us with 256 x 256, 187 with 512 x 128, 220 with 128 x 128; 30 k x 768, B = 256, 118
-// large tiles: 36, 39, 32; 50 k, 196 tiles: 40, 42, 52).  Queries are padded to whole tiles; the 512 x 128 tile runs at
-// 12/13 of the rate of the other large one, so it takes over where it saves more than that (1 M x 768, B = 300: 822 -> 745).
-int wide_shape(int cus, int64_t N, int B) {
-    auto enough = [&](int bm, int bn) { return 8 * ((N + bm - 1) / bm) * ((B + bn - 1) / bn) >= 5 * (int64_t)cus; };
-    if (B <= 64) return ((N + 127) / 128) >= cus ? WIDE_THIN : WIDE_TINY;
-    const int64_t cols256 = (B + 255) / 256 * 256, cols128 = (B + 127) / 128 * 128;
-    if (enough(256, 256) && 12 * cols256 <= 13 * cols128) return WIDE_LARGE;
-    if (enough(512, 128)) return WIDE_TALL;
-    return enough(128, 128) ? WIDE_SMALL : WIDE_TINY;
-}
-
-// Whether the matrix-core kernel takes a call, or the streaming kernel.  The streaming kernel reads large corpora at the
-// rate of HBM for up to 64 queries (1 M x 768, B = 64: 290 us against 380), but its lists cost every group of 16 queries
-// some 400 clocks a tile of 16 rows, whatever d is, which shows where rows are short or the corpus is in the caches
-// (streaming / matrix-core, us: 1 M x 64, B = 16 44 / 41, B = 64 106 / 46; 250 k x 256, B = 32 34 / 34, B = 64 45 / 35; 64 k x
-// 768, B = 32 30 / 32, B = 64 37 / 32).  Very small corpora are all latency: one-row maxima and one pass over them are as
-// fast as short lists and faster than long ones (4000 x 256, k = 16: 13 / 11).
-bool use_wide(int64_t N, int d, int dtype, int B, int k) {
-    if (dtype == ANN_F32) return false;
-    if (B >= WIDE_MIN_B) return true;
-    if (N <= 6000) return k > 4;
-    if (N <= 32 * 1024) return B > 32;
-    return B * (N <= 128 * 1024 ? 16 : N <= 512 * 1024 ? 8 : d <= 128 ? 4 : 0) >= d;
-}
-
-// fp32 keeps lists for up to 16 queries (HBM-bound on large corpora) and wherever picking costs more than the lists: the rows
-// of k groups (10 k d rows of scoring they are worth) and the launch-bound sizes.  Lists / maxima, us: 250 k x 64, B = 1000
-// 787 / 453; 1 M x 196, B = 100 818 / 666; 64 k x 384, B = 300 194 / 185; 16 k x 384, B = 1000, k = 16 164 / 208.
-bool use_f32_maxima(int64_t N, int d, int B, int k) {
-    return B > 16 && N >= (int64_t)10 * k * d && N * B >= (int64_t)32768 * d;
-}
-
-FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, size_t limit) {
-    FlatPlan pl{};
-    pl.st = stream_plan(cus, N, d, dtype, B, (k + 3) & ~3, 16);
-    pl.part = B;
-    if (dtype == ANN_F32 && use_f32_maxima(N, d, B, k)) {
-        pl.w.cus = cus;
-        pl.w.gs_log = wide_group_log(cus, 0, N, d * 4, B, k);
-        auto groups = [&] { return (((N - 1) >> pl.w.gs_log) + 1 + 3) & ~(int64_t)3; };
-        if ((size_t)groups() * sizeof(float) * (size_t)B > limit) pl.w.gs_log = 6;
-        pl.w.n = groups();
-        const size_t fit = limit / ((size_t)pl.w.n * sizeof(float));
-        if (fit >= 1) {
-            pl.maxima = true;
-            const int64_t parts = (B + (int64_t)fit - 1) / (int64_t)fit;
-            pl.part = (int)((B + parts - 1) / parts);
-            pl.st = stream_plan(cus, N, d, dtype, pl.part, 1 << (pl.w.gs_log - 4), 1 << pl.w.gs_log);
-            pl.ws_bytes = (size_t)pl.part * (size_t)pl.w.n * sizeof(float);
-            return pl;
-        }
-    }
-    // A corpus of one tile per wave of a workgroup: its lists are the answer, one launch instead of two (128 x 768 fp16, k = 1:
-    // B = 64 13.9 -> 10.8 us, B = 512 12.4 -> 11.1; 64 x 1024, B = 8192, k = 16 23.1 -> 17.3).  Lists of 4 per lane are complete
-    // there whatever k is, since a lane sees four rows; selecting k > 4 from all eight waves costs more than the launch
-    // saves where the other way is group maxima (128 x 1024 bf16, B = 5000, k = 16: 19.3 / 23.3).
-    pl.direct = N <= (k <= 4 || dtype == ANN_F32 ? 128 : 64);
-    if (pl.direct) {
-        pl.st = stream_plan(cus, N, d, dtype, B, (k + 3) & ~3, 16);
-        pl.st.P = 1;
-        pl.ws_bytes = 0;
-        return pl;
-    }
-    pl.wide = use_wide(N, d, dtype, B, k);
-    if (pl.wide) {
-        int shape = wide_shape(cus, N, B);
-        wide_geometry(pl.w, shape, cus, N, B);
-        pl.w.gs_log = wide_group_log(cus, pl.w.wmf, N, d * 2, B, k);
-        pl.w.n = pl.w.slots >> pl.w.gs_log;
-        const size_t per = (size_t)pl.w.n * sizeof(float);
-        if (per * (size_t)B > limit) {
-            // (large corpora: groups as large as they come)
-            pl.w.gs_log = pl.w.wmf == 4 ? 6 : pl.w.wmf == 2 ? 5 : 4;
-            pl.w.n = pl.w.slots >> pl.w.gs_log;
-            const size_t fit = limit / ((size_t)pl.w.n * sizeof(float));
-            if (fit < 1) pl.wide = false;
-            else if (fit < (size_t)B) {
-                const int parts = (int)((B + fit - 1) / fit);
-                pl.part = (B + parts - 1) / parts;
-                if (pl.part > 256 && (size_t)((pl.part + 255) & ~255) <= fit) pl.part = (pl.part + 255) & ~255;
-                wide_geometry(pl.w, shape, cus, N, pl.part);
-            }
-        }
-        pl.ws_bytes = (size_t)pl.part * (size_t)pl.w.n * sizeof(float);
-    }
-    if (!pl.wide) pl.ws_bytes = (size_t)B * pl.st.P * pl.st.K * sizeof(Cand);
-    return pl;
 }
 
 int flat_search_run(const FlatPlan &pl, const void *X, int64_t N, int d, int dtype, const void *Q, int B, int k,

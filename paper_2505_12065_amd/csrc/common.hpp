@@ -8,9 +8,9 @@
 #include <math.h>
 #include <utility>
 
-namespace ann {
+#include "plan.hpp"
 
-constexpr int WAVE = 64;
+namespace ann {
 
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));       // one raw 16-byte chunk
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));

@@ -15,7 +15,6 @@
 
 namespace ann {
 
-constexpr int LANE_KP = 4;                            // entries of a lane's list
 constexpr int STREAM_BATCH = 4;                       // 16-byte loads per batch; two batches per lane in flight
 
 // Row r of a 16-row MFMA tile is corpus row 16 tile + tile_row(r): lane group g = lane / 16 then receives the

@@ -1,18 +1,8 @@
-// The per-query merge kernels of the flat search, and the LDS sizing helpers of its streaming kernel.
+// The per-query merge kernels of the flat search, and a measurement kernel.
 #include "flat_merge.hpp"
 #include "launch.hpp"
 
 namespace ann {
-
-size_t stream_lds_bytes(int nqg, int lds_steps, int waves) {
-    const size_t q = (size_t)nqg * lds_steps * WAVE * 16;
-    const size_t m = (size_t)nqg * 16 * (4 * waves * LANE_KP + 4) * sizeof(Cand);
-    return q > m ? q : m;
-}
-
-int stream_waves(int elem_bytes, int nqg, int lds_steps) {
-    return elem_bytes == 2 && nqg >= 2 && stream_lds_bytes(nqg, lds_steps, 8) > LDS_MAX / 2 ? 16 : 8;
-}
 
 hipError_t launch_flat_merge(const Cand *partial, int P, int B, int k, int32_t *ids, float *scores, hipStream_t stream) {
     const int threads = P * LANE_KP <= 512 ? 64 : 256;            // one batch of loads per lane where possible

@@ -45,28 +45,7 @@ hipError_t pick(const WidePlan &pl, const void *X, int64_t N, int d, const void 
     else if (one) return pl.wmf == 4 ? go(flat_pick_kernel<T, 4, true>) : pl.wmf == 2 ? go(flat_pick_kernel<T, 2, true>) : go(flat_pick_kernel<T, 1, true>);
     else return pl.wmf == 4 ? go(flat_pick_kernel<T, 4, false>) : pl.wmf == 2 ? go(flat_pick_kernel<T, 2, false>) : go(flat_pick_kernel<T, 1, false>);
 }
-template <class C>
-void geometry(WidePlan &pl, int cus, int64_t N, int B) {
-    const int64_t tiles = (N + C::BM - 1) / C::BM;
-    pl.cus = cus;
-    pl.wmf = C::WMF;
-    pl.NT = (B + C::BN - 1) / C::BN;
-    const int64_t cap = (int64_t)cus * C::PER_CU / pl.NT;
-    pl.P = (int)(cap < 1 ? 1 : cap < tiles ? cap : tiles);
-    pl.slots = tiles * C::BM;
-}
 }  // namespace
-
-void wide_geometry(WidePlan &pl, int shape, int cus, int64_t N, int B) {
-    pl.shape = shape;
-    switch (shape) {
-    case WIDE_LARGE: return geometry<WideLarge>(pl, cus, N, B);
-    case WIDE_TALL: return geometry<WideTall>(pl, cus, N, B);
-    case WIDE_SMALL: return geometry<WideSmall>(pl, cus, N, B);
-    case WIDE_TINY: return geometry<WideTiny>(pl, cus, N, B);
-    default: return geometry<WideThin>(pl, cus, N, B);
-    }
-}
 
 hipError_t launch_flat_wide(const WidePlan &pl, int dtype, const void *X, int64_t N, int d, const void *Q, int B, float *maxima,
                             After after, hipStream_t stream) {

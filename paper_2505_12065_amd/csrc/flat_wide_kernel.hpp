@@ -25,22 +25,6 @@
 
 namespace ann {
 
-template <int WMF_, int WNF_, int NWM_, int NWN_, int STAGES_, int PER_CU_>
-struct WideCfg {
-    static constexpr int WMF = WMF_, WNF = WNF_, NWM = NWM_, NWN = NWN_, STAGES = STAGES_, PER_CU = PER_CU_;
-    static constexpr int WAVES = NWM * NWN, THREADS = WAVES * WAVE;
-    static constexpr int BM = 32 * WMF * NWM, BN = 32 * WNF * NWN;
-    static constexpr int A_BLK = BM / 16, BLKS = A_BLK + BN / 16;       // 1 KB blocks of a stage: 16 rows x 64 B each
-    static constexpr int LPW = BLKS / WAVES;                            // blocks loaded per wave and stage
-    static_assert(BLKS % WAVES == 0, "blocks must divide evenly over the waves");
-    static constexpr int STAGE_BYTES = BLKS * 1024, LDS_BYTES = STAGES * STAGE_BYTES;
-};
-using WideLarge = WideCfg<4, 2, 2, 4, 4, 1>;              // 256 x 256, 8 waves
-using WideTall = WideCfg<4, 2, 4, 2, 4, 1>;               // 512 x 128, 8 waves
-using WideSmall = WideCfg<2, 2, 2, 2, 3, 3>;              // 128 x 128, 4 waves, three workgroups per compute unit
-using WideThin = WideCfg<2, 1, 2, 2, 4, 3>;               // 128 x 64, 4 waves, three
-using WideTiny = WideCfg<1, 1, 2, 2, 6, 3>;               // 64 x 64, 4 waves, three
-
 #define ANN_GLOBAL_TO_LDS_16(gptr, lptr)                                                          \
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gptr),      \
                                      (__attribute__((address_space(3))) void *)(lptr), 16, 0, 0)

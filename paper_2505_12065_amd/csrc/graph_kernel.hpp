@@ -31,12 +31,7 @@
 
 namespace ann {
 
-constexpr int GRAPH_THREADS = 256;
-constexpr int GRAPH_WAVES = GRAPH_THREADS / WAVE;
-constexpr int LANES_PER_ROW = 8;
-constexpr int ROWS_PER_PASS = GRAPH_THREADS / LANES_PER_ROW;   // 32 neighbours scored at once
 constexpr uint32_t EXPANDED = 0x80000000u;
-constexpr int RMAX_LDS = 256;                                  // row stride of the read-ahead buffers (>= R)
 
 // Number of entries of the ordered list (s[0..len), id[0..len)) that precede (v, vid), found by
 // the 8 lanes of a row group together: every round each lane probes one entry, which

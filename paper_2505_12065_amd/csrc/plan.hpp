@@ -1,0 +1,415 @@
+// What a call does, decided on the host: tiles, slabs, groups and parts of the exact search, LDS layouts and the choice of
+// kernel of the graph search.  Plain C++ without the GPU's headers, so that the rules can be compiled and looked at alone.
+#pragma once
+
+#include <math.h>
+#include <stddef.h>
+#include <stdint.h>
+
+#include <initializer_list>
+
+#include "../../include/ann.h"
+
+namespace ann {
+
+constexpr int WAVE = 64;
+constexpr size_t LDS_MAX = 160 * 1024;   // LDS of one gfx950 compute unit
+constexpr size_t CAND_BYTES = 8;         // a (score, id) pair in the workspace
+inline int elem_bytes(int dtype) { return dtype == ANN_F32 ? 4 : 2; }
+
+// ---- exact search, streaming kernel -----------------------------------------------------------------
+constexpr int LANE_KP = 4;                            // entries of a lane's list
+constexpr int STREAM_NQG_MAX(int elem_bytes) { return elem_bytes == 2 ? 4 : 2; }   // fp32: eight accumulators a group
+constexpr int STREAM_WG_PER_CU(int elem_bytes, int nqg, int waves) { return waves == 16 || (elem_bytes == 4 && nqg > 1) ? 1 : 2; }
+
+// Geometry and options of a flat_stream_kernel launch.
+struct StreamPlan {
+    int nqg = 1;                 // groups of 16 queries a workgroup serves, 1 .. STREAM_NQG_MAX
+    int G = 1;                   // workgroups side by side over the queries, ceil(B / (16 nqg))
+    int P = 1;                   // slabs of the corpus
+    int waves = 8;               // wavefronts per workgroup
+    int lds_steps = 1;           // 64-byte steps of a query held in LDS
+    int K = 4;                   // entries of a slab's list: k rounded up to a multiple of 4
+    int slots() const { return P * waves; }
+};
+inline size_t stream_lds_bytes(int nqg, int lds_steps, int waves) {
+    const size_t q = (size_t)nqg * lds_steps * WAVE * 16;
+    const size_t m = (size_t)nqg * 16 * (4 * waves * LANE_KP + 4) * CAND_BYTES;
+    return q > m ? q : m;
+}
+
+// Wavefronts of a flat_stream_kernel workgroup: 8, or 16 when the queries' LDS leaves room for one
+// workgroup per compute unit only (the corpus loads in flight are what keeps HBM busy).
+inline int stream_waves(int elem_bytes, int nqg, int lds_steps) {
+    return elem_bytes == 2 && nqg >= 2 && stream_lds_bytes(nqg, lds_steps, 8) > LDS_MAX / 2 ? 16 : 8;
+}
+
+// ---- exact search, matrix-core kernel ----------------------------------------------------------------
+template <int WMF_, int WNF_, int NWM_, int NWN_, int STAGES_, int PER_CU_>
+struct WideCfg {
+    static constexpr int WMF = WMF_, WNF = WNF_, NWM = NWM_, NWN = NWN_, STAGES = STAGES_, PER_CU = PER_CU_;
+    static constexpr int WAVES = NWM * NWN, THREADS = WAVES * WAVE;
+    static constexpr int BM = 32 * WMF * NWM, BN = 32 * WNF * NWN;
+    static constexpr int A_BLK = BM / 16, BLKS = A_BLK + BN / 16;       // 1 KB blocks of a stage: 16 rows x 64 B each
+    static constexpr int LPW = BLKS / WAVES;                            // blocks loaded per wave and stage
+    static_assert(BLKS % WAVES == 0, "blocks must divide evenly over the waves");
+    static constexpr int STAGE_BYTES = BLKS * 1024, LDS_BYTES = STAGES * STAGE_BYTES;
+};
+using WideLarge = WideCfg<4, 2, 2, 4, 4, 1>;              // 256 x 256, 8 waves
+using WideTall = WideCfg<4, 2, 4, 2, 4, 1>;               // 512 x 128, 8 waves
+using WideSmall = WideCfg<2, 2, 2, 2, 3, 3>;              // 128 x 128, 4 waves, three workgroups per compute unit
+using WideThin = WideCfg<2, 1, 2, 2, 4, 3>;               // 128 x 64, 4 waves, three
+using WideTiny = WideCfg<1, 1, 2, 2, 6, 3>;               // 64 x 64, 4 waves, three
+
+constexpr int WIDE_LARGE = 0, WIDE_TALL = 1, WIDE_SMALL = 2, WIDE_THIN = 3, WIDE_TINY = 4;
+struct WidePlan {
+    int cus, shape, wmf;         // compute units; workgroup tile (a WideCfg); its row fragments per wave
+    int NT, P;                   // query tiles x slabs of the corpus
+    int gs_log;                  // a maximum stands for 2^gs_log rows
+    int64_t slots, n;            // rows of whole tiles; groups they make
+};
+
+template <class C>
+inline void geometry(WidePlan &pl, int cus, int64_t N, int B) {
+    const int64_t tiles = (N + C::BM - 1) / C::BM;
+    pl.cus = cus;
+    pl.wmf = C::WMF;
+    pl.NT = (B + C::BN - 1) / C::BN;
+    const int64_t cap = (int64_t)cus * C::PER_CU / pl.NT;
+    pl.P = (int)(cap < 1 ? 1 : cap < tiles ? cap : tiles);
+    pl.slots = tiles * C::BM;
+}
+inline void wide_geometry(WidePlan &pl, int shape, int cus, int64_t N, int B) {
+    pl.shape = shape;
+    switch (shape) {
+    case WIDE_LARGE: return geometry<WideLarge>(pl, cus, N, B);
+    case WIDE_TALL: return geometry<WideTall>(pl, cus, N, B);
+    case WIDE_SMALL: return geometry<WideSmall>(pl, cus, N, B);
+    case WIDE_TINY: return geometry<WideTiny>(pl, cus, N, B);
+    default: return geometry<WideThin>(pl, cus, N, B);
+    }
+}
+
+// ---- exact search, the whole call ----------------------------------------------------------------------
+constexpr int P_MAX = 2048;      // most slabs of the streaming kernel
+
+struct FlatPlan {
+    StreamPlan st;           // streaming kernel with lists, unless
+    bool direct;             // ... of one slab: no merge
+    bool wide;               // the matrix-core kernel, or
+    bool maxima;             // the streaming kernel with group maxima takes the call, `part` queries at a time
+    WidePlan w;
+    int part;
+    size_t ws_bytes;
+};
+
+constexpr int WIDE_MIN_B = 65;   // smallest batch sent to the matrix-core path
+// Workspace that the group maxima of one launch may take; more queries run one part after the other.
+constexpr size_t WIDE_WS_MAX = (size_t)1 << 30;
+
+// The streaming kernel's geometry.
+// K: see the kernel; unit: rows that go to a wave together.
+inline StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int K, int unit) {
+    StreamPlan pl;
+    pl.K = K;
+    const int steps = (d * elem_bytes(dtype) + 63) / 64;
+    const int fit = (int)((LDS_MAX - 16 * 1024) / (WAVE * 16));        // steps of one group of 16 queries that fit LDS
+    const int n16 = (B + 15) / 16;
+    int nqg = fit / steps;
+    nqg = nqg < 1 ? 1 : nqg > STREAM_NQG_MAX(elem_bytes(dtype)) ? STREAM_NQG_MAX(elem_bytes(dtype)) : nqg;
+    nqg = nqg > n16 ? n16 : nqg;
+    pl.lds_steps = steps < fit ? steps : fit;
+    // as many queries per workgroup as possible read the corpus least often; fewer when the tiles of 16 rows would not
+    // give every compute unit a workgroup of 8 waves
+    const int64_t tiles = (N + unit - 1) / unit;
+    while (nqg > 1 && tiles * ((n16 + nqg - 1) / nqg) < (int64_t)cus * 8) --nqg;
+    pl.G = (n16 + nqg - 1) / nqg;
+    pl.nqg = (n16 + pl.G - 1) / pl.G;
+    pl.waves = stream_waves(elem_bytes(dtype), pl.nqg, pl.lds_steps);
+    int occ = (int)(LDS_MAX / stream_lds_bytes(pl.nqg, pl.lds_steps, pl.waves));
+    const int most = STREAM_WG_PER_CU(elem_bytes(dtype), pl.nqg, pl.waves);   // measured: more than 2 do not help
+    occ = occ < 1 ? 1 : (occ > most ? most : occ);
+    // every wave takes whole 16-row tiles in rounds; size the grid so that the last round
+    // is as full as the others instead of leaving most of the chip idle
+    int64_t cap = (int64_t)cus * occ / pl.G;
+    cap = cap < 1 ? 1 : (cap > P_MAX ? P_MAX : cap);
+    const int64_t rounds = (tiles + cap * pl.waves - 1) / (cap * pl.waves);
+    const int64_t P = (tiles + rounds * pl.waves - 1) / (rounds * pl.waves);
+    pl.P = (int)(P < cap ? P : cap);
+    return pl;
+}
+
+// Rows per group of the matrix-core kernel, by the time of what follows the products, in us: the maxima are written and
+// read once and the rows of k groups are read again, at some 4 TB/s over all queries; one query alone waits for its
+// maxima (twice, 1024 a wave at a time) and, unless groups are single rows, for its rows (32 a wave, 192 columns at once).
+inline int wide_group_log(int cus, int wmf, int64_t N, int row_bytes, int B, int k) {
+    const int waves = B <= cus ? 8 : 4;                   // of a query
+    int best = 0;
+    double least = INFINITY;
+    for (int g : {0, 2, 4, 5, 6}) {
+        if (wmf == 0 ? g < 4 : (1 << g) > 16 * wmf) continue;
+        const double n = (double)N / (1 << g), rows = (double)k * (1 << g);
+        double us = 8.0 * n * B / 4e6 + 1.6 * n / (1024 * waves);
+        if (g > 0) us += rows * row_bytes * B / 4e6 + 3.0 + 1.2 * ceil(rows / (32 * waves)) * ceil(row_bytes / 384.0);
+        if (us < least) { least = us; best = g; }
+    }
+    return best;
+}
+
+// The tile of the matrix-core kernel: the largest of which there are enough for the chip (larger tiles move fewer bytes per
+// product: 300 k x 768, B = 256: 162 us with 256 x 256, 187 with 512 x 128, 220 with 128 x 128; 30 k x 768, B = 256, 118
+// large tiles: 36, 39, 32; 50 k, 196 tiles: 40, 42, 52).  Queries are padded to whole tiles; the 512 x 128 tile runs at
+// 12/13 of the rate of the other large one, so it takes over where it saves more than that (1 M x 768, B = 300: 822 -> 745).
+inline int wide_shape(int cus, int64_t N, int B) {
+    auto enough = [&](int bm, int bn) { return 8 * ((N + bm - 1) / bm) * ((B + bn - 1) / bn) >= 5 * (int64_t)cus; };
+    if (B <= 64) return ((N + 127) / 128) >= cus ? WIDE_THIN : WIDE_TINY;
+    const int64_t cols256 = (B + 255) / 256 * 256, cols128 = (B + 127) / 128 * 128;
+    if (enough(256, 256) && 12 * cols256 <= 13 * cols128) return WIDE_LARGE;
+    if (enough(512, 128)) return WIDE_TALL;
+    return enough(128, 128) ? WIDE_SMALL : WIDE_TINY;
+}
+
+// Whether the matrix-core kernel takes a call, or the streaming kernel.  The streaming kernel reads large corpora at the
+// rate of HBM for up to 64 queries (1 M x 768, B = 64: 290 us against 380), but its lists cost every group of 16 queries
+// some 400 clocks a tile of 16 rows, whatever d is, which shows where rows are short or the corpus is in the caches
+// (streaming / matrix-core, us: 1 M x 64, B = 16 44 / 41, B = 64 106 / 46; 250 k x 256, B = 32 34 / 34, B = 64 45 / 35; 64 k x
+// 768, B = 32 30 / 32, B = 64 37 / 32).  Very small corpora are all latency: one-row maxima and one pass over them are as
+// fast as short lists and faster than long ones (4000 x 256, k = 16: 13 / 11).
+inline bool use_wide(int64_t N, int d, int dtype, int B, int k) {
+    if (dtype == ANN_F32) return false;
+    if (B >= WIDE_MIN_B) return true;
+    if (N <= 6000) return k > 4;
+    if (N <= 32 * 1024) return B > 32;
+    return B * (N <= 128 * 1024 ? 16 : N <= 512 * 1024 ? 8 : d <= 128 ? 4 : 0) >= d;
+}
+
+// fp32 keeps lists for up to 16 queries (HBM-bound on large corpora) and wherever picking costs more than the lists: the rows
+// of k groups (10 k d rows of scoring they are worth) and the launch-bound sizes.  Lists / maxima, us: 250 k x 64, B = 1000
+// 787 / 453; 1 M x 196, B = 100 818 / 666; 64 k x 384, B = 300 194 / 185; 16 k x 384, B = 1000, k = 16 164 / 208.
+inline bool use_f32_maxima(int64_t N, int d, int B, int k) {
+    return B > 16 && N >= (int64_t)10 * k * d && N * B >= (int64_t)32768 * d;
+}
+
+inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, size_t limit) {
+    FlatPlan pl{};
+    pl.st = stream_plan(cus, N, d, dtype, B, (k + 3) & ~3, 16);
+    pl.part = B;
+    if (dtype == ANN_F32 && use_f32_maxima(N, d, B, k)) {
+        pl.w.cus = cus;
+        pl.w.gs_log = wide_group_log(cus, 0, N, d * 4, B, k);
+        auto groups = [&] { return (((N - 1) >> pl.w.gs_log) + 1 + 3) & ~(int64_t)3; };
+        if ((size_t)groups() * sizeof(float) * (size_t)B > limit) pl.w.gs_log = 6;
+        pl.w.n = groups();
+        const size_t fit = limit / ((size_t)pl.w.n * sizeof(float));
+        if (fit >= 1) {
+            pl.maxima = true;
+            const int64_t parts = (B + (int64_t)fit - 1) / (int64_t)fit;
+            pl.part = (int)((B + parts - 1) / parts);
+            pl.st = stream_plan(cus, N, d, dtype, pl.part, 1 << (pl.w.gs_log - 4), 1 << pl.w.gs_log);
+            pl.ws_bytes = (size_t)pl.part * (size_t)pl.w.n * sizeof(float);
+            return pl;
+        }
+    }
+    // A corpus of one tile per wave of a workgroup: its lists are the answer, one launch instead of two (128 x 768 fp16, k = 1:
+    // B = 64 13.9 -> 10.8 us, B = 512 12.4 -> 11.1; 64 x 1024, B = 8192, k = 16 23.1 -> 17.3).  Lists of 4 per lane are complete
+    // there whatever k is, since a lane sees four rows; selecting k > 4 from all eight waves costs more than the launch
+    // saves where the other way is group maxima (128 x 1024 bf16, B = 5000, k = 16: 19.3 / 23.3).
+    pl.direct = N <= (k <= 4 || dtype == ANN_F32 ? 128 : 64);
+    if (pl.direct) {
+        pl.st = stream_plan(cus, N, d, dtype, B, (k + 3) & ~3, 16);
+        pl.st.P = 1;
+        pl.ws_bytes = 0;
+        return pl;
+    }
+    pl.wide = use_wide(N, d, dtype, B, k);
+    if (pl.wide) {
+        int shape = wide_shape(cus, N, B);
+        wide_geometry(pl.w, shape, cus, N, B);
+        pl.w.gs_log = wide_group_log(cus, pl.w.wmf, N, d * 2, B, k);
+        pl.w.n = pl.w.slots >> pl.w.gs_log;
+        const size_t per = (size_t)pl.w.n * sizeof(float);
+        if (per * (size_t)B > limit) {
+            // (large corpora: groups as large as they come)
+            pl.w.gs_log = pl.w.wmf == 4 ? 6 : pl.w.wmf == 2 ? 5 : 4;
+            pl.w.n = pl.w.slots >> pl.w.gs_log;
+            const size_t fit = limit / ((size_t)pl.w.n * sizeof(float));
+            if (fit < 1) pl.wide = false;
+            else if (fit < (size_t)B) {
+                const int parts = (int)((B + fit - 1) / fit);
+                pl.part = (B + parts - 1) / parts;
+                if (pl.part > 256 && (size_t)((pl.part + 255) & ~255) <= fit) pl.part = (pl.part + 255) & ~255;
+                wide_geometry(pl.w, shape, cus, N, pl.part);
+            }
+        }
+        pl.ws_bytes = (size_t)pl.part * (size_t)pl.w.n * sizeof(float);
+    }
+    if (!pl.wide) pl.ws_bytes = (size_t)B * pl.st.P * pl.st.K * CAND_BYTES;
+    return pl;
+}
+
+// ---- graph search ---------------------------------------------------------------------------------------
+constexpr int GRAPH_THREADS = 256;
+constexpr int GRAPH_WAVES = GRAPH_THREADS / WAVE;
+constexpr int LANES_PER_ROW = 8;
+constexpr int ROWS_PER_PASS = GRAPH_THREADS / LANES_PER_ROW;   // 32 neighbours scored at once
+constexpr int RMAX_LDS = 256;                                  // row stride of the read-ahead buffers (>= R)
+
+constexpr int GRAPH_DENSE_MIN_B = 1280;   // batches beyond this run three graph-search workgroups per compute unit
+constexpr int GRAPH_EF_DOUBLE = 2048;    // candidate lists up to this length are double-buffered in LDS
+constexpr int GRAPH_EF_TWO_LEVEL = 512;  // beyond this, graphs of at most 32 slots per node use the two-level list
+struct GraphLds {
+    // byte offsets into dynamic LDS; all 16-byte aligned
+    uint32_t q, ls0, ls1, li0, li1, cs, ci, cpos, cache, ctl, adj, um, rq, co, total;
+    uint32_t cache_bits, rp;
+    // two-level list (search ranges beyond GRAPH_EF_TWO_LEVEL on graphs of at most 32 slots per node):
+    // ms / mi hold the large part of the list, ls0 .. li1 the small part (GRAPH_DELTA entries each)
+    uint32_t two_level, ms, mi;
+};
+constexpr int GRAPH_DELTA = 256;
+// The two-level layout keeps its small regions at fixed byte offsets at the start of LDS (the kernel
+// then addresses them with immediates and needs no register per region); the large part of the
+// list and the query, whose sizes depend on ef and d, follow.
+constexpr uint32_t TL_LS0 = 0, TL_LI0 = 4 * GRAPH_DELTA, TL_LS1 = 8 * GRAPH_DELTA, TL_LI1 = 12 * GRAPH_DELTA;
+constexpr uint32_t TL_CS = 16 * GRAPH_DELTA, TL_CI = TL_CS + 128, TL_CPOS = TL_CI + 128, TL_CTL = TL_CPOS + 128;
+constexpr uint32_t TL_ADJ = TL_CTL + 32, TL_UM = TL_ADJ + 256;
+constexpr uint32_t TL_MS = TL_UM + 8 * (16384 / 64) + 32;   // um: a bit per entry of the longest list, and 4 words
+// words of one query's visited bitset: one bit per node, rounded to 64-byte units
+inline int64_t visited_words(int64_t N) { return (N + 511) / 512 * 16; }
+
+// graph_step_kernel (graphs of at most 32 slots per node): how it runs a call, and its LDS
+constexpr int GRAPH_STEP_MAX_R = 32;
+constexpr int STEP_VIS_LDS = 0, STEP_VIS_CACHE = 1, STEP_VIS_GLOBAL = 2;   // where the visited set is
+struct StepLds {
+    // fixed byte offsets: scores, ids, positions, numbers of a step's neighbours (64 each), control words, then the scratch
+    // of every wave
+    static constexpr uint32_t CS = 0, CI = 256, CP = 512, EV = 768, EW = 1024, FM = 1280, CTL = 1312, MK = 1328,
+                              WAVE0 = 1456, WAVE_BYTES = 576;
+    // byte offsets: list scores and ids (two buffers of ls_bytes each), and for long lists the large part and its bits
+    uint32_t ls, li, ls_bytes, um, ms, mi, vis, q, total;
+    int vis_words, cache_shift, vis_mode;
+    int rows_per_group;                                   // neighbours a row group scores in a step: 1 or 2
+    bool dense;                                           // three workgroups per compute unit, query read from LDS
+    bool long_list;
+};
+
+inline GraphLds graph_lds_layout(int d, int elem_bytes, int R, int ef) {
+    auto up = [](uint32_t x) { return (x + 15u) & ~15u; };
+    const bool inplace = ef > GRAPH_EF_DOUBLE;           // long lists: one buffer, merged in place
+    auto lay = [&](uint32_t bits) {
+        GraphLds L{};
+        uint32_t off = 0;
+        L.rp = (uint32_t)((R + ROWS_PER_PASS - 1) / ROWS_PER_PASS * ROWS_PER_PASS);
+        L.cache_bits = bits;
+        L.q = off; off = up(off + (uint32_t)d * elem_bytes);
+        // score lists are padded to 64 entries; lists of up to 256 entries get buffers of 256, which
+        // the scan for the next unexpanded entry then reads without conditions
+        const uint32_t ef64 = ef <= GRAPH_DELTA ? (uint32_t)GRAPH_DELTA : ((uint32_t)ef + 63u) & ~63u;
+        const uint32_t efi = ef <= GRAPH_DELTA ? (uint32_t)GRAPH_DELTA : (uint32_t)ef;
+        L.ls0 = off; off = up(off + 4u * ef64);
+        if (inplace) L.ls1 = L.ls0; else { L.ls1 = off; off = up(off + 4u * ef64); }
+        L.li0 = off; off = up(off + 4u * efi);
+        if (inplace) L.li1 = L.li0; else { L.li1 = off; off = up(off + 4u * efi); }
+        L.cs = off; off = up(off + 4u * L.rp);
+        L.ci = off; off = up(off + 4u * L.rp);
+        L.cpos = off; off = up(off + 4u * L.rp);
+        L.cache = off; off = up(off + (4u << bits));
+        L.ctl = off; off = up(off + 16u);
+        L.adj = off; off = up(off + 2u * 4u * RMAX_LDS);
+        L.um = off; off = up(off + 8u * (((uint32_t)ef + 63u) / 64u) + 32u);   // the scans use um[0 .. 3] at any ef
+        L.rq = off; off = up(off + 4u * L.rp);
+        L.co = off; off = up(off + 4u * L.rp);
+        L.total = off;
+        return L;
+    };
+    // Long lists on graphs of at most 32 slots per node: the two-level list.  The large part has one
+    // buffer of ef entries, the small part two of GRAPH_DELTA; the adjacency rows read ahead take 32
+    // slots each; the words of um double as the position marks of a rebuild; there is no id cache.
+    auto lay2 = [&] {
+        GraphLds L{};
+        L.rp = ROWS_PER_PASS;
+        L.cache_bits = 0;                                  // no id cache: the visited set is asked first
+        L.two_level = 1;
+        L.ls0 = TL_LS0; L.li0 = TL_LI0; L.ls1 = TL_LS1; L.li1 = TL_LI1;
+        L.cs = TL_CS; L.ci = TL_CI; L.cpos = TL_CPOS;
+        L.ctl = L.cache = TL_CTL;
+        L.adj = TL_ADJ;
+        L.um = L.rq = L.co = TL_UM;                        // (rq, co: used by the plain loop only)
+        L.ms = TL_MS;
+        L.mi = up(L.ms + 4u * (uint32_t)ef);
+        L.q = up(L.mi + 4u * (uint32_t)ef);
+        L.total = up(L.q + (uint32_t)d * elem_bytes);
+        return L;
+    };
+    // (it is the only layout of such lists on such graphs: the software-pipelined loop has no code for
+    // a single list of more than 512 entries; with d <= ANN_D_MAX it always fits)
+    if (ef > GRAPH_EF_TWO_LEVEL && R <= ROWS_PER_PASS) return lay2();
+    // cache slots: a few times the number of nodes a search scores (about 10 ef), at most 2^14;
+    // fewer when that lets two workgroups share a compute unit, or when the list needs the room
+    uint32_t want = 10;
+    while ((1u << want) < 32u * (uint32_t)ef && want < 14) ++want;
+    uint32_t bits = want;
+    if (lay(11).total <= LDS_MAX / 2)
+        while (bits > 11 && lay(bits).total > LDS_MAX / 2) --bits;
+    while (bits > 10 && lay(bits).total > LDS_MAX) --bits;
+    return lay(bits);
+}
+
+// Where steps of several expansions are faster than one expansion at a time.  A step costs two to three expansions of the
+// other kernel, so what decides is how many expansions a step commits for the slowest query of the batch.  Measured over
+// drawn N (20 k to 200 k), d, R and types, time of the one-by-one loop / time in steps:
+//   maturity exit (tau < 1: most queries stop while their list fills, and a filling list commits whole steps): 1.1 to 2.4
+//     with lists of 96 up and some queries per call; 0.65 to 0.95 for one to four queries or shorter lists (over before
+//     the steps pay), and 0.6 to 1.05 where no average reaches tau and every search runs to its end
+//   two-level lists (over 512): 1.0 to 3.4, more for longer lists; 0.87 only at ef = 700 with 1.5 KB rows and 256 queries,
+//     hence the bound on the row below ef = 1024
+//   one list: more queries than two workgroups per compute unit hold (the rest waits for a place, so the mean over queries
+//     counts, not the slowest) 1.1 to 1.5 from ef = 192, 0.84 to 1.1 below; up to four queries 1.0 to 4.1 from ef = 320
+//     (0.85 to 1.1 below, or with rows of over 2 KB); else 0.75 to 1.0
+inline bool graph_step_pays(int cus, int row_bytes, int R, int B, int ef, bool counters, float tau) {
+    if (R > GRAPH_STEP_MAX_R) return false;
+    if (counters) return tau < 1.0f && R >= 16 && ef >= 96 && B >= 8 && (int64_t)B * ef >= 2048;
+    if (ef > GRAPH_EF_TWO_LEVEL) return ef >= 1024 || row_bytes <= 1024 || B <= 16;
+    return B > 2 * cus ? ef >= 192 : B <= 4 && ef >= 320 && row_bytes <= 2048;
+}
+
+inline StepLds graph_step_plan(int cus, int64_t N, int d, int elem_bytes, int B, int ef, bool counters) {
+    auto up = [](uint32_t x) { return (x + 15u) & ~15u; };
+    StepLds L{};
+    L.long_list = ef > GRAPH_EF_TWO_LEVEL;
+    L.rows_per_group = B <= cus ? 2 : 1;
+    const uint32_t entries = L.long_list || ef <= GRAPH_DELTA ? (uint32_t)GRAPH_DELTA : ((uint32_t)ef + 63u) & ~63u;
+    uint32_t off = up(StepLds::WAVE0 + GRAPH_WAVES * StepLds::WAVE_BYTES);
+    L.ls_bytes = 4u * entries;
+    L.ls = off; off = up(off + 2u * L.ls_bytes);
+    L.li = off; off = up(off + 2u * L.ls_bytes);
+    if (L.long_list) {
+        L.um = off; off = up(off + 8u * (((uint32_t)ef + 63u) / 64u) + 32u);
+        L.ms = off; off = up(off + 4u * (uint32_t)ef);
+        L.mi = off; off = up(off + 4u * (uint32_t)ef);
+    }
+    L.q = off; off = up(off + (uint32_t)d * elem_bytes);
+    L.vis = off;
+    // A bit per node in LDS if it leaves the workgroups per compute unit that the batch needs
+    const uint32_t room = (uint32_t)(B <= cus ? LDS_MAX : LDS_MAX / 2);
+    const int64_t words = visited_words(N);
+    if ((int64_t)off + words * 4 <= room) {
+        L.vis_mode = STEP_VIS_LDS;
+        L.vis_words = (int)words;
+    } else if (!counters && !L.long_list) {
+        // id cache: a few times the number of nodes a search scores (about 10 ef)
+        L.vis_mode = STEP_VIS_CACHE;
+        int bits = 10;
+        while ((1u << bits) < 32u * (uint32_t)ef && bits < 13) ++bits;
+        L.vis_words = 1 << bits;
+        L.cache_shift = 32 - bits;
+    } else {
+        L.vis_mode = STEP_VIS_GLOBAL;
+    }
+    L.total = up(off + 4u * (uint32_t)L.vis_words);
+    // More queries than two workgroups per compute unit hold at once, and a layout small enough for three: the form
+    // that reads the query from LDS and runs three per compute unit.
+    L.dense = !counters && !L.long_list && B > GRAPH_DENSE_MIN_B && 3 * (size_t)L.total <= LDS_MAX;
+    return L;
+}
+
+}  // namespace ann
