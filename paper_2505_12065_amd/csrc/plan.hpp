@@ -355,21 +355,43 @@ inline GraphLds graph_lds_layout(int d, int elem_bytes, int R, int ef) {
 }
 
 // Where steps of several expansions are faster than one expansion at a time.  A step costs two to three expansions of the
-// other kernel, so what decides is how many expansions a step commits for the slowest query of the batch.  Measured over
-// drawn N (20 k to 200 k), d, R and types, time of the one-by-one loop / time in steps:
-//   maturity exit (tau < 1: most queries stop while their list fills, and a filling list commits whole steps): 1.1 to 2.4
-//     with lists of 96 up and some queries per call; 0.65 to 0.95 for one to four queries or shorter lists (over before
-//     the steps pay), and 0.6 to 1.05 where no average reaches tau and every search runs to its end
-//   two-level lists (over 512): 1.0 to 3.4, more for longer lists; 0.87 only at ef = 700 with 1.5 KB rows and 256 queries,
-//     hence the bound on the row below ef = 1024
-//   one list: more queries than two workgroups per compute unit hold (the rest waits for a place, so the mean over queries
-//     counts, not the slowest) 1.1 to 1.5 from ef = 192, 0.84 to 1.1 below; up to four queries 1.0 to 4.1 from ef = 320
-//     (0.85 to 1.1 below, or with rows of over 2 KB); else 0.75 to 1.0
-inline bool graph_step_pays(int cus, int row_bytes, int R, int B, int ef, bool counters, float tau) {
+// other kernel, so what decides is how many expansions it commits: the neighbours a step holds (63 for a batch that leaves
+// every query a compute unit, else 32) against the unseen ones that an expansion brings.  Those get fewer as a search covers
+// more of the graph, so the line runs along N / ef, the nodes of the graph per entry of the list, and lies higher for narrow
+// graphs, for short rows (a step scores two to three rows for every one it keeps) and for batches that wait for a place
+// anyway (the mean over the queries counts there, not the slowest).  Time of the one-by-one loop / time in steps over
+// 2400 points (N 20 k to 2 M, d 64 to 1024, R 8 to 32, B 1 to 4096, ef 192 to 16384, all types):
+//   lists over 512, R = 32, 1.5 KB rows, B = 256 / 512: 50 k, ef = 1024 1.19 / 1.30; 200 k 0.93 / 0.95, ef = 2048 1.07 / 1.15,
+//     8192 1.56 / 1.62; 1 M, ef = 1024 0.80 / 0.71, 2048 0.85 / 0.78, 4096 0.86 / 0.90, 8192 0.96 / 1.05.  The two sides meet at
+//     N / ef = 140 to 180; 180 to 250 with rows of up to 1 KB, over 400 with 128 bytes; 1.5 and 8 times that for R = 24 and 16
+//     with B = 512, 1.6 and up with B = 800
+//   one list, more queries than two workgroups per compute unit hold, R = 32: 60 k, ef = 192 to 512, B = 600 1.3 to 1.5; 200 k 1.0 to
+//     1.2; 1 M 0.96 to 1.08; about two full rounds of places (B = 800 to 1100) gain least: 60 k 0.97 to 1.2, 200 k 0.89 to 1.05,
+//     1 M 0.78 to 0.84; B = 2048 200 k 1.05 to 1.43, 1 M 0.71 to 1.0.  R = 16: 1.0 to 2.1 at any of these N
+//   up to two queries 1.0 to 4.4 (0.8 at worst: it depends on the query); four: 60 k, ef = 320 1.05, 200 k 0.90 (R = 16, long
+//     lists, 800 k: 1.0 to 1.6)
+//   maturity exit (tau < 1: most queries stop while their list fills, and a filling list commits whole steps): 1.05 to 2.1
+//     at any N up to 1 M with lists of 96 up and some queries per call; 0.65 to 0.95 for one to four queries or shorter
+//     lists (over before the steps pay), and 0.6 to 1.05 where no average reaches tau and every search runs to its end
+inline bool graph_step_pays(int cus, int64_t N, int row_bytes, int R, int B, int ef, bool counters, float tau) {
     if (R > GRAPH_STEP_MAX_R) return false;
     if (counters) return tau < 1.0f && R >= 16 && ef >= 96 && B >= 8 && (int64_t)B * ef >= 2048;
-    if (ef > GRAPH_EF_TWO_LEVEL) return ef >= 1024 || row_bytes <= 1024 || B <= 16;
-    return B > 2 * cus ? ef >= 192 : B <= 4 && ef >= 320 && row_bytes <= 2048;
+    int64_t reach = row_bytes <= 256 ? 448 : row_bytes <= 1024 ? 240 : 160;     // nodes per list entry up to which steps pay
+    const bool long_list = ef > GRAPH_EF_TWO_LEVEL, waits = B > 2 * cus;
+    if (B <= 4) {
+        if (ef < 320 || (!long_list && row_bytes > 2048)) return false;
+        if (B <= 2) return true;
+        reach *= long_list && R <= 16 ? 8 : 2;
+    } else if (long_list) {
+        if (B > cus) reach *= R <= 16 ? 8 : 1;
+        if (B > cus && R > 16) reach = reach * (R <= 24 ? (waits ? 30 : 15) : (waits ? 16 : 10)) / 10;
+    } else {
+        if (!waits || ef < 192) return false;
+        if (R <= 16) return true;
+        const bool two_rounds = B >= 3 * cus && 2 * B <= 9 * cus;
+        reach = two_rounds ? (R <= 24 ? 800 : 400) : R <= 24 ? 3000 : B > GRAPH_DENSE_MIN_B ? 1024 : 1600;
+    }
+    return ef * reach >= N;
 }
 
 inline StepLds graph_step_plan(int cus, int64_t N, int d, int elem_bytes, int B, int ef, bool counters) {

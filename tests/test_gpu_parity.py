@@ -628,6 +628,28 @@ def test_graph_steps_of_several_expansions(dtype, N, d, R, B, ef, tau):
         compare_nonstall([t.cpu().numpy() for t in gpu], o, xn, gn, qn, name, 3, 3, ef, tau, 60)
 
 
+@pytest.mark.parametrize("N,R,B,ef", [(83_200, 32, 5, 520), (166_400, 32, 3, 520), (124_800, 24, 257, 520),
+                                      (133_120, 32, 513, 520), (307_200, 32, 513, 192)])
+def test_graph_either_side_of_the_size_up_to_which_steps_pay(N, R, B, ef):
+    """The last graph that is searched in steps and the first that is not, rows of just over 1 KB: the search with
+    counters and no exit threshold, which always goes one by one, gives the same bits; some queries against the oracle."""
+    say(f"graph steps end: N={N} R={R} B={B} ef={ef}")
+    d = 520
+    for n in (N, N + 1):
+        gen = torch.Generator(device=DEV).manual_seed(ef)
+        x = torch.nn.functional.normalize(torch.randn(n, d, generator=gen, device=DEV), dim=1).half()
+        q = torch.nn.functional.normalize(torch.randn(B, d, generator=gen, device=DEV), dim=1).half()
+        g = torch.randint(-1, n + 1, (n, R), generator=gen, dtype=torch.int32, device=DEV)
+        ids, sc = ann.ann_graph_search_typed(x, g, n - 1, q, 3, ef)
+        n_ids, n_sc, _, _ = ann.ann_graph_search_nonstall_typed(x, g, n - 1, q, 3, ef, tau=float("inf"))
+        torch.cuda.synchronize()
+        assert torch.equal(ids, n_ids) and torch.equal(sc, n_sc)
+        xn, qn = to_np(x), to_np(q[:4])
+        o_ids, _, o_sc64, _, _ = oracle.graph_search(xn, g.cpu().numpy(), n - 1, qn, 3, ef)
+        strict, tolerant, m = compare_topk(ids[:4].cpu().numpy(), sc[:4].cpu().numpy(), o_ids, o_sc64, xn, qn)
+        assert strict >= m - 1, (strict, m)
+
+
 def test_graph_padding_when_few_nodes_are_reachable():
     c = synth.make_corpus(200, 64, 4, seed=2, dtype=torch.float16, zipf_a=None, sigma=0.3)
     q = synth.make_queries(c, 4)
