@@ -35,8 +35,10 @@ int fail(int code, const char *fmt, ...) {
 // Workspace of ann_flat_search_static: lives in the code object, so every device the library
 // runs on holds one copy until the process ends.  In host code this name is only a handle for
 // hipGetSymbolAddress; the device address is looked up once per device (device_state) and is
-// what every launch and every offset computation uses.
-static __device__ __align__(256) unsigned char scratch[ANN_STATIC_WORKSPACE_BYTES];
+// what every launch and every offset computation uses.  Behind the workspace: room for the k best so far of the queries of
+// a part, so that they take nothing from its maxima (8 MiB of them are whole rounds of tiles on 256 compute units).
+constexpr size_t STATIC_BYTES = ANN_STATIC_WORKSPACE_BYTES + (size_t)PART_MAX_B * ANN_K_MAX * sizeof(uint64_t);
+static __device__ __align__(256) unsigned char scratch[STATIC_BYTES];
 
 namespace {
 
@@ -176,25 +178,34 @@ int flat_search_run(const FlatPlan &pl, const void *X, int64_t N, int d, int dty
                      : B >= WIDE_MIN_B && d % 32 == 0 ? ANN_KERNEL_FLAT_WIDE : ANN_KERNEL_FLAT_STREAM;
     StreamOut direct;
     if (pl.direct) direct = StreamOut{ids, scores, k};
-    auto stream_kernel = [&](const void *q, int b, Cand *partial, float *maxima, After a) {
+    auto stream_kernel = [&](const FlatPlan &one, const void *x, int64_t rows, const void *q, int b, Cand *partial, float *maxima,
+                             After a) {
         return (dtype == ANN_F16 ? launch_flat_stream_f16 : dtype == ANN_BF16 ? launch_flat_stream_bf16 : launch_flat_stream_f32)(
-            pl.st, X, N, d, q, b, partial, maxima, pl.w.n, direct, a, stream);
+            one.st, x, rows, d, q, b, partial, maxima, one.w.n, direct, a, stream);
     };
     if (pl.wide || pl.maxima) {
         float *maxima = static_cast<float *>(ws);
+        uint64_t *best = reinterpret_cast<uint64_t *>(static_cast<char *>(ws) + pl.best_ofs);
+        const size_t row_bytes = (size_t)d * elem_bytes(dtype);
         for (int q0 = 0; q0 < B; q0 += pl.part) {
             const int b = B - q0 < pl.part ? B - q0 : pl.part;
-            const void *q = static_cast<const char *>(Q) + (size_t)q0 * d * elem_bytes(dtype);
-            const After a{after.s ? after.s + q0 : nullptr, after.id ? after.id + q0 : nullptr};
-            hipError_t e;
-            {
-                TimedScope timed(q0 == 0 ? code : -1, stream);
-                e = pl.wide ? launch_flat_wide(pl.w, dtype, X, N, d, q, b, maxima, a, stream)
-                            : stream_kernel(q, b, nullptr, maxima, a);
+            const void *q = static_cast<const char *>(Q) + (size_t)q0 * row_bytes;
+            for (int64_t r0 = 0; r0 < N; r0 += pl.rows) {
+                const int64_t rows = N - r0 < pl.rows ? N - r0 : pl.rows;
+                const void *x = static_cast<const char *>(X) + (size_t)r0 * row_bytes;
+                const After a{after.s ? after.s + q0 : nullptr, after.id ? after.id + q0 : nullptr, (int)r0};
+                const FlatPlan one = maxima_part(pl, rows, b, d, dtype);
+                hipError_t e;
+                {
+                    TimedScope timed(q0 == 0 && r0 == 0 ? code : -1, stream);
+                    e = one.wide ? launch_flat_wide(one.w, dtype, x, rows, d, q, b, maxima, a, stream)
+                                 : stream_kernel(one, x, rows, q, b, nullptr, maxima, a);
+                }
+                if (int rc = check_launch(one.wide ? "flat_wide_kernel" : "flat_stream_kernel", e)) return rc;
+                e = launch_flat_pick(one.w, dtype, x, rows, d, q, b, k, maxima, ids + (size_t)q0 * k, scores + (size_t)q0 * k, a,
+                                     best, (r0 > 0 ? 1 : 0) | (r0 + rows < N ? 2 : 0), stream);
+                if (int rc = check_launch("flat_pick_kernel", e)) return rc;
             }
-            if (int rc = check_launch(pl.wide ? "flat_wide_kernel" : "flat_stream_kernel", e)) return rc;
-            e = launch_flat_pick(pl.w, dtype, X, N, d, q, b, k, maxima, ids + (size_t)q0 * k, scores + (size_t)q0 * k, a, stream);
-            if (int rc = check_launch("flat_pick_kernel", e)) return rc;
         }
         return ANN_OK;
     }
@@ -202,7 +213,7 @@ int flat_search_run(const FlatPlan &pl, const void *X, int64_t N, int d, int dty
     hipError_t e;
     {
         TimedScope timed(code, stream);
-        e = stream_kernel(Q, B, partial, nullptr, after);
+        e = stream_kernel(pl, X, N, Q, B, partial, nullptr, after);
     }
     if (int rc = check_launch("flat_stream_kernel", e)) return rc;
     if (pl.direct) return ANN_OK;
@@ -419,10 +430,10 @@ int ann_flat_search_static(const void *corpus, int64_t N, int32_t d, int32_t dty
     // with k > 4 is refused instead, as ann.h says.
     FlatPlan pl = flat_plan(st->cus, N, d, dtype, B, k, WIDE_WS_MAX);
     if (pl.ws_bytes > (size_t)ANN_STATIC_WORKSPACE_BYTES && (k <= 4 || B < 256)) {
-        const FlatPlan parts = flat_plan(st->cus, N, d, dtype, B, k, ANN_STATIC_WORKSPACE_BYTES);
-        if (parts.ws_bytes <= (size_t)ANN_STATIC_WORKSPACE_BYTES) pl = parts;
+        const FlatPlan parts = flat_plan(st->cus, N, d, dtype, B, k, STATIC_BYTES);
+        if (parts.ws_bytes <= STATIC_BYTES) pl = parts;
     }
-    if (pl.ws_bytes > (size_t)ANN_STATIC_WORKSPACE_BYTES)
+    if (pl.ws_bytes > STATIC_BYTES)
         return fail(ANN_ERR_INVALID, "this search needs %zu bytes of workspace, the static one holds %d",
                     pl.ws_bytes, ANN_STATIC_WORKSPACE_BYTES);
     g_timing_off = true;                                  // event pairs would have to be created

@@ -359,9 +359,11 @@ __device__ __forceinline__ f16v mfma32<BF16>(u4 a, u4 b, f16v c) {
 
 // Continuation of an exact search: with a boundary pair per query, only rows that come strictly
 // after (s[q], id[q]) in the order are candidates of query q.  Null pointers: no boundary.
+// A search that takes the corpus in parts counts rows from the start of the part, which is row `base`.
 struct After {
     const float *s = nullptr;
     const int *id = nullptr;
+    int base = 0;
 };
 // The score of a row for the selection: unchanged when the row comes after the boundary (or the
 // boundary score is NaN: nothing excluded), NaN otherwise, and a NaN score is never listed.

@@ -249,9 +249,9 @@ __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NW
                 asm volatile("" : "+v"(l));           // (nor to hold what their addresses are made of)
                 const int qb = min(q0 + g * 16 + (l & 15), B - 1);
                 const float bs = after.s[qb];
-                const int bid = after.id[qb];
+                const int bid = after.id[qb], rafter = rbase + after.base;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[g][i] = after_boundary(acc[g][i], rbase + 4 * i, bs, bid);
+                for (int i = 0; i < 4; ++i) acc[g][i] = after_boundary(acc[g][i], rafter + 4 * i, bs, bid);
             }
         }
         if constexpr (MAX) {

@@ -30,11 +30,15 @@ __device__ __forceinline__ int64_t wide_row(int64_t slot) {
 // are gone through in order, a few at a time, past those that can no longer improve the k best so far.
 // Bound by the latency of three dependent reads (maxima twice, rows) at 8 to 12 us, and beyond about 1000 queries by the
 // bytes of the rows.
+// PARTS: a search that takes the corpus in parts (sh.X and sh.N are the part, after.base its first row) goes on from the k
+// best of the parts before, which also bound what is worth looking at: best_so_far [B, k], read where `more` has bit 0;
+// the result goes back there where it has bit 1, else to ids and scores.  (A variant of its own: the calls of a few
+// microseconds do not wait for two more arguments.)
 constexpr int PICK_CAP = 512;
-template <class T, int WMF, bool ONE>
+template <class T, int WMF, bool ONE, bool PARTS>
 __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict__ maxima, int64_t n, int gs_log, int k,
                                                         int32_t *__restrict__ ids, float *__restrict__ scores, StreamShape sh,
-                                                        After after) {
+                                                        After after, uint64_t *__restrict__ best_so_far, int more) {
     __shared__ uint64_t ck[PICK_CAP];                 // gathered maxima, then scored rows
     __shared__ int sel[PICK_CAP];                     // groups to score
     __shared__ uint32_t top[8 * 16];
@@ -46,9 +50,10 @@ __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict_
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int NT = blockDim.x, nwaves = NT >> 6;
     const uint64_t empty = order_key(-INFINITY, EMPTY_ID);
+    const int base = PARTS ? after.base : 0;
     const float *mx = maxima + (size_t)q * n;
     const int rb = sh.d * T::bytes, nch = rb >> 4;
-    if (tid < 16) fin[tid] = empty;
+    if (tid < 16) fin[tid] = PARTS && (more & 1) && tid < k ? best_so_far[(size_t)q * k + tid] : empty;
     if (tid == 0) { n_c = 0; n_sel = 0; t_min = ~0u; }
     if (!ONE)
         for (int c = tid; c < nch; c += NT) qs[c] = load_chunk(static_cast<const char *>(sh.Q) + (size_t)q * rb + c * 16);
@@ -82,10 +87,11 @@ __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict_
     } else {
         __syncthreads();                              // the shared words are set
     }
-    const uint32_t bound = max(1u, (uint32_t)__builtin_amdgcn_readlane((int)m, k - 1));
+    uint32_t bound = max(1u, (uint32_t)__builtin_amdgcn_readlane((int)m, k - 1));
+    if (PARTS && (more & 1)) bound = max(bound, (uint32_t)(fin[k - 1] >> 32));
     // 64-bit key of entry e with value image x: what the ranks go by (one row: the row's own key)
     auto entry_key = [&](uint32_t x, int64_t e) {
-        return ((uint64_t)x << 32) | (uint32_t)~(uint32_t)(ONE ? wide_row<WMF>(e) : e);
+        return ((uint64_t)x << 32) | (uint32_t)~(uint32_t)(ONE ? base + wide_row<WMF>(e) : e);
     };
     for (int64_t i0 = tid; i0 < n4; i0 += 4 * NT) {
         if (n4 > 4 * NT) load_maxima(i0);
@@ -177,9 +183,9 @@ __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict_
                     at = 8 * ((col & 15) >> 2) + 4 * sub + (col & 3);
                 }
                 const int64_t e = e0 + at, id = row_of(e);
-                if (after.s) v = after_boundary(v, (int)id, after.s[q], after.id[q]);
+                if (after.s) v = after_boundary(v, base + (int)id, after.s[q], after.id[q]);
                 if (col < UNIT / CHUNKS && e < rows && id < sh.N && v == v) {
-                    const uint64_t key = order_key(v, (int)id);
+                    const uint64_t key = order_key(v, base + (int)id);
                     if ((uint32_t)(key >> 32) >= t && key > worst) ck[atomicAdd(&n_c, 1)] = key;
                 }
             }
@@ -213,7 +219,7 @@ __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict_
             const uint64_t worst = fin[k - 1];
             for (int64_t e = c0 + tid; e < min(c0 + (int64_t)step, n); e += NT) {
                 const uint32_t x = image(mx[e]);
-                const uint64_t best = ((uint64_t)x << 32) | (uint32_t)~(uint32_t)wide_row<WMF>(e << gs_log);
+                const uint64_t best = ((uint64_t)x << 32) | (uint32_t)~(uint32_t)(base + wide_row<WMF>(e << gs_log));
                 if (x >= bound && best > worst) {     // its best row may be better than the k-th so far
                     if (ONE) ck[atomicAdd(&n_c, 1)] = best;
                     else sel[atomicAdd(&n_sel, 1)] = (int)e;
@@ -225,7 +231,9 @@ __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict_
         }
     }
 
-    if (tid < k) {
+    if (PARTS && (more & 2)) {
+        if (tid < k) best_so_far[(size_t)q * k + tid] = fin[tid];
+    } else if (tid < k) {
         float s;
         int id;
         order_key_decode(fin[tid], s, id);

@@ -9,9 +9,8 @@ hipError_t launch(const WidePlan &pl, const void *X, int64_t N, int d, const voi
                   hipStream_t stream) {
     static size_t big = 0;
     if (hipError_t e = allow_big_lds(reinterpret_cast<const void *>(&flat_wide_kernel<T, C>), C::LDS_BYTES, &big)) return e;
-    const int nt = (B + C::BN - 1) / C::BN;               // (the last part of a call may have fewer than the plan)
-    hipLaunchKernelGGL((flat_wide_kernel<T, C>), dim3(pl.P * nt), dim3(C::THREADS), C::LDS_BYTES, stream, X, N, d, Q, B,
-                       maxima, pl.n, pl.P, nt, pl.gs_log, after);
+    hipLaunchKernelGGL((flat_wide_kernel<T, C>), dim3(pl.P * pl.NT), dim3(C::THREADS), C::LDS_BYTES, stream, X, N, d, Q, B,
+                       maxima, pl.n, pl.P, pl.NT, pl.gs_log, after);
     return hipGetLastError();
 }
 
@@ -29,7 +28,7 @@ hipError_t launch_any(const WidePlan &pl, const void *X, int64_t N, int d, const
 
 template <class T>
 hipError_t pick(const WidePlan &pl, const void *X, int64_t N, int d, const void *Q, int B, int k, const float *maxima,
-                int32_t *ids, float *scores, After after, hipStream_t stream) {
+                int32_t *ids, float *scores, After after, uint64_t *best, int more, hipStream_t stream) {
     const StreamShape sh{X, Q, N, d, B};
     // a wave for one-row groups of a small corpus; else a wave per 32 rows to score and per 4096 maxima, two at least;
     // eight only where every query has a compute unit to itself
@@ -38,12 +37,17 @@ hipError_t pick(const WidePlan &pl, const void *X, int64_t N, int d, const void 
     const int threads = one && pl.n <= 2048 ? 64 : !one && little ? 128 : much && B <= pl.cus ? 512 : 256;
     const size_t lds = one ? 0 : (size_t)d * T::bytes;
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(B), dim3(threads), lds, stream, maxima, pl.n, pl.gs_log, k, ids, scores, sh, after);
+        hipLaunchKernelGGL(kernel, dim3(B), dim3(threads), lds, stream, maxima, pl.n, pl.gs_log, k, ids, scores, sh, after,
+                           best, more);
         return hipGetLastError();
     };
-    if constexpr (T::bytes == 4) return go(flat_pick_kernel<T, 0, false>);
-    else if (one) return pl.wmf == 4 ? go(flat_pick_kernel<T, 4, true>) : pl.wmf == 2 ? go(flat_pick_kernel<T, 2, true>) : go(flat_pick_kernel<T, 1, true>);
-    else return pl.wmf == 4 ? go(flat_pick_kernel<T, 4, false>) : pl.wmf == 2 ? go(flat_pick_kernel<T, 2, false>) : go(flat_pick_kernel<T, 1, false>);
+    auto parts = [&](auto pc) {
+        constexpr bool P = decltype(pc)::value;
+        if constexpr (T::bytes == 4) return go(flat_pick_kernel<T, 0, false, P>);
+        else if (one) return pl.wmf == 4 ? go(flat_pick_kernel<T, 4, true, P>) : pl.wmf == 2 ? go(flat_pick_kernel<T, 2, true, P>) : go(flat_pick_kernel<T, 1, true, P>);
+        else return pl.wmf == 4 ? go(flat_pick_kernel<T, 4, false, P>) : pl.wmf == 2 ? go(flat_pick_kernel<T, 2, false, P>) : go(flat_pick_kernel<T, 1, false, P>);
+    };
+    return more ? parts(std::true_type{}) : parts(std::false_type{});
 }
 }  // namespace
 
@@ -54,10 +58,11 @@ hipError_t launch_flat_wide(const WidePlan &pl, int dtype, const void *X, int64_
 }
 
 hipError_t launch_flat_pick(const WidePlan &pl, int dtype, const void *X, int64_t N, int d, const void *Q, int B, int k,
-                            const float *maxima, int32_t *ids, float *scores, After after, hipStream_t stream) {
-    return dtype == 0   ? pick<F16>(pl, X, N, d, Q, B, k, maxima, ids, scores, after, stream)
-           : dtype == 2 ? pick<F32>(pl, X, N, d, Q, B, k, maxima, ids, scores, after, stream)
-                        : pick<BF16>(pl, X, N, d, Q, B, k, maxima, ids, scores, after, stream);
+                            const float *maxima, int32_t *ids, float *scores, After after, uint64_t *best, int more,
+                            hipStream_t stream) {
+    return dtype == 0   ? pick<F16>(pl, X, N, d, Q, B, k, maxima, ids, scores, after, best, more, stream)
+           : dtype == 2 ? pick<F32>(pl, X, N, d, Q, B, k, maxima, ids, scores, after, best, more, stream)
+                        : pick<BF16>(pl, X, N, d, Q, B, k, maxima, ids, scores, after, best, more, stream);
 }
 
 }  // namespace ann

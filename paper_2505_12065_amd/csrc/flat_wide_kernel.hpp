@@ -196,12 +196,12 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
             const int q = n0 + (wn * WNF + j) * 32 + l32;
             if (after.s) {                                // rows at or before the query's boundary do not take part
                 const float bs = after.s[min(q, B - 1)];
-                const int bid = after.id[min(q, B - 1)];
+                const int bid = after.id[min(q, B - 1)], rafter = rbase + after.base;
                 static_for<WMF>([&](auto ic) {
                     constexpr int i = decltype(ic)::value;
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
-                        acc[i][j][r] = after_boundary(acc[i][j][r], rbase + (i * 32 + 8 * (r / 4) + (r % 4)), bs, bid);
+                        acc[i][j][r] = after_boundary(acc[i][j][r], rafter + (i * 32 + 8 * (r / 4) + (r % 4)), bs, bid);
                 });
             }
             if (q < B) {

@@ -37,7 +37,8 @@ hipError_t launch_flat_stream_f32(const StreamPlan &pl, const void *X, int64_t N
 hipError_t launch_flat_wide(const WidePlan &pl, int dtype, const void *X, int64_t N, int d, const void *Q, int B, float *maxima,
                             After after, hipStream_t stream);
 hipError_t launch_flat_pick(const WidePlan &pl, int dtype, const void *X, int64_t N, int d, const void *Q, int B, int k,
-                            const float *maxima, int32_t *ids, float *scores, After after, hipStream_t stream);
+                            const float *maxima, int32_t *ids, float *scores, After after, uint64_t *best, int more,
+                            hipStream_t stream);
 // k <= 4: merge the P lists of 4 of every query.
 hipError_t launch_flat_merge(const Cand *partial, int P, int B, int k, int32_t *ids, float *scores, hipStream_t stream);
 // k > 4: merge the P lists of K of every query, made by flat_stream_kernel with `slots` = P waves.

@@ -90,6 +90,11 @@ inline void wide_geometry(WidePlan &pl, int shape, int cus, int64_t N, int B) {
     }
 }
 
+inline int wide_rows(int shape) {                         // corpus rows of a tile
+    return shape == WIDE_LARGE ? WideLarge::BM : shape == WIDE_TALL ? WideTall::BM : shape == WIDE_SMALL ? WideSmall::BM
+           : shape == WIDE_TINY ? WideTiny::BM : WideThin::BM;
+}
+
 // ---- exact search, the whole call ----------------------------------------------------------------------
 constexpr int P_MAX = 2048;      // most slabs of the streaming kernel
 
@@ -97,15 +102,24 @@ struct FlatPlan {
     StreamPlan st;           // streaming kernel with lists, unless
     bool direct;             // ... of one slab: no merge
     bool wide;               // the matrix-core kernel, or
-    bool maxima;             // the streaming kernel with group maxima takes the call, `part` queries at a time
+    bool maxima;             // the streaming kernel with group maxima takes the call, `part` queries and `rows` rows at a time
     WidePlan w;
     int part;
+    int64_t rows;
+    size_t best_ofs;         // rows < N: where the k best so far of every query of a part stand in the workspace
     size_t ws_bytes;
 };
 
 constexpr int WIDE_MIN_B = 65;   // smallest batch sent to the matrix-core path
-// Workspace that the group maxima of one launch may take; more queries run one part after the other.
+// Workspace that the group maxima of one launch may take; a call that needs more runs one part after the other.
 constexpr size_t WIDE_WS_MAX = (size_t)1 << 30;
+// A call whose maxima do not fit takes the queries in parts, as long as those are as many as a tile has columns (fp32: as
+// keep the products ahead of the reading): every part reads the whole corpus again.  Where fewer would fit, it takes the
+// corpus in parts instead, all queries (up to PART_MAX_B) against each, and the k best so far pass from part to part: a
+// part costs two launches and a look at its maxima, some 20 us.  8 MiB of maxima, before (queries in parts of 6 to 128) /
+// now / at once, ms: 1 M x 768, B = 512 1.76 / 0.96 / 0.88; 21 M x 384, B = 128 62.5 / 3.66 / 3.59, B = 512 344 / 10.3 / 9.45.
+constexpr int PART_MIN_B = 256, PART_MIN_B_F32 = 128, PART_MAX_B = 1024;
+constexpr int64_t PART_MIN_ROWS = 8192;          // fewer are not worth a launch: the call does not fit
 
 // The streaming kernel's geometry.
 // K: see the kernel; unit: rows that go to a wave together.
@@ -142,12 +156,14 @@ inline StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int K
 // Rows per group of the matrix-core kernel, by the time of what follows the products, in us: the maxima are written and
 // read once and the rows of k groups are read again, at some 4 TB/s over all queries; one query alone waits for its
 // maxima (twice, 1024 a wave at a time) and, unless groups are single rows, for its rows (32 a wave, 192 columns at once).
-inline int wide_group_log(int cus, int wmf, int64_t N, int row_bytes, int B, int k) {
+// most: maxima of a query that there is room for; the largest groups where no size fits.
+inline int wide_group_log(int cus, int wmf, int64_t N, int row_bytes, int B, int k, size_t most) {
     const int waves = B <= cus ? 8 : 4;                   // of a query
     int best = 0;
     double least = INFINITY;
     for (int g : {0, 2, 4, 5, 6}) {
         if (wmf == 0 ? g < 4 : (1 << g) > 16 * wmf) continue;
+        if ((size_t)(N >> g) + 1 > most) { best = g; continue; }
         const double n = (double)N / (1 << g), rows = (double)k * (1 << g);
         double us = 8.0 * n * B / 4e6 + 1.6 * n / (1024 * waves);
         if (g > 0) us += rows * row_bytes * B / 4e6 + 3.0 + 1.2 * ceil(rows / (32 * waves)) * ceil(row_bytes / 384.0);
@@ -190,60 +206,98 @@ inline bool use_f32_maxima(int64_t N, int d, int B, int k) {
     return B > 16 && N >= (int64_t)10 * k * d && N * B >= (int64_t)32768 * d;
 }
 
-inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, size_t limit) {
-    FlatPlan pl{};
-    pl.st = stream_plan(cus, N, d, dtype, B, (k + 3) & ~3, 16);
-    pl.part = B;
-    if (dtype == ANN_F32 && use_f32_maxima(N, d, B, k)) {
+// One pass of pl.part queries over pl.rows rows by a kernel that leaves group maxima; `room` bytes for them if that can be.
+inline size_t maxima_pass(FlatPlan &pl, int cus, int d, int dtype, int k, size_t room) {
+    const int64_t N = pl.rows;
+    const int B = pl.part;
+    const size_t most = room / ((size_t)B * sizeof(float));
+    if (pl.wide) {
+        wide_geometry(pl.w, wide_shape(cus, N, B), cus, N, B);
+        pl.w.gs_log = wide_group_log(cus, pl.w.wmf, pl.w.slots, d * 2, B, k, most);
+        pl.w.n = pl.w.slots >> pl.w.gs_log;
+    } else {
         pl.w.cus = cus;
-        pl.w.gs_log = wide_group_log(cus, 0, N, d * 4, B, k);
-        auto groups = [&] { return (((N - 1) >> pl.w.gs_log) + 1 + 3) & ~(int64_t)3; };
-        if ((size_t)groups() * sizeof(float) * (size_t)B > limit) pl.w.gs_log = 6;
-        pl.w.n = groups();
-        const size_t fit = limit / ((size_t)pl.w.n * sizeof(float));
-        if (fit >= 1) {
-            pl.maxima = true;
-            const int64_t parts = (B + (int64_t)fit - 1) / (int64_t)fit;
-            pl.part = (int)((B + parts - 1) / parts);
-            pl.st = stream_plan(cus, N, d, dtype, pl.part, 1 << (pl.w.gs_log - 4), 1 << pl.w.gs_log);
-            pl.ws_bytes = (size_t)pl.part * (size_t)pl.w.n * sizeof(float);
-            return pl;
+        pl.w.gs_log = wide_group_log(cus, 0, N, d * 4, B, k, most);
+        pl.w.n = (((N - 1) >> pl.w.gs_log) + 1 + 3) & ~(int64_t)3;
+        pl.st = stream_plan(cus, N, d, dtype, B, 1 << (pl.w.gs_log - 4), 1 << pl.w.gs_log);
+    }
+    return (size_t)B * (size_t)pl.w.n * sizeof(float);
+}
+// The same for the last part of a call, which may be smaller: same kernel, same groups.
+inline FlatPlan maxima_part(FlatPlan pl, int64_t rows, int part, int d, int dtype) {
+    if (rows == pl.rows && part == pl.part) return pl;
+    pl.rows = rows;
+    pl.part = part;
+    if (pl.wide) {
+        wide_geometry(pl.w, pl.w.shape, pl.w.cus, rows, part);
+        pl.w.n = pl.w.slots >> pl.w.gs_log;
+    } else {
+        pl.w.n = (((rows - 1) >> pl.w.gs_log) + 1 + 3) & ~(int64_t)3;
+        pl.st = stream_plan(pl.w.cus, rows, d, dtype, part, 1 << (pl.w.gs_log - 4), 1 << pl.w.gs_log);
+    }
+    return pl;
+}
+// A call on group maxima in `limit` bytes of workspace; false if it does not fit (pl.ws_bytes: what one pass would take).
+inline bool maxima_plan(FlatPlan &pl, int cus, int64_t N, int d, int dtype, int B, int k, size_t limit) {
+    pl.rows = N;
+    pl.part = B;
+    const size_t all = pl.ws_bytes = maxima_pass(pl, cus, d, dtype, k, limit);
+    if (all <= limit) return true;
+    // queries in parts
+    const size_t fit = limit / ((size_t)pl.w.n * sizeof(float));
+    if (fit >= (size_t)(pl.wide ? PART_MIN_B : PART_MIN_B_F32)) {
+        const int parts = (int)((B + fit - 1) / fit);
+        pl.part = (B + parts - 1) / parts;
+        if (pl.part > 256 && (size_t)((pl.part + 255) & ~255) <= fit) pl.part = (pl.part + 255) & ~255;
+        while ((pl.ws_bytes = maxima_pass(pl, cus, d, dtype, k, limit)) > limit) --pl.part;   // (another tile, a few groups more)
+        return true;
+    }
+    // the corpus in parts: whole rounds of the tiles, or as many rows as fit
+    for (pl.part = B < PART_MAX_B ? B : PART_MAX_B; pl.part >= 1; pl.part /= 2) {
+        const size_t best = (size_t)pl.part * k * sizeof(uint64_t);
+        if (best >= limit) continue;
+        const size_t room = limit - best;
+        pl.rows = (int64_t)(room / ((size_t)pl.part * sizeof(float))) << 6;
+        while (pl.rows >= PART_MIN_ROWS) {
+            pl.rows = pl.rows < N ? pl.rows : N;
+            const int64_t have = pl.rows;
+            maxima_pass(pl, cus, d, dtype, k, room);
+            const int64_t round = pl.wide ? (int64_t)pl.w.P * wide_rows(pl.w.shape) : (int64_t)pl.st.P * pl.st.waves << pl.w.gs_log;
+            if (pl.rows < N) pl.rows -= pl.rows >= round ? pl.rows % round : pl.rows % 512;
+            const size_t bytes = maxima_pass(pl, cus, d, dtype, k, room);
+            if (bytes <= room) {
+                pl.best_ofs = (bytes + 7) & ~(size_t)7;
+                pl.ws_bytes = pl.best_ofs + best;
+                if (pl.ws_bytes <= limit) return true;
+            }
+            pl.rows = have / 2;                           // (groups of the tile that so few rows get are smaller)
         }
     }
+    pl.rows = N;
+    pl.part = B;
+    pl.ws_bytes = all;
+    return false;
+}
+
+inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, size_t limit) {
+    FlatPlan pl{};
+    pl.part = B;
+    pl.rows = N;
     // A corpus of one tile per wave of a workgroup: its lists are the answer, one launch instead of two (128 x 768 fp16, k = 1:
     // B = 64 13.9 -> 10.8 us, B = 512 12.4 -> 11.1; 64 x 1024, B = 8192, k = 16 23.1 -> 17.3).  Lists of 4 per lane are complete
     // there whatever k is, since a lane sees four rows; selecting k > 4 from all eight waves costs more than the launch
     // saves where the other way is group maxima (128 x 1024 bf16, B = 5000, k = 16: 19.3 / 23.3).
-    pl.direct = N <= (k <= 4 || dtype == ANN_F32 ? 128 : 64);
-    if (pl.direct) {
-        pl.st = stream_plan(cus, N, d, dtype, B, (k + 3) & ~3, 16);
-        pl.st.P = 1;
-        pl.ws_bytes = 0;
+    pl.maxima = dtype == ANN_F32 && use_f32_maxima(N, d, B, k);
+    pl.direct = !pl.maxima && N <= (k <= 4 || dtype == ANN_F32 ? 128 : 64);
+    pl.wide = !pl.direct && use_wide(N, d, dtype, B, k);
+    if (pl.wide || pl.maxima) {
+        // (does not fit: ws_bytes says so)
+        maxima_plan(pl, cus, N, d, dtype, B, k, limit);
         return pl;
     }
-    pl.wide = use_wide(N, d, dtype, B, k);
-    if (pl.wide) {
-        int shape = wide_shape(cus, N, B);
-        wide_geometry(pl.w, shape, cus, N, B);
-        pl.w.gs_log = wide_group_log(cus, pl.w.wmf, N, d * 2, B, k);
-        pl.w.n = pl.w.slots >> pl.w.gs_log;
-        const size_t per = (size_t)pl.w.n * sizeof(float);
-        if (per * (size_t)B > limit) {
-            // (large corpora: groups as large as they come)
-            pl.w.gs_log = pl.w.wmf == 4 ? 6 : pl.w.wmf == 2 ? 5 : 4;
-            pl.w.n = pl.w.slots >> pl.w.gs_log;
-            const size_t fit = limit / ((size_t)pl.w.n * sizeof(float));
-            if (fit < 1) pl.wide = false;
-            else if (fit < (size_t)B) {
-                const int parts = (int)((B + fit - 1) / fit);
-                pl.part = (B + parts - 1) / parts;
-                if (pl.part > 256 && (size_t)((pl.part + 255) & ~255) <= fit) pl.part = (pl.part + 255) & ~255;
-                wide_geometry(pl.w, shape, cus, N, pl.part);
-            }
-        }
-        pl.ws_bytes = (size_t)pl.part * (size_t)pl.w.n * sizeof(float);
-    }
-    if (!pl.wide) pl.ws_bytes = (size_t)B * pl.st.P * pl.st.K * CAND_BYTES;
+    pl.st = stream_plan(cus, N, d, dtype, B, (k + 3) & ~3, 16);
+    if (pl.direct) pl.st.P = 1;
+    else pl.ws_bytes = (size_t)B * pl.st.P * pl.st.K * CAND_BYTES;
     return pl;
 }
 

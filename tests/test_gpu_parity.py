@@ -188,6 +188,38 @@ def test_flat_group_maxima(dtype, N, d, B, k):
     assert strict >= n - max(1, n // 20), (strict, n)
 
 
+@pytest.mark.parametrize("dtype,N,d,B,k", [
+    (torch.float16, 1_100_003, 16, 512, 3),     # five parts of 262 144 rows, the last one ragged
+    (torch.bfloat16, 3_000_000, 8, 200, 16),    # long lists between the parts
+    (torch.float16, 1_048_576, 8, 1300, 1),     # parts of the batch as well, whole parts of the corpus
+    (torch.float32, 1_500_000, 8, 200, 3),      # the streaming kernel with maxima
+])
+def test_flat_corpus_in_parts(dtype, N, d, B, k):
+    """Maxima that do not fit the workspace at once: the corpus is taken in parts and the best so far go from part to part.
+    Ids and scores equal those of the call that has the room, with copies of a row in every part, rows that are no
+    numbers, and a query whose every score is none."""
+    say(f"flat corpus in parts: dtype={dtype} N={N} d={d} B={B} k={k}")
+    gen = torch.Generator(device=DEV).manual_seed(k)
+    x = torch.randn(N, d, generator=gen, device=DEV).to(dtype)
+    q = torch.randn(B, d, generator=gen, device=DEV).to(dtype)
+    x[::97] = x[5].clone()
+    q[1] = x[5]
+    x[::7, 0] = float("nan")
+    q[B // 2] = float("nan")
+    want = ann.ann_flat_search_typed(x, q, k)
+    got = ann.binding.ann_flat_search_static(x, q, k, ids=torch.empty_like(want[0]), scores=torch.empty_like(want[1]))
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    assert (got[0][B // 2] == -1).all() and torch.isneginf(got[1][B // 2]).all()
+    few = [0, 1, B - 1]
+    s = q[few].double() @ x.double().T
+    s = torch.where(s == s, s, -torch.inf)
+    top = torch.topk(s, k, dim=1).values
+    mine = torch.gather(s, 1, got[0][few].long())
+    bound = d * 2.0 ** -23 * (q[few].double().norm(dim=1) * x.double().nan_to_num().norm(dim=1).max())[:, None]
+    assert ((mine - top).abs() <= bound).all()                       # sums of d products in fp32, any order
+
+
 @pytest.mark.parametrize("dtype,k", [(torch.float16, 4), (torch.float16, 5), (torch.bfloat16, 16), (torch.float32, 16), (torch.float32, 1)])
 @pytest.mark.parametrize("N", [16, 63, 64, 65, 127, 128, 129])
 def test_flat_corpus_of_one_workgroup(dtype, N, k):

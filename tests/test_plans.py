@@ -2,7 +2,9 @@
 
 The rules choose between ways of giving the same answer, so a wrong one costs time and no test of results sees it."""
 import ctypes
+import math
 import os
+import random
 import subprocess
 
 import pytest
@@ -16,7 +18,20 @@ using namespace ann;
 extern "C" int step_pays(int cus, int64_t N, int row_bytes, int R, int B, int ef, int counters, float tau) {
     return graph_step_pays(cus, N, row_bytes, R, B, ef, counters != 0, tau);
 }
+// out: kind (0 lists, 1 direct, 2 matrix cores, 3 streaming with maxima), queries and rows at a time, maxima of a query,
+// log2 of the rows they stand for, offset of the k best so far, workspace, maxima of the smallest last part
+extern "C" void flat(int cus, int64_t N, int d, int dtype, int B, int k, int64_t limit, int64_t *out) {
+    const FlatPlan pl = flat_plan(cus, N, d, dtype, B, k, (size_t)limit);
+    const int64_t rows = N % pl.rows ? N % pl.rows : pl.rows;
+    const int part = B % pl.part ? B % pl.part : pl.part;
+    const FlatPlan last = pl.wide || pl.maxima ? maxima_part(pl, rows, part, d, dtype) : pl;
+    const int64_t v[] = {pl.wide ? 2 : pl.maxima ? 3 : pl.direct ? 1 : 0, pl.part, pl.rows, pl.w.n, pl.w.gs_log,
+                         (int64_t)pl.best_ofs, (int64_t)pl.ws_bytes, last.w.n, last.w.gs_log};
+    for (int i = 0; i < 9; ++i) out[i] = v[i];
+}
 """
+KINDS = ("lists", "direct", "wide", "maxima")
+STATIC = 8 * 1024 * 1024 + 1024 * 16 * 8             # the static workspace, room for the k best of a part's queries included
 
 
 @pytest.fixture(scope="module")
@@ -28,7 +43,14 @@ def plans(tmp_path_factory):
                     os.path.join(ROOT, "paper_2505_12065_amd", "csrc"), "-o", str(lib), str(src)], check=True)
     L = ctypes.CDLL(str(lib))
     L.step_pays.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 5 + [ctypes.c_float]
+    L.flat.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64, ctypes.c_void_p]
     return L
+
+
+def flat(L, N, d, dtype, B, k, limit):
+    out = (ctypes.c_int64 * 9)()
+    L.flat(CUS, N, d, dtype, B, k, limit, out)
+    return dict(zip(("kind", "part", "rows", "n", "gs_log", "best_ofs", "bytes", "last_n", "last_gs_log"), out))
 
 
 # one-by-one / steps as measured, where the two sides differ by more than a tenth
@@ -66,3 +88,44 @@ def test_steps_pay_up_to_a_size_of_the_graph(plans):
                     got = [bool(plans.step_pays(CUS, N, row, R, B, ef, 0, float("inf"))) for N in
                            (100, 10_000, 50_000, 200_000, 1_000_000, 10_000_000, 2**31 - 1)]
                     assert got == sorted(got, reverse=True), (row, R, B, ef)
+
+
+@pytest.mark.parametrize("N,d,dtype,B,k", [
+    (1_000_000, 768, 0, 256, 3), (1_000_000, 768, 0, 512, 3), (21_000_000, 768, 0, 256, 3), (21_000_000, 384, 0, 512, 3),
+    (21_000_000, 384, 0, 128, 3), (21_000_000, 384, 1, 66, 16), (4_000_000, 64, 2, 100, 3)])
+def test_little_workspace_takes_the_corpus_in_parts(plans, N, d, dtype, B, k):
+    """Group maxima that do not fit: every query of the batch against one part of the corpus after the other (the
+    products of a few queries against the whole corpus, again and again, took up to 50 times as long)."""
+    p = flat(plans, N, d, dtype, B, k, STATIC)
+    assert KINDS[p["kind"]] in ("wide", "maxima") and p["bytes"] <= STATIC
+    assert p["part"] == B
+    cells = 64 * 8 * 1024 * 1024 // 4                # scores whose maxima, one of 64 rows, fill the workspace
+    assert -(-N // p["rows"]) <= N * B // cells + 2
+
+
+@pytest.mark.parametrize("limit", [64 * 1024, 1 << 20, STATIC, 1 << 26, 1 << 30])
+def test_parts_stay_inside_the_workspace(plans, limit):
+    """Over the sizes the entry points take: the maxima of a part and what stands behind them fit, the last part needs no
+    more than the others and uses their groups, and every row has a maximum."""
+    rng = random.Random(limit)
+    log = lambda lo, hi: int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+    kinds = set()
+    for _ in range(4000):
+        dtype = rng.choice([0, 1, 2])
+        step = 4 if dtype == 2 else 8
+        N, d, B, k = log(1, 2**31 - 1), step * log(1, 4096 // step), log(1, 100_000), rng.randint(1, 16)
+        k = min(k, N)
+        p = flat(plans, N, d, dtype, B, k, limit)
+        if KINDS[p["kind"]] not in ("wide", "maxima") or p["bytes"] > limit:
+            continue
+        call = (N, d, dtype, B, k, p)
+        kinds.add((p["kind"], p["part"] < B, p["rows"] < N))
+        assert 1 <= p["part"] <= B and 1 <= p["rows"] <= N, call
+        assert p["n"] % 4 == 0 and p["n"] << p["gs_log"] >= p["rows"], call
+        assert p["last_gs_log"] == p["gs_log"] and p["last_n"] <= p["n"], call
+        end = p["part"] * p["n"] * 4
+        if p["rows"] < N:
+            assert p["best_ofs"] >= end and p["best_ofs"] % 8 == 0, call
+            end = p["best_ofs"] + p["part"] * k * 8
+        assert end <= p["bytes"], call
+    assert len(kinds) >= 3, kinds
