@@ -18,8 +18,9 @@
  *     ann_register_corpus.  `stream` is a hipStream_t (NULL = default stream).
  *     Work is only enqueued: results are valid once the caller has
  *     synchronised `stream`.  No entry point synchronises the device except
- *     when the library-owned workspace has to grow (first call, or a larger
- *     B*k than any call before on this device).
+ *     when the library-owned workspace has to grow (a call that needs more of it
+ *     than any before on this device; it grows by a quarter more than needed, to
+ *     1.25 GiB at most for the flat search).
  *   - One workspace per device: calls that use it (the flat search, the graph
  *     search with ef > 512, the non-stall graph search) are safe one after the
  *     other on one stream, or on several streams if the caller orders them; two
@@ -89,11 +90,14 @@ const char *ann_last_error(void);
  *   scores  device, [B, k] float  (written)
  *
  * Every corpus row is scored against every query; the score matrix is never
- * materialised.  Uses the library workspace of the current device: per query P
- * lists of 4 or 16 (score, id) pairs (P = number of corpus slabs, at most 2048) and,
- * for k > 4 on corpora of 128 Ki rows or more (at any corpus size when B > 64 and d is
- * a multiple of 32), a candidate array of 4096 pairs;
- * ann_flat_workspace_bytes gives the exact size.
+ * materialised.  Uses the library workspace of the current device, which is one of
+ *   - per query and corpus slab (at most 2048) a list of 4, 8, 12 or 16 (score, id) pairs: up to
+ *     64 queries on large corpora, few queries in fp32;
+ *   - per query the largest score of every group of 1 to 64 rows, 4 bytes each: larger batches.
+ *     That grows with N B (1 M rows, B = 512: 64 MB; 21 M rows: 672 MB); beyond 1 GiB the search
+ *     runs in parts;
+ *   - nothing: corpora of at most 128 rows.
+ * ann_flat_workspace_bytes gives the size.
  */
 int ann_flat_search_typed(const void *corpus, int64_t N, int32_t d, int32_t dtype,
                           const void *queries, int32_t B, int32_t k,
@@ -127,9 +131,12 @@ int ann_flat_search(const void *corpus, int64_t N, int32_t d,
  * same results, but the workspace is a fixed array of ANN_STATIC_WORKSPACE_BYTES that is part of
  * the library's code object (every device the library runs on holds it until the process ends),
  * and the call never allocates, frees or grows anything and records no timing events.
- *   - A search whose workspace (ann_flat_workspace_bytes) exceeds ANN_STATIC_WORKSPACE_BYTES is
- *     rejected with ANN_ERR_INVALID; nothing is enqueued.  8 MiB covers k <= 4 at any of the
- *     batch sizes used here (1 M x 768 fp16, B = 512, k = 3 needs 4.2 MB).
+ *   - A search whose group maxima (see ann_flat_search_typed) do not fit takes the corpus in parts,
+ *     about 130 M scores each, with the same result.  A part costs some 20 us (1 M x 768 fp16,
+ *     B = 512, k = 3: 4 parts, 0.96 ms against 0.88 through the allocating entry point).
+ *   - Rejected with ANN_ERR_INVALID, nothing enqueued: lists that do not fit (batches beyond some
+ *     50 000 queries); and k > 4 with B >= 256 unless one pass fits (ann_flat_workspace_bytes is at
+ *     most ANN_STATIC_WORKSPACE_BYTES).
  *   - All calls on one device share that device's array: they are safe one after the other on
  *     one stream (or ordered by the caller across streams); calls that overlap on one device
  *     race.  It does not share anything with the workspace of the other entry points.
@@ -255,13 +262,16 @@ int ann_unregister_corpus(const void *corpus);
 /* Element type assumed by ann_flat_search (process-wide; default ANN_F16). */
 int ann_set_default_dtype(int32_t dtype);
 
-/* Bytes of device workspace a flat search of this shape needs. */
+/* Bytes of device workspace a flat search of this shape uses where it has them; less makes it run in
+ * parts (see ann_set_workspace). */
 int64_t ann_flat_workspace_bytes(int64_t N, int32_t d, int32_t dtype, int32_t B, int32_t k);
 
 /* Use a caller-owned device buffer as the workspace of the current device (so that, e.g., the
  * caller's allocator owns the memory and no entry point ever allocates): every call that needs
- * workspace (ann_flat_workspace_bytes, ann_graph_nonstall_workspace_bytes) then runs in it, and one
- * that needs more than `bytes` fails with ANN_ERR_NOMEM instead of growing anything.
+ * workspace (ann_flat_workspace_bytes, ann_graph_nonstall_workspace_bytes) then runs in it.  A flat
+ * search that does not fit `bytes` at once takes the corpus in parts, or fewer slabs; one that would
+ * need parts of fewer than 8192 rows, or less than a quarter of its slabs, and a graph search that
+ * needs more than `bytes`, fail with ANN_ERR_NOMEM instead of growing anything.
  *   workspace  device pointer, 256-byte aligned, valid until it is replaced; NULL: back to the
  *              library-owned buffers.  Not freed by the library.  Calls that use it must not overlap. */
 int ann_set_workspace(void *workspace, int64_t bytes);

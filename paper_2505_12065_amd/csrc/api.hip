@@ -401,7 +401,9 @@ int ann_flat_search_after_typed(const void *corpus, int64_t N, int32_t d, int32_
     std::lock_guard<std::mutex> lock(g_mu);
     DeviceState *st = nullptr;
     if (int rc = device_state(&st)) return rc;
-    const FlatPlan pl = flat_plan(st->cus, N, d, dtype, B, k, WIDE_WS_MAX);
+    // (in a caller's buffer: in parts if it does not hold the whole)
+    const size_t limit = st->user_ws && st->user_bytes < WIDE_WS_MAX ? st->user_bytes : WIDE_WS_MAX;
+    const FlatPlan pl = flat_plan(st->cus, N, d, dtype, B, k, limit);
     void *ws = nullptr;
     if (int rc = workspace_for(st, &st->ws, &st->ws_bytes, pl.ws_bytes, &ws)) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -426,8 +428,7 @@ int ann_flat_search_static(const void *corpus, int64_t N, int32_t d, int32_t dty
     std::lock_guard<std::mutex> lock(g_mu);
     DeviceState *st = nullptr;
     if (int rc = device_state(&st)) return rc;
-    // A search that the array does not hold at once runs in parts of as many queries as it does; a batch of 256 and more
-    // with k > 4 is refused instead, as ann.h says.
+    // A search that the array does not hold at once runs in parts; a batch of 256 and more with k > 4 is refused instead.
     FlatPlan pl = flat_plan(st->cus, N, d, dtype, B, k, WIDE_WS_MAX);
     if (pl.ws_bytes > (size_t)ANN_STATIC_WORKSPACE_BYTES && (k <= 4 || B < 256)) {
         const FlatPlan parts = flat_plan(st->cus, N, d, dtype, B, k, STATIC_BYTES);

@@ -296,8 +296,14 @@ inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, si
         return pl;
     }
     pl.st = stream_plan(cus, N, d, dtype, B, (k + 3) & ~3, 16);
-    if (pl.direct) pl.st.P = 1;
-    else pl.ws_bytes = (size_t)B * pl.st.P * pl.st.K * CAND_BYTES;
+    if (pl.direct) {
+        pl.st.P = 1;
+        return pl;
+    }
+    // lists that do not fit: fewer slabs, down to a quarter of those that fill the chip
+    const size_t slab = (size_t)B * pl.st.K * CAND_BYTES, fit = limit / slab;
+    if (fit < (size_t)pl.st.P && fit >= 1 && 4 * fit >= (size_t)pl.st.P) pl.st.P = (int)fit;
+    pl.ws_bytes = slab * pl.st.P;
     return pl;
 }
 

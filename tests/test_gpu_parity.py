@@ -371,6 +371,40 @@ def test_caller_owned_workspace():
     assert torch.equal(again[0], want[0])
 
 
+@pytest.mark.parametrize("dtype,N,d,B,k,size", [
+    (torch.float16, 300_007, 64, 300, 5, 1 << 20),      # the corpus in parts
+    (torch.bfloat16, 9_000, 64, 400, 16, 200_000),      # larger groups
+    (torch.float16, 100_000, 336, 20, 16, 700_000),     # lists of fewer slabs
+    (torch.float32, 60_000, 16, 70, 3, 1 << 17),        # fp32 maxima, the batch in parts as well
+])
+def test_flat_in_a_small_buffer_of_the_caller(dtype, N, d, B, k, size):
+    """A caller's buffer that does not hold the workspace of one pass: the same answers, two pages, and nothing outside
+    the buffer is touched."""
+    say(f"flat small buffer: dtype={dtype} N={N} d={d} B={B} k={k} bytes={size}")
+    gen = torch.Generator(device=DEV).manual_seed(size)
+    x = torch.randn(N, d, generator=gen, device=DEV).to(dtype)
+    x[N // 2: N // 2 + N // 4] = x[: N // 4].clone()
+    q = torch.randn(B, d, generator=gen, device=DEV).to(dtype)
+    assert ann.ann_flat_workspace_bytes(N, d, dtype, B, k) > size
+
+    def pages():
+        first = ann.ann_flat_search_typed(x, q, k)
+        second = ann.ann_flat_search_typed(x, q, k, after=(first[1][:, -1].contiguous(), first[0][:, -1].contiguous()))
+        return first + second
+
+    want = pages()
+    buf = torch.full((size + 4096,), 0xAB, dtype=torch.uint8, device=DEV)
+    try:
+        ann.ann_set_workspace(buf[:size])
+        got = pages()
+        torch.cuda.synchronize()
+    finally:
+        ann.ann_set_workspace(None)
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+    assert bool((buf[size:] == 0xAB).all()) and bool((buf[:1024] != 0xAB).any())
+
+
 def test_flat_is_deterministic():
     c = synth.make_corpus(50_000, 768, 32, seed=21, dtype=torch.float16)
     q = synth.make_queries(c, 48)

@@ -129,3 +129,17 @@ def test_parts_stay_inside_the_workspace(plans, limit):
             end = p["best_ofs"] + p["part"] * k * 8
         assert end <= p["bytes"], call
     assert len(kinds) >= 3, kinds
+
+
+# bytes: what the library asked for when it kept lists and candidate arrays, so buffers that callers have
+@pytest.mark.parametrize("N,d,dtype,B,k,buffer", [
+    (1_000_000, 768, 0, 512, 3, 4_212_736), (1_000_000, 768, 0, 65, 3, 1_194_180), (200_000, 768, 0, 100, 10, 6_186_400),
+    (21_000_000, 384, 0, 512, 3, 4_212_736), (4092, 2128, 0, 1043, 15, 4_272_128), (459, 1488, 0, 4853, 12, 2_484_736),
+    (2839, 40, 0, 743, 9, 2_187_392), (1_000_000, 128, 2, 256, 10, 33_554_432), (100_000, 768, 0, 16, 16, 401_408)])
+def test_a_buffer_that_served_still_serves(plans, N, d, dtype, B, k, buffer):
+    assert flat(plans, N, d, dtype, B, k, buffer)["bytes"] <= buffer
+
+
+def test_a_buffer_too_small_for_parts_is_refused(plans):
+    for N, d, dtype, B, k in ((40_000, 256, 0, 96, 3), (1_000_000, 768, 0, 512, 3), (1_000_000, 768, 0, 16, 3)):
+        assert flat(plans, N, d, dtype, B, k, 256)["bytes"] > 256
