@@ -136,7 +136,8 @@ int ann_flat_search(const void *corpus, int64_t N, int32_t d,
  *     B = 512, k = 3: 4 parts, 0.96 ms against 0.88 through the allocating entry point).
  *   - Rejected with ANN_ERR_INVALID, nothing enqueued: lists that do not fit (batches beyond some
  *     50 000 queries); and k > 4 with B >= 256 unless one pass fits (ann_flat_workspace_bytes is at
- *     most ANN_STATIC_WORKSPACE_BYTES).
+ *     most ANN_STATIC_WORKSPACE_BYTES) or: fp32 with B min(ceil(N / 32), 1024) <= 65536; 16 bits,
+ *     N < 128 Ki and d no multiple of 32, with B min(ceil(N / 128), 128) <= 65536.
  *   - All calls on one device share that device's array: they are safe one after the other on
  *     one stream (or ordered by the caller across streams); calls that overlap on one device
  *     race.  It does not share anything with the workspace of the other entry points.

@@ -428,12 +428,7 @@ int ann_flat_search_static(const void *corpus, int64_t N, int32_t d, int32_t dty
     std::lock_guard<std::mutex> lock(g_mu);
     DeviceState *st = nullptr;
     if (int rc = device_state(&st)) return rc;
-    // A search that the array does not hold at once runs in parts; a batch of 256 and more with k > 4 is refused instead.
-    FlatPlan pl = flat_plan(st->cus, N, d, dtype, B, k, WIDE_WS_MAX);
-    if (pl.ws_bytes > (size_t)ANN_STATIC_WORKSPACE_BYTES && (k <= 4 || B < 256)) {
-        const FlatPlan parts = flat_plan(st->cus, N, d, dtype, B, k, STATIC_BYTES);
-        if (parts.ws_bytes <= STATIC_BYTES) pl = parts;
-    }
+    const FlatPlan pl = static_plan(st->cus, N, d, dtype, B, k, STATIC_BYTES);
     if (pl.ws_bytes > STATIC_BYTES)
         return fail(ANN_ERR_INVALID, "this search needs %zu bytes of workspace, the static one holds %d",
                     pl.ws_bytes, ANN_STATIC_WORKSPACE_BYTES);

@@ -307,6 +307,25 @@ inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, si
     return pl;
 }
 
+// Long answers of large batches that the static workspace takes though one pass does not fit it.  They once needed a list of 16
+// pairs per slab or a candidate array per query; callers go by the error that the latter gave, so the line stays where it was
+// (for a 16-bit corpus of over 32 Ki rows, where slabs depended on d, at the fewest there were).
+inline bool static_takes_long(int64_t N, int d, int dtype, int B) {
+    if (dtype != ANN_F32 && (d % 32 == 0 || N >= 128 * 1024)) return false;
+    const int64_t rows = dtype == ANN_F32 ? 32 : 128, most = dtype == ANN_F32 ? 1024 : 128, slabs = (N + rows - 1) / rows;
+    return (slabs < most ? slabs : most) * B * 16 * (int64_t)CAND_BYTES <= ANN_STATIC_WORKSPACE_BYTES;
+}
+// The plan of a call on the static workspace of `bytes` bytes, ANN_STATIC_WORKSPACE_BYTES and room for the best so far behind
+// them; ws_bytes > bytes: refused.
+inline FlatPlan static_plan(int cus, int64_t N, int d, int dtype, int B, int k, size_t bytes) {
+    if (k > 4 && B >= 256 && !static_takes_long(N, d, dtype, B)) {
+        FlatPlan pl = flat_plan(cus, N, d, dtype, B, k, WIDE_WS_MAX);
+        if (pl.ws_bytes > (size_t)ANN_STATIC_WORKSPACE_BYTES && pl.ws_bytes <= bytes) pl.ws_bytes = bytes + 1;
+        return pl;
+    }
+    return flat_plan(cus, N, d, dtype, B, k, bytes);
+}
+
 // ---- graph search ---------------------------------------------------------------------------------------
 constexpr int GRAPH_THREADS = 256;
 constexpr int GRAPH_WAVES = GRAPH_THREADS / WAVE;

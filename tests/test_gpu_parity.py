@@ -405,6 +405,17 @@ def test_flat_in_a_small_buffer_of_the_caller(dtype, N, d, B, k, size):
     assert bool((buf[size:] == 0xAB).all()) and bool((buf[:1024] != 0xAB).any())
 
 
+@pytest.mark.parametrize("N,d,B,k", [(2839, 40, 743, 9), (459, 1488, 4853, 12), (4092, 2128, 1043, 15)])
+def test_static_entry_takes_long_answers_of_narrow_corpora(N, d, B, k):
+    say(f"static long answers: N={N} d={d} B={B} k={k}")
+    gen = torch.Generator(device=DEV).manual_seed(N)
+    x, q = (torch.randn(n, d, generator=gen, device=DEV).half() for n in (N, B))
+    want = ann.ann_flat_search_typed(x, q, k)
+    got = ann.binding.ann_flat_search_static(x, q, k, ids=torch.empty_like(want[0]), scores=torch.empty_like(want[1]))
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
 def test_flat_is_deterministic():
     c = synth.make_corpus(50_000, 768, 32, seed=21, dtype=torch.float16)
     q = synth.make_queries(c, 48)

@@ -29,6 +29,9 @@ extern "C" void flat(int cus, int64_t N, int d, int dtype, int B, int k, int64_t
                          (int64_t)pl.best_ofs, (int64_t)pl.ws_bytes, last.w.n, last.w.gs_log};
     for (int i = 0; i < 9; ++i) out[i] = v[i];
 }
+extern "C" int static_accepts(int cus, int64_t N, int d, int dtype, int B, int k, int64_t bytes) {
+    return static_plan(cus, N, d, dtype, B, k, (size_t)bytes).ws_bytes <= (size_t)bytes;
+}
 """
 KINDS = ("lists", "direct", "wide", "maxima")
 STATIC = 8 * 1024 * 1024 + 1024 * 16 * 8             # the static workspace, room for the k best of a part's queries included
@@ -44,6 +47,7 @@ def plans(tmp_path_factory):
     L = ctypes.CDLL(str(lib))
     L.step_pays.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 5 + [ctypes.c_float]
     L.flat.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64, ctypes.c_void_p]
+    L.static_accepts.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64]
     return L
 
 
@@ -143,3 +147,12 @@ def test_a_buffer_that_served_still_serves(plans, N, d, dtype, B, k, buffer):
 def test_a_buffer_too_small_for_parts_is_refused(plans):
     for N, d, dtype, B, k in ((40_000, 256, 0, 96, 3), (1_000_000, 768, 0, 512, 3), (1_000_000, 768, 0, 16, 3)):
         assert flat(plans, N, d, dtype, B, k, 256)["bytes"] > 256
+
+
+@pytest.mark.parametrize("N,d,dtype,B,k,accepted", [
+    (2839, 40, 0, 743, 9, True), (459, 1488, 0, 4853, 12, True), (4092, 2128, 0, 1043, 15, True),
+    (1_000_000, 768, 0, 512, 4, True), (21_000_000, 768, 1, 255, 16, True), (1000, 64, 2, 512, 10, True),
+    (200_000, 64, 0, 2048, 10, False), (1_000_000, 768, 0, 512, 5, False), (1_000_000, 128, 2, 256, 10, False),
+    (16_384, 40, 0, 512, 9, True), (127_999, 40, 0, 2048, 16, False)])
+def test_what_the_static_workspace_takes(plans, N, d, dtype, B, k, accepted):
+    assert bool(plans.static_accepts(CUS, N, d, dtype, B, k, STATIC)) == accepted
