@@ -283,12 +283,15 @@ int ann_release_workspace(void);
 /* Kernel timing for benchmarks (measurement support, no paper passage).  While it is on,
  * every launch of a main kernel is bracketed by a pair of HIP events recorded on the
  * call's own stream, so a benchmark can report a kernel's average duration without a
- * profiler and without synchronising between calls.  The small helper kernels of a call
- * (merges, the sampling pass, clearing) are not bracketed. */
-#define ANN_KERNEL_FLAT_STREAM 0   /* flat search, streaming kernel (small batches) */
-#define ANN_KERNEL_FLAT_WIDE   1   /* flat search, matrix-core kernel (main pass) */
+ * profiler and without synchronising between calls.  The main kernel of a flat search is
+ * the one that reads the corpus, of a graph search the search itself; what merges, picks or
+ * clears beside it is not bracketed.  A search in parts is one launch, and one record, per part.
+ * Records go by the class of the call, which its arguments tell, and not by which kernel the
+ * library runs for its sizes. */
+#define ANN_KERNEL_FLAT_STREAM 0   /* flat search, 16 bits: at most 64 queries, or d no multiple of 32 */
+#define ANN_KERNEL_FLAT_WIDE   1   /* flat search, 16 bits: 65 queries and more, d a multiple of 32 */
 #define ANN_KERNEL_FLAT_F32    2   /* flat search, fp32 corpus */
-#define ANN_KERNEL_GRAPH       3   /* graph search, either variant */
+#define ANN_KERNEL_GRAPH       3   /* graph search */
 #define ANN_KERNEL_COUNT       4
 
 /* on != 0: drop earlier records and start recording; on == 0: stop (records are kept). */

@@ -132,8 +132,8 @@ hipEvent_t pooled_event() {
 struct TimedScope {
     hipStream_t stream;
     int index = -1;
-    TimedScope(int kernel, hipStream_t s) : stream(s) {     // kernel < 0: not recorded
-        if (!g_timing || g_timing_off || kernel < 0) return;
+    TimedScope(int kernel, hipStream_t s) : stream(s) {
+        if (!g_timing || g_timing_off) return;
         TimedLaunch t{pooled_event(), pooled_event(), kernel};
         if (!t.a || !t.b) return;
         if (hipEventRecord(t.a, stream) != hipSuccess) { (void)hipGetLastError(); return; }
@@ -173,7 +173,7 @@ int check_common(const void *corpus, int64_t N, int32_t d, int32_t dtype, const 
 
 int flat_search_run(const FlatPlan &pl, const void *X, int64_t N, int d, int dtype, const void *Q, int B, int k,
                     int32_t *ids, float *scores, void *ws, After after, hipStream_t stream) {
-    // (launches are recorded by what the caller asked for: fp32, or the batch class whose kernel this is or stands in for)
+    // launches are recorded by the class of the call, as ann.h lists them, not by the kernel that its sizes choose
     const int code = dtype == ANN_F32 ? ANN_KERNEL_FLAT_F32
                      : B >= WIDE_MIN_B && d % 32 == 0 ? ANN_KERNEL_FLAT_WIDE : ANN_KERNEL_FLAT_STREAM;
     StreamOut direct;
@@ -197,7 +197,7 @@ int flat_search_run(const FlatPlan &pl, const void *X, int64_t N, int d, int dty
                 const FlatPlan one = maxima_part(pl, rows, b, d, dtype);
                 hipError_t e;
                 {
-                    TimedScope timed(q0 == 0 && r0 == 0 ? code : -1, stream);
+                    TimedScope timed(code, stream);
                     e = one.wide ? launch_flat_wide(one.w, dtype, x, rows, d, q, b, maxima, a, stream)
                                  : stream_kernel(one, x, rows, q, b, nullptr, maxima, a);
                 }

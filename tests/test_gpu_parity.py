@@ -405,6 +405,25 @@ def test_flat_in_a_small_buffer_of_the_caller(dtype, N, d, B, k, size):
     assert bool((buf[size:] == 0xAB).all()) and bool((buf[:1024] != 0xAB).any())
 
 
+def test_flat_timing_records_every_part():
+    """A search in parts leaves a record per part (here 7 of 43 520 rows), all under the code of its class of calls."""
+    N, d, B, k, size = 300_007, 64, 300, 5, 1 << 20
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    x, q = (torch.randn(n, d, generator=gen, device=DEV).half() for n in (N, B))
+    codes = (ann.binding.KERNEL_FLAT_STREAM, ann.binding.KERNEL_FLAT_WIDE, ann.binding.KERNEL_FLAT_F32)
+    buf = torch.empty(size, dtype=torch.uint8, device=DEV)
+    try:
+        ann.ann_set_workspace(buf)
+        ann.ann_timing_enable(True)
+        ann.ann_flat_search_typed(x, q, k)
+        assert [ann.ann_timing_read(c)[0] for c in codes] == [0, 7, 0]
+        each = ann.ann_timing_read_each(codes[1])
+        assert len(each) == 7 and all(ms > 0 for ms in each)
+    finally:
+        ann.ann_timing_enable(False)
+        ann.ann_set_workspace(None)
+
+
 @pytest.mark.parametrize("N,d,B,k", [(2839, 40, 743, 9), (459, 1488, 4853, 12), (4092, 2128, 1043, 15)])
 def test_static_entry_takes_long_answers_of_narrow_corpora(N, d, B, k):
     say(f"static long answers: N={N} d={d} B={B} k={k}")
