@@ -89,7 +89,11 @@ __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *_
             mn = (double)part_i[m >> 1];
             mx = (double)part_i[2 + (m >> 1)];
         }
-        thr[e] = __dadd_rn(mn, __dmul_rn((double)j / (double)G, mx - mn));
+        {
+#pragma clang fp contract(off)                                          // (__dmul_rn and __dadd_rn do not keep the two from being fused)
+            const double part = (double)j / (double)G * (mx - mn);
+            thr[e] = mn + part;
+        }
     }
     __syncthreads();
     // levels of NU requests at once: the thresholds are read once for all of them

@@ -1017,6 +1017,21 @@ def test_priority_order_matches_oracle(n, G):
     assert np.array_equal(order.cpu().numpy(), o_order)
 
 
+@pytest.mark.parametrize("G,low,high", [(6, 0.1, 59.9), (7, 0.1, 59.9), (13, 5.0, 65.0), (29, 5.0, 65.0), (31, 1 / 3, 41.7)])
+def test_priority_values_on_thresholds(G, low, high):
+    """Waiting times that are thresholds: the product and the sum are rounded once each, a fused multiply-add would put
+    some of these on the other side."""
+    W = low + (np.arange(G + 1) / G) * (high - low)
+    W[G] = high
+    n = W.size
+    R, C, Wcur = np.zeros(n, np.int32), np.full(n, 100, np.int32), np.zeros(n)
+    level, order = ann.ann_priority_order(torch.from_numpy(R).to(DEV), torch.from_numpy(W).to(DEV),
+                                          torch.from_numpy(C).to(DEV), torch.from_numpy(Wcur).to(DEV), G)
+    torch.cuda.synchronize()
+    o_level, o_order = oracle.priority_order(R, W, C, Wcur, G)
+    assert np.array_equal(level.cpu().numpy(), o_level) and np.array_equal(order.cpu().numpy(), o_order)
+
+
 def test_priority_order_with_nan_queueing_times():
     n = 700
     gen = np.random.default_rng(8)
