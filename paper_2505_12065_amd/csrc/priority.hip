@@ -23,7 +23,7 @@ constexpr int PRIO_WAVES = PRIO_THREADS / WAVE;
 // request at a time of the n to compare with and tests it against all of them, so the n^2 comparisons are spread
 // over the whole chip instead of one thread walking all n; the comparisons are made on a 64-bit image of the
 // queueing time that orders like the number.  n = 3000, G = 6: 300 us a call before (two launches, 290 of it the
-// walk), 13.4 us now, which is the host's share of the call (the same for n = 32); n = 16384: 82 us, bound by the
+// walk), 11.8 us now (8.4 for n = 32, the host's share of a call); n = 16384: 1590 -> 76 us, bound by the
 // comparisons.
 constexpr int PRIO_TILE = 16;
 
@@ -34,6 +34,14 @@ __device__ __forceinline__ uint64_t wait_key(double w) {
     return (b >> 63) ? ~b : b | 0x8000000000000000ull;
 }
 
+// MANY (more than PRIO_FEW levels): a request's level is looked up instead of tried level by level, log2(G) steps per metric.  The thresholds of a
+// metric never descend with j (j / G, the product with a difference that is not negative and the sum each round
+// monotonically; where an extreme is infinite they are all infinite or all NaN), so the largest j passed is found by halving
+// and the level is the largest over the three metrics.  Every workgroup looks at all n requests, so level by level costs
+// n^2 G / 16 tests.  Level by level / halving, us: n = 256, G = 32 12.4 / 13.4, G = 64 17.4 / 14.8, G = 1024 161 / 20.6; n = 3000,
+// G = 32 19.0 / 20.9, G = 64 27.5 / 23.2, G = 1024 285 / 34.4; n = 65 536, G = 32 1764 / 1659, G = 1024 33 100 / 3470.
+constexpr int PRIO_FEW = 32;
+template <bool MANY>
 __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *__restrict__ R, const double *__restrict__ W,
                                                                 const int32_t *__restrict__ C,
                                                                 const double *__restrict__ Wcur, int n, int G,
@@ -101,6 +109,24 @@ __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *_
         constexpr int NU = decltype(nu)::value;
 #pragma unroll
         for (int u = 0; u < NU; ++u) l[u] = 0;                           // (level 0 needs no threshold passed)
+        if constexpr (MANY) {
+#pragma unroll
+            for (int m = 0; m < 3; ++m) {
+                int at[NU];
+#pragma unroll
+                for (int u = 0; u < NU; ++u) at[u] = 0;
+                for (int h = 1 << (31 - __builtin_clz(G - 1)); h > 0; h >>= 1)
+#pragma unroll
+                    for (int u = 0; u < NU; ++u) {
+                        const double x = m == 0 ? (double)r[u] : m == 1 ? w[u] : (double)c[u];
+                        const int j = at[u] + h;
+                        at[u] = j < G && x > thr[min(j, G - 1) * 3 + m] ? j : at[u];
+                    }
+#pragma unroll
+                for (int u = 0; u < NU; ++u) l[u] = max(l[u], at[u]);
+            }
+            return;
+        }
 #pragma unroll 2
         for (int j = 1; j < G; ++j) {
             const double tr = thr[j * 3], tw = thr[j * 3 + 1], tc = thr[j * 3 + 2];
@@ -183,7 +209,7 @@ __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *_
 
 hipError_t launch_priority(const int32_t *R, const double *W, const int32_t *C, const double *Wcur, int n, int G,
                            int32_t *level, int32_t *order, hipStream_t stream) {
-    hipLaunchKernelGGL(priority_kernel, dim3((n + PRIO_TILE - 1) / PRIO_TILE), dim3(PRIO_THREADS), (size_t)G * 3 * sizeof(double),
+    hipLaunchKernelGGL((G > PRIO_FEW ? priority_kernel<true> : priority_kernel<false>), dim3((n + PRIO_TILE - 1) / PRIO_TILE), dim3(PRIO_THREADS), (size_t)G * 3 * sizeof(double),
                        stream, R, W, C, Wcur, n, G, level, order);
     return hipGetLastError();
 }

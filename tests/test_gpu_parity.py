@@ -1017,6 +1017,36 @@ def test_priority_order_matches_oracle(n, G):
     assert np.array_equal(order.cpu().numpy(), o_order)
 
 
+@pytest.mark.parametrize("n,G", [(700, 32), (700, 33), (513, 64), (300, 65), (1000, 1023), (40, 1024)])
+@pytest.mark.parametrize("W", ["plain", "on thresholds", "inf", "nan", "huge", "equal"])
+def test_priority_many_levels(n, G, W):
+    """Around the number of levels from which they are looked up by halving: values on thresholds, metrics without a
+    range, and metrics whose range is not a finite number."""
+    gen = np.random.default_rng(n + G)
+    R = gen.integers(0, 9, n).astype(np.int32) * (W != "equal")
+    C = gen.integers(64, 8192, n).astype(np.int32)
+    w = gen.random(n) * 60.0
+    if W == "on thresholds":
+        w = 5.0 + (gen.integers(0, G, n) / G) * (65.0 - 5.0)
+        w[:2] = 5.0, 65.0
+    elif W == "inf":
+        w[gen.random(n) < 0.1] = np.inf
+    elif W == "nan":
+        w[gen.random(n) < 0.3] = np.nan
+    elif W == "huge":
+        w = (w - 30.0) * 5e306                                       # the range overflows
+    elif W == "equal":
+        w[:] = 3.0
+    Wcur = np.round(gen.random(n) * 5.0, 1)
+    R = R.astype(np.int32)
+    level, order = ann.ann_priority_order(torch.from_numpy(R).to(DEV), torch.from_numpy(w).to(DEV),
+                                          torch.from_numpy(C).to(DEV), torch.from_numpy(Wcur).to(DEV), G)
+    torch.cuda.synchronize()
+    o_level, o_order = oracle.priority_order(R, w, C, Wcur, G)
+    assert np.array_equal(level.cpu().numpy(), o_level)
+    assert np.array_equal(order.cpu().numpy(), o_order)
+
+
 @pytest.mark.parametrize("G,low,high", [(6, 0.1, 59.9), (7, 0.1, 59.9), (13, 5.0, 65.0), (29, 5.0, 65.0), (31, 1 / 3, 41.7)])
 def test_priority_values_on_thresholds(G, low, high):
     """Waiting times that are thresholds: the product and the sum are rounded once each, a fused multiply-add would put
