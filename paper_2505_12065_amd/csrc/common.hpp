@@ -76,17 +76,6 @@ struct TopList {
         s[0] = before[0] ? v : s[0];
         id[0] = before[0] ? vid : id[0];
     }
-    // merge with the list held by lane (lane ^ mask); the two lists must hold
-    // different ids (empty slots aside), nothing is de-duplicated
-    __device__ __forceinline__ void merge_xor(int mask) {
-        float ps[KP];
-        int pid[KP];
-#pragma unroll
-        for (int i = 0; i < KP; ++i) { ps[i] = __shfl_xor(s[i], mask); pid[i] = __shfl_xor(id[i], mask); }
-#pragma unroll
-        for (int i = 0; i < KP; ++i)
-            if (admits(ps[i], pid[i])) insert(ps[i], pid[i]);
-    }
 };
 
 // ---- selection across lanes ------------------------------------------------------------------
@@ -223,44 +212,13 @@ __device__ __forceinline__ u4 load_chunk(const void *p) { return *reinterpret_ca
 
 __device__ __forceinline__ u4 zero_chunk() { u4 z = {0u, 0u, 0u, 0u}; return z; }
 
-// acc + <x, q> over one 16-byte chunk of each operand, fp32 accumulation,
-// products formed exactly (16-bit inputs) or by fp32 FMA.
-template <class T>
-__device__ __forceinline__ float dot_chunk(u4 x, u4 q, float acc);
-
-// 16-bit inputs: v_dot2c_f32_{f16,bf16}, two exact products added to the fp32 accumulator per
-// instruction (four instructions per chunk instead of eight conversions and eight FMAs).
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 
-template <>
-__device__ __forceinline__ float dot_chunk<F16>(u4 x, u4 q, float acc) {
-    const h8 a = __builtin_bit_cast(h8, x), b = __builtin_bit_cast(h8, q);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        acc = __builtin_amdgcn_fdot2(h2{a[2 * i], a[2 * i + 1]}, h2{b[2 * i], b[2 * i + 1]}, acc, false);
-    return acc;
-}
-
-template <>
-__device__ __forceinline__ float dot_chunk<BF16>(u4 x, u4 q, float acc) {
-    const b8 a = __builtin_bit_cast(b8, x), b = __builtin_bit_cast(b8, q);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        acc = __builtin_amdgcn_fdot2_f32_bf16(bf2{a[2 * i], a[2 * i + 1]}, bf2{b[2 * i], b[2 * i + 1]}, acc, false);
-    return acc;
-}
-
-template <>
-__device__ __forceinline__ float dot_chunk<F32>(u4 x, u4 q, float acc) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc = fmaf(__uint_as_float(x[i]), __uint_as_float(q[i]), acc);
-    return acc;
-}
-
-// The same with four accumulators, one per 4 bytes of the chunk: four independent chains, for
-// callers whose lanes add up many chunks one after the other (a dependent chain of dot
-// instructions issues several times slower than independent ones).  The caller adds the four.
+// acc + <x, q> over one 16-byte chunk of each operand, fp32 accumulation: 16-bit inputs by v_dot2c_f32_{f16,bf16}, two exact
+// products added to the fp32 accumulator per instruction, fp32 by FMA.  Four accumulators, one per 4 bytes of the chunk:
+// four independent chains (a dependent chain of dot instructions issues several times slower than independent ones), for
+// lanes that add up many chunks one after the other.  The caller adds the four.
 template <class T>
 __device__ __forceinline__ void dot_chunk4(u4 x, u4 q, f4 &acc);
 
