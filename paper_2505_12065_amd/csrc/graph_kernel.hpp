@@ -252,6 +252,150 @@ struct RowScorer {
     }
 };
 
+// ---- the two-level list (search ranges beyond GRAPH_EF_TWO_LEVEL): parts that both kernels use -----------------
+// A list of thousands of entries is not moved for every insertion.  It is kept as a large part M (ordered, rewritten only by a
+// rebuild) and a small part D (ordered, at most GRAPH_DELTA entries, double-buffered); the candidate list of the method
+// is the merge of the two, cut at ef entries.
+
+// m1 <- first position >= from whose bit is set among the mlen bits of um, -1 if there is none; the same in all lanes.
+// (By reference: as the value returned it cost the step kernel 1.5 % with long lists.)
+__device__ __forceinline__ void first_unexpanded(const uint64_t *um, int mlen, int from, int lane, int &m1) {
+    m1 = -1;
+    const int nw = (mlen + 63) >> 6;
+    // (as a rule the next one is a few entries further on, in the word that holds `from`: that word alone is read
+    // first, by all lanes at once)
+    if ((from >> 6) < nw) {
+        uint64_t word = um[from >> 6] & (~0ull << (from & 63));
+        if ((from >> 6) == nw - 1 && (mlen & 63) != 0) word &= (1ull << (mlen & 63)) - 1ull;
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)word);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(word >> 32));
+        const uint64_t wu = ((uint64_t)hi << 32) | lo;
+        if (wu != 0) { m1 = (from & ~63) + __builtin_ctzll(wu); return; }
+        from = (from | 63) + 1;
+    }
+    for (int w0 = from >> 6; w0 < nw; w0 += WAVE) {
+        const int w = w0 + lane;
+        uint64_t word = w < nw ? um[w] : 0ull;
+        if (w == (from >> 6)) word &= ~0ull << (from & 63);
+        if (w == nw - 1 && (mlen & 63) != 0) word &= (1ull << (mlen & 63)) - 1ull;
+        const uint64_t any = __builtin_amdgcn_ballot_w64(word != 0);
+        if (any != 0) {
+            const int l = __builtin_ctzll(any);
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)word, l);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(word >> 32), l);
+            m1 = (w0 + l) * 64 + __builtin_ctzll(((uint64_t)hi << 32) | lo);
+            break;
+        }
+    }
+}
+
+// How many of the `pend` worst entries of M and D together M loses (D loses the rest): lane j reads M's and D's j-th entries
+// from the end (a_s, a_v; t_s, t_v: the first that stay are lane M's loss of the one and lane D's loss of the other); lane
+// j < pend asks whether M's is among the pend worst, i.e. whether fewer than pend - j entries of D are worse than it (it
+// reads that entry of D as well); the count of such lanes is the answer.  All in one round trip.
+struct ListTails {
+    float a_s, t_s;
+    int a_v, t_v;
+};
+__device__ __forceinline__ int tail_of_m(const float *Ms, const uint32_t *Mi, int mlen, const float *ds, const uint32_t *di, int len,
+                                         int pend, int lane, ListTails &t) {
+    const int ia = mlen - 1 - lane, it = len - 1 - lane, ix = len - pend + lane;
+    t.a_s = Ms[max(ia, 0)];
+    t.a_v = (int)(Mi[max(ia, 0)] & ~EXPANDED);
+    t.t_s = ds[max(it, 0)];
+    t.t_v = (int)(di[max(it, 0)] & ~EXPANDED);
+    const int ixc = min(max(ix, 0), GRAPH_DELTA - 1);
+    const float x_s = ds[ixc];
+    const int x_v = (int)(di[ixc] & ~EXPANDED);
+    const bool c = lane < pend && ia >= 0 && (ix < 0 || precedes(x_s, x_v, t.a_s, t.a_v));
+    return __builtin_popcountll(__builtin_amdgcn_ballot_w64(c));
+}
+
+// M <- merge of M (mlen entries) and D (dn entries, ds / di), in place; um <- M's new bits.  At most ef entries in all: the
+// tails have been cut.  Returns the lowest position that changed.  Thread t places D's entry t: its final position
+// is (entries of M that precede it) + t.  Those positions are marked in a bit per final position
+// (the words of um from the lowest marked position's block on: um is rewritten there
+// anyway), with the number of marks before every word beside it; then every final position,
+// a block at a time from the top down, takes D's entry (rank) if marked and M's entry
+// (position - rank) if not.  Its sources lie at most GRAPH_DELTA below it, so one barrier between the
+// reads and the writes of a block suffices.  The expanded flags travel with the ids and give
+// the new bits of um.  os, oi: D's other buffer, scratch here; word: one int of LDS.  Ends with a barrier: D and its other
+// buffer have been read.
+__device__ __forceinline__ int rebuild_list(float *Ms, uint32_t *Mi, uint64_t *um, int mlen, const float *ds, const uint32_t *di, int dn,
+                                            float *os, uint32_t *oi, int *word_lds, int tid) {
+    constexpr int NT = GRAPH_THREADS, BLOCK = 4 * NT;
+    static_assert(NT >= GRAPH_DELTA && BLOCK >= 2 * GRAPH_DELTA, "a thread per entry of D; sources stay within two blocks");
+    static_assert(NT >= 16384 / 64, "a thread per word of um");
+    const int lane = tid & (WAVE - 1), wave = tid >> 6;
+    auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    const int total = mlen + dn;
+    int f = -1;
+    if (tid < dn) {
+        const float s = ds[tid];
+        const int v = (int)(di[tid] & ~EXPANDED);
+        int lo = 0, hi = mlen;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (precedes(Ms[mid], (int)(Mi[mid] & ~EXPANDED), s, v)) lo = mid + 1; else hi = mid;
+        }
+        f = lo + tid;
+    }
+    if (tid == 0) word_lds[0] = f;
+    barrier();
+    const int f0 = word_lds[0];
+    const int lo_b = f0 & ~(BLOCK - 1);
+    const int w_lo = lo_b >> 6, w_hi = (total + 63) >> 6;
+    for (int w = w_lo + tid; w < w_hi; w += NT) um[w] = 0ull;
+    barrier();
+    if (f >= 0) atomicOr(reinterpret_cast<uint32_t *>(um) + (f >> 5), 1u << (f & 31));
+    barrier();
+    int *rk = reinterpret_cast<int *>(os);                // marks before word w_lo + t
+    int *wt = reinterpret_cast<int *>(oi);
+    {
+        const int w = w_lo + tid;                         // w_hi - w_lo <= ef / 64 <= GRAPH_THREADS
+        const int c = w < w_hi ? __builtin_popcountll(um[w]) : 0;
+        int incl = c;
+        for (int o = 1; o < WAVE; o <<= 1) {
+            const int t = __shfl_up(incl, o);
+            if (lane >= o) incl += t;
+        }
+        if (lane == WAVE - 1) wt[wave] = incl;
+        barrier();
+        int off = 0;
+        for (int ww = 0; ww < wave; ++ww) off += wt[ww];
+        rk[tid] = off + incl - c;
+    }
+    barrier();
+    for (int base = (total - 1) & ~(BLOCK - 1); base >= lo_b; base -= BLOCK) {
+        float vs[4];
+        uint32_t ve[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int g = base + u * NT + tid;
+            vs[u] = 0.f;
+            ve[u] = EXPANDED;
+            if (g < total) {
+                const uint64_t word = um[g >> 6];
+                const int bit = g & 63;
+                const int r = rk[(g >> 6) - w_lo] + __builtin_popcountll(word & ((1ull << bit) - 1ull));
+                if ((word >> bit) & 1ull) { vs[u] = ds[r]; ve[u] = di[r]; }
+                else { vs[u] = Ms[g - r]; ve[u] = Mi[g - r]; }
+            }
+        }
+        barrier();
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int g = base + u * NT + tid;
+            if (g < total) { Ms[g] = vs[u]; Mi[g] = ve[u]; }
+            const uint64_t un = __builtin_amdgcn_ballot_w64(g < total && !(ve[u] & EXPANDED));
+            const int w = (base + u * NT + wave * WAVE) >> 6;
+            if (lane == 0 && w < w_hi) um[w] = un;
+        }
+    }
+    barrier();
+    return f0;
+}
+
 // RPT: 32 for graphs with R <= 32 slots per node (one scoring pass per expansion, loops over the
 // scored neighbours fully unrolled: the software-pipelined loop), 0 for wider graphs (the number
 // of slots, rounded up to 32, comes from the layout at run time: the plain loop).
@@ -313,95 +457,7 @@ __global__ __launch_bounds__(GRAPH_THREADS, QREG ? 2 : 3) void graph_search_kern
     const int sub = lane & (LANES_PER_ROW - 1);           // lane's position inside its row group
     const int grp = wave * (WAVE / LANES_PER_ROW) + lane / LANES_PER_ROW;   // 0..31
 
-    // The lane's share of the first 128 chunks of the query (chunks sub, sub + 8, ...) stays in
-    // registers for the whole search: up to 1024 16-bit dimensions are scored without reading
-    // the query from LDS at all.
-    constexpr int NX = QREG ? 16 : 8;                     // 16-byte loads of a row a lane keeps in flight
-    constexpr int BLK = NX * LANES_PER_ROW;               // chunks of a row covered by those loads
-    constexpr int TAIL = 8 * LANES_PER_ROW;               // chunks per round of the loop over the rest of a row
-    u4 qr[QREG ? 16 : 1];
-    if constexpr (QREG) {
-#pragma unroll
-        for (int u = 0; u < 16; ++u) qr[u] = qs[min(sub + u * LANES_PER_ROW, nch - 1)];
-    }
-    auto q_chunk = [&](int u) -> u4 {
-        if constexpr (QREG) return qr[u];
-        else return qs[min(sub + u * LANES_PER_ROW, nch - 1)];
-    };
-
-    // <q, x_v> by the 8 lanes of a row group; every lane of the group gets the sum.  All
-    // of a lane's 16-byte loads of the row are issued before the first one is used, so a
-    // whole expansion costs one memory latency, not one per batch of loads.  Loads and
-    // products come in runs of four with one scalar test each (is any of the run's 32
-    // chunks inside the row?); a lane whose chunk lies past the end of the row loads the
-    // row's last chunk instead and leaves the product out of the sum (`lim` is re-derived
-    // per call on purpose: sixteen loop-invariant lane masks would not fit the scalar registers).
-    // (in two halves, so that other work can be put between the loads and their use)
-    auto row_issue = [&](int v, u4 (&x)[NX]) {
-        const char *rp = static_cast<const char *>(X) + (size_t)v * nch * 16;
-        int lim = nch - sub;                              // chunk sub + 8u is in the row iff 8u < lim
-        asm volatile("" : "+v"(lim));
-        const char *rl = rp + sub * 16;
-#pragma unroll
-        for (int g = 0; g < NX / 4; ++g)
-            if ((g + 1) * 4 * LANES_PER_ROW <= nch) {      // the whole run is inside: constant offsets
-#pragma unroll
-                for (int u = 4 * g; u < 4 * g + 4; ++u) x[u] = load_chunk(rl + u * LANES_PER_ROW * 16);
-            } else if (g * 4 * LANES_PER_ROW < nch) {
-#pragma unroll
-                for (int u = 4 * g; u < 4 * g + 4; ++u)
-                    x[u] = load_chunk(rp + (size_t)(sub + min(u * LANES_PER_ROW, lim - 1)) * 16);
-            }
-    };
-    auto row_dots = [&](int v, u4 (&x)[NX]) -> float {
-        const char *rp = static_cast<const char *>(X) + (size_t)v * nch * 16;
-        f4 acc = {0.f, 0.f, 0.f, 0.f};                    // four independent chains, added at the end
-        int lim = nch - sub;
-        asm volatile("" : "+v"(lim));
-#pragma unroll
-        for (int g = 0; g < NX / 4; ++g)
-            if ((g + 1) * 4 * LANES_PER_ROW <= nch) {      // the whole run is inside the row
-#pragma unroll
-                for (int u = 4 * g; u < 4 * g + 4; ++u) dot_chunk4<T>(x[u], q_chunk(u), acc);
-            } else if (g * 4 * LANES_PER_ROW < nch) {
-#pragma unroll
-                for (int u = 4 * g; u < 4 * g + 4; ++u) {
-                    f4 t = acc;
-                    dot_chunk4<T>(x[u], q_chunk(u), t);
-                    acc = u * LANES_PER_ROW < lim ? t : acc;
-                }
-            }
-        for (int cb = BLK; cb < nch; cb += TAIL) {        // longer rows: the query comes from LDS
-            u4 qv[8];
-            lim -= cb == BLK ? BLK : TAIL;
-#pragma unroll
-            for (int g = 0; g < 2; ++g)
-                if (cb + g * 4 * LANES_PER_ROW < nch) {
-#pragma unroll
-                    for (int u = 4 * g; u < 4 * g + 4; ++u) {
-                        const int c = cb + sub + min(u * LANES_PER_ROW, lim - 1);
-                        x[u] = load_chunk(rp + (size_t)c * 16);
-                        qv[u] = qs[c];
-                    }
-                }
-#pragma unroll
-            for (int g = 0; g < 2; ++g)
-                if (cb + g * 4 * LANES_PER_ROW < nch) {
-#pragma unroll
-                    for (int u = 4 * g; u < 4 * g + 4; ++u) {
-                        f4 t = acc;
-                        dot_chunk4<T>(x[u], qv[u], t);
-                        acc = u * LANES_PER_ROW < lim ? t : acc;
-                    }
-                }
-        }
-        return group_sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
-    };
-    auto score_row = [&](int v) -> float {
-        u4 x[NX];
-        row_issue(v, x);
-        return row_dots(v, x);
-    };
+    RowScorer<T, QREG> rows(X, qs, nch, sub);
 
     // list <- the entry nodes (at most 32, one row group each), scored and put in order; ids that
     // are no nodes and ids named by an earlier slot are left out, a NaN score is never listed
@@ -415,7 +471,7 @@ __global__ __launch_bounds__(GRAPH_THREADS, QREG ? 2 : 3) void graph_search_kern
                 if (my_entries[j] == v0) v0 = -1;
         }
         float s0 = 0.f;
-        if (v0 >= 0) s0 = score_row(v0);
+        if (v0 >= 0) s0 = rows.score(v0);
         if (sub == 0) { cs[grp] = s0; ci[grp] = v0; }
         __syncthreads();
         const int cl = lane & 31;
@@ -476,7 +532,7 @@ __global__ __launch_bounds__(GRAPH_THREADS, QREG ? 2 : 3) void graph_search_kern
     int aid0 = -1, aid1 = -1, tog = 0;                    // whose adjacency rows adj[0], adj[1] hold
     int node = entry, p = 0;                              // the node being expanded and its list index
     if (tid == 0) li(0)[0] = (uint32_t)entry | EXPANDED;  // (scans leave entry p out by index as well)
-    u4 x[NX];
+    typename RowScorer<T, QREG>::Loads x;
     int v = -1, fresh = 0;                                // this group's neighbour of `node`; to be scored?
     uint32_t seen = 0;                                    // NS: the word of the exact visited set that holds v
     float *ema_s = reinterpret_cast<float *>(adj_id + 3);
@@ -542,7 +598,7 @@ __global__ __launch_bounds__(GRAPH_THREADS, QREG ? 2 : 3) void graph_search_kern
         // after their scoring) and set after scoring by an atomic that returns nothing
         if (NS && fresh && sub == 0)
             seen = __hip_atomic_load(&seen_bits[v >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (fresh) row_issue(v, x);
+        if (fresh) rows.issue(v, x);
     };
     request_row(node);
     request_rest();
@@ -551,14 +607,11 @@ __global__ __launch_bounds__(GRAPH_THREADS, QREG ? 2 : 3) void graph_search_kern
     auto issue_rows = [&] {
         const bool unseen = sub == 0 && fresh && !((seen >> (v & 31)) & 1u);
         fresh = (int)((__builtin_amdgcn_ballot_w64(unseen) >> gbase) & 1u);
-        if (fresh) row_issue(v, x);
+        if (fresh) rows.issue(v, x);
     };
 
-    // ---- LONG: the two-level list ------------------------------------------------------------------
-    // A list of thousands of entries is not moved for every insertion.  It is kept as a large part M
-    // (ordered, rewritten only by a rebuild) and a small part D (ordered, at most DCAP entries: the
-    // double-buffered list ls / li / len of the code below); the candidate list of the method is the
-    // merge of the two, cut at ef entries.  New entries go into D; when D is nearly full, it is
+    // ---- LONG: the two-level list, M and D -----------------------------------------------------------
+    // New entries go into D, which is the double-buffered list ls / li / len of the code below; when it is nearly full, it is
     // merged into M in one pass over M (once in some tens of expansions).
     //   * the worst entry of the list is the worse of the two tails.  A merge of new entries into D
     //     that takes the total past ef is followed, before the next expansion looks at the list, by
@@ -575,156 +628,36 @@ __global__ __launch_bounds__(GRAPH_THREADS, QREG ? 2 : 3) void graph_search_kern
     float m1_s = 0.f;
     float w_s = 0.f;                                      // the worst entry of the list (w_v < 0: the list is empty)
     int w_v = -1;
-    // m1 <- first position >= from whose bit is set
     // (Lane and thread numbers go through an empty asm in these routines, so that nothing computed
     // from them is kept in a register across the whole search loop, where registers are short.)
     auto opaque = [](int x) { asm volatile("" : "+v"(x)); return x; };
     auto m_find = [&](int from) {
-        m1 = -1;
-        const int nw = (mlen + 63) >> 6;
-        // (as a rule the next one is a few entries further on, in the word that holds `from`:
-        // that word alone is read first, by all lanes at once)
-        if ((from >> 6) < nw) {
-            uint64_t word = um[from >> 6] & (~0ull << (from & 63));
-            if ((from >> 6) == nw - 1 && (mlen & 63) != 0) word &= (1ull << (mlen & 63)) - 1ull;
-            const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)word);
-            const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(word >> 32));
-            const uint64_t wu = ((uint64_t)hi << 32) | lo;
-            if (wu != 0) m1 = (from & ~63) + __builtin_ctzll(wu);
-            else from = (from | 63) + 1;
-        }
-        if (m1 >= 0) {
-            m1_s = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(Ms[m1])));
-            m1_v = __builtin_amdgcn_readfirstlane((int)(Mi[m1] & ~EXPANDED));
-            return;
-        }
-        const int lane_ = opaque(lane);
-        for (int w0 = from >> 6; w0 < nw; w0 += WAVE) {
-            const int w = w0 + lane_;
-            uint64_t word = w < nw ? um[w] : 0ull;
-            if (w == (from >> 6)) word &= ~0ull << (from & 63);
-            if (w == nw - 1 && (mlen & 63) != 0) word &= (1ull << (mlen & 63)) - 1ull;
-            const uint64_t any = __builtin_amdgcn_ballot_w64(word != 0);
-            if (any != 0) {
-                const int l = __builtin_ctzll(any);
-                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)word, l);
-                const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(word >> 32), l);
-                m1 = (w0 + l) * 64 + __builtin_ctzll(((uint64_t)hi << 32) | lo);
-                break;
-            }
-        }
+        first_unexpanded(um, mlen, from, opaque(lane), m1);
         if (m1 >= 0) {
             m1_s = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(Ms[m1])));
             m1_v = __builtin_amdgcn_readfirstlane((int)(Mi[m1] & ~EXPANDED));
         }
     };
-    // After a merge into D: the `pend` worst entries of M and D together leave, and the worst entry
-    // that remains is read again, in one round trip.  Lane j reads M's and D's j-th entries from the
-    // end; lane j < pend asks whether M's is among the pend worst, i.e. whether fewer than pend - j
-    // entries of D are worse than it (it reads that entry of D as well); the count of such lanes is
-    // what M loses, D loses the rest, and the new worst is the worse of the first entries that stay.
+    // After a merge into D: the `pend` worst entries leave, and the worst entry that remains, the worse of the first that
+    // stay, is read again
     auto trim_tails = [&] {
-        const int lane_ = opaque(lane);
-        const float *dsc = ls(cur);
-        const uint32_t *did = li(cur);
-        const int ia = mlen - 1 - lane_, it = len - 1 - lane_, ix = len - pend + lane_;
-        const float a_s = Ms[max(ia, 0)];
-        const int a_v = (int)(Mi[max(ia, 0)] & ~EXPANDED);
-        const float t_s = dsc[max(it, 0)];
-        const int t_v = (int)(did[max(it, 0)] & ~EXPANDED);
-        const int ixc = min(max(ix, 0), DCAP - 1);
-        const float x_s = dsc[ixc];
-        const int x_v = (int)(did[ixc] & ~EXPANDED);
-        const bool c = lane_ < pend && ia >= 0 && (ix < 0 || precedes(x_s, x_v, a_s, a_v));
-        const int tm = __builtin_popcountll(__builtin_amdgcn_ballot_w64(c)), td = pend - tm;
+        ListTails t;
+        const int tm = tail_of_m(Ms, Mi, mlen, ls(cur), li(cur), len, pend, opaque(lane), t), td = pend - tm;
         mlen -= tm;
         len -= td;
         pend = 0;
         if (m1 >= mlen) m1 = -1;
-        const float wa_s = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a_s), tm));
-        const int wa_v = __builtin_amdgcn_readlane(a_v, tm);
-        const float wt_s = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t_s), td));
-        const int wt_v = __builtin_amdgcn_readlane(t_v, td);
+        const float wa_s = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t.a_s), tm));
+        const int wa_v = __builtin_amdgcn_readlane(t.a_v, tm);
+        const float wt_s = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t.t_s), td));
+        const int wt_v = __builtin_amdgcn_readlane(t.t_v, td);
         const bool take_d = len > 0 && (mlen <= 0 || precedes(wa_s, wa_v, wt_s, wt_v));
         w_s = take_d ? wt_s : wa_s;
         w_v = take_d ? wt_v : (mlen > 0 ? wa_v : -1);
     };
-    // M <- merge of M and D, in place; D <- empty.  Thread t places D's entry t: its final position
-    // is (entries of M that precede it) + t.  Those positions are marked in a bit per final position
-    // (the words of um from the lowest marked position's block of 1024 on: um is rewritten there
-    // anyway), with the number of marks before every word beside it; then every final position,
-    // 1024 at a time from the top down, takes D's entry (rank) if marked and M's entry
-    // (position - rank) if not.  Its sources lie at most DCAP below it, so one barrier between the
-    // reads and the writes of a block suffices.  The expanded flags travel with the ids and give
-    // the new bits of um.
     auto rebuild = [&] {
-        constexpr int BLOCK = 4 * GRAPH_THREADS;
-        const int tid_ = opaque(tid), lane_ = tid_ & (WAVE - 1), wave_ = tid_ >> 6;
-        const int dn = len, total = mlen + dn;            // total <= ef: the tails have been cut
-        int f = -1;
-        if (tid_ < dn) {
-            const float ds = ls(cur)[tid_];
-            const int dv = (int)(li(cur)[tid_] & ~EXPANDED);
-            int lo = 0, hi = mlen;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (precedes(Ms[mid], (int)(Mi[mid] & ~EXPANDED), ds, dv)) lo = mid + 1; else hi = mid;
-            }
-            f = lo + tid_;
-        }
-        if (tid_ == 0) adj_id[2] = f;
-        lds_barrier();
-        const int f0 = adj_id[2];                         // lowest position that changes
-        const int lo_b = f0 & ~(BLOCK - 1);
-        const int w_lo = lo_b >> 6, w_hi = (total + 63) >> 6;
-        for (int w = w_lo + tid_; w < w_hi; w += GRAPH_THREADS) um[w] = 0ull;
-        lds_barrier();
-        if (f >= 0) atomicOr(reinterpret_cast<uint32_t *>(um) + (f >> 5), 1u << (f & 31));
-        lds_barrier();
-        int *rk = reinterpret_cast<int *>(ls(cur ^ 1));   // marks before word w_lo + t (D's other buffer is free)
-        int *wt = reinterpret_cast<int *>(li(cur ^ 1));
-        {
-            const int w = w_lo + tid_;                     // w_hi - w_lo <= ef / 64 <= GRAPH_THREADS
-            const int c = w < w_hi ? __builtin_popcountll(um[w]) : 0;
-            int incl = c;
-            for (int o = 1; o < WAVE; o <<= 1) {
-                const int t = __shfl_up(incl, o);
-                if (lane_ >= o) incl += t;
-            }
-            if (lane_ == WAVE - 1) wt[wave_] = incl;
-            lds_barrier();
-            int off = 0;
-            for (int ww = 0; ww < wave_; ++ww) off += wt[ww];
-            rk[tid_] = off + incl - c;
-        }
-        lds_barrier();
-        for (int base = (total - 1) & ~(BLOCK - 1); base >= lo_b; base -= BLOCK) {
-            float vs[4];
-            uint32_t ve[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int g = base + u * GRAPH_THREADS + tid_;
-                vs[u] = 0.f;
-                ve[u] = EXPANDED;
-                if (g < total) {
-                    const uint64_t word = um[g >> 6];
-                    const int bit = g & 63;
-                    const int r = rk[(g >> 6) - w_lo] + __builtin_popcountll(word & ((1ull << bit) - 1ull));
-                    if ((word >> bit) & 1ull) { vs[u] = ls(cur)[r]; ve[u] = li(cur)[r]; }
-                    else { vs[u] = Ms[g - r]; ve[u] = Mi[g - r]; }
-                }
-            }
-            lds_barrier();
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int g = base + u * GRAPH_THREADS + tid_;
-                if (g < total) { Ms[g] = vs[u]; Mi[g] = ve[u]; }
-                const uint64_t un = __builtin_amdgcn_ballot_w64(g < total && !(ve[u] & EXPANDED));
-                const int w = (base + u * GRAPH_THREADS + wave_ * WAVE) >> 6;
-                if (lane_ == 0 && w < w_hi) um[w] = un;
-            }
-        }
-        lds_barrier();                                    // D and its other buffer have been read
+        const int tid_ = opaque(tid), total = mlen + len;
+        const int f0 = rebuild_list(Ms, Mi, um, mlen, ls(cur), li(cur), len, ls(cur ^ 1), li(cur ^ 1), adj_id + 2, tid_);
         for (int i = tid_; i < DCAP; i += GRAPH_THREADS) { ls(0)[i] = -INFINITY; ls(1)[i] = -INFINITY; }
         const int from = min(m1 >= 0 ? m1 : total, f0);   // nothing unexpanded lies below either
         mlen = total;
@@ -833,7 +766,7 @@ __global__ __launch_bounds__(GRAPH_THREADS, QREG ? 2 : 3) void graph_search_kern
         // products and list positions of the neighbours of `node`
         ++n_expand;
         float s = 0.f;
-        if (fresh) s = row_dots(v, x);
+        if (fresh) s = rows.dots(v, x);
         if (NS) {                                         // the cache may have forgotten v: the bitset has not
             if constexpr (!LONG) {                        // (LONG: only unseen nodes were requested)
                 const bool was_seen = sub == 0 && fresh && ((seen >> (v & 31)) & 1u);
@@ -1099,7 +1032,7 @@ __global__ __launch_bounds__(GRAPH_THREADS, QREG ? 2 : 3) void graph_search_kern
             if (NS && fresh && sub == 0)
                 seen = __hip_atomic_load(&seen_bits[v >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             float s = 0.f;
-            if (fresh) s = score_row(v);
+            if (fresh) s = rows.score(v);
             if (NS) {                                     // the cache may have forgotten v: the bitset has not
                 const bool was_seen = sub == 0 && fresh && ((seen >> (v & 31)) & 1u);
                 if ((__builtin_amdgcn_ballot_w64(was_seen) >> (lane & ~(LANES_PER_ROW - 1))) & 1u) fresh = 0;

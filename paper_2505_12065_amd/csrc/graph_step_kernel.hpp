@@ -136,135 +136,23 @@ __global__ __launch_bounds__(GRAPH_THREADS, RPG == 2 ? 1 : QREG ? 2 : 3) void gr
     float *Ms = reinterpret_cast<float *>(smem + L.ms);
     uint32_t *Mi = reinterpret_cast<uint32_t *>(smem + L.mi);
 
-    // m1 <- first position >= from whose bit is set
-    auto m_find = [&](int from) {
-        m1 = -1;
-        const int nw = (mlen + 63) >> 6;
-        // (as a rule the next one is a few entries further on, in the word that holds `from`: that word alone is read
-        // first, by all lanes at once)
-        if ((from >> 6) < nw) {
-            uint64_t word = um[from >> 6] & (~0ull << (from & 63));
-            if ((from >> 6) == nw - 1 && (mlen & 63) != 0) word &= (1ull << (mlen & 63)) - 1ull;
-            const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)word);
-            const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(word >> 32));
-            const uint64_t wu = ((uint64_t)hi << 32) | lo;
-            if (wu != 0) { m1 = (from & ~63) + __builtin_ctzll(wu); return; }
-            from = (from | 63) + 1;
-        }
-        for (int w0 = from >> 6; w0 < nw; w0 += WAVE) {
-            const int w = w0 + lane;
-            uint64_t word = w < nw ? um[w] : 0ull;
-            if (w == (from >> 6)) word &= ~0ull << (from & 63);
-            if (w == nw - 1 && (mlen & 63) != 0) word &= (1ull << (mlen & 63)) - 1ull;
-            const uint64_t any = __builtin_amdgcn_ballot_w64(word != 0);
-            if (any != 0) {
-                const int l = __builtin_ctzll(any);
-                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)word, l);
-                const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(word >> 32), l);
-                m1 = (w0 + l) * 64 + __builtin_ctzll(((uint64_t)hi << 32) | lo);
-                break;
-            }
-        }
-    };
-    // LONG: the `pend` worst entries of M and D together leave, and the worst entry that remains is read.  Lane j reads M's
-    // and D's j-th entries from the end; lane j < pend asks whether M's is among the pend worst, i.e. whether
-    // fewer than pend - j entries of D are worse than it; the count of such lanes is what M loses, D loses the rest.
+    auto m_find = [&](int from) { first_unexpanded(um, mlen, from, lane, m1); };
+    // LONG: the `pend` worst entries of M and D together leave, and the worst entry that remains is read
     auto trim_tails = [&] {
-        const float *dsc = ls(cur);
-        const uint32_t *did = li(cur);
-        const int ia = mlen - 1 - lane, it = len - 1 - lane, ix = len - pend + lane;
-        const float a_s = Ms[max(ia, 0)];
-        const int a_v = (int)(Mi[max(ia, 0)] & ~EXPANDED);
-        const float t_s = dsc[max(it, 0)];
-        const int ixc = min(max(ix, 0), DCAP - 1);
-        const float x_s = dsc[ixc];
-        const int x_v = (int)(did[ixc] & ~EXPANDED);
-        const bool c = lane < pend && ia >= 0 && (ix < 0 || precedes(x_s, x_v, a_s, a_v));
-        const int tm = __builtin_popcountll(__builtin_amdgcn_ballot_w64(c)), td = pend - tm;
+        ListTails t;
+        const int tm = tail_of_m(Ms, Mi, mlen, ls(cur), li(cur), len, pend, lane, t), td = pend - tm;
         mlen -= tm;
         len -= td;
         pend = 0;
         if (m1 >= mlen) m1 = -1;
-        const uint32_t wa = score_key(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(a_s), tm)));
-        const uint32_t wt = score_key(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(t_s), td)));
+        const uint32_t wa = score_key(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(t.a_s), tm)));
+        const uint32_t wt = score_key(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(t.t_s), td)));
         worst_k = mlen + len < ef ? 0u : len <= 0 ? wa : mlen <= 0 ? wt : min(wa, wt);
     };
-    // LONG: M <- merge of M and D, in place; D <- empty.  Thread t places D's entry t: its final position
-    // is (entries of M that precede it) + t.  Those positions are marked in a bit per final position
-    // (the words of um from the lowest marked position's block on: um is rewritten there
-    // anyway), with the number of marks before every word beside it; then every final position,
-    // a block at a time from the top down, takes D's entry (rank) if marked and M's entry
-    // (position - rank) if not.  Its sources lie at most DCAP below it, so one barrier between the
-    // reads and the writes of a block suffices.  The expanded flags travel with the ids and give
-    // the new bits of um.
+    // LONG: M <- merge of M and D; D <- empty
     auto rebuild = [&] {
-        constexpr int BLOCK = 4 * NT;
-        static_assert(NT >= DCAP && BLOCK >= 2 * DCAP, "a thread per entry of D; sources stay within two blocks");
-        const int dn = len, total = mlen + dn;            // total <= ef: the tails have been cut
-        int f = -1;
-        if (tid < dn) {
-            const float ds = ls(cur)[tid];
-            const int dv = (int)(li(cur)[tid] & ~EXPANDED);
-            int lo = 0, hi = mlen;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (precedes(Ms[mid], (int)(Mi[mid] & ~EXPANDED), ds, dv)) lo = mid + 1; else hi = mid;
-            }
-            f = lo + tid;
-        }
-        if (tid == 0) ctl[0] = f;
-        lds_barrier();
-        const int f0 = ctl[0];                            // lowest position that changes
-        const int lo_b = f0 & ~(BLOCK - 1);
-        const int w_lo = lo_b >> 6, w_hi = (total + 63) >> 6;
-        for (int w = w_lo + tid; w < w_hi; w += NT) um[w] = 0ull;
-        lds_barrier();
-        if (f >= 0) atomicOr(reinterpret_cast<uint32_t *>(um) + (f >> 5), 1u << (f & 31));
-        lds_barrier();
-        int *rk = reinterpret_cast<int *>(ls(cur ^ 1));   // marks before word w_lo + t (D's other buffer is free)
-        int *wt = reinterpret_cast<int *>(li(cur ^ 1));
-        {
-            const int w = w_lo + tid;                     // w_hi - w_lo <= ef / 64 <= 256
-            const int c = w < w_hi ? __builtin_popcountll(um[w]) : 0;
-            int incl = c;
-            for (int o = 1; o < WAVE; o <<= 1) {
-                const int t = __shfl_up(incl, o);
-                if (lane >= o) incl += t;
-            }
-            if (lane == WAVE - 1) wt[wave] = incl;
-            lds_barrier();
-            int off = 0;
-            for (int ww = 0; ww < wave; ++ww) off += wt[ww];
-            if (tid < DCAP) rk[tid] = off + incl - c;
-        }
-        lds_barrier();
-        for (int base = (total - 1) & ~(BLOCK - 1); base >= lo_b; base -= BLOCK) {
-            float vs[4];
-            uint32_t ve[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int g = base + u * NT + tid;
-                vs[u] = 0.f;
-                ve[u] = EXPANDED;
-                if (g < total) {
-                    const uint64_t word = um[g >> 6];
-                    const int bit = g & 63;
-                    const int r = rk[(g >> 6) - w_lo] + __builtin_popcountll(word & ((1ull << bit) - 1ull));
-                    if ((word >> bit) & 1ull) { vs[u] = ls(cur)[r]; ve[u] = li(cur)[r]; }
-                    else { vs[u] = Ms[g - r]; ve[u] = Mi[g - r]; }
-                }
-            }
-            lds_barrier();
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int g = base + u * NT + tid;
-                if (g < total) { Ms[g] = vs[u]; Mi[g] = ve[u]; }
-                const uint64_t un = __builtin_amdgcn_ballot_w64(g < total && !(ve[u] & EXPANDED));
-                const int w = (base + u * NT + wave * WAVE) >> 6;
-                if (lane == 0 && w < w_hi) um[w] = un;
-            }
-        }
-        lds_barrier();                                    // D and its other buffer have been read
+        const int total = mlen + len;                     // <= ef: the tails have been cut
+        const int f0 = rebuild_list(Ms, Mi, um, mlen, ls(cur), li(cur), len, ls(cur ^ 1), li(cur ^ 1), ctl, tid);
         for (int i = tid; i < DCAP; i += NT) { ls(0)[i] = -INFINITY; ls(1)[i] = -INFINITY; li(0)[i] = EXPANDED; li(1)[i] = EXPANDED; }
         const int from = min(m1 >= 0 ? m1 : total, f0);   // nothing unexpanded lies below either
         mlen = total;
