@@ -70,25 +70,25 @@ def test_cfg0_graph_fp32(cfg0):
     (1, 64, 2, 1),                  # single row
     (7, 32, 3, 7),                  # k = N, fewer rows than a tile
     (5000, 136, 17, 10),            # d not a multiple of 32, B not a multiple of 16
-    (20000, 768, 64, 3),            # four query groups in one pass
-    (9001, 256, 70, 16),            # two passes, k = K_MAX
-    (4099, 384, 130, 5),            # the paper's embedding width
-    (3000, 1024, 33, 4),
-    (5000, 768, 100, 3),            # matrix-core path, 128-query tile, ragged corpus tile
-    (777, 64, 300, 4),              # matrix-core path, two 256-query tiles, second one ragged
-    (70001, 256, 129, 1),           # matrix-core path, many tiles per slab
-    (100, 32, 2100, 2),             # more query tiles than tile groups; corpus smaller than a tile
-    (50_000, 768, 32, 3),           # two query groups, many tiles per wave
-    (2049, 96, 20, 10),             # ... ragged tile, k > 4
+    (20000, 768, 64, 3),            # (16 bits:) matrix cores, tiles of 64 x 64, one-row groups
+    (9001, 256, 70, 16),            # ... ragged tile, two query tiles, k = K_MAX
+    (4099, 384, 130, 5),            # ... the paper's embedding width
+    (3000, 1024, 33, 4),            # streaming kernel, three groups of queries
+    (5000, 768, 100, 3),            # 64 x 64, ragged corpus tile
+    (777, 64, 300, 4),              # ... five query tiles, the last one ragged
+    (70001, 256, 129, 1),           # 256 x 256, groups of 32 rows
+    (100, 32, 2100, 2),             # one workgroup's lists are the answer
+    (50_000, 768, 32, 3),           # streaming kernel, two query groups, many tiles per wave
+    (2049, 96, 20, 10),             # 64 x 64, ragged tile, k > 4
     (300, 4096, 9, 2),              # largest d
-    (600_001, 64, 200, 3),          # matrix-core path with the sampling pass, one query tile
-    (300_000, 32, 600, 4),          # ... three query tiles
-    (131_072 + 77, 128, 96, 5),     # matrix-core path with candidate arrays (k > 4), 128-query tile
-    (200_003, 64, 300, 16),         # ... two 256-query tiles, k = K_MAX
-    (150_000, 96, 130, 10),         # ... ragged sample tile
-    (131_072, 64, 1, 5),            # streaming path with candidate arrays (k > 4), one query
-    (140_000, 136, 17, 10),         # ... d not a multiple of 32
-    (150_001, 72, 70, 7),           # ... two passes of queries
+    (600_001, 64, 200, 3),          # 256 x 256, groups of 64
+    (300_000, 32, 600, 4),          # 512 x 128, groups of 64, five query tiles
+    (131_072 + 77, 128, 96, 5),     # 512 x 128, groups of 32, one query tile
+    (200_003, 64, 300, 16),         # ... three query tiles, k = K_MAX
+    (150_000, 96, 130, 10),         # 256 x 256, groups of 16
+    (131_072, 64, 1, 5),            # streaming kernel, lists of 8, one query
+    (140_000, 136, 17, 10),         # 128 x 64, d not a multiple of 32
+    (150_001, 72, 70, 7),           # 512 x 128, d not a multiple of 32
 ])
 def test_flat_shapes(dtype, N, d, B, k):
     say(f"flat shapes: dtype={dtype} N={N} d={d} B={B} k={k}")
@@ -101,15 +101,15 @@ def test_flat_shapes(dtype, N, d, B, k):
 
 @pytest.mark.parametrize("dtype,N,d,B,k", [
     (torch.float16, 30_000, 128, 9, 16),        # streaming kernel, lists of 16
-    (torch.float16, 200_000, 64, 20, 16),       # streaming kernel, candidate arrays
-    (torch.bfloat16, 70_000, 96, 300, 4),       # matrix-core kernel, lists, sampled thresholds
-    (torch.float16, 700_000, 64, 100, 3),       # matrix-core kernel, the sample is the first tile of every slab
-    (torch.float16, 150_000, 128, 260, 16),     # matrix-core kernel, candidate arrays
-    (torch.float32, 9_000, 64, 11, 16),         # fp32 kernel
-    (torch.float16, 40, 64, 5, 16),             # pages run past the end of a small corpus
-    (torch.float16, 40, 64, 200, 16),           # the same through the matrix-core kernel: the sample has < k rows
-    (torch.bfloat16, 300, 96, 700, 16),         # ragged last tile of 256 rows, threshold of -inf, three query tiles
-    (torch.float16, 5000, 64, 90, 9),           # candidate arrays on a corpus of a few thousand rows
+    (torch.float16, 200_000, 64, 20, 16),       # matrix-core kernel, tiles of 128 x 64, groups of 32 rows
+    (torch.bfloat16, 70_000, 96, 300, 4),       # ... 512 x 128, groups of 32, three query tiles
+    (torch.float16, 700_000, 64, 100, 3),       # ... groups of 64
+    (torch.float16, 150_000, 128, 260, 16),     # ... groups of 16
+    (torch.float32, 9_000, 64, 11, 16),         # fp32, streaming kernel, lists of 16
+    (torch.float16, 40, 64, 5, 16),             # one workgroup's lists, pages run past the end of a small corpus
+    (torch.float16, 40, 64, 200, 16),           # ... many queries
+    (torch.bfloat16, 300, 96, 700, 16),         # matrix-core kernel, 64 x 64, one-row groups, ragged last tile
+    (torch.float16, 5000, 64, 90, 9),           # ... a corpus of a few thousand rows
 ])
 def test_flat_continuation_pages(dtype, N, d, B, k):
     """The next k rows after a boundary pair, three pages in a row: each side continues from its own last
@@ -150,15 +150,17 @@ def test_flat_continuation_pages(dtype, N, d, B, k):
 
 
 @pytest.mark.parametrize("dtype,N,d,B,k", [
-    (torch.float16, 65_000, 40, 257, 5),        # tiles of 256 x 256, row end inside a stage, one query in the last tile
-    (torch.bfloat16, 65_537, 32, 128, 1),       # 256 x 128, one stage, one row in the last tile
+    (torch.float16, 65_000, 40, 257, 5),        # tiles of 512 x 128, row end inside a stage, one query in the last tile
+    (torch.bfloat16, 65_537, 32, 128, 1),       # 128 x 128, one stage, one row in the last tile
+    (torch.float16, 300_001, 40, 256, 5),       # 256 x 256, row end inside a stage, a full tile of queries
+    (torch.bfloat16, 170_001, 72, 500, 3),      # ... ragged last tile of queries
     (torch.float16, 10_001, 72, 300, 16),       # 128 x 128
     (torch.bfloat16, 33_000, 72, 64, 2),        # 128 x 64
     (torch.float16, 65, 136, 70, 16),           # 64 x 64, one-row groups
     (torch.bfloat16, 4_097, 8, 1, 9),           # ... one query, the shortest row
     (torch.float16, 400_000, 8, 65, 1),         # groups of 64
-    (torch.float16, 1_000_000, 32, 512, 3),     # ... in parts, through the static workspace
-    (torch.bfloat16, 400_000, 8, 513, 2),       # ... parts of 257 and 256 queries
+    (torch.float16, 1_000_000, 32, 512, 3),     # ... the corpus in parts through the static workspace
+    (torch.bfloat16, 400_000, 8, 513, 2),       # ... the batch in parts of 257 and 256 queries
     (torch.float32, 70_001, 36, 40, 3),         # the streaming kernel with maxima, ragged tile
     (torch.float32, 150_003, 64, 17, 9),        # ... whole steps, one query in the second group
 ])
@@ -241,12 +243,14 @@ def test_flat_corpus_of_one_workgroup(dtype, N, k):
         assert strict >= n - max(1, n // 20), (B, strict, n)
 
 
-@pytest.mark.parametrize("dtype,B", [(torch.float16, 1), (torch.bfloat16, 37), (torch.float32, 20)])
-def test_flat_many_of_the_best_rows_in_one_lane(dtype, B):
+@pytest.mark.parametrize("dtype,B,d", [(torch.float16, 1, 64), (torch.bfloat16, 37, 64), (torch.float32, 20, 64),
+                                       (torch.bfloat16, 37, 320), (torch.float32, 16, 64)])
+def test_flat_many_of_the_best_rows_in_one_lane(dtype, B, d):
     """k > 4: a lane of the streaming kernel keeps the 4 best of its rows, so rows a whole number of grid strides
     apart, of which more than 4 belong to the answer, are found by the merge's second look.  (The stride
-    follows from the number of slabs, which the workspace size tells.)"""
-    N, d, k = 450_000, 64, 16
+    follows from the number of slabs, which the workspace size tells.  The second and third case run on group maxima,
+    where such rows are nothing special.)"""
+    N, k = 450_000, 16
     slabs = ann.ann_flat_workspace_bytes(N, d, dtype, B, k) // (B * k * 8)
     stride = 16 * 8 * slabs
     rows = torch.arange(16 * 7 + 6, N, stride)
@@ -294,10 +298,9 @@ def test_flat_ties_go_to_lower_id():
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("B,a,b,n_wide,n_stream", [(80, 7, 66, 1, 0), (20, 7, 13, 0, 1)])
 def test_flat_candidate_array_overflow_is_repaired(dtype, B, a, b, n_wide, n_stream):
-    """k > 4 on a large corpus collects, per query, the rows that reach a sampled bound of the
-    k-th best score (large batches on the matrix cores, small ones in the streaming kernel).  Thousands of rows tied at the top overflow that array; such a query is then
-    recomputed by the streaming kernel while the others keep their results.  Rows sorted by
-    cluster (the sample must still represent every cluster) are covered as well."""
+    """Thousands of rows tied at the top of two queries, on a corpus sorted by cluster: hundreds of group maxima tie with the
+    k-th, more than the picking kernel gathers at once, and it goes through the groups in order instead while the other
+    queries keep the short way.  (Both cases run on the matrix cores; the records go by the class of the call.)"""
     N, d, k = 140_000, 64, 6
     c = synth.make_corpus(N, d, 16, seed=31, dtype=dtype, zipf_a=None, sigma=0.3)
     order = torch.argsort(c.labels.cpu(), stable=True)
@@ -308,12 +311,12 @@ def test_flat_candidate_array_overflow_is_repaired(dtype, B, a, b, n_wide, n_str
     q = synth.make_queries(c, B).cpu()
     q[a] = x[int(copies[0])]
     q[b] = x[int(copies[0])]
-    say(f"flat candidate arrays with 6000 tied rows: dtype={dtype} B={B}")
+    say(f"flat with 6000 tied rows: dtype={dtype} B={B}")
     ann.ann_timing_enable(True)
     ids, sc, (o_ids, o_sc, o_sc64) = flat_both(x, q, k)
     wide, stream = ann.ann_timing_read(ann.binding.KERNEL_FLAT_WIDE), ann.ann_timing_read(ann.binding.KERNEL_FLAT_STREAM)
     ann.ann_timing_enable(False)
-    assert wide[0] == n_wide and stream[0] == n_stream          # the main pass; the repair pass is not recorded
+    assert wide[0] == n_wide and stream[0] == n_stream          # the kernel that reads the corpus, once
     low = sorted(copies.tolist())[:k]
     assert ids[a].tolist() == low and ids[b].tolist() == low and o_ids[a].tolist() == low
     strict, tolerant, n = compare_topk(ids, sc, o_ids, o_sc64, to_np(x), to_np(q), dtype=np_dtype_name(x))
@@ -1097,8 +1100,8 @@ def test_kernel_timing_records_main_kernels():
     xd, qd = c.x.to(DEV), q.to(DEV)
     ann.ann_timing_enable(True)
     for _ in range(3):
-        ann.ann_flat_search_typed(xd, qd[:16].contiguous(), 3)       # streaming kernel
-        ann.ann_flat_search_typed(xd, qd, 3)                         # matrix-core kernel (+ helpers, not timed)
+        ann.ann_flat_search_typed(xd, qd[:16].contiguous(), 3)       # a small batch
+        ann.ann_flat_search_typed(xd, qd, 3)                         # a large one (+ helpers, not timed)
         ann.ann_graph_search_typed(xd, g, 0, qd, 3, 16)
     ann.ann_timing_enable(False)
     ann.ann_flat_search_typed(xd, qd, 3)                             # not recorded any more

@@ -95,8 +95,7 @@ def test_cfg1_flat_full_size(cfg1, cfg1_oracle, B):
 
 @pytest.mark.parametrize("B,k", [(16, 10), (128, 5), (512, 5), (512, 16)])
 def test_cfg1_flat_full_size_larger_k(cfg1, B, k):
-    """k > 4 (the paper retrieves k = 5): candidate arrays behind a sampled threshold, in the
-    streaming kernel (B = 16) and on the matrix cores."""
+    """k > 4 (the paper retrieves k = 5): lists of 12 in the streaming kernel (B = 16), group maxima on the matrix cores."""
     c, q, xh = cfg1
     strict, tolerant, n, _ = check_flat_sampled(c.x, xh, q, B, k)
     say(f"cfg1 flat N=1,000,000 B={B} k={k}: oracle on {n} sampled queries, strict={strict} tolerant={tolerant}")

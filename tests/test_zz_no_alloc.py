@@ -33,9 +33,9 @@ def static_call(lib, x, q, k):
 
 @pytest.mark.parametrize("dtype,first,second,k", [
     (torch.float16, (60_000, 768, 300), (9_000, 768, 70), 3),     # matrix-core path, then fewer rows and queries
-    (torch.float16, (60_000, 256, 16), (5_000, 256, 3), 4),       # streaming kernel
-    (torch.bfloat16, (150_000, 128, 40), (140_000, 128, 9), 10),  # candidate arrays (k > 4)
-    (torch.float32, (10_000, 128, 64), (700, 128, 5), 10),        # fp32 path
+    (torch.float16, (60_000, 256, 16), (5_000, 256, 3), 4),       # ... then the streaming kernel
+    (torch.bfloat16, (150_000, 128, 40), (140_000, 128, 9), 10),  # ... the same with k > 4
+    (torch.float32, (10_000, 128, 64), (700, 128, 5), 10),        # fp32, streaming kernel
 ])
 def test_static_entry_matches_allocating_entry_twice(dtype, first, second, k):
     lib = binding.lib()
@@ -55,7 +55,7 @@ def test_static_entry_matches_allocating_entry_twice(dtype, first, second, k):
 
 def test_static_entry_rejects_what_does_not_fit():
     lib = binding.lib()
-    N, d, B, k = 200_000, 64, 2048, 10            # candidate arrays alone: 2048 x 4096 x 8 bytes
+    N, d, B, k = 200_000, 64, 2048, 10            # a long answer for a large batch whose one pass needs 51 MB
     assert binding.ann_flat_workspace_bytes(N, d, torch.float16, B, k) > binding.ANN_STATIC_WORKSPACE_BYTES
     x = torch.zeros(N, d, dtype=torch.float16, device=DEV)
     q = torch.zeros(B, d, dtype=torch.float16, device=DEV)
