@@ -156,7 +156,9 @@ __device__ __forceinline__ int group_lower_bound_fast(const float *s, const uint
 // and products come in runs of four with one scalar test each (is any of the run's 32 chunks inside the row?); a lane
 // whose chunk lies past the end of the row loads the row's last chunk instead and leaves the product out of the sum
 // (`lim` is re-derived per call on purpose: sixteen loop-invariant lane masks would not fit the scalar registers).
-template <class T, bool QREG>
+// APART: the rest of a long row starts from values of its own; that suits graph_step_kernel (without: up to 1 % more of its
+// searches with counters) and not graph_search_kernel (with: up to 2 % more of its searches with long lists).
+template <class T, bool QREG, bool APART>
 struct RowScorer {
     static constexpr int NX = QREG ? 16 : 8;              // 16-byte loads of a row a lane keeps in flight
     static constexpr int BLK = NX * LANES_PER_ROW;        // chunks of a row covered by those loads
@@ -194,11 +196,8 @@ struct RowScorer {
                     x[u] = load_chunk(rp + (size_t)(sub + min(u * LANES_PER_ROW, lim - 1)) * 16);
             }
     }
-    // acc + the products of row v's chunks beyond the first BLK
-    __device__ __forceinline__ f4 rest(int v, Loads &x, f4 acc) const {
-        const char *rp = static_cast<const char *>(X) + (size_t)v * nch * 16;
-        int lim = nch - sub;
-        asm volatile("" : "+v"(lim));
+    // acc + the products of the chunks beyond the first BLK of the row at rp; lim as below
+    __device__ __forceinline__ f4 rest(const char *rp, int lim, Loads &x, f4 acc) const {
         for (int cb = BLK; cb < nch; cb += TAIL) {        // longer rows: the query comes from LDS
             u4 qv[8];
             lim -= cb == BLK ? BLK : TAIL;
@@ -242,7 +241,16 @@ struct RowScorer {
                     acc = u * LANES_PER_ROW < lim ? t : acc;
                 }
             }
-        if (BLK < nch) acc = rest(v, x, acc);
+        if constexpr (APART) {
+            if (BLK < nch) {
+                const char *rp = static_cast<const char *>(X) + (size_t)v * nch * 16;
+                int own = nch - sub;
+                asm volatile("" : "+v"(own));
+                acc = rest(rp, own, x, acc);
+            }
+        } else {
+            acc = rest(static_cast<const char *>(X) + (size_t)v * nch * 16, lim, x, acc);
+        }
         return group_sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
     }
     __device__ __forceinline__ float score(int v) const {
@@ -256,38 +264,6 @@ struct RowScorer {
 // A list of thousands of entries is not moved for every insertion.  It is kept as a large part M (ordered, rewritten only by a
 // rebuild) and a small part D (ordered, at most GRAPH_DELTA entries, double-buffered); the candidate list of the method
 // is the merge of the two, cut at ef entries.
-
-// m1 <- first position >= from whose bit is set among the mlen bits of um, -1 if there is none; the same in all lanes.
-// (By reference: as the value returned it cost the step kernel 1.5 % with long lists.)
-__device__ __forceinline__ void first_unexpanded(const uint64_t *um, int mlen, int from, int lane, int &m1) {
-    m1 = -1;
-    const int nw = (mlen + 63) >> 6;
-    // (as a rule the next one is a few entries further on, in the word that holds `from`: that word alone is read
-    // first, by all lanes at once)
-    if ((from >> 6) < nw) {
-        uint64_t word = um[from >> 6] & (~0ull << (from & 63));
-        if ((from >> 6) == nw - 1 && (mlen & 63) != 0) word &= (1ull << (mlen & 63)) - 1ull;
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)word);
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(word >> 32));
-        const uint64_t wu = ((uint64_t)hi << 32) | lo;
-        if (wu != 0) { m1 = (from & ~63) + __builtin_ctzll(wu); return; }
-        from = (from | 63) + 1;
-    }
-    for (int w0 = from >> 6; w0 < nw; w0 += WAVE) {
-        const int w = w0 + lane;
-        uint64_t word = w < nw ? um[w] : 0ull;
-        if (w == (from >> 6)) word &= ~0ull << (from & 63);
-        if (w == nw - 1 && (mlen & 63) != 0) word &= (1ull << (mlen & 63)) - 1ull;
-        const uint64_t any = __builtin_amdgcn_ballot_w64(word != 0);
-        if (any != 0) {
-            const int l = __builtin_ctzll(any);
-            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)word, l);
-            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(word >> 32), l);
-            m1 = (w0 + l) * 64 + __builtin_ctzll(((uint64_t)hi << 32) | lo);
-            break;
-        }
-    }
-}
 
 // How many of the `pend` worst entries of M and D together M loses (D loses the rest): lane j reads M's and D's j-th entries
 // from the end (a_s, a_v; t_s, t_v: the first that stay are lane M's loss of the one and lane D's loss of the other); lane
@@ -457,7 +433,7 @@ __global__ __launch_bounds__(GRAPH_THREADS, QREG ? 2 : 3) void graph_search_kern
     const int sub = lane & (LANES_PER_ROW - 1);           // lane's position inside its row group
     const int grp = wave * (WAVE / LANES_PER_ROW) + lane / LANES_PER_ROW;   // 0..31
 
-    RowScorer<T, QREG> rows(X, qs, nch, sub);
+    RowScorer<T, QREG, false> rows(X, qs, nch, sub);
 
     // list <- the entry nodes (at most 32, one row group each), scored and put in order; ids that
     // are no nodes and ids named by an earlier slot are left out, a NaN score is never listed
@@ -532,7 +508,7 @@ __global__ __launch_bounds__(GRAPH_THREADS, QREG ? 2 : 3) void graph_search_kern
     int aid0 = -1, aid1 = -1, tog = 0;                    // whose adjacency rows adj[0], adj[1] hold
     int node = entry, p = 0;                              // the node being expanded and its list index
     if (tid == 0) li(0)[0] = (uint32_t)entry | EXPANDED;  // (scans leave entry p out by index as well)
-    typename RowScorer<T, QREG>::Loads x;
+    typename RowScorer<T, QREG, false>::Loads x;
     int v = -1, fresh = 0;                                // this group's neighbour of `node`; to be scored?
     uint32_t seen = 0;                                    // NS: the word of the exact visited set that holds v
     float *ema_s = reinterpret_cast<float *>(adj_id + 3);
@@ -631,8 +607,41 @@ __global__ __launch_bounds__(GRAPH_THREADS, QREG ? 2 : 3) void graph_search_kern
     // (Lane and thread numbers go through an empty asm in these routines, so that nothing computed
     // from them is kept in a register across the whole search loop, where registers are short.)
     auto opaque = [](int x) { asm volatile("" : "+v"(x)); return x; };
+    // m1 <- first position >= from whose bit is set
     auto m_find = [&](int from) {
-        first_unexpanded(um, mlen, from, opaque(lane), m1);
+        m1 = -1;
+        const int nw = (mlen + 63) >> 6;
+        // (as a rule the next one is a few entries further on, in the word that holds `from`:
+        // that word alone is read first, by all lanes at once)
+        if ((from >> 6) < nw) {
+            uint64_t word = um[from >> 6] & (~0ull << (from & 63));
+            if ((from >> 6) == nw - 1 && (mlen & 63) != 0) word &= (1ull << (mlen & 63)) - 1ull;
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)word);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(word >> 32));
+            const uint64_t wu = ((uint64_t)hi << 32) | lo;
+            if (wu != 0) m1 = (from & ~63) + __builtin_ctzll(wu);
+            else from = (from | 63) + 1;
+        }
+        if (m1 >= 0) {
+            m1_s = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(Ms[m1])));
+            m1_v = __builtin_amdgcn_readfirstlane((int)(Mi[m1] & ~EXPANDED));
+            return;
+        }
+        const int lane_ = opaque(lane);
+        for (int w0 = from >> 6; w0 < nw; w0 += WAVE) {
+            const int w = w0 + lane_;
+            uint64_t word = w < nw ? um[w] : 0ull;
+            if (w == (from >> 6)) word &= ~0ull << (from & 63);
+            if (w == nw - 1 && (mlen & 63) != 0) word &= (1ull << (mlen & 63)) - 1ull;
+            const uint64_t any = __builtin_amdgcn_ballot_w64(word != 0);
+            if (any != 0) {
+                const int l = __builtin_ctzll(any);
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)word, l);
+                const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(word >> 32), l);
+                m1 = (w0 + l) * 64 + __builtin_ctzll(((uint64_t)hi << 32) | lo);
+                break;
+            }
+        }
         if (m1 >= 0) {
             m1_s = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(Ms[m1])));
             m1_v = __builtin_amdgcn_readfirstlane((int)(Mi[m1] & ~EXPANDED));

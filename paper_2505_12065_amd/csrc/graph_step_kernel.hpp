@@ -110,7 +110,7 @@ __global__ __launch_bounds__(GRAPH_THREADS, RPG == 2 ? 1 : QREG ? 2 : 3) void gr
     for (int i = tid; i < L.ls_bytes / 4; i += NT) { ls(0)[i] = -INFINITY; ls(1)[i] = -INFINITY; li(0)[i] = EXPANDED; li(1)[i] = EXPANDED; }
     __syncthreads();
 
-    RowScorer<T, QREG> rows(X, qs, nch, sub);
+    RowScorer<T, QREG, true> rows(X, qs, nch, sub);
     auto lds_barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
     // (the visited marks of a step in global memory have to be complete before the next one asks)
     auto step_barrier = [&] { if constexpr (VIS == STEP_VIS_GLOBAL) __syncthreads(); else lds_barrier(); };
@@ -136,7 +136,37 @@ __global__ __launch_bounds__(GRAPH_THREADS, RPG == 2 ? 1 : QREG ? 2 : 3) void gr
     float *Ms = reinterpret_cast<float *>(smem + L.ms);
     uint32_t *Mi = reinterpret_cast<uint32_t *>(smem + L.mi);
 
-    auto m_find = [&](int from) { first_unexpanded(um, mlen, from, lane, m1); };
+    // m1 <- first position >= from whose bit is set.  (The other kernel's m_find in other words: a common function, by value or
+    // by reference, took 0.7 to 4 % more of the searches with long lists, as m1 then left the scalar registers.)
+    auto m_find = [&](int from) {
+        m1 = -1;
+        const int nw = (mlen + 63) >> 6;
+        // (as a rule the next one is a few entries further on, in the word that holds `from`: that word alone is read
+        // first, by all lanes at once)
+        if ((from >> 6) < nw) {
+            uint64_t word = um[from >> 6] & (~0ull << (from & 63));
+            if ((from >> 6) == nw - 1 && (mlen & 63) != 0) word &= (1ull << (mlen & 63)) - 1ull;
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)word);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(word >> 32));
+            const uint64_t wu = ((uint64_t)hi << 32) | lo;
+            if (wu != 0) { m1 = (from & ~63) + __builtin_ctzll(wu); return; }
+            from = (from | 63) + 1;
+        }
+        for (int w0 = from >> 6; w0 < nw; w0 += WAVE) {
+            const int w = w0 + lane;
+            uint64_t word = w < nw ? um[w] : 0ull;
+            if (w == (from >> 6)) word &= ~0ull << (from & 63);
+            if (w == nw - 1 && (mlen & 63) != 0) word &= (1ull << (mlen & 63)) - 1ull;
+            const uint64_t any = __builtin_amdgcn_ballot_w64(word != 0);
+            if (any != 0) {
+                const int l = __builtin_ctzll(any);
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)word, l);
+                const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(word >> 32), l);
+                m1 = (w0 + l) * 64 + __builtin_ctzll(((uint64_t)hi << 32) | lo);
+                break;
+            }
+        }
+    };
     // LONG: the `pend` worst entries of M and D together leave, and the worst entry that remains is read
     auto trim_tails = [&] {
         ListTails t;
@@ -150,9 +180,12 @@ __global__ __launch_bounds__(GRAPH_THREADS, RPG == 2 ? 1 : QREG ? 2 : 3) void gr
         worst_k = mlen + len < ef ? 0u : len <= 0 ? wa : mlen <= 0 ? wt : min(wa, wt);
     };
     // LONG: M <- merge of M and D; D <- empty
+    // (the thread number through an empty asm: nothing computed from it is kept in registers across the search loop, 1 to
+    // 2.5 % of the searches with long lists; with counters and two neighbours per group it costs 2 % instead)
+    auto opaque = [](int x) { if constexpr (!(NS && RPG == 2)) asm volatile("" : "+v"(x)); return x; };
     auto rebuild = [&] {
         const int total = mlen + len;                     // <= ef: the tails have been cut
-        const int f0 = rebuild_list(Ms, Mi, um, mlen, ls(cur), li(cur), len, ls(cur ^ 1), li(cur ^ 1), ctl, tid);
+        const int f0 = rebuild_list(Ms, Mi, um, mlen, ls(cur), li(cur), len, ls(cur ^ 1), li(cur ^ 1), ctl, opaque(tid));
         for (int i = tid; i < DCAP; i += NT) { ls(0)[i] = -INFINITY; ls(1)[i] = -INFINITY; li(0)[i] = EXPANDED; li(1)[i] = EXPANDED; }
         const int from = min(m1 >= 0 ? m1 : total, f0);   // nothing unexpanded lies below either
         mlen = total;
@@ -252,7 +285,7 @@ __global__ __launch_bounds__(GRAPH_THREADS, RPG == 2 ? 1 : QREG ? 2 : 3) void gr
     int n_expand = 0, early = 0;
     // the samples are followed only when they can end the search or the caller wants the counters
     const bool track = NS && (ns.tau < INFINITY || ns.stats != nullptr || ns.ema != nullptr);
-    typename RowScorer<T, QREG>::Loads x[RPG];
+    typename RowScorer<T, QREG, true>::Loads x[RPG];
 
     // ---- select: the first SW unexpanded entries of the list, in order, into this wave's sel arrays --------------
     int nsel = 0;
