@@ -153,6 +153,9 @@ inline StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int K
     return pl;
 }
 
+// Maxima of a query, one of 2^g rows: N is a whole number of tiles (wmf > 0), or any number, and there are a multiple of 4.
+inline int64_t maxima_of(int wmf, int64_t N, int g) { return wmf > 0 ? N >> g : (((N - 1) >> g) + 1 + 3) & ~(int64_t)3; }
+
 // Rows per group of the matrix-core kernel, by the time of what follows the products, in us: the maxima are written and
 // read once and the rows of k groups are read again, at some 4 TB/s over all queries; one query alone waits for its
 // maxima (twice, 1024 a wave at a time) and, unless groups are single rows, for its rows (32 a wave, 192 columns at once).
@@ -163,7 +166,7 @@ inline int wide_group_log(int cus, int wmf, int64_t N, int row_bytes, int B, int
     double least = INFINITY;
     for (int g : {0, 2, 4, 5, 6}) {
         if (wmf == 0 ? g < 4 : (1 << g) > 16 * wmf) continue;
-        if ((size_t)(N >> g) + 1 > most) { best = g; continue; }
+        if ((size_t)maxima_of(wmf, N, g) > most) { best = g; continue; }
         const double n = (double)N / (1 << g), rows = (double)k * (1 << g);
         double us = 8.0 * n * B / 4e6 + 1.6 * n / (1024 * waves);
         if (g > 0) us += rows * row_bytes * B / 4e6 + 3.0 + 1.2 * ceil(rows / (32 * waves)) * ceil(row_bytes / 384.0);
@@ -214,11 +217,11 @@ inline size_t maxima_pass(FlatPlan &pl, int cus, int d, int dtype, int k, size_t
     if (pl.wide) {
         wide_geometry(pl.w, wide_shape(cus, N, B), cus, N, B);
         pl.w.gs_log = wide_group_log(cus, pl.w.wmf, pl.w.slots, d * 2, B, k, most);
-        pl.w.n = pl.w.slots >> pl.w.gs_log;
+        pl.w.n = maxima_of(pl.w.wmf, pl.w.slots, pl.w.gs_log);
     } else {
         pl.w.cus = cus;
         pl.w.gs_log = wide_group_log(cus, 0, N, d * 4, B, k, most);
-        pl.w.n = (((N - 1) >> pl.w.gs_log) + 1 + 3) & ~(int64_t)3;
+        pl.w.n = maxima_of(0, N, pl.w.gs_log);
         pl.st = stream_plan(cus, N, d, dtype, B, 1 << (pl.w.gs_log - 4), 1 << pl.w.gs_log);
     }
     return (size_t)B * (size_t)pl.w.n * sizeof(float);
@@ -230,9 +233,9 @@ inline FlatPlan maxima_part(FlatPlan pl, int64_t rows, int part, int d, int dtyp
     pl.part = part;
     if (pl.wide) {
         wide_geometry(pl.w, pl.w.shape, pl.w.cus, rows, part);
-        pl.w.n = pl.w.slots >> pl.w.gs_log;
+        pl.w.n = maxima_of(pl.w.wmf, pl.w.slots, pl.w.gs_log);
     } else {
-        pl.w.n = (((rows - 1) >> pl.w.gs_log) + 1 + 3) & ~(int64_t)3;
+        pl.w.n = maxima_of(0, rows, pl.w.gs_log);
         pl.st = stream_plan(pl.w.cus, rows, d, dtype, part, 1 << (pl.w.gs_log - 4), 1 << pl.w.gs_log);
     }
     return pl;

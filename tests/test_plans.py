@@ -144,6 +144,19 @@ def test_a_buffer_that_served_still_serves(plans, N, d, dtype, B, k, buffer):
     assert flat(plans, N, d, dtype, B, k, buffer)["bytes"] <= buffer
 
 
+def test_a_buffer_of_the_size_that_is_asked_for_gives_the_same_plan(plans):
+    rng = random.Random(11)
+    log = lambda lo, hi: int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+    for _ in range(4000):
+        dtype = rng.choice([0, 1, 2])
+        step = 4 if dtype == 2 else 8
+        N, d, B = log(1, 3e7), step * log(1, 4096 // step), log(1, 5000)
+        k = min(N, rng.randint(1, 16))
+        whole = flat(plans, N, d, dtype, B, k, 1 << 30)
+        if whole["part"] == B and whole["rows"] == N:                 # (not in parts in 1 GiB either)
+            assert flat(plans, N, d, dtype, B, k, max(1, whole["bytes"])) == whole, (N, d, dtype, B, k)
+
+
 def test_a_buffer_too_small_for_parts_is_refused(plans):
     for N, d, dtype, B, k in ((40_000, 256, 0, 96, 3), (1_000_000, 768, 0, 512, 3), (1_000_000, 768, 0, 16, 3)):
         assert flat(plans, N, d, dtype, B, k, 256)["bytes"] > 256
