@@ -408,6 +408,33 @@ def test_flat_in_a_small_buffer_of_the_caller(dtype, N, d, B, k, size):
     assert bool((buf[size:] == 0xAB).all()) and bool((buf[:1024] != 0xAB).any())
 
 
+def test_flat_corpus_in_parts_in_a_graph():
+    """A search in parts through the static entry point, captured and replayed: every replay gives the eager answer for the
+    inputs it finds, with eager searches that use the same workspace between the replays."""
+    N, d, B, k = 1_100_003, 16, 512, 3                               # five parts
+    gen = torch.Generator(device=DEV).manual_seed(9)
+    x = torch.randn(N, d, generator=gen, device=DEV).half()
+    batches = [torch.randn(B, d, generator=gen, device=DEV).half() for _ in range(3)]
+    q = batches[0].clone()
+    ids, sc = torch.empty(B, k, dtype=torch.int32, device=DEV), torch.empty(B, k, device=DEV)
+    static = ann.binding.ann_flat_search_static
+    static(x, q, k, ids=ids, scores=sc)                              # (kernels are loaded before the capture)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        static(x, q, k, ids=ids, scores=sc)
+    other = torch.empty_like(ids), torch.empty_like(sc)
+    for b in batches + batches[:1]:
+        q.copy_(b)
+        ids.fill_(-7)
+        g.replay()
+        torch.cuda.synchronize()
+        want = ann.ann_flat_search_typed(x, b, k)
+        assert torch.equal(ids, want[0]) and torch.equal(sc, want[1])
+        static(x[:300_000], b, k, ids=other[0], scores=other[1])
+        torch.cuda.synchronize()
+
+
 def test_flat_timing_records_every_part():
     """A search in parts leaves a record per part (here 7 of 43 520 rows), all under the code of its class of calls."""
     N, d, B, k, size = 300_007, 64, 300, 5, 1 << 20
