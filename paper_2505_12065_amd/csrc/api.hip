@@ -507,7 +507,7 @@ int ann_graph_search_nonstall_typed(const void *corpus, int64_t N, int32_t d, in
     ns.stats = stats;
     ns.ema = ema;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (graph_step_pays(st->cus, N, d * elem_bytes(dtype), R, B, ef, true, tau))
+    if (graph_step_pays(st->cus, N, d, elem_bytes(dtype), R, B, ef, true, tau))
         return graph_step_run(st, corpus, N, d, dtype, graph, R, entry, queries, B, k, ef, ids, scores, true, ns, s);
     void *vis = nullptr;
     if (int rc = workspace_for(st, &st->vis, &st->vis_bytes, (size_t)B * (size_t)ns.words * 4, &vis)) return rc;
@@ -529,7 +529,7 @@ static int graph_search_any(const void *corpus, int64_t N, int32_t d, int32_t dt
     std::lock_guard<std::mutex> lock(g_mu);
     DeviceState *st = nullptr;
     if (int rc = device_state(&st)) return rc;
-    if (graph_step_pays(st->cus, N, d * elem_bytes(dtype), R, B, ef, false, INFINITY)) {
+    if (graph_step_pays(st->cus, N, d, elem_bytes(dtype), R, B, ef, false, INFINITY)) {
         NonStall ns{};
         ns.entries = entries;
         ns.n_entries = n_entries;

@@ -16,7 +16,7 @@ SHIM = r"""
 #include "plan.hpp"
 using namespace ann;
 extern "C" int step_pays(int cus, int64_t N, int row_bytes, int R, int B, int ef, int counters, float tau) {
-    return graph_step_pays(cus, N, row_bytes, R, B, ef, counters != 0, tau);
+    return graph_step_pays(cus, N, row_bytes / 2, 2, R, B, ef, counters != 0, tau);
 }
 // out: kind (0 lists, 1 direct, 2 matrix cores, 3 streaming with maxima), queries and rows at a time, maxima of a query,
 // log2 of the rows they stand for, offset of the k best so far, workspace, maxima of the smallest last part
@@ -78,6 +78,10 @@ def flat(L, N, d, dtype, B, k, limit):
     (200_000, 1536, 32, 4, 320, False),          # 0.90
     (1_000_000, 1536, 32, 1, 512, True),         # 2.97
     (1_000_000, 1536, 32, 512, 64, False),
+    (1_000_000, 1536, 32, 512, 9000, False),     # 0.66: two workgroups per compute unit one by one, one in steps
+    (50_000, 1536, 32, 512, 9000, True),         # 1.42
+    (1_000_000, 1536, 32, 512, 10_000, True),    # 1.18: one and one
+    (1_000_000, 1536, 32, 512, 8192, True),      # 1.05: two and two
 ])
 def test_steps_only_where_they_were_measured_to_pay(plans, N, row, R, B, ef, pays):
     assert bool(plans.step_pays(CUS, N, row, R, B, ef, 0, float("inf"))) == pays
