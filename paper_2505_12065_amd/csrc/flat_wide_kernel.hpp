@@ -191,12 +191,15 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
                 });
             });
         }
+        // Where the part starts is added only where a boundary is: left to itself the compiler takes the sum out of the
+        // branch and keeps a second set of row numbers for every search, 0.15 us of the 12.5 of 4096 x 768 rows, B = 12.
+        auto part_start = [&] { int b = after.base; asm volatile("" : "+s"(b)); return b; };
         static_for<WNF>([&](auto jc) {
             constexpr int j = decltype(jc)::value;
             const int q = n0 + (wn * WNF + j) * 32 + l32;
             if (after.s) {                                // rows at or before the query's boundary do not take part
                 const float bs = after.s[min(q, B - 1)];
-                const int bid = after.id[min(q, B - 1)], rafter = rbase + after.base;
+                const int bid = after.id[min(q, B - 1)], rafter = rbase + part_start();
                 static_for<WMF>([&](auto ic) {
                     constexpr int i = decltype(ic)::value;
 #pragma unroll
