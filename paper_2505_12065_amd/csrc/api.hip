@@ -194,7 +194,10 @@ int flat_search_run(const FlatPlan &pl, const void *X, int64_t N, int d, int dty
                 const int64_t rows = N - r0 < pl.rows ? N - r0 : pl.rows;
                 const void *x = static_cast<const char *>(X) + (size_t)r0 * row_bytes;
                 const After a{after.s ? after.s + q0 : nullptr, after.id ? after.id + q0 : nullptr, (int)r0};
-                const FlatPlan one = maxima_part(pl, rows, b, d, dtype);
+                FlatPlan last;
+                const bool whole = rows == pl.rows && b == pl.part;
+                if (!whole) last = maxima_part(pl, rows, b, d, dtype);
+                const FlatPlan &one = whole ? pl : last;
                 hipError_t e;
                 {
                     TimedScope timed(code, stream);
