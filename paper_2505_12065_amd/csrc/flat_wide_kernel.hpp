@@ -192,7 +192,7 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
             });
         }
         // Where the part starts is added only where a boundary is: left to itself the compiler takes the sum out of the
-        // branch and keeps a second set of row numbers for every search, 0.15 us of the 12.5 of 4096 x 768 rows, B = 12.
+        // branch and keeps a second set of row numbers for every search, 0.15 us of the 12.6 of 1024 rows x 768, B = 512.
         auto part_start = [&] { int b = after.base; asm volatile("" : "+s"(b)); return b; };
         static_for<WNF>([&](auto jc) {
             constexpr int j = decltype(jc)::value;
