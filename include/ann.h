@@ -167,8 +167,9 @@ int ann_flat_search_static(const void *corpus, int64_t N, int32_t d, int32_t dty
  *
  * One workgroup serves one query; the candidate list lives in LDS.  Up to ef = 512
  * (2048 when R > 32) the visited filter does too and no workspace is used; longer lists
- * score so many nodes that an exact visited bitset in global memory is used instead (the
- * workspace of ann_graph_search_nonstall_typed, same size and rules).  d, R and ef together
+ * score so many nodes that an exact visited bitset is used instead, in global memory (the
+ * workspace of ann_graph_search_nonstall_typed, same size and rules) unless it fits LDS beside the
+ * list and either pays there or finds no workspace at hand.  d, R and ef together
  * must fit the 160 KB of LDS (ef = 16384 fits with d <= 1024 at 16 bits), else
  * ANN_ERR_INVALID.
  */

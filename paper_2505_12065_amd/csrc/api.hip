@@ -96,7 +96,6 @@ int grow(void **buf, size_t *have, size_t bytes) {
 
 // The device buffer a call may use as workspace: the caller's when one was set (never grown: a call
 // that needs more fails), else the library's own, grown on demand.
-
 int workspace_for(DeviceState *st, void **own, size_t *own_bytes, size_t bytes, void **out) {
     if (st->user_ws) {
         if (bytes > st->user_bytes)
@@ -108,6 +107,19 @@ int workspace_for(DeviceState *st, void **own, size_t *own_bytes, size_t bytes, 
     if (int rc = grow(own, own_bytes, bytes)) return rc;
     *out = *own;
     return ANN_OK;
+}
+
+// Whether workspace_for gives `bytes` to a call on `stream`: in a caller's buffer if they fit, in the library's own unless that
+// would have to grow while the stream is captured.
+bool at_hand(const DeviceState *st, size_t own_bytes, size_t bytes, hipStream_t stream) {
+    if (st->user_ws) return bytes <= st->user_bytes;
+    if (bytes <= own_bytes) return true;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+        (void)hipGetLastError();                          // (the null stream, while another stream is captured)
+        return false;
+    }
+    return status == hipStreamCaptureStatusNone;
 }
 
 // ---- optional event timing of the main kernels -----------------------------------------------
@@ -532,26 +544,25 @@ static int graph_search_any(const void *corpus, int64_t N, int32_t d, int32_t dt
     std::lock_guard<std::mutex> lock(g_mu);
     DeviceState *st = nullptr;
     if (int rc = device_state(&st)) return rc;
-    if (graph_step_pays(st->cus, N, d, elem_bytes(dtype), R, B, ef, false, INFINITY)) {
-        NonStall ns{};
-        ns.entries = entries;
-        ns.n_entries = n_entries;
-        ns.tau = INFINITY;
+    NonStall ns{};
+    ns.entries = entries;
+    ns.n_entries = n_entries;
+    ns.tau = INFINITY;
+    const size_t vis_bytes = (size_t)B * (size_t)visited_words(N) * 4;
+    const bool pays = graph_step_pays(st->cus, N, d, elem_bytes(dtype), R, B, ef, false, INFINITY);
+    // Steps also where they do not pay but keep the visited set in LDS, and the one-by-one loop's workspace is not at hand.
+    if (pays || (L.two_level && !at_hand(st, st->vis_bytes, vis_bytes, s) &&
+                 graph_step_plan(st->cus, N, d, elem_bytes(dtype), B, ef, false).vis_mode == STEP_VIS_LDS))
         return graph_step_run(st, corpus, N, d, dtype, graph, R, entry, queries, B, k, ef, ids, scores, false, ns, s);
-    }
     if (ef <= GRAPH_EF_DOUBLE && !L.two_level) {
         TimedScope timed(ANN_KERNEL_GRAPH, s);
         return check_launch("graph_search_kernel", launch_graph_search(dtype, corpus, N, d, graph, R, entry, entries, n_entries,
                                                                        queries, B, k, ef, ids, scores, L, s));
     }
-    NonStall ns{};
-    ns.entries = entries;
-    ns.n_entries = n_entries;
-    ns.tau = INFINITY;
     ns.alpha = 0.f;
     ns.words = visited_words(N);
     void *vis = nullptr;
-    if (int rc = workspace_for(st, &st->vis, &st->vis_bytes, (size_t)B * (size_t)ns.words * 4, &vis)) return rc;
+    if (int rc = workspace_for(st, &st->vis, &st->vis_bytes, vis_bytes, &vis)) return rc;
     ns.visited = static_cast<uint32_t *>(vis);
     if (int rc = check_launch("zero_words_kernel", launch_zero_words(ns.visited, (size_t)B * (size_t)ns.words, s)))
         return rc;

@@ -776,6 +776,42 @@ def test_graph_either_side_of_the_size_up_to_which_steps_pay(N, R, B, ef):
         assert strict >= m - 1, (strict, m)
 
 
+def test_graph_long_list_without_workspace_at_hand():
+    """A long list on a graph too large for steps to pay, whose visited set fits LDS: with a caller's buffer too small for the
+    visited sets in memory, and captured while the library holds none, it is searched all the same, to the same bits."""
+    N, d, R, B, ef = 150_001, 520, 32, 20, 600
+    gen = torch.Generator(device=DEV).manual_seed(4)
+    x = torch.nn.functional.normalize(torch.randn(N, d, generator=gen, device=DEV), dim=1).half()
+    batches = [torch.nn.functional.normalize(torch.randn(B, d, generator=gen, device=DEV), dim=1).half() for _ in range(2)]
+    g = torch.randint(-1, N + 1, (N, R), generator=gen, dtype=torch.int32, device=DEV)
+    want = [ann.ann_graph_search_typed(x, g, 5, b, 3, ef) for b in batches]
+    torch.cuda.synchronize()
+    small = torch.full((4096,), 0xAB, dtype=torch.uint8, device=DEV)
+    assert ann.binding.ann_graph_nonstall_workspace_bytes(N, B) > small.numel()
+    try:
+        ann.ann_set_workspace(small)
+        got = ann.ann_graph_search_typed(x, g, 5, batches[0], 3, ef)
+        torch.cuda.synchronize()
+    finally:
+        ann.ann_set_workspace(None)
+    assert torch.equal(got[0], want[0][0]) and torch.equal(got[1], want[0][1])
+    assert bool((small == 0xAB).all())
+    ann.ann_release_workspace()
+    q = batches[0].clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = ann.ann_graph_search_typed(x, g, 5, q, 3, ef)
+    for i in (0, 1, 0):
+        q.copy_(batches[i])
+        got[0].fill_(-7)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[i][0]) and torch.equal(got[1], want[i][1])
+        again = ann.ann_graph_search_typed(x, g, 5, batches[i], 3, ef)        # (grows the workspace between replays)
+        torch.cuda.synchronize()
+        assert torch.equal(again[0], want[i][0])
+
+
 def test_graph_padding_when_few_nodes_are_reachable():
     c = synth.make_corpus(200, 64, 4, seed=2, dtype=torch.float16, zipf_a=None, sigma=0.3)
     q = synth.make_queries(c, 4)
