@@ -385,7 +385,8 @@ def ann_flat_workspace_bytes(N: int, d: int, dtype: torch.dtype, B: int, k: int)
 
 def ann_set_workspace(buf: Optional[torch.Tensor]) -> None:
     """Use `buf` (a contiguous uint8 device tensor the caller keeps alive) as the workspace of its device;
-    None hands the workspace back to the library."""
+    None hands the workspace back to the library.  An exact search that wants more (ann_flat_workspace_bytes) runs in parts,
+    down to parts of 8192 rows; what does not fit even so raises."""
     if buf is None:
         _check(lib().ann_set_workspace(None, 0))
         return
