@@ -204,10 +204,10 @@ def main() -> int:
     kernel_ms = {"flat_b16": sum(stream_ms) / args.steps, "flat_b512": sum(wide_ms[0::2]) / args.steps,
                  "graph_b512": sum(graph_ms) / args.steps}
     coarse_ms = sum(wide_ms[1::2]) / args.steps
-    # (which of its two graph kernels the library runs depends on the sizes: for rows of over 1 KB, 32 slots per node and
-    # up to two queries per compute unit, steps of several expansions from N / 160 list entries up)
+    # (which of its graph kernels the library runs depends on the sizes: for rows of over 512 bytes, 32 slots per node, a visited
+    # set too large for LDS and up to two queries per compute unit, graph_frontier_kernel from 1400 list entries up)
     kernel_of_leg = {"flat_b16": "flat_stream_kernel", "flat_b512": "flat_wide_kernel",
-                     "graph_b512": "graph_step_kernel" if 160 * ef_op >= N else "graph_search_kernel"}
+                     "graph_b512": "graph_frontier_kernel" if ef_op >= 1400 else "graph_search_kernel"}
     leg_ms = [sum(ev[s][i][0].elapsed_time(ev[s][i][1]) for s in range(args.steps)) / args.steps
               for i in range(len(legs))]
     value = B_LARGE / (leg_ms[2] * 1e-3)                         # graph queries/s at the operating point

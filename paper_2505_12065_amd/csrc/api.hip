@@ -470,21 +470,33 @@ static int check_graph(const void *corpus, int64_t N, int32_t d, int32_t dtype, 
 }
 
 // Graphs of at most 32 slots per node.  The visited set needs workspace only where it does not fit LDS.
-static int graph_step_run(DeviceState *st, const void *corpus, int64_t N, int32_t d, int32_t dtype, const int32_t *graph, int32_t R,
-                          int32_t entry, const void *queries, int32_t B, int32_t k, int32_t ef, int32_t *ids, float *scores,
-                          bool counters, NonStall ns, hipStream_t s) {
-    const StepLds L = graph_step_plan(st->cus, N, d, elem_bytes(dtype), B, ef, counters);
-    if (L.total > LDS_MAX) return fail(ANN_ERR_INVALID, "d = %d, ef = %d need %u bytes of LDS", d, ef, L.total);
-    if (L.vis_mode == STEP_VIS_GLOBAL) {
-        ns.words = visited_words(N);
+static int graph_frontier_run(DeviceState *st, int32_t dtype, int32_t B, FrontierArgs args, bool counters, hipStream_t s) {
+    if (args.L.vis_mode == FRONTIER_VIS_GLOBAL) {
+        args.ns.words = visited_words(args.N);
         void *vis = nullptr;
-        if (int rc = workspace_for(st, &st->vis, &st->vis_bytes, (size_t)B * (size_t)ns.words * 4, &vis)) return rc;
-        ns.visited = static_cast<uint32_t *>(vis);
-        if (int rc = check_launch("zero_words_kernel", launch_zero_words(ns.visited, (size_t)B * (size_t)ns.words, s))) return rc;
+        if (int rc = workspace_for(st, &st->vis, &st->vis_bytes, (size_t)B * (size_t)args.ns.words * 4, &vis)) return rc;
+        args.ns.visited = static_cast<uint32_t *>(vis);
+        if (int rc = check_launch("zero_words_kernel", launch_zero_words(args.ns.visited, (size_t)B * (size_t)args.ns.words, s))) return rc;
     }
     TimedScope timed(ANN_KERNEL_GRAPH, s);
-    return check_launch("graph_step_kernel", launch_graph_step(dtype, corpus, N, d, graph, R, entry, queries, B, k, ef, ids, scores,
-                                                               L, counters, ns, s));
+    return check_launch("graph_frontier_kernel", launch_graph_frontier(dtype, B, args, counters, s));
+}
+
+// Whether graph_frontier_kernel takes a call, and its layout.  Where the call would want the workspace of the visited sets
+// (`workspace`: the other kernel does) and that is not at hand, it takes it with the visited set in LDS if that fits.
+static bool frontier_takes(const DeviceState *st, int64_t N, int32_t d, int32_t dtype, int32_t R, int32_t B, int32_t ef, bool counters,
+                           float tau, bool workspace, hipStream_t s, FrontierLds *L) {
+    const int bytes = elem_bytes(dtype);
+    *L = frontier_plan(st->cus, N, d, bytes, B, ef, counters, tau);
+    const bool pays = frontier_pays(st->cus, d * bytes, R, B, ef, counters, tau, *L);
+    if ((pays ? L->vis_mode == FRONTIER_VIS_GLOBAL : workspace) && !at_hand(st, st->vis_bytes, (size_t)B * (size_t)visited_words(N) * 4, s)) {
+        FrontierLds in_lds;
+        if (frontier_in_lds(N, d, bytes, R, ef, in_lds)) {
+            *L = in_lds;
+            return true;
+        }
+    }
+    return pays;
 }
 
 int64_t ann_graph_nonstall_workspace_bytes(int64_t N, int32_t B) {
@@ -522,8 +534,9 @@ int ann_graph_search_nonstall_typed(const void *corpus, int64_t N, int32_t d, in
     ns.stats = stats;
     ns.ema = ema;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (graph_step_pays(st->cus, N, d, elem_bytes(dtype), R, B, ef, true, tau))
-        return graph_step_run(st, corpus, N, d, dtype, graph, R, entry, queries, B, k, ef, ids, scores, true, ns, s);
+    FrontierLds F;
+    if (frontier_takes(st, N, d, dtype, R, B, ef, true, tau, true, s, &F))
+        return graph_frontier_run(st, dtype, B, FrontierArgs{corpus, N, d, R, graph, queries, entry, k, ef, ids, scores, F, ns}, true, s);
     void *vis = nullptr;
     if (int rc = workspace_for(st, &st->vis, &st->vis_bytes, (size_t)B * (size_t)ns.words * 4, &vis)) return rc;
     ns.visited = static_cast<uint32_t *>(vis);
@@ -548,12 +561,15 @@ static int graph_search_any(const void *corpus, int64_t N, int32_t d, int32_t dt
     ns.entries = entries;
     ns.n_entries = n_entries;
     ns.tau = INFINITY;
-    const size_t vis_bytes = (size_t)B * (size_t)visited_words(N) * 4;
-    const bool pays = graph_step_pays(st->cus, N, d, elem_bytes(dtype), R, B, ef, false, INFINITY);
-    // Steps also where they do not pay but keep the visited set in LDS, and the one-by-one loop's workspace is not at hand.
-    if (pays || (L.two_level && !at_hand(st, st->vis_bytes, vis_bytes, s) &&
-                 graph_step_plan(st->cus, N, d, elem_bytes(dtype), B, ef, false).vis_mode == STEP_VIS_LDS))
-        return graph_step_run(st, corpus, N, d, dtype, graph, R, entry, queries, B, k, ef, ids, scores, false, ns, s);
+    FrontierLds F;
+    if (frontier_takes(st, N, d, dtype, R, B, ef, false, INFINITY, L.two_level, s, &F))
+        return graph_frontier_run(st, dtype, B, FrontierArgs{corpus, N, d, R, graph, queries, entry, k, ef, ids, scores, F, ns}, false, s);
+    if (ef <= GRAPH_EF_TWO_LEVEL && graph_step_pays(st->cus, N, d, elem_bytes(dtype), R, B, ef, false, INFINITY)) {
+        const StepLds S = graph_step_plan(st->cus, d, elem_bytes(dtype), B, ef);
+        TimedScope timed(ANN_KERNEL_GRAPH, s);
+        return check_launch("graph_step_kernel", launch_graph_step(dtype, corpus, N, d, graph, R, entry, entries, n_entries, queries, B, k,
+                                                                   ef, ids, scores, S, s));
+    }
     if (ef <= GRAPH_EF_DOUBLE && !L.two_level) {
         TimedScope timed(ANN_KERNEL_GRAPH, s);
         return check_launch("graph_search_kernel", launch_graph_search(dtype, corpus, N, d, graph, R, entry, entries, n_entries,
@@ -562,7 +578,7 @@ static int graph_search_any(const void *corpus, int64_t N, int32_t d, int32_t dt
     ns.alpha = 0.f;
     ns.words = visited_words(N);
     void *vis = nullptr;
-    if (int rc = workspace_for(st, &st->vis, &st->vis_bytes, vis_bytes, &vis)) return rc;
+    if (int rc = workspace_for(st, &st->vis, &st->vis_bytes, (size_t)B * (size_t)ns.words * 4, &vis)) return rc;
     ns.visited = static_cast<uint32_t *>(vis);
     if (int rc = check_launch("zero_words_kernel", launch_zero_words(ns.visited, (size_t)B * (size_t)ns.words, s)))
         return rc;

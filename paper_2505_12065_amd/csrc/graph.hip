@@ -19,18 +19,26 @@ __global__ __launch_bounds__(256) void zero_words_kernel(u4 *__restrict__ p, siz
         p[i] = zero_chunk();
 }
 
-hipError_t launch_graph_step_f16(const void *, int64_t, int, const int32_t *, int, int, const void *, int, int, int, int32_t *,
-                                 float *, const StepLds &, bool, const NonStall &, hipStream_t);
-hipError_t launch_graph_step_bf16(const void *, int64_t, int, const int32_t *, int, int, const void *, int, int, int, int32_t *,
-                                  float *, const StepLds &, bool, const NonStall &, hipStream_t);
-hipError_t launch_graph_step_f32(const void *, int64_t, int, const int32_t *, int, int, const void *, int, int, int, int32_t *,
-                                 float *, const StepLds &, bool, const NonStall &, hipStream_t);
+#define ANN_STEP_ARGS \
+    const void *X, int64_t N, int d, const int32_t *graph, int R, int entry, const int32_t *entries, int n_entries, const void *Q, int B, \
+        int k, int ef, int32_t *ids, float *scores, const StepLds &L, hipStream_t stream
+hipError_t launch_graph_step_f16(ANN_STEP_ARGS);
+hipError_t launch_graph_step_bf16(ANN_STEP_ARGS);
+hipError_t launch_graph_step_f32(ANN_STEP_ARGS);
 
-hipError_t launch_graph_step(int dtype, const void *X, int64_t N, int d, const int32_t *graph, int R, int entry, const void *Q,
-                             int B, int k, int ef, int32_t *ids, float *scores, const StepLds &L, bool counters,
-                             const NonStall &ns, hipStream_t stream) {
+hipError_t launch_graph_step(int dtype, ANN_STEP_ARGS) {
     return (dtype == 0 ? launch_graph_step_f16 : dtype == 1 ? launch_graph_step_bf16 : launch_graph_step_f32)(
-        X, N, d, graph, R, entry, Q, B, k, ef, ids, scores, L, counters, ns, stream);
+        X, N, d, graph, R, entry, entries, n_entries, Q, B, k, ef, ids, scores, L, stream);
+}
+#undef ANN_STEP_ARGS
+
+hipError_t launch_graph_frontier_f16(int, const FrontierArgs &, bool, hipStream_t);
+hipError_t launch_graph_frontier_bf16(int, const FrontierArgs &, bool, hipStream_t);
+hipError_t launch_graph_frontier_f32(int, const FrontierArgs &, bool, hipStream_t);
+
+hipError_t launch_graph_frontier(int dtype, int B, const FrontierArgs &args, bool counters, hipStream_t stream) {
+    return (dtype == 0 ? launch_graph_frontier_f16 : dtype == 1 ? launch_graph_frontier_bf16 : launch_graph_frontier_f32)(B, args, counters,
+                                                                                                                         stream);
 }
 
 namespace {

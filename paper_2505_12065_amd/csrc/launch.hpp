@@ -60,9 +60,26 @@ struct NonStall {
     int32_t *stats;           // [B][3] = (early exit, scored nodes, expansions), may be null
     float *ema;               // [B] final moving average, may be null
 };
-hipError_t launch_graph_step(int dtype, const void *X, int64_t N, int d, const int32_t *graph, int R, int entry, const void *Q,
-                             int B, int k, int ef, int32_t *ids, float *scores, const StepLds &L, bool counters,
-                             const NonStall &ns, hipStream_t stream);
+// dtype: ANN_F16 / ANN_BF16 / ANN_F32 codes 0 / 1 / 2
+// graph_frontier_kernel, the search of most calls on graphs of at most 32 slots per node.  counters: with the maturity exit and
+// its counters; else only the entry nodes of `ns` and, where the visited set is in memory, that.
+struct FrontierArgs {
+    const void *X;            // [N, d]
+    int64_t N;
+    int d, R;
+    const int32_t *graph;     // [N, R]
+    const void *Q;            // [B, d]
+    int entry, k, ef;
+    int32_t *ids;             // [B, k]
+    float *scores;
+    FrontierLds L;
+    NonStall ns;
+};
+hipError_t launch_graph_frontier(int dtype, int B, const FrontierArgs &args, bool counters, hipStream_t stream);
+// Steps of several expansions on a list in LDS, with an id cache: short lists without counters.
+hipError_t launch_graph_step(int dtype, const void *X, int64_t N, int d, const int32_t *graph, int R, int entry,
+                             const int32_t *entries, int n_entries, const void *Q, int B, int k, int ef, int32_t *ids, float *scores,
+                             const StepLds &L, hipStream_t stream);
 // dtype: ANN_F16 / ANN_BF16 / ANN_F32 codes 0 / 1 / 2
 // entries: null, or device [B, n_entries] per-query entry nodes used instead of `entry`
 hipError_t launch_graph_search(int dtype, const void *X, int64_t N, int d, const int32_t *graph, int R, int entry,

@@ -358,20 +358,16 @@ constexpr uint32_t TL_MS = TL_UM + 8 * (16384 / 64) + 32;   // um: a bit per ent
 // words of one query's visited bitset: one bit per node, rounded to 64-byte units
 inline int64_t visited_words(int64_t N) { return (N + 511) / 512 * 16; }
 
-// graph_step_kernel (graphs of at most 32 slots per node): how it runs a call, and its LDS
+// graph_step_kernel (graphs of at most 32 slots per node, lists of up to GRAPH_EF_TWO_LEVEL entries): how it runs a call, and its LDS
 constexpr int GRAPH_STEP_MAX_R = 32;
-constexpr int STEP_VIS_LDS = 0, STEP_VIS_CACHE = 1, STEP_VIS_GLOBAL = 2;   // where the visited set is
 struct StepLds {
-    // fixed byte offsets: scores, ids, positions, numbers of a step's neighbours (64 each), control words, then the scratch
-    // of every wave
-    static constexpr uint32_t CS = 0, CI = 256, CP = 512, EV = 768, EW = 1024, FM = 1280, CTL = 1312, MK = 1328,
-                              WAVE0 = 1456, WAVE_BYTES = 576;
-    // byte offsets: list scores and ids (two buffers of ls_bytes each), and for long lists the large part and its bits
-    uint32_t ls, li, ls_bytes, um, ms, mi, vis, q, total;
-    int vis_words, cache_shift, vis_mode;
+    // fixed byte offsets: scores, ids, positions, numbers of a step's neighbours (64 each), marks, then the scratch of every wave
+    static constexpr uint32_t CS = 0, CI = 256, CP = 512, EV = 768, EW = 1024, FM = 1280, MK = 1312, WAVE0 = 1440, WAVE_BYTES = 96;
+    // byte offsets: list scores and ids (two buffers of ls_bytes each), id cache, query
+    uint32_t ls, li, ls_bytes, vis, q, total;
+    int vis_words, cache_shift;                           // of the id cache
     int rows_per_group;                                   // neighbours a row group scores in a step: 1 or 2
     bool dense;                                           // three workgroups per compute unit, query read from LDS
-    bool long_list;
 };
 
 inline GraphLds graph_lds_layout(int d, int elem_bytes, int R, int ef) {
@@ -436,47 +432,126 @@ inline GraphLds graph_lds_layout(int d, int elem_bytes, int R, int ef) {
     return lay(bits);
 }
 
-inline StepLds graph_step_plan(int cus, int64_t N, int d, int elem_bytes, int B, int ef, bool counters) {
+inline StepLds graph_step_plan(int cus, int d, int elem_bytes, int B, int ef) {
     auto up = [](uint32_t x) { return (x + 15u) & ~15u; };
     StepLds L{};
-    L.long_list = ef > GRAPH_EF_TWO_LEVEL;
     L.rows_per_group = B <= cus ? 2 : 1;
-    const uint32_t entries = L.long_list || ef <= GRAPH_DELTA ? (uint32_t)GRAPH_DELTA : ((uint32_t)ef + 63u) & ~63u;
+    const uint32_t entries = ef <= GRAPH_DELTA ? (uint32_t)GRAPH_DELTA : ((uint32_t)ef + 63u) & ~63u;
     uint32_t off = up(StepLds::WAVE0 + GRAPH_WAVES * StepLds::WAVE_BYTES);
     L.ls_bytes = 4u * entries;
     L.ls = off; off = up(off + 2u * L.ls_bytes);
     L.li = off; off = up(off + 2u * L.ls_bytes);
-    if (L.long_list) {
-        L.um = off; off = up(off + 8u * (((uint32_t)ef + 63u) / 64u) + 32u);
-        L.ms = off; off = up(off + 4u * (uint32_t)ef);
-        L.mi = off; off = up(off + 4u * (uint32_t)ef);
-    }
     L.q = off; off = up(off + (uint32_t)d * elem_bytes);
     L.vis = off;
-    // A bit per node in LDS if it leaves the workgroups per compute unit that the batch needs
-    const uint32_t room = (uint32_t)(B <= cus ? LDS_MAX : LDS_MAX / 2);
-    const int64_t words = visited_words(N);
-    if ((int64_t)off + words * 4 <= room) {
-        L.vis_mode = STEP_VIS_LDS;
-        L.vis_words = (int)words;
-    } else if (!counters && !L.long_list) {
-        // id cache: a few times the number of nodes a search scores (about 10 ef)
-        L.vis_mode = STEP_VIS_CACHE;
-        int bits = 10;
-        while ((1u << bits) < 32u * (uint32_t)ef && bits < 13) ++bits;
-        L.vis_words = 1 << bits;
-        L.cache_shift = 32 - bits;
-    } else {
-        L.vis_mode = STEP_VIS_GLOBAL;
-    }
+    // id cache: a few times the number of nodes a search scores (about 10 ef)
+    int bits = 10;
+    while ((1u << bits) < 32u * (uint32_t)ef && bits < 13) ++bits;
+    L.vis_words = 1 << bits;
+    L.cache_shift = 32 - bits;
     L.total = up(off + 4u * (uint32_t)L.vis_words);
     // More queries than two workgroups per compute unit hold at once, and a layout small enough for three: the form
     // that reads the query from LDS and runs three per compute unit.
-    L.dense = !counters && !L.long_list && B > GRAPH_DENSE_MIN_B && 3 * (size_t)L.total <= LDS_MAX;
+    L.dense = B > GRAPH_DENSE_MIN_B && 3 * (size_t)L.total <= LDS_MAX;
     return L;
 }
 
-// Where steps of several expansions are faster than one expansion at a time.  A step costs two to three expansions of the
+// graph_frontier_kernel (graphs of at most 32 slots per node)
+constexpr int FRONTIER_MOST = 63;                         // most neighbours a step scores
+constexpr int FRONTIER_VIS_LDS = 0, FRONTIER_VIS_GLOBAL = 1;              // where the visited set is
+constexpr int FRONTIER_SPARE = 512, FRONTIER_SPARE_MIN = 280;            // places beyond ef, at least; where room is what counts
+struct FrontierLds {
+    // fixed byte offsets: keys of a step's neighbours (twice), a place to order them in, where they are by hash (twice), counts of
+    // the waves, then the scratch of every wave
+    static constexpr int HASH_BITS = 7, HASHES = 1 << HASH_BITS;
+    static constexpr uint32_t CK = 0, SORTED = 1024, HASH = 1536, CTL = HASH + 8 * HASHES, WAVES = CTL + 80, WAVE_BYTES = 544;
+    // byte offsets: expanded nodes and pool, visited bits, query
+    uint32_t keys, vis, q, total;
+    int cap, spare, vis_words, vis_mode;                  // places of the array; how many above ef a bound may leave in it
+    int waves, width, per_cu;                             // variant: waves of a workgroup, expansions a step tries, workgroups per compute unit
+};
+// A query has a compute unit to itself: 8 waves, which score all neighbours of a step at once.  More queries: 4 waves, two
+// workgroups to a compute unit; beyond what these hold at once three, with the query read from LDS.  200 k x 768, R = 32, ef = 192, us,
+// one / two / three workgroups: B = 256 427 / 605 / -; 512 794 / 662 / 720; 1024 1424 / 1206 / 1071.  (Three where little room is left
+// for the array find bounds all the time: 1 M x 768, B = 1024, ef = 4096 18.8 ms by two, 20.3 by three.)
+// width: trying 8 expansions instead of 4 costs a step some 500 clocks and pays where steps commit more than three: where a
+// search covers most of its graph (200 k x 768, B = 256, ef = 2048 2480 / 2580 us with 4 / 8; 60 k x 384, ef = 4096 3240 / 2770), and
+// with the maturity exit, which most queries leave while nearly every expansion stands (ef = 256, d = 384 312 / 257).
+inline bool frontier_layout(int64_t N, int d, int elem_bytes, int ef, int waves, int per_cu, int width, int spare_min, FrontierLds &L) {
+    auto up = [](uint32_t x) { return (x + 15u) & ~15u; };
+    L = FrontierLds{};
+    L.waves = waves;
+    L.per_cu = per_cu;
+    L.width = width;
+    const int64_t room = (int64_t)(LDS_MAX / per_cu) & ~15, words = visited_words(N);
+    uint32_t off = up(FrontierLds::WAVES + waves * FrontierLds::WAVE_BYTES);
+    L.q = off; off = up(off + (uint32_t)d * elem_bytes);
+    L.vis = off;
+    if (off + words * 4 + 8 * ((int64_t)ef + spare_min) <= room) {
+        L.vis_mode = FRONTIER_VIS_LDS;
+        L.vis_words = (int)words;
+    } else {
+        L.vis_mode = FRONTIER_VIS_GLOBAL;
+    }
+    off = up(off + 4u * (uint32_t)L.vis_words);
+    L.keys = off;
+    // The more places beyond ef, the rarer a bound has to be found; all that a search of a short list scores fits.
+    int64_t spare = ef / 2 < 1536 ? 1536 : ef / 2 > 4096 ? 4096 : ef / 2;
+    const int64_t fit = (room - off) / 8 - ef;
+    if (spare > fit) spare = fit < spare_min ? spare_min : fit;
+    L.cap = ef + (int)spare;
+    L.spare = (int)spare / 2 - 136;                       // (a bound leaves room for a step and more: see the kernel)
+    L.total = up(off + 8u * (uint32_t)L.cap);
+    return (int64_t)L.total <= room;
+}
+inline FrontierLds frontier_plan(int cus, int64_t N, int d, int elem_bytes, int B, int ef, bool counters, float tau) {
+    const int width = (counters && tau < 1.0f) || 32 * (int64_t)ef >= N ? 8 : 4;
+    auto lay = [&](int waves, int per_cu, FrontierLds &L) {
+        return frontier_layout(N, d, elem_bytes, ef, waves, per_cu, width, per_cu == 3 ? 2 * FRONTIER_SPARE : FRONTIER_SPARE, L);
+    };
+    FrontierLds L;
+    if (B > 2 * cus && lay(4, 3, L)) return L;
+    if (B > cus && lay(4, 2, L)) return L;
+    lay(8, 1, L);
+    return L;
+}
+// The layout that finds room for the visited set in LDS on the largest graphs; false: too large.
+inline bool frontier_in_lds(int64_t N, int d, int elem_bytes, int R, int ef, FrontierLds &L) {
+    return R <= GRAPH_STEP_MAX_R && frontier_layout(N, d, elem_bytes, ef, 4, 1, 8, FRONTIER_SPARE_MIN, L) && L.vis_mode == FRONTIER_VIS_LDS;
+}
+
+// Where graph_frontier_kernel is faster than the others (graph_search_kernel, graph_step_kernel, whichever was better), us, others / it:
+//   every query a compute unit to itself, R = 32: 200 k x 768 fp16, B = 256 ef = 16 93 / 91, 48 198 / 174, 192 587 / 427, 768 2202 / 1122,
+//     4096 7992 / 4101; B = 1 128 / 86, 416 / 226, 1916 / 558 at ef = 48, 192, 768; 60 k x 384 1121 / 510 (ef = 384); 1 M x 768 with the
+//     visited set in memory 6196 / 3535 (ef = 2048), 22 838 / 12 592 (8192).  The very shortest lists end before its larger start is
+//     paid for (ef = 3: 30.4 / 35.8), and rows of 4 KB, of which a step scores some for nothing, make it later (B = 256, ef = 16
+//     134 / 156, 64 360 / 349)
+//   two workgroups a compute unit (B = 512): narrow graphs any list (R = 16 97 / 96, 362 / 304, 2150 / 1334 at ef = 16, 96, 768); at
+//     R = 32 steps hold little more than one expansion's neighbours while the list fills: ef = 48 217 / 257, 192 640 / 662, 384
+//     1264 / 1041, 1536 4372 / 2684; R = 24 253 / 284 at ef = 64, 629 / 586 at 192
+//   three (B = 2048): R = 32 799 / 804 at ef = 64, 2074 / 1726 at 192; B = 1024 490 / 512, 1222 / 1071
+//   visited set in memory: short lists stay with the id caches, which need no workspace; R = 32, B = 512, 1 M x 768 ef = 600 2215 /
+//     2516, 1024 3619 / 3799, 2048 6959 / 6364, 4096 13 421 / 10 524; R = 24 or rows of 256 bytes all of them (700 k, ef = 600 2086 /
+//     1983, 1907 / 1812)
+//   maturity exit, tau = 0.9: R = 32, 200 k x 384 bf16, B = 256 ef = 32 103 / 94, 64 174 / 113, 256 326 / 249, 2048 2249 / 1488; R = 16 B = 256
+//     ef = 32 106 / 128, 64 170 / 166; B = 1024 64 339 / 352, 96 429 / 427.  tau = 3 (no query leaves): B = 256 R = 32 64 318 / 319,
+//     128 535 / 516, R = 16 96 357 / 391, 200 651 / 641; B = 512 256 1036 / 1137, 512 2032 / 1891
+inline bool frontier_pays(int cus, int row_bytes, int R, int B, int ef, bool counters, float tau, const FrontierLds &L) {
+    if (R > GRAPH_STEP_MAX_R || L.total > LDS_MAX) return false;
+    if (counters) {
+        if (tau < 1.0f) return ef >= (B > 2 * cus ? 96 : R > 16 && B >= 8 ? 32 : 64);
+        return ef >= (B > cus ? 448 : R > 16 ? 128 : 192);
+    }
+    const bool global = L.vis_mode == FRONTIER_VIS_GLOBAL;
+    if (global && ef <= GRAPH_EF_TWO_LEVEL) return false;
+    if (B <= cus) return ef >= (row_bytes > 2048 ? 72 : R > 16 ? 12 : 8);
+    if (R <= 16) return ef >= 16;
+    if (global) return B > 2 * cus || R <= 24 || row_bytes <= 512 || ef >= 1400;
+    return ef >= (B > 2 * cus ? 96 : R <= 24 ? 128 : 200);
+}
+
+// Where graph_step_kernel is faster than graph_search_kernel, among the calls that graph_frontier_kernel does not take: today
+// those with lists of up to 512 entries on graphs whose visited set does not fit LDS.  (Lists over 512 and the maturity exit are
+// all measured here, but graph_frontier_kernel is faster than both there.)  A step costs two to three expansions of the
 // other kernel, so what decides is how many expansions it commits: the neighbours a step holds (63 for a batch that leaves
 // every query a compute unit, else 32) against the unseen ones that an expansion brings.  Those get fewer as a search covers
 // more of the graph, so the line runs along N / ef, the nodes of the graph per entry of the list, and lies higher for narrow
@@ -512,9 +587,8 @@ inline bool graph_step_pays(int cus, int64_t N, int d, int elem_bytes, int R, in
     } else if (long_list) {
         if (B > cus) reach *= R <= 16 ? 8 : 1;
         if (B > cus && R > 16) reach = reach * (R <= 24 ? (waits ? 30 : 15) : (waits ? 16 : 10)) / 10;
-        if (2 * B > 3 * cus && graph_lds_layout(d, elem_bytes, R, ef).total <= LDS_MAX / 2 &&
-            graph_step_plan(cus, N, d, elem_bytes, B, ef, counters).total > LDS_MAX / 2)
-            reach /= 8;
+        const int64_t step_bytes = 7888 + (ef + 63) / 64 * 8 + 8 * (int64_t)ef + (int64_t)row_bytes;
+        if (2 * B > 3 * cus && graph_lds_layout(d, elem_bytes, R, ef).total <= LDS_MAX / 2 && step_bytes > (int64_t)LDS_MAX / 2) reach /= 8;
     } else {
         if (!waits || ef < 192) return false;
         if (R <= 16) return true;
