@@ -4,14 +4,21 @@
 
 namespace ann {
 namespace {
+template <class T, class C, bool ONE>
+hipError_t launch_one(const WidePlan &pl, const void *X, int64_t N, int d, const void *Q, int B, float *maxima, After after,
+                  hipStream_t stream) {
+    static size_t big = 0;
+    if (hipError_t e = allow_big_lds(reinterpret_cast<const void *>(&flat_wide_kernel<T, C, ONE>), C::LDS_BYTES, &big)) return e;
+    hipLaunchKernelGGL((flat_wide_kernel<T, C, ONE>), dim3(pl.P * pl.NT), dim3(C::THREADS), C::LDS_BYTES, stream, X, N, d, Q, B,
+                       maxima, pl.n, pl.P, pl.NT, pl.gs_log, after);
+    return hipGetLastError();
+}
+
 template <class T, class C>
 hipError_t launch(const WidePlan &pl, const void *X, int64_t N, int d, const void *Q, int B, float *maxima, After after,
                   hipStream_t stream) {
-    static size_t big = 0;
-    if (hipError_t e = allow_big_lds(reinterpret_cast<const void *>(&flat_wide_kernel<T, C>), C::LDS_BYTES, &big)) return e;
-    hipLaunchKernelGGL((flat_wide_kernel<T, C>), dim3(pl.P * pl.NT), dim3(C::THREADS), C::LDS_BYTES, stream, X, N, d, Q, B,
-                       maxima, pl.n, pl.P, pl.NT, pl.gs_log, after);
-    return hipGetLastError();
+    return pl.gs_log == 0 ? launch_one<T, C, true>(pl, X, N, d, Q, B, maxima, after, stream)
+                          : launch_one<T, C, false>(pl, X, N, d, Q, B, maxima, after, stream);
 }
 
 template <class T>
@@ -20,7 +27,7 @@ hipError_t launch_any(const WidePlan &pl, const void *X, int64_t N, int d, const
     switch (pl.shape) {
     case WIDE_LARGE: return launch<T, WideLarge>(pl, X, N, d, Q, B, maxima, after, stream);
     case WIDE_TALL: return launch<T, WideTall>(pl, X, N, d, Q, B, maxima, after, stream);
-    case WIDE_SMALL: return launch<T, WideSmall>(pl, X, N, d, Q, B, maxima, after, stream);
+    case WIDE_MID: return launch<T, WideMid>(pl, X, N, d, Q, B, maxima, after, stream);
     case WIDE_TINY: return launch<T, WideTiny>(pl, X, N, d, Q, B, maxima, after, stream);
     default: return launch<T, WideThin>(pl, X, N, d, Q, B, maxima, after, stream);
     }

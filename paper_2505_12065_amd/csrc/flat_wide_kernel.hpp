@@ -3,16 +3,21 @@
 //
 //   workgroup tile  32 WMF NWM corpus rows x 32 WNF NWN queries, NWM x NWN wavefronts
 //   wavefront tile  32 WMF rows x 32 WNF queries = WMF x WNF MFMA 32x32x16 accumulators
-//   K loop          32 columns of d (64 bytes of a row) per stage, 3 or 4 LDS stages; every stage is filled by direct
-//                   global->LDS loads issued two or three stages ahead.  One load instruction brings 16 rows x
-//                   64 B (4 lanes per row, whole half cache lines) and lands as a 1 KB block of 16 rows; inside a row
-//                   the four 16-byte chunks sit in slots XOR-swizzled by the row number, so the MFMA operand reads
-//                   (32 rows x one chunk) hit all banks
+//   K loop          stages of 64 bytes of a row (the two large tiles) or 128 (the others), 3 or 4 of them in LDS; every stage is
+//                   filled by direct global->LDS loads issued two or three stages ahead.  One load instruction brings a 1 KB
+//                   block, 16 rows x 64 B or 8 rows x 128 B (whole cache lines); inside a row the 16-byte chunks sit in slots
+//                   XOR-swizzled by the row number, so the MFMA operand reads (32 rows x one chunk) hit all banks
 //   epilogue        the largest score of every group of 1, 4, 16, 32 or 16 WMF rows (all of one lane's), nothing else:
 //                   maxima[q, group].  flat_pick_kernel finds the k best groups of a query, which hold its k best
 //                   rows, scores their rows once more by the same instructions and picks the rows
 //
-// A workgroup walks a slab of corpus tiles for one query tile.
+// A workgroup walks a slab of corpus tiles for one query tile.  Blocks are numbered so that neighbours, which run on one
+// XCD, share the operand that is read more often: the slab where the corpus is the larger, else the query tile
+// (977 x 768, B = 5000: 26 -> 23 us with the stores below; every XCD had read all the queries).
+//
+// Stages of whole lines halve the barriers and the L2's requests; three of them leave room for tiles of 256 x 128 at most.
+// 300 k x 768, B = 128: 132 us by 512 x 128 tiles of half lines, 112 by 256 x 128 of whole ones; 123 457 x 776, B = 77 (a row of
+// 12 1/8 lines) 70 -> 64.
 //
 // The epilogue is what decides at most sizes.  Sorted lists per lane, with thresholds from a sampling pass, cost two to
 // three launches, 130 registers of lists and queues, and insertions that never become rare unless a slab has
@@ -46,29 +51,33 @@ __device__ __forceinline__ void bare_barrier() {
 static __device__ __align__(16) unsigned char zero_row_end[16];          // what lies behind the end of a row
 
 // X [N, d], Q [B, d] 16-bit, d a multiple of 8.  maxima [B, n]: n = groups of all tiles, in the order of wide_row.
-// gridDim.x = P * NT; block -> (slab, query tile), blocks of one slab on one XCD; the tiles are dealt to P slabs.
-// 2^gs_log: rows per group, 1, 4, 16, 32 or 16 WMF.  Rows that do not exist or do not come after a query's boundary count as NaN.
-template <class T, class C>
+// gridDim.x = P * NT; the tiles are dealt to P slabs.
+// 2^gs_log: rows per group, ONE: 1, else 4, 16, 32 or 16 WMF (two kernels: the stores of single rows are 40 % of the code,
+// and in one kernel with the rest they cost 1 M x 768, B = 512 1 %).  Rows that do not exist or do not come after a query's boundary count as NaN.
+template <class T, class C, bool ONE>
 __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wide_kernel(
     const void *__restrict__ X, int64_t N, int d, const void *__restrict__ Q, int B, float *__restrict__ maxima, int64_t n,
     int P, int NT, int gs_log, After after) {
     constexpr int WMF = C::WMF, WNF = C::WNF, NST = C::STAGES, LPW = C::LPW, BM = C::BM;
+    constexpr int SB = C::SB, CPR = C::CPR, RPB = C::RPB, NKH = SB / 32;
     extern __shared__ __align__(16) unsigned char stage_mem[];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % C::NWM, wn = wave / C::NWM;
     const int l32 = lane & 31, lhi = lane >> 5;
-    const int rb = d * 2, ksteps = (rb + 63) >> 6;
+    const int rb = d * 2, ksteps = (rb + SB - 1) / SB;
 
     const int lb = xcd_block();
-    const int nt = lb % NT, slab = lb / NT, n0 = nt * C::BN;
+    const bool by_query = N < B;
+    const int nt = by_query ? lb / P : lb % NT, slab = by_query ? lb % P : lb / NT, n0 = nt * C::BN;
     const int64_t mtiles = (N + BM - 1) / BM;
     const int64_t t0 = mtiles * slab / P, t1 = mtiles * (slab + 1) / P;
     const int total = (int)(t1 - t0) * ksteps;
 
-    // Block e of a stage: blocks 0 .. A_BLK - 1 corpus rows, the rest queries.  Lane l fetches row l / 4 of the block;
-    // LDS slot l % 4 of that row receives chunk (l % 4) ^ ((row / 4) % 4) of the stage's 64 bytes.
-    const int my_chunk = (lane & 3) ^ ((lane >> 4) & 3);
+    // Block e of a stage: blocks 0 .. A_BLK - 1 corpus rows, the rest queries.  Lane l fetches row l / CPR of the block;
+    // LDS slot l % CPR of that row receives chunk (l % CPR) ^ swz(row) of the stage's bytes of the row.
+    auto swz = [](int row) { return SB == 64 ? (row >> 2) & 3 : row & 7; };
+    const int my_chunk = (lane & (CPR - 1)) ^ swz(lane / CPR);
     // Address of a load = uniform base (corpus: start of the tile, advanced per k step; queries: start of the query
     // tile) + a 32-bit per-lane offset that does not change from tile to tile, except in the ragged last tile
     // where rows are clamped to N - 1.  In the last stage of rows that end inside it, chunks behind the end come
@@ -79,11 +88,11 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
         for (int e = 0; e < LPW; ++e) {
             const int blk = wave * LPW + e;
             if (blk < C::A_BLK) {
-                int64_t row = tile * BM + blk * 16 + (lane >> 2);
+                int64_t row = tile * BM + blk * RPB + lane / CPR;
                 row = row < N ? row : N - 1;
                 loff[e] = (uint32_t)(row - tile * BM) * (uint32_t)rb + my_chunk * 16;
             } else {
-                int q = n0 + (blk - C::A_BLK) * 16 + (lane >> 2);
+                int q = n0 + (blk - C::A_BLK) * RPB + lane / CPR;
                 q = q < B ? q : B - 1;
                 loff[e] = (uint32_t)(q - n0) * (uint32_t)rb + my_chunk * 16;
             }
@@ -92,7 +101,7 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
     lane_offsets(t0);
     const char *xbase = static_cast<const char *>(X) + (size_t)t0 * BM * rb;              // tile start
     const char *qbase = static_cast<const char *>(Q) + (size_t)n0 * rb;
-    const bool ragged_row = (rb & 63) != 0;
+    const bool ragged_row = (rb & (SB - 1)) != 0;
     int iks = 0, issued = 0, iofs = 0;                   // k step and LDS offset of the next stage to issue
     int64_t itile = t0;
     auto issue = [&] {
@@ -100,12 +109,12 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
         ++issued;
         unsigned char *sbase = stage_mem + iofs;
         if (ragged_row && iks == ksteps - 1) {
-            const bool inside = iks * 64 + my_chunk * 16 < rb;
+            const bool inside = iks * SB + my_chunk * 16 < rb;
 #pragma unroll
             for (int e = 0; e < LPW; ++e) {
                 const int blk = wave * LPW + e;
                 const char *base = blk < C::A_BLK ? xbase : qbase;
-                const char *p = base + iks * 64 + loff[e];
+                const char *p = base + iks * SB + loff[e];
                 ANN_GLOBAL_TO_LDS_16(inside ? p : reinterpret_cast<const char *>(zero_row_end), sbase + blk * 1024);
             }
         } else {
@@ -113,7 +122,7 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
             for (int e = 0; e < LPW; ++e) {
                 const int blk = wave * LPW + e;
                 const char *base = blk < C::A_BLK ? xbase : qbase;
-                ANN_GLOBAL_TO_LDS_16(base + iks * 64 + loff[e], sbase + blk * 1024);
+                ANN_GLOBAL_TO_LDS_16(base + iks * SB + loff[e], sbase + blk * 1024);
             }
         }
         iofs = iofs + C::STAGE_BYTES == C::LDS_BYTES ? 0 : iofs + C::STAGE_BYTES;
@@ -140,19 +149,19 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
         // Operand row r = lane % 32 of a 32-row block pair, chunk 2 kh + lane / 32.  All operand reads of the stage
         // are issued before the first MFMA, so the LDS pipeline always has several 1 KB reads of this wave in flight.
         const unsigned char *sb = stage_mem + cofs;
-        u4 a[2][WMF], b[2][WNF];
+        u4 a[NKH][WMF], b[NKH][WNF];
 #pragma unroll
-        for (int kh = 0; kh < 2; ++kh) {
-            const int lofs = (l32 >> 4) * 1024 + (l32 & 15) * 64 + (((2 * kh + lhi) ^ ((l32 >> 2) & 3)) * 16);
+        for (int kh = 0; kh < NKH; ++kh) {
+            const int lofs = (l32 / RPB) * 1024 + (l32 & (RPB - 1)) * SB + (((2 * kh + lhi) ^ swz(l32 & (RPB - 1))) * 16);
 #pragma unroll
             for (int j = 0; j < WNF; ++j)
-                b[kh][j] = *reinterpret_cast<const u4 *>(sb + (C::A_BLK + (wn * WNF + j) * 2) * 1024 + lofs);
+                b[kh][j] = *reinterpret_cast<const u4 *>(sb + (C::A_BLK + (wn * WNF + j) * (32 / RPB)) * 1024 + lofs);
 #pragma unroll
             for (int i = 0; i < WMF; ++i)
-                a[kh][i] = *reinterpret_cast<const u4 *>(sb + (wm * WMF * 2 + i * 2) * 1024 + lofs);
+                a[kh][i] = *reinterpret_cast<const u4 *>(sb + (wm * WMF + i) * (32 / RPB) * 1024 + lofs);
         }
         __builtin_amdgcn_sched_barrier(0);                // keep the reads ahead of the MFMAs
-        static_for<2>([&](auto kc) {
+        static_for<NKH>([&](auto kc) {
             static_for<WMF>([&](auto ic) {
                 static_for<WNF>([&](auto jc) {
                     constexpr int kh = decltype(kc)::value, i = decltype(ic)::value, j = decltype(jc)::value;
@@ -207,10 +216,37 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
                         acc[i][j][r] = after_boundary(acc[i][j][r], rafter + (i * 32 + 8 * (r / 4) + (r % 4)), bs, bid);
                 });
             }
-            if (q < B) {
-                // this lane's groups of the tile, side by side
-                float *o = maxima + (size_t)q * n + (((size_t)tile * BM + (wm * 2 + lhi) * (16 * WMF)) >> gs_log);
-                if (gs_log == 0) {
+            if constexpr (ONE) {
+                if (tile + 1 == t1 && B > 64) {
+                    // The stages are free: through LDS, so that a store writes whole lines, past the L2 (from the registers
+                    // it is 16 bytes to each of 64 lines, and 20 MB of them wait for the end of the kernel: 977 x 64, B = 5000
+                    // 16.9 -> 11.9 us; 3224 x 576, B = 3326 51 -> 41.5).  Few queries do without the barrier (4364 x 608, B = 28
+                    // 12.6, 12.9 through LDS).
+                    if constexpr (j == 0) bare_barrier();     // every wave has read the last stage
+                    constexpr int U = WMF < 2 ? WMF : 2, ROW = 32 * U + 4, UNITS = 8 * U;
+                    static_assert(32 * ROW * 4 <= C::LDS_BYTES / C::WAVES, "a wave's share of the stages");
+                    float *own = reinterpret_cast<float *>(stage_mem) + wave * (C::LDS_BYTES / C::WAVES / 4);
+                    static_for<WMF / U>([&](auto pc) {
+                        constexpr int i0 = decltype(pc)::value * U;
+                        static_for<U>([&](auto uc) {
+                            constexpr int i = i0 + decltype(uc)::value, u = decltype(uc)::value;
+#pragma unroll
+                            for (int r = 0; r < 16; r += 4)
+                                *reinterpret_cast<f4 *>(own + l32 * ROW + lhi * 16 * U + u * 16 + r) =
+                                    f4{acc[i][j][r], acc[i][j][r + 1], acc[i][j][r + 2], acc[i][j][r + 3]};
+                        });
+                        float *o = maxima + tile * BM + i0 * 16;
+#pragma unroll
+                        for (int e = 0; e < 32 * UNITS / 64; ++e) {
+                            const int row = (e * 64 + ln) / UNITS, unit = ln % UNITS;
+                            const int qr = n0 + (wn * WNF + j) * 32 + row;
+                            const f4 v = *reinterpret_cast<const f4 *>(own + row * ROW + unit * 4);
+                            const int at = (wm * 2 + unit / (4 * U)) * (16 * WMF) + unit % (4 * U) * 4;
+                            if (qr < B) __builtin_nontemporal_store(v, reinterpret_cast<f4 *>(o + (size_t)qr * n + at));
+                        }
+                    });
+                } else if (q < B) {
+                    float *o = maxima + (size_t)q * n + (size_t)tile * BM + (wm * 2 + lhi) * (16 * WMF);
                     static_for<WMF>([&](auto ic) {
                         constexpr int i = decltype(ic)::value;
 #pragma unroll
@@ -218,29 +254,31 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
                             *reinterpret_cast<f4 *>(o + i * 16 + r) =
                                 f4{acc[i][j][r], acc[i][j][r + 1], acc[i][j][r + 2], acc[i][j][r + 3]};
                     });
-                } else {
-                    float m16[WMF];
-                    static_for<WMF>([&](auto ic) {
+                }
+            } else if (q < B) {
+                // this lane's groups of the tile, side by side
+                float *o = maxima + (size_t)q * n + (((size_t)tile * BM + (wm * 2 + lhi) * (16 * WMF)) >> gs_log);
+                float m16[WMF];
+                static_for<WMF>([&](auto ic) {
+                    constexpr int i = decltype(ic)::value;
+                    f4 m;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        m[u] = fmaxf(fmaxf(acc[i][j][4 * u], acc[i][j][4 * u + 1]),
+                                     fmaxf(acc[i][j][4 * u + 2], acc[i][j][4 * u + 3]));
+                    if (gs_log == 2) *reinterpret_cast<f4 *>(o + i * 4) = m;
+                    m16[i] = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
+                });
+                if (gs_log == 4) {
+#pragma unroll
+                    for (int i = 0; i < WMF; ++i) o[i] = m16[i];
+                } else if (gs_log == 5) {
+                    if constexpr (WMF >= 2) static_for<WMF / 2>([&](auto ic) {
                         constexpr int i = decltype(ic)::value;
-                        f4 m;
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-                            m[u] = fmaxf(fmaxf(acc[i][j][4 * u], acc[i][j][4 * u + 1]),
-                                         fmaxf(acc[i][j][4 * u + 2], acc[i][j][4 * u + 3]));
-                        if (gs_log == 2) *reinterpret_cast<f4 *>(o + i * 4) = m;
-                        m16[i] = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
+                        o[i] = fmaxf(m16[2 * i], m16[2 * i + 1]);
                     });
-                    if (gs_log == 4) {
-#pragma unroll
-                        for (int i = 0; i < WMF; ++i) o[i] = m16[i];
-                    } else if (gs_log == 5) {
-                        if constexpr (WMF >= 2) static_for<WMF / 2>([&](auto ic) {
-                            constexpr int i = decltype(ic)::value;
-                            o[i] = fmaxf(m16[2 * i], m16[2 * i + 1]);
-                        });
-                    } else if (gs_log == 6) {
-                        if constexpr (WMF == 4) *o = fmaxf(fmaxf(m16[0], m16[1]), fmaxf(m16[2], m16[3]));
-                    }
+                } else if (gs_log == 6) {
+                    if constexpr (WMF == 4) *o = fmaxf(fmaxf(m16[0], m16[1]), fmaxf(m16[2], m16[3]));
                 }
             }
         });

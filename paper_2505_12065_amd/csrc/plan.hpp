@@ -45,23 +45,24 @@ inline int stream_waves(int elem_bytes, int nqg, int lds_steps) {
 }
 
 // ---- exact search, matrix-core kernel ----------------------------------------------------------------
-template <int WMF_, int WNF_, int NWM_, int NWN_, int STAGES_, int PER_CU_>
+template <int WMF_, int WNF_, int NWM_, int NWN_, int STAGES_, int PER_CU_, int SB_ = 64>
 struct WideCfg {
     static constexpr int WMF = WMF_, WNF = WNF_, NWM = NWM_, NWN = NWN_, STAGES = STAGES_, PER_CU = PER_CU_;
     static constexpr int WAVES = NWM * NWN, THREADS = WAVES * WAVE;
     static constexpr int BM = 32 * WMF * NWM, BN = 32 * WNF * NWN;
-    static constexpr int A_BLK = BM / 16, BLKS = A_BLK + BN / 16;       // 1 KB blocks of a stage: 16 rows x 64 B each
+    static constexpr int SB = SB_, CPR = SB / 16, RPB = 1024 / SB;      // bytes and 16-byte chunks of a row in a stage; rows to a block
+    static constexpr int A_BLK = BM / RPB, BLKS = A_BLK + BN / RPB;     // 1 KB blocks of a stage
     static constexpr int LPW = BLKS / WAVES;                            // blocks loaded per wave and stage
     static_assert(BLKS % WAVES == 0, "blocks must divide evenly over the waves");
     static constexpr int STAGE_BYTES = BLKS * 1024, LDS_BYTES = STAGES * STAGE_BYTES;
 };
 using WideLarge = WideCfg<4, 2, 2, 4, 4, 1>;              // 256 x 256, 8 waves
 using WideTall = WideCfg<4, 2, 4, 2, 4, 1>;               // 512 x 128, 8 waves
-using WideSmall = WideCfg<2, 2, 2, 2, 3, 3>;              // 128 x 128, 4 waves, three workgroups per compute unit
-using WideThin = WideCfg<2, 1, 2, 2, 4, 3>;               // 128 x 64, 4 waves, three
-using WideTiny = WideCfg<1, 1, 2, 2, 6, 3>;               // 64 x 64, 4 waves, three
+using WideMid = WideCfg<2, 2, 4, 2, 3, 1, 128>;           // 256 x 128, 8 waves
+using WideThin = WideCfg<2, 1, 2, 2, 3, 2, 128>;          // 128 x 64, 4 waves, two workgroups per compute unit
+using WideTiny = WideCfg<1, 1, 2, 2, 4, 2, 128>;          // 64 x 64, 4 waves, two
 
-constexpr int WIDE_LARGE = 0, WIDE_TALL = 1, WIDE_SMALL = 2, WIDE_THIN = 3, WIDE_TINY = 4;
+constexpr int WIDE_LARGE = 0, WIDE_TALL = 1, WIDE_MID = 2, WIDE_THIN = 3, WIDE_TINY = 4;
 struct WidePlan {
     int cus, shape, wmf;         // compute units; workgroup tile (a WideCfg); its row fragments per wave
     int NT, P;                   // query tiles x slabs of the corpus
@@ -84,14 +85,14 @@ inline void wide_geometry(WidePlan &pl, int shape, int cus, int64_t N, int B) {
     switch (shape) {
     case WIDE_LARGE: return geometry<WideLarge>(pl, cus, N, B);
     case WIDE_TALL: return geometry<WideTall>(pl, cus, N, B);
-    case WIDE_SMALL: return geometry<WideSmall>(pl, cus, N, B);
+    case WIDE_MID: return geometry<WideMid>(pl, cus, N, B);
     case WIDE_TINY: return geometry<WideTiny>(pl, cus, N, B);
     default: return geometry<WideThin>(pl, cus, N, B);
     }
 }
 
 inline int wide_rows(int shape) {                         // corpus rows of a tile
-    return shape == WIDE_LARGE ? WideLarge::BM : shape == WIDE_TALL ? WideTall::BM : shape == WIDE_SMALL ? WideSmall::BM
+    return shape == WIDE_LARGE ? WideLarge::BM : shape == WIDE_TALL ? WideTall::BM : shape == WIDE_MID ? WideMid::BM
            : shape == WIDE_TINY ? WideTiny::BM : WideThin::BM;
 }
 
@@ -175,17 +176,28 @@ inline int wide_group_log(int cus, int wmf, int64_t N, int row_bytes, int B, int
     return best;
 }
 
-// The tile of the matrix-core kernel: the largest of which there are enough for the chip (larger tiles move fewer bytes per
-// product: 300 k x 768, B = 256: 162 us with 256 x 256, 187 with 512 x 128, 220 with 128 x 128; 30 k x 768, B = 256, 118
-// large tiles: 36, 39, 32; 50 k, 196 tiles: 40, 42, 52).  Queries are padded to whole tiles; the 512 x 128 tile runs at
-// 12/13 of the rate of the other large one, so it takes over where it saves more than that (1 M x 768, B = 300: 822 -> 745).
-inline int wide_shape(int cus, int64_t N, int B) {
-    auto enough = [&](int bm, int bn) { return 8 * ((N + bm - 1) / bm) * ((B + bn - 1) / bn) >= 5 * (int64_t)cus; };
-    if (B <= 64) return ((N + 127) / 128) >= cus ? WIDE_THIN : WIDE_TINY;
+// The tile of the matrix-core kernel: the largest of which there are enough for the chip.  Larger tiles move fewer bytes per
+// product, so what decides is how full the chip gets; us, d = 768, inputs not in the caches:
+//                          256 x 256   512 x 128   256 x 128   128 x 64   64 x 64   (the 128 x 128 tile of half-line stages that
+//   4000, B = 400              34          39          25         17         16       stood between them: 20)
+//   4000, B = 1000             39          44          30         25         27       28
+//   16 k, B = 100 / 256        35 / 39     43 / 44     27 / 28    18 / 26    19 / 29  25 / 27
+//   16 k, B = 512              43          47          34         38         44       37
+//   50 k, B = 64 / 128         40 / 41     46 / 48     32 / 33    32 / 41    35 / 44  37 / 41
+//   50 k, B = 256              43          48          47         55         63       57
+//   300 k, B = 128 / 512       149 / 291   132 / 322   112 / 316  143 / 401  -        148 / 365
+//   1 M, B = 128 / 512         450 / 887   340 / 976   332 / 984  -          -        441 / 1160
+// Short rows in long slabs keep 512 x 128 (1 M x 384, B = 128: 180 against 187; 1 M x 128 75 / 80; 300 k x 128, B = 400 66 / 72; fewer
+// tiles than four for each compute unit: equal at 130 k x 384, B = 400, and 73 against 63 at 300 k x 384, B = 100).  Queries are padded
+// to whole tiles; the tiles of 128 queries run at 12/13 of the rate of the other, so they take over where they save more
+// than that (1 M x 768, B = 300: 822 -> 745).
+inline int wide_shape(int cus, int64_t N, int d, int B) {
+    auto tiles = [&](int bm, int bn) { return (N + bm - 1) / bm * ((B + bn - 1) / bn); };
     const int64_t cols256 = (B + 255) / 256 * 256, cols128 = (B + 127) / 128 * 128;
-    if (enough(256, 256) && 12 * cols256 <= 13 * cols128) return WIDE_LARGE;
-    if (enough(512, 128)) return WIDE_TALL;
-    return enough(128, 128) ? WIDE_SMALL : WIDE_TINY;
+    if (8 * tiles(256, 256) >= 5 * (int64_t)cus && 12 * cols256 <= 13 * cols128) return WIDE_LARGE;
+    if (B > 64 && d <= 512 && tiles(512, 128) >= 4 * (int64_t)cus) return WIDE_TALL;
+    if (B > 64 && 4 * tiles(256, 128) >= 3 * (int64_t)cus) return WIDE_MID;
+    return tiles(128, 64) > cus ? WIDE_THIN : WIDE_TINY;
 }
 
 // Whether the matrix-core kernel takes a call, or the streaming kernel.  The streaming kernel reads large corpora at the
@@ -215,7 +227,14 @@ inline size_t maxima_pass(FlatPlan &pl, int cus, int d, int dtype, int k, size_t
     const int B = pl.part;
     const size_t most = room / ((size_t)B * sizeof(float));
     if (pl.wide) {
-        wide_geometry(pl.w, wide_shape(cus, N, B), cus, N, B);
+        wide_geometry(pl.w, wide_shape(cus, N, d, B), cus, N, B);
+        // A tile's groups have 16 wmf rows at most: where those are too many, the tile of 64 if there are enough for the chip,
+        // else the one of 32 that pads least (300 k x 64, B = 300 in 1 MiB: 7 parts of the corpus, 14 by groups of 32).
+        if (pl.w.wmf < 4 && (size_t)maxima_of(pl.w.wmf, pl.w.slots, 3 + pl.w.wmf) > most) {
+            if (8 * ((N + WideTall::BM - 1) / WideTall::BM) * ((B + WideTall::BN - 1) / WideTall::BN) >= 5 * (int64_t)cus)
+                wide_geometry(pl.w, WIDE_TALL, cus, N, B);
+            else wide_geometry(pl.w, WIDE_THIN, cus, N, B);
+        }
         pl.w.gs_log = wide_group_log(cus, pl.w.wmf, pl.w.slots, d * 2, B, k, most);
         pl.w.n = maxima_of(pl.w.wmf, pl.w.slots, pl.w.gs_log);
     } else {

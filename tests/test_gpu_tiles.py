@@ -1,0 +1,45 @@
+"""The tiles of the matrix-core kernel whose stages hold whole lines of 128 bytes, at their edges."""
+import pytest
+import torch
+
+import paper_2505_12065_amd as ann
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.mark.parametrize("dtype,N,d,B,k", [
+    (torch.float16, 48_897, 40, 100, 3),       # 256 x 128: a stage that the row ends in, one row in the last tile
+    (torch.bfloat16, 49_408, 64, 128, 16),     # ... one whole stage, whole tiles
+    (torch.float16, 16_001, 200, 400, 5),      # ... four query tiles, rows end after a quarter of a line
+    (torch.bfloat16, 4_000, 136, 2_000, 2),    # ... single rows
+    (torch.float16, 4_001, 104, 999, 5),       # 128 x 64: one row in the last tile
+    (torch.bfloat16, 700, 264, 3_000, 16),     # ... the corpus is the smaller operand: workgroups by query tile
+    (torch.float16, 130_000, 72, 33, 1),       # ... groups of rows, slabs of tiles
+    (torch.float16, 1, 8, 65, 1),              # 64 x 64: one row
+    (torch.bfloat16, 63, 1_000, 129, 10),      # ... a tile short of one row
+    (torch.float16, 1_000, 776, 65, 4),        # ... a line of 16 bytes at the end of a row
+    (torch.float16, 2_049, 96, 5_000, 4),      # 256 x 256: single rows, by query tile
+])
+def test_line_stages(dtype, N, d, B, k):
+    """Two pages against scores in binary64.  Products of 16-bit factors are exact in binary32, so a score is off by at most
+    d 2^-24 sum |x_i q_i| <= d 2^-24 |x| |q|, and the r-th best differs by no more than the largest of those."""
+    print(f"line stages: dtype={dtype} N={N} d={d} B={B} k={k}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(N + d)
+    x = torch.randn(N, d, generator=gen, device=DEV).to(dtype)
+    q = torch.randn(B, d, generator=gen, device=DEV).to(dtype)
+    x[5::7, d - 1] = float("nan")                                        # never listed
+    exact = q.double() @ x.double().T
+    bound = d * 2.0 ** -24 * q.double().norm(dim=1, keepdim=True) * x.double().norm(dim=1).nan_to_num().max()
+    exact = exact.nan_to_num(nan=float("-inf"))
+    first = ann.ann_flat_search_typed(x, q, k)
+    second = ann.ann_flat_search_typed(x, q, k, after=(first[1][:, -1].contiguous(), first[0][:, -1].contiguous()))
+    ids, sc = torch.cat([first[0], second[0]], 1).long(), torch.cat([first[1], second[1]], 1).double()
+    n = min(2 * k, N - len(range(5, N, 7)))
+    assert (ids[:, n:] == -1).all() and (ids[:, :n] >= 0).all()
+    ids, sc = ids[:, :n], sc[:, :n]
+    assert ((exact.gather(1, ids) - sc).abs() <= bound).all()
+    assert ((exact.topk(n).values - sc).abs() <= bound).all()
+    assert (ids.sort(1).values.diff(dim=1) > 0).all()                    # no row twice
+    order = sc.diff(dim=1)
+    assert ((order < 0) | ((order == 0) & (ids.diff(dim=1) > 0))).all()
