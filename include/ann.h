@@ -271,9 +271,11 @@ int64_t ann_flat_workspace_bytes(int64_t N, int32_t d, int32_t dtype, int32_t B,
 /* Use a caller-owned device buffer as the workspace of the current device (so that, e.g., the
  * caller's allocator owns the memory and no entry point ever allocates): every call that needs
  * workspace (ann_flat_workspace_bytes, ann_graph_nonstall_workspace_bytes) then runs in it.  A flat
- * search that does not fit `bytes` at once takes the corpus in parts, or fewer slabs; one that would
- * need parts of fewer than 8192 rows, or less than a quarter of its slabs, and a graph search that
- * needs more than `bytes`, fail with ANN_ERR_NOMEM instead of growing anything.
+ * search that does not fit `bytes` at once takes the corpus in parts, or fewer slabs, or (up to 64
+ * queries of 16 bits) the kernel that needs less; one that would need parts of fewer than 8192 rows, or
+ * less than a quarter of its slabs, and a graph search that needs more than `bytes`, fail with
+ * ANN_ERR_NOMEM instead of growing anything.  A flat search captured into a graph while the library's
+ * own buffer would have to grow does likewise with the buffer as it is.
  *   workspace  device pointer, 256-byte aligned, valid until it is replaced; NULL: back to the
  *              library-owned buffers.  Not freed by the library.  Calls that use it must not overlap. */
 int ann_set_workspace(void *workspace, int64_t bytes);

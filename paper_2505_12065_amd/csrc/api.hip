@@ -418,10 +418,14 @@ int ann_flat_search_after_typed(const void *corpus, int64_t N, int32_t d, int32_
     if (int rc = device_state(&st)) return rc;
     // (in a caller's buffer: in parts if it does not hold the whole)
     const size_t limit = st->user_ws && st->user_bytes < WIDE_WS_MAX ? st->user_bytes : WIDE_WS_MAX;
-    const FlatPlan pl = flat_plan(st->cus, N, d, dtype, B, k, limit);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    FlatPlan pl = flat_plan(st->cus, N, d, dtype, B, k, limit);
+    if (!st->user_ws && !at_hand(st, st->ws_bytes, pl.ws_bytes, s)) {         // (captured: in what there is, if that can be)
+        const FlatPlan less = flat_plan(st->cus, N, d, dtype, B, k, st->ws_bytes);
+        if (less.ws_bytes <= st->ws_bytes) pl = less;
+    }
     void *ws = nullptr;
     if (int rc = workspace_for(st, &st->ws, &st->ws_bytes, pl.ws_bytes, &ws)) return rc;
-    hipStream_t s = static_cast<hipStream_t>(stream);
     return flat_search_run(pl, corpus, N, d, dtype, queries, B, k, ids, scores, ws, after, s);
 }
 

@@ -124,11 +124,12 @@ constexpr int64_t PART_MIN_ROWS = 8192;          // fewer are not worth a launch
 
 // The streaming kernel's geometry.
 // K: see the kernel; unit: rows that go to a wave together.
+constexpr int STREAM_LDS_STEPS = (int)((LDS_MAX - 16 * 1024) / (WAVE * 16));   // steps of 64 bytes of a group of 16 queries that LDS holds
 inline StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int K, int unit) {
     StreamPlan pl;
     pl.K = K;
     const int steps = (d * elem_bytes(dtype) + 63) / 64;
-    const int fit = (int)((LDS_MAX - 16 * 1024) / (WAVE * 16));        // steps of one group of 16 queries that fit LDS
+    const int fit = STREAM_LDS_STEPS;
     const int n16 = (B + 15) / 16;
     int nqg = fit / steps;
     nqg = nqg < 1 ? 1 : nqg > STREAM_NQG_MAX(elem_bytes(dtype)) ? STREAM_NQG_MAX(elem_bytes(dtype)) : nqg;
@@ -200,18 +201,32 @@ inline int wide_shape(int cus, int64_t N, int d, int B) {
     return tiles(128, 64) > cus ? WIDE_THIN : WIDE_TINY;
 }
 
-// Whether the matrix-core kernel takes a call, or the streaming kernel.  The streaming kernel reads large corpora at the
-// rate of HBM for up to 64 queries (1 M x 768, B = 64: 290 us against 380), but its lists cost every group of 16 queries
-// some 400 clocks a tile of 16 rows, whatever d is, which shows where rows are short or the corpus is in the caches
-// (streaming / matrix-core, us: 1 M x 64, B = 16 44 / 41, B = 64 106 / 46; 250 k x 256, B = 32 34 / 34, B = 64 45 / 35; 64 k x
-// 768, B = 32 30 / 32, B = 64 37 / 32).  Very small corpora are all latency: one-row maxima and one pass over them are as
-// fast as short lists and faster than long ones (4000 x 256, k = 16: 13 / 11).
+// Whether the matrix-core kernel takes a call, or the streaming kernel, which reads large corpora at the rate of HBM for up to
+// 64 queries but sorts lists: some 400 clocks a tile of 16 rows and group of 16 queries, whatever d is.  That shows where
+// rows are short or the corpus is in the caches; and a wave takes all columns of its rows, a serial chain where there are
+// few rows and many columns.  Streaming / matrix-core, us of a call (k = 3 where nothing else is said; 10 to 11 us are the host's):
+//   up to 16 Ki rows (no more 64 x 64 tiles than compute units): long rows 1000 x 768, B = 2 14.8 / 12.3; 4000 x 768 15.2 / 12.3; x 384
+//   12.4 / 11.2; 16 k x 768, B = 16 16.7 / 15.0, x 384 14.0 / 12.7; long lists 8000 x 128, k = 16 12.6 / 11.3.  Short rows and lists are
+//   level, single-row maxima cost a little more than lists of 4: 6000 x 64, B = 64 11.0 / 12.4; 14 k x 256, B = 16 11.6 / 12.2; but 16 k x 128,
+//   B = 40 12.9 / 12.4.
+//   queries that do not fit the LDS together, so that the corpus is read twice: 128 k x 1280, B = 48 / 56 77 / 83, 102 / 84; 300 k x 2048,
+//   B = 32 / 40 241 / 274, 323 / 275.
+//   rows of up to 128 bytes: 64 k x 64, B = 1 13.7 / 11.7; 1 M x 64, B = 1 45 / 38, B = 64 107 / 45; 4 M x 32, B = 8 133 / 96.  (1 M x 96, B = 8
+//   48 / 57, 300 k 23 / 25, 128 k 16.3 / 16.0.)
+//   up to 32 Ki rows: 20 k x 768, B = 16 / 24 16.2 / 18.9, 22.0 / 19.3; x 384, B = 24 16.4 / 16.5; 32 k x 768, B = 48 26 / 24.
+//   beyond, by groups of 16 queries against d: 64 k x 128, B = 16 / 24 13.3 / 13.2, 16.8 / 13.2; 64 k x 768, B = 32 / 48 31 / 33, 36 / 33;
+//   128 k x 256, B = 16 / 24 20.6 / 23.5, 24.8 / 23.7; 300 k x 128, B = 16 / 24 23 / 27, 28 / 27; 300 k x 256, B = 32 / 48 41 / 43, 47 / 44;
+//   1 M x 128, B = 32 / 48 62 / 63, 85 / 68; 1 M x 256, B = 64 125 / 121; 1 M x 768, B = 64 290 / 320.
+inline bool many_queries(int64_t N, int d, int B) { return B * (N <= 128 * 1024 ? 16 : N <= 512 * 1024 ? 8 : 4) >= d; }
 inline bool use_wide(int64_t N, int d, int dtype, int B, int k) {
     if (dtype == ANN_F32) return false;
     if (B >= WIDE_MIN_B) return true;
-    if (N <= 6000) return k > 4;
-    if (N <= 32 * 1024) return B > 32;
-    return B * (N <= 128 * 1024 ? 16 : N <= 512 * 1024 ? 8 : d <= 128 ? 4 : 0) >= d;
+    if (N <= 16 * 1024) return k > 4 || d >= 384 || (N > 6000 && B > 32);
+    const int groups = (B + 15) / 16, steps = (d * 2 + 63) / 64;
+    if (d <= 64 || (groups > 1 && groups * steps > STREAM_LDS_STEPS)) return true;
+    if (N <= 32 * 1024) return B > 32 || (B > 16 && d >= 768);
+    if (B <= 16) return N <= 128 * 1024 && d <= 96;
+    return many_queries(N, d, B);
 }
 
 // fp32 keeps lists for up to 16 queries (HBM-bound on large corpora) and wherever picking costs more than the lists: the rows
@@ -301,6 +316,19 @@ inline bool maxima_plan(FlatPlan &pl, int cus, int64_t N, int d, int dtype, int 
     return false;
 }
 
+// A call on lists.
+inline void lists_plan(FlatPlan &pl, int cus, int64_t N, int d, int dtype, int B, int k, size_t limit) {
+    pl.st = stream_plan(cus, N, d, dtype, B, (k + 3) & ~3, 16);
+    if (pl.direct) {
+        pl.st.P = 1;
+        return;
+    }
+    // lists that do not fit: fewer slabs, down to a quarter of those that fill the chip
+    const size_t slab = (size_t)B * pl.st.K * CAND_BYTES, fit = limit / slab;
+    if (fit < (size_t)pl.st.P && fit >= 1 && 4 * fit >= (size_t)pl.st.P) pl.st.P = (int)fit;
+    pl.ws_bytes = slab * pl.st.P;
+}
+
 inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, size_t limit) {
     FlatPlan pl{};
     pl.part = B;
@@ -312,21 +340,19 @@ inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, si
     pl.maxima = dtype == ANN_F32 && use_f32_maxima(N, d, B, k);
     pl.direct = !pl.maxima && N <= (k <= 4 || dtype == ANN_F32 ? 128 : 64);
     pl.wide = !pl.direct && use_wide(N, d, dtype, B, k);
-    if (pl.wide || pl.maxima) {
-        // (does not fit: ws_bytes says so)
-        maxima_plan(pl, cus, N, d, dtype, B, k, limit);
-        return pl;
-    }
-    pl.st = stream_plan(cus, N, d, dtype, B, (k + 3) & ~3, 16);
-    if (pl.direct) {
-        pl.st.P = 1;
-        return pl;
-    }
-    // lists that do not fit: fewer slabs, down to a quarter of those that fill the chip
-    const size_t slab = (size_t)B * pl.st.K * CAND_BYTES, fit = limit / slab;
-    if (fit < (size_t)pl.st.P && fit >= 1 && 4 * fit >= (size_t)pl.st.P) pl.st.P = (int)fit;
-    pl.ws_bytes = slab * pl.st.P;
-    return pl;
+    auto plan = [&] {
+        if (pl.wide || pl.maxima) maxima_plan(pl, cus, N, d, dtype, B, k, limit);
+        else lists_plan(pl, cus, N, d, dtype, B, k, limit);
+    };
+    plan();
+    if (pl.ws_bytes <= limit || dtype == ANN_F32 || B >= WIDE_MIN_B) return pl;
+    // The other kernel, if its workspace fits (lists of less than a quarter of their slabs: only for many queries).  Where
+    // neither does ws_bytes says so.
+    if (!pl.wide && (pl.direct || N <= 32 * 1024 || !many_queries(N, d, B))) return pl;
+    const FlatPlan first = pl;
+    pl.wide = !pl.wide;
+    plan();
+    return pl.ws_bytes <= limit ? pl : first;
 }
 
 // Long answers of large batches that the static workspace takes though one pass does not fit it.  They once needed a list of 16
@@ -337,11 +363,23 @@ inline bool static_takes_long(int64_t N, int d, int dtype, int B) {
     const int64_t rows = dtype == ANN_F32 ? 32 : 128, most = dtype == ANN_F32 ? 1024 : 128, slabs = (N + rows - 1) / rows;
     return (slabs < most ? slabs : most) * B * 16 * (int64_t)CAND_BYTES <= ANN_STATIC_WORKSPACE_BYTES;
 }
+// ... and the line of one pass: that of the tile that pads least, and where tiles of 512 x 128 would do, of their larger groups.
+inline bool static_one_pass(const WidePlan &w, int64_t N, int d, int B, int k) {
+    int64_t n = maxima_of(1, (N + 63) / 64 * 64, w.gs_log);
+    const int64_t tall = (N + 511) / 512;
+    if (w.shape == WIDE_MID && 8 * tall * ((B + 127) / 128) >= 5 * (int64_t)w.cus) {
+        const int64_t g = maxima_of(4, tall * 512, wide_group_log(w.cus, 4, tall * 512, d * 2, B, k, WIDE_WS_MAX / ((size_t)B * sizeof(float))));
+        n = g < n ? g : n;
+    }
+    return (size_t)B * (size_t)n * sizeof(float) <= (size_t)ANN_STATIC_WORKSPACE_BYTES;
+}
 // The plan of a call on the static workspace of `bytes` bytes, ANN_STATIC_WORKSPACE_BYTES and room for the best so far behind
 // them; ws_bytes > bytes: refused.
 inline FlatPlan static_plan(int cus, int64_t N, int d, int dtype, int B, int k, size_t bytes) {
     if (k > 4 && B >= 256 && !static_takes_long(N, d, dtype, B)) {
         FlatPlan pl = flat_plan(cus, N, d, dtype, B, k, WIDE_WS_MAX);
+        if (pl.wide && pl.ws_bytes > (size_t)ANN_STATIC_WORKSPACE_BYTES && static_one_pass(pl.w, N, d, B, k))
+            pl = flat_plan(cus, N, d, dtype, B, k, ANN_STATIC_WORKSPACE_BYTES);
         if (pl.ws_bytes > (size_t)ANN_STATIC_WORKSPACE_BYTES && pl.ws_bytes <= bytes) pl.ws_bytes = bytes + 1;
         return pl;
     }

@@ -20,6 +20,12 @@ DEV = "cuda"
     (torch.bfloat16, 63, 1_000, 129, 10),      # ... a tile short of one row
     (torch.float16, 1_000, 776, 65, 4),        # ... a line of 16 bytes at the end of a row
     (torch.float16, 2_049, 96, 5_000, 4),      # 256 x 256: single rows, by query tile
+    (torch.bfloat16, 4_000, 768, 1, 3),        # up to 64 queries by these tiles: few long rows
+    (torch.float16, 16_384, 384, 32, 1),       # ... one tile for each compute unit
+    (torch.float16, 20_001, 768, 17, 16),      # ... up to 32 Ki rows
+    (torch.bfloat16, 33_000, 1_544, 33, 4),    # ... rows of three groups of queries that do not fit LDS
+    (torch.float16, 70_001, 64, 1, 10),        # ... short rows
+    (torch.bfloat16, 131_072, 96, 16, 16),     # ...
 ])
 def test_line_stages(dtype, N, d, B, k):
     """Two pages against scores in binary64.  Products of 16-bit factors are exact in binary32, so a score is off by at most
@@ -43,3 +49,39 @@ def test_line_stages(dtype, N, d, B, k):
     assert (ids.sort(1).values.diff(dim=1) > 0).all()                    # no row twice
     order = sc.diff(dim=1)
     assert ((order < 0) | ((order == 0) & (ids.diff(dim=1) > 0))).all()
+
+
+@pytest.mark.parametrize("N,d,B,k,size", [
+    (15_656, 512, 1, 1, 1_163),                # maxima do not fit, lists do
+    (85_001, 144, 10, 10, 9_789),              # lists do not fit, the corpus in parts does
+])
+def test_other_kernel_where_the_workspace_is_short(N, d, B, k, size):
+    """In a caller's buffer and, captured, in a library buffer that cannot grow: the answer of the call that has the room."""
+    gen = torch.Generator(device=DEV).manual_seed(N)
+    x, q = (torch.randn(n, d, generator=gen, device=DEV).half() for n in (N, B))
+    assert ann.ann_flat_workspace_bytes(N, d, torch.float16, B, k) > size
+    want = ann.ann_flat_search_typed(x, q, k)
+    ids, sc = torch.empty_like(want[0]), torch.empty_like(want[1])
+    torch.cuda.synchronize()
+    try:
+        ann.ann_set_workspace(torch.empty(size, dtype=torch.uint8, device=DEV))
+        got = ann.ann_flat_search_typed(x, q, k)
+        torch.cuda.synchronize()
+    finally:
+        ann.ann_set_workspace(None)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    ann.ann_release_workspace()
+    few = ann.ann_flat_search_typed(x[:1_000], q, k)                         # (the buffer has room for this and stays)
+    assert 2 * ann.ann_flat_workspace_bytes(1_000, d, torch.float16, B, k) < ann.ann_flat_workspace_bytes(N, d, torch.float16, B, k)
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        ann.ann_flat_search_typed(x, q, k, ids=ids, scores=sc)
+    for _ in range(3):
+        ids.fill_(-7)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(ids, want[0]) and torch.equal(sc, want[1])
+        again = ann.ann_flat_search_typed(x[:1_000], q, k)
+        torch.cuda.synchronize()
+        assert torch.equal(again[0], few[0]) and torch.equal(again[1], few[1])
