@@ -28,8 +28,12 @@ __device__ __forceinline__ int64_t wide_row(int64_t slot) {
 //      tie) are ranked.
 // Groups of one row: their maxima are the scores, step 3 falls away.  Hundreds of maxima that tie with the k-th: the groups
 // are gone through in order, a few at a time, past those that can no longer improve the k best so far.
-// Bound by the latency of three dependent reads (maxima twice, rows) at 8 to 12 us, and beyond about 1000 queries by the
-// bytes of the rows.
+// Bound by latency: three dependent reads (maxima twice, rows), and between them the reads of the LDS.  Beyond about 1000
+// queries by the bytes of the rows.  The serial parts are therefore written as few long batches: a row's loads 24 steps at a
+// time and the query's operands read 6 steps ahead of the products (one at a time they were three quarters of step 3), ranks
+// eight reads at a time, and gathering by a thread's mask of hits instead of a test and an atomic for each maximum.  us, before / now:
+// 77 queries x 7716 maxima, 160 rows of 1552 bytes 17.0 / 12.7; 128 x 18 k, 320 rows of 768 20.8 / 13.3; 64 x 31 k, 320 rows of 3072
+// 52 / 33; 512 x 15 k, 192 rows of 1536 41.8 / 34.2; single rows 5000 x 1024, k = 16 9.8 / 8.2, 512 x 1024, k = 1 4.7 / 4.0.
 // PARTS: a search that takes the corpus in parts (sh.X and sh.N are the part, after.base its first row) goes on from the k
 // best of the parts before, which also bound what is worth looking at: best_so_far [B, k], read where `more` has bit 0;
 // the result goes back there where it has bit 1, else to ids and scores.  (A variant of its own: the calls of a few
@@ -63,11 +67,11 @@ __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict_
     uint32_t m = 0;
     const int64_t n4 = n >> 2;                        // (n is a multiple of 4)
     f4 v[4];                                          // 16 maxima: all of this thread's, if n <= 16 NT
-    auto load_maxima = [&](int64_t i0) {
+    auto load_maxima = [&](int64_t i0) {              // (i0 may lie behind the end, for lanes)
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int64_t i = i0 + u * NT;
-            v[u] = *reinterpret_cast<const f4 *>(mx + 4 * (i < n4 ? i : i0));
+            v[u] = *reinterpret_cast<const f4 *>(mx + 4 * (i < n4 ? i : min(i0, n4 - 1)));
         }
     };
     for (int64_t i0 = tid; i0 < n4; i0 += 4 * NT) {
@@ -93,30 +97,63 @@ __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict_
     auto entry_key = [&](uint32_t x, int64_t e) {
         return ((uint64_t)x << 32) | (uint32_t)~(uint32_t)(ONE ? base + wide_row<WMF>(e) : e);
     };
-    for (int64_t i0 = tid; i0 < n4; i0 += 4 * NT) {
-        if (n4 > 4 * NT) load_maxima(i0);
+    // as a number (images below that of -inf: every number reaches it)
+    float least;
+    int none;
+    order_key_decode((uint64_t)max(bound, (uint32_t)(order_key(-INFINITY, 0) >> 32)) << 32, least, none);
+    for (int64_t b = 0; b < n4; b += 4 * NT) {
+        if (n4 > 4 * NT) load_maxima(b + tid);
+        uint32_t hits = 0;                            // those of this thread's 16 that reach the bound
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t x = image(v[u][c]);
-                if (x >= bound && i0 + u * NT < n4) {
-                    const int at = atomicAdd(&n_c, 1);
-                    if (at < PICK_CAP) ck[at] = entry_key(x, 4 * (i0 + u * NT) + c);
-                }
+            for (int c = 0; c < 4; ++c) hits |= v[u][c] >= least ? 1u << (4 * u + c) : 0u;
+        const int64_t have = n4 - b - tid;            // (places behind the end repeat the first)
+        hits &= have > 3 * NT ? 0xffffu : have > 2 * NT ? 0xfffu : have > NT ? 0xffu : have > 0 ? 0xfu : 0u;
+        while (const uint64_t lanes = __ballot(hits != 0)) {
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&n_c, __popcll(lanes));
+            at = __builtin_amdgcn_readfirstlane(at) +
+                 __builtin_amdgcn_mbcnt_hi((uint32_t)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lanes, 0));
+            if (hits != 0 && at < PICK_CAP) {
+                const int e = __ffs(hits) - 1;
+                const int64_t g = 4 * (b + tid + (e >> 2) * NT) + (e & 3);
+                ck[at] = entry_key(image(mx[g]), g);
             }
+            hits &= hits - 1;
+        }
     }
     __syncthreads();
     const int found = n_c;
 
-    // fin <- the k best of fin and ck[0 .. c)
-    auto merge = [&](int c) {
+    // how many of ck[0 .. c) are larger, eight reads at a time
+    auto larger_than = [&](uint64_t mine, int c) {
+        int r = 0;
+        for (int j = 0; j < c; j += 8) {
+            uint64_t o[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) o[u] = ck[j + u];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) r += (int)(j + u < c && o[u] > mine);
+        }
+        return r;
+    };
+    // fin <- the k best of fin and ck[0 .. c); empty: fin holds nothing yet
+    auto merge = [&](int c, bool empty = false) {
+        if (empty) {
+            for (int i = tid; i < c; i += NT) {
+                const uint64_t mine = ck[i];
+                const int r = larger_than(mine, c);
+                if (r < k) fin[r] = mine;
+            }
+            __syncthreads();
+            return;
+        }
         if (tid < 16) old[tid] = fin[tid];
         __syncthreads();
         for (int i = tid; i < c + k; i += NT) {
             const uint64_t mine = i < c ? ck[i] : old[i - c];
-            int r = i < c ? 0 : i - c;
-            for (int j = 0; j < c; ++j) r += (int)(ck[j] > mine);
+            int r = larger_than(mine, c) + (i < c ? 0 : i - c);
             if (i < c)
                 for (int j = 0; j < k; ++j) r += (int)(old[j] > mine);
             if (r < k) fin[r] = mine;
@@ -124,7 +161,7 @@ __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict_
         __syncthreads();
     };
     // the rows of groups sel[0 .. ns) scored and merged, PICK_CAP at a time; t: image that a row has to reach
-    auto score_groups = [&](int ns, uint32_t t) {
+    auto score_groups = [&](int ns, uint32_t t, bool first) {
         const int64_t rows = (int64_t)ns << gs_log;
         auto row_of = [&](int64_t e) {
             e = e < rows ? e : rows - 1;
@@ -140,7 +177,9 @@ __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict_
                 int64_t row = row_of(e0 + (lane & (UNIT - 1)));
                 row = row < sh.N ? row : sh.N - 1;
                 const char *rp = static_cast<const char *>(sh.X) + (size_t)row * rb;
-                constexpr int RUN = 12;               // steps whose loads are in flight together
+                // RUN steps whose loads are in flight together, PART steps whose operands of the query are read together: a read
+                // of the LDS before each product, waited for, took three quarters of the time
+                constexpr int RUN = 24, PART = 6, TAIL = 12;
                 const int sub = lane / UNIT;          // this lane's chunk of a step
                 constexpr int CHUNKS = WAVE / UNIT;
                 const int steps = (nch + CHUNKS - 1) / CHUNKS;
@@ -148,18 +187,40 @@ __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict_
                 float v;
                 int col, at;                          // this lane's column, and which of the rows it looks after
                 auto run = [&](auto &&product) {
-                    for (int s0 = 0; s0 < steps; s0 += RUN) {
+                    int s0 = 0;
+                    for (; CHUNKS * (s0 + RUN) <= nch; s0 += RUN) {
+                        const char *p = rp + (CHUNKS * s0 + sub) * 16;
+                        const u4 *yp = qs + CHUNKS * s0 + sub;
                         u4 x[RUN];
 #pragma unroll
-                        for (int s = 0; s < RUN; ++s) {
-                            x[s] = zero_chunk();
-                            if (s0 + s < steps) x[s] = load_chunk(rp + min(CHUNKS * (s0 + s) + sub, nch - 1) * 16);
-                        }
+                        for (int s = 0; s < RUN; ++s) x[s] = load_chunk(p + CHUNKS * s * 16);
 #pragma unroll
-                        for (int s = 0; s < RUN; ++s)
+                        for (int g = 0; g < RUN; g += PART) {
+                            u4 y[PART];
+#pragma unroll
+                            for (int s = 0; s < PART; ++s) y[s] = yp[CHUNKS * (g + s)];
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                            for (int s = 0; s < PART; ++s) product(s & 3, x[g + s], y[s]);
+                        }
+                    }
+                    for (; s0 < steps; s0 += TAIL) {
+                        u4 x[TAIL], y[TAIL];
+#pragma unroll
+                        for (int s = 0; s < TAIL; ++s) {
+                            x[s] = y[s] = zero_chunk();
                             if (s0 + s < steps) {
-                                const int ch = CHUNKS * (s0 + s) + sub;
-                                product(s, mask_tail(x[s], ch < nch), mask_tail(qs[min(ch, nch - 1)], ch < nch));
+                                const int ch = min(CHUNKS * (s0 + s) + sub, nch - 1);
+                                x[s] = load_chunk(rp + ch * 16);
+                                y[s] = qs[ch];
+                            }
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int s = 0; s < TAIL; ++s)
+                            if (s0 + s < steps) {
+                                const bool inside = CHUNKS * (s0 + s) + sub < nch;
+                                product(s & 3, mask_tail(x[s], inside), mask_tail(y[s], inside));
                             }
                     }
                 };
@@ -190,25 +251,23 @@ __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict_
                 }
             }
             __syncthreads();
-            merge(n_c);
+            merge(n_c, first && b0 == 0);
         }
     };
 
     if (found <= PICK_CAP) {
         if (ONE) {
-            merge(found);
+            merge(found, !(PARTS && (more & 1)));
         } else {
             for (int i = tid; i < found; i += NT) {
                 const uint32_t mine = (uint32_t)(ck[i] >> 32);
-                int larger = 0;
-                for (int j = 0; j < found; ++j) larger += (int)((uint32_t)(ck[j] >> 32) > mine);
-                if (larger < k) {
+                if (larger_than(ck[i] | 0xffffffffu, found) < k) {
                     sel[atomicAdd(&n_sel, 1)] = (int)~(uint32_t)ck[i];
                     atomicMin(&t_min, mine);
                 }
             }
             __syncthreads();
-            score_groups(n_sel, found < k ? 0u : t_min);
+            score_groups(n_sel, found < k ? 0u : t_min, !(PARTS && (more & 1)));
         }
     } else {
         const int step = ONE ? PICK_CAP : 64;
@@ -227,7 +286,7 @@ __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict_
             }
             __syncthreads();
             if (ONE) { if (n_c > 0) merge(n_c); }
-            else if (n_sel > 0) score_groups(n_sel, bound);
+            else if (n_sel > 0) score_groups(n_sel, bound, false);
         }
     }
 

@@ -158,9 +158,12 @@ inline StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int K
 // Maxima of a query, one of 2^g rows: N is a whole number of tiles (wmf > 0), or any number, and there are a multiple of 4.
 inline int64_t maxima_of(int wmf, int64_t N, int g) { return wmf > 0 ? N >> g : (((N - 1) >> g) + 1 + 3) & ~(int64_t)3; }
 
-// Rows per group of the matrix-core kernel, by the time of what follows the products, in us: the maxima are written and
-// read once and the rows of k groups are read again, at some 4 TB/s over all queries; one query alone waits for its
-// maxima (twice, 1024 a wave at a time) and, unless groups are single rows, for its rows (32 a wave, 192 columns at once).
+// Rows per group of the matrix-core kernel, by the time of what follows the products, in us: 4 bytes of maxima are written
+// in small pieces and read again, at 1.3 TB/s over all queries, the rows of k groups are read at 5 TB/s; one query alone waits
+// for its maxima (twice, 1024 a wave at a time) and, unless groups are single rows, for its rows (32 a wave, 24 steps of 32 bytes
+// at once).  The constants are fitted to 112 calls of 4000 to 1 M rows, 16 to 1000 queries, k = 1 to 16: on average 0.4 % behind the
+// best size of each, 12 % at most.  fp32 (wmf = 0) writes whole lines and keeps its own constants: 300 k x 128, B = 64 groups of 16 / 32 /
+// 64 rows 78 / 76 / 75, k = 10 83 / 83 / 88, B = 300, k = 16 333 / 325 / 346.
 // most: maxima of a query that there is room for; the largest groups where no size fits.
 inline int wide_group_log(int cus, int wmf, int64_t N, int row_bytes, int B, int k, size_t most) {
     const int waves = B <= cus ? 8 : 4;                   // of a query
@@ -170,8 +173,10 @@ inline int wide_group_log(int cus, int wmf, int64_t N, int row_bytes, int B, int
         if (wmf == 0 ? g < 4 : (1 << g) > 16 * wmf) continue;
         if ((size_t)maxima_of(wmf, N, g) > most) { best = g; continue; }
         const double n = (double)N / (1 << g), rows = (double)k * (1 << g);
-        double us = 8.0 * n * B / 4e6 + 1.6 * n / (1024 * waves);
-        if (g > 0) us += rows * row_bytes * B / 4e6 + 3.0 + 1.2 * ceil(rows / (32 * waves)) * ceil(row_bytes / 384.0);
+        double us;
+        if (wmf == 0) us = 2.0 * n * B / 1e6 + 1.6 * n / (1024 * waves) + rows * row_bytes * B / 4e6 + 1.2 * ceil(rows / (32 * waves)) * ceil(row_bytes / 384.0);
+        else us = 3.0 * n * B / 1e6 + 1.2 * n / (1024 * waves);
+        if (wmf > 0 && g > 0) us += rows * row_bytes * B / 5e6 + 3.5 + 0.4 * ceil(rows / (32 * waves)) * ceil(row_bytes / 768.0);
         if (us < least) { least = us; best = g; }
     }
     return best;

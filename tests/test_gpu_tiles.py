@@ -26,9 +26,11 @@ DEV = "cuda"
     (torch.bfloat16, 33_000, 1_544, 33, 4),    # ... rows of three groups of queries that do not fit LDS
     (torch.float16, 70_001, 64, 1, 10),        # ... short rows
     (torch.bfloat16, 131_072, 96, 16, 16),     # ...
+    (torch.bfloat16, 60_000, 1_160, 300, 9),   # rows scored once more: three long runs of steps and a last one of half a step
+    (torch.float32, 40_000, 392, 400, 3),      # ... fp32, one long run and half a step
 ])
 def test_line_stages(dtype, N, d, B, k):
-    """Two pages against scores in binary64.  Products of 16-bit factors are exact in binary32, so a score is off by at most
+    """Two pages against scores in binary64.  Every product is rounded together with its sum, so a score is off by at most
     d 2^-24 sum |x_i q_i| <= d 2^-24 |x| |q|, and the r-th best differs by no more than the largest of those."""
     print(f"line stages: dtype={dtype} N={N} d={d} B={B} k={k}", flush=True)
     gen = torch.Generator(device=DEV).manual_seed(N + d)
