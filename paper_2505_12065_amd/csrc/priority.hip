@@ -4,6 +4,56 @@
 #include "launch.hpp"
 
 namespace ann {
+namespace {
+// x over all lanes of the wave by op
+template <class Op>
+__device__ __forceinline__ int wave_reduce(int x, Op op) {
+    x = op(x, (int)lane_swap<1>((uint32_t)x));
+    x = op(x, (int)lane_swap<2>((uint32_t)x));
+    x = op(x, (int)lane_swap<4>((uint32_t)x));
+    x = op(x, (int)lane_swap<8>((uint32_t)x));
+    uint32_t a, b;
+    row_pair<16>((uint32_t)x, a, b);
+    row_pair<32>((uint32_t)op((int)a, (int)b), a, b);
+    return op((int)a, (int)b);
+}
+template <class Op>
+__device__ __forceinline__ double wave_reduce(double x, Op op) {
+    auto swapped = [](double v, auto mc) {
+        constexpr int M = decltype(mc)::value;
+        const uint64_t b = (uint64_t)__double_as_longlong(v);
+        return __longlong_as_double((long long)((uint64_t)lane_swap<M>((uint32_t)(b >> 32)) << 32 | lane_swap<M>((uint32_t)b)));
+    };
+    x = op(x, swapped(x, std::integral_constant<int, 1>{}));
+    x = op(x, swapped(x, std::integral_constant<int, 2>{}));
+    x = op(x, swapped(x, std::integral_constant<int, 4>{}));
+    x = op(x, swapped(x, std::integral_constant<int, 8>{}));
+    auto rows = [&](auto mc) {
+        constexpr int M = decltype(mc)::value;
+        const uint64_t v = (uint64_t)__double_as_longlong(x);
+        uint32_t l0, l1, h0, h1;
+        row_pair<M>((uint32_t)v, l0, l1);
+        row_pair<M>((uint32_t)(v >> 32), h0, h1);
+        x = op(__longlong_as_double((long long)((uint64_t)h0 << 32 | l0)), __longlong_as_double((long long)((uint64_t)h1 << 32 | l1)));
+    };
+    rows(std::integral_constant<int, 16>{});
+    rows(std::integral_constant<int, 32>{});
+    return x;
+}
+
+// cnt += (level, wait) > (ml, mw), both read as one number of 96 bits: the borrow of a subtraction, four instructions
+// (a carry takes the one scalar operand that an instruction may have, so all but the lowest word of the tile's are vectors)
+__device__ __forceinline__ void count_larger(uint32_t &cnt, uint32_t level, uint64_t wait, uint32_t ml, uint64_t mw) {
+    uint32_t t;
+    asm("v_sub_co_u32_e32 %0, vcc, %2, %3\n\t"
+        "v_subb_co_u32_e32 %0, vcc, %4, %5, vcc\n\t"
+        "v_subb_co_u32_e32 %0, vcc, %6, %7, vcc\n\t"
+        "v_addc_co_u32_e32 %1, vcc, 0, %1, vcc"
+        : "=&v"(t), "+v"(cnt)
+        : "s"((uint32_t)mw), "v"((uint32_t)wait), "v"((uint32_t)(mw >> 32)), "v"((uint32_t)(wait >> 32)), "v"(ml), "v"(level)
+        : "vcc");
+}
+}  // namespace
 
 constexpr int PRIO_THREADS = 512;
 constexpr int PRIO_WAVES = PRIO_THREADS / WAVE;
@@ -19,13 +69,15 @@ constexpr int PRIO_WAVES = PRIO_THREADS / WAVE;
 //   inside a level longer current queueing time first, equal times in index order; a queueing time
 //   that is NaN counts as the shortest possible wait (-inf), so every request gets exactly one place.
 //
-// Workgroup b places the PRIO_TILE requests from b PRIO_TILE on: they sit in scalar registers, every thread holds one
-// request at a time of the n to compare with and tests it against all of them, so the n^2 comparisons are spread
-// over the whole chip instead of one thread walking all n; the comparisons are made on a 64-bit image of the
-// queueing time that orders like the number.  n = 3000, G = 6: 300 us a call before (two launches, 290 of it the
-// walk), 11.8 us now (8.4 for n = 32, the host's share of a call); n = 16384: 1590 -> 76 us, bound by the
-// comparisons.
+// Workgroup b places the PRIO_TILE requests from b PRIO_TILE on: every thread holds one request at a time of the n to compare
+// with and tests it against all of them, so the n^2 comparisons are spread over the whole chip instead of one thread walking
+// all n.  A level and a 64-bit image of the queueing time that orders like the number are compared as one number of 96 bits.
+// Bound by latency up to some 3000 requests: one read of the requests, which are kept (a second one cost 0.5 us), reductions
+// that stay out of the LDS crossbar, three barriers; beyond that by the comparisons and the levels that every workgroup
+// computes again.  us of a call, one thread walking all n (two launches) / read twice, 8 instructions a comparison / now, 4 of them:
+// n = 3000, G = 6 300 / 12.1 / 9.1 (the host's share is 8.5; the kernel 13.2 -> 9.5), n = 4661 - / 21.5 / 18.0, n = 16384 1590 / 76 / 71.
 constexpr int PRIO_TILE = 16;
+constexpr int HELD = 8;                                                   // requests that a thread keeps from the extremes to the comparisons
 
 // order-preserving image of a queueing time (a NaN counts as -inf, -0 as +0)
 __device__ __forceinline__ uint64_t wait_key(double w) {
@@ -38,7 +90,7 @@ __device__ __forceinline__ uint64_t wait_key(double w) {
 // metric never descend with j (j / G, the product with a difference that is not negative and the sum each round
 // monotonically; where an extreme is infinite they are all infinite or all NaN), so the largest j passed is found by halving
 // and the level is the largest over the three metrics.  Every workgroup looks at all n requests, so level by level costs
-// n^2 G / 16 tests.  Level by level / halving, us: n = 256, G = 32 12.4 / 13.4, G = 64 17.4 / 14.8, G = 1024 161 / 20.6; n = 3000,
+// n^2 G / 16 tests.  Level by level / halving, us (of the kernel that read the requests twice): n = 256, G = 32 12.4 / 13.4, G = 64 17.4 / 14.8, G = 1024 161 / 20.6; n = 3000,
 // G = 32 19.0 / 20.9, G = 64 27.5 / 23.2, G = 1024 285 / 34.4; n = 65 536, G = 32 1764 / 1659, G = 1024 33 100 / 3470.
 constexpr int PRIO_FEW = 32;
 template <bool MANY>
@@ -48,41 +100,60 @@ __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *_
                                                                 int32_t *__restrict__ level, int32_t *__restrict__ order) {
     extern __shared__ __align__(16) unsigned char smem[];
     double *thr = reinterpret_cast<double *>(smem);                      // [G][3] thresholds
-    __shared__ double part_w[2 * PRIO_WAVES];                            // a wave's smallest and largest W
-    __shared__ int part_i[4];                                            // smallest R, C; largest R, C
+    __shared__ double part_w[2][PRIO_WAVES];                             // a wave's smallest and largest W
+    __shared__ int part_i[4][PRIO_WAVES];                                // smallest R, C; largest R, C
     __shared__ uint64_t mine_w[PRIO_TILE];
     __shared__ int mine_l[PRIO_TILE], before[PRIO_TILE];
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
-    if (tid < 2) { part_i[tid] = INT_MAX; part_i[2 + tid] = INT_MIN; }
+    const int i0 = blockIdx.x * PRIO_TILE, in = min(PRIO_TILE, n - i0);
     if (tid < PRIO_TILE) before[tid] = 0;
-    __syncthreads();
+    // The tile's requests and the first eight of a thread are loaded once, together.
+    const int own = min(i0 + (tid & (PRIO_TILE - 1)), n - 1);
+    const int own_r = R[own], own_c = C[own];
+    const double own_w = W[own], own_q = Wcur[own];
+    int r[HELD], c[HELD];
+    double w[HELD], q[HELD];
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) {
+        const int i = min(tid + u * PRIO_THREADS, n - 1);
+        r[u] = R[i]; w[u] = W[i]; c[u] = C[i];
+    }
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) q[u] = Wcur[min(tid + u * PRIO_THREADS, n - 1)];
     {
-        int r0 = INT_MAX, r1 = INT_MIN, c0 = INT_MAX, c1 = INT_MIN;
+        int r0 = r[0], r1 = r[0], c0 = c[0], c1 = c[0];
         double w0 = INFINITY, w1 = -INFINITY;
-        for (int b = tid; b < n; b += 8 * PRIO_THREADS) {                // eight requests' loads in flight per thread
-            int r[8], c[8];
-            double w[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < HELD; ++u) {
+            r0 = min(r0, r[u]); r1 = max(r1, r[u]);
+            c0 = min(c0, c[u]); c1 = max(c1, c[u]);
+            w0 = fmin(w0, w[u]); w1 = fmax(w1, w[u]);
+        }
+        for (int b = tid + HELD * PRIO_THREADS; b < n; b += HELD * PRIO_THREADS) {
+            int br[HELD], bc[HELD];
+            double bw[HELD];
+#pragma unroll
+            for (int u = 0; u < HELD; ++u) {
                 const int i = min(b + u * PRIO_THREADS, n - 1);
-                r[u] = R[i]; w[u] = W[i]; c[u] = C[i];
+                br[u] = R[i]; bw[u] = W[i]; bc[u] = C[i];
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                r0 = min(r0, r[u]); r1 = max(r1, r[u]);
-                c0 = min(c0, c[u]); c1 = max(c1, c[u]);
-                w0 = fmin(w0, w[u]); w1 = fmax(w1, w[u]);
+            for (int u = 0; u < HELD; ++u) {
+                r0 = min(r0, br[u]); r1 = max(r1, br[u]);
+                c0 = min(c0, bc[u]); c1 = max(c1, bc[u]);
+                w0 = fmin(w0, bw[u]); w1 = fmax(w1, bw[u]);
             }
         }
-        for (int m = 1; m < WAVE; m <<= 1) { w0 = fmin(w0, __shfl_xor(w0, m)); w1 = fmax(w1, __shfl_xor(w1, m)); }
-        if (lane == 0) { part_w[wave] = w0; part_w[PRIO_WAVES + wave] = w1; }
-        for (int m = 1; m < WAVE; m <<= 1) {
-            r0 = min(r0, __shfl_xor(r0, m)); r1 = max(r1, __shfl_xor(r1, m));
-            c0 = min(c0, __shfl_xor(c0, m)); c1 = max(c1, __shfl_xor(c1, m));
-        }
+        auto least = [](auto a, auto b) { return a < b ? a : b; };
+        auto most = [](auto a, auto b) { return a > b ? a : b; };
+        r0 = wave_reduce(r0, least); r1 = wave_reduce(r1, most);
+        c0 = wave_reduce(c0, least); c1 = wave_reduce(c1, most);
+        w0 = wave_reduce(w0, [](double a, double b) { return fmin(a, b); });
+        w1 = wave_reduce(w1, [](double a, double b) { return fmax(a, b); });
         if (lane == 0) {
-            atomicMin(&part_i[0], r0); atomicMin(&part_i[1], c0);
-            atomicMax(&part_i[2], r1); atomicMax(&part_i[3], c1);
+            part_w[0][wave] = w0; part_w[1][wave] = w1;
+            part_i[0][wave] = r0; part_i[1][wave] = c0;
+            part_i[2][wave] = r1; part_i[3][wave] = c1;
         }
     }
     __syncthreads();
@@ -90,12 +161,16 @@ __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *_
         const int j = e / 3, m = e % 3;
         double mn, mx;
         if (m == 1) {
-            mn = part_w[0];
-            mx = part_w[PRIO_WAVES];
-            for (int w = 1; w < PRIO_WAVES; ++w) { mn = fmin(mn, part_w[w]); mx = fmax(mx, part_w[PRIO_WAVES + w]); }
+            mn = part_w[0][0];
+            mx = part_w[1][0];
+#pragma unroll
+            for (int v = 1; v < PRIO_WAVES; ++v) { mn = fmin(mn, part_w[0][v]); mx = fmax(mx, part_w[1][v]); }
         } else {
-            mn = (double)part_i[m >> 1];
-            mx = (double)part_i[2 + (m >> 1)];
+            int lo = part_i[m >> 1][0], hi = part_i[2 + (m >> 1)][0];
+#pragma unroll
+            for (int v = 1; v < PRIO_WAVES; ++v) { lo = min(lo, part_i[m >> 1][v]); hi = max(hi, part_i[2 + (m >> 1)][v]); }
+            mn = (double)lo;
+            mx = (double)hi;
         }
         {
 #pragma clang fp contract(off)                                          // (__dmul_rn and __dadd_rn do not keep the two from being fused)
@@ -134,69 +209,72 @@ __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *_
             for (int u = 0; u < NU; ++u) l[u] = (((double)r[u] > tr) | (w[u] > tw) | ((double)c[u] > tc)) ? j : l[u];
         }
     };
-    const int i0 = blockIdx.x * PRIO_TILE, in = min(PRIO_TILE, n - i0);
     if (tid < PRIO_TILE) {
-        const int i = min(i0 + tid, n - 1);
-        const int r = R[i], c = C[i];
-        const double w = W[i];
         int l;
-        levels_of(std::integral_constant<int, 1>{}, &r, &w, &c, &l);
+        levels_of(std::integral_constant<int, 1>{}, &own_r, &own_w, &own_c, &l);
         mine_l[tid] = l;
-        mine_w[tid] = wait_key(Wcur[i]);
-        if (tid < in) level[i] = l;
+        mine_w[tid] = wait_key(own_q);
+        if (tid < in) level[own] = l;
     }
     __syncthreads();
-    int ml[PRIO_TILE];                                                   // the tile, in scalar registers
+    uint32_t ml[PRIO_TILE];                                              // the tile; levels from 1 on
     uint64_t mw[PRIO_TILE];
 #pragma unroll
     for (int t = 0; t < PRIO_TILE; ++t) {
-        ml[t] = __builtin_amdgcn_readfirstlane(mine_l[t]);
-        mw[t] = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(mine_w[t] >> 32)) << 32 |
-                (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)mine_w[t]);
+        ml[t] = (uint32_t)mine_l[t] + 1;
+        mw[t] = (mine_w[t] >> 32) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)mine_w[t]);
     }
-    uint32_t cnt[PRIO_TILE / 2];                                         // two counts of 16 bits: at most n / 8 a wave
+    uint32_t count[PRIO_TILE];
 #pragma unroll
-    for (int t = 0; t < PRIO_TILE / 2; ++t) cnt[t] = 0;
+    for (int t = 0; t < PRIO_TILE; ++t) count[t] = 0;
     for (int b = tid; b < n; b += 4 * PRIO_THREADS) {
-        int r[4], c[4];
-        double w[4], q[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int j = min(b + u * PRIO_THREADS, n - 1);
-            r[u] = R[j]; w[u] = W[j]; c[u] = C[j]; q[u] = Wcur[j];
-        }
         int l[4];
         levels_of(std::integral_constant<int, 4>{}, r, w, c, l);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int j = b + u * PRIO_THREADS;
-            const int lj = j < n ? l[u] : -1;                            // (past the end: runs before nobody)
+            const uint32_t lj = j < n ? (uint32_t)l[u] + 1 : 0u;         // (past the end: runs before nobody)
             // a request of lower index runs first at equal times: its image is compared with >= by adding one
             const uint64_t wj = wait_key(q[u]) + (j < i0 ? 1u : 0u);
 #pragma unroll
-            for (int t = 0; t < PRIO_TILE; ++t)
-                cnt[t >> 1] += ((lj > ml[t]) | ((lj == ml[t]) & (wj > mw[t]))) ? 1u << (16 * (t & 1)) : 0u;
+            for (int t = 0; t < PRIO_TILE; ++t) count_larger(count[t], lj, wj, ml[t], mw[t]);
+        }
+        // the next four: those that are held, then from memory
+#pragma unroll
+        for (int u = 0; u + 4 < HELD; ++u) { r[u] = r[u + 4]; w[u] = w[u + 4]; c[u] = c[u + 4]; q[u] = q[u + 4]; }
+        if (b + HELD * PRIO_THREADS < n) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = min(b + HELD * PRIO_THREADS + u * PRIO_THREADS, n - 1);
+                constexpr int to = HELD - 4;
+                r[to + u] = R[i]; w[to + u] = W[i]; c[to + u] = C[i]; q[to + u] = Wcur[i];
+            }
         }
     }
-    // sums over the wave: every step halves the counts a lane keeps, then the lanes that keep the same ones add up
+    uint32_t cnt[PRIO_TILE / 2];                                         // two counts of 16 bits: at most n / 8 a wave
 #pragma unroll
-    for (int s = 0; s < 3; ++s) {
-        const int half = PRIO_TILE / 4 >> s;
-        const bool upper = (lane >> s) & 1;
+    for (int t = 0; t < PRIO_TILE / 2; ++t) cnt[t] = count[2 * t] | count[2 * t + 1] << 16;
+    // sums over the wave: every step halves the counts a lane keeps, then the lanes that keep the same ones add up
+    auto halve = [&](auto sc) {
+        constexpr int S = decltype(sc)::value, half = PRIO_TILE / 4 >> S;
+        const bool upper = (lane >> S) & 1;
 #pragma unroll
         for (int t = 0; t < half; ++t) {
             const uint32_t keep = upper ? cnt[t + half] : cnt[t], give = upper ? cnt[t] : cnt[t + half];
-            cnt[t] = keep + (uint32_t)__shfl_xor((int)give, 1 << s);
+            cnt[t] = keep + lane_swap<1 << S>(give);
         }
-    }
-    uint32_t c = cnt[0];
-    c += (uint32_t)__shfl_xor((int)c, 8);
-    c += (uint32_t)__shfl_xor((int)c, 16);
-    c += (uint32_t)__shfl_xor((int)c, 32);
+    };
+    halve(std::integral_constant<int, 0>{});
+    halve(std::integral_constant<int, 1>{});
+    halve(std::integral_constant<int, 2>{});
+    uint32_t sum = cnt[0] + lane_swap<8>(cnt[0]), sa, sb;
+    row_pair<16>(sum, sa, sb);
+    row_pair<32>(sa + sb, sa, sb);
+    sum = sa + sb;
     if (lane < 8) {                                                      // lane's bits 0, 1, 2 chose halves of 4, 2, 1 words
         const int t = 2 * ((lane & 1) * 4 + (lane & 2) + (lane >> 2));
-        atomicAdd(&before[t], (int)(c & 0xffffu));
-        atomicAdd(&before[t + 1], (int)(c >> 16));
+        atomicAdd(&before[t], (int)(sum & 0xffffu));
+        atomicAdd(&before[t + 1], (int)(sum >> 16));
     }
     if (tid < in) {                                                      // equal times inside the tile
         int e = 0;
