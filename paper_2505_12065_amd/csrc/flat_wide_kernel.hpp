@@ -17,7 +17,11 @@
 //
 // Stages of whole lines halve the barriers and the L2's requests; three of them leave room for tiles of 256 x 128 at most.
 // 300 k x 768, B = 128: 132 us by 512 x 128 tiles of half lines, 112 by 256 x 128 of whole ones; 123 457 x 776, B = 77 (a row of
-// 12 1/8 lines) 70 -> 64.
+// 12 1/8 lines) 70 -> 64.  With whole lines a 64 x 64 tile spends 810 clocks a stage, 150 of them on products: its
+// loads are there, barrier, addresses and LDS reads follow each other.  So the steps inside a tile run in a loop without a look
+// at where the loads are, and the addresses are made while the reads run: 977 x 768, B = 5000 32.2 -> 31.2 us a search, 16 k x 768,
+// B = 256 24.1 -> 23.6, 1024 x 768, B = 512 11.9 -> 11.6 (the large tiles, two waves of them on a SIMD, lose 4 % that way: 1 M x
+// 768, B = 512 895 -> 937; reading the operands a stage ahead gains nothing at any).
 //
 // The epilogue is what decides at most sizes.  Sorted lists per lane, with thresholds from a sampling pass, cost two to
 // three launches, 130 registers of lists and queues, and insertions that never become rare unless a slab has
@@ -104,8 +108,25 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
     const bool ragged_row = (rb & (SB - 1)) != 0;
     int iks = 0, issued = 0, iofs = 0;                   // k step and LDS offset of the next stage to issue
     int64_t itile = t0;
+    constexpr bool LINES = SB == 128;
+    const char *xs = xbase, *qs = qbase;                 // LINES: the next stage's place in them
+    // LINES: inside a tile, before its last step
+    auto issue_inside = [&] {
+        unsigned char *sbase = stage_mem + iofs;
+#pragma unroll
+        for (int e = 0; e < LPW; ++e) {
+            const int blk = wave * LPW + e;
+            ANN_GLOBAL_TO_LDS_16((blk < C::A_BLK ? xs : qs) + loff[e], sbase + blk * 1024);
+        }
+        iofs = iofs + C::STAGE_BYTES == C::LDS_BYTES ? 0 : iofs + C::STAGE_BYTES;
+        xs += SB;
+        qs += SB;
+        ++issued;
+        ++iks;
+    };
     auto issue = [&] {
         if (issued >= total) return;
+        if (LINES && iks < ksteps - 1) return issue_inside();
         ++issued;
         unsigned char *sbase = stage_mem + iofs;
         if (ragged_row && iks == ksteps - 1) {
@@ -130,22 +151,24 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
             iks = 0;
             ++itile;
             xbase += (size_t)BM * rb;
+            if (LINES) { xs = xbase; qs = qbase; }
             if ((itile + 1) * BM > N && itile < t1) lane_offsets(itile);                  // ragged last tile
         }
     };
 
     f16v acc[WMF][WNF];
     int it = 0, cofs = 0;                                 // stage being computed, its LDS offset
-    auto stage = [&](auto first) {
+    // `inside` (LINES): there is a stage to load, and it lies inside its tile
+    auto stage = [&](auto first, auto inside) {
         // it has landed once only the newer stages' loads are outstanding (a tile's stores are newer still: the
         // wait right behind an epilogue is a little longer than it has to be)
-        const int newer = min(NST - 2, total - 1 - it);
+        const int newer = decltype(inside)::value ? NST - 2 : min(NST - 2, total - 1 - it);
         if (newer == NST - 2) wait_vmcnt<(NST - 2) * LPW>();
         else static_for<NST - 2>([&](auto rc) {
             if (newer == decltype(rc)::value) wait_vmcnt<decltype(rc)::value * LPW>();
         });
         bare_barrier();                                   // ... for every wave; the buffer of stage it - 1 is free
-        issue();
+        if constexpr (!LINES) issue();
         // Operand row r = lane % 32 of a 32-row block pair, chunk 2 kh + lane / 32.  All operand reads of the stage
         // are issued before the first MFMA, so the LDS pipeline always has several 1 KB reads of this wave in flight.
         const unsigned char *sb = stage_mem + cofs;
@@ -159,6 +182,11 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
 #pragma unroll
             for (int i = 0; i < WMF; ++i)
                 a[kh][i] = *reinterpret_cast<const u4 *>(sb + (wm * WMF + i) * (32 / RPB) * 1024 + lofs);
+        }
+        if constexpr (LINES) {                            // (the addresses are made while the reads run)
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (decltype(inside)::value) issue_inside();
+            else issue();
         }
         __builtin_amdgcn_sched_barrier(0);                // keep the reads ahead of the MFMAs
         static_for<NKH>([&](auto kc) {
@@ -182,8 +210,17 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
 
     for (int s = 0; s < NST - 1; ++s) issue();
     for (int64_t tile = t0; tile < t1; ++tile) {
-        stage(std::true_type{});
-        for (int ks = 1; ks < ksteps; ++ks) stage(std::false_type{});
+        stage(std::true_type{}, std::false_type{});
+        for (int ks = 1; ks < ksteps;) {
+            if constexpr (LINES) {                        // steps that need no look at where the loads are
+                int n = min(min(ksteps - ks, ksteps - 1 - iks), total - issued);
+                ks += max(n, 0);
+                for (; n > 0; --n) stage(std::false_type{}, std::true_type{});
+                if (ks == ksteps) break;
+            }
+            stage(std::false_type{}, std::false_type{});
+            ++ks;
+        }
 
         int ln = lane;
         asm volatile("" : "+v"(ln));                      // (nothing of the epilogue is worth a register in the loop above)
