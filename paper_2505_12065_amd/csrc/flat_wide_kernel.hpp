@@ -79,9 +79,12 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
     const int total = (int)(t1 - t0) * ksteps;
 
     // Block e of a stage: blocks 0 .. A_BLK - 1 corpus rows, the rest queries.  Lane l fetches row l / CPR of the block;
-    // LDS slot l % CPR of that row receives chunk (l % CPR) ^ swz(row) of the stage's bytes of the row.
-    auto swz = [](int row) { return SB == 64 ? (row >> 2) & 3 : row & 7; };
-    const int my_chunk = (lane & (CPR - 1)) ^ swz(lane / CPR);
+    // LDS slot l % CPR of that row receives chunk (l % CPR) ^ swz(row) of the stage's bytes of the row: 16 rows, which an operand
+    // read takes at a time, lie in 16 different places of the 256 bytes that
+    // the banks hold (whole lines swizzled by the row's lowest bits: half of the reads' clocks were conflicts, 977 x 768, B = 5000 31.1
+    // -> 30.4 us).
+    auto swz = [](int row) { return SB == 64 ? (row >> 2) & 3 : (row >> 1) & 7; };
+    auto my_chunk = [&](int e) { return (lane & (CPR - 1)) ^ swz((wave * LPW + e) * RPB + lane / CPR); };
     // Address of a load = uniform base (corpus: start of the tile, advanced per k step; queries: start of the query
     // tile) + a 32-bit per-lane offset that does not change from tile to tile, except in the ragged last tile
     // where rows are clamped to N - 1.  In the last stage of rows that end inside it, chunks behind the end come
@@ -94,11 +97,11 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
             if (blk < C::A_BLK) {
                 int64_t row = tile * BM + blk * RPB + lane / CPR;
                 row = row < N ? row : N - 1;
-                loff[e] = (uint32_t)(row - tile * BM) * (uint32_t)rb + my_chunk * 16;
+                loff[e] = (uint32_t)(row - tile * BM) * (uint32_t)rb + my_chunk(e) * 16;
             } else {
                 int q = n0 + (blk - C::A_BLK) * RPB + lane / CPR;
                 q = q < B ? q : B - 1;
-                loff[e] = (uint32_t)(q - n0) * (uint32_t)rb + my_chunk * 16;
+                loff[e] = (uint32_t)(q - n0) * (uint32_t)rb + my_chunk(e) * 16;
             }
         }
     };
@@ -130,12 +133,12 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
         ++issued;
         unsigned char *sbase = stage_mem + iofs;
         if (ragged_row && iks == ksteps - 1) {
-            const bool inside = iks * SB + my_chunk * 16 < rb;
 #pragma unroll
             for (int e = 0; e < LPW; ++e) {
                 const int blk = wave * LPW + e;
                 const char *base = blk < C::A_BLK ? xbase : qbase;
                 const char *p = base + iks * SB + loff[e];
+                const bool inside = iks * SB + my_chunk(e) * 16 < rb;
                 ANN_GLOBAL_TO_LDS_16(inside ? p : reinterpret_cast<const char *>(zero_row_end), sbase + blk * 1024);
             }
         } else {
@@ -175,7 +178,7 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
         u4 a[NKH][WMF], b[NKH][WNF];
 #pragma unroll
         for (int kh = 0; kh < NKH; ++kh) {
-            const int lofs = (l32 / RPB) * 1024 + (l32 & (RPB - 1)) * SB + (((2 * kh + lhi) ^ swz(l32 & (RPB - 1))) * 16);
+            const int lofs = (l32 / RPB) * 1024 + (l32 & (RPB - 1)) * SB + (((2 * kh + lhi) ^ swz(l32)) * 16);
 #pragma unroll
             for (int j = 0; j < WNF; ++j)
                 b[kh][j] = *reinterpret_cast<const u4 *>(sb + (C::A_BLK + (wn * WNF + j) * (32 / RPB)) * 1024 + lofs);
