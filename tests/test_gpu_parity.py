@@ -76,19 +76,19 @@ def test_cfg0_graph_fp32(cfg0):
     (3000, 1024, 33, 4),            # streaming kernel, three groups of queries
     (5000, 768, 100, 3),            # 64 x 64, ragged corpus tile
     (777, 64, 300, 4),              # ... five query tiles, the last one ragged
-    (70001, 256, 129, 1),           # 256 x 256, groups of 32 rows
+    (70001, 256, 129, 1),           # 256 x 256, groups of 64 rows
     (100, 32, 2100, 2),             # one workgroup's lists are the answer
     (50_000, 768, 32, 3),           # streaming kernel, two query groups, many tiles per wave
     (2049, 96, 20, 10),             # 64 x 64, ragged tile, k > 4
     (300, 4096, 9, 2),              # largest d
     (600_001, 64, 200, 3),          # 256 x 256, groups of 64
     (300_000, 32, 600, 4),          # 512 x 128, groups of 64, five query tiles
-    (131_072 + 77, 128, 96, 5),     # 512 x 128, groups of 32, one query tile
-    (200_003, 64, 300, 16),         # ... three query tiles, k = K_MAX
-    (150_000, 96, 130, 10),         # 256 x 256, groups of 16
-    (131_072, 64, 1, 5),            # streaming kernel, lists of 8, one query
+    (131_072 + 77, 128, 96, 5),     # 256 x 128, one query tile
+    (200_003, 64, 300, 16),         # 512 x 128, three query tiles, k = K_MAX
+    (150_000, 96, 130, 10),         # 256 x 256, groups of 32
+    (131_072, 64, 1, 5),            # short rows: 128 x 64 (fp32: streaming kernel, lists of 8), one query
     (140_000, 136, 17, 10),         # 128 x 64, d not a multiple of 32
-    (150_001, 72, 70, 7),           # 512 x 128, d not a multiple of 32
+    (150_001, 72, 70, 7),           # 256 x 128, d not a multiple of 32
 ])
 def test_flat_shapes(dtype, N, d, B, k):
     say(f"flat shapes: dtype={dtype} N={N} d={d} B={B} k={k}")
@@ -102,9 +102,9 @@ def test_flat_shapes(dtype, N, d, B, k):
 @pytest.mark.parametrize("dtype,N,d,B,k", [
     (torch.float16, 30_000, 128, 9, 16),        # streaming kernel, lists of 16
     (torch.float16, 200_000, 64, 20, 16),       # matrix-core kernel, tiles of 128 x 64, groups of 32 rows
-    (torch.bfloat16, 70_000, 96, 300, 4),       # ... 512 x 128, groups of 32, three query tiles
-    (torch.float16, 700_000, 64, 100, 3),       # ... groups of 64
-    (torch.float16, 150_000, 128, 260, 16),     # ... groups of 16
+    (torch.bfloat16, 70_000, 96, 300, 4),       # ... 256 x 128, three query tiles
+    (torch.float16, 700_000, 64, 100, 3),       # ... 512 x 128, groups of 64
+    (torch.float16, 150_000, 128, 260, 16),     # ... 256 x 128, groups of 32
     (torch.float32, 9_000, 64, 11, 16),         # fp32, streaming kernel, lists of 16
     (torch.float16, 40, 64, 5, 16),             # one workgroup's lists, pages run past the end of a small corpus
     (torch.float16, 40, 64, 200, 16),           # ... many queries
@@ -150,15 +150,15 @@ def test_flat_continuation_pages(dtype, N, d, B, k):
 
 
 @pytest.mark.parametrize("dtype,N,d,B,k", [
-    (torch.float16, 65_000, 40, 257, 5),        # tiles of 512 x 128, row end inside a stage, one query in the last tile
-    (torch.bfloat16, 65_537, 32, 128, 1),       # 128 x 128, one stage, one row in the last tile
+    (torch.float16, 65_000, 40, 257, 5),        # tiles of 256 x 128, row end inside a stage, one query in the last tile
+    (torch.bfloat16, 65_537, 32, 128, 1),       # ... half a stage, one row in the last tile
     (torch.float16, 300_001, 40, 256, 5),       # 256 x 256, row end inside a stage, a full tile of queries
     (torch.bfloat16, 170_001, 72, 500, 3),      # ... ragged last tile of queries
-    (torch.float16, 10_001, 72, 300, 16),       # 128 x 128
+    (torch.float16, 10_001, 72, 300, 16),       # 128 x 64, five query tiles
     (torch.bfloat16, 33_000, 72, 64, 2),        # 128 x 64
     (torch.float16, 65, 136, 70, 16),           # 64 x 64, one-row groups
     (torch.bfloat16, 4_097, 8, 1, 9),           # ... one query, the shortest row
-    (torch.float16, 400_000, 8, 65, 1),         # groups of 64
+    (torch.float16, 400_000, 8, 65, 1),         # 256 x 128, groups of 32
     (torch.float16, 1_000_000, 32, 512, 3),     # ... the corpus in parts through the static workspace
     (torch.bfloat16, 400_000, 8, 513, 2),       # ... the batch in parts of 257 and 256 queries
     (torch.float32, 70_001, 36, 40, 3),         # the streaming kernel with maxima, ragged tile

@@ -12,14 +12,17 @@ DEV = "cuda"
     (torch.float16, 48_897, 40, 100, 3),       # 256 x 128: a stage that the row ends in, one row in the last tile
     (torch.bfloat16, 49_408, 64, 128, 16),     # ... one whole stage, whole tiles
     (torch.float16, 16_001, 200, 400, 5),      # ... four query tiles, rows end after a quarter of a line
-    (torch.bfloat16, 4_000, 136, 2_000, 2),    # ... single rows
+    (torch.bfloat16, 4_000, 136, 2_000, 2),    # ... groups of 16
+    (torch.bfloat16, 4_000, 520, 2_000, 16),   # ... single rows
     (torch.float16, 4_001, 104, 999, 5),       # 128 x 64: one row in the last tile
+    (torch.float16, 4_001, 264, 999, 16),      # ... single rows
     (torch.bfloat16, 700, 264, 3_000, 16),     # ... the corpus is the smaller operand: workgroups by query tile
     (torch.float16, 130_000, 72, 33, 1),       # ... groups of rows, slabs of tiles
     (torch.float16, 1, 8, 65, 1),              # 64 x 64: one row
     (torch.bfloat16, 63, 1_000, 129, 10),      # ... a tile short of one row
     (torch.float16, 1_000, 776, 65, 4),        # ... a line of 16 bytes at the end of a row
-    (torch.float16, 2_049, 96, 5_000, 4),      # 256 x 256: single rows, by query tile
+    (torch.float16, 2_049, 96, 5_000, 4),      # 256 x 256, by query tile: groups of 4
+    (torch.float16, 2_049, 520, 5_000, 16),    # ... single rows
     (torch.bfloat16, 4_000, 768, 1, 3),        # up to 64 queries by these tiles: few long rows
     (torch.float16, 16_384, 384, 32, 1),       # ... one tile for each compute unit
     (torch.float16, 20_001, 768, 17, 16),      # ... up to 32 Ki rows
