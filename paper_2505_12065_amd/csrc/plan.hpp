@@ -596,14 +596,17 @@ inline bool frontier_in_lds(int64_t N, int d, int elem_bytes, int R, int ef, Fro
 //     1983, 1907 / 1812)
 //   maturity exit, tau = 0.9: R = 32, 200 k x 384 bf16, B = 256 ef = 32 103 / 94, 64 174 / 113, 256 326 / 249, 2048 2249 / 1488; R = 16 B = 256
 //     ef = 32 106 / 128, 64 170 / 166; B = 1024 64 339 / 352, 96 429 / 427.  tau = 3 (no query leaves): B = 256 R = 32 64 318 / 319,
-//     128 535 / 516, R = 16 96 357 / 391, 200 651 / 641; B = 512 256 1036 / 1137, 512 2032 / 1891
+//     128 535 / 516, R = 16 96 357 / 391, 200 651 / 641; B = 512 256 1036 / 1137, 512 2032 / 1891; 500 k x 128, B = 64 128 600 / 630, 256 943 / 837;
+//     visited set in memory, 1 M x 256: B = 512 512 2138 / 2678, 2048 7438 / 8428 (two of its workgroups a compute unit wait for more of
+//     these reads than hide), B = 1024 1024 7648 / 7185, B = 256 1024 3600 / 2894
 inline bool frontier_pays(int cus, int row_bytes, int R, int B, int ef, bool counters, float tau, const FrontierLds &L) {
     if (R > GRAPH_STEP_MAX_R || L.total > LDS_MAX) return false;
+    const bool global = L.vis_mode == FRONTIER_VIS_GLOBAL;
     if (counters) {
         if (tau < 1.0f) return ef >= (B > 2 * cus ? 96 : R > 16 && B >= 8 ? 32 : 64);
-        return ef >= (B > cus ? 448 : R > 16 ? 128 : 192);
+        if (global && B > cus && B <= 2 * cus) return false;
+        return ef >= (B > cus ? 448 : R > 16 && (B <= 8 || row_bytes > 256) ? 128 : 192);
     }
-    const bool global = L.vis_mode == FRONTIER_VIS_GLOBAL;
     if (global && ef <= GRAPH_EF_TWO_LEVEL) return false;
     if (B <= cus) return ef >= (row_bytes > 2048 ? 72 : R > 16 ? 12 : 8);
     if (R <= 16) return ef >= 16;
