@@ -193,7 +193,7 @@ inline int wide_group_log(int cus, int wmf, int64_t N, int row_bytes, int B, int
 //   50 k, B = 256              43          48          47         55         63       57
 //   300 k, B = 128 / 512       149 / 291   132 / 322   112 / 316  143 / 401  -        148 / 365
 //   1 M, B = 128 / 512         450 / 887   340 / 976   332 / 984  -          -        441 / 1160
-// Short rows in long slabs keep 512 x 128 (1 M x 384, B = 128: 180 against 187; 1 M x 128 75 / 80; 300 k x 128, B = 400 66 / 72; fewer
+// (The K loop of the last three has lost another 2 to 4 % since.)  Short rows in long slabs keep 512 x 128 (1 M x 384, B = 128: 180 against 187; 1 M x 128 75 / 80; 300 k x 128, B = 400 66 / 72; fewer
 // tiles than four for each compute unit: equal at 130 k x 384, B = 400, and 73 against 63 at 300 k x 384, B = 100).  Queries are padded
 // to whole tiles; the tiles of 128 queries run at 12/13 of the rate of the other, so they take over where they save more
 // than that (1 M x 768, B = 300: 822 -> 745).
