@@ -842,10 +842,12 @@ __global__ __launch_bounds__(GRAPH_THREADS, QREG ? 2 : 3) void graph_search_kern
                 s_best = ls(cur)[0];
                 s_worst = ls(cur)[len - 1];
             }
-            float r = NAN;                                // NaN: no sample; -inf: one, but best == worst
-            if (lane < 32 && ci[lane] >= 0) r = s_best != s_worst ? (s_best - cs[lane]) / (s_best - s_worst) : -INFINITY;
+            // (a NaN score is counted, and gives no sample)
+            const bool scored = lane < 32 && ci[lane] >= 0;
+            float r = NAN;                                // no sample
+            if (scored && s_best != s_worst) r = (s_best - cs[lane]) / (s_best - s_worst);
             const uint32_t mag = __float_as_uint(r) & 0x7fffffffu;
-            n_dist += __builtin_popcountll(__builtin_amdgcn_ballot_w64(mag <= 0x7f800000u));
+            n_dist += __builtin_popcountll(__builtin_amdgcn_ballot_w64(scored));
             for (uint64_t defined = __builtin_amdgcn_ballot_w64(mag < 0x7f800000u); defined != 0; defined &= defined - 1) {
                 const float ri = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r), __builtin_ctzll(defined)));
                 ema = fmaf(ns.alpha, ri - ema, ema);
@@ -1090,13 +1092,14 @@ __global__ __launch_bounds__(GRAPH_THREADS, QREG ? 2 : 3) void graph_search_kern
         if (NS && wave == GRAPH_WAVES - 1) {
             // best / worst of the list as it stands before this expansion's entries go in
             const float s_best = ls(cur)[0], s_worst = ls(cur)[len - 1];
-            // RQ of slot i, or NaN: no newly scored node there, or -inf: one, but best == worst.
+            // RQ of slot i, or NaN: no newly scored node there, or -inf: one, but its RQ is undefined (best == worst, or
+            // a NaN score: counted, and no sample).
             // An id named more than once in the row is scored by whichever slot won the race
             // for the cache entry (rarely by two); its one sample belongs to the first slot
             // that names it.
             auto rq_of = [&](int i, int me, bool first, bool scored, float sv) -> float {
                 (void)i; (void)me;
-                return !(first && scored) ? NAN : s_best != s_worst ? (s_best - sv) / (s_best - s_worst) : -INFINITY;
+                return !(first && scored) ? NAN : s_best != s_worst && sv == sv ? (s_best - sv) / (s_best - s_worst) : -INFINITY;
             };
             auto take = [&](float r) {
                 if (r == r) {

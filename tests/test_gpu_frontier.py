@@ -83,9 +83,8 @@ def test_graph_frontier_entries_and_nan(ef):
     torch.cuda.synchronize()
     o_ids, _, _, n_dist, n_expand = oracle.graph_search(to_np(x), g.numpy(), 0, to_np(q), 10, ef, entries=e.numpy())
     assert np.array_equal(ids.cpu().numpy(), o_ids)
-    if ef >= 64:
-        ids, _, stats, _ = ann.ann_graph_search_nonstall_typed(x.to(DEV), g.to(DEV), 0, q.to(DEV), 10, ef, entries=e.to(DEV), tau=0.999,
-                                                               window=2_000_000_000)
-        torch.cuda.synchronize()
-        st = stats.cpu().numpy()
-        assert np.array_equal(ids.cpu().numpy(), o_ids) and np.array_equal(st[:, 1], n_dist) and np.array_equal(st[:, 2], n_expand)
+    ids, _, stats, _ = ann.ann_graph_search_nonstall_typed(x.to(DEV), g.to(DEV), 0, q.to(DEV), 10, ef, entries=e.to(DEV), tau=0.999,
+                                                           window=2_000_000_000)
+    torch.cuda.synchronize()
+    st = stats.cpu().numpy()
+    assert np.array_equal(ids.cpu().numpy(), o_ids) and np.array_equal(st[:, 1], n_dist) and np.array_equal(st[:, 2], n_expand)

@@ -142,3 +142,26 @@ def test_nonstall_bad_arguments(small):
         ann.ann_graph_search_nonstall_typed(xd, gd, 5, qd, 3, 64, tau=float("nan"))
     with pytest.raises(ann.AnnError):
         ann.ann_graph_search_nonstall_typed(xd, gd, 5, qd, 3, 2)      # ef < k
+
+
+@pytest.mark.parametrize("N,R,B,ef,tau", [
+    (4000, 12, 9, 16, float("inf")),          # graph_search_kernel, one expansion ahead
+    (4000, 12, 9, 300, float("inf")),         # graph_frontier_kernel
+    (4000, 40, 9, 40, float("inf")),          # the plain loop of wide graphs
+    (4000, 40, 3, 2500, 0.9),                 # ... one list merged in place
+    (700_000, 4, 257, 700, float("inf")),     # the two-level list: visited sets that leave no room for two workgroups
+])
+def test_nan_rows_are_counted(N, R, B, ef, tau):
+    """A row whose score is NaN is scored and counted like any other, gives no sample and is never listed."""
+    say(f"NaN rows counted: N={N} R={R} B={B} ef={ef} tau={tau}")
+    gen = torch.Generator().manual_seed(N + R)
+    x = torch.randn(N, 8, generator=gen).half()
+    x[::5, 3] = float("nan")
+    q = torch.randn(B, 8, generator=gen).half()
+    g = torch.randint(-1, N + 1, (N, R), generator=gen, dtype=torch.int32)
+    ids, _, stats, ema, o = run_both(x, g, 1, q, 5, ef, tau, 200)
+    o_ids, _, _, o_stats, o_ema = o
+    assert (ids == o_ids).all(1).mean() >= 0.98 and (ids % 5 != 0).all()
+    same = (stats == o_stats).all(1)
+    assert same.mean() >= 0.98, (stats[~same][:4], o_stats[~same][:4])      # (scores that differ by one rounding)
+    assert np.allclose(ema[same], o_ema[same], atol=1e-4)
