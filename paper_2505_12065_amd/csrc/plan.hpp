@@ -222,7 +222,12 @@ inline int wide_shape(int cus, int64_t N, int d, int B) {
 //   beyond, by groups of 16 queries against d: 64 k x 128, B = 16 / 24 13.3 / 13.2, 16.8 / 13.2; 64 k x 768, B = 32 / 48 31 / 33, 36 / 33;
 //   128 k x 256, B = 16 / 24 20.6 / 23.5, 24.8 / 23.7; 300 k x 128, B = 16 / 24 23 / 27, 28 / 27; 300 k x 256, B = 32 / 48 41 / 43, 47 / 44;
 //   1 M x 128, B = 32 / 48 62 / 63, 85 / 68; 1 M x 256, B = 64 125 / 121; 1 M x 768, B = 64 290 / 320.
-inline bool many_queries(int64_t N, int d, int B) { return B * (N <= 128 * 1024 ? 16 : N <= 512 * 1024 ? 8 : 4) >= d; }
+//   beyond 4 Mi rows, where lists seldom change any more: 17.2 M x 232, B = 59, k = 5 1623 / 2185 (2234 in the parts of 8 MiB); 21 M x 256,
+//   B = 64 1841 / 2571; 4.3 M x 248, B = 64 451 / 570; 6.0 M x 200, B = 61 587 / 691; 15.9 M x 120, B = 37 841 / 1020; 9.8 M x 120, B = 64
+//   602 / 675, but 6.6 M x 112, B = 62 502 / 438, x 80, B = 47 392 / 316; 9.4 M x 72, B = 39 516 / 413.
+inline bool many_queries(int64_t N, int d, int B) {
+    return B * (N <= 128 * 1024 ? 16 : N <= 512 * 1024 ? 8 : N <= 4 * 1024 * 1024 ? 4 : 2) >= d;
+}
 inline bool use_wide(int64_t N, int d, int dtype, int B, int k) {
     if (dtype == ANN_F32) return false;
     if (B >= WIDE_MIN_B) return true;

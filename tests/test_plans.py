@@ -173,3 +173,23 @@ def test_a_buffer_too_small_for_parts_is_refused(plans):
     (16_384, 40, 0, 512, 9, True), (127_999, 40, 0, 2048, 16, False)])
 def test_what_the_static_workspace_takes(plans, N, d, dtype, B, k, accepted):
     assert bool(plans.static_accepts(CUS, N, d, dtype, B, k, STATIC)) == accepted
+
+
+# us of a call, lists / matrix cores with all the room there is, where the two differ by a tenth
+@pytest.mark.parametrize("N,d,B,k,kind", [
+    (17_200_000, 232, 59, 5, "lists"),           # 1623 / 2185: in 8 MiB one pass, and not parts
+    (21_000_000, 256, 64, 5, "lists"),           # 1841 / 2571
+    (8_600_000, 200, 63, 12, "lists"),           # 800 / 1007
+    (15_939_049, 120, 37, 1, "lists"),           # 841 / 1020
+    (4_294_538, 248, 64, 3, "lists"),            # 451 / 570
+    (6_634_886, 112, 62, 1, "wide"),             # 502 / 438
+    (9_365_109, 72, 39, 1, "wide"),              # 516 / 413
+    (14_313_870, 56, 31, 1, "wide"),             # 543 / 447
+    (1_542_172, 112, 43, 1, "wide"),             # 127 / 92
+    (1_545_228, 176, 56, 16, "wide")])           # 183 / 151
+def test_many_queries_on_large_corpora(plans, N, d, B, k, kind):
+    """The same kernel with all the room and in the static workspace, so that both entry points give the same bits."""
+    for limit in (1 << 30, STATIC):
+        p = flat(plans, N, d, 0, B, k, limit)
+        assert KINDS[p["kind"]] == kind and p["bytes"] <= limit
+        assert kind == "wide" or (p["rows"] == N and p["part"] == B)
