@@ -225,8 +225,11 @@ inline int wide_shape(int cus, int64_t N, int d, int B) {
 //   beyond 4 Mi rows, where lists seldom change any more: 17.2 M x 232, B = 59, k = 5 1623 / 2185 (2234 in the parts of 8 MiB); 21 M x 256,
 //   B = 64 1841 / 2571; 4.3 M x 248, B = 64 451 / 570; 6.0 M x 200, B = 61 587 / 691; 15.9 M x 120, B = 37 841 / 1020; 9.8 M x 120, B = 64
 //   602 / 675, but 6.6 M x 112, B = 62 502 / 438, x 80, B = 47 392 / 316; 9.4 M x 72, B = 39 516 / 413.
+//   from 1.25 Mi rows of over 192 elements (B = 64): 1.5 M x 256 166 / 178, 2.2 M 226 / 264, 4 M 389 / 485; x 224, B = 60 183 / 175, 245 / 255,
+//   403 / 468; but x 192, B = 52 172 / 137, 234 / 203, 384 / 365; x 136, B = 64 163 / 128, 222 / 194, 352 / 335.
 inline bool many_queries(int64_t N, int d, int B) {
-    return B * (N <= 128 * 1024 ? 16 : N <= 512 * 1024 ? 8 : N <= 4 * 1024 * 1024 ? 4 : 2) >= d;
+    const bool large = N > 4 * 1024 * 1024 || (N > 1280 * 1024 && d > 192);
+    return B * (N <= 128 * 1024 ? 16 : N <= 512 * 1024 ? 8 : large ? 2 : 4) >= d;
 }
 inline bool use_wide(int64_t N, int d, int dtype, int B, int k) {
     if (dtype == ANN_F32) return false;

@@ -186,7 +186,10 @@ def test_what_the_static_workspace_takes(plans, N, d, dtype, B, k, accepted):
     (9_365_109, 72, 39, 1, "wide"),              # 516 / 413
     (14_313_870, 56, 31, 1, "wide"),             # 543 / 447
     (1_542_172, 112, 43, 1, "wide"),             # 127 / 92
-    (1_545_228, 176, 56, 16, "wide")])           # 183 / 151
+    (1_545_228, 176, 56, 16, "wide"),            # 183 / 151
+    (2_200_000, 256, 64, 3, "lists"),            # 226 / 264
+    (4_000_000, 224, 60, 3, "lists"),            # 403 / 468
+    (2_200_000, 192, 52, 3, "wide")])            # 234 / 203
 def test_many_queries_on_large_corpora(plans, N, d, B, k, kind):
     """The same kernel with all the room and in the static workspace, so that both entry points give the same bits."""
     for limit in (1 << 30, STATIC):
