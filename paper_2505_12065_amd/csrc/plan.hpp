@@ -227,10 +227,8 @@ inline int wide_shape(int cus, int64_t N, int d, int B) {
 //   602 / 675, but 6.6 M x 112, B = 62 502 / 438, x 80, B = 47 392 / 316; 9.4 M x 72, B = 39 516 / 413.
 //   from 1.25 Mi rows of over 192 elements (B = 64): 1.5 M x 256 166 / 178, 2.2 M 226 / 264, 4 M 389 / 485; x 224, B = 60 183 / 175, 245 / 255,
 //   403 / 468; but x 192, B = 52 172 / 137, 234 / 203, 384 / 365; x 136, B = 64 163 / 128, 222 / 194, 352 / 335.
-inline bool many_queries(int64_t N, int d, int B) {
-    const bool large = N > 4 * 1024 * 1024 || (N > 1280 * 1024 && d > 192);
-    return B * (N <= 128 * 1024 ? 16 : N <= 512 * 1024 ? 8 : large ? 2 : 4) >= d;
-}
+inline bool many_queries(int64_t N, int d, int B) { return B * (N <= 128 * 1024 ? 16 : N <= 512 * 1024 ? 8 : 4) >= d; }
+inline bool lists_settle(int64_t N, int d, int B) { return (N > 4 * 1024 * 1024 || (N > 1280 * 1024 && d > 192)) && 2 * B < d; }
 inline bool use_wide(int64_t N, int d, int dtype, int B, int k) {
     if (dtype == ANN_F32) return false;
     if (B >= WIDE_MIN_B) return true;
@@ -239,7 +237,7 @@ inline bool use_wide(int64_t N, int d, int dtype, int B, int k) {
     if (d <= 64 || (groups > 1 && groups * steps > STREAM_LDS_STEPS)) return true;
     if (N <= 32 * 1024) return B > 32 || (B > 16 && d >= 768);
     if (B <= 16) return N <= 128 * 1024 && d <= 96;
-    return many_queries(N, d, B);
+    return many_queries(N, d, B) && !lists_settle(N, d, B);
 }
 
 // fp32 keeps lists for up to 16 queries (HBM-bound on large corpora) and wherever picking costs more than the lists: the rows

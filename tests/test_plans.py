@@ -196,3 +196,12 @@ def test_many_queries_on_large_corpora(plans, N, d, B, k, kind):
         p = flat(plans, N, d, 0, B, k, limit)
         assert KINDS[p["kind"]] == kind and p["bytes"] <= limit
         assert kind == "wide" or (p["rows"] == N and p["part"] == B)
+
+
+@pytest.mark.parametrize("N,d,B,k,buffer", [
+    (5_000_000, 200, 60, 3, 200_000), (8_600_000, 120, 40, 12, 100_000), (1_500_000, 256, 64, 3, 150_000)])
+def test_lists_that_do_not_fit_leave_the_parts(plans, N, d, B, k, buffer):
+    """Calls whose lists get less than a quarter of their slabs are taken in parts where there are many queries."""
+    p = flat(plans, N, d, 0, B, k, buffer)
+    assert KINDS[flat(plans, N, d, 0, B, k, 1 << 30)["kind"]] == "lists"
+    assert KINDS[p["kind"]] == "wide" and p["rows"] < N and p["bytes"] <= buffer
