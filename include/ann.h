@@ -110,9 +110,9 @@ int ann_flat_search_typed(const void *corpus, int64_t N, int32_t d, int32_t dtyp
  * rows with a smaller score, or the same score and a larger id.  Feeding the last pair of one answer
  * into the next call enumerates the corpus in order, k rows at a time; when fewer than k rows are
  * left the tail is id -1, score -inf.  The boundary score is compared with the fp32 scores the
- * kernels compute, so pass the scores as they were returned, and use the same B, k and element type
- * for every page (each kernel variant sums in its own order; a row within one rounding of the
- * boundary could otherwise be seen on the other side of it).
+ * kernels compute, so pass the scores as they were returned, and use the same B, k, element type and
+ * workspace (ann_set_workspace; none) for every page (each kernel variant sums in its own order; a
+ * row within one rounding of the boundary could otherwise be seen on the other side of it).
  *   after_scores, after_ids   device [B] float / int32, both or neither; NULL = ann_flat_search_typed.
  *                             A NaN boundary score excludes nothing for that query. */
 int ann_flat_search_after_typed(const void *corpus, int64_t N, int32_t d, int32_t dtype,
@@ -272,7 +272,7 @@ int64_t ann_flat_workspace_bytes(int64_t N, int32_t d, int32_t dtype, int32_t B,
  * caller's allocator owns the memory and no entry point ever allocates): every call that needs
  * workspace (ann_flat_workspace_bytes, ann_graph_nonstall_workspace_bytes) then runs in it.  A flat
  * search that does not fit `bytes` at once takes the corpus in parts, or fewer slabs, or (up to 64
- * queries of 16 bits) the kernel that needs less; one that would need parts of fewer than 8192 rows, or
+ * queries of 16 bits) the kernel that needs less, if its own needs parts that take longer; one that would need parts of fewer than 8192 rows, or
  * less than a quarter of its slabs, and a graph search that needs more than `bytes`, fail with
  * ANN_ERR_NOMEM instead of growing anything.  A flat search captured into a graph while the library's
  * own buffer would have to grow does likewise with the buffer as it is.

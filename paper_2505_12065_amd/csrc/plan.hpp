@@ -340,7 +340,31 @@ inline void lists_plan(FlatPlan &pl, int cus, int64_t N, int d, int dtype, int B
     pl.ws_bytes = slab * pl.st.P;
 }
 
-inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, size_t limit) {
+// A call of up to 64 queries whose maxima do not fit at once: the matrix-core kernel in parts, or lists in one pass, whichever takes
+// less, in us.  A part costs 8 us beside the rows of its k groups, and its tiles go in rounds of one for every compute unit;
+// lists read the corpus more than once where the queries do not fit the LDS together, cost more with every group of 16
+// queries, and have too few workgroups where their slabs are cut.  Fitted to 220 calls of 20 k to 20 M rows, d = 8 to 4096, in 16 KB to
+// 8 MiB: 1 % behind the better side on average (always in parts 12 %, always lists 74 %), half again as long at worst.  Lists / parts:
+// 1 M x 128, B = 64 in 1 MiB 107 / 146; 16 M x 64, B = 32 in 1 MiB 486 / 905; 1.9 M x 24, B = 4 in 85 KB 61 / 96; but 4 M x 64, B = 64 in
+// 8 MiB 301 / 144; 16 M x 8, B = 1 in 63 KB 436 / 286; 1.6 M x 1600, B = 57 in 123 KB 4354 / 2649.
+inline double parts_us(const FlatPlan &pl, int64_t N, int d, int B, int k) {
+    const int64_t parts = (N + pl.rows - 1) / pl.rows;
+    const double round = (double)pl.w.cus * wide_rows(pl.w.shape), row = ceil(d / 32.0) * 64 / 6.1e6;
+    const double rounds = (parts - 1) * ceil(pl.rows / round) + ceil((N - (parts - 1) * pl.rows) / round) + 0.3 * parts;
+    const double pick = (double)(k << pl.w.gs_log) * d * 2 * pl.part / 4e6;
+    return (B + pl.part - 1) / pl.part * (parts * (8 + pick) + 1.1 * rounds * round * row);
+}
+inline double lists_us(const FlatPlan &pl, int cus, int64_t N, int d, int dtype, int B, int k) {
+    FlatPlan whole{};
+    lists_plan(whole, cus, N, d, dtype, B, k, SIZE_MAX);
+    const double all = (double)whole.st.P * whole.st.G, wgs = (double)pl.st.P * pl.st.G, groups = (B + 15) / 16, rows = N * 1e-6;
+    const double cut = wgs >= cus ? 1 + 0.3 * (all / wgs - 1) : (1 + 0.3 * (fmax(all / cus, 1.0) - 1)) * fmin(all, cus) / wgs;
+    const double read = (0.45 + 0.6 * pl.st.G) * rows * d * 2 / 6.1 * cut;
+    return fmax(read, rows * (24 + 3 * groups) * cut + groups * fmin(35, 2 + 8 * rows)) + 10;
+}
+
+// in_parts: a call keeps its kernel, and its bits, where that takes parts (the static entry point, whose workspace is of one size).
+inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, size_t limit, bool in_parts = false) {
     FlatPlan pl{};
     pl.part = B;
     pl.rows = N;
@@ -356,14 +380,19 @@ inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, si
         else lists_plan(pl, cus, N, d, dtype, B, k, limit);
     };
     plan();
-    if (pl.ws_bytes <= limit || dtype == ANN_F32 || B >= WIDE_MIN_B) return pl;
-    // The other kernel, if its workspace fits (lists of less than a quarter of their slabs: only for many queries).  Where
-    // neither does ws_bytes says so.
+    const bool fits = pl.ws_bytes <= limit;
+    if (dtype == ANN_F32 || B >= WIDE_MIN_B || (fits && (!pl.wide || in_parts || (pl.rows == N && pl.part == B)))) return pl;
+    // The other kernel, if its workspace fits: where the first has none (lists of less than a quarter of their slabs: only for many
+    // queries), or would need parts that take longer than lists.  Where neither fits ws_bytes says so.
     if (!pl.wide && (pl.direct || N <= 32 * 1024 || !many_queries(N, d, B))) return pl;
     const FlatPlan first = pl;
-    pl.wide = !pl.wide;
+    pl = FlatPlan{};
+    pl.part = B;
+    pl.rows = N;
+    pl.wide = !first.wide;
     plan();
-    return pl.ws_bytes <= limit ? pl : first;
+    if (pl.ws_bytes > limit || (fits && lists_us(pl, cus, N, d, dtype, B, k) >= parts_us(first, N, d, B, k))) return first;
+    return pl;
 }
 
 // Long answers of large batches that the static workspace takes though one pass does not fit it.  They once needed a list of 16
@@ -394,7 +423,7 @@ inline FlatPlan static_plan(int cus, int64_t N, int d, int dtype, int B, int k, 
         if (pl.ws_bytes > (size_t)ANN_STATIC_WORKSPACE_BYTES && pl.ws_bytes <= bytes) pl.ws_bytes = bytes + 1;
         return pl;
     }
-    return flat_plan(cus, N, d, dtype, B, k, bytes);
+    return flat_plan(cus, N, d, dtype, B, k, bytes, true);
 }
 
 // ---- graph search ---------------------------------------------------------------------------------------

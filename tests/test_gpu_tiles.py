@@ -90,3 +90,30 @@ def test_other_kernel_where_the_workspace_is_short(N, d, B, k, size):
         again = ann.ann_flat_search_typed(x[:1_000], q, k)
         torch.cuda.synchronize()
         assert torch.equal(again[0], few[0]) and torch.equal(again[1], few[1])
+
+
+@pytest.mark.parametrize("N,d,B,k,size", [
+    (100_000, 256, 32, 3, 1 << 17),            # all slabs but a few
+    (73_541, 128, 25, 10, 204_400),            # k > 4, a third of the slabs
+])
+def test_one_pass_on_lists_where_parts_take_longer(N, d, B, k, size):
+    """Two pages in a caller's buffer that the matrix-core kernel's parts would fit as well, against scores in binary64 (bound: see
+    test_line_stages); nothing behind the buffer is written."""
+    print(f"lists in a small buffer: N={N} d={d} B={B} k={k} bytes={size}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(N)
+    x, q = (torch.randn(n, d, generator=gen, device=DEV).half() for n in (N, B))
+    assert ann.ann_flat_workspace_bytes(N, d, torch.float16, B, k) > size
+    buf = torch.full((size + 4096,), 0xAB, dtype=torch.uint8, device=DEV)
+    try:
+        ann.ann_set_workspace(buf[:size])
+        first = ann.ann_flat_search_typed(x, q, k)
+        second = ann.ann_flat_search_typed(x, q, k, after=(first[1][:, -1].contiguous(), first[0][:, -1].contiguous()))
+        torch.cuda.synchronize()
+    finally:
+        ann.ann_set_workspace(None)
+    assert bool((buf[size:] == 0xAB).all())
+    ids, sc = torch.cat([first[0], second[0]], 1).long(), torch.cat([first[1], second[1]], 1).double()
+    exact = q.double() @ x.double().T
+    bound = d * 2.0 ** -24 * q.double().norm(dim=1, keepdim=True) * x.double().norm(dim=1).max()
+    assert ((exact.gather(1, ids) - sc).abs() <= bound).all() and ((exact.topk(2 * k).values - sc).abs() <= bound).all()
+    assert (ids.sort(1).values.diff(dim=1) > 0).all()

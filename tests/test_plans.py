@@ -32,6 +32,10 @@ extern "C" void flat(int cus, int64_t N, int d, int dtype, int B, int k, int64_t
 extern "C" int static_accepts(int cus, int64_t N, int d, int dtype, int B, int k, int64_t bytes) {
     return static_plan(cus, N, d, dtype, B, k, (size_t)bytes).ws_bytes <= (size_t)bytes;
 }
+extern "C" int static_kind(int cus, int64_t N, int d, int dtype, int B, int k, int64_t bytes) {
+    const FlatPlan pl = static_plan(cus, N, d, dtype, B, k, (size_t)bytes);
+    return pl.ws_bytes > (size_t)bytes ? -1 : pl.wide ? 2 : pl.maxima ? 3 : pl.direct ? 1 : 0;
+}
 """
 KINDS = ("lists", "direct", "wide", "maxima")
 STATIC = 8 * 1024 * 1024 + 1024 * 16 * 8             # the static workspace, room for the k best of a part's queries included
@@ -47,7 +51,7 @@ def plans(tmp_path_factory):
     L = ctypes.CDLL(str(lib))
     L.step_pays.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 5 + [ctypes.c_float]
     L.flat.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64, ctypes.c_void_p]
-    L.static_accepts.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64]
+    L.static_accepts.argtypes = L.static_kind.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64]
     return L
 
 
@@ -205,3 +209,42 @@ def test_lists_that_do_not_fit_leave_the_parts(plans, N, d, B, k, buffer):
     p = flat(plans, N, d, 0, B, k, buffer)
     assert KINDS[flat(plans, N, d, 0, B, k, 1 << 30)["kind"]] == "lists"
     assert KINDS[p["kind"]] == "wide" and p["rows"] < N and p["bytes"] <= buffer
+
+
+# us of a call in a buffer of so many bytes, one pass on lists / parts on the matrix cores
+@pytest.mark.parametrize("N,d,B,k,buffer,kind", [
+    (1_000_000, 128, 64, 3, 1 << 20, "lists"),       # 107 / 146
+    (16_000_000, 64, 32, 3, 1 << 20, "lists"),       # 486 / 905
+    (300_000, 128, 32, 3, 1 << 18, "lists"),         # 31 / 53
+    (100_000, 256, 32, 3, 1 << 17, "lists"),         # 28 / 55
+    (1_884_008, 24, 4, 1, 84_927, "lists"),          # 61 / 96
+    (558_736, 32, 4, 3, 17_158, "lists"),            # 54 / 172
+    (1_773_482, 1384, 61, 3, 267_598, "lists"),      # 1374 / 2465
+    (1_052_988, 96, 41, 3, 205_116, "lists"),        # 163 / 331, a third of the slabs
+    (344_490, 2752, 25, 10, 367_182, "lists"),       # 534 / 706
+    (16_000_000, 8, 1, 2, 63_000, "wide"),           # 436 / 286, 18 parts
+    (16_000_000, 32, 8, 3, 1 << 20, "wide"),         # 487 / 308
+    (3_003_528, 40, 24, 1, 3_134_841, "wide"),       # 145 / 75
+    (2_000_000, 2048, 40, 3, 1 << 20, "wide"),       # 1982 / 1770
+    (1_185_604, 2976, 39, 3, 2_251_554, "wide"),     # 2689 / 1533
+    (1_549_591, 1600, 57, 5, 122_708, "wide"),       # 4354 / 2649, a quarter of the slabs
+    (258_523, 3392, 41, 16, 180_826, "wide")])       # 1647 / 1030
+def test_parts_or_lists_in_a_small_buffer(plans, N, d, B, k, buffer, kind):
+    p = flat(plans, N, d, 0, B, k, buffer)
+    assert KINDS[p["kind"]] == kind and p["bytes"] <= buffer
+    assert (kind == "lists") == (p["rows"] == N)
+
+
+def test_the_static_workspace_keeps_the_kernel(plans):
+    """Up to 64 queries of 16 bits: what one pass would take, if it fits at all."""
+    rng = random.Random(3)
+    log = lambda lo, hi: int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+    parts = 0
+    for _ in range(4000):
+        N, d, B, k = log(1, 5e7), 8 * log(1, 512), rng.randint(1, 64), rng.randint(1, 16)
+        k = min(k, N)
+        whole, static = (plans.static_kind(CUS, N, d, 0, B, k, size) for size in (1 << 40, STATIC))
+        if static >= 0:
+            assert whole == static, (N, d, B, k)
+        parts += static == 2 and flat(plans, N, d, 0, B, k, 1 << 30)["bytes"] > STATIC
+    assert parts > 20
