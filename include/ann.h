@@ -20,7 +20,8 @@
  *     synchronised `stream`.  No entry point synchronises the device except
  *     when the library-owned workspace has to grow (a call that needs more of it
  *     than any before on this device; it grows by a quarter more than needed, to
- *     1.25 GiB at most for the flat search).
+ *     1.25 GiB at most for the flat search).  A buffer that a captured graph may hold
+ *     is not freed then but kept until ann_release_workspace, so the graph can be replayed.
  *   - One workspace per device: calls that use it (the flat search, the graph
  *     search with ef > 512, the non-stall graph search) are safe one after the
  *     other on one stream, or on several streams if the caller orders them; two
@@ -276,11 +277,12 @@ int64_t ann_flat_workspace_bytes(int64_t N, int32_t d, int32_t dtype, int32_t B,
  * less than a quarter of its slabs, and a graph search that needs more than `bytes`, fail with
  * ANN_ERR_NOMEM instead of growing anything.  A flat search captured into a graph while the library's
  * own buffer would have to grow does likewise with the buffer as it is.
- *   workspace  device pointer, 256-byte aligned, valid until it is replaced; NULL: back to the
- *              library-owned buffers.  Not freed by the library.  Calls that use it must not overlap. */
+ *   workspace  device pointer, 256-byte aligned, valid until it is replaced (and as long as graphs
+ *              captured with it are replayed); NULL: back to the library-owned buffers.  Not freed by the library.  Calls that use it must not overlap. */
 int ann_set_workspace(void *workspace, int64_t bytes);
 
-/* Release the library-owned workspace of the current device (synchronises it). */
+/* Release the library-owned workspace of the current device (synchronises it), what is kept for
+ * captured graphs included: those that hold it must not be replayed any more. */
 int ann_release_workspace(void);
 
 /* Kernel timing for benchmarks (measurement support, no paper passage).  While it is on,

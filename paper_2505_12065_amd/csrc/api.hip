@@ -42,12 +42,16 @@ static __device__ __align__(256) unsigned char scratch[STATIC_BYTES];
 
 namespace {
 
+struct Buffer {
+    void *ptr = nullptr;
+    size_t bytes = 0;
+    bool captured = false;        // a graph may hold it
+};
 struct DeviceState {
     int cus = 0;
-    void *ws = nullptr;
-    size_t ws_bytes = 0;
-    void *vis = nullptr;          // visited bitsets of the non-stall graph search
-    size_t vis_bytes = 0;
+    Buffer ws;
+    Buffer vis;                   // visited bitsets of the non-stall graph search
+    std::vector<void *> kept;     // outgrown buffers that a graph may hold
     void *scratch_ptr = nullptr;  // this device's address of `scratch`
     void *user_ws = nullptr;      // caller-owned workspace (ann_set_workspace), used instead of ws and vis
     size_t user_bytes = 0;
@@ -80,23 +84,34 @@ int device_state(DeviceState **out) {
     return ANN_OK;
 }
 
-int grow(void **buf, size_t *have, size_t bytes) {
-    if (*have >= bytes) return ANN_OK;
-    if (*buf) (void)hipFree(*buf);               // synchronises the device: no kernel still uses it
-    *buf = nullptr;
-    *have = 0;
+// Buffers grow by a quarter at least, so what is kept for graphs adds up to four times the present size at most.
+int grow(DeviceState *st, Buffer *buf, size_t bytes) {
+    if (buf->bytes >= bytes) return ANN_OK;
+    if (buf->ptr && buf->captured) st->kept.push_back(buf->ptr);
+    else if (buf->ptr) (void)hipFree(buf->ptr);  // synchronises the device: no kernel still uses it
+    *buf = Buffer();
     size_t want = bytes + bytes / 4;
-    if (hipMalloc(buf, want) != hipSuccess) {
+    if (hipMalloc(&buf->ptr, want) != hipSuccess) {
         (void)hipGetLastError();
+        buf->ptr = nullptr;
         return fail(ANN_ERR_NOMEM, "cannot allocate %zu bytes of device workspace", want);
     }
-    *have = want;
+    buf->bytes = want;
     return ANN_OK;
 }
 
+bool is_captured(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+        (void)hipGetLastError();                          // (the null stream, while another stream is captured)
+        return true;
+    }
+    return status != hipStreamCaptureStatusNone;
+}
+
 // The device buffer a call may use as workspace: the caller's when one was set (never grown: a call
-// that needs more fails), else the library's own, grown on demand.
-int workspace_for(DeviceState *st, void **own, size_t *own_bytes, size_t bytes, void **out) {
+// that needs more fails), else the library's own, grown on demand and, once a graph may hold it, not freed by growing.
+int workspace_for(DeviceState *st, Buffer *own, size_t bytes, hipStream_t stream, void **out) {
     if (st->user_ws) {
         if (bytes > st->user_bytes)
             return fail(ANN_ERR_NOMEM, "this call needs %zu bytes of workspace, the buffer given to ann_set_workspace has %zu",
@@ -104,22 +119,17 @@ int workspace_for(DeviceState *st, void **own, size_t *own_bytes, size_t bytes, 
         *out = st->user_ws;
         return ANN_OK;
     }
-    if (int rc = grow(own, own_bytes, bytes)) return rc;
-    *out = *own;
+    if (int rc = grow(st, own, bytes)) return rc;
+    own->captured = own->captured || (bytes > 0 && is_captured(stream));
+    *out = own->ptr;
     return ANN_OK;
 }
 
 // Whether workspace_for gives `bytes` to a call on `stream`: in a caller's buffer if they fit, in the library's own unless that
 // would have to grow while the stream is captured.
-bool at_hand(const DeviceState *st, size_t own_bytes, size_t bytes, hipStream_t stream) {
+bool at_hand(const DeviceState *st, const Buffer &own, size_t bytes, hipStream_t stream) {
     if (st->user_ws) return bytes <= st->user_bytes;
-    if (bytes <= own_bytes) return true;
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
-        (void)hipGetLastError();                          // (the null stream, while another stream is captured)
-        return false;
-    }
-    return status == hipStreamCaptureStatusNone;
+    return bytes <= own.bytes || !is_captured(stream);
 }
 
 // ---- optional event timing of the main kernels -----------------------------------------------
@@ -354,13 +364,13 @@ int ann_measure_mfma_rate(int32_t random_operands, int32_t iters, double *tflops
     std::lock_guard<std::mutex> lock(g_mu);
     DeviceState *st = nullptr;
     if (int rc = device_state(&st)) return rc;
-    if (int rc = grow(&st->ws, &st->ws_bytes, 256)) return rc;
+    if (int rc = grow(st, &st->ws, 256)) return rc;
     hipEvent_t a = pooled_event(), b = pooled_event();
     if (!a || !b) return fail(ANN_ERR_LAUNCH, "cannot create events");
     float ms = 0.f;
-    hipError_t e = launch_mfma_rate(random_operands != 0, st->cus, iters, static_cast<float *>(st->ws), nullptr);   // warm-up
+    hipError_t e = launch_mfma_rate(random_operands != 0, st->cus, iters, static_cast<float *>(st->ws.ptr), nullptr);   // warm-up
     if (e == hipSuccess) e = hipEventRecord(a, nullptr);
-    if (e == hipSuccess) e = launch_mfma_rate(random_operands != 0, st->cus, iters, static_cast<float *>(st->ws), nullptr);
+    if (e == hipSuccess) e = launch_mfma_rate(random_operands != 0, st->cus, iters, static_cast<float *>(st->ws.ptr), nullptr);
     if (e == hipSuccess) e = hipEventRecord(b, nullptr);
     if (e == hipSuccess) e = hipEventSynchronize(b);
     if (e == hipSuccess) e = hipEventElapsedTime(&ms, a, b);
@@ -386,12 +396,12 @@ int ann_release_workspace(void) {
     std::lock_guard<std::mutex> lock(g_mu);
     DeviceState *st = nullptr;
     if (int rc = device_state(&st)) return rc;
-    if (st->ws) (void)hipFree(st->ws);
-    st->ws = nullptr;
-    st->ws_bytes = 0;
-    if (st->vis) (void)hipFree(st->vis);
-    st->vis = nullptr;
-    st->vis_bytes = 0;
+    for (Buffer *b : {&st->ws, &st->vis}) {
+        if (b->ptr) (void)hipFree(b->ptr);
+        *b = Buffer();
+    }
+    for (void *p : st->kept) (void)hipFree(p);
+    st->kept.clear();
     return ANN_OK;
 }
 
@@ -420,12 +430,12 @@ int ann_flat_search_after_typed(const void *corpus, int64_t N, int32_t d, int32_
     const size_t limit = st->user_ws && st->user_bytes < WIDE_WS_MAX ? st->user_bytes : WIDE_WS_MAX;
     hipStream_t s = static_cast<hipStream_t>(stream);
     FlatPlan pl = flat_plan(st->cus, N, d, dtype, B, k, limit);
-    if (!st->user_ws && !at_hand(st, st->ws_bytes, pl.ws_bytes, s)) {         // (captured: in what there is, if that can be)
-        const FlatPlan less = flat_plan(st->cus, N, d, dtype, B, k, st->ws_bytes);
-        if (less.ws_bytes <= st->ws_bytes) pl = less;
+    if (!st->user_ws && !at_hand(st, st->ws, pl.ws_bytes, s)) {         // (captured: in what there is, if that can be)
+        const FlatPlan less = flat_plan(st->cus, N, d, dtype, B, k, st->ws.bytes);
+        if (less.ws_bytes <= st->ws.bytes) pl = less;
     }
     void *ws = nullptr;
-    if (int rc = workspace_for(st, &st->ws, &st->ws_bytes, pl.ws_bytes, &ws)) return rc;
+    if (int rc = workspace_for(st, &st->ws, pl.ws_bytes, s, &ws)) return rc;
     return flat_search_run(pl, corpus, N, d, dtype, queries, B, k, ids, scores, ws, after, s);
 }
 
@@ -478,7 +488,7 @@ static int graph_frontier_run(DeviceState *st, int32_t dtype, int32_t B, Frontie
     if (args.L.vis_mode == FRONTIER_VIS_GLOBAL) {
         args.ns.words = visited_words(args.N);
         void *vis = nullptr;
-        if (int rc = workspace_for(st, &st->vis, &st->vis_bytes, (size_t)B * (size_t)args.ns.words * 4, &vis)) return rc;
+        if (int rc = workspace_for(st, &st->vis, (size_t)B * (size_t)args.ns.words * 4, s, &vis)) return rc;
         args.ns.visited = static_cast<uint32_t *>(vis);
         if (int rc = check_launch("zero_words_kernel", launch_zero_words(args.ns.visited, (size_t)B * (size_t)args.ns.words, s))) return rc;
     }
@@ -493,7 +503,7 @@ static bool frontier_takes(const DeviceState *st, int64_t N, int32_t d, int32_t 
     const int bytes = elem_bytes(dtype);
     *L = frontier_plan(st->cus, N, d, bytes, B, ef, counters, tau);
     const bool pays = frontier_pays(st->cus, d * bytes, R, B, ef, counters, tau, *L);
-    if ((pays ? L->vis_mode == FRONTIER_VIS_GLOBAL : workspace) && !at_hand(st, st->vis_bytes, (size_t)B * (size_t)visited_words(N) * 4, s)) {
+    if ((pays ? L->vis_mode == FRONTIER_VIS_GLOBAL : workspace) && !at_hand(st, st->vis, (size_t)B * (size_t)visited_words(N) * 4, s)) {
         FrontierLds in_lds;
         if (frontier_in_lds(N, d, bytes, R, ef, in_lds)) {
             *L = in_lds;
@@ -542,7 +552,7 @@ int ann_graph_search_nonstall_typed(const void *corpus, int64_t N, int32_t d, in
     if (frontier_takes(st, N, d, dtype, R, B, ef, true, tau, true, s, &F))
         return graph_frontier_run(st, dtype, B, FrontierArgs{corpus, N, d, R, graph, queries, entry, k, ef, ids, scores, F, ns}, true, s);
     void *vis = nullptr;
-    if (int rc = workspace_for(st, &st->vis, &st->vis_bytes, (size_t)B * (size_t)ns.words * 4, &vis)) return rc;
+    if (int rc = workspace_for(st, &st->vis, (size_t)B * (size_t)ns.words * 4, s, &vis)) return rc;
     ns.visited = static_cast<uint32_t *>(vis);
     if (int rc = check_launch("zero_words_kernel", launch_zero_words(ns.visited, (size_t)B * (size_t)ns.words, s)))
         return rc;
@@ -582,7 +592,7 @@ static int graph_search_any(const void *corpus, int64_t N, int32_t d, int32_t dt
     ns.alpha = 0.f;
     ns.words = visited_words(N);
     void *vis = nullptr;
-    if (int rc = workspace_for(st, &st->vis, &st->vis_bytes, (size_t)B * (size_t)ns.words * 4, &vis)) return rc;
+    if (int rc = workspace_for(st, &st->vis, (size_t)B * (size_t)ns.words * 4, s, &vis)) return rc;
     ns.visited = static_cast<uint32_t *>(vis);
     if (int rc = check_launch("zero_words_kernel", launch_zero_words(ns.visited, (size_t)B * (size_t)ns.words, s)))
         return rc;

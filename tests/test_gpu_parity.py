@@ -408,6 +408,41 @@ def test_flat_in_a_small_buffer_of_the_caller(dtype, N, d, B, k, size):
     assert bool((buf[size:] == 0xAB).all()) and bool((buf[:1024] != 0xAB).any())
 
 
+def test_captured_searches_outlive_the_growth_of_the_workspace():
+    """Graphs captured while the library's buffers were small are replayed after larger calls have made them grow: the eager
+    answers, whatever has been put into the memory that a free would have given back."""
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    x, q = torch.randn(60_000, 64, generator=gen, device=DEV).half(), torch.randn(3000, 64, generator=gen, device=DEV).half()
+    near = torch.randint(0, 60_000, (60_000, 8), generator=gen, device=DEV, dtype=torch.int32)
+
+    def flat(B):
+        return ann.ann_flat_search_typed(x, q[:B], 3)
+
+    def walk(B):                                          # 40 slots a node: the visited sets are in memory
+        return ann.ann_graph_search_nonstall_typed(x, wide, 0, q[:B], 3, 24, tau=float("inf"))[:2]
+
+    wide = near.repeat(1, 5).contiguous()
+    ann.ann_release_workspace()
+    want = flat(100) + walk(10)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        got = flat(100) + walk(10)
+    large = flat(3000) + walk(600)
+    torch.cuda.synchronize()
+    for i in range(3):
+        fill = [torch.full((1 << s,), 0x5A, dtype=torch.uint8, device=DEV) for s in range(12, 26)]
+        for t in got:
+            t.fill_(-7)
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want)) and all(bool((f == 0x5A).all()) for f in fill)
+        assert all(torch.equal(a, b) for a, b in zip(flat(3000) + walk(600), large))
+    del g
+    ann.ann_release_workspace()
+    assert all(torch.equal(a, b) for a, b in zip(flat(100) + walk(10), want))
+
+
 def test_flat_corpus_in_parts_in_a_graph():
     """A search in parts through the static entry point, captured and replayed: every replay gives the eager answer for the
     inputs it finds, with eager searches that use the same workspace between the replays."""
