@@ -505,7 +505,7 @@ static bool frontier_takes(const DeviceState *st, int64_t N, int32_t d, int32_t 
     const bool pays = frontier_pays(st->cus, d * bytes, R, B, ef, counters, tau, *L);
     if ((pays ? L->vis_mode == FRONTIER_VIS_GLOBAL : workspace) && !at_hand(st, st->vis, (size_t)B * (size_t)visited_words(N) * 4, s)) {
         FrontierLds in_lds;
-        if (frontier_in_lds(N, d, bytes, R, ef, in_lds)) {
+        if (frontier_in_lds(N, d, bytes, R, ef, counters, in_lds)) {
             *L = in_lds;
             return true;
         }

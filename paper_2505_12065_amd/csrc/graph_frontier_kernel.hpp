@@ -308,7 +308,8 @@ struct FrontierScorer {
     }
 };
 
-template <class T, int NW, int W, int VIS, bool NS, bool QREG, int OCC>
+// TIGHT: see settle, and the end
+template <class T, int NW, int W, int VIS, bool NS, bool QREG, int OCC, bool TIGHT = false>
 __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
     FrontierArgs args) {
     const int64_t N = args.N;
@@ -591,7 +592,8 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
         }
     };
     auto settle = [&] {
-        if (n_exp + n_pool + 128 + W > cap) prune();      // (a step leaves up to 64 + W nodes there, the end another 64)
+        // (a step leaves up to 64 + W nodes there, the end another 64: TIGHT sees to those there)
+        if (n_exp + n_pool + (TIGHT ? 64 : 128) + W > cap) prune();
         if (n_t < LOW && live > 0) refill();
     };
     settle();
@@ -854,6 +856,8 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
         const int k = late()->k;
         int32_t *ids = late()->ids + (size_t)b * k;
         float *scores = late()->scores + (size_t)b * k;
+        if constexpr (TIGHT)
+            if (k > WAVE && n_exp + n_pool + WAVE > cap) prune();         // (no longer than ef with t: room for it)
         barrier();
         uint64_t under = ~0ull;
         for (int j0 = 0; j0 < k; j0 += WAVE) {

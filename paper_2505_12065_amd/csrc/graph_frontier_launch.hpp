@@ -23,8 +23,18 @@ hipError_t launch_frontier_as(int B, const FrontierArgs &args, bool counters, hi
 }
 
 template <class T>
+hipError_t launch_frontier_tight(int B, const FrontierArgs &args, hipStream_t stream) {
+    auto *kernel = graph_frontier_kernel<T, 4, 8, FRONTIER_VIS_LDS, true, true, 2, true>;
+    static size_t big = 0;
+    if (hipError_t e = allow_big_lds(reinterpret_cast<const void *>(kernel), args.L.total, &big)) return e;
+    hipLaunchKernelGGL(kernel, dim3(B), dim3(4 * WAVE), args.L.total, stream, args);
+    return hipGetLastError();
+}
+
+template <class T>
 hipError_t launch_frontier(int B, const FrontierArgs &args, bool counters, hipStream_t stream) {
     const FrontierLds &L = args.L;
+    if (L.tight) return counters ? launch_frontier_tight<T>(B, args, stream) : hipErrorInvalidValue;
     auto wide = [&](auto wc) {
         constexpr int W = decltype(wc)::value;
         return (L.waves == 8 ? launch_frontier_as<T, 8, W, true, 2> : L.per_cu == 3 ? launch_frontier_as<T, 4, W, false, 3>

@@ -555,7 +555,7 @@ inline StepLds graph_step_plan(int cus, int d, int elem_bytes, int B, int ef) {
 // graph_frontier_kernel (graphs of at most 32 slots per node)
 constexpr int FRONTIER_MOST = 63;                         // most neighbours a step scores
 constexpr int FRONTIER_VIS_LDS = 0, FRONTIER_VIS_GLOBAL = 1;              // where the visited set is
-constexpr int FRONTIER_SPARE = 512, FRONTIER_SPARE_MIN = 280;            // places beyond ef, at least; where room is what counts
+constexpr int FRONTIER_SPARE = 512, FRONTIER_SPARE_MIN = 280, FRONTIER_SPARE_TIGHT = 124;   // places beyond ef, at least; where room is what counts; tight
 struct FrontierLds {
     // fixed byte offsets: keys of a step's neighbours (twice), a place to order them in, where they are by hash (twice), counts of
     // the waves, then the scratch of every wave
@@ -565,6 +565,7 @@ struct FrontierLds {
     uint32_t keys, vis, q, total;
     int cap, spare, vis_words, vis_mode;                  // places of the array; how many above ef a bound may leave in it
     int waves, width, per_cu;                             // variant: waves of a workgroup, expansions a step tries, workgroups per compute unit
+    bool tight;                                           // ... that keeps no places for the queue's end
 };
 // A query has a compute unit to itself: 8 waves, which score all neighbours of a step at once.  More queries: 4 waves, two
 // workgroups to a compute unit; beyond what these hold at once three, with the query read from LDS.  200 k x 768, R = 32, ef = 192, us,
@@ -596,7 +597,8 @@ inline bool frontier_layout(int64_t N, int d, int elem_bytes, int ef, int waves,
     const int64_t fit = (room - off) / 8 - ef;
     if (spare > fit) spare = fit < spare_min ? spare_min : fit;
     L.cap = ef + (int)spare;
-    L.spare = (int)spare / 2 - 136;                       // (a bound leaves room for a step and more: see the kernel)
+    L.tight = spare < FRONTIER_SPARE_MIN;
+    L.spare = L.tight ? ((int)spare - 72) / 2 : (int)spare / 2 - 136;     // (a bound leaves room for a step and more: see the kernel)
     L.total = up(off + 8u * (uint32_t)L.cap);
     return (int64_t)L.total <= room;
 }
@@ -611,9 +613,11 @@ inline FrontierLds frontier_plan(int cus, int64_t N, int d, int elem_bytes, int 
     lay(8, 1, L);
     return L;
 }
-// The layout that finds room for the visited set in LDS on the largest graphs; false: too large.
-inline bool frontier_in_lds(int64_t N, int d, int elem_bytes, int R, int ef, FrontierLds &L) {
-    return R <= GRAPH_STEP_MAX_R && frontier_layout(N, d, elem_bytes, ef, 4, 1, 8, FRONTIER_SPARE_MIN, L) && L.vis_mode == FRONTIER_VIS_LDS;
+// The layout that finds room for the visited set in LDS on the largest graphs; false: too large.  (Lists of up to 512 entries left
+// more room when they were written out: with counters, so that the same calls need no workspace, a tight array will do.)
+inline bool frontier_in_lds(int64_t N, int d, int elem_bytes, int R, int ef, bool counters, FrontierLds &L) {
+    auto fits = [&](int spare_min) { return frontier_layout(N, d, elem_bytes, ef, 4, 1, 8, spare_min, L) && L.vis_mode == FRONTIER_VIS_LDS; };
+    return R <= GRAPH_STEP_MAX_R && (fits(FRONTIER_SPARE_MIN) || (counters && fits(FRONTIER_SPARE_TIGHT)));
 }
 
 // Where graph_frontier_kernel is faster than the others (graph_search_kernel, graph_step_kernel, whichever was better), us, others / it:

@@ -88,3 +88,24 @@ def test_graph_frontier_entries_and_nan(ef):
     torch.cuda.synchronize()
     st = stats.cpu().numpy()
     assert np.array_equal(ids.cpu().numpy(), o_ids) and np.array_equal(st[:, 1], n_dist) and np.array_equal(st[:, 2], n_expand)
+
+
+@pytest.mark.parametrize("N,ef,k", [(1_247_200, 256, 7), (1_246_000, 130, 130), (1_240_000, 256, 70)])
+def test_graph_frontier_in_all_of_lds(N, ef, k):
+    """The largest graphs whose visited set fits LDS beside the array, in a buffer that holds none: the array has its fewest
+    places, so that a bound is found in every other step (the first two: none for the queue's end either)."""
+    say(f"frontier, no workspace: N={N} ef={ef} k={k}")
+    x, q, g = _random(N, 8, 16, 8, torch.float16, ef)
+    buf = torch.full((4096,), 0xAB, dtype=torch.uint8, device=DEV)
+    try:
+        ann.ann_set_workspace(buf[:256])
+        ids, _, stats, _ = ann.ann_graph_search_nonstall_typed(x.to(DEV), g.to(DEV), 3, q.to(DEV), k, ef, tau=0.999, window=2_000_000_000)
+        torch.cuda.synchronize()
+    finally:
+        ann.ann_set_workspace(None)
+    assert bool((buf == 0xAB).all())
+    o_ids, _, _, n_dist, n_expand = oracle.graph_search(to_np(x), g.numpy(), 3, to_np(q), k, ef)
+    st = stats.cpu().numpy()
+    # (rows of 8 numbers: scores of the two sides differ by about 1e-7, and nodes that close change places)
+    same = (st[:, 1] == n_dist) & (st[:, 2] == n_expand)
+    assert same.mean() >= 0.75 and (ids.cpu().numpy() == o_ids).mean() >= 0.9 and (st[:, 0] == 0).all()

@@ -18,6 +18,10 @@ using namespace ann;
 extern "C" int step_pays(int cus, int64_t N, int row_bytes, int R, int B, int ef, int counters, float tau) {
     return graph_step_pays(cus, N, row_bytes / 2, 2, R, B, ef, counters != 0, tau);
 }
+extern "C" int in_lds(int64_t N, int d, int elem_bytes, int R, int ef) {
+    FrontierLds L;
+    return frontier_in_lds(N, d, elem_bytes, R, ef, true, L);
+}
 // out: kind (0 lists, 1 direct, 2 matrix cores, 3 streaming with maxima), queries and rows at a time, maxima of a query,
 // log2 of the rows they stand for, offset of the k best so far, workspace, maxima of the smallest last part
 extern "C" void flat(int cus, int64_t N, int d, int dtype, int B, int k, int64_t limit, int64_t *out) {
@@ -50,6 +54,7 @@ def plans(tmp_path_factory):
                     os.path.join(ROOT, "paper_2505_12065_amd", "csrc"), "-o", str(lib), str(src)], check=True)
     L = ctypes.CDLL(str(lib))
     L.step_pays.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 5 + [ctypes.c_float]
+    L.in_lds.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4
     L.flat.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64, ctypes.c_void_p]
     L.static_accepts.argtypes = L.static_kind.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64]
     return L
@@ -248,3 +253,12 @@ def test_the_static_workspace_keeps_the_kernel(plans):
             assert whole == static, (N, d, B, k)
         parts += static == 2 and flat(plans, N, d, 0, B, k, 1 << 30)["bytes"] > STATIC
     assert parts > 20
+
+
+@pytest.mark.parametrize("N,d,elem_bytes,ef", [
+    (1_246_720, 64, 2, 256), (1_246_720, 64, 2, 200), (1_241_088, 416, 2, 117), (1_238_528, 64, 2, 320), (1_223_168, 1024, 2, 257),
+    (1_214_976, 1024, 4, 256), (1_213_952, 64, 2, 512), (1_200_640, 64, 2, 700), (165_888, 1024, 2, 16_384)])
+def test_searches_that_need_no_workspace(plans, N, d, elem_bytes, ef):
+    """The largest graphs whose maturity search keeps its visited set in LDS where no workspace is at hand: the calls that ran
+    with none when lists were written out."""
+    assert plans.in_lds(N, d, elem_bytes, 32, ef)
