@@ -757,9 +757,8 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
             const bool sample = mag < 0x7f800000u;
             const uint64_t samples = __builtin_amdgcn_ballot_w64(sample);
             // the samples side by side: lane p gets the p-th
-            float *row = reinterpret_cast<float *>(ent);
-            row[sample ? rank_in(samples) : 64] = r;
-            const float in_order = row[lane];
+            ent[sample ? rank_in(samples) : 64] = __float_as_int(r);      // (the neighbours are not read any more)
+            const float in_order = __int_as_float(ent[lane]);
             // Most steps cannot take the average past tau whatever the order of their samples: then it is brought up to date
             // while the next adjacency rows are on their way.
             n_due = __builtin_popcountll(samples);
