@@ -578,7 +578,7 @@ static int graph_search_any(const void *corpus, int64_t N, int32_t d, int32_t dt
     FrontierLds F;
     if (frontier_takes(st, N, d, dtype, R, B, ef, false, INFINITY, L.two_level, s, &F))
         return graph_frontier_run(st, dtype, B, FrontierArgs{corpus, N, d, R, graph, queries, entry, k, ef, ids, scores, F, ns}, false, s);
-    if (ef <= GRAPH_EF_TWO_LEVEL && graph_step_pays(st->cus, N, d, elem_bytes(dtype), R, B, ef, false, INFINITY)) {
+    if (graph_step_pays(st->cus, N, d * elem_bytes(dtype), R, B, ef)) {
         const StepLds S = graph_step_plan(st->cus, d, elem_bytes(dtype), B, ef);
         TimedScope timed(ANN_KERNEL_GRAPH, s);
         return check_launch("graph_step_kernel", launch_graph_step(dtype, corpus, N, d, graph, R, entry, entries, n_entries, queries, B, k,

@@ -653,53 +653,25 @@ inline bool frontier_pays(int cus, int row_bytes, int R, int B, int ef, bool cou
     return ef >= (B > 2 * cus ? 96 : R <= 24 ? 128 : 200);
 }
 
-// Where graph_step_kernel is faster than graph_search_kernel, among the calls that graph_frontier_kernel does not take: today
-// those with lists of up to 512 entries on graphs whose visited set does not fit LDS.  (Lists over 512 and the maturity exit are
-// all measured here, but graph_frontier_kernel is faster than both there.)  A step costs two to three expansions of the
+// Where graph_step_kernel is faster than graph_search_kernel, among the calls that graph_frontier_kernel does not take: lists of
+// up to 512 entries without counters on graphs whose visited set does not fit LDS beside them.  A step costs two to three expansions of the
 // other kernel, so what decides is how many expansions it commits: the neighbours a step holds (63 for a batch that leaves
 // every query a compute unit, else 32) against the unseen ones that an expansion brings.  Those get fewer as a search covers
 // more of the graph, so the line runs along N / ef, the nodes of the graph per entry of the list, and lies higher for narrow
-// graphs, for short rows (a step scores two to three rows for every one it keeps) and for batches that wait for a place
-// anyway (the mean over the queries counts there, not the slowest).  Time of the one-by-one loop / time in steps over
-// 2400 points (N 20 k to 2 M, d 64 to 1024, R 8 to 32, B 1 to 4096, ef 192 to 16384, all types):
-//   lists over 512, R = 32, 1.5 KB rows, B = 256 / 512: 50 k, ef = 1024 1.19 / 1.30; 200 k 0.93 / 0.95, ef = 2048 1.07 / 1.15,
-//     8192 1.56 / 1.62; 1 M, ef = 1024 0.80 / 0.71, 2048 0.85 / 0.78, 4096 0.86 / 0.90, 8192 0.96 / 1.05.  The two sides meet at
-//     N / ef = 140 to 180; 180 to 250 with rows of up to 1 KB, over 400 with 128 bytes; 1.5 and 8 times that for R = 24 and 16
-//     with B = 512, 1.6 and up with B = 800
-//   one list, more queries than two workgroups per compute unit hold, R = 32: 60 k, ef = 192 to 512, B = 600 1.3 to 1.5; 200 k 1.0 to
-//     1.2; 1 M 0.96 to 1.08; about two full rounds of places (B = 800 to 1100) gain least: 60 k 0.97 to 1.2, 200 k 0.89 to 1.05,
-//     1 M 0.78 to 0.84; B = 2048 200 k 1.05 to 1.43, 1 M 0.71 to 1.0.  R = 16: 1.0 to 2.1 at any of these N
-//   up to two queries 1.0 to 4.4 (0.8 at worst: it depends on the query); four: 60 k, ef = 320 1.05, 200 k 0.90 (R = 16, long
-//     lists, 800 k: 1.0 to 1.6)
-//   maturity exit (tau < 1: most queries stop while their list fills, and a filling list commits whole steps): 1.05 to 2.1
-//     at any N up to 1 M with lists of 96 up and some queries per call; 0.65 to 0.95 for one to four queries or shorter
-//     lists (over before the steps pay), and 0.6 to 1.05 where no average reaches tau and every search runs to its end
-// And a step's layout of a long list takes some 1.5 KB more than the other kernel's, so there are lengths (8700 to 9100 with
-// 1.5 KB rows) that leave two workgroups of the one a compute unit and one of the other.  ef = 9000, B = 512 (against the
-// same at 8192): 50 k 1.42 (2.29), 200 k 0.99 (1.63), 500 k 0.76 (1.25), 1 M 0.66 (1.05); B = 300 as elsewhere; with the
-// maturity exit 1.0 to 1.2 still.
-inline bool graph_step_pays(int cus, int64_t N, int d, int elem_bytes, int R, int B, int ef, bool counters, float tau) {
-    if (R > GRAPH_STEP_MAX_R) return false;
-    const int row_bytes = d * elem_bytes;
-    if (counters) return tau < 1.0f && R >= 16 && ef >= 96 && B >= 8 && (int64_t)B * ef >= 2048;
-    int64_t reach = row_bytes <= 256 ? 448 : row_bytes <= 1024 ? 240 : 160;     // nodes per list entry up to which steps pay
-    const bool long_list = ef > GRAPH_EF_TWO_LEVEL, waits = B > 2 * cus;
-    if (B <= 4) {
-        if (ef < 320 || (!long_list && row_bytes > 2048)) return false;
-        if (B <= 2) return true;
-        reach *= long_list && R <= 16 ? 8 : 2;
-    } else if (long_list) {
-        if (B > cus) reach *= R <= 16 ? 8 : 1;
-        if (B > cus && R > 16) reach = reach * (R <= 24 ? (waits ? 30 : 15) : (waits ? 16 : 10)) / 10;
-        const int64_t step_bytes = 7888 + (ef + 63) / 64 * 8 + 8 * (int64_t)ef + (int64_t)row_bytes;
-        if (2 * B > 3 * cus && graph_lds_layout(d, elem_bytes, R, ef).total <= LDS_MAX / 2 && step_bytes > (int64_t)LDS_MAX / 2) reach /= 8;
-    } else {
-        if (!waits || ef < 192) return false;
-        if (R <= 16) return true;
-        const bool two_rounds = B >= 3 * cus && 2 * B <= 9 * cus;
-        reach = two_rounds ? (R <= 24 ? 800 : 400) : R <= 24 ? 3000 : B > GRAPH_DENSE_MIN_B ? 1024 : 1600;
-    }
-    return ef * reach >= N;
+// graphs and for batches that wait for a place anyway (the mean over the queries counts there, not the slowest).  Time of the
+// one-by-one loop / time in steps:
+//   more queries than two workgroups per compute unit hold, R = 32: 200 k, ef = 192 to 512, B = 600 1.0 to 1.2; 1 M 0.96 to 1.08; about
+//     two full rounds of places (B = 800 to 1100) gain least: 200 k 0.89 to 1.05, 1 M 0.78 to 0.84; B = 2048 200 k 1.05 to 1.43,
+//     1 M 0.71 to 1.0.  R = 16: 1.0 to 2.1 at any of these N
+//   up to two queries 1.0 to 4.4 (0.8 at worst: it depends on the query); rows of more than 2 KB not
+inline bool graph_step_pays(int cus, int64_t N, int row_bytes, int R, int B, int ef) {
+    if (R > GRAPH_STEP_MAX_R || ef > GRAPH_EF_TWO_LEVEL) return false;
+    if (B <= 2) return ef >= 320 && row_bytes <= 2048;
+    if (B <= 2 * cus || ef < 192) return false;
+    if (R <= 16) return true;
+    const bool two_rounds = B >= 3 * cus && 2 * B <= 9 * cus;
+    const int64_t reach = two_rounds ? (R <= 24 ? 800 : 400) : R <= 24 ? 3000 : B > GRAPH_DENSE_MIN_B ? 1024 : 1600;
+    return ef * reach >= N;                               // nodes per list entry up to which steps pay
 }
 
 }  // namespace ann

@@ -15,8 +15,22 @@ CUS = 256
 SHIM = r"""
 #include "plan.hpp"
 using namespace ann;
-extern "C" int step_pays(int cus, int64_t N, int row_bytes, int R, int B, int ef, int counters, float tau) {
-    return graph_step_pays(cus, N, row_bytes / 2, 2, R, B, ef, counters != 0, tau);
+// 0 graph_search_kernel, 1 graph_frontier_kernel, 2 graph_step_kernel (all workspace at hand)
+extern "C" int graph_kernel(int cus, int64_t N, int row_bytes, int R, int B, int ef, int counters, float tau) {
+    const FrontierLds L = frontier_plan(cus, N, row_bytes / 2, 2, B, ef, counters != 0, tau);
+    if (frontier_pays(cus, row_bytes, R, B, ef, counters != 0, tau, L)) return 1;
+    return !counters && graph_step_pays(cus, N, row_bytes, R, B, ef) ? 2 : 0;
+}
+// tight: frontier_in_lds's layout instead of the call's; out: fits, waves, workgroups per compute unit, expansions a step tries, tight,
+// visited set in LDS, its words, the query's, visited set's and array's places, places of the array, those a bound may leave, LDS bytes
+extern "C" void frontier(int cus, int64_t N, int row_bytes, int B, int ef, int counters, float tau, int in_lds, int64_t *out) {
+    FrontierLds L;
+    bool fits = true;
+    if (in_lds) fits = frontier_in_lds(N, row_bytes / 2, 2, 32, ef, counters != 0, L);
+    else L = frontier_plan(cus, N, row_bytes / 2, 2, B, ef, counters != 0, tau);
+    const int64_t v[] = {fits, L.waves, L.per_cu, L.width, L.tight, L.vis_mode == FRONTIER_VIS_LDS, L.vis_words, L.q, L.vis, L.keys, L.cap,
+                         L.spare, L.total, (int64_t)FrontierLds::WAVES + L.waves * FrontierLds::WAVE_BYTES};
+    for (int i = 0; i < 14; ++i) out[i] = v[i];
 }
 extern "C" int in_lds(int64_t N, int d, int elem_bytes, int R, int ef) {
     FrontierLds L;
@@ -53,7 +67,8 @@ def plans(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I",
                     os.path.join(ROOT, "paper_2505_12065_amd", "csrc"), "-o", str(lib), str(src)], check=True)
     L = ctypes.CDLL(str(lib))
-    L.step_pays.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 5 + [ctypes.c_float]
+    L.graph_kernel.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 5 + [ctypes.c_float]
+    L.frontier.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_float, ctypes.c_int, ctypes.c_void_p]
     L.in_lds.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4
     L.flat.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64, ctypes.c_void_p]
     L.static_accepts.argtypes = L.static_kind.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64]
@@ -66,45 +81,87 @@ def flat(L, N, d, dtype, B, k, limit):
     return dict(zip(("kind", "part", "rows", "n", "gs_log", "best_ofs", "bytes", "last_n", "last_gs_log"), out))
 
 
-# one-by-one / steps as measured, where the two sides differ by more than a tenth
-@pytest.mark.parametrize("N,row,R,B,ef,pays", [
-    (1_000_000, 1536, 32, 512, 1024, False),     # 0.68 .. 0.71: the corpus of the benchmark, mid search ranges
-    (1_000_000, 1536, 32, 512, 2048, False),     # 0.75
-    (1_000_000, 1536, 32, 512, 4096, False),     # 0.87
-    (1_000_000, 1536, 32, 512, 12288, True),     # 1.13
-    (1_000_000, 1536, 32, 256, 1024, False),     # 0.80: here the visited bits fit LDS
-    (1_000_000, 768, 32, 512, 1024, False),      # 0.70
-    (1_000_000, 1024, 32, 256, 600, False),      # 0.79
-    (200_000, 1536, 32, 256, 2048, True),        # 1.07
-    (200_000, 1536, 32, 512, 4096, True),        # 1.36
-    (200_000, 768, 32, 256, 600, False),         # 0.90
-    (50_000, 1536, 32, 256, 1024, True),         # 1.19
-    (200_000, 1536, 16, 512, 1024, True),        # 1.15
-    (1_000_000, 1536, 32, 2048, 192, False),     # 0.77: one list, more queries than places
-    (1_000_000, 1536, 32, 1024, 512, False),     # 0.77
-    (400_000, 1536, 32, 2048, 192, False),       # 0.79
-    (200_000, 768, 32, 600, 320, True),          # 1.25
-    (200_000, 1536, 32, 4, 320, False),          # 0.90
-    (1_000_000, 1536, 32, 1, 512, True),         # 2.97
-    (1_000_000, 1536, 32, 512, 64, False),
-    (1_000_000, 1536, 32, 512, 9000, False),     # 0.66: two workgroups per compute unit one by one, one in steps
-    (50_000, 1536, 32, 512, 9000, True),         # 1.42
-    (1_000_000, 1536, 32, 512, 10_000, True),    # 1.18: one and one
-    (1_000_000, 1536, 32, 512, 8192, True),      # 1.05: two and two
+SEARCH, FRONTIER, STEP = 0, 1, 2
+NEVER = float("inf")                                  # no average passes it
+
+
+# us, or the ratio, of the others (graph_search_kernel, graph_step_kernel) / graph_frontier_kernel, or one by one / in steps
+@pytest.mark.parametrize("N,row,R,B,ef,tau,kernel", [
+    (200_000, 1536, 32, 256, 48, None, FRONTIER),         # 198 / 174
+    (200_000, 1536, 32, 1, 768, None, FRONTIER),          # 1916 / 558
+    (200_000, 1536, 32, 256, 3, None, SEARCH),            # 30.4 / 35.8
+    (200_000, 4096, 32, 256, 16, None, SEARCH),           # 134 / 156
+    (200_000, 1536, 32, 512, 48, None, SEARCH),           # 217 / 257
+    (200_000, 1536, 32, 512, 384, None, FRONTIER),        # 1264 / 1041
+    (200_000, 1536, 16, 512, 96, None, FRONTIER),         # 362 / 304
+    (200_000, 1536, 24, 512, 64, None, SEARCH),           # 253 / 284
+    (200_000, 1536, 32, 2048, 192, None, FRONTIER),       # 2074 / 1726
+    (1_000_000, 1536, 32, 512, 64, None, SEARCH),         # the corpus of the benchmark
+    (1_000_000, 1536, 32, 512, 600, None, SEARCH),        # 2215 / 2516
+    (1_000_000, 1536, 32, 512, 2048, None, FRONTIER),     # 6959 / 6364
+    (1_000_000, 1536, 32, 512, 8192, None, FRONTIER),     # 24.1 / 19.4 ms
+    (1_000_000, 1536, 24, 512, 600, None, FRONTIER),      # 2086 / 1983
+    (1_000_000, 1536, 32, 256, 8192, None, FRONTIER),     # 22 838 / 12 592
+    (1_000_000, 1536, 32, 2048, 192, None, SEARCH),       # 0.77 one by one against steps: one list, more queries than places
+    (1_000_000, 1536, 32, 1024, 512, None, SEARCH),       # 0.77
+    (800_000, 1536, 32, 600, 512, None, STEP),            # 1.0 to 1.08
+    (1_500_000, 1536, 16, 600, 256, None, STEP),          # 1.0 to 2.1
+    (1_500_000, 1536, 32, 1, 512, None, STEP),            # 2.97
+    (1_500_000, 1536, 32, 4, 512, None, SEARCH),
+    (200_000, 1536, 40, 512, 512, None, SEARCH),          # wide graphs
+    (200_000, 768, 32, 256, 32, 0.9, FRONTIER),           # 103 / 94
+    (200_000, 768, 32, 256, 256, 0.9, FRONTIER),          # 326 / 249
+    (200_000, 768, 16, 256, 32, 0.9, SEARCH),             # 106 / 128
+    (200_000, 768, 16, 1024, 64, 0.9, SEARCH),            # 339 / 352
+    (200_000, 768, 32, 256, 64, NEVER, SEARCH),           # 318 / 319
+    (200_000, 768, 32, 512, 256, NEVER, SEARCH),          # 1036 / 1137
+    (200_000, 768, 32, 512, 512, NEVER, FRONTIER),        # 2032 / 1891
+    (500_000, 256, 32, 64, 128, NEVER, SEARCH),           # 600 / 630
+    (1_000_000, 512, 32, 512, 2048, NEVER, SEARCH),       # 7438 / 8428: visited sets in memory, two workgroups a compute unit
+    (1_000_000, 512, 32, 1024, 1024, NEVER, FRONTIER),    # 7648 / 7185
 ])
-def test_steps_only_where_they_were_measured_to_pay(plans, N, row, R, B, ef, pays):
-    assert bool(plans.step_pays(CUS, N, row, R, B, ef, 0, float("inf"))) == pays
+def test_graph_kernels_where_they_were_measured_to_pay(plans, N, row, R, B, ef, tau, kernel):
+    assert plans.graph_kernel(CUS, N, row, R, B, ef, tau is not None, NEVER if tau is None else tau) == kernel
 
 
 def test_steps_pay_up_to_a_size_of_the_graph(plans):
-    """Whatever the other sizes are: never again on a larger graph once they no longer do."""
+    """Lists of up to 512 entries without counters go from graph_frontier_kernel to steps to one by one as the graph grows, never back."""
+    order = {FRONTIER: 0, STEP: 1, SEARCH: 2}
     for row in (128, 768, 1536, 4096):
         for R in (8, 24, 32):
             for B in (1, 4, 16, 256, 257, 512, 513, 800, 1024, 2048):
-                for ef in (64, 192, 320, 512, 513, 1024, 4096, 16384):
-                    got = [bool(plans.step_pays(CUS, N, row, R, B, ef, 0, float("inf"))) for N in
-                           (100, 10_000, 50_000, 200_000, 1_000_000, 10_000_000, 2**31 - 1)]
-                    assert got == sorted(got, reverse=True), (row, R, B, ef)
+                for ef in (192, 320, 512):
+                    got = [order[plans.graph_kernel(CUS, N, row, R, B, ef, 0, NEVER)] for N in
+                           (400_000, 1_300_000, 4_000_000, 10_000_000, 100_000_000, 2**31 - 1)]
+                    assert got == sorted(got), (row, R, B, ef, got)
+
+
+@pytest.mark.parametrize("in_lds", [0, 1])
+def test_frontier_layouts(plans, in_lds):
+    """Whatever graph_frontier_kernel is launched with: regions one behind the other inside the share of the compute unit's LDS,
+    a bit for every node, and room for what a step adds to a bound's leavings and for the queue's end (tight: not for that)."""
+    rng = random.Random(in_lds)
+    log = lambda lo, hi: int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+    seen = set()
+    out = (ctypes.c_int64 * 14)()
+    for _ in range(60_000):
+        N, row, B, ef = log(1, 2**31 - 1), 16 * log(1, 1024), log(1, 5000), log(1, 16_384)
+        if rng.random() < 0.5:
+            N = rng.randint(100_000, 1_260_000)
+        counters, tau = rng.randint(0, 1), rng.choice([0.9, NEVER])
+        plans.frontier(CUS, N, row, B, ef, counters, tau, in_lds, out)
+        fits, waves, per_cu, width, tight, bits, words, q, vis, keys, cap, spare, total, scratch = out
+        call = (N, row, B, ef, counters, tau, list(out))
+        if not fits or (not in_lds and not plans.graph_kernel(CUS, N, row, 32, B, ef, counters, tau) == FRONTIER):
+            continue
+        assert (waves, per_cu) in ((8, 1), (4, 1), (4, 2), (4, 3)) and width in (4, 8), call
+        assert total <= 160 * 1024 // per_cu and scratch <= q and q + row <= vis and vis + 4 * words <= keys and keys + 8 * cap <= total, call
+        assert not any(x % 16 for x in (q, vis, keys, total)), call
+        assert 32 * words >= N if bits else words == 0 and not in_lds, call
+        assert spare >= 0 and ef + spare + 64 + width + (0 if tight else 64) <= cap, call
+        assert not tight or (in_lds and counters), call
+        seen.add((waves, per_cu, width, tight, bits))
+    assert len(seen) >= (2 if in_lds else 7), seen
 
 
 @pytest.mark.parametrize("N,d,dtype,B,k", [
