@@ -67,14 +67,16 @@ def test_other_kernel_where_the_workspace_is_short(N, d, B, k, size):
     assert ann.ann_flat_workspace_bytes(N, d, torch.float16, B, k) > size
     want = ann.ann_flat_search_typed(x, q, k)
     ids, sc = torch.empty_like(want[0]), torch.empty_like(want[1])
+    buf = torch.full((size + 4096,), 0xAB, dtype=torch.uint8, device=DEV)    # (the library keeps its address only)
     torch.cuda.synchronize()
     try:
-        ann.ann_set_workspace(torch.empty(size, dtype=torch.uint8, device=DEV))
+        ann.ann_set_workspace(buf[:size])
         got = ann.ann_flat_search_typed(x, q, k)
         torch.cuda.synchronize()
     finally:
         ann.ann_set_workspace(None)
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    assert bool((buf[size:] == 0xAB).all()) and bool((buf[:size] != 0xAB).any())
     ann.ann_release_workspace()
     few = ann.ann_flat_search_typed(x[:1_000], q, k)                         # (the buffer has room for this and stays)
     assert 2 * ann.ann_flat_workspace_bytes(1_000, d, torch.float16, B, k) < ann.ann_flat_workspace_bytes(N, d, torch.float16, B, k)
