@@ -34,12 +34,16 @@ __device__ __forceinline__ int64_t wide_row(int64_t slot) {
 // eight reads at a time, and gathering by a thread's mask of hits instead of a test and an atomic for each maximum.  us, before / now:
 // 77 queries x 7716 maxima, 160 rows of 1552 bytes 17.0 / 12.7; 128 x 18 k, 320 rows of 768 20.8 / 13.3; 64 x 31 k, 320 rows of 3072
 // 52 / 33; 512 x 15 k, 192 rows of 1536 41.8 / 34.2; single rows 5000 x 1024, k = 16 9.8 / 8.2, 512 x 1024, k = 1 4.7 / 4.0.
+// RUNS (pick_runs): the long runs and held operands, 92 registers.  Shorter rows have none, and many queries want waves more than
+// runs: 12 steps at a time, 64 registers.  us of the kernel, with / without: 11 212 x 48, B = 2765, k = 10 41.2 / 24.3; 48 434 x 128, B = 4007
+// 71.0 / 45.6; 219 465 x 32, B = 514, k = 16 28.4 / 18.2; 16 000 x 1024, B = 4000, k = 10 69.7 / 62.3; but 123 457 x 776, B = 77 8.6 / 12.0, 512
+// 14.9 / 16.5; 60 000 x 768, B = 1000, k = 3 17.6 / 19.7; 30 000 x 1544, B = 4000 59.0 / 67.4.
 // PARTS: a search that takes the corpus in parts (sh.X and sh.N are the part, after.base its first row) goes on from the k
 // best of the parts before, which also bound what is worth looking at: best_so_far [B, k], read where `more` has bit 0;
 // the result goes back there where it has bit 1, else to ids and scores.  (A variant of its own: the calls of a few
 // microseconds do not wait for two more arguments.)
 constexpr int PICK_CAP = 512;
-template <class T, int WMF, bool ONE, bool PARTS>
+template <class T, int WMF, bool ONE, bool PARTS, bool RUNS>
 __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict__ maxima, int64_t n, int gs_log, int k,
                                                         int32_t *__restrict__ ids, float *__restrict__ scores, StreamShape sh,
                                                         After after, uint64_t *__restrict__ best_so_far, int more) {
@@ -188,39 +192,42 @@ __global__ __launch_bounds__(512) void flat_pick_kernel(const float *__restrict_
                 int col, at;                          // this lane's column, and which of the rows it looks after
                 auto run = [&](auto &&product) {
                     int s0 = 0;
-                    for (; CHUNKS * (s0 + RUN) <= nch; s0 += RUN) {
-                        const char *p = rp + (CHUNKS * s0 + sub) * 16;
-                        const u4 *yp = qs + CHUNKS * s0 + sub;
-                        u4 x[RUN];
+                    if constexpr (RUNS) {
+                        for (; CHUNKS * (s0 + RUN) <= nch; s0 += RUN) {
+                            const char *p = rp + (CHUNKS * s0 + sub) * 16;
+                            const u4 *yp = qs + CHUNKS * s0 + sub;
+                            u4 x[RUN];
 #pragma unroll
-                        for (int s = 0; s < RUN; ++s) x[s] = load_chunk(p + CHUNKS * s * 16);
+                            for (int s = 0; s < RUN; ++s) x[s] = load_chunk(p + CHUNKS * s * 16);
 #pragma unroll
-                        for (int g = 0; g < RUN; g += PART) {
-                            u4 y[PART];
+                            for (int g = 0; g < RUN; g += PART) {
+                                u4 y[PART];
 #pragma unroll
-                            for (int s = 0; s < PART; ++s) y[s] = yp[CHUNKS * (g + s)];
-                            __builtin_amdgcn_sched_barrier(0);
+                                for (int s = 0; s < PART; ++s) y[s] = yp[CHUNKS * (g + s)];
+                                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                            for (int s = 0; s < PART; ++s) product(s & 3, x[g + s], y[s]);
+                                for (int s = 0; s < PART; ++s) product(s & 3, x[g + s], y[s]);
+                            }
                         }
                     }
                     for (; s0 < steps; s0 += TAIL) {
                         u4 x[TAIL], y[TAIL];
 #pragma unroll
                         for (int s = 0; s < TAIL; ++s) {
-                            x[s] = y[s] = zero_chunk();
+                            x[s] = zero_chunk();
+                            if (RUNS) y[s] = zero_chunk();
                             if (s0 + s < steps) {
                                 const int ch = min(CHUNKS * (s0 + s) + sub, nch - 1);
                                 x[s] = load_chunk(rp + ch * 16);
-                                y[s] = qs[ch];
+                                if (RUNS) y[s] = qs[ch];
                             }
                         }
-                        __builtin_amdgcn_sched_barrier(0);
+                        if (RUNS) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                         for (int s = 0; s < TAIL; ++s)
                             if (s0 + s < steps) {
-                                const bool inside = CHUNKS * (s0 + s) + sub < nch;
-                                product(s & 3, mask_tail(x[s], inside), mask_tail(y[s], inside));
+                                const int ch = CHUNKS * (s0 + s) + sub;
+                                product(s & 3, mask_tail(x[s], ch < nch), mask_tail(RUNS ? y[s] : qs[min(ch, nch - 1)], ch < nch));
                             }
                     }
                 };

@@ -48,11 +48,16 @@ hipError_t pick(const WidePlan &pl, const void *X, int64_t N, int d, const void 
                            best, more);
         return hipGetLastError();
     };
+    auto form = [&](auto pc, auto rc) {
+        constexpr bool P = decltype(pc)::value, R = decltype(rc)::value;
+        if constexpr (T::bytes == 4) return go(flat_pick_kernel<T, 0, false, P, R>);
+        else return pl.wmf == 4 ? go(flat_pick_kernel<T, 4, false, P, R>) : pl.wmf == 2 ? go(flat_pick_kernel<T, 2, false, P, R>) : go(flat_pick_kernel<T, 1, false, P, R>);
+    };
     auto parts = [&](auto pc) {
         constexpr bool P = decltype(pc)::value;
-        if constexpr (T::bytes == 4) return go(flat_pick_kernel<T, 0, false, P>);
-        else if (one) return pl.wmf == 4 ? go(flat_pick_kernel<T, 4, true, P>) : pl.wmf == 2 ? go(flat_pick_kernel<T, 2, true, P>) : go(flat_pick_kernel<T, 1, true, P>);
-        else return pl.wmf == 4 ? go(flat_pick_kernel<T, 4, false, P>) : pl.wmf == 2 ? go(flat_pick_kernel<T, 2, false, P>) : go(flat_pick_kernel<T, 1, false, P>);
+        if constexpr (T::bytes == 2)
+            if (one) return pl.wmf == 4 ? go(flat_pick_kernel<T, 4, true, P, false>) : pl.wmf == 2 ? go(flat_pick_kernel<T, 2, true, P, false>) : go(flat_pick_kernel<T, 1, true, P, false>);
+        return pick_runs(pl.cus, (size_t)d * T::bytes, T::bytes == 4 ? 64 : 32, B) ? form(pc, std::true_type{}) : form(pc, std::false_type{});
     };
     return more ? parts(std::true_type{}) : parts(std::false_type{});
 }

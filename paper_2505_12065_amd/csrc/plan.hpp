@@ -158,6 +158,12 @@ inline StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int K
 // Maxima of a query, one of 2^g rows: N is a whole number of tiles (wmf > 0), or any number, and there are a multiple of 4.
 inline int64_t maxima_of(int wmf, int64_t N, int g) { return wmf > 0 ? N >> g : (((N - 1) >> g) + 1 + 3) & ~(int64_t)3; }
 
+// Whether flat_pick_kernel takes rows of so many bytes in runs of 24 steps (both sides measured there).
+inline bool pick_runs(int cus, size_t row_bytes, size_t step_bytes, int B) {
+    const size_t steps = row_bytes / step_bytes;
+    return steps >= 24 && (B <= 6 * cus || steps >= 96);
+}
+
 // Rows per group of the matrix-core kernel, by the time of what follows the products, in us: 4 bytes of maxima are written
 // in small pieces and read again, at 1.3 TB/s over all queries, the rows of k groups are read at 5 TB/s; one query alone waits
 // for its maxima (twice, 1024 a wave at a time) and, unless groups are single rows, for its rows (32 a wave, 24 steps of 32 bytes

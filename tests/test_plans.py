@@ -36,6 +36,7 @@ extern "C" int in_lds(int64_t N, int d, int elem_bytes, int R, int ef) {
     FrontierLds L;
     return frontier_in_lds(N, d, elem_bytes, R, ef, true, L);
 }
+extern "C" int runs(int cus, int d, int elem_bytes, int B) { return pick_runs(cus, (size_t)d * elem_bytes, 16 * elem_bytes, B); }
 // out: kind (0 lists, 1 direct, 2 matrix cores, 3 streaming with maxima), queries and rows at a time, maxima of a query,
 // log2 of the rows they stand for, offset of the k best so far, workspace, maxima of the smallest last part
 extern "C" void flat(int cus, int64_t N, int d, int dtype, int B, int k, int64_t limit, int64_t *out) {
@@ -319,3 +320,20 @@ def test_searches_that_need_no_workspace(plans, N, d, elem_bytes, ef):
     """The largest graphs whose maturity search keeps its visited set in LDS where no workspace is at hand: the calls that ran
     with none when lists were written out."""
     assert plans.in_lds(N, d, elem_bytes, 32, ef)
+
+
+# us of flat_pick_kernel with long runs of steps / without
+@pytest.mark.parametrize("d,elem_bytes,B,runs", [
+    (48, 2, 2765, False),        # 41.2 / 24.3
+    (32, 2, 514, False),         # 28.4 / 18.2
+    (320, 2, 3989, False),       # 30.5 / 20.7
+    (376, 2, 77, False),         # 23 steps and a half
+    (384, 2, 77, True),          # 9.1 / 10.5
+    (776, 2, 512, True),         # 14.9 / 16.5
+    (1024, 2, 4000, False),      # 69.7 / 62.3
+    (768, 2, 4000, False),       # 125.9 / 108.9
+    (1544, 2, 4000, True),       # 59.0 / 67.4
+    (392, 4, 400, True),         # 20.1 / 21.9
+    (128, 4, 300, False)])
+def test_long_runs_where_they_were_measured_to_pay(plans, d, elem_bytes, B, runs):
+    assert bool(plans.runs(CUS, d, elem_bytes, B)) == runs
