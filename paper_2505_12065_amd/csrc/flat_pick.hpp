@@ -37,7 +37,8 @@ __device__ __forceinline__ int64_t wide_row(int64_t slot) {
 // RUNS (pick_runs): the long runs and held operands, 92 registers.  Shorter rows have none, and many queries want waves more than
 // runs: 12 steps at a time, 64 registers.  us of the kernel, with / without: 11 212 x 48, B = 2765, k = 10 41.2 / 24.3; 48 434 x 128, B = 4007
 // 71.0 / 45.6; 219 465 x 32, B = 514, k = 16 28.4 / 18.2; 16 000 x 1024, B = 4000, k = 10 69.7 / 62.3; but 123 457 x 776, B = 77 8.6 / 12.0, 512
-// 14.9 / 16.5; 60 000 x 768, B = 1000, k = 3 17.6 / 19.7; 30 000 x 1544, B = 4000 59.0 / 67.4.
+// 14.9 / 16.5; 10 953 x 544, B = 900 / 1100 10.3 / 12.2, 16.3 / 14.0; 16 000 x 1024, B = 900 / 1100 13.3 / 16.5, 20.7 / 18.4; 9000 x 1152, B = 1531
+// 19.7 / 20.5; 30 000 x 1544, B = 4000 59.0 / 67.4.
 // PARTS: a search that takes the corpus in parts (sh.X and sh.N are the part, after.base its first row) goes on from the k
 // best of the parts before, which also bound what is worth looking at: best_so_far [B, k], read where `more` has bit 0;
 // the result goes back there where it has bit 1, else to ids and scores.  (A variant of its own: the calls of a few

@@ -161,7 +161,7 @@ inline int64_t maxima_of(int wmf, int64_t N, int g) { return wmf > 0 ? N >> g : 
 // Whether flat_pick_kernel takes rows of so many bytes in runs of 24 steps (both sides measured there).
 inline bool pick_runs(int cus, size_t row_bytes, size_t step_bytes, int B) {
     const size_t steps = row_bytes / step_bytes;
-    return steps >= 24 && (B <= 6 * cus || steps >= 96);
+    return steps >= 24 && (B <= 4 * cus || steps >= 72);
 }
 
 // Rows per group of the matrix-core kernel, by the time of what follows the products, in us: 4 bytes of maxima are written

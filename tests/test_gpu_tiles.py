@@ -31,8 +31,8 @@ DEV = "cuda"
     (torch.bfloat16, 131_072, 96, 16, 16),     # ...
     (torch.bfloat16, 60_000, 1_160, 300, 9),   # rows scored once more: three long runs of steps and a last one of half a step
     (torch.float32, 40_000, 392, 400, 3),      # ... fp32, one long run and half a step
-    (torch.float16, 3_000, 776, 1_537, 9),     # ... more queries than long runs pay for
-    (torch.float16, 3_000, 1_544, 1_537, 9),   # ... for rows of up to 95 steps
+    (torch.float16, 3_000, 776, 1_025, 9),     # ... more queries than long runs pay for
+    (torch.float16, 3_000, 1_160, 1_025, 9),   # ... for rows of up to 71 steps
     (torch.bfloat16, 30_000, 376, 100, 16),    # ... a step and a half less than a long run
 ])
 def test_line_stages(dtype, N, d, B, k):

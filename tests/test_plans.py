@@ -331,6 +331,9 @@ def test_searches_that_need_no_workspace(plans, N, d, elem_bytes, ef):
     (384, 2, 77, True),          # 9.1 / 10.5
     (776, 2, 512, True),         # 14.9 / 16.5
     (1024, 2, 4000, False),      # 69.7 / 62.3
+    (544, 2, 900, True),         # 10.3 / 12.2
+    (544, 2, 1100, False),       # 16.3 / 14.0
+    (1152, 2, 1531, True),       # 19.7 / 20.5
     (768, 2, 4000, False),       # 125.9 / 108.9
     (1544, 2, 4000, True),       # 59.0 / 67.4
     (392, 4, 400, True),         # 20.1 / 21.9
