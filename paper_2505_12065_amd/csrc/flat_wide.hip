@@ -37,11 +37,8 @@ template <class T>
 hipError_t pick(const WidePlan &pl, const void *X, int64_t N, int d, const void *Q, int B, int k, const float *maxima,
                 int32_t *ids, float *scores, After after, uint64_t *best, int more, hipStream_t stream) {
     const StreamShape sh{X, Q, N, d, B};
-    // a wave for one-row groups of a small corpus; else a wave per 32 rows to score and per 4096 maxima, two at least;
-    // eight only where every query has a compute unit to itself
     const bool one = pl.gs_log == 0;
-    const bool little = (k << pl.gs_log) <= 64 && pl.n <= 8192, much = (k << pl.gs_log) > 128 || pl.n > 8192;
-    const int threads = one && pl.n <= 2048 ? 64 : !one && little ? 128 : much && B <= pl.cus ? 512 : 256;
+    const int threads = pick_threads(pl.cus, pl.gs_log, pl.n, B, k);
     const size_t lds = one ? 0 : (size_t)d * T::bytes;
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(B), dim3(threads), lds, stream, maxima, pl.n, pl.gs_log, k, ids, scores, sh, after,

@@ -164,25 +164,40 @@ inline bool pick_runs(int cus, size_t row_bytes, size_t step_bytes, int B) {
     return steps >= 24 && (B <= 4 * cus || steps >= 72);
 }
 
-// Rows per group of the matrix-core kernel, by the time of what follows the products, in us: 4 bytes of maxima are written
-// in small pieces and read again, at 1.3 TB/s over all queries, the rows of k groups are read at 5 TB/s; one query alone waits
-// for its maxima (twice, 1024 a wave at a time) and, unless groups are single rows, for its rows (32 a wave, 24 steps of 32 bytes
-// at once).  The constants are fitted to 112 calls of 4000 to 1 M rows, 16 to 1000 queries, k = 1 to 16: on average 0.4 % behind the
-// best size of each, 12 % at most.  fp32 (wmf = 0) writes whole lines and keeps its own constants: 300 k x 128, B = 64 groups of 16 / 32 /
-// 64 rows 78 / 76 / 75, k = 10 83 / 83 / 88, B = 300, k = 16 333 / 325 / 346.
+// Threads of a flat_pick_kernel workgroup: a wave for single rows of a small corpus; else a wave per 32 rows to score and per 4096 maxima, two
+// at least; eight only where every query has a compute unit to itself.
+inline int pick_threads(int cus, int gs_log, int64_t n, int B, int k) {
+    const int rows = k << gs_log;
+    if (gs_log == 0 && n <= 2048) return WAVE;
+    if (gs_log > 0 && rows <= 64 && n <= 8192) return 2 * WAVE;
+    return (rows > 128 || n > 8192) && B <= cus ? 8 * WAVE : 4 * WAVE;
+}
+
+// Rows per group of the matrix-core kernel, by the time of what follows the products, in us: 4 bytes of maxima are written in small
+// pieces and read again, at 1.6 TB/s over all queries, the rows of k groups are read at 4.5 TB/s; one query alone waits for its maxima (twice,
+// 1024 a wave at a time) and, unless groups are single rows, for its rows (32 a wave, 24 steps of 32 bytes at once); and over all queries
+// every wave takes its turn on a SIMD, 1.3 us beside its rows.  The constants are fitted to 648 calls of 200 to 3 M rows, 1 to 5000 queries, d = 8 to 2048,
+// k = 1 to 16: on average 0.4 % behind the best size of each, 2 % of them by more than 5 %, the worst 20 (without the turns, fitted up to 1000
+// queries, 1.2 %, 7 % and 68: 1216 x 848, B = 4933, k = 1 single rows / groups of 4 30.5 / 51.3, 766 x 8, B = 2357, k = 10 11.8 / 16.5).
+// fp32 (wmf = 0) writes whole lines and keeps its own constants: 300 k x 128, B = 64 groups of 16 / 32 / 64 rows 78 / 76 / 75, k = 10
+// 83 / 83 / 88, B = 300, k = 16 333 / 325 / 346.
 // most: maxima of a query that there is room for; the largest groups where no size fits.
 inline int wide_group_log(int cus, int wmf, int64_t N, int row_bytes, int B, int k, size_t most) {
-    const int waves = B <= cus ? 8 : 4;                   // of a query
     int best = 0;
     double least = INFINITY;
     for (int g : {0, 2, 4, 5, 6}) {
         if (wmf == 0 ? g < 4 : (1 << g) > 16 * wmf) continue;
         if ((size_t)maxima_of(wmf, N, g) > most) { best = g; continue; }
-        const double n = (double)N / (1 << g), rows = (double)k * (1 << g);
+        const double n = (double)N / (1 << g), rows = (double)k * (1 << g), units = ceil(rows / 32);
         double us;
-        if (wmf == 0) us = 2.0 * n * B / 1e6 + 1.6 * n / (1024 * waves) + rows * row_bytes * B / 4e6 + 1.2 * ceil(rows / (32 * waves)) * ceil(row_bytes / 384.0);
-        else us = 3.0 * n * B / 1e6 + 1.2 * n / (1024 * waves);
-        if (wmf > 0 && g > 0) us += rows * row_bytes * B / 5e6 + 3.5 + 0.4 * ceil(rows / (32 * waves)) * ceil(row_bytes / 768.0);
+        if (wmf == 0) {
+            const int waves = B <= cus ? 8 : 4;           // of a query
+            us = 2.0 * n * B / 1e6 + 1.6 * n / (1024 * waves) + rows * row_bytes * B / 4e6 + 1.2 * ceil(rows / (32 * waves)) * ceil(row_bytes / 384.0);
+        } else {
+            const int waves = pick_threads(cus, g, (int64_t)n, B, k) / WAVE;
+            us = 2.5 * n * B / 1e6 + 1.8 * n / (1024 * waves) + 1.3 * waves * B / (4.0 * cus);
+            if (g > 0) us += rows * row_bytes * B / 4.5e6 + 2.6 + ceil(units / waves) * (1 + row_bytes / 1280.0) + 0.1 * units * B / (4.0 * cus);
+        }
         if (us < least) { least = us; best = g; }
     }
     return best;
@@ -409,12 +424,29 @@ inline bool static_takes_long(int64_t N, int d, int dtype, int B) {
     const int64_t rows = dtype == ANN_F32 ? 32 : 128, most = dtype == ANN_F32 ? 1024 : 128, slabs = (N + rows - 1) / rows;
     return (slabs < most ? slabs : most) * B * 16 * (int64_t)CAND_BYTES <= ANN_STATIC_WORKSPACE_BYTES;
 }
-// ... and the line of one pass: that of the tile that pads least, and where tiles of 512 x 128 would do, of their larger groups.
+// ... and the line of one pass: that of the call's tile, of the one that pads least, and where tiles of 512 x 128 would do, of their larger
+// groups.  (The group sizes are those of earlier constants, which the line was drawn by, and not those that the call gets.)
+inline int static_group_log(int cus, int wmf, int64_t N, int row_bytes, int B, int k) {
+    const int waves = B <= cus ? 8 : 4;
+    int best = 0;
+    double least = INFINITY;
+    for (int g : {0, 2, 4, 5, 6}) {
+        if ((1 << g) > 16 * wmf) continue;
+        if ((size_t)maxima_of(wmf, N, g) > WIDE_WS_MAX / ((size_t)B * sizeof(float))) { best = g; continue; }
+        const double n = (double)N / (1 << g), rows = (double)k * (1 << g);
+        double us = 3.0 * n * B / 1e6 + 1.2 * n / (1024 * waves);
+        if (g > 0) us += rows * row_bytes * B / 5e6 + 3.5 + 0.4 * ceil(rows / (32 * waves)) * ceil(row_bytes / 768.0);
+        if (us < least) { least = us; best = g; }
+    }
+    return best;
+}
 inline bool static_one_pass(const WidePlan &w, int64_t N, int d, int B, int k) {
-    int64_t n = maxima_of(1, (N + 63) / 64 * 64, w.gs_log);
-    const int64_t tall = (N + 511) / 512;
+    const int log = static_group_log(w.cus, w.wmf, w.slots, d * 2, B, k);
+    int64_t n = maxima_of(1, (N + 63) / 64 * 64, log);
+    const int64_t own = maxima_of(w.wmf, w.slots, log), tall = (N + 511) / 512;
+    n = own < n ? own : n;
     if (w.shape == WIDE_MID && 8 * tall * ((B + 127) / 128) >= 5 * (int64_t)w.cus) {
-        const int64_t g = maxima_of(4, tall * 512, wide_group_log(w.cus, 4, tall * 512, d * 2, B, k, WIDE_WS_MAX / ((size_t)B * sizeof(float))));
+        const int64_t g = maxima_of(4, tall * 512, static_group_log(w.cus, 4, tall * 512, d * 2, B, k));
         n = g < n ? g : n;
     }
     return (size_t)B * (size_t)n * sizeof(float) <= (size_t)ANN_STATIC_WORKSPACE_BYTES;

@@ -340,3 +340,20 @@ def test_searches_that_need_no_workspace(plans, N, d, elem_bytes, ef):
     (128, 4, 300, False)])
 def test_long_runs_where_they_were_measured_to_pay(plans, d, elem_bytes, B, runs):
     assert bool(plans.runs(CUS, d, elem_bytes, B)) == runs
+
+
+# taken though one pass with the group sizes of today needs more than the static workspace: in parts, or by larger groups
+STATIC_LINE = ((8229, 928, 297, 5), (9226, 64, 2414, 14), (7516, 96, 2011, 7), (210058, 32, 337, 13),
+               (135374, 32, 749, 13), (1687, 96, 4734, 10), (4871, 64, 5009, 5), (215654, 64, 581, 9))
+
+
+def test_the_static_workspace_takes_what_one_pass_fits(plans):
+    """Whatever ann_flat_workspace_bytes says fits it, and the calls of long answers that it took by other group sizes."""
+    rng = random.Random(8)
+    log = lambda lo, hi: int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+    for _ in range(20_000):
+        N, d, B, k = log(16, 1e6), 8 * log(1, 512), log(256, 20_000), rng.randint(5, 16)
+        if flat(plans, N, d, 0, B, k, 1 << 30)["bytes"] <= 8 * 1024 * 1024:
+            assert plans.static_accepts(CUS, N, d, 0, B, k, STATIC), (N, d, B, k)
+    for N, d, B, k in STATIC_LINE:
+        assert plans.static_accepts(CUS, N, d, 0, B, k, STATIC), (N, d, B, k)
