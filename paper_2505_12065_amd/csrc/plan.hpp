@@ -61,8 +61,9 @@ using WideTall = WideCfg<4, 2, 4, 2, 4, 1>;               // 512 x 128, 8 waves
 using WideMid = WideCfg<2, 2, 4, 2, 3, 1, 128>;           // 256 x 128, 8 waves
 using WideThin = WideCfg<2, 1, 2, 2, 3, 2, 128>;          // 128 x 64, 4 waves, two workgroups per compute unit
 using WideTiny = WideCfg<1, 1, 2, 2, 4, 2, 128>;          // 64 x 64, 4 waves, two
+using WideShort = WideCfg<2, 1, 2, 2, 4, 3>;              // 128 x 64, 4 waves, three: half lines, for short rows
 
-constexpr int WIDE_LARGE = 0, WIDE_TALL = 1, WIDE_MID = 2, WIDE_THIN = 3, WIDE_TINY = 4;
+constexpr int WIDE_LARGE = 0, WIDE_TALL = 1, WIDE_MID = 2, WIDE_THIN = 3, WIDE_TINY = 4, WIDE_SHORT = 5;
 struct WidePlan {
     int cus, shape, wmf;         // compute units; workgroup tile (a WideCfg); its row fragments per wave
     int NT, P;                   // query tiles x slabs of the corpus
@@ -87,13 +88,14 @@ inline void wide_geometry(WidePlan &pl, int shape, int cus, int64_t N, int B) {
     case WIDE_TALL: return geometry<WideTall>(pl, cus, N, B);
     case WIDE_MID: return geometry<WideMid>(pl, cus, N, B);
     case WIDE_TINY: return geometry<WideTiny>(pl, cus, N, B);
+    case WIDE_SHORT: return geometry<WideShort>(pl, cus, N, B);
     default: return geometry<WideThin>(pl, cus, N, B);
     }
 }
 
 inline int wide_rows(int shape) {                         // corpus rows of a tile
     return shape == WIDE_LARGE ? WideLarge::BM : shape == WIDE_TALL ? WideTall::BM : shape == WIDE_MID ? WideMid::BM
-           : shape == WIDE_TINY ? WideTiny::BM : WideThin::BM;
+           : shape == WIDE_TINY ? WideTiny::BM : shape == WIDE_SHORT ? WideShort::BM : WideThin::BM;
 }
 
 // ---- exact search, the whole call ----------------------------------------------------------------------
@@ -218,13 +220,21 @@ inline int wide_group_log(int cus, int wmf, int64_t N, int row_bytes, int B, int
 // tiles than four for each compute unit: equal at 130 k x 384, B = 400, and 73 against 63 at 300 k x 384, B = 100).  Queries are padded
 // to whole tiles; the tiles of 128 queries run at 12/13 of the rate of the other, so they take over where they save more
 // than that (1 M x 768, B = 300: 822 -> 745).
+// 128 x 64 comes in two forms.  Whole lines of a row of up to 32 elements are half empty, and half lines leave room for three
+// workgroups a compute unit, which is one round instead of two where there are tiles for more than two.  Whole / half lines: 3.7 M x 8, B = 6
+// 80 / 56; 1.2 M x 24, B = 18 33.9 / 26.0; 1.3 M x 32, B = 54 35.4 / 28.5; 45 k x 8, B = 11 9.5 / 9.1; 35 k x 224, B = 85 16.0 / 14.5, 90 k x 88,
+// B = 28 13.3 / 11.8; but 2.7 M x 64, B = 3 79 / 90; 107 k x 384, B = 28 21.9 / 23.7; 23 k x 376, B = 133 18.9 / 19.5.
+inline int wide_thin(int cus, int64_t N, int d, int B) {
+    const int64_t tiles = (N + WideThin::BM - 1) / WideThin::BM * ((B + WideThin::BN - 1) / WideThin::BN);
+    return d <= 32 || (d <= 256 && tiles > 2 * (int64_t)cus && tiles <= 3 * (int64_t)cus) ? WIDE_SHORT : WIDE_THIN;
+}
 inline int wide_shape(int cus, int64_t N, int d, int B) {
     auto tiles = [&](int bm, int bn) { return (N + bm - 1) / bm * ((B + bn - 1) / bn); };
     const int64_t cols256 = (B + 255) / 256 * 256, cols128 = (B + 127) / 128 * 128;
     if (8 * tiles(256, 256) >= 5 * (int64_t)cus && 12 * cols256 <= 13 * cols128) return WIDE_LARGE;
     if (B > 64 && d <= 512 && tiles(512, 128) >= 4 * (int64_t)cus) return WIDE_TALL;
     if (B > 64 && 4 * tiles(256, 128) >= 3 * (int64_t)cus) return WIDE_MID;
-    return tiles(128, 64) > cus ? WIDE_THIN : WIDE_TINY;
+    return tiles(128, 64) > cus ? wide_thin(cus, N, d, B) : WIDE_TINY;
 }
 
 // Whether the matrix-core kernel takes a call, or the streaming kernel, which reads large corpora at the rate of HBM for up to
@@ -280,7 +290,7 @@ inline size_t maxima_pass(FlatPlan &pl, int cus, int d, int dtype, int k, size_t
         if (pl.w.wmf < 4 && (size_t)maxima_of(pl.w.wmf, pl.w.slots, 3 + pl.w.wmf) > most) {
             if (8 * ((N + WideTall::BM - 1) / WideTall::BM) * ((B + WideTall::BN - 1) / WideTall::BN) >= 5 * (int64_t)cus)
                 wide_geometry(pl.w, WIDE_TALL, cus, N, B);
-            else wide_geometry(pl.w, WIDE_THIN, cus, N, B);
+            else wide_geometry(pl.w, wide_thin(cus, N, d, B), cus, N, B);
         }
         pl.w.gs_log = wide_group_log(cus, pl.w.wmf, pl.w.slots, d * 2, B, k, most);
         pl.w.n = maxima_of(pl.w.wmf, pl.w.slots, pl.w.gs_log);

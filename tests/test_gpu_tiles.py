@@ -29,6 +29,10 @@ DEV = "cuda"
     (torch.bfloat16, 33_000, 1_544, 33, 4),    # ... rows of three groups of queries that do not fit LDS
     (torch.float16, 70_001, 64, 1, 10),        # ... short rows
     (torch.bfloat16, 131_072, 96, 16, 16),     # ...
+    (torch.float16, 131_073, 8, 3, 4),         # 128 x 64 of half lines: a quarter of a stage, one row in the last tile
+    (torch.bfloat16, 40_000, 24, 100, 16),     # ... two query tiles
+    (torch.float16, 98_303, 200, 64, 16),      # ... 768 tiles, rows that end in a stage
+    (torch.bfloat16, 700, 24, 3_000, 16),      # ... single rows, the corpus the smaller operand
     (torch.bfloat16, 60_000, 1_160, 300, 9),   # rows scored once more: three long runs of steps and a last one of half a step
     (torch.float32, 40_000, 392, 400, 3),      # ... fp32, one long run and half a step
     (torch.float16, 3_000, 776, 1_025, 9),     # ... more queries than long runs pay for

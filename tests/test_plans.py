@@ -37,6 +37,7 @@ extern "C" int in_lds(int64_t N, int d, int elem_bytes, int R, int ef) {
     return frontier_in_lds(N, d, elem_bytes, R, ef, true, L);
 }
 extern "C" int runs(int cus, int d, int elem_bytes, int B) { return pick_runs(cus, (size_t)d * elem_bytes, 16 * elem_bytes, B); }
+extern "C" int shape(int cus, int64_t N, int d, int B) { return wide_shape(cus, N, d, B); }
 // out: kind (0 lists, 1 direct, 2 matrix cores, 3 streaming with maxima), queries and rows at a time, maxima of a query,
 // log2 of the rows they stand for, offset of the k best so far, workspace, maxima of the smallest last part
 extern "C" void flat(int cus, int64_t N, int d, int dtype, int B, int k, int64_t limit, int64_t *out) {
@@ -70,6 +71,7 @@ def plans(tmp_path_factory):
     L = ctypes.CDLL(str(lib))
     L.graph_kernel.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 5 + [ctypes.c_float]
     L.frontier.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_float, ctypes.c_int, ctypes.c_void_p]
+    L.shape.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 2
     L.in_lds.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4
     L.flat.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64, ctypes.c_void_p]
     L.static_accepts.argtypes = L.static_kind.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64]
@@ -357,3 +359,22 @@ def test_the_static_workspace_takes_what_one_pass_fits(plans):
             assert plans.static_accepts(CUS, N, d, 0, B, k, STATIC), (N, d, B, k)
     for N, d, B, k in STATIC_LINE:
         assert plans.static_accepts(CUS, N, d, 0, B, k, STATIC), (N, d, B, k)
+
+
+LARGE, TALL, MID, THIN, TINY, SHORT = range(6)
+
+
+# us of a call with 128 x 64 tiles of whole / half lines
+@pytest.mark.parametrize("N,d,B,shape", [
+    (3_737_423, 8, 6, SHORT),        # 79.8 / 55.9
+    (1_243_025, 24, 18, SHORT),      # 33.9 / 26.0
+    (1_273_004, 32, 54, SHORT),      # 35.4 / 28.5
+    (45_140, 8, 11, SHORT),          # 9.5 / 9.1
+    (35_294, 224, 85, SHORT),        # 16.0 / 14.5: 552 tiles
+    (90_354, 88, 28, SHORT),         # 13.3 / 11.8: 706 tiles
+    (2_746_069, 64, 3, THIN),        # 79.1 / 90.4
+    (106_876, 384, 28, THIN),        # 21.9 / 23.7
+    (21_798, 448, 183, THIN),        # 17.9 / 18.5: 513 tiles
+    (48_119, 112, 7, THIN)])         # 12.9 / 12.8
+def test_half_lines_for_short_rows(plans, N, d, B, shape):
+    assert plans.shape(CUS, N, d, B) == shape
