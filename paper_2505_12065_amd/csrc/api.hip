@@ -500,10 +500,10 @@ static int graph_frontier_run(DeviceState *st, int32_t dtype, int32_t B, Frontie
 // Whether graph_frontier_kernel takes a call, and its layout.  Where the call would want the workspace of the visited sets
 // (`workspace`: the other kernel does) and that is not at hand, it takes it with the visited set in LDS if that fits.
 static bool frontier_takes(const DeviceState *st, int64_t N, int32_t d, int32_t dtype, int32_t R, int32_t B, int32_t ef, bool counters,
-                           float tau, bool workspace, hipStream_t s, FrontierLds *L) {
+                           float tau, float alpha, bool workspace, hipStream_t s, FrontierLds *L) {
     const int bytes = elem_bytes(dtype);
-    *L = frontier_plan(st->cus, N, d, bytes, B, ef, counters, tau);
-    const bool pays = frontier_pays(st->cus, d * bytes, R, B, ef, counters, tau, *L);
+    *L = frontier_plan(st->cus, N, d, bytes, B, ef, counters && tau < 1.0f);
+    const bool pays = frontier_pays(st->cus, d * bytes, R, B, ef, counters, counters && exit_likely(tau, alpha, R, ef), *L);
     if ((pays ? L->vis_mode == FRONTIER_VIS_GLOBAL : workspace) && !at_hand(st, st->vis, (size_t)B * (size_t)visited_words(N) * 4, s)) {
         FrontierLds in_lds;
         if (frontier_in_lds(N, d, bytes, R, ef, counters, in_lds)) {
@@ -550,7 +550,7 @@ int ann_graph_search_nonstall_typed(const void *corpus, int64_t N, int32_t d, in
     ns.ema = ema;
     hipStream_t s = static_cast<hipStream_t>(stream);
     FrontierLds F;
-    if (frontier_takes(st, N, d, dtype, R, B, ef, true, tau, true, s, &F))
+    if (frontier_takes(st, N, d, dtype, R, B, ef, true, tau, ns.alpha, true, s, &F))
         return graph_frontier_run(st, dtype, B, FrontierArgs{corpus, N, d, R, graph, queries, entry, k, ef, ids, scores, F, ns}, true, s);
     void *vis = nullptr;
     if (int rc = workspace_for(st, &st->vis, (size_t)B * (size_t)ns.words * 4, s, &vis)) return rc;
@@ -577,7 +577,7 @@ static int graph_search_any(const void *corpus, int64_t N, int32_t d, int32_t dt
     ns.n_entries = n_entries;
     ns.tau = INFINITY;
     FrontierLds F;
-    if (frontier_takes(st, N, d, dtype, R, B, ef, false, INFINITY, L.two_level, s, &F))
+    if (frontier_takes(st, N, d, dtype, R, B, ef, false, INFINITY, 0.f, L.two_level, s, &F))
         return graph_frontier_run(st, dtype, B, FrontierArgs{corpus, N, d, R, graph, queries, entry, k, ef, ids, scores, F, ns}, false, s);
     if (graph_step_pays(st->cus, N, d * elem_bytes(dtype), R, B, ef)) {
         const StepLds S = graph_step_plan(st->cus, d, elem_bytes(dtype), B, ef);

@@ -650,8 +650,8 @@ inline bool frontier_layout(int64_t N, int d, int elem_bytes, int ef, int waves,
     L.total = up(off + 8u * (uint32_t)L.cap);
     return (int64_t)L.total <= room;
 }
-inline FrontierLds frontier_plan(int cus, int64_t N, int d, int elem_bytes, int B, int ef, bool counters, float tau) {
-    const int width = (counters && tau < 1.0f) || 32 * (int64_t)ef >= N ? 8 : 4;
+inline FrontierLds frontier_plan(int cus, int64_t N, int d, int elem_bytes, int B, int ef, bool exits) {
+    const int width = exits || 32 * (int64_t)ef >= N ? 8 : 4;
     auto lay = [&](int waves, int per_cu, FrontierLds &L) {
         return frontier_layout(N, d, elem_bytes, ef, waves, per_cu, width, per_cu == 3 ? 2 * FRONTIER_SPARE : FRONTIER_SPARE, L);
     };
@@ -668,6 +668,11 @@ inline bool frontier_in_lds(int64_t N, int d, int elem_bytes, int R, int ef, boo
     return R <= GRAPH_STEP_MAX_R && (fits(FRONTIER_SPARE_MIN) || (counters && fits(FRONTIER_SPARE_TIGHT)));
 }
 
+// Whether most queries of a search with the maturity exit leave by it.  An average that moves by alpha a sample passes tau after about
+// -log(1 - tau) / alpha samples of 1; a search that runs to its end scores up to ef R nodes, and relative qualities beyond 1 shorten the way.  Early
+// exits of 450 random calls against samples / (ef R): up to 1 76 to 91 %, 1 to 3 63 %, beyond 3 20 %.
+inline bool exit_likely(float tau, float alpha, int R, int ef) { return tau < 1.0f && -logf(1.0f - tau) < 3.0f * ef * R * alpha; }
+
 // Where graph_frontier_kernel is faster than the others (graph_search_kernel, graph_step_kernel, whichever was better), us, others / it:
 //   every query a compute unit to itself, R = 32: 200 k x 768 fp16, B = 256 ef = 16 93 / 91, 48 198 / 174, 192 587 / 427, 768 2202 / 1122,
 //     4096 7992 / 4101; B = 1 128 / 86, 416 / 226, 1916 / 558 at ef = 48, 192, 768; 60 k x 384 1121 / 510 (ef = 384); 1 M x 768 with the
@@ -678,27 +683,36 @@ inline bool frontier_in_lds(int64_t N, int d, int elem_bytes, int R, int ef, boo
 //     R = 32 steps hold little more than one expansion's neighbours while the list fills: ef = 48 217 / 257, 192 640 / 662, 384
 //     1264 / 1041, 1536 4372 / 2684; R = 24 253 / 284 at ef = 64, 629 / 586 at 192
 //   three (B = 2048): R = 32 799 / 804 at ef = 64, 2074 / 1726 at 192; B = 1024 490 / 512, 1222 / 1071
+//   rows of more than 2.5 KB start a little later there: 40 k x 1024 fp32, B = 512, R = 16 ef = 16 139 / 169, 48 268 / 270; B = 1024, R = 32 96 1002 /
+//     1137, 192 0.92 times as long (2.5 KB 753 / 767)
 //   visited set in memory: short lists stay with the id caches, which need no workspace; R = 32, B = 512, 1 M x 768 ef = 600 2215 /
 //     2516, 1024 3619 / 3799, 2048 6959 / 6364, 4096 13 421 / 10 524; R = 24 or rows of 256 bytes all of them (700 k, ef = 600 2086 /
 //     1983, 1907 / 1812)
 //   maturity exit, tau = 0.9: R = 32, 200 k x 384 bf16, B = 256 ef = 32 103 / 94, 64 174 / 113, 256 326 / 249, 2048 2249 / 1488; R = 16 B = 256
-//     ef = 32 106 / 128, 64 170 / 166; B = 1024 64 339 / 352, 96 429 / 427.  tau = 3 (no query leaves): B = 256 R = 32 64 318 / 319,
+//     ef = 32 106 / 128, 64 170 / 166; B = 1024 64 339 / 352, 96 429 / 427; one query, which may have left before it pays, 120 k x 256 fp32, ef = 92
+//     69 / 79, 40 k x 1024 fp32 99 83 / 103, but 200 k x 128, R = 16, 124 219 / 127; 100 k x 768, B = 512, R = 32 ef = 32 105 / 112, 40 122 / 116, R = 16
+//     64 186 / 208, 96 271 / 237, R = 8 96 291 / 285; B = 1024, R = 8 96 563 / 592, rows of 3 KB 128 1.09 times as long, 192 0.98.  tau = 3, or a window too long (no query leaves): B = 256 R = 32 64 318 / 319,
 //     128 535 / 516, R = 16 96 357 / 391, 200 651 / 641; B = 512 256 1036 / 1137, 512 2032 / 1891; 500 k x 128, B = 64 128 600 / 630, 256 943 / 837;
 //     visited set in memory, 1 M x 256: B = 512 512 2138 / 2678, 2048 7438 / 8428 (two of its workgroups a compute unit wait for more of
-//     these reads than hide), B = 1024 1024 7648 / 7185, B = 256 1024 3600 / 2894
-inline bool frontier_pays(int cus, int row_bytes, int R, int B, int ef, bool counters, float tau, const FrontierLds &L) {
+//     these reads than hide), B = 1024 1024 7648 / 7185, B = 256 1024 3600 / 2894.  Medians of 680 more calls, it / others: B = 2 to 8 ef = 64 to 96
+//     0.95 to 1.01, 96 to 128 0.99; B = 9 to 256 64 to 96 1.02 to 1.07, 96 to 128 0.99 to 1.03, 128 to 192 0.94 to 0.98; B = 512, R = 16 128 to 192 1.08,
+//     256 to 384 0.86, R = 24 192 to 256 1.09, 256 to 384 0.94, R = 32 256 to 384 1.07, 384 to 512 0.95; B = 600 and more, R = 16 24 to 48 0.94, 96 to 128
+//     0.75, R = 24 96 to 128 1.02 (rows of 4 KB 1.12), 128 to 192 0.93, R = 32 128 to 192 0.93 to 1.11, 192 to 256 0.87 to 1.01
+inline bool frontier_pays(int cus, int row_bytes, int R, int B, int ef, bool counters, bool leaves, const FrontierLds &L) {
     if (R > GRAPH_STEP_MAX_R || L.total > LDS_MAX) return false;
-    const bool global = L.vis_mode == FRONTIER_VIS_GLOBAL;
+    const bool global = L.vis_mode == FRONTIER_VIS_GLOBAL, own = B <= cus, waits = B > 2 * cus, long_rows = row_bytes > 2560;
     if (counters) {
-        if (tau < 1.0f) return ef >= (B > 2 * cus ? 96 : R > 16 && B >= 8 ? 32 : 64);
-        if (global && B > cus && B <= 2 * cus) return false;
-        return ef >= (B > cus ? 448 : R > 16 && (B <= 8 || row_bytes > 256) ? 128 : 192);
+        if (leaves && own) return ef >= (B == 1 ? 112 : R > 16 && B >= 8 ? 32 : 64);
+        if (leaves) return ef >= (waits ? (R > 8 || B > 6 * cus ? 96 : 176) : R > 16 ? 40 : R > 8 ? 72 : 112);
+        if (own) return ef >= (B <= 8 ? 96 : row_bytes > 256 ? 112 : 192);
+        if (waits) return ef >= (R <= 16 ? 48 : (R <= 24 || B > 6 * cus) && !long_rows ? 112 : 176);
+        return R <= 16 ? ef >= 224 : !global && ef >= (R <= 24 ? 256 : 448);
     }
     if (global && ef <= GRAPH_EF_TWO_LEVEL) return false;
-    if (B <= cus) return ef >= (row_bytes > 2048 ? 72 : R > 16 ? 12 : 8);
-    if (R <= 16) return ef >= 16;
-    if (global) return B > 2 * cus || R <= 24 || row_bytes <= 512 || ef >= 1400;
-    return ef >= (B > 2 * cus ? 96 : R <= 24 ? 128 : 200);
+    if (own) return ef >= (row_bytes > 2048 ? 72 : R > 16 ? 12 : 8);
+    if (R <= 16) return ef >= (long_rows && !waits ? 36 : 16);
+    if (global) return waits || R <= 24 || row_bytes <= 512 || ef >= 1400;
+    return ef >= (waits ? (long_rows && B <= 6 * cus ? 136 : 96) : R <= 24 ? 128 : 200);
 }
 
 // Where graph_step_kernel is faster than graph_search_kernel, among the calls that graph_frontier_kernel does not take: lists of

@@ -42,8 +42,9 @@ def test_graph_frontier(dtype, N, d, R, B, ef, k, seed):
     x, q, g = _random(N, d, R, B, dtype, seed)
     xn, qn, name = to_np(x), to_np(q), np_dtype_name(x)
     ids, sc = ann.ann_graph_search_typed(x.to(DEV), g.to(DEV), 3, q.to(DEV), k, ef)
-    # an average that moves by 1e-9 a sample never passes the threshold: the natural stop, with counters
-    n_ids, n_sc, stats, _ = ann.ann_graph_search_nonstall_typed(x.to(DEV), g.to(DEV), 3, q.to(DEV), k, ef, tau=0.999, window=2_000_000_000)
+    # an engine that is never ready: the natural stop, with counters and the averages kept
+    n_ids, n_sc, stats, _ = ann.ann_graph_search_nonstall_typed(x.to(DEV), g.to(DEV), 3, q.to(DEV), k, ef, tau=0.999, window=10,
+                                                                engine_ready=torch.zeros(1, dtype=torch.int32, device=DEV))
     torch.cuda.synchronize()
     o_ids, _, o_sc64, n_dist, n_expand = oracle.graph_search(xn, g.numpy(), 3, qn, k, ef, dtype=name)
     strict, tolerant, n = compare_topk(ids.cpu().numpy(), sc.cpu().numpy(), o_ids, o_sc64, xn, qn, dtype=name)
@@ -84,7 +85,7 @@ def test_graph_frontier_entries_and_nan(ef):
     o_ids, _, _, n_dist, n_expand = oracle.graph_search(to_np(x), g.numpy(), 0, to_np(q), 10, ef, entries=e.numpy())
     assert np.array_equal(ids.cpu().numpy(), o_ids)
     ids, _, stats, _ = ann.ann_graph_search_nonstall_typed(x.to(DEV), g.to(DEV), 0, q.to(DEV), 10, ef, entries=e.to(DEV), tau=0.999,
-                                                           window=2_000_000_000)
+                                                           window=10, engine_ready=torch.zeros(1, dtype=torch.int32, device=DEV))
     torch.cuda.synchronize()
     st = stats.cpu().numpy()
     assert np.array_equal(ids.cpu().numpy(), o_ids) and np.array_equal(st[:, 1], n_dist) and np.array_equal(st[:, 2], n_expand)

@@ -17,17 +17,19 @@ SHIM = r"""
 using namespace ann;
 // 0 graph_search_kernel, 1 graph_frontier_kernel, 2 graph_step_kernel (all workspace at hand)
 extern "C" int graph_kernel(int cus, int64_t N, int row_bytes, int R, int B, int ef, int counters, float tau) {
-    const FrontierLds L = frontier_plan(cus, N, row_bytes / 2, 2, B, ef, counters != 0, tau);
-    if (frontier_pays(cus, row_bytes, R, B, ef, counters != 0, tau, L)) return 1;
+    const bool leaves = counters && exit_likely(tau, 2.0f / 501, R, ef);                  // (a window of 500)
+    const FrontierLds L = frontier_plan(cus, N, row_bytes / 2, 2, B, ef, counters && tau < 1);
+    if (frontier_pays(cus, row_bytes, R, B, ef, counters != 0, leaves, L)) return 1;
     return !counters && graph_step_pays(cus, N, row_bytes, R, B, ef) ? 2 : 0;
 }
+extern "C" int leaves(float tau, int window, int R, int ef) { return exit_likely(tau, 2.0f / ((float)window + 1.0f), R, ef); }
 // tight: frontier_in_lds's layout instead of the call's; out: fits, waves, workgroups per compute unit, expansions a step tries, tight,
 // visited set in LDS, its words, the query's, visited set's and array's places, places of the array, those a bound may leave, LDS bytes
 extern "C" void frontier(int cus, int64_t N, int row_bytes, int B, int ef, int counters, float tau, int in_lds, int64_t *out) {
     FrontierLds L;
     bool fits = true;
     if (in_lds) fits = frontier_in_lds(N, row_bytes / 2, 2, 32, ef, counters != 0, L);
-    else L = frontier_plan(cus, N, row_bytes / 2, 2, B, ef, counters != 0, tau);
+    else L = frontier_plan(cus, N, row_bytes / 2, 2, B, ef, counters && tau < 1);
     const int64_t v[] = {fits, L.waves, L.per_cu, L.width, L.tight, L.vis_mode == FRONTIER_VIS_LDS, L.vis_words, L.q, L.vis, L.keys, L.cap,
                          L.spare, L.total, (int64_t)FrontierLds::WAVES + L.waves * FrontierLds::WAVE_BYTES};
     for (int i = 0; i < 14; ++i) out[i] = v[i];
@@ -70,6 +72,7 @@ def plans(tmp_path_factory):
                     os.path.join(ROOT, "paper_2505_12065_amd", "csrc"), "-o", str(lib), str(src)], check=True)
     L = ctypes.CDLL(str(lib))
     L.graph_kernel.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 5 + [ctypes.c_float]
+    L.leaves.argtypes = [ctypes.c_float] + [ctypes.c_int] * 3
     L.frontier.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_float, ctypes.c_int, ctypes.c_void_p]
     L.shape.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 2
     L.in_lds.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4
@@ -116,10 +119,31 @@ NEVER = float("inf")                                  # no average passes it
     (200_000, 768, 32, 256, 256, 0.9, FRONTIER),          # 326 / 249
     (200_000, 768, 16, 256, 32, 0.9, SEARCH),             # 106 / 128
     (200_000, 768, 16, 1024, 64, 0.9, SEARCH),            # 339 / 352
+    (120_000, 1024, 32, 1, 92, 0.9, SEARCH),              # 69 / 79: one query
+    (200_000, 256, 16, 1, 124, 0.9, FRONTIER),            # 219 / 127
+    (100_000, 1536, 32, 512, 32, 0.9, SEARCH),            # 105 / 112
+    (100_000, 1536, 32, 512, 48, 0.9, FRONTIER),          # 144 / 126
+    (100_000, 1536, 16, 512, 64, 0.9, SEARCH),            # 186 / 208
+    (100_000, 1536, 16, 512, 96, 0.9, FRONTIER),          # 271 / 237
+    (100_000, 1536, 8, 512, 64, 0.9, SEARCH),             # 223 / 233
+    (100_000, 1536, 8, 1024, 96, 0.9, SEARCH),            # 563 / 592
+    (40_000, 4096, 16, 512, 22, None, SEARCH),            # 164 / 186
+    (40_000, 4096, 16, 512, 64, None, FRONTIER),          # 329 / 311
+    (40_000, 4096, 32, 1024, 96, None, SEARCH),           # 1002 / 1137
+    (60_000, 2304, 32, 1024, 128, None, FRONTIER),        # 0.93
     (200_000, 768, 32, 256, 64, NEVER, SEARCH),           # 318 / 319
     (200_000, 768, 32, 512, 256, NEVER, SEARCH),          # 1036 / 1137
     (200_000, 768, 32, 512, 512, NEVER, FRONTIER),        # 2032 / 1891
     (500_000, 256, 32, 64, 128, NEVER, SEARCH),           # 600 / 630
+    (60_000, 768, 32, 8, 112, NEVER, FRONTIER),           # 0.98: the median of such calls
+    (200_000, 1536, 32, 256, 80, NEVER, SEARCH),          # 1.05
+    (200_000, 1536, 32, 256, 160, NEVER, FRONTIER),       # 0.97
+    (400_000, 768, 16, 512, 160, NEVER, SEARCH),          # 1.08
+    (1_000_000, 512, 16, 512, 300, NEVER, FRONTIER),      # 0.86
+    (200_000, 512, 24, 512, 200, NEVER, SEARCH),          # 1.09
+    (40_000, 4096, 24, 512, 300, NEVER, FRONTIER),        # 0.94
+    (1_000_000, 512, 16, 700, 56, NEVER, FRONTIER),       # 0.88
+    (200_000, 512, 32, 1024, 160, NEVER, SEARCH),         # 1.11
     (1_000_000, 512, 32, 512, 2048, NEVER, SEARCH),       # 7438 / 8428: visited sets in memory, two workgroups a compute unit
     (1_000_000, 512, 32, 1024, 1024, NEVER, FRONTIER),    # 7648 / 7185
 ])
@@ -378,3 +402,18 @@ LARGE, TALL, MID, THIN, TINY, SHORT = range(6)
     (48_119, 112, 7, THIN)])         # 12.9 / 12.8
 def test_half_lines_for_short_rows(plans, N, d, B, shape):
     assert plans.shape(CUS, N, d, B) == shape
+
+
+# share of queries that leave early
+@pytest.mark.parametrize("tau,window,R,ef,likely", [
+    (0.9, 500, 32, 256, True),            # 0.8 and more
+    (0.9, 500, 24, 64, True),
+    (0.7, 100, 8, 10, True),              # 0.9
+    (0.95, 2000, 32, 64, True),           # 0.5 to 0.9
+    (0.95, 2000, 16, 32, False),          # 0.2
+    (0.999, 2_000_000_000, 32, 512, False),
+    (0.999, 2_000_000_000, 32, 16_384, False),
+    (3.0, 500, 32, 2048, False), (NEVER, 500, 32, 2048, False), (1.0, 1, 32, 16_384, False),
+    (0.0, 2_000_000_000, 1, 1, True), (-1.0, 500, 1, 1, True), (-NEVER, 500, 1, 1, True)])
+def test_whether_the_exit_is_likely(plans, tau, window, R, ef, likely):
+    assert bool(plans.leaves(tau, window, R, ef)) == likely
