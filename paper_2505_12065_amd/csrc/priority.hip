@@ -59,8 +59,8 @@ constexpr int PRIO_THREADS = 512;
 constexpr int PRIO_WAVES = PRIO_THREADS / WAVE;
 
 // One launch does it all; every workgroup computes the extremes and, for the requests it compares with, the
-// levels again instead of waiting for another launch to do so (n is a serving batch: a few kilobytes from the L2,
-// a few hundred instructions; a second launch costs more than either).
+// levels again instead of waiting for another launch to do so: of a serving batch that is a few kilobytes from the L2 and
+// a few hundred instructions.
 //
 //   level_i = largest j in [0, G) with R_i > T_{R,j} or W_i > T_{W,j} or C_i > T_{C,j}, else 0,
 //   T_{M,j} = min(M) + j/G (max(M) - min(M)), evaluated in binary64 exactly as written: the quotient,
@@ -72,12 +72,12 @@ constexpr int PRIO_WAVES = PRIO_THREADS / WAVE;
 // Workgroup b places the PRIO_TILE requests from b PRIO_TILE on: every thread holds one request at a time of the n to compare
 // with and tests it against all of them, so the n^2 comparisons are spread over the whole chip instead of one thread walking
 // all n.  A level and a 64-bit image of the queueing time that orders like the number are compared as one number of 96 bits.
-// Bound by latency up to some 3000 requests: one read of the requests, which are kept (a second one cost 0.5 us), reductions
+// Bound by latency up to some 3000 requests: one read of the first 2048, which are kept (a second one cost 0.5 us), reductions
 // that stay out of the LDS crossbar, three barriers; beyond that by the comparisons and the levels that every workgroup
 // computes again.  us of a call, one thread walking all n (two launches) / read twice, 8 instructions a comparison / now, 4 of them:
-// n = 3000, G = 6 300 / 12.1 / 9.1 (the host's share is 8.5; the kernel 13.2 -> 9.5), n = 4661 - / 21.5 / 18.0, n = 16384 1590 / 76 / 71.
+// n = 3000, G = 6 300 / 11.8 / 8.2, n = 16384 1590 / 76 / 69.
 constexpr int PRIO_TILE = 16;
-constexpr int HELD = 8;                                                   // requests that a thread keeps from the extremes to the comparisons
+constexpr int HELD = 4;                                                   // requests that a thread keeps from the extremes to the comparisons
 
 // order-preserving image of a queueing time (a NaN counts as -inf, -0 as +0)
 __device__ __forceinline__ uint64_t wait_key(double w) {
@@ -90,9 +90,11 @@ __device__ __forceinline__ uint64_t wait_key(double w) {
 // metric never descend with j (j / G, the product with a difference that is not negative and the sum each round
 // monotonically; where an extreme is infinite they are all infinite or all NaN), so the largest j passed is found by halving
 // and the level is the largest over the three metrics.  Every workgroup looks at all n requests, so level by level costs
-// n^2 G / 16 tests.  Level by level / halving, us (of the kernel that read the requests twice): n = 256, G = 32 12.4 / 13.4, G = 64 17.4 / 14.8, G = 1024 161 / 20.6; n = 3000,
-// G = 32 19.0 / 20.9, G = 64 27.5 / 23.2, G = 1024 285 / 34.4; n = 65 536, G = 32 1764 / 1659, G = 1024 33 100 / 3470.
-constexpr int PRIO_FEW = 32;
+// n^2 G / 16 tests.  The three metrics are halved side by side, without a branch: a request's reads of a step are in flight together,
+// twelve a thread (one metric after the other, each read waited for: n = 3000, G = 64 20.2 us, now 12.1; n = 65 536, G = 256 2870,
+// now 1990).  Level by level / halving, us: n = 16, G = 20 7.4 / 6.9, G = 22 7.7 / 6.9, G = 32 9.0 / 6.9; n = 3000, G = 20
+// 11.7 / 11.2, G = 22 12.3 / 11.2, G = 32 15.2 / 11.2; n = 65 536, G = 20 1405 / 1430, G = 22 1479 / 1430, G = 32 1826 / 1430.
+constexpr int PRIO_FEW = 20;
 template <bool MANY>
 __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *__restrict__ R, const double *__restrict__ W,
                                                                 const int32_t *__restrict__ C,
@@ -107,7 +109,7 @@ __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *_
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
     const int i0 = blockIdx.x * PRIO_TILE, in = min(PRIO_TILE, n - i0);
     if (tid < PRIO_TILE) before[tid] = 0;
-    // The tile's requests and the first eight of a thread are loaded once, together.
+    // The tile's requests and the first four of a thread are loaded once, together.
     const int own = min(i0 + (tid & (PRIO_TILE - 1)), n - 1);
     const int own_r = R[own], own_c = C[own];
     const double own_w = W[own], own_q = Wcur[own];
@@ -185,21 +187,23 @@ __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *_
 #pragma unroll
         for (int u = 0; u < NU; ++u) l[u] = 0;                           // (level 0 needs no threshold passed)
         if constexpr (MANY) {
+            int at[3][NU];                                               // a request's three chains of reads side by side
 #pragma unroll
-            for (int m = 0; m < 3; ++m) {
-                int at[NU];
+            for (int m = 0; m < 3; ++m)
 #pragma unroll
-                for (int u = 0; u < NU; ++u) at[u] = 0;
-                for (int h = 1 << (31 - __builtin_clz(G - 1)); h > 0; h >>= 1)
+                for (int u = 0; u < NU; ++u) at[m][u] = 0;
+            for (int h = 1 << (31 - __builtin_clz(G - 1)); h > 0; h >>= 1) {
+#pragma unroll
+                for (int m = 0; m < 3; ++m)
 #pragma unroll
                     for (int u = 0; u < NU; ++u) {
                         const double x = m == 0 ? (double)r[u] : m == 1 ? w[u] : (double)c[u];
-                        const int j = at[u] + h;
-                        at[u] = j < G && x > thr[min(j, G - 1) * 3 + m] ? j : at[u];
+                        const int j = at[m][u] + h;
+                        at[m][u] = (j < G) & (x > thr[min(j, G - 1) * 3 + m]) ? j : at[m][u];
                     }
-#pragma unroll
-                for (int u = 0; u < NU; ++u) l[u] = max(l[u], at[u]);
             }
+#pragma unroll
+            for (int u = 0; u < NU; ++u) l[u] = max(max(at[0][u], at[1][u]), at[2][u]);
             return;
         }
 #pragma unroll 2
@@ -227,11 +231,11 @@ __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *_
     uint32_t count[PRIO_TILE];
 #pragma unroll
     for (int t = 0; t < PRIO_TILE; ++t) count[t] = 0;
-    for (int b = tid; b < n; b += 4 * PRIO_THREADS) {
-        int l[4];
-        levels_of(std::integral_constant<int, 4>{}, r, w, c, l);
+    for (int b = tid; b < n; b += HELD * PRIO_THREADS) {
+        int l[HELD];
+        levels_of(std::integral_constant<int, HELD>{}, r, w, c, l);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < HELD; ++u) {
             const int j = b + u * PRIO_THREADS;
             const uint32_t lj = j < n ? (uint32_t)l[u] + 1 : 0u;         // (past the end: runs before nobody)
             // a request of lower index runs first at equal times: its image is compared with >= by adding one
@@ -239,15 +243,11 @@ __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *_
 #pragma unroll
             for (int t = 0; t < PRIO_TILE; ++t) count_larger(count[t], lj, wj, ml[t], mw[t]);
         }
-        // the next four: those that are held, then from memory
-#pragma unroll
-        for (int u = 0; u + 4 < HELD; ++u) { r[u] = r[u + 4]; w[u] = w[u + 4]; c[u] = c[u + 4]; q[u] = q[u + 4]; }
         if (b + HELD * PRIO_THREADS < n) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int i = min(b + HELD * PRIO_THREADS + u * PRIO_THREADS, n - 1);
-                constexpr int to = HELD - 4;
-                r[to + u] = R[i]; w[to + u] = W[i]; c[to + u] = C[i]; q[to + u] = Wcur[i];
+            for (int u = 0; u < HELD; ++u) {
+                const int i = min(b + (HELD + u) * PRIO_THREADS, n - 1);
+                r[u] = R[i]; w[u] = W[i]; c[u] = C[i]; q[u] = Wcur[i];
             }
         }
     }

@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
 
-@pytest.mark.parametrize("n,G", [(16, 6), (17, 2), (511, 6), (2048, 6), (2049, 32), (4096, 33), (4097, 6), (6145, 7), (9001, 64)])
+@pytest.mark.parametrize("n,G", [(16, 6), (17, 2), (511, 6), (2048, 6), (2049, 32), (4096, 33), (4097, 6), (6145, 7), (9001, 64),
+                                 (2047, 4), (2048, 20), (2049, 21), (4097, 21), (600, 1024)])
 def test_priority_requests_held_and_read_again(n, G):
     """Equal levels and equal times throughout, infinite times among them: places are decided by every word of the comparison."""
     gen = np.random.default_rng(n)
