@@ -248,7 +248,10 @@ inline int wide_shape(int cus, int64_t N, int d, int B) {
 //   queries that do not fit the LDS together, so that the corpus is read twice: 128 k x 1280, B = 48 / 56 77 / 83, 102 / 84; 300 k x 2048,
 //   B = 32 / 40 241 / 274, 323 / 275.
 //   rows of up to 128 bytes: 64 k x 64, B = 1 13.7 / 11.7; 1 M x 64, B = 1 45 / 38, B = 64 107 / 45; 4 M x 32, B = 8 133 / 96.  (1 M x 96, B = 8
-//   48 / 57, 300 k 23 / 25, 128 k 16.3 / 16.0.)
+//   48 / 57.)
+//   up to 16 queries, at most 480 bytes a row up to 128 Ki rows, 192 up to 512 Ki: 66 k x 112, B = 2 15.6 / 11.7; 55 k x 192, B = 1 17.4 / 13.7;
+//   81 k x 160, B = 10 19.1 / 13.2; 97 k x 160, B = 14 20.3 / 14.4; 72 k x 240, B = 6 19.3 / 16.6; 211 k x 96, B = 6 23.8 / 20.2; but 100 k x 248,
+//   B = 2 18.1 / 18.9; 112 k x 256, B = 14 18.2 / 19.2; 180 k x 224, B = 12 25.5 / 26.5; 454 k x 128, B = 14 29.7 / 31.1.
 //   up to 32 Ki rows: 20 k x 768, B = 16 / 24 16.2 / 18.9, 22.0 / 19.3; x 384, B = 24 16.4 / 16.5; 32 k x 768, B = 48 26 / 24.
 //   beyond, by groups of 16 queries against d: 64 k x 128, B = 16 / 24 13.3 / 13.2, 16.8 / 13.2; 64 k x 768, B = 32 / 48 31 / 33, 36 / 33;
 //   128 k x 256, B = 16 / 24 20.6 / 23.5, 24.8 / 23.7; 300 k x 128, B = 16 / 24 23 / 27, 28 / 27; 300 k x 256, B = 32 / 48 41 / 43, 47 / 44;
@@ -267,7 +270,7 @@ inline bool use_wide(int64_t N, int d, int dtype, int B, int k) {
     const int groups = (B + 15) / 16, steps = (d * 2 + 63) / 64;
     if (d <= 64 || (groups > 1 && groups * steps > STREAM_LDS_STEPS)) return true;
     if (N <= 32 * 1024) return B > 32 || (B > 16 && d >= 768);
-    if (B <= 16) return N <= 128 * 1024 && d <= 96;
+    if (B <= 16) return N <= 128 * 1024 ? d <= 240 : N <= 512 * 1024 && d <= 96;
     return many_queries(N, d, B) && !lists_settle(N, d, B);
 }
 

@@ -291,6 +291,22 @@ def test_many_queries_on_large_corpora(plans, N, d, B, k, kind):
         assert kind == "wide" or (p["rows"] == N and p["part"] == B)
 
 
+@pytest.mark.parametrize("N,d,B,kind", [                 # us, lists / maxima
+    (66_376, 112, 2, "wide"),                             # 15.6 / 11.7
+    (55_000, 192, 1, "wide"),                             # 17.4 / 13.7
+    (97_000, 160, 14, "wide"),                            # 20.3 / 14.4
+    (72_000, 240, 6, "wide"),                             # 19.3 / 16.6
+    (100_000, 248, 2, "lists"),                           # 18.1 / 18.9
+    (112_000, 256, 14, "lists"),                          # 18.2 / 19.2
+    (211_000, 96, 6, "wide"),                             # 23.8 / 20.2
+    (180_000, 224, 12, "lists"),                          # 25.5 / 26.5
+    (454_000, 128, 14, "lists"),                          # 29.7 / 31.1
+    (1_000_000, 96, 8, "lists"),                          # 48 / 57
+])
+def test_few_queries_against_the_length_of_rows(plans, N, d, B, kind):
+    assert KINDS[flat(plans, N, d, 0, B, 3, 1 << 34)["kind"]] == kind
+
+
 @pytest.mark.parametrize("N,d,B,k,buffer", [
     (5_000_000, 200, 60, 3, 200_000), (8_600_000, 120, 40, 12, 100_000), (1_500_000, 256, 64, 3, 150_000)])
 def test_lists_that_do_not_fit_leave_the_parts(plans, N, d, B, k, buffer):
