@@ -21,18 +21,19 @@
 //   gather   their adjacency rows; neighbours scored before are left out, the rest is numbered in order (every wave does
 //            this for itself); as many u's as fit 63 neighbours take part, the first always does
 //   score    one row group of 8 lanes per neighbour, all rows in flight at once; a neighbour that the step before scored without
-//            committing it brings its key along; the keys go round through LDS: the one barrier of a step
+//            committing it brings its key along; the keys go round through LDS: the one barrier of a step (a second after the
+//            marks where the visited set is in memory)
 //   commit   u_0 is expanded; u_j as well if no neighbour of u_0 .. u_{j-1} precedes it.  Those are the expansions that the
 //            search one by one makes, in its order, with its visited set.  What was scored for the others is dropped.
 //   insert   the neighbours of the committed nodes: into the lanes one by one if they are few, in the order of their ranks, which the
-//            row groups find, if not.  The next adjacency rows are asked for before the marks and counters are seen to.
+//            row groups find, if not (one more barrier).  The next adjacency rows are asked for before the marks and counters are seen to.
 //
 // Bound by the chain inside a step: 6.7 k clocks at 200 k x 768 fp16, ef = 2048 (wait for the adjacency rows 0.8, visited bits and
 // numbering 0.4, lookup of kept keys 0.6, rows 2.0, barrier, i.e. the other waves' rows through the one L1, 0.7, commit 0.5, insert
 // 0.8, rest 1.0) at 2.2 expansions a step for the slowest query.  The ordered list in LDS that this replaces cost 12 to 15 k clocks a
 // step: 64 list positions looked up, one list in two parts merged, cut and rebuilt.  us, before (the better of
-// graph_search_kernel and the steps on an ordered list) / now: 200 k x 768, B = 256, ef = 2048 5190 / 2480; B = 1, ef = 64 186 / 136
-// with its coarse search; maturity exit, 200 k x 384 bf16, ef = 256, B = 256 337 / 257; 1 M x 768, B = 512, ef = 8192 24.1 / 19.4 ms.
+// graph_search_kernel and the steps on an ordered list) / now: 200 k x 768, B = 256, ef = 2048 5190 / 2480; B = 1, ef = 64 178 / 115
+// with its coarse search; 1 M x 768, B = 512, ef = 8192 24.4 / 18.5 ms (more, and the maturity exit, at frontier_pays).
 // Keeping the keys of uncommitted neighbours takes the rows a step loads from 54 to 26 at ef = 2048; 64-bit compares instead
 // of maxima of doubles in the networks and insertions cost 4 % of a short list.  Not faster: 8 waves and two workgroups per compute
 // unit (413 us against 309 at B = 512, ef = 64: 128 registers a lane), the smallest place a neighbour stops found by LDS atomics before the

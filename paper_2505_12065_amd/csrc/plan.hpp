@@ -624,7 +624,7 @@ struct FrontierLds {
 // for the array find bounds all the time: 1 M x 768, B = 1024, ef = 4096 18.8 ms by two, 20.3 by three.)
 // width: trying 8 expansions instead of 4 costs a step some 500 clocks and pays where steps commit more than three: where a
 // search covers most of its graph (200 k x 768, B = 256, ef = 2048 2480 / 2580 us with 4 / 8; 60 k x 384, ef = 4096 3240 / 2770), and
-// with the maturity exit, which most queries leave while nearly every expansion stands (ef = 256, d = 384 312 / 257).
+// with the maturity exit, which most queries leave while nearly every expansion stands (200 k x 384 bf16, B = 256, ef = 256, the kernel as first built, 312 / 257).
 inline bool frontier_layout(int64_t N, int d, int elem_bytes, int ef, int waves, int per_cu, int width, int spare_min, FrontierLds &L) {
     auto up = [](uint32_t x) { return (x + 15u) & ~15u; };
     L = FrontierLds{};
