@@ -503,7 +503,7 @@ static bool frontier_takes(const DeviceState *st, int64_t N, int32_t d, int32_t 
                            float tau, float alpha, bool workspace, hipStream_t s, FrontierLds *L) {
     const int bytes = elem_bytes(dtype);
     *L = frontier_plan(st->cus, N, d, bytes, B, ef, counters && tau < 1.0f);
-    const bool pays = frontier_pays(st->cus, d * bytes, R, B, ef, counters, counters && exit_likely(tau, alpha, R, ef), *L);
+    const bool pays = frontier_pays(st->cus, N, d * bytes, R, B, ef, counters, counters && exit_likely(tau, alpha, R, ef), *L);
     if ((pays ? L->vis_mode == FRONTIER_VIS_GLOBAL : workspace) && !at_hand(st, st->vis, (size_t)B * (size_t)visited_words(N) * 4, s)) {
         FrontierLds in_lds;
         if (frontier_in_lds(N, d, bytes, R, ef, counters, in_lds)) {

@@ -2,6 +2,7 @@
 // kernel of the graph search.  Plain C++ without the GPU's headers, so that the rules can be compiled and looked at alone.
 #pragma once
 
+#include <limits.h>
 #include <math.h>
 #include <stddef.h>
 #include <stdint.h>
@@ -676,6 +677,39 @@ inline bool frontier_in_lds(int64_t N, int d, int elem_bytes, int R, int ef, boo
 // exits of 450 random calls against samples / (ef R): up to 1 76 to 91 %, 1 to 3 63 %, beyond 3 20 %.
 inline bool exit_likely(float tau, float alpha, int R, int ef) { return tau < 1.0f && -logf(1.0f - tau) < 3.0f * ef * R * alpha; }
 
+// Maturity exit: the shortest list that graph_frontier_kernel takes.  Lines drawn through 9260 calls (20 k to 2.5 M nodes, rows of 128 bytes to 4 KB,
+// R = 8 to 32, B = 1 to 2000, ef = 8 to 2048), both kernels timed for each.  Time above the better of the two, on average, by these lines / by
+// graph_search_kernel alone, in %: queries that leave B = 2 to 8 6 / 31, 9 to 256 0.4 / 68, 257 to 512 0.2 / 60, 513 to 768 0.1 / 67, more 0.3 / 51;
+// that stay B = 2 to 8 0.9 / 11, 9 to 256 0.3 / 13, 257 to 512 0.4 / 9, 513 to 768 0.2 / 35, to 1280 0.6 / 18, more 0.4 / 24.  One query is what its own
+// walk is (leaves 6 / 21, stays 2 / 29); all together 1.1.
+// What moves the lines: R (a step of 63 or 32 neighbours holds the expansions of several narrow rows); the rounds of workgroups (200 k x 768, R = 32,
+// ef = 384, queries that stay, this kernel's time over the other's: B = 600 0.83, 1024 1.08, 1990 0.94); the visited set in memory (B = 1024, R = 32,
+// ef = 192 1.3 M x 64 1.26, in LDS 200 k x 128 0.96, 40 k x 384, which it covers more of, 0.85); and long rows of a corpus beyond the caches: a step
+// scores some neighbours that it drops, at the rate of memory there (B = 1024, R = 32, ef = 512, rows of 1536 bytes 200 k 0.97, 400 k 1.24, 800 k 1.31;
+// 768 bytes, 1.3 M, 0.98).
+inline bool beyond_caches(int64_t N, int row_bytes) { return row_bytes > 1024 && N * row_bytes > (int64_t)448 << 20; }
+inline int frontier_from_leaving(int cus, int64_t N, int row_bytes, int R, int B, bool global) {
+    const bool long_rows = row_bytes > 1024, once = B <= 3 * cus;
+    if (B == 1) return global ? 144 : R <= 16 ? 48 : row_bytes > 256 ? 112 : 64;
+    if (B < 8) return long_rows || global ? 64 : 48;
+    if (B <= cus) return R <= 8 ? 72 : R <= 16 ? 56 : R <= 24 ? 40 : 32;
+    if (B <= 2 * cus) return R <= 8 ? 72 : R <= 16 ? (long_rows ? 72 : 56) : global ? 64 : long_rows && R <= 24 ? 56 : 40;
+    if (beyond_caches(N, row_bytes)) return once ? 96 : 144;
+    return !long_rows ? 40 : once ? 56 : R <= 8 ? 120 : 80;
+}
+inline int frontier_from_staying(int cus, int64_t N, int row_bytes, int R, int B, bool global) {
+    const bool long_rows = row_bytes > 1024, far = beyond_caches(N, row_bytes), once = B <= 3 * cus, most = B > 5 * cus;
+    if (B == 1 && !global) return 48;
+    if (B <= 8) return R <= 8 ? 48 : global ? 160 : R <= 16 ? 72 : 112;
+    if (B <= cus) return R <= 8 ? (long_rows ? 72 : 48) : R <= 16 ? (global || far ? 144 : 80) : global || far ? 288 : 144;
+    if (B <= 2 * cus) return R <= 8 ? (global ? 144 : 80) : R <= 16 ? (global || far ? 288 : 176) : global ? INT_MAX : far ? 1200 : 288;
+    if (R <= 8) return far ? (once ? 64 : most ? 96 : 256) : long_rows && !once ? 80 : 40;
+    if (R <= 16) return far ? (once ? 112 : 320) : long_rows && !once ? 144 : 48;
+    if (far) return once && R <= 24 ? 600 : INT_MAX;
+    if (global) return once ? 176 : most ? 240 : 448;
+    return long_rows ? (once ? 144 : 288) : once ? 40 : most ? 56 : 64 + (int)(N / 1536);
+}
+
 // Where graph_frontier_kernel is faster than the others (graph_search_kernel, graph_step_kernel, whichever was better), us, others / it:
 //   every query a compute unit to itself, R = 32: 200 k x 768 fp16, B = 256 ef = 16 93 / 91, 48 198 / 174, 192 587 / 427, 768 2202 / 1122,
 //     4096 7992 / 4101; B = 1 128 / 86, 416 / 226, 1916 / 558 at ef = 48, 192, 768; 60 k x 384 1121 / 510 (ef = 384); 1 M x 768 with the
@@ -691,26 +725,12 @@ inline bool exit_likely(float tau, float alpha, int R, int ef) { return tau < 1.
 //   visited set in memory: short lists stay with the id caches, which need no workspace; R = 32, B = 512, 1 M x 768 ef = 600 2215 /
 //     2516, 1024 3619 / 3799, 2048 6959 / 6364, 4096 13 421 / 10 524; R = 24 or rows of 256 bytes all of them (700 k, ef = 600 2086 /
 //     1983, 1907 / 1812)
-//   maturity exit, tau = 0.9: R = 32, 200 k x 384 bf16, B = 256 ef = 32 103 / 94, 64 174 / 113, 256 326 / 249, 2048 2249 / 1488; R = 16 B = 256
-//     ef = 32 106 / 128, 64 170 / 166; B = 1024 64 339 / 352, 96 429 / 427; one query, which may have left before it pays, 120 k x 256 fp32, ef = 92
-//     69 / 79, 40 k x 1024 fp32 99 83 / 103, but 200 k x 128, R = 16, 124 219 / 127; 100 k x 768, B = 512, R = 32 ef = 32 105 / 112, 40 122 / 116, R = 16
-//     64 186 / 208, 96 271 / 237, R = 8 96 291 / 285; B = 1024, R = 8 96 563 / 592, rows of 3 KB 128 1.09 times as long, 192 0.98.  tau = 3, or a window too long (no query leaves): B = 256 R = 32 64 318 / 319,
-//     128 535 / 516, R = 16 96 357 / 391, 200 651 / 641; B = 512 256 1036 / 1137, 512 2032 / 1891; 500 k x 128, B = 64 128 600 / 630, 256 943 / 837;
-//     visited set in memory, 1 M x 256: B = 512 512 2138 / 2678, 2048 7438 / 8428 (two of its workgroups a compute unit wait for more of
-//     these reads than hide), B = 1024 1024 7648 / 7185, B = 256 1024 3600 / 2894.  Medians of 680 more calls, it / others: B = 2 to 8 ef = 64 to 96
-//     0.95 to 1.01, 96 to 128 0.99; B = 9 to 256 64 to 96 1.02 to 1.07, 96 to 128 0.99 to 1.03, 128 to 192 0.94 to 0.98; B = 512, R = 16 128 to 192 1.08,
-//     256 to 384 0.86, R = 24 192 to 256 1.09, 256 to 384 0.94, R = 32 256 to 384 1.07, 384 to 512 0.95; B = 600 and more, R = 16 24 to 48 0.94, 96 to 128
-//     0.75, R = 24 96 to 128 1.02 (rows of 4 KB 1.12), 128 to 192 0.93, R = 32 128 to 192 0.93 to 1.11, 192 to 256 0.87 to 1.01
-inline bool frontier_pays(int cus, int row_bytes, int R, int B, int ef, bool counters, bool leaves, const FrontierLds &L) {
+//   no counters, visited set in memory, B = 600 / 1024: 0.31 to 0.97 times as long wherever measured (700 to 2048, 200 k to 2.5 M, rows of 128 to 1536 bytes)
+//   maturity exit: by the lines above
+inline bool frontier_pays(int cus, int64_t N, int row_bytes, int R, int B, int ef, bool counters, bool leaves, const FrontierLds &L) {
     if (R > GRAPH_STEP_MAX_R || L.total > LDS_MAX) return false;
     const bool global = L.vis_mode == FRONTIER_VIS_GLOBAL, own = B <= cus, waits = B > 2 * cus, long_rows = row_bytes > 2560;
-    if (counters) {
-        if (leaves && own) return ef >= (B == 1 ? 112 : R > 16 && B >= 8 ? 32 : 64);
-        if (leaves) return ef >= (waits ? (R > 8 || B > 6 * cus ? 96 : 176) : R > 16 ? 40 : R > 8 ? 72 : 112);
-        if (own) return ef >= (B <= 8 ? 96 : row_bytes > 256 ? 112 : 192);
-        if (waits) return ef >= (R <= 16 ? 48 : (R <= 24 || B > 6 * cus) && !long_rows ? 112 : 176);
-        return R <= 16 ? ef >= 224 : !global && ef >= (R <= 24 ? 256 : 448);
-    }
+    if (counters) return ef >= (leaves ? frontier_from_leaving(cus, N, row_bytes, R, B, global) : frontier_from_staying(cus, N, row_bytes, R, B, global));
     if (global && ef <= GRAPH_EF_TWO_LEVEL) return false;
     if (own) return ef >= (row_bytes > 2048 ? 72 : R > 16 ? 12 : 8);
     if (R <= 16) return ef >= (long_rows && !waits ? 36 : 16);

@@ -19,7 +19,7 @@ using namespace ann;
 extern "C" int graph_kernel(int cus, int64_t N, int row_bytes, int R, int B, int ef, int counters, float tau) {
     const bool leaves = counters && exit_likely(tau, 2.0f / 501, R, ef);                  // (a window of 500)
     const FrontierLds L = frontier_plan(cus, N, row_bytes / 2, 2, B, ef, counters && tau < 1);
-    if (frontier_pays(cus, row_bytes, R, B, ef, counters != 0, leaves, L)) return 1;
+    if (frontier_pays(cus, N, row_bytes, R, B, ef, counters != 0, leaves, L)) return 1;
     return !counters && graph_step_pays(cus, N, row_bytes, R, B, ef) ? 2 : 0;
 }
 extern "C" int leaves(float tau, int window, int R, int ef) { return exit_likely(tau, 2.0f / ((float)window + 1.0f), R, ef); }
@@ -118,7 +118,7 @@ NEVER = float("inf")                                  # no average passes it
     (200_000, 768, 32, 256, 32, 0.9, FRONTIER),           # 103 / 94
     (200_000, 768, 32, 256, 256, 0.9, FRONTIER),          # 326 / 249
     (200_000, 768, 16, 256, 32, 0.9, SEARCH),             # 106 / 128
-    (200_000, 768, 16, 1024, 64, 0.9, SEARCH),            # 339 / 352
+    (200_000, 768, 16, 1024, 64, 0.9, FRONTIER),          # 354 / 291
     (120_000, 1024, 32, 1, 92, 0.9, SEARCH),              # 69 / 79: one query
     (200_000, 256, 16, 1, 124, 0.9, FRONTIER),            # 219 / 127
     (100_000, 1536, 32, 512, 32, 0.9, SEARCH),            # 105 / 112
@@ -126,7 +126,7 @@ NEVER = float("inf")                                  # no average passes it
     (100_000, 1536, 16, 512, 64, 0.9, SEARCH),            # 186 / 208
     (100_000, 1536, 16, 512, 96, 0.9, FRONTIER),          # 271 / 237
     (100_000, 1536, 8, 512, 64, 0.9, SEARCH),             # 223 / 233
-    (100_000, 1536, 8, 1024, 96, 0.9, SEARCH),            # 563 / 592
+    (100_000, 1536, 8, 1024, 96, 0.9, SEARCH),            # 560 / 618
     (40_000, 4096, 16, 512, 22, None, SEARCH),            # 164 / 186
     (40_000, 4096, 16, 512, 64, None, FRONTIER),          # 329 / 311
     (40_000, 4096, 32, 1024, 96, None, SEARCH),           # 1002 / 1137
@@ -146,6 +146,22 @@ NEVER = float("inf")                                  # no average passes it
     (200_000, 512, 32, 1024, 160, NEVER, SEARCH),         # 1.11
     (1_000_000, 512, 32, 512, 2048, NEVER, SEARCH),       # 7438 / 8428: visited sets in memory, two workgroups a compute unit
     (1_000_000, 512, 32, 1024, 1024, NEVER, FRONTIER),    # 7648 / 7185
+    (40_000, 768, 32, 1024, 144, NEVER, FRONTIER),        # 0.92: the search covers more of a small graph
+    (200_000, 256, 24, 1024, 128, NEVER, SEARCH),         # 857 / 918, 1.06
+    (700_000, 256, 32, 1, 80, NEVER, FRONTIER),           # 0.60, 0.86, 0.61, 0.91: four queries
+    (1_300_000, 128, 24, 16, 128, NEVER, SEARCH),         # 1.20
+    (1_300_000, 128, 32, 64, 512, NEVER, FRONTIER),       # 0.90
+    (400_000, 1536, 32, 512, 1024, NEVER, SEARCH),        # rows that come from memory
+    (200_000, 1536, 32, 600, 384, NEVER, FRONTIER),       # 0.83
+    (1_300_000, 128, 32, 1024, 192, NEVER, SEARCH),       # 1.26
+    (1_300_000, 128, 32, 1990, 256, NEVER, FRONTIER),     # 0.94
+    (400_000, 1536, 16, 1024, 256, NEVER, SEARCH),        # 1.23
+    (400_000, 1536, 8, 1990, 128, NEVER, FRONTIER),       # 0.94
+    (800_000, 1536, 24, 600, 700, NEVER, FRONTIER),       # 0.98
+    (800_000, 1536, 32, 1024, 512, NEVER, SEARCH),        # 1.31
+    (700_000, 256, 8, 600, 64, 0.9, FRONTIER),            # 0.79
+    (800_000, 1536, 32, 1024, 128, 0.9, SEARCH),          # 1.04
+    (800_000, 1536, 24, 1024, 192, 0.9, FRONTIER),        # 0.93
 ])
 def test_graph_kernels_where_they_were_measured_to_pay(plans, N, row, R, B, ef, tau, kernel):
     assert plans.graph_kernel(CUS, N, row, R, B, ef, tau is not None, NEVER if tau is None else tau) == kernel
