@@ -36,6 +36,7 @@ def _random(N, d, R, B, dtype, seed):
     (torch.float16, 3000, 136, 16, 513, 130, 70, 6),     # three workgroups
     (torch.float16, 120_000, 64, 32, 2, 16_384, 130, 7),  # visited set in memory
     (torch.float16, 40, 8, 1, 2, 40, 40, 8),             # one chunk, one slot: a path
+    (torch.bfloat16, 9000, 776, 8, 257, 80, 5, 9),       # two workgroups, with the counters too
 ])
 def test_graph_frontier(dtype, N, d, R, B, ef, k, seed):
     say(f"frontier: {dtype} N={N} d={d} R={R} B={B} ef={ef} k={k}")
