@@ -199,6 +199,22 @@ int flat_search_run(const FlatPlan &pl, const void *X, int64_t N, int d, int dty
     // launches are recorded by the class of the call, as ann.h lists them, not by the kernel that its sizes choose
     const int code = dtype == ANN_F32 ? ANN_KERNEL_FLAT_F32
                      : B >= WIDE_MIN_B && d % 32 == 0 ? ANN_KERNEL_FLAT_WIDE : ANN_KERNEL_FLAT_STREAM;
+    if (pl.quick) {
+        TimedScope timed(code, stream);
+        return check_launch("flat_direct_kernel",
+                            launch_flat_direct(dtype, X, N, d, Q, B, k, ids, scores, after, stream));
+    }
+    if (pl.scores) {
+        float *maxima = static_cast<float *>(ws);
+        hipError_t e;
+        {
+            TimedScope timed(code, stream);
+            e = launch_flat_scores(dtype, X, N, d, Q, B, maxima, pl.w.n, after, stream);
+        }
+        if (int rc = check_launch("flat_scores_kernel", e)) return rc;
+        return check_launch("flat_pick_kernel",
+                            launch_flat_pick(pl.w, dtype, X, N, d, Q, B, k, maxima, ids, scores, after, nullptr, 0, stream));
+    }
     StreamOut direct;
     if (pl.direct) direct = StreamOut{ids, scores, k};
     auto stream_kernel = [&](const FlatPlan &one, const void *x, int64_t rows, const void *q, int b, Cand *partial, float *maxima,

@@ -53,6 +53,8 @@ hipError_t pick(const WidePlan &pl, const void *X, int64_t N, int d, const void 
     };
     auto parts = [&](auto pc) {
         constexpr bool P = decltype(pc)::value;
+        if constexpr (!P)
+            if (one && pl.wmf == 0) return go(flat_pick_kernel<T, 0, true, false, false>);
         if constexpr (T::bytes == 2)
             if (one) return pl.wmf == 4 ? go(flat_pick_kernel<T, 4, true, P, false>) : pl.wmf == 2 ? go(flat_pick_kernel<T, 2, true, P, false>) : go(flat_pick_kernel<T, 1, true, P, false>);
         return pick_runs(pl.cus, (size_t)d * T::bytes, T::bytes == 4 ? 64 : 32, B) ? form(pc, std::true_type{}) : form(pc, std::false_type{});

@@ -33,6 +33,12 @@ hipError_t launch_flat_stream_bf16(const StreamPlan &pl, const void *X, int64_t 
                                   float *maxima, int64_t n, StreamOut out, After after, hipStream_t stream);
 hipError_t launch_flat_stream_f32(const StreamPlan &pl, const void *X, int64_t N, int d, const void *Q, int B, Cand *partial,
                                   float *maxima, int64_t n, StreamOut out, After after, hipStream_t stream);
+// All scores of few queries and few rows: maxima [B, n].
+hipError_t launch_flat_scores(int dtype, const void *X, int64_t N, int d, const void *Q, int B, float *maxima, int64_t n, After after,
+                              hipStream_t stream);
+// N <= DIRECT_ROWS: the answer.
+hipError_t launch_flat_direct(int dtype, const void *X, int64_t N, int d, const void *Q, int B, int k, int32_t *ids, float *scores,
+                              After after, hipStream_t stream);
 // Large batches on the matrix cores (16-bit corpora): maxima [B, pl.n].
 hipError_t launch_flat_wide(const WidePlan &pl, int dtype, const void *X, int64_t N, int d, const void *Q, int B, float *maxima,
                             After after, hipStream_t stream);

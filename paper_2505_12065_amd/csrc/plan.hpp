@@ -23,6 +23,8 @@ constexpr int LANE_KP = 4;                            // entries of a lane's lis
 constexpr int STREAM_NQG_MAX(int elem_bytes) { return elem_bytes == 2 ? 4 : 2; }   // fp32: eight accumulators a group
 constexpr int STREAM_WG_PER_CU(int elem_bytes, int nqg, int waves) { return waves == 16 || (elem_bytes == 4 && nqg > 1) ? 1 : 2; }
 
+constexpr int STREAM_LDS_STEPS = (int)((LDS_MAX - 16 * 1024) / (WAVE * 16));   // steps of 64 bytes of a group of 16 queries that LDS holds
+
 // Geometry and options of a flat_stream_kernel launch.
 struct StreamPlan {
     int nqg = 1;                 // groups of 16 queries a workgroup serves, 1 .. STREAM_NQG_MAX
@@ -102,9 +104,36 @@ inline int wide_rows(int shape) {                         // corpus rows of a ti
 // ---- exact search, the whole call ----------------------------------------------------------------------
 constexpr int P_MAX = 2048;      // most slabs of the streaming kernel
 
+// Few queries against few rows.  flat_scores_kernel: tiles of 16 rows x 16 queries, a wave each, and flat_pick_kernel.  It has no tile
+// that spares the L1s, so the line is that of the bytes they bring in; short rows make the pick, which looks at every score, the larger part, and
+// more than 64 queries fill the tiles of the matrix-core kernel.  Fitted to 900 calls of 129 to 60 000 rows, B = 1 to 1024, rows of 128 bytes to 4 KB,
+// others / this, us: up to 250 tiles 0.73 times as long on average (fp32 0.66), 200 x 768, B = 1 8.5 / 6.3; 21 025 x 480, B = 14 13.8 / 12.4; 32 877 x
+// 544, B = 3 24.6 / 17.1; but 15 197 x 704, B = 43 13.1 / 24.3; 33 953 x 64, B = 8 10.0 / 12.6; 1024 x 768, B = 512 10.4 / 17.3.
+// flat_direct_kernel: one launch, up to 128 rows in one workgroup, which then has them all to bring in: 31 x 928, B = 8 5.8 (scores 6.7), 26 x
+// 1760, B = 4 6.8; from some 60 KB (fp32, whose products are longer, 100) scores: 16 bits 10.9 / 6.9 beyond 160 KB.  The streaming kernel's one
+// slab starts quicker where there is hardly a row (7 x 32, B = 2 4.0 / 4.8) and holds two workgroups a compute unit for many queries (3 x 832 fp32,
+// B = 11 876 25.4 / 37.2).
+constexpr int DIRECT_WAVES = 8, DIRECT_ROWS = 16 * DIRECT_WAVES;
+inline int direct_held(int d, int elem_bytes) {           // steps of a query in LDS
+    const int steps = ((d * elem_bytes + 63) / 64 + 3) & ~3;
+    return steps < STREAM_LDS_STEPS ? steps : STREAM_LDS_STEPS;
+}
+inline size_t direct_lds_bytes(int d, int elem_bytes) {
+    const size_t q = (size_t)direct_held(d, elem_bytes) * WAVE * 16, m = 16 * (4 * DIRECT_WAVES * LANE_KP + 4) * CAND_BYTES;
+    return q > m ? q : m;
+}
+inline int64_t score_tiles(int64_t N, int B) { return (N + 15) / 16 * (((int64_t)B + 15) / 16); }
+inline bool scores_pay(int64_t N, int row_bytes, int dtype, int B) {
+    const double most = dtype == ANN_F32 ? 48e3 : B <= 64 ? 95e3 : 35e3;
+    return (double)score_tiles(N, B) * sqrt(row_bytes + 256.0) * (1 + (double)N / (100.0 * row_bytes)) <= most;
+}
+inline bool direct_pays(int64_t N, int row_bytes, int dtype) { return N <= DIRECT_ROWS && N * row_bytes < (dtype == ANN_F32 ? 100 : 60) * 1000; }
+
 struct FlatPlan {
+    bool scores;             // flat_scores_kernel and flat_pick_kernel (w.n scores a query), or
     StreamPlan st;           // streaming kernel with lists, unless
     bool direct;             // ... of one slab: no merge
+    bool quick;              // ... by flat_direct_kernel
     bool wide;               // the matrix-core kernel, or
     bool maxima;             // the streaming kernel with group maxima takes the call, `part` queries and `rows` rows at a time
     WidePlan w;
@@ -127,7 +156,6 @@ constexpr int64_t PART_MIN_ROWS = 8192;          // fewer are not worth a launch
 
 // The streaming kernel's geometry.
 // K: see the kernel; unit: rows that go to a wave together.
-constexpr int STREAM_LDS_STEPS = (int)((LDS_MAX - 16 * 1024) / (WAVE * 16));   // steps of 64 bytes of a group of 16 queries that LDS holds
 inline StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int K, int unit) {
     StreamPlan pl;
     pl.K = K;
@@ -403,12 +431,22 @@ inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, si
     FlatPlan pl{};
     pl.part = B;
     pl.rows = N;
-    // A corpus of one tile per wave of a workgroup: its lists are the answer, one launch instead of two (128 x 768 fp16, k = 1:
-    // B = 64 13.9 -> 10.8 us, B = 512 12.4 -> 11.1; 64 x 1024, B = 8192, k = 16 23.1 -> 17.3).  Lists of 4 per lane are complete
-    // there whatever k is, since a lane sees four rows; selecting k > 4 from all eight waves costs more than the launch
-    // saves where the other way is group maxima (128 x 1024 bf16, B = 5000, k = 16: 19.3 / 23.3).
-    pl.maxima = dtype == ANN_F32 && use_f32_maxima(N, d, B, k);
-    pl.direct = !pl.maxima && N <= (k <= 4 || dtype == ANN_F32 ? 128 : 64);
+    const int row_bytes = d * elem_bytes(dtype);
+    const size_t scores = (size_t)B * (size_t)((N + 3) & ~(int64_t)3) * sizeof(float);
+    const bool few = scores_pay(N, row_bytes, dtype, B);
+    pl.scores = few && scores <= limit && !direct_pays(N, row_bytes, dtype);
+    if (pl.scores) {
+        pl.w.cus = cus;
+        pl.w.n = (N + 3) & ~(int64_t)3;
+        pl.ws_bytes = scores;
+        return pl;
+    }
+    // A corpus of one tile per wave of a workgroup: its lists are the answer, one launch instead of two (64 x 1024, B = 8192, k = 16 23.1 -> 17.3 us),
+    // and no workspace.  Lists of 4 per lane are complete there whatever k is, since a lane sees four rows; selecting k > 4 from all eight
+    // waves costs more than the launch saves where the other way is group maxima (128 x 1024 bf16, B = 5000, k = 16: 19.3 / 23.3).
+    pl.maxima = !(few && N <= DIRECT_ROWS) && dtype == ANN_F32 && use_f32_maxima(N, d, B, k);
+    pl.direct = !pl.maxima && N <= (few || k <= 4 || dtype == ANN_F32 ? DIRECT_ROWS : DIRECT_ROWS / 2);
+    if (pl.direct && N * row_bytes >= 2000 && (B + 15) / 16 <= cus) pl.quick = true;
     pl.wide = !pl.direct && use_wide(N, d, dtype, B, k);
     auto plan = [&] {
         if (pl.wide || pl.maxima) maxima_plan(pl, cus, N, d, dtype, B, k, limit);
