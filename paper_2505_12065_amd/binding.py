@@ -1,10 +1,14 @@
 """ctypes binding of libann.so: the same entry points as include/ann.h, taking
 torch device tensors.  Argument marshalling only — shapes, pointers, the current
 HIP stream; every step of the search runs in the library's kernels.  There is no
-fallback: if the library is missing or a call fails, an exception is raised."""
+fallback: if the library is missing or a call fails, an exception is raised.
+
+Calls of the usual form are marshalled in native code (csrc/marshal.cpp), which hands every other one back."""
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 from typing import Optional, Tuple
 
@@ -80,7 +84,27 @@ def lib() -> ctypes.CDLL:
             if name not in ("ann_last_error", "ann_flat_workspace_bytes", "ann_graph_nonstall_workspace_bytes"):
                 getattr(L, name).restype = c.c_int
         _lib = L
+        _load_marshal(L)
     return _lib
+
+
+_marshal = None
+
+
+def _load_marshal(L: ctypes.CDLL) -> None:
+    """csrc/marshal.cpp is built against one torch; where it does not load, every call is marshalled here."""
+    global _marshal
+    path = os.path.join(_HERE, "_marshal.so")
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", path, loader=loader))
+        loader.exec_module(module)
+    except ImportError:
+        return
+    module.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
+                  (L.ann_flat_search_typed, L.ann_flat_search_after_typed, L.ann_graph_search_typed, L.ann_graph_search_entries_typed,
+                   L.ann_graph_search_nonstall_typed, L.ann_gather_ids, L.ann_priority_order)))
+    _marshal = module
 
 
 def _check(rc: int) -> None:
@@ -91,6 +115,23 @@ def _check(rc: int) -> None:
 # The stream's handle without a Stream object around it (2.5 us), where this torch has the call for it
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or \
     (lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
+_current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+
+
+def _usual(function: str, first, *rest):
+    """What csrc/marshal.cpp answers to a call on the current device and stream; None: it is not of the usual form."""
+    if not getattr(first, "is_cuda", False):
+        return None
+    lib()
+    if _marshal is None:
+        return None
+    device = _current_device()
+    out = getattr(_marshal, function)(first, *rest, device, _raw_stream(device))
+    if type(out) is int:
+        _check(out)
+    return out
 
 
 def _stream(stream, index: int) -> int:
@@ -143,6 +184,14 @@ def ann_flat_search_typed(corpus: torch.Tensor, queries: torch.Tensor, k: int, *
     """Exact top-k of every query over the corpus; element type taken from the tensors.
     after = (scores float32 [B], ids int32 [B]) device tensors: the continuation entry point, the k best rows
     that come strictly after that pair in the order."""
+    if ids is None and scores is None and stream is None:
+        out = None
+        if after is None:
+            out = _usual("flat", corpus, queries, k, None, None)
+        elif type(after) is tuple and len(after) == 2 and after[0] is not None:
+            out = _usual("flat", corpus, queries, k, *after)
+        if out is not None:
+            return out
     _matrix(corpus, "corpus"), _matrix(queries, "queries")
     if queries.dtype != corpus.dtype or queries.shape[1] != corpus.shape[1]:
         raise ValueError("queries must have the corpus' element type and dimension")
@@ -202,6 +251,10 @@ def _graph(graph: torch.Tensor, N: int) -> torch.Tensor:
 def ann_graph_search_typed(corpus: torch.Tensor, graph: torch.Tensor, entry: int, queries: torch.Tensor, k: int,
                            ef: int, *, ids=None, scores=None, stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """Best-first graph search with a candidate list of ef entries."""
+    if ids is None and scores is None and stream is None and type(entry) is int:
+        out = _usual("graph", corpus, graph, entry, queries, k, ef)
+        if out is not None:
+            return out
     _matrix(corpus, "corpus"), _matrix(queries, "queries")
     if queries.dtype != corpus.dtype or queries.shape[1] != corpus.shape[1]:
         raise ValueError("queries must have the corpus' element type and dimension")
@@ -220,6 +273,10 @@ def ann_graph_search_nonstall_typed(corpus: torch.Tensor, graph: torch.Tensor, e
     """Graph search with the maturity (non-stall) exit.  `engine_ready` is an int32 tensor of one
     element on the device or in pinned host memory (None = always ready).  Returns
     (ids, scores, stats [B,3] = (early, scored, expansions), ema [B])."""
+    if engine_ready is None and ids is None and scores is None and stats is None and ema is None and stream is None:
+        out = _usual("nonstall", corpus, graph, entry, queries, k, ef, entries, tau, window)
+        if out is not None:
+            return out
     _matrix(corpus, "corpus"), _matrix(queries, "queries")
     if queries.dtype != corpus.dtype or queries.shape[1] != corpus.shape[1]:
         raise ValueError("queries must have the corpus' element type and dimension")
@@ -279,6 +336,10 @@ def ann_graph_search_entries_typed(corpus: torch.Tensor, graph: torch.Tensor, en
                                    queries: torch.Tensor, k: int, ef: int, *, ids=None, scores=None,
                                    stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """Graph search with one entry node per query."""
+    if ids is None and scores is None and stream is None:
+        out = _usual("graph", corpus, graph, entries, queries, k, ef)
+        if out is not None:
+            return out
     _matrix(corpus, "corpus"), _matrix(queries, "queries")
     if queries.dtype != corpus.dtype or queries.shape[1] != corpus.shape[1]:
         raise ValueError("queries must have the corpus' element type and dimension")
@@ -295,6 +356,10 @@ def ann_graph_search_entries_typed(corpus: torch.Tensor, graph: torch.Tensor, en
 
 def ann_gather_ids(table: torch.Tensor, idx: torch.Tensor, *, out=None, stream=None) -> torch.Tensor:
     """out[i] = table[idx[i]] (-1 where idx[i] is out of range); int32 device tensors."""
+    if out is None and stream is None:
+        usual = _usual("gather", table, idx)
+        if usual is not None:
+            return usual[0]
     for t in (table, idx):
         if t.dtype != torch.int32 or not t.is_contiguous() or not t.is_cuda:
             raise ValueError("table and idx must be contiguous int32 device tensors")
@@ -313,6 +378,10 @@ KERNEL_FLAT_STREAM, KERNEL_FLAT_WIDE, KERNEL_FLAT_F32, KERNEL_GRAPH = 0, 1, 2, 3
 def ann_priority_order(R: torch.Tensor, W: torch.Tensor, C: torch.Tensor, Wcur: torch.Tensor, G: int = 6, *,
                        stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """Scheduler priority levels and execution order.  R, C int32 [n]; W, Wcur float64 [n]; device tensors."""
+    if stream is None:
+        out = _usual("order", R, W, C, Wcur, G)
+        if out is not None:
+            return out
     n = R.numel()
     for t, dt in ((R, torch.int32), (C, torch.int32), (W, torch.float64), (Wcur, torch.float64)):
         if t.dtype != dt or t.numel() != n or not t.is_contiguous() or not t.is_cuda:

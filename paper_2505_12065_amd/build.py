@@ -1,5 +1,6 @@
 """Build libann.so (gfx950) from csrc/*.hip with hipcc: one object per
-translation unit, compiled in parallel, linked into the package directory."""
+translation unit, compiled in parallel, linked into the package directory; and _marshal.so,
+the binding's native half, from csrc/marshal.cpp with the host compiler and torch's headers."""
 from __future__ import annotations
 
 import os
@@ -11,6 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libann.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # -packed-fp32-ops is switched off on purpose: some packed fp32 forms have been
 # seen to give wrong results on the test machines.
@@ -44,10 +46,26 @@ def _compile(src: str, force: bool) -> str:
     return obj
 
 
+def _build_marshal(force: bool) -> None:
+    src = os.path.join(CSRC, "marshal.cpp")
+    if not force and os.path.exists(MARSHAL) and os.path.getmtime(MARSHAL) > max(os.path.getmtime(src), _headers_mtime()):
+        return
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    include = [f"-isystem{p}" for p in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]]
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+                           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *include, src, "-o", MARSHAL,
+                           f"-L{libs}", "-ltorch_python", "-ltorch_cpu", "-lc10"])
+
+
 def build_library(force: bool = True, jobs: int = 8) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        marshal = ex.submit(_build_marshal, force)
         objs = list(ex.map(lambda s: _compile(s, force), _sources()))
+        marshal.result()
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
     return LIB
 

@@ -1,0 +1,97 @@
+"""The native half of the binding: the same answers and the same refusals as the Python half."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2505_12065_amd as ann
+from paper_2505_12065_amd import binding
+
+DEV = "cuda"
+
+
+def test_other_forms_are_handed_back():
+    """Tensors that are not on a device, wrong counts of arguments and modes that look at calls: for the Python to deal with."""
+    binding.lib()
+    m = binding._marshal
+    assert m is not None, "_marshal.so does not load: build it with python -m paper_2505_12065_amd.build"
+    x, i = torch.zeros(4, 8), torch.zeros(4, dtype=torch.int32)
+    assert m.flat(x, x, 1, None, None, 0, 0) is None
+    assert m.flat(x, x, 1) is None and m.flat(None, x, 1, None, None, 0, 0) is None
+    assert m.graph(x, i, 0, x, 1, 4, 0, 0) is None
+    assert m.nonstall(x, i, 0, x, 1, 4, None, 0.9, 500, 0, 0) is None
+    assert m.gather(i, i, 0, 0) is None
+    assert m.order(i, x, i, x, 6, 0, 0) is None
+    for call in (lambda: ann.ann_flat_search_typed(x, x, 1), lambda: ann.ann_gather_ids(i, i),
+                 lambda: ann.ann_priority_order(i, x[0].double(), i, x[0].double())):
+        with pytest.raises(ValueError):
+            call()
+
+
+def both(call, monkeypatch):
+    """What a call gives, or raises, by either half."""
+    got = []
+    for native in (True, False):
+        with monkeypatch.context() as m:
+            if not native:
+                m.setattr(binding, "_marshal", None)
+            try:
+                out = call()
+                got.append([t.cpu() for t in (out if isinstance(out, tuple) else (out,))])
+            except Exception as e:                    # noqa: BLE001
+                got.append((type(e), str(e)))
+    return got
+
+
+@pytest.mark.gpu
+def test_both_halves_give_the_same(monkeypatch):
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    x = torch.nn.functional.normalize(torch.randn(3000, 64, generator=gen, device=DEV), dim=1).half()
+    q = x[:9].contiguous()
+    g = torch.randint(0, 3000, (3000, 16), generator=gen, device=DEV, dtype=torch.int32)
+    e = torch.arange(9, device=DEV, dtype=torch.int32)
+    ids, sc = ann.ann_flat_search_typed(x, q, 4)
+    after = (sc[:, -1].contiguous(), ids[:, -1].contiguous())
+    n = torch.arange(40, device=DEV)
+    w = n.double()
+    r = n.int()
+    stream = torch.cuda.Stream()
+    calls = [
+        lambda: ann.ann_flat_search_typed(x, q, 4), lambda: ann.ann_flat_search_typed(x, q, 4, after=after),
+        lambda: ann.ann_graph_search_typed(x, g, 7, q, 3, 20), lambda: ann.ann_graph_search_entries_typed(x, g, e, q, 3, 20),
+        lambda: ann.ann_graph_search_nonstall_typed(x, g, 7, q, 3, 20),
+        lambda: ann.ann_graph_search_nonstall_typed(x, g, 0, q, 3, 20, entries=e, tau=3, window=20),
+        lambda: ann.ann_graph_search_nonstall_typed(x, g, 0, q, 3, 20, entries=e.view(9, 1), tau=0.5),
+        lambda: ann.ann_gather_ids(r, e), lambda: ann.ann_gather_ids(r, e.view(3, 3)), lambda: ann.ann_priority_order(r, w, r, w),
+        lambda: ann.ann_priority_order(r, w, r, w, 3), lambda: ann.ann_flat_search_typed(x, q[:0], 4),
+        # numbers of other kinds, refusals of either half and of the library
+        lambda: ann.ann_flat_search_typed(x, q, np.int64(4)), lambda: ann.ann_flat_search_typed(x, q, 0),
+        lambda: ann.ann_flat_search_typed(x, q, -1), lambda: ann.ann_flat_search_typed(x, q, 17),
+        lambda: ann.ann_flat_search_typed(x, q.float(), 4), lambda: ann.ann_flat_search_typed(x.T, q, 4),
+        lambda: ann.ann_flat_search_typed(x.double(), q.double(), 4), lambda: ann.ann_flat_search_typed(x, q.cpu(), 4),
+        lambda: ann.ann_flat_search_typed(x, q[0], 4), lambda: ann.ann_flat_search_typed(x, q, 4, after=(None, None)),
+        lambda: ann.ann_flat_search_typed(x, q, 4, after=(after[0][:3], after[1])),
+        lambda: ann.ann_flat_search_typed(x, q, 4, after=after[:1]), lambda: ann.ann_graph_search_typed(x, g, 3000, q, 3, 20),
+        lambda: ann.ann_graph_search_typed(x, g, 7, q, 30, 20), lambda: ann.ann_graph_search_typed(x, g[:5], 7, q, 3, 20),
+        lambda: ann.ann_graph_search_entries_typed(x, g, e.view(9, 1), q, 3, 20),
+        lambda: ann.ann_graph_search_entries_typed(x, g, e[:4], q, 3, 20),
+        lambda: ann.ann_graph_search_nonstall_typed(x, g, 7, q, 3, 20, tau=float("nan")),
+        lambda: ann.ann_graph_search_nonstall_typed(x, g, 7, q, 3, 20, window=0),
+        lambda: ann.ann_gather_ids(r, e.long()), lambda: ann.ann_priority_order(r, w, r, w[:3]),
+        lambda: ann.ann_priority_order(r, w, r, w, 0),
+    ]
+    refused = 0
+    for number, call in enumerate(calls):
+        print("call", number, flush=True)
+        a, b = both(call, monkeypatch)
+        if isinstance(b, tuple):
+            assert a == b, (number, a, b)
+            refused += 1
+        else:
+            assert not isinstance(a, tuple), (number, a)
+            assert len(a) == len(b) and all(s.dtype == t.dtype and s.shape == t.shape and torch.equal(s, t) for s, t in zip(a, b)), number
+    assert refused == len(calls) - 13                  # the first 13 are answered
+    # another stream and inference tensors
+    with torch.cuda.stream(stream), torch.inference_mode():
+        a, b = both(lambda: ann.ann_flat_search_typed(x, q, 4), monkeypatch)
+        stream.synchronize()
+    assert torch.equal(a[0], ids.cpu()) and torch.equal(b[0], ids.cpu())
