@@ -21,19 +21,21 @@
 //   gather   their adjacency rows; neighbours scored before are left out, the rest is numbered in order (every wave does
 //            this for itself); as many u's as fit 63 neighbours take part, the first always does
 //   score    one row group of 8 lanes per neighbour, all rows in flight at once; a neighbour that the step before scored without
-//            committing it brings its key along; the keys go round through LDS: the one barrier of a step (a second after the
+//            committing it brings its key along, the others fill the row groups without a gap; the keys go round through LDS: the one barrier of a step (a second after the
 //            marks where the visited set is in memory)
 //   commit   u_0 is expanded; u_j as well if no neighbour of u_0 .. u_{j-1} precedes it.  Those are the expansions that the
 //            search one by one makes, in its order, with its visited set.  What was scored for the others is dropped.
 //   insert   the neighbours of the committed nodes: into the lanes one by one if they are few, in the order of their ranks, which the
 //            row groups find, if not (one more barrier).  The next adjacency rows are asked for before the marks and counters are seen to.
 //
-// Bound by the chain inside a step: 6.7 k clocks at 200 k x 768 fp16, ef = 2048 (wait for the adjacency rows 0.8, visited bits and
-// numbering 0.4, lookup of kept keys 0.6, rows 2.0, barrier, i.e. the other waves' rows through the one L1, 0.7, commit 0.5, insert
-// 0.8, rest 1.0) at 2.2 expansions a step for the slowest query.  The ordered list in LDS that this replaces cost 12 to 15 k clocks a
-// step: 64 list positions looked up, one list in two parts merged, cut and rebuilt.  us, before (the better of
-// graph_search_kernel and the steps on an ordered list) / now: 200 k x 768, B = 256, ef = 2048 5190 / 2480; B = 1, ef = 64 178 / 115
-// with its coarse search; 1 M x 768, B = 512, ef = 8192 24.4 / 18.5 ms (more, and the maturity exit, at frontier_pays).
+// Bound by the chain inside a step: 6.3 k clocks at 200 k x 768 fp16, ef = 2048, B = 256 (wait for the adjacency rows 0.6, visited bits
+// and numbering 0.5, lookup of kept keys 0.3, rows 2.2, barrier 0.3, commit 0.5, insert 0.8, queue and pool 0.6, marks 0.4) at 2.2
+// expansions a step for the slowest query; 8.4 k at ef = 64, where 40 rows take 3.1 and the insertion of as many keys 1.6.  A load
+// instruction of 16 bytes a lane takes the memory path 16 clocks, for one row of eight or for all: 24 rows spread over eight waves
+// keep it as busy as 64 (0.80 us a step from the L2, 0.41 without gaps; 8 rows 0.80 / 0.23).  Without gaps, us: B = 256, ef = 2048 2457 / 2266;
+// B = 1, ef = 64 with its coarse search 108 / 99.5; maturity exit, 200 k x 384 bf16, B = 256, ef = 256 268 / 261.
+// The ordered list in LDS that this replaces cost 12 to 15 k clocks a step: 64 list positions looked up, one list in two parts merged, cut
+// and rebuilt (200 k x 768, B = 256, ef = 2048 5190 us; more, and the maturity exit, at frontier_pays).
 // Keeping the keys of uncommitted neighbours takes the rows a step loads from 54 to 26 at ef = 2048; 64-bit compares instead
 // of maxima of doubles in the networks and insertions cost 4 % of a short list.  Not faster: 8 waves and two workgroups per compute
 // unit (413 us against 309 at B = 512, ef = 64: 128 registers a lane), the smallest place a neighbour stops found by LDS atomics before the
@@ -336,6 +338,9 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int *ent = reinterpret_cast<int *>(smem + FrontierLds::WAVES + wave * FrontierLds::WAVE_BYTES);   // [64] this wave's list of the neighbours, and [64]
     int *ent_u = ent + FrontierLds::WAVE_BYTES / 8;                                                   // whose they are (and a place for the rest)
+    auto again_of = [&](int w) {                          // [2] which neighbours of wave w's share an earlier one names, behind its list
+        return reinterpret_cast<uint32_t *>(smem + FrontierLds::WAVES + w * FrontierLds::WAVE_BYTES + FrontierLds::WAVE_BYTES - 12);
+    };
     uint64_t *tops = reinterpret_cast<uint64_t *>(smem + FrontierLds::WAVES);           // [NW][64], in the place of the waves' lists
     uint64_t *A = reinterpret_cast<uint64_t *>(smem + L.keys);                         // [cap] expanded from the left, pool from the right
     uint32_t *bits = reinterpret_cast<uint32_t *>(smem + L.vis);
@@ -346,7 +351,7 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
     const int nch = d * T::bytes / 16;                    // 16-byte chunks per row
     uint32_t *gbits = VIS == FRONTIER_VIS_GLOBAL ? ns.visited + (size_t)b * ns.words : nullptr;   // zero on entry
     const int sub = lane & (LANES_PER_ROW - 1);           // lane's position inside its row group
-    const int grp = tid / LANES_PER_ROW;                  // takes neighbours grp, grp + GROUPS
+    const int grp = tid / LANES_PER_ROW;                  // takes the grp-th neighbour that is not known
 
     for (int c = tid; c < nch; c += NT) qs[c] = load_chunk(static_cast<const char *>(args.Q) + ((size_t)b * nch + c) * 16);
     if constexpr (VIS == FRONTIER_VIS_LDS)
@@ -631,65 +636,59 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
         const int n_ent = __builtin_amdgcn_readlane(upto, n_part - 1);                                   // neighbours of the step
 
         // ---- score ---------------------------------------------------------------------------------------------
-        // Row group g looks after neighbours g and (of 32 groups) 63 - g.  A neighbour named twice in the step belongs to the
-        // first that names it: the 8 lanes of the group look at the neighbours before theirs.  One that the step before
-        // has scored but not committed brings its key along.  Of the rest a group scores one; a second is left unknown.
-        int v[SETS], slot[SETS];
-        uint64_t k_of[SETS];
-        int4 oa, ob;
+        // Lane i of every wave looks after neighbour i.  One that the step before has scored but not committed brings its key
+        // along; the rest goes to the row groups without a gap, since a load instruction takes the memory path as long for one row as for
+        // eight.  More than there are groups are left unknown.
+        const int mine = ent[lane], from_u = ent_u[lane];                 // whose the neighbour of this lane is
+        const uint64_t kept = ck[(buf ^ 1) * 64 + at_hash[(buf ^ 1) * HASHES + hash_of(mine)]];
+        const bool known = lane < n_ent && key_node(kept) == mine, need = lane < n_ent && !known;
+        const uint64_t need_m = __builtin_amdgcn_ballot_w64(need);
+        const int n_need = __builtin_popcountll(need_m), rank = rank_in(need_m);
+        if (need) ent_u[rank] = mine;
+        const int todo = grp < n_need ? ent_u[grp] : -1;
+        if (todo >= 0) rows.issue(todo);
+        // A neighbour named twice in the step belongs to the first that names it: eight lanes, eight apart, look at those before one of
+        // this wave's share.
         {
-            const int *first = ent + sub * 8;
-            oa = *reinterpret_cast<const int4 *>(first);
-            ob = *reinterpret_cast<const int4 *>(first + 4);
-        }
-#pragma unroll
-        for (int h = 0; h < SETS; ++h) {
-            const int i = h == 0 ? grp : 63 - grp;
-            v[h] = ent[i];
-        }
-#pragma unroll
-        for (int h = 0; h < SETS; ++h) slot[h] = at_hash[(buf ^ 1) * HASHES + hash_of(v[h])];
-#pragma unroll
-        for (int h = 0; h < SETS; ++h) k_of[h] = ck[(buf ^ 1) * 64 + slot[h]];
-        int todo = -1, todo_set = 0;
-#pragma unroll
-        for (int h = 0; h < SETS; ++h) {
-            const int i = h == 0 ? grp : 63 - grp, i0 = sub * 8, mine = v[h];
-            const int dup = ((int)(i0 + 0 < i) & (int)(oa.x == mine)) | ((int)(i0 + 1 < i) & (int)(oa.y == mine)) |
-                            ((int)(i0 + 2 < i) & (int)(oa.z == mine)) | ((int)(i0 + 3 < i) & (int)(oa.w == mine)) |
-                            ((int)(i0 + 4 < i) & (int)(ob.x == mine)) | ((int)(i0 + 5 < i) & (int)(ob.y == mine)) |
-                            ((int)(i0 + 6 < i) & (int)(ob.z == mine)) | ((int)(i0 + 7 < i) & (int)(ob.w == mine));
-            const bool again = ((unsigned)(__builtin_amdgcn_ballot_w64(dup != 0) >> (lane & ~(LANES_PER_ROW - 1))) & 0xffu) != 0;
-            const bool here = i < n_ent && !again, known = key_node(k_of[h]) == mine && k_of[h] != UNKNOWN;
-            const bool next = here && !known && todo < 0;
-            k_of[h] = !here ? 0ull : known ? k_of[h] : UNKNOWN;
-            todo_set = next ? h : todo_set;
-            todo = next ? mine : todo;
-        }
-        float s = 0.f;
-        if (todo >= 0) {
-            rows.issue(todo);
-            // (its adjacency row into the near caches: it is likely a node of the next steps)
-            const int touch = graph[(size_t)todo * R + min(sub * 4, R - 1)];
-            s = rows.dots(todo);
-            asm volatile("" ::"v"(touch));
-        }
-        const uint64_t own = node_key(s, todo);
-#pragma unroll
-        for (int h = 0; h < SETS; ++h) k_of[h] = todo >= 0 && todo_set == h ? own : k_of[h];
-        if (sub == 0) {
+            const int part = lane >> 3;
+            const int4 oa = *reinterpret_cast<const int4 *>(ent + part * 8), ob = *reinterpret_cast<const int4 *>(ent + part * 8 + 4);
+            uint32_t word = 0;
 #pragma unroll
             for (int h = 0; h < SETS; ++h) {
-                const int i = h == 0 ? grp : 63 - grp;
-                ck[buf * 64 + i] = k_of[h];
-                if (k_of[h] + 1 > 1) at_hash[buf * HASHES + hash_of(v[h])] = i;          // (neither none nor unknown)
+                const int i = (wave * SETS + h) * 8 + sub, i0 = part * 8, e = ent[i];
+                const int dup = ((int)(i0 + 0 < i) & (int)(oa.x == e)) | ((int)(i0 + 1 < i) & (int)(oa.y == e)) |
+                                ((int)(i0 + 2 < i) & (int)(oa.z == e)) | ((int)(i0 + 3 < i) & (int)(oa.w == e)) |
+                                ((int)(i0 + 4 < i) & (int)(ob.x == e)) | ((int)(i0 + 5 < i) & (int)(ob.y == e)) |
+                                ((int)(i0 + 6 < i) & (int)(ob.z == e)) | ((int)(i0 + 7 < i) & (int)(ob.w == e));
+                uint64_t m = __builtin_amdgcn_ballot_w64(dup != 0);
+                m |= m >> 32;
+                m |= m >> 16;
+                m |= m >> 8;
+                word |= ((uint32_t)m & 0xffu) << (8 * h);
+            }
+            if (lane == 0) again_of(wave)[buf] = word;
+        }
+        if (todo >= 0) {
+            // (its adjacency row into the near caches: it is likely a node of the next steps)
+            const int touch = graph[(size_t)todo * R + min(sub * 4, R - 1)];
+            const uint64_t own = node_key(rows.dots(todo), todo);
+            asm volatile("" ::"v"(touch));
+            if (sub == 0) {
+                ck[buf * 64 + grp] = own;
+                at_hash[buf * HASHES + hash_of(todo)] = grp;
             }
         }
-        const int from_u = ent_u[lane];                   // whose the neighbour of this lane is
+        if (wave == NW - 1 && known) {                    // (the last wave is the one that has the fewest rows)
+            const int slot = n_need + rank_in(__builtin_amdgcn_ballot_w64(known));
+            ck[buf * 64 + slot] = kept;
+            at_hash[buf * HASHES + hash_of(mine)] = slot;
+        }
         barrier();
 
         // ---- commit ------------------------------------------------------------------------------------------
-        uint64_t key = lane < n_ent ? ck[buf * 64 + lane] : 0ull;
+        uint64_t key = need ? ck[buf * 64 + rank] : known ? kept : 0ull;
+        if constexpr (SETS == 2) key = need && rank >= GROUPS ? UNKNOWN : key;
+        key = again_of(lane / (8 * SETS))[buf] >> (lane & (8 * SETS - 1)) & 1u ? 0ull : key;
         buf ^= 1;
         // A neighbour stops the expansions from the first whose node it precedes, but none up to its own; one that is unknown stops
         // its own.
@@ -805,14 +804,14 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
         }
         // ---- insert; the next rows are asked for as soon as their nodes are known ------------------------------
         const int n_com = __builtin_amdgcn_readlane(upto, C - 1);         // neighbours of committed nodes
-        const bool mine = lane < n_com;
+        const bool in = lane < n_com;
         n_expand += C;
         if (lane < C) A[n_exp + lane] = t;
         n_exp += C;
         n_t -= C;
         if (C > 2) t = lanes_down_by(t, C, lane);
         else for (int i = 0; i < C; ++i) t = lanes_down(t);
-        const bool taken = mine && key >= bound, high = taken && key > floor_key;
+        const bool taken = in && key >= bound, high = taken && key > floor_key;
         const uint64_t high_m = __builtin_amdgcn_ballot_w64(high);
         if (__builtin_amdgcn_ballot_w64(taken && !high) != 0) to_pool(key, taken && !high);
         const int n_high = __builtin_popcountll(high_m);
@@ -822,14 +821,15 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
         } else {
             // Many: every row group finds the rank of its own among them, its 8 lanes look at 8 each; the keys come
             // back in order through LDS.
-            const uint64_t *now = ck + (buf ^ 1) * 64 + sub * 8;
+            uint64_t *now = reinterpret_cast<uint64_t *>(ent);            // (the neighbours are not read any more)
+            now[lane] = key;
             uint64_t o[8];
 #pragma unroll
-            for (int c = 0; c < 8; ++c) o[c] = now[c];
+            for (int c = 0; c < 8; ++c) o[c] = now[sub * 8 + c];
 #pragma unroll
             for (int h = 0; h < SETS; ++h) {
-                const int i = h == 0 ? grp : 63 - grp;
-                const uint64_t own = k_of[h];
+                const int i = grp + h * GROUPS;
+                const uint64_t own = now[i];
                 int r = 0;
 #pragma unroll
                 for (int c = 0; c < 8; ++c) r += (int)(o[c] > own) & (int)(sub * 8 + c < n_com);
@@ -843,7 +843,7 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
         settle();
         request();
         if (NS && track) average(due, 0, n_due);
-        mark(key, mine && key != 0);
+        mark(key, in && key != 0);
         if (NS && n_t > 0) {
             const uint64_t head = read_lane(t, 0);
             best_key = head > best_key ? head : best_key;

@@ -111,3 +111,27 @@ def test_graph_frontier_in_all_of_lds(N, ef, k):
     # (rows of 8 numbers: scores of the two sides differ by about 1e-7, and nodes that close change places)
     same = (st[:, 1] == n_dist) & (st[:, 2] == n_expand)
     assert same.mean() >= 0.75 and (ids.cpu().numpy() == o_ids).mean() >= 0.9 and (st[:, 0] == 0).all()
+
+
+@pytest.mark.parametrize("N,R,B,ef", [
+    (4000, 32, 3, 100),      # eight waves, four expansions a step
+    (4000, 32, 3, 128),      # ... eight expansions
+    (4000, 32, 300, 128),    # four waves: more unknown neighbours than row groups
+    (4000, 24, 600, 128),    # ... three workgroups a compute unit
+])
+def test_graph_frontier_shared_neighbours(N, R, B, ef):
+    """Rows that name the same few nodes again and again, within a row and from row to row of a step, some scored by the step before."""
+    say(f"shared neighbours: N={N} R={R} B={B} ef={ef}")
+    x, q, _ = _random(N, 96, R, B, torch.float16, 21)
+    gen = torch.Generator().manual_seed(22)
+    g = (torch.arange(N)[:, None] // 20 * 20 + torch.randint(-20, 60, (N, R), generator=gen)).to(torch.int32)
+    xn, qn = to_np(x), to_np(q)
+    ids, sc, stats, _ = ann.ann_graph_search_nonstall_typed(x.to(DEV), g.to(DEV), 3, q.to(DEV), 10, ef, tau=float("inf"), window=10)
+    p_ids, p_sc = ann.ann_graph_search_typed(x.to(DEV), g.to(DEV), 3, q.to(DEV), 10, ef)
+    torch.cuda.synchronize()
+    o_ids, _, o_sc64, n_dist, n_expand = oracle.graph_search(xn, g.numpy(), 3, qn, 10, ef, dtype="f16")
+    strict, tolerant, n = compare_topk(ids.cpu().numpy(), sc.cpu().numpy(), o_ids, o_sc64, xn, qn, dtype="f16")
+    assert strict >= n - max(2, n // 100), (strict, n)
+    assert torch.equal(ids, p_ids) and torch.equal(sc, p_sc)
+    st = stats.cpu().numpy()
+    assert ((st[:, 1] == n_dist) & (st[:, 2] == n_expand)).mean() >= 0.99
