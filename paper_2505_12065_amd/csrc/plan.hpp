@@ -754,12 +754,15 @@ inline int frontier_from_staying(int cus, int64_t N, int row_bytes, int R, int B
 //     visited set in memory 6196 / 3535 (ef = 2048), 22 838 / 12 592 (8192).  The very shortest lists end before its larger start is
 //     paid for (ef = 3: 30.4 / 35.8), and rows of 4 KB, of which a step scores some for nothing, make it later (B = 256, ef = 16
 //     134 / 156, 64 360 / 349)
-//   two workgroups a compute unit (B = 512): narrow graphs any list (R = 16 97 / 96, 362 / 304, 2150 / 1334 at ef = 16, 96, 768); at
-//     R = 32 steps hold little more than one expansion's neighbours while the list fills: ef = 48 217 / 257, 192 640 / 662, 384
-//     1264 / 1041, 1536 4372 / 2684; R = 24 253 / 284 at ef = 64, 629 / 586 at 192
-//   three (B = 2048): R = 32 799 / 804 at ef = 64, 2074 / 1726 at 192; B = 1024 490 / 512, 1222 / 1071
-//   rows of more than 2.5 KB start a little later there: 40 k x 1024 fp32, B = 512, R = 16 ef = 16 139 / 169, 48 268 / 270; B = 1024, R = 32 96 1002 /
-//     1137, 192 0.92 times as long (2.5 KB 753 / 767)
+//   two workgroups a compute unit: a step of four waves holds 32 unknown neighbours, little more than one expansion's while the list
+//     fills.  200 k x 768, R = 32, B = 300 ef = 64 224 / 244, 96 326 / 348, 128 418 / 394, 192 644 / 562, B = 512 254 / 266, 359 / 373, 442 / 432, 653 / 582;
+//     100 k x 256 96 292 / 295, 128 378 / 346; R = 31, whose two rows fit 63 places, 50 k x 128 fp32 64 190 / 179; R = 24 200 k x 768 48 196 / 196,
+//     96 354 / 327, 100 k x 256 32 144 / 142, 48 187 / 180; R = 16 8 57 / 59, 12 73 / 71
+//   three: once round (B = 700) any but the shortest: 200 k x 768, R = 32 ef = 16 143 / 136, 48 318 / 252, R = 24 64 418 / 289; 100 k x 256 16 133 / 117, 64
+//     356 / 230.  More queries, which take turns (B = 1024), have longer rows waiting for the memory path: 200 k x 768, R = 32 24 223 / 245, 48 373 / 378,
+//     64 454 / 442, R = 24 24 218 / 209, 48 364 / 350; 100 k x 256, R = 32 24 191 / 188, 64 391 / 321, R = 24 24 194 / 165; R = 16 8 107 / 94
+//   rows of 4 KB start later there: 60 k x 1024 fp32, R = 32, B = 300 ef = 128 618 / 646, 160 735 / 711, B = 512 160 794 / 819; B = 700 48 513 / 508, 64 648 /
+//     577; B = 1024 96 998 / 1112, 128 1282 / 1305; R = 16, B = 512 16 139 / 169, 48 268 / 270
 //   visited set in memory: short lists stay with the id caches, which need no workspace; R = 32, B = 512, 1 M x 768 ef = 600 2215 /
 //     2516, 1024 3619 / 3799, 2048 6959 / 6364, 4096 13 421 / 10 524; R = 24 or rows of 256 bytes all of them (700 k, ef = 600 2086 /
 //     1983, 1907 / 1812)
@@ -771,9 +774,12 @@ inline bool frontier_pays(int cus, int64_t N, int row_bytes, int R, int B, int e
     if (counters) return ef >= (leaves ? frontier_from_leaving(cus, N, row_bytes, R, B, global) : frontier_from_staying(cus, N, row_bytes, R, B, global));
     if (global && ef <= GRAPH_EF_TWO_LEVEL) return false;
     if (own) return ef >= (row_bytes > 2048 ? 72 : R > 16 ? 12 : 8);
-    if (R <= 16) return ef >= (long_rows && !waits ? 36 : 16);
+    if (R <= 16) return ef >= (long_rows ? (waits ? 16 : 36) : waits ? 8 : 12);
     if (global) return waits || R <= 24 || row_bytes <= 512 || ef >= 1400;
-    return ef >= (waits ? (long_rows && B <= 6 * cus ? 136 : 96) : R <= 24 ? 128 : 200);
+    const bool once = B <= 3 * cus, mid_rows = row_bytes > 1024;
+    if (waits) return ef >= (once ? (long_rows ? 64 : 16) : long_rows ? (B <= 6 * cus ? 136 : 96) : mid_rows && R > 24 ? 64 : 24);
+    if (R <= 24) return ef >= (long_rows ? 128 : mid_rows ? 72 : 40);
+    return ef >= (long_rows ? 200 : mid_rows ? 128 : R < GRAPH_STEP_MAX_R ? 64 : 96);
 }
 
 // Where graph_step_kernel is faster than graph_search_kernel, among the calls that graph_frontier_kernel does not take: lists of

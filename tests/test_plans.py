@@ -162,6 +162,17 @@ NEVER = float("inf")                                  # no average passes it
     (700_000, 256, 8, 600, 64, 0.9, FRONTIER),            # 0.79
     (800_000, 1536, 32, 1024, 128, 0.9, SEARCH),          # 1.04
     (800_000, 1536, 24, 1024, 192, 0.9, FRONTIER),        # 0.93
+    # row groups without gaps
+    (200_000, 1536, 32, 512, 96, None, SEARCH),           # 359 / 373
+    (200_000, 1536, 32, 512, 128, None, FRONTIER),        # 442 / 432
+    (200_000, 1536, 32, 700, 16, None, FRONTIER),         # 143 / 136
+    (200_000, 1536, 32, 1024, 48, None, SEARCH),          # 373 / 378
+    (100_000, 512, 32, 1024, 24, None, FRONTIER),         # 191 / 188
+    (100_000, 512, 24, 300, 24, None, SEARCH),            # 103 / 111
+    (100_000, 512, 24, 300, 48, None, FRONTIER),          # 187 / 180
+    (50_000, 512, 31, 512, 64, None, FRONTIER),           # 190 / 179
+    (60_000, 4096, 32, 700, 64, None, FRONTIER),          # 648 / 577
+    (100_000, 768, 16, 300, 8, None, SEARCH),             # 52 / 59
 ])
 def test_graph_kernels_where_they_were_measured_to_pay(plans, N, row, R, B, ef, tau, kernel):
     assert plans.graph_kernel(CUS, N, row, R, B, ef, tau is not None, NEVER if tau is None else tau) == kernel
