@@ -29,6 +29,7 @@ hipError_t launch_any(const WidePlan &pl, const void *X, int64_t N, int d, const
     case WIDE_TALL: return launch<T, WideTall>(pl, X, N, d, Q, B, maxima, after, stream);
     case WIDE_MID: return launch<T, WideMid>(pl, X, N, d, Q, B, maxima, after, stream);
     case WIDE_TINY: return launch<T, WideTiny>(pl, X, N, d, Q, B, maxima, after, stream);
+    case WIDE_SQUARE: return launch<T, WideSquare>(pl, X, N, d, Q, B, maxima, after, stream);
     case WIDE_SHORT: return launch<T, WideShort>(pl, X, N, d, Q, B, maxima, after, stream);
     default: return launch<T, WideThin>(pl, X, N, d, Q, B, maxima, after, stream);
     }

@@ -3,8 +3,8 @@
 //
 //   workgroup tile  32 WMF NWM corpus rows x 32 WNF NWN queries, NWM x NWN wavefronts
 //   wavefront tile  32 WMF rows x 32 WNF queries = WMF x WNF MFMA 32x32x16 accumulators
-//   K loop          stages of 64 bytes of a row (the two large tiles) or 128 (the others), 3 or 4 of them in LDS; every stage is
-//                   filled by direct global->LDS loads issued two or three stages ahead.  One load instruction brings a 1 KB
+//   K loop          stages of 64 bytes of a row (the two large tiles) or 128 (the others), 2 to 4 of them in LDS; every stage is
+//                   filled by direct global->LDS loads issued one to three stages ahead.  One load instruction brings a 1 KB
 //                   block, 16 rows x 64 B or 8 rows x 128 B (whole cache lines); inside a row the 16-byte chunks sit in slots
 //                   XOR-swizzled by the row number, so the MFMA operand reads (32 rows x one chunk) hit all banks
 //   epilogue        the largest score of every group of 1, 4, 16, 32 or 16 WMF rows (all of one lane's), nothing else:
@@ -89,8 +89,10 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
     // tile) + a 32-bit per-lane offset that does not change from tile to tile, except in the ragged last tile
     // where rows are clamped to N - 1.  In the last stage of rows that end inside it, chunks behind the end come
     // from a row of zeros.
+    // (Lambdas of the K loop are inlined by order: those of the 128 x 128 tile were called otherwise, its accumulators in scratch memory, 121 us
+    // instead of 25 at 977 x 768, B = 5000.  The other tiles' code is the same either way.)
     uint32_t loff[LPW];
-    auto lane_offsets = [&](int64_t tile) {
+    auto lane_offsets = [&](int64_t tile) __attribute__((always_inline)) {
 #pragma unroll
         for (int e = 0; e < LPW; ++e) {
             const int blk = wave * LPW + e;
@@ -114,7 +116,7 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
     constexpr bool LINES = SB == 128;
     const char *xs = xbase, *qs = qbase;                 // LINES: the next stage's place in them
     // LINES: inside a tile, before its last step
-    auto issue_inside = [&] {
+    auto issue_inside = [&]() __attribute__((always_inline)) {
         unsigned char *sbase = stage_mem + iofs;
 #pragma unroll
         for (int e = 0; e < LPW; ++e) {
@@ -127,7 +129,7 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
         ++issued;
         ++iks;
     };
-    auto issue = [&] {
+    auto issue = [&]() __attribute__((always_inline)) {
         if (issued >= total) return;
         if (LINES && iks < ksteps - 1) return issue_inside();
         ++issued;
@@ -162,7 +164,7 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
     f16v acc[WMF][WNF];
     int it = 0, cofs = 0;                                 // stage being computed, its LDS offset
     // `inside` (LINES): there is a stage to load, and it lies inside its tile
-    auto stage = [&](auto first, auto inside) {
+    auto stage = [&](auto first, auto inside) __attribute__((always_inline)) {
         // it has landed once only the newer stages' loads are outstanding (a tile's stores are newer still: the
         // wait right behind an epilogue is a little longer than it has to be)
         const int newer = decltype(inside)::value ? NST - 2 : min(NST - 2, total - 1 - it);

@@ -62,11 +62,12 @@ struct WideCfg {
 using WideLarge = WideCfg<4, 2, 2, 4, 4, 1>;              // 256 x 256, 8 waves
 using WideTall = WideCfg<4, 2, 4, 2, 4, 1>;               // 512 x 128, 8 waves
 using WideMid = WideCfg<2, 2, 4, 2, 3, 1, 128>;           // 256 x 128, 8 waves
+using WideSquare = WideCfg<2, 2, 2, 2, 2, 2, 128>;        // 128 x 128, 4 waves, two workgroups per compute unit
 using WideThin = WideCfg<2, 1, 2, 2, 3, 2, 128>;          // 128 x 64, 4 waves, two workgroups per compute unit
 using WideTiny = WideCfg<1, 1, 2, 2, 4, 2, 128>;          // 64 x 64, 4 waves, two
 using WideShort = WideCfg<2, 1, 2, 2, 4, 3>;              // 128 x 64, 4 waves, three: half lines, for short rows
 
-constexpr int WIDE_LARGE = 0, WIDE_TALL = 1, WIDE_MID = 2, WIDE_THIN = 3, WIDE_TINY = 4, WIDE_SHORT = 5;
+constexpr int WIDE_LARGE = 0, WIDE_TALL = 1, WIDE_MID = 2, WIDE_THIN = 3, WIDE_TINY = 4, WIDE_SHORT = 5, WIDE_SQUARE = 6;
 struct WidePlan {
     int cus, shape, wmf;         // compute units; workgroup tile (a WideCfg); its row fragments per wave
     int NT, P;                   // query tiles x slabs of the corpus
@@ -92,13 +93,14 @@ inline void wide_geometry(WidePlan &pl, int shape, int cus, int64_t N, int B) {
     case WIDE_MID: return geometry<WideMid>(pl, cus, N, B);
     case WIDE_TINY: return geometry<WideTiny>(pl, cus, N, B);
     case WIDE_SHORT: return geometry<WideShort>(pl, cus, N, B);
+    case WIDE_SQUARE: return geometry<WideSquare>(pl, cus, N, B);
     default: return geometry<WideThin>(pl, cus, N, B);
     }
 }
 
 inline int wide_rows(int shape) {                         // corpus rows of a tile
     return shape == WIDE_LARGE ? WideLarge::BM : shape == WIDE_TALL ? WideTall::BM : shape == WIDE_MID ? WideMid::BM
-           : shape == WIDE_TINY ? WideTiny::BM : shape == WIDE_SHORT ? WideShort::BM : WideThin::BM;
+           : shape == WIDE_TINY ? WideTiny::BM : shape == WIDE_SHORT ? WideShort::BM : shape == WIDE_SQUARE ? WideSquare::BM : WideThin::BM;
 }
 
 // ---- exact search, the whole call ----------------------------------------------------------------------
@@ -135,6 +137,7 @@ struct FlatPlan {
     bool direct;             // ... of one slab: no merge
     bool quick;              // ... by flat_direct_kernel
     bool wide;               // the matrix-core kernel, or
+    bool by_fill;            // ... its tile by the first rule
     bool maxima;             // the streaming kernel with group maxima takes the call, `part` queries and `rows` rows at a time
     WidePlan w;
     int part;
@@ -234,7 +237,7 @@ inline int wide_group_log(int cus, int wmf, int64_t N, int row_bytes, int B, int
     return best;
 }
 
-// The tile of the matrix-core kernel: the largest of which there are enough for the chip.  Larger tiles move fewer bytes per
+// The tile of the matrix-core kernel, first rule: the largest of which there are enough for the chip.  Larger tiles move fewer bytes per
 // product, so what decides is how full the chip gets; us, d = 768, inputs not in the caches:
 //                          256 x 256   512 x 128   256 x 128   128 x 64   64 x 64   (the 128 x 128 tile of half-line stages that
 //   4000, B = 400              34          39          25         17         16       stood between them: 20)
@@ -264,6 +267,57 @@ inline int wide_shape(int cus, int64_t N, int d, int B) {
     if (B > 64 && d <= 512 && tiles(512, 128) >= 4 * (int64_t)cus) return WIDE_TALL;
     if (B > 64 && 4 * tiles(256, 128) >= 3 * (int64_t)cus) return WIDE_MID;
     return tiles(128, 64) > cus ? wide_thin(cus, N, d, B) : WIDE_TINY;
+}
+
+// Second rule, for batches beyond 64 queries with tiles for more than one round of small ones: by the rounds of tiles that the slowest
+// compute unit goes through, since a last round that is nearly empty costs a whole one.  A tile takes a + b (lines of 128 bytes) us
+// with the chip full of its kind; where two workgroups share a compute unit and do not fill it, less by `share` of what is missing.  The
+// 128 x 128 tile stands between: two fragments each way (a byte read from LDS feeds half as many products again as with 128 x 64) and
+// two workgroups to a compute unit, which fill each other's waits, so that two stages do.  Constants fitted to 287 calls of 200 to 2.5 M rows,
+// 66 to 8192 queries, d = 72 to 1024: 0.8 % behind the best tile on average (the first rule 3.2 %); 190 others 2.3 % faster on average
+// than by the first rule, the slowest of them 2 % slower.  First
+// rule / this, us: 977 x 768, B = 5000, k = 16 26.6 / 25.2; 2000 x 768, B = 3000 26.9 / 24.0; 24 k x 768, B = 200 26.2 / 21.9;
+// 10.5 k x 768, B = 6152 211 / 195; 46 k x 384, B = 883 72.4 / 66.3; 38.8 k x 776, B = 68 32.9 / 27.4; 110 k x 384, B = 535 82 / 76.
+// Corpora beyond 64 MB come from memory, where tiles of few queries read them too often (110 k x 768, B = 301 92 by 256 x 128, 101 by 128 x 128, 105 by
+// 128 x 64); rows of up to 64 elements are mostly start and end of a tile (10 k x 64, B = 808 18.7 / 20.7).
+inline double wide_rounds_us(int shape, int cus, int64_t N, int d, int B) {
+    double a, b, share = 0;
+    int lines = 2 * ((d + 63) / 64), bm, bn, per_cu = 1;  // half lines
+    auto tile = [&](auto c) {
+        bm = decltype(c)::BM;
+        bn = decltype(c)::BN;
+        per_cu = decltype(c)::PER_CU;
+        if (decltype(c)::SB == 64) lines = (d + 31) / 32;
+    };
+    switch (shape) {
+    case WIDE_LARGE: tile(WideLarge{}); a = 1.26; b = 1.35; break;
+    case WIDE_TALL: tile(WideTall{}); a = 1.32; b = 1.51; break;
+    case WIDE_MID: tile(WideMid{}); a = 0.93; b = 0.69; break;
+    case WIDE_SQUARE: tile(WideSquare{}); a = 0.94; b = 0.52; share = 0.40; break;
+    default: tile(WideThin{}); a = 0.61; b = 0.43; share = 0.10; break;
+    }
+    const int64_t slots = (int64_t)cus * per_cu, rows = (N + bm - 1) / bm, cols = (B + bn - 1) / bn;
+    const int64_t slabs = slots / cols < 1 ? 1 : slots / cols < rows ? slots / cols : rows, groups = slabs * cols;
+    const double rounds = (double)((rows + slabs - 1) / slabs * ((groups + slots - 1) / slots));
+    const double full = (double)(groups < slots ? groups : slots) / cus;              // workgroups on a compute unit
+    return rounds * (a + b * lines / 2 * (1 + share * (full > 1 ? full - 1 : 0)));
+}
+inline int wide_tile(int cus, int64_t N, int d, int B) {
+    const int first = wide_shape(cus, N, d, B);
+    if (B <= 64 || d <= 64 || first == WIDE_TINY) return first;
+    const bool cached = N * d * 2 <= 64000000;
+    if (!cached && (first == WIDE_THIN || first == WIDE_SHORT)) return first;
+    int best = first;
+    const double stays = wide_rounds_us(first, cus, N, d, B);
+    double least = 0.95 * stays;                          // (closer than that the model does not tell them apart)
+    for (int shape : {WIDE_LARGE, WIDE_TALL, WIDE_MID, WIDE_SQUARE, WIDE_THIN}) {
+        if (!cached && (shape == WIDE_SQUARE || shape == WIDE_THIN)) continue;
+        const double us = wide_rounds_us(shape, cus, N, d, B);
+        // (256 x 128 with a half empty last round runs faster in it than the model has it: 15.7 k x 384, B = 839 29.7 / 32.1 by 256 x 256)
+        if (shape == WIDE_LARGE && first == WIDE_MID && us > 0.9 * stays) continue;
+        if (us < least) { least = us; best = shape; }
+    }
+    return best == WIDE_THIN ? wide_thin(cus, N, d, B) : best;
 }
 
 // Whether the matrix-core kernel takes a call, or the streaming kernel, which reads large corpora at the rate of HBM for up to
@@ -316,7 +370,7 @@ inline size_t maxima_pass(FlatPlan &pl, int cus, int d, int dtype, int k, size_t
     const int B = pl.part;
     const size_t most = room / ((size_t)B * sizeof(float));
     if (pl.wide) {
-        wide_geometry(pl.w, wide_shape(cus, N, d, B), cus, N, B);
+        wide_geometry(pl.w, pl.by_fill ? wide_shape(cus, N, d, B) : wide_tile(cus, N, d, B), cus, N, B);
         // A tile's groups have 16 wmf rows at most: where those are too many, the tile of 64 if there are enough for the chip,
         // else the one of 32 that pads least (300 k x 64, B = 300 in 1 MiB: 7 parts of the corpus, 14 by groups of 32).
         if (pl.w.wmf < 4 && (size_t)maxima_of(pl.w.wmf, pl.w.slots, 3 + pl.w.wmf) > most) {
@@ -352,7 +406,22 @@ inline FlatPlan maxima_part(FlatPlan pl, int64_t rows, int part, int d, int dtyp
 inline bool maxima_plan(FlatPlan &pl, int cus, int64_t N, int d, int dtype, int B, int k, size_t limit) {
     pl.rows = N;
     pl.part = B;
+    const bool by_fill = pl.by_fill || !pl.wide;
+    pl.by_fill = true;
     const size_t all = pl.ws_bytes = maxima_pass(pl, cus, d, dtype, k, limit);
+    // The tile that takes the fewest rounds, if its maxima fit at once: what must go in parts keeps the first rule, which the lines of small
+    // buffers were drawn with.  (No less is asked for than the first rule's tile needs: what ann_flat_workspace_bytes of 8 MiB at
+    // most says of the static entry point stays true.)
+    if (!by_fill) {
+        FlatPlan own = pl;
+        own.by_fill = false;
+        const size_t bytes = maxima_pass(own, cus, d, dtype, k, limit);
+        if (bytes <= limit) {
+            own.ws_bytes = all <= limit && all > bytes ? all : bytes;
+            pl = own;
+            return true;
+        }
+    }
     if (all <= limit) return true;
     // queries in parts
     const size_t fit = limit / ((size_t)pl.w.n * sizeof(float));
@@ -426,9 +495,11 @@ inline double lists_us(const FlatPlan &pl, int cus, int64_t N, int d, int dtype,
     return fmax(read, rows * (24 + 3 * groups) * cut + groups * fmin(35, 2 + 8 * rows)) + 10;
 }
 
+// by_fill: the tile by the first rule (the static entry point, whose lines were drawn with it).
 // in_parts: a call keeps its kernel, and its bits, where that takes parts (the static entry point, whose workspace is of one size).
-inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, size_t limit, bool in_parts = false) {
+inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, size_t limit, bool in_parts = false, bool by_fill = false) {
     FlatPlan pl{};
+    pl.by_fill = by_fill;
     pl.part = B;
     pl.rows = N;
     const int row_bytes = d * elem_bytes(dtype);
@@ -460,6 +531,7 @@ inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, si
     if (!pl.wide && (pl.direct || N <= 32 * 1024 || !many_queries(N, d, B))) return pl;
     const FlatPlan first = pl;
     pl = FlatPlan{};
+    pl.by_fill = by_fill;
     pl.part = B;
     pl.rows = N;
     pl.wide = !first.wide;
@@ -507,13 +579,13 @@ inline bool static_one_pass(const WidePlan &w, int64_t N, int d, int B, int k) {
 // them; ws_bytes > bytes: refused.
 inline FlatPlan static_plan(int cus, int64_t N, int d, int dtype, int B, int k, size_t bytes) {
     if (k > 4 && B >= 256 && !static_takes_long(N, d, dtype, B)) {
-        FlatPlan pl = flat_plan(cus, N, d, dtype, B, k, WIDE_WS_MAX);
+        FlatPlan pl = flat_plan(cus, N, d, dtype, B, k, WIDE_WS_MAX, false, true);
         if (pl.wide && pl.ws_bytes > (size_t)ANN_STATIC_WORKSPACE_BYTES && static_one_pass(pl.w, N, d, B, k))
-            pl = flat_plan(cus, N, d, dtype, B, k, ANN_STATIC_WORKSPACE_BYTES);
+            pl = flat_plan(cus, N, d, dtype, B, k, ANN_STATIC_WORKSPACE_BYTES, false, true);
         if (pl.ws_bytes > (size_t)ANN_STATIC_WORKSPACE_BYTES && pl.ws_bytes <= bytes) pl.ws_bytes = bytes + 1;
         return pl;
     }
-    return flat_plan(cus, N, d, dtype, B, k, bytes, true);
+    return flat_plan(cus, N, d, dtype, B, k, bytes, true, true);
 }
 
 // ---- graph search ---------------------------------------------------------------------------------------

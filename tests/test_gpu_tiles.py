@@ -63,6 +63,18 @@ def test_line_stages(dtype, N, d, B, k):
     assert ((order < 0) | ((order == 0) & (ids.diff(dim=1) > 0))).all()
 
 
+@pytest.mark.parametrize("dtype,N,d,B,k", [
+    (torch.float16, 977, 776, 5_000, 16),      # single rows, workgroups by query tile, a line of 16 bytes at the end of a row
+    (torch.bfloat16, 1_025, 72, 4_097, 16),    # ... one row, one query in the last tiles
+    (torch.float16, 24_001, 264, 200, 3),      # groups of rows, one row in the last tile
+    (torch.bfloat16, 38_784, 96, 68, 10),      # ... whole tiles of rows, one query tile half empty
+    (torch.float16, 46_408, 384, 883, 5),      # ... slabs of several tiles
+])
+def test_square_tiles(dtype, N, d, B, k):
+    """128 x 128 with two stages."""
+    test_line_stages(dtype, N, d, B, k)
+
+
 @pytest.mark.parametrize("N,d,B,k,size", [
     (15_656, 512, 1, 1, 1_163),                # maxima do not fit, lists do
     (85_001, 144, 10, 10, 9_789),              # lists do not fit, the corpus in parts does

@@ -40,6 +40,7 @@ extern "C" int in_lds(int64_t N, int d, int elem_bytes, int R, int ef) {
 }
 extern "C" int runs(int cus, int d, int elem_bytes, int B) { return pick_runs(cus, (size_t)d * elem_bytes, 16 * elem_bytes, B); }
 extern "C" int shape(int cus, int64_t N, int d, int B) { return wide_shape(cus, N, d, B); }
+extern "C" int tile(int cus, int64_t N, int d, int B) { return wide_tile(cus, N, d, B); }
 // out: kind (0 lists, 1 direct, 2 matrix cores, 3 streaming with maxima), queries and rows at a time, maxima of a query,
 // log2 of the rows they stand for, offset of the k best so far, workspace, maxima of the smallest last part
 extern "C" void flat(int cus, int64_t N, int d, int dtype, int B, int k, int64_t limit, int64_t *out) {
@@ -74,7 +75,7 @@ def plans(tmp_path_factory):
     L.graph_kernel.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 5 + [ctypes.c_float]
     L.leaves.argtypes = [ctypes.c_float] + [ctypes.c_int] * 3
     L.frontier.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_float, ctypes.c_int, ctypes.c_void_p]
-    L.shape.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 2
+    L.shape.argtypes = L.tile.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 2
     L.in_lds.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4
     L.flat.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64, ctypes.c_void_p]
     L.static_accepts.argtypes = L.static_kind.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64]
@@ -445,6 +446,41 @@ LARGE, TALL, MID, THIN, TINY, SHORT = range(6)
     (48_119, 112, 7, THIN)])         # 12.9 / 12.8
 def test_half_lines_for_short_rows(plans, N, d, B, shape):
     assert plans.shape(CUS, N, d, B) == shape
+
+
+SQUARE = 6
+
+
+# us of a call with the first rule's tile / this one
+@pytest.mark.parametrize("N,d,B,tile", [
+    (977, 768, 5_000, SQUARE),       # 26.6 / 25.2: 320 tiles in one round, 632 of 128 x 64 in two
+    (24_000, 768, 200, SQUARE),      # 26.2 / 21.9
+    (10_564, 768, 6_152, MID),       # 211 / 195: nine rounds of half the work instead of five
+    (2_500, 768, 977, THIN),         # one round of them: stays
+    (1_000_000, 768, 512, LARGE),
+    (110_746, 768, 301, MID),        # from memory: tiles of few queries read too often, 92 / 101 by 128 x 128
+    (10_427, 64, 808, MID),          # short rows: the first rule's, 18.7 / 20.7 by 256 x 256
+    (977, 776, 5_000, SQUARE), (1_025, 72, 4_097, SQUARE), (24_001, 264, 200, SQUARE), (38_784, 96, 68, SQUARE), (46_408, 384, 883, SQUARE),
+    (40_000, 768, 64, THIN), (1_024, 768, 512, TINY), (1_200_000, 24, 18, SHORT)])
+def test_tiles_by_rounds(plans, N, d, B, tile):
+    assert plans.tile(CUS, N, d, B) == tile
+
+
+@pytest.mark.parametrize("seed", range(3))
+def test_fewest_rounds_only_where_the_maxima_fit_at_once(plans, seed):
+    """A call that has no room for all maxima gets the plan that it got by the first rule alone."""
+    rng = random.Random(seed)
+    for _ in range(400):
+        N, B = (int(math.exp(rng.uniform(math.log(lo), math.log(hi)))) for lo, hi in ((200, 3e6), (66, 8192)))
+        d, k = 8 * rng.randint(1, 128), rng.choice([1, 3, 10, 16])
+        k = min(k, N)
+        whole = flat(plans, N, d, 0, B, k, 1 << 30)
+        again = flat(plans, N, d, 0, B, k, whole["bytes"])
+        assert again["bytes"] <= whole["bytes"] and (again["part"], again["rows"]) == (whole["part"], whole["rows"])
+        small = flat(plans, N, d, 0, B, k, int(whole["bytes"] * rng.uniform(0.01, 0.9)))
+        assert small["bytes"] <= whole["bytes"]
+        if whole["bytes"] <= 8 * 1024 * 1024:
+            assert plans.static_accepts(CUS, N, d, 0, B, k, STATIC), (N, d, B, k)
 
 
 # share of queries that leave early
