@@ -72,12 +72,11 @@ constexpr int PRIO_WAVES = PRIO_THREADS / WAVE;
 // Workgroup b places the PRIO_TILE requests from b PRIO_TILE on: every thread holds one request at a time of the n to compare
 // with and tests it against all of them, so the n^2 comparisons are spread over the whole chip instead of one thread walking
 // all n.  A level and a 64-bit image of the queueing time that orders like the number are compared as one number of 96 bits.
-// Bound by latency up to some 3000 requests: one read of the first 2048, which are kept (a second one cost 0.5 us), reductions
+// Bound by latency up to some 3000 requests: one read, what a thread reads is kept (a second one cost 0.5 us), reductions
 // that stay out of the LDS crossbar, three barriers; beyond that by the comparisons and the levels that every workgroup
 // computes again.  us of a call, one thread walking all n (two launches) / read twice, 8 instructions a comparison / now, 4 of them:
-// n = 3000, G = 6 300 / 11.8 / 8.2, n = 16384 1590 / 76 / 69.
+// n = 3000, G = 6 300 / 11.8 / 7.1 (HELD, below), n = 16384 1590 / 76 / 69.
 constexpr int PRIO_TILE = 16;
-constexpr int HELD = 4;                                                   // requests that a thread keeps from the extremes to the comparisons
 
 // order-preserving image of a queueing time (a NaN counts as -inf, -0 as +0)
 __device__ __forceinline__ uint64_t wait_key(double w) {
@@ -95,7 +94,11 @@ __device__ __forceinline__ uint64_t wait_key(double w) {
 // now 1990).  Level by level / halving, us: n = 16, G = 20 7.4 / 6.9, G = 22 7.7 / 6.9, G = 32 9.0 / 6.9; n = 3000, G = 20
 // 11.7 / 11.2, G = 22 12.3 / 11.2, G = 32 15.2 / 11.2; n = 65 536, G = 20 1405 / 1430, G = 22 1479 / 1430, G = 32 1826 / 1430.
 constexpr int PRIO_FEW = 20;
-template <bool MANY>
+// HELD: requests that a thread keeps from the extremes to the comparisons.  ONCE: they are all that there are, and what no thread of
+// the workgroup has is left out, by a test that calls of several batches would pay for (n = 65 536 938 / 953): n = 1000, G = 6 5.94 / 5.32,
+// n = 256 5.97 / 5.54, two held instead of four.  Four of them, read in two batches of which the second is half empty, against six, us: n = 2049, G = 6 7.62 / 6.90, n = 3000, G = 6 8.26 / 7.13, G = 13
+// 10.04 / 8.28, G = 32 11.25 / 10.54.  Six cost smaller calls more than they skip (n = 2048 6.02 / 6.58), eight larger ones (n = 4096 8.33 / 8.37, n = 2500 6.89 / 7.48).
+template <bool MANY, int HELD, bool ONCE>
 __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *__restrict__ R, const double *__restrict__ W,
                                                                 const int32_t *__restrict__ C,
                                                                 const double *__restrict__ Wcur, int n, int G,
@@ -109,7 +112,7 @@ __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *_
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
     const int i0 = blockIdx.x * PRIO_TILE, in = min(PRIO_TILE, n - i0);
     if (tid < PRIO_TILE) before[tid] = 0;
-    // The tile's requests and the first four of a thread are loaded once, together.
+    // The tile's requests and the first HELD of a thread are loaded once, together.
     const int own = min(i0 + (tid & (PRIO_TILE - 1)), n - 1);
     const int own_r = R[own], own_c = C[own];
     const double own_w = W[own], own_q = Wcur[own];
@@ -131,7 +134,7 @@ __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *_
             c0 = min(c0, c[u]); c1 = max(c1, c[u]);
             w0 = fmin(w0, w[u]); w1 = fmax(w1, w[u]);
         }
-        for (int b = tid + HELD * PRIO_THREADS; b < n; b += HELD * PRIO_THREADS) {
+        for (int b = tid + HELD * PRIO_THREADS; !ONCE && b < n; b += HELD * PRIO_THREADS) {
             int br[HELD], bc[HELD];
             double bw[HELD];
 #pragma unroll
@@ -237,13 +240,14 @@ __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *_
 #pragma unroll
         for (int u = 0; u < HELD; ++u) {
             const int j = b + u * PRIO_THREADS;
+            if (ONCE && u * PRIO_THREADS >= n) break;                     // (nothing left for any thread)
             const uint32_t lj = j < n ? (uint32_t)l[u] + 1 : 0u;         // (past the end: runs before nobody)
             // a request of lower index runs first at equal times: its image is compared with >= by adding one
             const uint64_t wj = wait_key(q[u]) + (j < i0 ? 1u : 0u);
 #pragma unroll
             for (int t = 0; t < PRIO_TILE; ++t) count_larger(count[t], lj, wj, ml[t], mw[t]);
         }
-        if (b + HELD * PRIO_THREADS < n) {
+        if (!ONCE && b + HELD * PRIO_THREADS < n) {
 #pragma unroll
             for (int u = 0; u < HELD; ++u) {
                 const int i = min(b + (HELD + u) * PRIO_THREADS, n - 1);
@@ -287,9 +291,17 @@ __global__ __launch_bounds__(PRIO_THREADS) void priority_kernel(const int32_t *_
 
 hipError_t launch_priority(const int32_t *R, const double *W, const int32_t *C, const double *Wcur, int n, int G,
                            int32_t *level, int32_t *order, hipStream_t stream) {
-    hipLaunchKernelGGL((G > PRIO_FEW ? priority_kernel<true> : priority_kernel<false>), dim3((n + PRIO_TILE - 1) / PRIO_TILE), dim3(PRIO_THREADS), (size_t)G * 3 * sizeof(double),
-                       stream, R, W, C, Wcur, n, G, level, order);
-    return hipGetLastError();
+    auto go = [&](auto held, auto once) {
+        constexpr int HELD = decltype(held)::value;
+        constexpr bool ONCE = decltype(once)::value;
+        hipLaunchKernelGGL((G > PRIO_FEW ? priority_kernel<true, HELD, ONCE> : priority_kernel<false, HELD, ONCE>), dim3((n + PRIO_TILE - 1) / PRIO_TILE),
+                           dim3(PRIO_THREADS), (size_t)G * 3 * sizeof(double), stream, R, W, C, Wcur, n, G, level, order);
+        return hipGetLastError();
+    };
+    if (n <= 2 * PRIO_THREADS) return go(std::integral_constant<int, 2>{}, std::true_type{});
+    if (n <= 4 * PRIO_THREADS) return go(std::integral_constant<int, 4>{}, std::true_type{});
+    if (n <= 6 * PRIO_THREADS) return go(std::integral_constant<int, 6>{}, std::true_type{});
+    return go(std::integral_constant<int, 4>{}, std::false_type{});
 }
 
 }  // namespace ann

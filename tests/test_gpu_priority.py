@@ -22,3 +22,9 @@ def test_priority_requests_held_and_read_again(n, G):
                                           torch.from_numpy(Wcur).to(DEV), G)
     o_level, o_order = oracle.priority_order(R, W, C, Wcur, G)
     assert np.array_equal(level.cpu().numpy(), o_level) and np.array_equal(order.cpu().numpy(), o_order)
+
+
+@pytest.mark.parametrize("n,G", [(1023, 6), (1024, 21), (1025, 6), (1536, 33), (3071, 21), (3072, 6), (3073, 6), (3073, 64), (2560, 13)])
+def test_priority_number_of_requests_held(n, G):
+    """Two, four or six requests of a thread are all that there are, or not all."""
+    test_priority_requests_held_and_read_again(n, G)
