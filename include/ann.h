@@ -22,11 +22,12 @@
  *     than any before on this device; it grows by a quarter more than needed, to
  *     1.25 GiB at most for the flat search).  A buffer that a captured graph may hold
  *     is not freed then but kept until ann_release_workspace, so the graph can be replayed.
- *   - One workspace per device: calls that use it (the flat search, the graph
- *     search with ef > 512, the non-stall graph search) are safe one after the
- *     other on one stream, or on several streams if the caller orders them; two
- *     of them running at once on one device race on the workspace.  The plain
- *     graph search with ef <= 512 uses no workspace and may overlap anything.
+ *   - One workspace per device: calls that use it (the flat search over more rows than
+ *     it says below, the graph search with ef > 512, the non-stall graph search) are safe
+ *     one after the other on one stream, or on several streams if the caller orders them;
+ *     two of them running at once on one device race on the workspace.  The plain
+ *     graph search with ef <= 512 uses no workspace and may overlap anything, as
+ *     may a flat search over so few rows that it uses none.
  *   - corpus  [N, d] row-major, contiguous, 16-byte aligned base.
  *     queries [B, d] row-major, same element type as the corpus.
  *     graph   [N, R] row-major int32; a slot < 0 or >= N is empty and skipped.
@@ -97,7 +98,7 @@ const char *ann_last_error(void);
  *   - per query the largest score of every group of 1 to 64 rows, 4 bytes each: larger batches.
  *     That grows with N B (1 M rows, B = 512: 64 MB; 21 M rows: 672 MB); beyond 1 GiB the search
  *     runs in parts;
- *   - nothing: corpora of at most 128 rows.
+ *   - nothing: corpora of at most 128 rows with k <= 4 or in fp32, of at most 64 with any k.
  * ann_flat_workspace_bytes gives the size.
  */
 int ann_flat_search_typed(const void *corpus, int64_t N, int32_t d, int32_t dtype,

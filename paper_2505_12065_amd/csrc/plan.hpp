@@ -112,8 +112,8 @@ constexpr int P_MAX = 2048;      // most slabs of the streaming kernel
 // others / this, us: up to 250 tiles 0.73 times as long on average (fp32 0.66), 200 x 768, B = 1 8.5 / 6.3; 21 025 x 480, B = 14 13.8 / 12.4; 32 877 x
 // 544, B = 3 24.6 / 17.1; but 15 197 x 704, B = 43 13.1 / 24.3; 33 953 x 64, B = 8 10.0 / 12.6; 1024 x 768, B = 512 10.4 / 17.3.
 // flat_direct_kernel: one launch, up to 128 rows in one workgroup, which then has them all to bring in: 31 x 928, B = 8 5.8 (scores 6.7), 26 x
-// 1760, B = 4 6.8; from some 60 KB (fp32, whose products are longer, 100) scores: 16 bits 10.9 / 6.9 beyond 160 KB.  The streaming kernel's one
-// slab starts quicker where there is hardly a row (7 x 32, B = 2 4.0 / 4.8) and holds two workgroups a compute unit for many queries (3 x 832 fp32,
+// 1760, B = 4 6.8; from some 60 KB (fp32, whose products are longer, 100) scores where the call may use the workspace (128 x 384, k = 10), the streaming
+// kernel's one slab where it may not.  That starts quicker where there is hardly a row (7 x 32, B = 2 4.0 / 4.8) and holds two workgroups a compute unit for many queries (3 x 832 fp32,
 // B = 11 876 25.4 / 37.2).
 constexpr int DIRECT_WAVES = 8, DIRECT_ROWS = 16 * DIRECT_WAVES;
 inline int direct_held(int d, int elem_bytes) {           // steps of a query in LDS
@@ -504,20 +504,22 @@ inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, si
     pl.rows = N;
     const int row_bytes = d * elem_bytes(dtype);
     const size_t scores = (size_t)B * (size_t)((N + 3) & ~(int64_t)3) * sizeof(float);
-    const bool few = scores_pay(N, row_bytes, dtype, B);
-    pl.scores = few && scores <= limit && !direct_pays(N, row_bytes, dtype);
+    const bool few = scores_pay(N, row_bytes, dtype, B), one = direct_pays(N, row_bytes, dtype);
+    // So few rows never need a workspace, whatever their length and the batch: such searches may overlap anything, and each other.
+    const bool none = N <= (k <= 4 || dtype == ANN_F32 ? DIRECT_ROWS : DIRECT_ROWS / 2);
+    pl.scores = few && !none && !one && scores <= limit;
     if (pl.scores) {
         pl.w.cus = cus;
         pl.w.n = (N + 3) & ~(int64_t)3;
         pl.ws_bytes = scores;
         return pl;
     }
-    // A corpus of one tile per wave of a workgroup: its lists are the answer, one launch instead of two (64 x 1024, B = 8192, k = 16 23.1 -> 17.3 us),
-    // and no workspace.  Lists of 4 per lane are complete there whatever k is, since a lane sees four rows; selecting k > 4 from all eight
+    // A corpus of one tile per wave of a workgroup: its lists are the answer, one launch instead of two (64 x 1024, B = 8192, k = 16 23.1 -> 17.3 us).
+    // Lists of 4 per lane are complete there whatever k is, since a lane sees four rows; selecting k > 4 from all eight
     // waves costs more than the launch saves where the other way is group maxima (128 x 1024 bf16, B = 5000, k = 16: 19.3 / 23.3).
-    pl.maxima = !(few && N <= DIRECT_ROWS) && dtype == ANN_F32 && use_f32_maxima(N, d, B, k);
-    pl.direct = !pl.maxima && N <= (few || k <= 4 || dtype == ANN_F32 ? DIRECT_ROWS : DIRECT_ROWS / 2);
-    if (pl.direct && N * row_bytes >= 2000 && (B + 15) / 16 <= cus) pl.quick = true;
+    pl.direct = none || (few && N <= DIRECT_ROWS);
+    pl.quick = pl.direct && one && N * row_bytes >= 2000 && (B + 15) / 16 <= cus;
+    pl.maxima = !pl.direct && dtype == ANN_F32 && use_f32_maxima(N, d, B, k);
     pl.wide = !pl.direct && use_wide(N, d, dtype, B, k);
     auto plan = [&] {
         if (pl.wide || pl.maxima) maxima_plan(pl, cus, N, d, dtype, B, k, limit);

@@ -77,3 +77,24 @@ def test_scores_that_tie():
         ids, sc = ann.ann_flat_search_typed(x, q, 16, after=after)
         assert (ids == torch.arange(16, device=DEV) + 16 * page).all() and (sc == 64).all()
         after = (sc[:, -1].contiguous(), ids[:, -1].contiguous())
+
+
+@pytest.mark.parametrize("dtype,N,d,B,k", [(F16, 128, 768, 64, 4), (BF16, 64, 2_048, 33, 16), (F32, 100, 512, 40, 10), (F16, 80, 768, 512, 1)])
+def test_few_rows_on_two_streams_at_once(dtype, N, d, B, k):
+    """Searches that need no workspace overlap: two corpora, a stream each, nothing between them."""
+    print(f"two streams: dtype={dtype} N={N} d={d} B={B} k={k}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(d)
+    x = [torch.randn(N, d, generator=gen, device=DEV).to(dtype) for _ in range(2)]
+    q = [torch.randn(B, d, generator=gen, device=DEV).to(dtype) for _ in range(2)]
+    assert ann.ann_flat_workspace_bytes(N, d, dtype, B, k) == 0
+    alone = [ann.ann_flat_search_typed(x[i], q[i], k) for i in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    out = [[], []]
+    for _ in range(50):
+        for i in range(2):
+            with torch.cuda.stream(streams[i]):
+                out[i].append(ann.ann_flat_search_typed(x[i], q[i], k))
+    torch.cuda.synchronize()
+    for i in range(2):
+        assert all(torch.equal(ids, alone[i][0]) and torch.equal(sc, alone[i][1]) for ids, sc in out[i])

@@ -392,6 +392,24 @@ def test_searches_that_need_no_workspace(plans, N, d, elem_bytes, ef):
     assert plans.in_lds(N, d, elem_bytes, 32, ef)
 
 
+@pytest.mark.parametrize("dtype", [0, 1, 2])
+def test_few_rows_need_no_workspace(plans, dtype):
+    """Exact searches of so few rows may overlap anything, so none of them, however long its rows and large its batch, may write the
+    workspace that the calls of a device share."""
+    rng = random.Random(dtype)
+    log = lambda lo, hi: int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+    step = 4 if dtype == 2 else 8
+    calls = [(128, 768, 1, 1), (128, 768, 64, 4), (80, 768, 512, 1), (64, 4096, 16, 16), (65, 3304, 123, 1), (1, 8, 1, 1), (128, 4, 9719, 1)]
+    for _ in range(8000):
+        N = rng.randint(1, 128)
+        calls.append((N, step * log(1, 4096 // step), log(1, 70_000), min(N, rng.choice([1, 3, 4, 5, 10, 16]))))
+    for N, d, B, k in calls:
+        if N > (128 if dtype == 2 or k <= 4 else 64) or d % step:
+            continue
+        assert flat(plans, N, d, dtype, B, k, 1 << 30)["bytes"] == 0, (N, d, B, k)
+        assert flat(plans, N, d, dtype, B, k, 1)["bytes"] == 0, (N, d, B, k)
+
+
 # us of flat_pick_kernel with long runs of steps / without
 @pytest.mark.parametrize("d,elem_bytes,B,runs", [
     (48, 2, 2765, False),        # 41.2 / 24.3
