@@ -251,7 +251,7 @@ def _graph(graph: torch.Tensor, N: int) -> torch.Tensor:
 def ann_graph_search_typed(corpus: torch.Tensor, graph: torch.Tensor, entry: int, queries: torch.Tensor, k: int,
                            ef: int, *, ids=None, scores=None, stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """Best-first graph search with a candidate list of ef entries."""
-    if ids is None and scores is None and stream is None and type(entry) is int:
+    if ids is None and scores is None and stream is None:
         out = _usual("graph", corpus, graph, entry, queries, k, ef)
         if out is not None:
             return out
@@ -337,7 +337,7 @@ def ann_graph_search_entries_typed(corpus: torch.Tensor, graph: torch.Tensor, en
                                    stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """Graph search with one entry node per query."""
     if ids is None and scores is None and stream is None:
-        out = _usual("graph", corpus, graph, entries, queries, k, ef)
+        out = _usual("graph_entries", corpus, graph, entries, queries, k, ef)
         if out is not None:
             return out
     _matrix(corpus, "corpus"), _matrix(queries, "queries")

@@ -153,29 +153,33 @@ PyObject *flat(PyObject *, PyObject *const *args, Py_ssize_t n) {
     });
 }
 
-// corpus, graph, entry (a number, or the tensor of one entry per query), queries, k, ef, device, stream
-PyObject *graph(PyObject *, PyObject *const *args, Py_ssize_t n) {
+// corpus, graph, entry (ENTRIES: the tensor of one entry per query, else a number), queries, k, ef, device, stream
+template <bool ENTRIES>
+PyObject *graph_of_either(PyObject *, PyObject *const *args, Py_ssize_t n) {
     return usual<8>(args, n, [](PyObject *const *a) {
         const Call c(a[0], a[3], integer(a[6], 0, INT32_MAX));
         const int32_t k = int32(a[4]), ef = int32(a[5]);
         int32_t R, E = 0;
         const int32_t *g = graph_of(a[1], c, &R), *entries = nullptr;
         int32_t entry = 0;
-        if (PyLong_CheckExact(a[2])) {
-            entry = int32(a[2]);
-        } else {
+        if (ENTRIES) {
             entries = entries_of(a[2], c, &E);
             if (tensor(a[2]).dim() != 1) throw OtherForm();
+        } else {
+            entry = int32(a[2]);
         }
         void *stream = stream_of(a[7]);
         const at::Tensor ids = empty({c.B, k}, at::kInt, *c.x), scores = empty({c.B, k}, at::kFloat, *c.x);
-        const int code = E ? without_gil(graph_search_entries, c.x->data_ptr(), c.N, c.d, c.dtype, g, R, entries, c.q->data_ptr(), c.B, k,
+        const int code = ENTRIES ? without_gil(graph_search_entries, c.x->data_ptr(), c.N, c.d, c.dtype, g, R, entries, c.q->data_ptr(), c.B, k,
                                          ef, ints(ids), floats(scores), stream)
-                           : without_gil(graph_search, c.x->data_ptr(), c.N, c.d, c.dtype, g, R, entry, c.q->data_ptr(), c.B, k, ef,
+                                 : without_gil(graph_search, c.x->data_ptr(), c.N, c.d, c.dtype, g, R, entry, c.q->data_ptr(), c.B, k, ef,
                                          ints(ids), floats(scores), stream);
         return answer(code, {&ids, &scores});
     });
 }
+
+PyObject *graph(PyObject *self, PyObject *const *args, Py_ssize_t n) { return graph_of_either<false>(self, args, n); }
+PyObject *graph_entries(PyObject *self, PyObject *const *args, Py_ssize_t n) { return graph_of_either<true>(self, args, n); }
 
 // corpus, graph, entry, queries, k, ef, entries or None, tau, window, device, stream
 PyObject *nonstall(PyObject *, PyObject *const *args, Py_ssize_t n) {
@@ -245,7 +249,7 @@ PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t n) {
 }
 
 #define ENTRY(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {ENTRY(bind), ENTRY(flat), ENTRY(graph), ENTRY(nonstall), ENTRY(gather), ENTRY(order), {nullptr, nullptr, 0, nullptr}};
+PyMethodDef methods[] = {ENTRY(bind), ENTRY(flat), ENTRY(graph), ENTRY(graph_entries), ENTRY(nonstall), ENTRY(gather), ENTRY(order), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

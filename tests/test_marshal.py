@@ -18,6 +18,7 @@ def test_other_forms_are_handed_back():
     assert m.flat(x, x, 1, None, None, 0, 0) is None
     assert m.flat(x, x, 1) is None and m.flat(None, x, 1, None, None, 0, 0) is None
     assert m.graph(x, i, 0, x, 1, 4, 0, 0) is None
+    assert m.graph_entries(x, i, i, x, 1, 4, 0, 0) is None and m.graph_entries(x, i, 0, x, 1, 4, 0, 0) is None
     assert m.nonstall(x, i, 0, x, 1, 4, None, 0.9, 500, 0, 0) is None
     assert m.gather(i, i, 0, 0) is None
     assert m.order(i, x, i, x, 6, 0, 0) is None
@@ -73,6 +74,7 @@ def test_both_halves_give_the_same(monkeypatch):
         lambda: ann.ann_flat_search_typed(x, q, 4, after=after[:1]), lambda: ann.ann_graph_search_typed(x, g, 3000, q, 3, 20),
         lambda: ann.ann_graph_search_typed(x, g, 7, q, 30, 20), lambda: ann.ann_graph_search_typed(x, g[:5], 7, q, 3, 20),
         lambda: ann.ann_graph_search_entries_typed(x, g, e.view(9, 1), q, 3, 20),
+        lambda: ann.ann_graph_search_entries_typed(x, g, 5, q, 3, 20), lambda: ann.ann_graph_search_typed(x, g, e, q, 3, 20),
         lambda: ann.ann_graph_search_entries_typed(x, g, e[:4], q, 3, 20),
         lambda: ann.ann_graph_search_nonstall_typed(x, g, 7, q, 3, 20, tau=float("nan")),
         lambda: ann.ann_graph_search_nonstall_typed(x, g, 7, q, 3, 20, window=0),
