@@ -92,14 +92,18 @@ _marshal = None
 
 
 def _load_marshal(L: ctypes.CDLL) -> None:
-    """csrc/marshal.cpp is built against one torch; where it does not load, every call is marshalled here."""
+    """csrc/marshal.cpp is built against one torch and one Python; where it is not there, does not load or was built for others, every
+    call is marshalled here."""
     global _marshal
+    from . import build                                  # (here: the package does not import what `python -m` runs)
     path = os.path.join(_HERE, "_marshal.so")
     try:
         loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
         module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", path, loader=loader))
         loader.exec_module(module)
     except ImportError:
+        return
+    if getattr(module, "built_for", None) != build.marshal_target():
         return
     module.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
                   (L.ann_flat_search_typed, L.ann_flat_search_after_typed, L.ann_graph_search_typed, L.ann_graph_search_entries_typed,

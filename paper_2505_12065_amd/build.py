@@ -46,24 +46,46 @@ def _compile(src: str, force: bool) -> str:
     return obj
 
 
+def marshal_target() -> str:
+    """What _marshal.so is built for: it has the layouts of one torch's and one Python's objects compiled into it."""
+    import torch
+    return f"torch {torch.__version__} python {sys.version_info[0]}.{sys.version_info[1]}"
+
+
 def _build_marshal(force: bool) -> None:
     src = os.path.join(CSRC, "marshal.cpp")
+    target, record = marshal_target(), os.path.join(OBJ, "marshal.target")
     if not force and os.path.exists(MARSHAL) and os.path.getmtime(MARSHAL) > max(os.path.getmtime(src), _headers_mtime()):
-        return
+        if os.path.exists(record):
+            with open(record) as f:
+                if f.read() == target:
+                    return
     import sysconfig
     import torch
     from torch.utils import cpp_extension
     include = [f"-isystem{p}" for p in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]]
     libs = os.path.join(os.path.dirname(torch.__file__), "lib")
     subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
-                           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *include, src, "-o", MARSHAL,
-                           f"-L{libs}", "-ltorch_python", "-ltorch_cpu", "-lc10"])
+                           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DANN_BUILT_FOR="{target}"', *include, src,
+                           "-o", MARSHAL, f"-L{libs}", "-ltorch_python", "-ltorch_cpu", "-lc10"])
+    with open(record, "w") as f:
+        f.write(target)
+
+
+def _try_marshal(force: bool) -> None:
+    """The library does not need it: where it cannot be built, none is left and the binding marshals in Python."""
+    try:
+        _build_marshal(force)
+    except (OSError, ImportError, subprocess.CalledProcessError) as e:
+        if os.path.exists(MARSHAL):
+            os.remove(MARSHAL)
+        sys.stderr.write(f"_marshal.so was not built: {e}\n")
 
 
 def build_library(force: bool = True, jobs: int = 8) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
-        marshal = ex.submit(_build_marshal, force)
+        marshal = ex.submit(_try_marshal, force)
         objs = list(ex.map(lambda s: _compile(s, force), _sources()))
         marshal.result()
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])

@@ -1,10 +1,12 @@
 """The native half of the binding: the same answers and the same refusals as the Python half."""
+import subprocess
+
 import numpy as np
 import pytest
 import torch
 
 import paper_2505_12065_amd as ann
-from paper_2505_12065_amd import binding
+from paper_2505_12065_amd import binding, build
 
 DEV = "cuda"
 
@@ -26,6 +28,49 @@ def test_other_forms_are_handed_back():
                  lambda: ann.ann_priority_order(i, x[0].double(), i, x[0].double())):
         with pytest.raises(ValueError):
             call()
+
+
+@pytest.mark.parametrize("target", ["torch 1.0.0 python 3.10", None])
+def test_built_for_another_torch_is_not_used(monkeypatch, target):
+    """One that loads all the same would read another torch's objects."""
+    L = binding.lib()
+    assert binding._marshal.built_for == build.marshal_target()
+    monkeypatch.setattr(binding, "_marshal", None)
+    if target:
+        monkeypatch.setattr(build, "marshal_target", lambda: target)
+    binding._load_marshal(L)
+    assert (binding._marshal is None) == (target is not None)
+
+
+@pytest.mark.parametrize("error", [FileNotFoundError("g++"), subprocess.CalledProcessError(1, "g++")])
+def test_the_library_is_linked_without_it(monkeypatch, tmp_path, capsys, error):
+    """No host compiler, or no headers of Python or torch: libann.so all the same, and no _marshal.so of an older source."""
+    stale, linked = tmp_path / "_marshal.so", []
+
+    def call(cmd, **kw):
+        if cmd[0] == "g++":
+            raise error
+        linked.append(cmd)
+
+    stale.write_bytes(b"")
+    for name, value in (("OBJ", str(tmp_path)), ("MARSHAL", str(stale)), ("LIB", str(tmp_path / "libann.so")), ("_compile", lambda src, force: src)):
+        monkeypatch.setattr(build, name, value)
+    monkeypatch.setattr(build.subprocess, "check_call", call)
+    build.build_library(force=True)
+    assert len(linked) == 1 and str(tmp_path / "libann.so") in linked[0] and not stale.exists()
+    assert "_marshal.so was not built" in capsys.readouterr().err
+
+
+def test_built_again_for_another_torch(monkeypatch, tmp_path):
+    """A module newer than its source is kept if it was built for this torch and Python."""
+    calls = []
+    for name, value in (("OBJ", str(tmp_path)), ("MARSHAL", str(tmp_path / "_marshal.so"))):
+        monkeypatch.setattr(build, name, value)
+    monkeypatch.setattr(build.subprocess, "check_call", lambda cmd, **kw: (calls.append(cmd), open(build.MARSHAL, "w").close()))
+    for target, built in (("a", 1), ("a", 1), ("b", 2), ("b", 2)):
+        monkeypatch.setattr(build, "marshal_target", lambda target=target: target)
+        build._build_marshal(force=False)
+        assert len(calls) == built
 
 
 def both(call, monkeypatch):
