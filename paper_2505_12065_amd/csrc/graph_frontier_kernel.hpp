@@ -682,11 +682,11 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
             }
         }
         if (wave == NW - 1) {                             // (the last wave has the fewest rows)
-            // The adjacency rows of the queue's next nodes into the L2, out of which the rows drive what is not asked for again: 200 k x 768,
-            // B = 256, ef = 2048 2265 -> 2212 us.  Not before there is a pool (what is scored lately is there), nor with the maturity
+            // The adjacency rows of the queue's next nodes into the L2, out of which the rows drive what is not asked for again
+            // (frontier_ahead says where that pays).  Not before there is a pool (what is scored lately is there), nor with the maturity
             // exit (267 against 261 us at 200 k x 384, ef = 256).
             int touch = 0;
-            if (!NS && live > 0 && lane >= W && lane < AHEAD && t != 0) touch = graph[(size_t)key_node(t) * R];
+            if (!NS && frontier_ahead(NW) && live > 0 && lane >= W && lane < AHEAD && t != 0) touch = graph[(size_t)key_node(t) * R];
             if (known) {
                 const int slot = n_need + rank_in(__builtin_amdgcn_ballot_w64(known));
                 ck[buf * 64 + slot] = kept;

@@ -38,6 +38,7 @@ extern "C" int in_lds(int64_t N, int d, int elem_bytes, int R, int ef) {
     FrontierLds L;
     return frontier_in_lds(N, d, elem_bytes, R, ef, true, L);
 }
+extern "C" int ahead(int waves) { return frontier_ahead(waves); }
 extern "C" int runs(int cus, int d, int elem_bytes, int B) { return pick_runs(cus, (size_t)d * elem_bytes, 16 * elem_bytes, B); }
 extern "C" int shape(int cus, int64_t N, int d, int B) { return wide_shape(cus, N, d, B); }
 extern "C" int tile(int cus, int64_t N, int d, int B) { return wide_tile(cus, N, d, B); }
@@ -177,6 +178,17 @@ NEVER = float("inf")                                  # no average passes it
 ])
 def test_graph_kernels_where_they_were_measured_to_pay(plans, N, row, R, B, ef, tau, kernel):
     assert plans.graph_kernel(CUS, N, row, R, B, ef, tau is not None, NEVER if tau is None else tau) == kernel
+
+
+# us of a call with adjacency rows touched ahead / without, 200 k x 768, R = 32, B = 256 and 512
+@pytest.mark.parametrize("B,ef,ahead", [
+    (256, 2048, True),           # 2202 / 2265: the last of eight waves has nothing else to wait for
+    (512, 512, False),           # 1110 / 1030: the last of four has
+    (512, 128, False)])          # 443 / 429
+def test_adjacency_rows_touched_ahead_where_that_pays(plans, B, ef, ahead):
+    out = (ctypes.c_int64 * 14)()
+    plans.frontier(CUS, 200_000, 1536, B, ef, 0, NEVER, 0, out)
+    assert bool(plans.ahead(int(out[1]))) == ahead
 
 
 def test_steps_pay_up_to_a_size_of_the_graph(plans):
