@@ -112,9 +112,7 @@ constexpr int P_MAX = 2048;      // most slabs of the streaming kernel
 // others / this, us: up to 250 tiles 0.73 times as long on average (fp32 0.66), 200 x 768, B = 1 8.5 / 6.3; 21 025 x 480, B = 14 13.8 / 12.4; 32 877 x
 // 544, B = 3 24.6 / 17.1; but 15 197 x 704, B = 43 13.1 / 24.3; 33 953 x 64, B = 8 10.0 / 12.6; 1024 x 768, B = 512 10.4 / 17.3.
 // flat_direct_kernel: one launch, up to 128 rows in one workgroup, which then has them all to bring in: 31 x 928, B = 8 5.8 (scores 6.7), 26 x
-// 1760, B = 4 6.8; from some 60 KB (fp32, whose products are longer, 100) scores where the call may use the workspace (128 x 384, k = 10), the streaming
-// kernel's one slab where it may not.  That starts quicker where there is hardly a row (7 x 32, B = 2 4.0 / 4.8) and holds two workgroups a compute unit for many queries (3 x 832 fp32,
-// B = 11 876 25.4 / 37.2).
+// 1760, B = 4 6.8; from some 60 KB (fp32, whose products are longer, 100) scores where the call may use the workspace (more than 64 rows and k > 4).
 constexpr int DIRECT_WAVES = 8, DIRECT_ROWS = 16 * DIRECT_WAVES;
 inline int direct_held(int d, int elem_bytes) {           // steps of a query in LDS
     const int steps = ((d * elem_bytes + 63) / 64 + 3) & ~3;
@@ -130,6 +128,17 @@ inline bool scores_pay(int64_t N, int row_bytes, int dtype, int B) {
     return (double)score_tiles(N, B) * sqrt(row_bytes + 256.0) * (1 + (double)N / (100.0 * row_bytes)) <= most;
 }
 inline bool direct_pays(int64_t N, int row_bytes, int dtype) { return N <= DIRECT_ROWS && N * row_bytes < (dtype == ANN_F32 ? 100 : 60) * 1000; }
+// ... or the streaming kernel's one slab, whose scores have the same bits.  It starts quicker where there is hardly a row (7 x 32, B = 2 4.0 / 4.8),
+// holds two workgroups a compute unit for many queries (3 x 832 fp32, B = 11 876 25.4 / 37.2), and goes by whole runs of four steps: rows that end inside
+// one cost it much.  1048 calls of up to 128 rows, its us / flat_direct_kernel's.  Whole runs: 128 x 128, B = 16 4.95 / 4.38; 16 x 384, B = 64 4.54 / 4.04; but
+// 16 x 1536, B = 16 6.67 / 8.41; 128 x 768, B = 1 9.30 / 9.25; fp32 128 x 64, B = 16 6.39 / 5.38, 64 x 384, B = 64 8.13 / 9.83, 128 x 384, B = 64 10.6 / 14.1.
+// Others: 17 x 496, B = 1 6.34 / 4.36; 35 x 3944, B = 578 22.5 / 17.0; fp32 18 x 4048, B = 554 70.9 / 62.3, 121 x 272, B = 65 10.0 / 11.4.  By this line 0.924 times as long as the
+// streaming kernel on average (the better of both 0.911), eight calls longer by 5 to 9 %; by bytes alone, as for scores, 0.945, 58 longer by up to 26 %.
+inline bool direct_quick(int cus, int64_t N, int row_bytes, int dtype, int B) {
+    if (N > DIRECT_ROWS || N * row_bytes < 2000 || (B + 15) / 16 > cus) return false;
+    if (row_bytes % 256 == 0) return dtype == ANN_F32 ? row_bytes <= 512 && N * row_bytes <= 48000 : row_bytes <= 1024;
+    return dtype != ANN_F32 || N <= 64 || row_bytes <= 384 || row_bytes >= 4096;
+}
 
 struct FlatPlan {
     bool scores;             // flat_scores_kernel and flat_pick_kernel (w.n scores a query), or
@@ -518,7 +527,7 @@ inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, si
     // Lists of 4 per lane are complete there whatever k is, since a lane sees four rows; selecting k > 4 from all eight
     // waves costs more than the launch saves where the other way is group maxima (128 x 1024 bf16, B = 5000, k = 16: 19.3 / 23.3).
     pl.direct = none || (few && N <= DIRECT_ROWS);
-    pl.quick = pl.direct && one && N * row_bytes >= 2000 && (B + 15) / 16 <= cus;
+    pl.quick = pl.direct && direct_quick(cus, N, row_bytes, dtype, B);
     pl.maxima = !pl.direct && dtype == ANN_F32 && use_f32_maxima(N, d, B, k);
     pl.wide = !pl.direct && use_wide(N, d, dtype, B, k);
     auto plan = [&] {

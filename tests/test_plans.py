@@ -42,14 +42,15 @@ extern "C" int ahead(int waves) { return frontier_ahead(waves); }
 extern "C" int runs(int cus, int d, int elem_bytes, int B) { return pick_runs(cus, (size_t)d * elem_bytes, 16 * elem_bytes, B); }
 extern "C" int shape(int cus, int64_t N, int d, int B) { return wide_shape(cus, N, d, B); }
 extern "C" int tile(int cus, int64_t N, int d, int B) { return wide_tile(cus, N, d, B); }
-// out: kind (0 lists, 1 direct, 2 matrix cores, 3 streaming with maxima), queries and rows at a time, maxima of a query,
+static int kind(const FlatPlan &pl) { return pl.scores ? 4 : pl.quick ? 5 : pl.wide ? 2 : pl.maxima ? 3 : pl.direct ? 1 : 0; }
+// out: kind (0 lists, 1 direct, 2 matrix cores, 3 streaming with maxima, 4 scores, 5 direct by flat_direct_kernel), queries and rows at a time, maxima of a query,
 // log2 of the rows they stand for, offset of the k best so far, workspace, maxima of the smallest last part
 extern "C" void flat(int cus, int64_t N, int d, int dtype, int B, int k, int64_t limit, int64_t *out) {
     const FlatPlan pl = flat_plan(cus, N, d, dtype, B, k, (size_t)limit);
     const int64_t rows = N % pl.rows ? N % pl.rows : pl.rows;
     const int part = B % pl.part ? B % pl.part : pl.part;
     const FlatPlan last = pl.wide || pl.maxima ? maxima_part(pl, rows, part, d, dtype) : pl;
-    const int64_t v[] = {pl.wide ? 2 : pl.maxima ? 3 : pl.direct ? 1 : 0, pl.part, pl.rows, pl.w.n, pl.w.gs_log,
+    const int64_t v[] = {kind(pl), pl.part, pl.rows, pl.w.n, pl.w.gs_log,
                          (int64_t)pl.best_ofs, (int64_t)pl.ws_bytes, last.w.n, last.w.gs_log};
     for (int i = 0; i < 9; ++i) out[i] = v[i];
 }
@@ -58,10 +59,10 @@ extern "C" int static_accepts(int cus, int64_t N, int d, int dtype, int B, int k
 }
 extern "C" int static_kind(int cus, int64_t N, int d, int dtype, int B, int k, int64_t bytes) {
     const FlatPlan pl = static_plan(cus, N, d, dtype, B, k, (size_t)bytes);
-    return pl.ws_bytes > (size_t)bytes ? -1 : pl.wide ? 2 : pl.maxima ? 3 : pl.direct ? 1 : 0;
+    return pl.ws_bytes > (size_t)bytes ? -1 : kind(pl);
 }
 """
-KINDS = ("lists", "direct", "wide", "maxima")
+KINDS = ("lists", "direct", "wide", "maxima", "scores", "quick")
 STATIC = 8 * 1024 * 1024 + 1024 * 16 * 8             # the static workspace, room for the k best of a part's queries included
 
 
@@ -402,6 +403,29 @@ def test_searches_that_need_no_workspace(plans, N, d, elem_bytes, ef):
     """The largest graphs whose maturity search keeps its visited set in LDS where no workspace is at hand: the calls that ran
     with none when lists were written out."""
     assert plans.in_lds(N, d, elem_bytes, 32, ef)
+
+
+# us of a call, the streaming kernel's one slab / flat_direct_kernel
+@pytest.mark.parametrize("N,d,dtype,B,kind", [
+    (128, 128, 0, 16, "quick"),          # 4.95 / 4.38
+    (16, 384, 0, 64, "quick"),           # 4.54 / 4.04
+    (64, 512, 0, 16, "quick"),
+    (16, 1_536, 0, 16, "direct"),        # 6.67 / 8.41: whole runs of steps, long rows
+    (4, 2_048, 1, 512, "direct"),        # 7.76 / 9.62
+    (128, 768, 0, 64, "direct"),         # 10.2 / 10.4
+    (17, 496, 0, 1, "quick"),            # 6.34 / 4.36: rows that end inside a run
+    (35, 3_944, 0, 578, "quick"),        # 22.5 / 17.0
+    (74, 528, 0, 1, "quick"),            # 7.47 / 6.39
+    (128, 64, 2, 16, "quick"),           # 6.39 / 5.38
+    (64, 384, 2, 64, "direct"),          # 8.13 / 9.83
+    (93, 448, 2, 1_514, "direct"),       # 11.1 / 14.1
+    (128, 384, 2, 64, "direct"),         # 10.6 / 14.1
+    (18, 4_048, 2, 554, "quick"),        # 70.9 / 62.3
+    (121, 272, 2, 65, "direct"),         # 10.0 / 11.4
+    (7, 32, 0, 2, "direct"),             # 4.0 / 4.8
+    (3, 832, 2, 11_876, "direct")])      # 25.4 / 37.2
+def test_one_launch_for_few_rows(plans, N, d, dtype, B, kind):
+    assert KINDS[flat(plans, N, d, dtype, B, 1, 1 << 30)["kind"]] == kind
 
 
 @pytest.mark.parametrize("dtype", [0, 1, 2])
