@@ -107,10 +107,13 @@ inline int wide_rows(int shape) {                         // corpus rows of a ti
 constexpr int P_MAX = 2048;      // most slabs of the streaming kernel
 
 // Few queries against few rows.  flat_scores_kernel: tiles of 16 rows x 16 queries, a wave each, and flat_pick_kernel.  It has no tile
-// that spares the L1s, so the line is that of the bytes they bring in; short rows make the pick, which looks at every score, the larger part, and
-// more than 64 queries fill the tiles of the matrix-core kernel.  Fitted to 900 calls of 129 to 60 000 rows, B = 1 to 1024, rows of 128 bytes to 4 KB,
-// others / this, us: up to 250 tiles 0.73 times as long on average (fp32 0.66), 200 x 768, B = 1 8.5 / 6.3; 21 025 x 480, B = 14 13.8 / 12.4; 32 877 x
-// 544, B = 3 24.6 / 17.1; but 15 197 x 704, B = 43 13.1 / 24.3; 33 953 x 64, B = 8 10.0 / 12.6; 1024 x 768, B = 512 10.4 / 17.3.
+// that spares the L1s, so the line is that of the bytes they bring in; short rows make the pick, which looks at every score, the larger part.
+// Where the streaming kernel's lists would take the call instead, they pay longest (a little less where one group of 16 queries is well filled); the
+// matrix-core kernel's tiles are the better the more queries fill them.  us, lists / this: 10 000 x 128 fp32, B = 16, k = 10 11.6 / 10.3; 21 025 x 480,
+// B = 14 13.8 / 12.4; 18 204 x 416, B = 20 18.1 / 14.8; but 27 070 x 896, B = 16 17.4 / 21.4; 33 953 x 64, B = 8 10.0 / 12.6.  Matrix cores / this: 200 x 768, B = 1
+// 8.5 / 6.3, B = 256 9.6 / 7.2; 2860 x 352, B = 1 10.7 / 6.2; but 12 383 x 768, B = 22 12.7 / 17.5; 5087 x 1984, B = 17 14.5 / 18.7; 2781 x 2496, B = 38 14.7 / 19.2; 8691 x
+// 192, B = 57 10.5 / 12.8; 1024 x 768, B = 512 10.4 / 17.3.  Of 1068 16-bit calls of 129 to 60 000 rows and B = 1 to 1024 0.874 times as long on average, 17 longer by
+// more than 3 %, 14 % at most (by one line of 95 000 up to 64 queries, 35 000 beyond: 0.878, 62, 70 %).  fp32 0.72 times, 2 and 8 %.
 // flat_direct_kernel: one launch, up to 128 rows in one workgroup, which then has them all to bring in: 31 x 928, B = 8 5.8 (scores 6.7), 26 x
 // 1760, B = 4 6.8; from some 60 KB (fp32, whose products are longer, 100) scores where the call may use the workspace (more than 64 rows and k > 4).
 constexpr int DIRECT_WAVES = 8, DIRECT_ROWS = 16 * DIRECT_WAVES;
@@ -123,8 +126,9 @@ inline size_t direct_lds_bytes(int d, int elem_bytes) {
     return q > m ? q : m;
 }
 inline int64_t score_tiles(int64_t N, int B) { return (N + 15) / 16 * (((int64_t)B + 15) / 16); }
-inline bool scores_pay(int64_t N, int row_bytes, int dtype, int B) {
-    const double most = dtype == ANN_F32 ? 48e3 : B <= 64 ? 95e3 : 35e3;
+inline bool scores_pay(int64_t N, int row_bytes, int dtype, int B, bool lists) {
+    const double most = dtype == ANN_F32 ? 48e3 : lists ? (B > 8 && B <= 16 ? 75e3 : 95e3)
+                        : B <= 8 ? 95e3 : B <= 16 ? 60e3 : 35e3;
     return (double)score_tiles(N, B) * sqrt(row_bytes + 256.0) * (1 + (double)N / (100.0 * row_bytes)) <= most;
 }
 inline bool direct_pays(int64_t N, int row_bytes, int dtype) { return N <= DIRECT_ROWS && N * row_bytes < (dtype == ANN_F32 ? 100 : 60) * 1000; }
@@ -513,7 +517,7 @@ inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, si
     pl.rows = N;
     const int row_bytes = d * elem_bytes(dtype);
     const size_t scores = (size_t)B * (size_t)((N + 3) & ~(int64_t)3) * sizeof(float);
-    const bool few = scores_pay(N, row_bytes, dtype, B), one = direct_pays(N, row_bytes, dtype);
+    const bool few = scores_pay(N, row_bytes, dtype, B, !use_wide(N, d, dtype, B, k)), one = direct_pays(N, row_bytes, dtype);
     // So few rows never need a workspace, whatever their length and the batch: such searches may overlap anything, and each other.
     const bool none = N <= (k <= 4 || dtype == ANN_F32 ? DIRECT_ROWS : DIRECT_ROWS / 2);
     pl.scores = few && !none && !one && scores <= limit;

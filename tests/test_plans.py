@@ -428,6 +428,28 @@ def test_one_launch_for_few_rows(plans, N, d, dtype, B, kind):
     assert KINDS[flat(plans, N, d, dtype, B, 1, 1 << 30)["kind"]] == kind
 
 
+# us of a call, the streaming kernel's lists or the matrix cores / flat_scores_kernel and a pick
+@pytest.mark.parametrize("N,d,dtype,B,k,scores", [
+    (21_025, 480, 0, 14, 2, True),       # lists 13.8 / 12.4
+    (10_000, 128, 2, 16, 10, True),      # 11.6 / 10.3
+    (18_204, 416, 1, 20, 3, True),       # 18.1 / 14.8
+    (12_722, 32, 0, 18, 3, True),        # 10.0 / 8.5
+    (27_070, 896, 1, 16, 16, False),     # 17.4 / 21.4
+    (33_953, 64, 0, 8, 3, False),        # 10.0 / 12.6
+    (200, 768, 0, 1, 3, True),           # matrix cores 8.5 / 6.3
+    (200, 768, 0, 256, 1, True),         # 9.6 / 7.2
+    (128, 384, 0, 9, 10, True),          # more than 64 rows, k > 4: may use the workspace
+    (14_587, 320, 0, 30, 10, False),     # 11.4 / 14.0
+    (12_383, 768, 1, 22, 5, False),      # 12.7 / 17.5
+    (7_912, 1_408, 1, 22, 5, False),     # 12.9 / 17.4
+    (5_087, 1_984, 1, 17, 16, False),    # 14.5 / 18.7
+    (2_781, 2_496, 0, 38, 1, False),     # 14.7 / 19.2
+    (8_691, 192, 0, 57, 10, False),      # 10.5 / 12.8
+    (1_024, 768, 0, 512, 1, False)])     # 10.4 / 17.3
+def test_scores_where_they_were_measured_to_pay(plans, N, d, dtype, B, k, scores):
+    assert (KINDS[flat(plans, N, d, dtype, B, k, 1 << 30)["kind"]] == "scores") == scores
+
+
 @pytest.mark.parametrize("dtype", [0, 1, 2])
 def test_few_rows_need_no_workspace(plans, dtype):
     """Exact searches of so few rows may overlap anything, so none of them, however long its rows and large its batch, may write the
