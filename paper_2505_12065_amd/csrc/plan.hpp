@@ -287,9 +287,8 @@ inline int wide_shape(int cus, int64_t N, int d, int B) {
 // with the chip full of its kind; where two workgroups share a compute unit and do not fill it, less by `share` of what is missing.  The
 // 128 x 128 tile stands between: two fragments each way (a byte read from LDS feeds half as many products again as with 128 x 64) and
 // two workgroups to a compute unit, which fill each other's waits, so that two stages do.  Constants fitted to 287 calls of 200 to 2.5 M rows,
-// 66 to 8192 queries, d = 72 to 1024: 0.8 % behind the best tile on average (the first rule 3.2 %); 190 others 2.3 % faster on average
-// than by the first rule, the slowest of them 2 % slower.  First
-// rule / this, us: 977 x 768, B = 5000, k = 16 26.6 / 25.2; 2000 x 768, B = 3000 26.9 / 24.0; 24 k x 768, B = 200 26.2 / 21.9;
+// 66 to 8192 queries, d = 72 to 1024: 0.8 % behind the best tile on average (the first rule 3.2 %).  1256 other calls whose tile it changes take 0.938 times as long
+// on average, 31 of them longer by more than 2 %, 12.5 % at most (before the lines of wide_tile 0.940, 108, 13.6 %).  First rule / this, us: 977 x 768, B = 5000, k = 16 26.6 / 25.2; 2000 x 768, B = 3000 26.9 / 24.0; 24 k x 768, B = 200 26.2 / 21.9;
 // 10.5 k x 768, B = 6152 211 / 195; 46 k x 384, B = 883 72.4 / 66.3; 38.8 k x 776, B = 68 32.9 / 27.4; 110 k x 384, B = 535 82 / 76.
 // Corpora beyond 64 MB come from memory, where tiles of few queries read them too often (110 k x 768, B = 301 92 by 256 x 128, 101 by 128 x 128, 105 by
 // 128 x 64); rows of up to 64 elements are mostly start and end of a tile (10 k x 64, B = 808 18.7 / 20.7).
@@ -315,19 +314,23 @@ inline double wide_rounds_us(int shape, int cus, int64_t N, int d, int B) {
     const double full = (double)(groups < slots ? groups : slots) / cus;              // workgroups on a compute unit
     return rounds * (a + b * lines / 2 * (1 + share * (full > 1 ? full - 1 : 0)));
 }
-inline int wide_tile(int cus, int64_t N, int d, int B) {
+inline int wide_tile(int cus, int64_t N, int d, int B, int k) {
     const int first = wide_shape(cus, N, d, B);
     if (B <= 64 || d <= 64 || first == WIDE_TINY) return first;
     const bool cached = N * d * 2 <= 64000000;
     if (!cached && (first == WIDE_THIN || first == WIDE_SHORT)) return first;
+    // (the model takes the half-line tile for the one of whole lines: 38 784 x 96, B = 68 12.9 / 13.8 by 128 x 128, 1025 x 72, B = 4097 21.0 / 21.5, 22 463 x
+    // 160, B = 133 3 % longer; from 161 elements on 0.97 times as long)
+    if (first == WIDE_SHORT && d <= 160) return first;
     int best = first;
     const double stays = wide_rounds_us(first, cus, N, d, B);
-    double least = 0.95 * stays;                          // (closer than that the model does not tell them apart)
+    double least = (cached ? 0.95 : 0.93) * stays;        // (closer than that the model does not tell them apart)
     for (int shape : {WIDE_LARGE, WIDE_TALL, WIDE_MID, WIDE_SQUARE, WIDE_THIN}) {
         if (!cached && (shape == WIDE_SQUARE || shape == WIDE_THIN)) continue;
         const double us = wide_rounds_us(shape, cus, N, d, B);
-        // (256 x 128 with a half empty last round runs faster in it than the model has it: 15.7 k x 384, B = 839 29.7 / 32.1 by 256 x 256)
-        if (shape == WIDE_LARGE && first == WIDE_MID && us > 0.9 * stays) continue;
+        // (256 x 128 with a half empty last round runs faster in it than the model has it: 15.7 k x 384, B = 839 29.7 / 32.1 by 256 x 256; and the pick of long
+        // answers, which the model leaves out, has more to do behind the large tiles: 17.0 k x 128, B = 867, k = 16 24.8 / 28.2 by 512 x 128)
+        if (first == WIDE_MID && (shape == WIDE_LARGE || shape == WIDE_TALL) && us > (k > 10 && cached ? 0.84 : shape == WIDE_LARGE ? 0.9 : 1) * stays) continue;
         if (us < least) { least = us; best = shape; }
     }
     return best == WIDE_THIN ? wide_thin(cus, N, d, B) : best;
@@ -383,7 +386,7 @@ inline size_t maxima_pass(FlatPlan &pl, int cus, int d, int dtype, int k, size_t
     const int B = pl.part;
     const size_t most = room / ((size_t)B * sizeof(float));
     if (pl.wide) {
-        wide_geometry(pl.w, pl.by_fill ? wide_shape(cus, N, d, B) : wide_tile(cus, N, d, B), cus, N, B);
+        wide_geometry(pl.w, pl.by_fill ? wide_shape(cus, N, d, B) : wide_tile(cus, N, d, B, k), cus, N, B);
         // A tile's groups have 16 wmf rows at most: where those are too many, the tile of 64 if there are enough for the chip,
         // else the one of 32 that pads least (300 k x 64, B = 300 in 1 MiB: 7 parts of the corpus, 14 by groups of 32).
         if (pl.w.wmf < 4 && (size_t)maxima_of(pl.w.wmf, pl.w.slots, 3 + pl.w.wmf) > most) {

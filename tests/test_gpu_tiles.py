@@ -68,6 +68,8 @@ def test_line_stages(dtype, N, d, B, k):
     (torch.bfloat16, 1_025, 72, 4_097, 16),    # ... one row, one query in the last tiles
     (torch.float16, 24_001, 264, 200, 3),      # groups of rows, one row in the last tile
     (torch.bfloat16, 38_784, 96, 68, 10),      # ... whole tiles of rows, one query tile half empty
+    (torch.bfloat16, 1_025, 72, 5_000, 16),    # ... a line of 16 bytes behind one (B = 4097 goes by half lines, as does d = 96)
+    (torch.float16, 50_049, 136, 66, 10),      # ... two queries in the tile
     (torch.float16, 46_408, 384, 883, 5),      # ... slabs of several tiles
 ])
 def test_square_tiles(dtype, N, d, B, k):

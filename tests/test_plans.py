@@ -41,7 +41,7 @@ extern "C" int in_lds(int64_t N, int d, int elem_bytes, int R, int ef) {
 extern "C" int ahead(int waves) { return frontier_ahead(waves); }
 extern "C" int runs(int cus, int d, int elem_bytes, int B) { return pick_runs(cus, (size_t)d * elem_bytes, 16 * elem_bytes, B); }
 extern "C" int shape(int cus, int64_t N, int d, int B) { return wide_shape(cus, N, d, B); }
-extern "C" int tile(int cus, int64_t N, int d, int B) { return wide_tile(cus, N, d, B); }
+extern "C" int tile(int cus, int64_t N, int d, int B, int k) { return wide_tile(cus, N, d, B, k); }
 static int kind(const FlatPlan &pl) { return pl.scores ? 4 : pl.quick ? 5 : pl.wide ? 2 : pl.maxima ? 3 : pl.direct ? 1 : 0; }
 // out: kind (0 lists, 1 direct, 2 matrix cores, 3 streaming with maxima, 4 scores, 5 direct by flat_direct_kernel), queries and rows at a time, maxima of a query,
 // log2 of the rows they stand for, offset of the k best so far, workspace, maxima of the smallest last part
@@ -77,7 +77,8 @@ def plans(tmp_path_factory):
     L.graph_kernel.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 5 + [ctypes.c_float]
     L.leaves.argtypes = [ctypes.c_float] + [ctypes.c_int] * 3
     L.frontier.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_float, ctypes.c_int, ctypes.c_void_p]
-    L.shape.argtypes = L.tile.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 2
+    L.shape.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 2
+    L.tile.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 3
     L.in_lds.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4
     L.flat.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64, ctypes.c_void_p]
     L.static_accepts.argtypes = L.static_kind.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64]
@@ -536,10 +537,21 @@ SQUARE = 6
     (1_000_000, 768, 512, LARGE),
     (110_746, 768, 301, MID),        # from memory: tiles of few queries read too often, 92 / 101 by 128 x 128
     (10_427, 64, 808, MID),          # short rows: the first rule's, 18.7 / 20.7 by 256 x 256
-    (977, 776, 5_000, SQUARE), (1_025, 72, 4_097, SQUARE), (24_001, 264, 200, SQUARE), (38_784, 96, 68, SQUARE), (46_408, 384, 883, SQUARE),
+    (977, 776, 5_000, SQUARE), (1_025, 72, 5_000, SQUARE), (24_001, 264, 200, SQUARE), (50_049, 136, 66, SQUARE), (46_408, 384, 883, SQUARE),
+    (1_025, 72, 4_097, SHORT),       # 21.0 / 21.5 by 128 x 128: the half-line tile, which the model does not know, up to 160 elements
+    (38_784, 96, 68, SHORT),         # 12.9 / 13.8
+    (22_463, 160, 133, SHORT),       # 3 % longer by 128 x 128
+    (22_751, 192, 210, SQUARE),      # 0.94 times as long
+    (2_268_470, 384, 70, TALL),      # 366 / 381 by 256 x 128: from memory too close to tell
     (40_000, 768, 64, THIN), (1_024, 768, 512, TINY), (1_200_000, 24, 18, SHORT)])
 def test_tiles_by_rounds(plans, N, d, B, tile):
-    assert plans.tile(CUS, N, d, B) == tile
+    assert plans.tile(CUS, N, d, B, 3) == tile
+
+
+@pytest.mark.parametrize("N,d,B", [(16_958, 128, 867), (18_158, 160, 778), (15_932, 168, 822)])
+def test_long_answers_behind_large_tiles(plans, N, d, B):
+    """k = 16: 24.8 us by 256 x 128, 28.2 by 512 x 128; 26.4 / 28.2; 26.3 / 29.1 by 256 x 256, whose pick has more to do."""
+    assert plans.tile(CUS, N, d, B, 16) == MID and plans.tile(CUS, N, d, B, 10) != MID
 
 
 @pytest.mark.parametrize("seed", range(3))
