@@ -14,11 +14,14 @@ F16, BF16, F32 = torch.float16, torch.bfloat16, torch.float32
     (BF16, 17, 104, 17, 16),               # ... a row and a query in a second tile, a step of 16 bytes
     (F16, 64, 456, 33, 7),                 # ... whole tiles
     (F16, 113, 264, 5, 16),                # ... the last wave has one row
-    (F32, 128, 132, 16, 10),               # ... all waves full
+    (F32, 128, 132, 16, 10),               # the streaming kernel's one slab: fp32, a row that ends inside a run, all waves full
+    (F32, 128, 96, 16, 10),                # one launch: all waves full
     (F32, 20, 1_092, 40, 5),               # ... more steps than are in flight at once
-    (F32, 4, 4_096, 3, 4),                 # ... queries longer than the LDS holds
+    (F32, 4, 4_096, 3, 4),                 # one slab: whole runs of long rows
+    (F32, 4, 4_092, 3, 4),                 # one launch: queries longer than the LDS holds
     (F16, 16, 1_040, 300, 3),              # ... many queries
-    (F16, 128, 240, 2, 3),                 # scores: the fewest bytes of 128 rows
+    (F16, 128, 240, 2, 3),                 # ... all waves full, 60 KB
+    (F16, 100, 1_024, 2, 16),              # scores: up to 128 rows
     (F16, 129, 8, 1, 16),                  # ... one chunk of a step
     (BF16, 1_999, 776, 16, 16),            # ... a run cut after its first chunk, scores not a multiple of 4
     (F16, 2_048, 768, 17, 10),             # ... all steps in flight
@@ -98,3 +101,25 @@ def test_few_rows_on_two_streams_at_once(dtype, N, d, B, k):
     torch.cuda.synchronize()
     for i in range(2):
         assert all(torch.equal(ids, alone[i][0]) and torch.equal(sc, alone[i][1]) for ids, sc in out[i])
+
+
+@pytest.mark.parametrize("dtype,N,d,B,k", [(F32, 10_000, 132, 16, 10), (F32, 700, 2_052, 9, 4), (F16, 21_025, 480, 14, 2)])
+def test_scores_are_the_streaming_kernels_bits(dtype, N, d, B, k):
+    """In a buffer that does not hold the scores the same call goes by lists: the same ids and the same bits, page after page."""
+    print(f"bits: dtype={dtype} N={N} d={d} B={B} k={k}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(N)
+    x, q = (torch.randn(n, d, generator=gen, device=DEV).to(dtype) for n in (N, B))
+    size = ann.ann_flat_workspace_bytes(N, d, dtype, B, k) - 16
+    buf = torch.empty(size, dtype=torch.uint8, device=DEV)
+    pages = []
+    try:
+        for given in (None, buf):
+            torch.cuda.synchronize()
+            ann.ann_set_workspace(given)
+            first = ann.ann_flat_search_typed(x, q, k)
+            after = (first[1][:, -1].contiguous(), first[0][:, -1].contiguous())
+            pages.append([*first, *ann.ann_flat_search_typed(x, q, k, after=after)])
+            torch.cuda.synchronize()
+    finally:
+        ann.ann_set_workspace(None)
+    assert all(torch.equal(a, b) for a, b in zip(*pages))

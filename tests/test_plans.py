@@ -44,15 +44,21 @@ extern "C" int shape(int cus, int64_t N, int d, int B) { return wide_shape(cus, 
 extern "C" int tile(int cus, int64_t N, int d, int B, int k) { return wide_tile(cus, N, d, B, k); }
 static int kind(const FlatPlan &pl) { return pl.scores ? 4 : pl.quick ? 5 : pl.wide ? 2 : pl.maxima ? 3 : pl.direct ? 1 : 0; }
 // out: kind (0 lists, 1 direct, 2 matrix cores, 3 streaming with maxima, 4 scores, 5 direct by flat_direct_kernel), queries and rows at a time, maxima of a query,
-// log2 of the rows they stand for, offset of the k best so far, workspace, maxima of the smallest last part
-extern "C" void flat(int cus, int64_t N, int d, int dtype, int B, int k, int64_t limit, int64_t *out) {
-    const FlatPlan pl = flat_plan(cus, N, d, dtype, B, k, (size_t)limit);
+// log2 of the rows they stand for, offset of the k best so far, workspace, maxima of the smallest last part and the rows they stand for, tile;
+// by_fill: by the first rule for the tile alone
+static void describe(const FlatPlan &pl, int64_t N, int d, int dtype, int B, int64_t *out) {
     const int64_t rows = N % pl.rows ? N % pl.rows : pl.rows;
     const int part = B % pl.part ? B % pl.part : pl.part;
     const FlatPlan last = pl.wide || pl.maxima ? maxima_part(pl, rows, part, d, dtype) : pl;
-    const int64_t v[] = {kind(pl), pl.part, pl.rows, pl.w.n, pl.w.gs_log,
-                         (int64_t)pl.best_ofs, (int64_t)pl.ws_bytes, last.w.n, last.w.gs_log};
-    for (int i = 0; i < 9; ++i) out[i] = v[i];
+    const int64_t v[] = {kind(pl), pl.part, pl.rows, pl.w.n, pl.w.gs_log, (int64_t)pl.best_ofs, (int64_t)pl.ws_bytes, last.w.n, last.w.gs_log,
+                         pl.w.shape};
+    for (int i = 0; i < 10; ++i) out[i] = v[i];
+}
+extern "C" void flat(int cus, int64_t N, int d, int dtype, int B, int k, int64_t limit, int64_t *out) {
+    describe(flat_plan(cus, N, d, dtype, B, k, (size_t)limit), N, d, dtype, B, out);
+}
+extern "C" void flat_by_fill(int cus, int64_t N, int d, int dtype, int B, int k, int64_t limit, int64_t *out) {
+    describe(flat_plan(cus, N, d, dtype, B, k, (size_t)limit, false, true), N, d, dtype, B, out);
 }
 extern "C" int static_accepts(int cus, int64_t N, int d, int dtype, int B, int k, int64_t bytes) {
     return static_plan(cus, N, d, dtype, B, k, (size_t)bytes).ws_bytes <= (size_t)bytes;
@@ -80,15 +86,15 @@ def plans(tmp_path_factory):
     L.shape.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 2
     L.tile.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 3
     L.in_lds.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4
-    L.flat.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64, ctypes.c_void_p]
+    L.flat.argtypes = L.flat_by_fill.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64, ctypes.c_void_p]
     L.static_accepts.argtypes = L.static_kind.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64]
     return L
 
 
-def flat(L, N, d, dtype, B, k, limit):
-    out = (ctypes.c_int64 * 9)()
-    L.flat(CUS, N, d, dtype, B, k, limit, out)
-    return dict(zip(("kind", "part", "rows", "n", "gs_log", "best_ofs", "bytes", "last_n", "last_gs_log"), out))
+def flat(L, N, d, dtype, B, k, limit, by_fill=False):
+    out = (ctypes.c_int64 * 10)()
+    (L.flat_by_fill if by_fill else L.flat)(CUS, N, d, dtype, B, k, limit, out)
+    return dict(zip(("kind", "part", "rows", "n", "gs_log", "best_ofs", "bytes", "last_n", "last_gs_log", "shape"), out))
 
 
 SEARCH, FRONTIER, STEP = 0, 1, 2
@@ -451,6 +457,28 @@ def test_scores_where_they_were_measured_to_pay(plans, N, d, dtype, B, k, scores
     assert (KINDS[flat(plans, N, d, dtype, B, k, 1 << 30)["kind"]] == "scores") == scores
 
 
+# the shapes of tests/test_gpu_small.py reach what they are there for
+@pytest.mark.parametrize("dtype,N,d,B,k,kind", [
+    (0, 1, 1_000, 1, 1, "quick"), (1, 17, 104, 17, 16, "quick"), (0, 64, 456, 33, 7, "quick"), (0, 113, 264, 5, 16, "quick"),
+    (2, 128, 96, 16, 10, "quick"), (2, 20, 1_092, 40, 5, "quick"), (2, 4, 4_092, 3, 4, "quick"), (0, 16, 1_040, 300, 3, "quick"),
+    (0, 128, 240, 2, 3, "quick"), (0, 100, 200, 20, 8, "quick"),
+    (0, 100, 1_024, 2, 16, "scores"), (0, 129, 8, 1, 16, "scores"), (1, 1_999, 776, 16, 16, "scores"), (0, 2_048, 768, 17, 10, "scores"),
+    (0, 2_049, 1_544, 3, 1, "scores"), (2, 10_000, 132, 16, 10, "scores"), (2, 700, 2_052, 9, 4, "scores"), (0, 21_025, 480, 14, 2, "scores"),
+    (0, 2_000, 200, 20, 8, "scores"), (1, 4_000, 64, 3, 16, "scores"),
+    (2, 128, 132, 16, 10, "direct"), (2, 4, 4_096, 3, 4, "direct"), (0, 128, 768, 64, 4, "direct"), (1, 64, 2_048, 33, 16, "direct"),
+    (2, 100, 512, 40, 10, "direct"), (0, 80, 768, 512, 1, "direct")])
+def test_kernels_of_few_rows(plans, dtype, N, d, B, k, kind):
+    assert KINDS[flat(plans, N, d, dtype, B, k, 1 << 30)["kind"]] == kind
+
+
+@pytest.mark.parametrize("dtype,N,d,B,k", [(2, 10_000, 132, 16, 10), (2, 700, 2_052, 9, 4), (0, 21_025, 480, 14, 2)])
+def test_scores_give_way_to_lists_in_a_smaller_buffer(plans, dtype, N, d, B, k):
+    """What tests/test_gpu_small.py compares the bits of."""
+    p = flat(plans, N, d, dtype, B, k, 1 << 30)
+    q = flat(plans, N, d, dtype, B, k, p["bytes"] - 16)
+    assert KINDS[p["kind"]] == "scores" and KINDS[q["kind"]] == "lists" and q["bytes"] < p["bytes"]
+
+
 @pytest.mark.parametrize("dtype", [0, 1, 2])
 def test_few_rows_need_no_workspace(plans, dtype):
     """Exact searches of so few rows may overlap anything, so none of them, however long its rows and large its batch, may write the
@@ -556,19 +584,27 @@ def test_long_answers_behind_large_tiles(plans, N, d, B):
 
 @pytest.mark.parametrize("seed", range(3))
 def test_fewest_rounds_only_where_the_maxima_fit_at_once(plans, seed):
-    """A call that has no room for all maxima gets the plan that it got by the first rule alone."""
+    """A call that goes in parts gets the plan of the first rule alone, tile included; one that does not may get another tile, in any room that holds its
+    maxima, of larger groups if need be.  What the first rule's plan fits, either fits."""
     rng = random.Random(seed)
-    for _ in range(400):
+    other = parts = 0
+    for _ in range(1500):
         N, B = (int(math.exp(rng.uniform(math.log(lo), math.log(hi)))) for lo, hi in ((200, 3e6), (66, 8192)))
         d, k = 8 * rng.randint(1, 128), rng.choice([1, 3, 10, 16])
         k = min(k, N)
         whole = flat(plans, N, d, 0, B, k, 1 << 30)
+        for limit in (1 << 30, whole["bytes"], int(whole["bytes"] * rng.uniform(0.01, 0.9))):
+            p, first = flat(plans, N, d, 0, B, k, limit), flat(plans, N, d, 0, B, k, limit, by_fill=True)
+            assert p["bytes"] <= limit or first["bytes"] > limit, (N, d, B, k, limit)
+            if p["part"] < B or p["rows"] < N:
+                assert p == first, (N, d, B, k, limit)
+                parts += 1
+            other += p["shape"] != first["shape"]
         again = flat(plans, N, d, 0, B, k, whole["bytes"])
-        assert again["bytes"] <= whole["bytes"] and (again["part"], again["rows"]) == (whole["part"], whole["rows"])
-        small = flat(plans, N, d, 0, B, k, int(whole["bytes"] * rng.uniform(0.01, 0.9)))
-        assert small["bytes"] <= whole["bytes"]
+        assert again["bytes"] <= whole["bytes"] and (again["part"], again["rows"], again["shape"]) == (whole["part"], whole["rows"], whole["shape"])
         if whole["bytes"] <= 8 * 1024 * 1024:
             assert plans.static_accepts(CUS, N, d, 0, B, k, STATIC), (N, d, B, k)
+    assert parts > 100 and other > 100, (parts, other)
 
 
 # share of queries that leave early
