@@ -95,7 +95,8 @@ const char *ann_last_error(void);
  * materialised.  Uses the library workspace of the current device, which is one of
  *   - per query and corpus slab (at most 2048) a list of 4, 8, 12 or 16 (score, id) pairs: up to
  *     64 queries on large corpora, few queries in fp32;
- *   - per query the largest score of every group of 1 to 64 rows, 4 bytes each: larger batches.
+ *   - per query the largest score of every group of 1 to 64 rows, 4 bytes each: larger batches, and
+ *     few queries against few rows.
  *     That grows with N B (1 M rows, B = 512: 64 MB; 21 M rows: 672 MB); beyond 1 GiB the search
  *     runs in parts;
  *   - nothing: corpora of at most 128 rows with k <= 4 or in fp32, of at most 64 with any k.

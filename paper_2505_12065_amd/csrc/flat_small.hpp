@@ -14,9 +14,6 @@ namespace ann {
 // d = 768, 3 us longer).  us of a call, lists or matrix-core tiles / this: 2860 x 352, B = 1 10.7 / 6.2; 977 x 1024 bf16, B = 5, k = 16 10.1 / 7.6;
 // 3978 x 104, B = 9 8.4 / 6.3; 200 x 768, B = 1 8.5 / 6.3, B = 256 9.6 / 7.2; 10 000 x 128 fp32, B = 16, k = 10 11.6 / 10.3; 1202 x 128 fp32, B = 11, k = 10
 // 12.8 / 8.2.
-// One wave scores 16 rows against 16 queries: maxima[q, row], n of them a query (a multiple of 4; NaN: no row, or not after the
-// query's boundary).  Workgroups of one wave, ceil(N / 16) x G of them, so that rows go to as many compute units as there are.
-// Products and their order are those of flat_stream_kernel, so the scores are its bits.
 template <class T>
 __global__ __launch_bounds__(WAVE, 1) void flat_scores_kernel(StreamShape sh, float *__restrict__ maxima, int n, int G, After after) {
     constexpr int RUN = 4, RUNS = 6, STEPS = RUN * RUNS;
@@ -79,7 +76,8 @@ __global__ __launch_bounds__(WAVE, 1) void flat_scores_kernel(StreamShape sh, fl
     *reinterpret_cast<f4 *>(maxima + (size_t)q * n + r0) = v;
 }
 
-// N <= 128: a tile of 16 rows per wave, 8 waves, a workgroup per 16 queries; its lists are the answer.  held: steps of a query in LDS,
+// N <= 128: a tile of 16 rows per wave, 8 waves, a workgroup per 16 queries; its lists are the answer, and nothing is written but that (direct_quick
+// says where it is taken instead of the streaming kernel's one slab).  held: steps of a query in LDS,
 // whole runs (fewer than all of them only for rows of over 9 KB: the rest comes from memory).
 template <class T>
 __global__ __launch_bounds__(DIRECT_WAVES * WAVE, DIRECT_WAVES / 4) void flat_direct_kernel(

@@ -33,7 +33,7 @@
 // expansions a step for the slowest query; 8.4 k at ef = 64, where 40 rows take 3.1 and the insertion of as many keys 1.6.  A load
 // instruction of 16 bytes a lane takes the memory path 16 clocks, for one row of eight or for all: 24 rows spread over eight waves
 // keep it as busy as 64 (0.80 us a step from the L2, 0.41 without gaps; 8 rows 0.80 / 0.23).  Without gaps, us: B = 256, ef = 2048 2457 / 2266;
-// B = 1, ef = 64 with its coarse search 108 / 99.5; maturity exit, 200 k x 384 bf16, B = 256, ef = 256 268 / 261.
+// B = 1, ef = 64 with its coarse search 108 / 99.5; maturity exit, rows of 768 bytes, B = 256, ef = 64 and 256 0.97 to 1.00 times as long.
 // The ordered list in LDS that this replaces cost 12 to 15 k clocks a step: 64 list positions looked up, one list in two parts merged, cut
 // and rebuilt (200 k x 768, B = 256, ef = 2048 5190 us; more, and the maturity exit, at frontier_pays).
 // Keeping the keys of uncommitted neighbours takes the rows a step loads from 54 to 26 at ef = 2048; 64-bit compares instead
@@ -641,7 +641,11 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
         // ---- score ---------------------------------------------------------------------------------------------
         // Lane i of every wave looks after neighbour i.  One that the step before has scored but not committed brings its key
         // along; the rest goes to the row groups without a gap, since a load instruction takes the memory path as long for one row as for
-        // eight.  More than there are groups are left unknown.
+        // eight.  More than there are groups are left unknown.  (The rank takes a trip through the LDS before the first row is asked for.  Against a row
+        // group for every place of the list, eight waves, times as long: rows of 1.5 KB 0.91 to 0.97 at any R; of 768 bytes 0.93 to 0.98 for 256 queries, 0.94 to
+        // 1.01 for 16, 1.01 to 1.03 for one; of up to 512 bytes 0.94 to 1.02, 0.96 to 1.04, 0.96 to 1.04, the upper ends at R <= 8 and rows of up to 256 bytes.
+        // By ds_permute and two lane moves instead of the LDS 1.3 % longer on average; chosen by a flag at run time 2 to 3 %.  A name given twice takes a
+        // row group as often as it is named: on graphs of overlapping rows 0.99 to 1.01 by eight waves, 0.85 to 0.97 by four.)
         const int mine = ent[lane], from_u = ent_u[lane];                 // whose the neighbour of this lane is
         const uint64_t kept = ck[(buf ^ 1) * 64 + at_hash[(buf ^ 1) * HASHES + hash_of(mine)]];
         const bool known = lane < n_ent && key_node(kept) == mine, need = lane < n_ent && !known;
