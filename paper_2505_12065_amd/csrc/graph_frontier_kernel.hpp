@@ -25,8 +25,8 @@
 //            marks where the visited set is in memory)
 //   commit   u_0 is expanded; u_j as well if no neighbour of u_0 .. u_{j-1} precedes it.  Those are the expansions that the
 //            search one by one makes, in its order, with its visited set.  What was scored for the others is dropped.
-//   insert   the neighbours of the committed nodes: into the lanes one by one if they are few, in the order of their ranks, which the
-//            row groups find, if not (one more barrier).  The next adjacency rows are asked for before the marks and counters are seen to.
+//   insert   the neighbours of the committed nodes: into the lanes one by one if they are few, in the order of their ranks, a share of
+//            which every wave finds, if not (one more barrier).
 //
 // Bound by the chain inside a step: 6.3 k clocks at 200 k x 768 fp16, ef = 2048, B = 256 (wait for the adjacency rows 0.6, visited bits
 // and numbering 0.5, lookup of kept keys 0.3, rows 2.2, barrier 0.3, commit 0.5, insert 0.8, queue and pool 0.6, marks 0.4) at 2.2
@@ -36,10 +36,17 @@
 // B = 1, ef = 64 with its coarse search 108 / 99.5; maturity exit, rows of 768 bytes, B = 256, ef = 64 and 256 0.97 to 1.00 times as long.
 // The ordered list in LDS that this replaces cost 12 to 15 k clocks a step: 64 list positions looked up, one list in two parts merged, cut
 // and rebuilt (200 k x 768, B = 256, ef = 2048 5190 us; more, and the maturity exit, at frontier_pays).
+// Off the chain of a step (together 200 k x 768, R = 32: B = 1, ef = 64 with its coarse search 121.5 / 118.3 us, B = 256, ef = 2048 2164 / 2120, B = 512,
+// ef = 256 712 / 672; 200 k x 256, B = 32, ef = 512 628 / 569): loads that only warm the caches are waited for with the next adjacency rows instead of
+// before the barrier; the ranks of many new keys come from compares with a lane's key (eight reads of 16 bytes a lane, by eight waves, kept
+// the LDS busy for as long as the compares took); the marks, LDS atomics by every wave, some 500 clocks of that queue, go ahead of the insertion,
+// which hardly reads the LDS, by eight waves (by four, two workgroups a compute unit, that is 1 % longer).
 // Keeping the keys of uncommitted neighbours takes the rows a step loads from 54 to 26 at ef = 2048; 64-bit compares instead
 // of maxima of doubles in the networks and insertions cost 4 % of a short list.  Not faster: 8 waves and two workgroups per compute
 // unit (413 us against 309 at B = 512, ef = 64: 128 registers a lane), the smallest place a neighbour stops found by LDS atomics before the
-// barrier (0.95 k clocks more there, 0.5 fewer after it).
+// barrier (0.95 k clocks more there, 0.5 fewer after it); the place where the commits stop found by ballots (1.5 % longer: a compare, a ballot
+// and scalar work in a row are 28 clocks, a lane move 14); visited bits set by one wave and kept keys looked up with them, which take one more
+// barrier a step (8 % longer by eight waves: the two of a SIMD come to it 250 clocks apart).
 #pragma once
 
 #include "graph_kernel.hpp"
@@ -607,6 +614,7 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
     };
     settle();
     request();
+    int touched = 0, ahead = 0;                           // (loads for the caches' sake: waited for with the next adjacency rows, which come after them)
     for (;;) {
         if (n_t == 0) break;                              // nothing left to expand
         if (n_exp >= ef && expanded_before(read_lane(t, 0)) >= ef) break;
@@ -620,6 +628,7 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
             if constexpr (VIS == FRONTIER_VIS_LDS) word[r] = bits[at];
             else word[r] = __hip_atomic_load(&gbits[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+        asm volatile("" ::"v"(touched), "v"(ahead));
         // lane j of upto: neighbours of u_0 .. u_j.  (No branches: what does not take part goes to a place nobody reads.)
         int upto = 0, sum = 0;
 #pragma unroll
@@ -653,7 +662,11 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
         const int n_need = __builtin_popcountll(need_m), rank = rank_in(need_m);
         if (need) ent_u[rank] = mine;
         const int todo = grp < n_need ? ent_u[grp] : -1;
-        if (todo >= 0) rows.issue(todo);
+        if (todo >= 0) {
+            rows.issue(todo);
+            // (its adjacency row into the near caches: it is likely a node of the next steps)
+            touched = graph[(size_t)todo * R + min(sub * 4, R - 1)];
+        }
         // A neighbour named twice in the step belongs to the first that names it: eight lanes, eight apart, look at those before one of
         // this wave's share.
         {
@@ -675,11 +688,15 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
             }
             if (lane == 0) again_of(wave)[buf] = word;
         }
+        // The samples of the step before enter the average, some 40 clocks each and one after the other: by the last of eight waves alone, which has
+        // the fewest rows, while these come in (50 k x 768, R = 24, B = 10, ef = 400 846 us by all waves after the request of the
+        // next adjacency rows, 810).  Of four waves each has rows in most steps (B = 500 by the last 1140, by all 1122).
+        if (NS && track && NW == 8 && wave == NW - 1) {
+            average(due, 0, n_due);
+            if (lane == 0) ctl[17 + buf] = __float_as_int(ema);
+        }
         if (todo >= 0) {
-            // (its adjacency row into the near caches: it is likely a node of the next steps)
-            const int touch = graph[(size_t)todo * R + min(sub * 4, R - 1)];
             const uint64_t own = node_key(rows.dots(todo), todo);
-            asm volatile("" ::"v"(touch));
             if (sub == 0) {
                 ck[buf * 64 + grp] = own;
                 at_hash[buf * HASHES + hash_of(todo)] = grp;
@@ -689,14 +706,12 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
             // The adjacency rows of the queue's next nodes into the L2, out of which the rows drive what is not asked for again
             // (frontier_ahead says where that pays).  Not before there is a pool (what is scored lately is there), nor with the maturity
             // exit (267 against 261 us at 200 k x 384, ef = 256).
-            int touch = 0;
-            if (!NS && frontier_ahead(NW) && live > 0 && lane >= W && lane < AHEAD && t != 0) touch = graph[(size_t)key_node(t) * R];
+            if (!NS && frontier_ahead(NW) && live > 0 && lane >= W && lane < AHEAD && t != 0) ahead = graph[(size_t)key_node(t) * R];
             if (known) {
                 const int slot = n_need + rank_in(__builtin_amdgcn_ballot_w64(known));
                 ck[buf * 64 + slot] = kept;
                 at_hash[buf * HASHES + hash_of(mine)] = slot;
             }
-            asm volatile("" ::"v"(touch));
         }
         barrier();
 
@@ -704,6 +719,7 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
         uint64_t key = need ? ck[buf * 64 + rank] : known ? kept : 0ull;
         if constexpr (SETS == 2) key = need && rank >= GROUPS ? UNKNOWN : key;
         key = again_of(lane / (8 * SETS))[buf] >> (lane & (8 * SETS - 1)) & 1u ? 0ull : key;
+        if (NS && track && NW == 8) ema = __int_as_float(__builtin_amdgcn_readfirstlane(ctl[17 + buf]));
         buf ^= 1;
         // A neighbour stops the expansions from the first whose node it precedes, but none up to its own; one that is unknown stops
         // its own.
@@ -820,6 +836,7 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
         // ---- insert; the next rows are asked for as soon as their nodes are known ------------------------------
         const int n_com = __builtin_amdgcn_readlane(upto, C - 1);         // neighbours of committed nodes
         const bool in = lane < n_com;
+        if constexpr (NW == 8) mark(key, in && key != 0);
         n_expand += C;
         if (lane < C) A[n_exp + lane] = t;
         n_exp += C;
@@ -834,31 +851,22 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
             n_t += n_high;
             for (uint64_t m = high_m; m != 0; m &= m - 1) t = insert_desc(t, read_lane(key, __builtin_ctzll(m)));
         } else {
-            // Many: every row group finds the rank of its own among them, its 8 lanes look at 8 each; the keys come
-            // back in order through LDS.
-            uint64_t *now = reinterpret_cast<uint64_t *>(ent);            // (the neighbours are not read any more)
-            now[lane] = key;
-            uint64_t o[8];
-#pragma unroll
-            for (int c = 0; c < 8; ++c) o[c] = now[sub * 8 + c];
-#pragma unroll
-            for (int h = 0; h < SETS; ++h) {
-                const int i = grp + h * GROUPS;
-                const uint64_t own = now[i];
-                int r = 0;
-#pragma unroll
-                for (int c = 0; c < 8; ++c) r += (int)(o[c] > own) & (int)(sub * 8 + c < n_com);
-                r = group_sum(r);
-                if (sub == 0 && i < n_com && own >= bound && own > floor_key) sorted[63 - r] = own;
+            // Many: every wave finds the ranks of its share, a lane's key against all; they come back in order through LDS.
+            int r = 0;
+            for (uint64_t m = high_m & (lanes_below(8 * SETS) << (8 * SETS * wave)); m != 0; m &= m - 1) {
+                const int i = __builtin_ctzll(m);
+                const uint64_t before = __builtin_amdgcn_ballot_w64(key > read_lane(key, i)) & high_m;
+                r = lane == i ? __builtin_popcountll(before) : r;
             }
+            if (high && lane / (8 * SETS) == wave) sorted[63 - r] = key;
             barrier();
             merge(63 - lane < n_high ? sorted[lane] : 0ull, n_high);
         }
         if ((NS && leave) || (int64_t)n_expand > N + W) break;            // (the latter: never on a sound graph)
         settle();
         request();
-        if (NS && track) average(due, 0, n_due);
-        mark(key, in && key != 0);
+        if (NS && track && NW != 8) average(due, 0, n_due);
+        if constexpr (NW != 8) mark(key, in && key != 0);
         if (NS && n_t > 0) {
             const uint64_t head = read_lane(t, 0);
             best_key = head > best_key ? head : best_key;
@@ -866,6 +874,7 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
         if constexpr (VIS == FRONTIER_VIS_GLOBAL) __syncthreads();        // (the marks are complete before the next step asks)
     }
 
+    if (NS && track && NW == 8) average(due, 0, n_due);
     // the k best of all, 64 at a time
     {
         const int k = late()->k;

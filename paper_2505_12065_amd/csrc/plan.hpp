@@ -736,11 +736,11 @@ inline StepLds graph_step_plan(int cus, int d, int elem_bytes, int B, int ef) {
 constexpr int FRONTIER_MOST = 63;                         // most neighbours a step scores
 constexpr int FRONTIER_VIS_LDS = 0, FRONTIER_VIS_GLOBAL = 1;              // where the visited set is
 constexpr int FRONTIER_SPARE = 512, FRONTIER_SPARE_MIN = 280, FRONTIER_SPARE_TIGHT = 124;   // places beyond ef, at least; where room is what counts; tight
-// Whether a step of graph_frontier_kernel touches the adjacency rows of the queue's next nodes ahead.  The wave that does so waits for them
-// before the step's barrier.  Of eight waves the last one seldom has a row to score: R = 32, B = 1, ef = 512, 1024, 2048 1.2, 2.7, 3.1 % longer without
-// (200 k x 768 fp16; 0.1, 0.9, 2.1 % at 100 k x 256, but 1.6 % shorter at ef = 128, which a test of ef in the step would cost lists of up to 64
-// entries half of).  Of four it has one in most steps, so its wait is the workgroup's: with / without, us, 200 k x 768, R = 32, B = 512 ef = 128
-// 443 / 429, 512 1110 / 1030, 1024 1779 / 1670, R = 16, B = 512, ef = 512 859 / 835; only R = 8 is 0.3 to 1.5 % longer without from ef = 512 on.
+// Whether a step of graph_frontier_kernel touches the adjacency rows of the queue's next nodes ahead.  Of eight waves the last one, which does so, seldom
+// has a row to score: R = 32, B = 1, ef = 512, 1024, 2048 1.2, 2.7, 3.1 % longer without (200 k x 768 fp16; 0.1, 0.9, 2.1 % at 100 k x 256, but 1.6 %
+// shorter at ef = 128, which a test of ef in the step would cost lists of up to 64 entries half of; taken while the wave waited for them, which no
+// longer is so).  Two workgroups of four waves keep the memory path busy with rows: with / without, us, 200 k x 768, R = 32, B = 512, ef = 256 710 / 702 and
+// 693 / 677, 200 k x 384, B = 1000, ef = 200 784 / 779 and 818 / 803.
 constexpr bool frontier_ahead(int waves) { return waves == 8; }
 
 struct FrontierLds {
