@@ -4,12 +4,12 @@
 
 namespace ann {
 namespace {
-template <class T, class C, bool ONE>
+template <class T, class C, bool ONE, bool BY_LINE>
 hipError_t launch_one(const WidePlan &pl, const void *X, int64_t N, int d, const void *Q, int B, float *maxima, After after,
                   hipStream_t stream) {
     static size_t big = 0;
-    if (hipError_t e = allow_big_lds(reinterpret_cast<const void *>(&flat_wide_kernel<T, C, ONE>), C::LDS_BYTES, &big)) return e;
-    hipLaunchKernelGGL((flat_wide_kernel<T, C, ONE>), dim3(pl.P * pl.NT), dim3(C::THREADS), C::LDS_BYTES, stream, X, N, d, Q, B,
+    if (hipError_t e = allow_big_lds(reinterpret_cast<const void *>(&flat_wide_kernel<T, C, ONE, BY_LINE>), C::LDS_BYTES, &big)) return e;
+    hipLaunchKernelGGL((flat_wide_kernel<T, C, ONE, BY_LINE>), dim3(pl.P * pl.NT), dim3(C::THREADS), C::LDS_BYTES, stream, X, N, d, Q, B,
                        maxima, pl.n, pl.P, pl.NT, pl.gs_log, after);
     return hipGetLastError();
 }
@@ -17,8 +17,10 @@ hipError_t launch_one(const WidePlan &pl, const void *X, int64_t N, int d, const
 template <class T, class C>
 hipError_t launch(const WidePlan &pl, const void *X, int64_t N, int d, const void *Q, int B, float *maxima, After after,
                   hipStream_t stream) {
-    return pl.gs_log == 0 ? launch_one<T, C, true>(pl, X, N, d, Q, B, maxima, after, stream)
-                          : launch_one<T, C, false>(pl, X, N, d, Q, B, maxima, after, stream);
+    if constexpr (C::SB == 128 && (C::WAVES == 8 || C::STAGES == 3))      // (the tiles that corpora beyond the caches get)
+        if (pl.gs_log > 0 && wide_by_line(N, d)) return launch_one<T, C, false, true>(pl, X, N, d, Q, B, maxima, after, stream);
+    return pl.gs_log == 0 ? launch_one<T, C, true, false>(pl, X, N, d, Q, B, maxima, after, stream)
+                          : launch_one<T, C, false, false>(pl, X, N, d, Q, B, maxima, after, stream);
 }
 
 template <class T>

@@ -23,6 +23,14 @@
 // B = 256 24.1 -> 23.6, 1024 x 768, B = 512 11.9 -> 11.6 (the large tiles, two waves of them on a SIMD, lose 4 % that way: 1 M x
 // 768, B = 512 895 -> 937; reading the operands a stage ahead gains nothing at any).
 //
+// BY_LINE: rows that are no whole number of lines.  128 bytes of such a row lie in two lines, each of which the L2 serves twice (1 M x 776,
+// B = 128: 37 M requests, 21 M for x 768 and x 832), so stages go by the lines of memory instead: a row's first chunk is chunk `lead` of its first
+// line.  A line's chunks go to the LDS places of their number in the row modulo 8, so operand reads stay what they are, and the products of a
+// step, one line later, take a lane's chunks from the line before where that had them: same operands, same bits.  Only corpus rows go
+// by lines; with the queries too, both lines' operands and the choice between them take 256 registers and twice the selects (160 k x 776, B = 77 57.2 ->
+// 61.5 us from the caches, this 57.5 -> 57.2).  us, stages of rows / of lines: 1 M x 776, B = 128 412 / 367; 123 457 x 776, B = 77
+// 56.4 / 51.3; 300 k x 264, B = 40 51.2 / 45.9; 800 k x 864, B = 77 315 / 297.
+//
 // The epilogue is what decides at most sizes.  Sorted lists per lane, with thresholds from a sampling pass, cost two to
 // three launches, 130 registers of lists and queues, and insertions that never become rare unless a slab has
 // thousands of rows: 3 to 10 times the products' time below 200 k rows.  Maxima take a few instructions per
@@ -58,7 +66,7 @@ static __device__ __align__(16) unsigned char zero_row_end[16];          // what
 // gridDim.x = P * NT; the tiles are dealt to P slabs.
 // 2^gs_log: rows per group, ONE: 1, else 4, 16, 32 or 16 WMF (two kernels: the stores of single rows are 40 % of the code,
 // and in one kernel with the rest they cost 1 M x 768, B = 512 1 %).  Rows that do not exist or do not come after a query's boundary count as NaN.
-template <class T, class C, bool ONE>
+template <class T, class C, bool ONE, bool BY_LINE>
 __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wide_kernel(
     const void *__restrict__ X, int64_t N, int d, const void *__restrict__ Q, int B, float *__restrict__ maxima, int64_t n,
     int P, int NT, int gs_log, After after) {
@@ -70,13 +78,19 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
     const int wm = wave % C::NWM, wn = wave / C::NWM;
     const int l32 = lane & 31, lhi = lane >> 5;
     const int rb = d * 2, ksteps = (rb + SB - 1) / SB;
+    static_assert(!BY_LINE || SB == 128, "a stage is a line");
+    const int nch = rb >> 4;
+    auto lead = [&](int64_t row) { return (int)((reinterpret_cast<uintptr_t>(X) >> 4) + (uint64_t)row * nch) & 7; };
+    // stages of a tile; leads are multiples of `common`, so 8 - common is the longest
+    const uint32_t common = (uint32_t)nch | 8u | (uint32_t)(reinterpret_cast<uintptr_t>(X) >> 4);
+    const int lines = BY_LINE ? (nch + 8 - (int)(common & -common) + 7) >> 3 : ksteps;
 
     const int lb = xcd_block();
     const bool by_query = N < B;
     const int nt = by_query ? lb / P : lb % NT, slab = by_query ? lb % P : lb / NT, n0 = nt * C::BN;
     const int64_t mtiles = (N + BM - 1) / BM;
     const int64_t t0 = mtiles * slab / P, t1 = mtiles * (slab + 1) / P;
-    const int total = (int)(t1 - t0) * ksteps;
+    const int total = (int)(t1 - t0) * lines;
 
     // Block e of a stage: blocks 0 .. A_BLK - 1 corpus rows, the rest queries.  Lane l fetches row l / CPR of the block;
     // LDS slot l % CPR of that row receives chunk (l % CPR) ^ swz(row) of the stage's bytes of the row: 16 rows, which an operand
@@ -91,22 +105,30 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
     // from a row of zeros.
     // (Lambdas of the K loop are inlined by order: those of the 128 x 128 tile were called otherwise, its accumulators in scratch memory, 121 us
     // instead of 25 at 977 x 768, B = 5000.  The other tiles' code is the same either way.)
-    uint32_t loff[LPW];
+    // BY_LINE: the offset in the row's first line may lie before the row, and so before the tile.
+    uint32_t loff[LPW], first_chunk = 0;                  // first_chunk: 7 more than the chunk of its row that the lane brings first, 4 bits each
+    static_assert(LPW <= 8, "a register of first chunks");
     auto lane_offsets = [&](int64_t tile) __attribute__((always_inline)) {
+        first_chunk = 0;
 #pragma unroll
         for (int e = 0; e < LPW; ++e) {
             const int blk = wave * LPW + e;
+            int ch = my_chunk(e);
             if (blk < C::A_BLK) {
                 int64_t row = tile * BM + blk * RPB + lane / CPR;
                 row = row < N ? row : N - 1;
-                loff[e] = (uint32_t)(row - tile * BM) * (uint32_t)rb + my_chunk(e) * 16;
+                if constexpr (BY_LINE) ch = ((ch + lead(row)) & 7) - lead(row);
+                loff[e] = (uint32_t)(row - tile * BM) * (uint32_t)rb + ch * 16;
             } else {
                 int q = n0 + (blk - C::A_BLK) * RPB + lane / CPR;
                 q = q < B ? q : B - 1;
-                loff[e] = (uint32_t)(q - n0) * (uint32_t)rb + my_chunk(e) * 16;
+                loff[e] = (uint32_t)(q - n0) * (uint32_t)rb + ch * 16;
             }
+            if constexpr (BY_LINE) first_chunk |= (uint32_t)(ch + 7) << (4 * e);
         }
     };
+    auto offset = [&](int e) -> int64_t { return BY_LINE ? (int64_t)(int32_t)loff[e] : (int64_t)loff[e]; };
+    auto chunk_of = [&](int e) { return BY_LINE ? (int)(first_chunk >> (4 * e) & 15) - 7 : my_chunk(e); };
     lane_offsets(t0);
     const char *xbase = static_cast<const char *>(X) + (size_t)t0 * BM * rb;              // tile start
     const char *qbase = static_cast<const char *>(Q) + (size_t)n0 * rb;
@@ -121,7 +143,7 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
 #pragma unroll
         for (int e = 0; e < LPW; ++e) {
             const int blk = wave * LPW + e;
-            ANN_GLOBAL_TO_LDS_16((blk < C::A_BLK ? xs : qs) + loff[e], sbase + blk * 1024);
+            ANN_GLOBAL_TO_LDS_16((blk < C::A_BLK ? xs : qs) + offset(e), sbase + blk * 1024);
         }
         iofs = iofs + C::STAGE_BYTES == C::LDS_BYTES ? 0 : iofs + C::STAGE_BYTES;
         xs += SB;
@@ -131,28 +153,29 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
     };
     auto issue = [&]() __attribute__((always_inline)) {
         if (issued >= total) return;
-        if (LINES && iks < ksteps - 1) return issue_inside();
+        if (BY_LINE ? iks > 0 && 8 * iks + 7 < nch : LINES && iks < ksteps - 1) return issue_inside();
         ++issued;
         unsigned char *sbase = stage_mem + iofs;
-        if (ragged_row && iks == ksteps - 1) {
+        if (BY_LINE || (ragged_row && iks == ksteps - 1)) {
 #pragma unroll
             for (int e = 0; e < LPW; ++e) {
                 const int blk = wave * LPW + e;
                 const char *base = blk < C::A_BLK ? xbase : qbase;
-                const char *p = base + iks * SB + loff[e];
-                const bool inside = iks * SB + my_chunk(e) * 16 < rb;
+                const char *p = base + iks * SB + offset(e);
+                const bool inside = (uint32_t)(iks * CPR + chunk_of(e)) < (uint32_t)nch;
                 ANN_GLOBAL_TO_LDS_16(inside ? p : reinterpret_cast<const char *>(zero_row_end), sbase + blk * 1024);
             }
+            if constexpr (BY_LINE) { xs += SB; qs += SB; }
         } else {
 #pragma unroll
             for (int e = 0; e < LPW; ++e) {
                 const int blk = wave * LPW + e;
                 const char *base = blk < C::A_BLK ? xbase : qbase;
-                ANN_GLOBAL_TO_LDS_16(base + iks * SB + loff[e], sbase + blk * 1024);
+                ANN_GLOBAL_TO_LDS_16(base + iks * SB + offset(e), sbase + blk * 1024);
             }
         }
         iofs = iofs + C::STAGE_BYTES == C::LDS_BYTES ? 0 : iofs + C::STAGE_BYTES;
-        if (++iks == ksteps) {
+        if (++iks == lines) {
             iks = 0;
             ++itile;
             xbase += (size_t)BM * rb;
@@ -163,8 +186,9 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
 
     f16v acc[WMF][WNF];
     int it = 0, cofs = 0;                                 // stage being computed, its LDS offset
-    // `inside` (LINES): there is a stage to load, and it lies inside its tile
-    auto stage = [&](auto first, auto inside) __attribute__((always_inline)) {
+    using Operands = u4[NKH][WMF + WNF];
+    // the stage's operands; `inside` (LINES): there is a stage to load, and it lies inside its tile
+    auto read = [&](Operands &x, auto inside) __attribute__((always_inline)) {
         // it has landed once only the newer stages' loads are outstanding (a tile's stores are newer still: the
         // wait right behind an epilogue is a little longer than it has to be)
         const int newer = decltype(inside)::value ? NST - 2 : min(NST - 2, total - 1 - it);
@@ -177,16 +201,15 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
         // Operand row r = lane % 32 of a 32-row block pair, chunk 2 kh + lane / 32.  All operand reads of the stage
         // are issued before the first MFMA, so the LDS pipeline always has several 1 KB reads of this wave in flight.
         const unsigned char *sb = stage_mem + cofs;
-        u4 a[NKH][WMF], b[NKH][WNF];
 #pragma unroll
         for (int kh = 0; kh < NKH; ++kh) {
             const int lofs = (l32 / RPB) * 1024 + (l32 & (RPB - 1)) * SB + (((2 * kh + lhi) ^ swz(l32)) * 16);
 #pragma unroll
             for (int j = 0; j < WNF; ++j)
-                b[kh][j] = *reinterpret_cast<const u4 *>(sb + (C::A_BLK + (wn * WNF + j) * (32 / RPB)) * 1024 + lofs);
+                x[kh][WMF + j] = *reinterpret_cast<const u4 *>(sb + (C::A_BLK + (wn * WNF + j) * (32 / RPB)) * 1024 + lofs);
 #pragma unroll
             for (int i = 0; i < WMF; ++i)
-                a[kh][i] = *reinterpret_cast<const u4 *>(sb + (wm * WMF + i) * (32 / RPB) * 1024 + lofs);
+                x[kh][i] = *reinterpret_cast<const u4 *>(sb + (wm * WMF + i) * (32 / RPB) * 1024 + lofs);
         }
         if constexpr (LINES) {                            // (the addresses are made while the reads run)
             __builtin_amdgcn_sched_barrier(0);
@@ -194,6 +217,10 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
             else issue();
         }
         __builtin_amdgcn_sched_barrier(0);                // keep the reads ahead of the MFMAs
+        cofs = cofs + C::STAGE_BYTES == C::LDS_BYTES ? 0 : cofs + C::STAGE_BYTES;
+        ++it;
+    };
+    auto multiply = [&](Operands &x, auto first) __attribute__((always_inline)) {
         static_for<NKH>([&](auto kc) {
             static_for<WMF>([&](auto ic) {
                 static_for<WNF>([&](auto jc) {
@@ -202,29 +229,81 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
                         f16v zero;
 #pragma unroll
                         for (int r = 0; r < 16; ++r) zero[r] = 0.f;
-                        acc[i][j] = mfma32<T>(a[kh][i], b[kh][j], zero);
+                        acc[i][j] = mfma32<T>(x[kh][i], x[kh][WMF + j], zero);
                     } else {
-                        acc[i][j] = mfma32<T>(a[kh][i], b[kh][j], acc[i][j]);
+                        acc[i][j] = mfma32<T>(x[kh][i], x[kh][WMF + j], acc[i][j]);
                     }
                 });
             });
         });
-        cofs = cofs + C::STAGE_BYTES == C::LDS_BYTES ? 0 : cofs + C::STAGE_BYTES;
-        ++it;
+    };
+    auto stage = [&](auto first, auto inside) __attribute__((always_inline)) {
+        Operands x;
+        read(x, inside);
+        multiply(x, first);
+    };
+    // BY_LINE: the LDS place of chunk 2 kh + lane / 32 of a step holds, of the line as many stages into the tile, that chunk if kh < keep,
+    // else that of the step before.  So the products of a step follow the reads of the next line.
+    int keep[WMF];
+    if constexpr (BY_LINE) {
+#pragma unroll
+        for (int i = 0; i < WMF; ++i) keep[i] = 4 - ((lead((wm * WMF + i) * 32 + l32) + lhi) >> 1);
+    }
+    // the corpus operands of a step, in `x` as its own line had them: the rest from `next`, the line after it, or zeros behind the last one
+    auto complete = [&](Operands &x, const Operands &next, auto end) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kh = 0; kh < NKH; ++kh)
+#pragma unroll
+            for (int i = 0; i < WMF; ++i)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) x[kh][i][c] = kh < keep[i] ? x[kh][i][c] : decltype(end)::value ? 0u : next[kh][i][c];
+    };
+    // the next line into `y`, and the products of the step that `x` was read for
+    auto line = [&](Operands &x, Operands &y, auto first, auto inside) __attribute__((always_inline)) {
+        read(y, inside);
+        complete(x, y, std::false_type{});
+        multiply(x, first);
     };
 
     for (int s = 0; s < NST - 1; ++s) issue();
     for (int64_t tile = t0; tile < t1; ++tile) {
-        stage(std::true_type{}, std::false_type{});
-        for (int ks = 1; ks < ksteps;) {
-            if constexpr (LINES) {                        // steps that need no look at where the loads are
-                int n = min(min(ksteps - ks, ksteps - 1 - iks), total - issued);
-                ks += max(n, 0);
-                for (; n > 0; --n) stage(std::false_type{}, std::true_type{});
-                if (ks == ksteps) break;
+        if constexpr (BY_LINE) {                          // (rows of more than a line: at least two stages)
+            Operands u, v;
+            read(u, std::false_type{});
+            line(u, v, std::true_type{}, std::false_type{});
+            int j = 2;
+            // pairs of lines that need no look at where the loads are, which are not in a tile's first line
+            for (int n = iks > 0 ? min((nch >> 3) - iks, total - issued) >> 1 : 0; n > 0; --n, j += 2) {
+                line(v, u, std::false_type{}, std::true_type{});
+                line(u, v, std::false_type{}, std::true_type{});
             }
-            stage(std::false_type{}, std::false_type{});
-            ++ks;
+            for (; j + 1 < lines; j += 2) {
+                line(v, u, std::false_type{}, std::false_type{});
+                line(u, v, std::false_type{}, std::false_type{});
+            }
+            auto flush = [&](Operands &x) __attribute__((always_inline)) {
+                if (lines != ksteps) return;              // (else the last line ends the last step)
+                complete(x, x, std::true_type{});
+                multiply(x, std::false_type{});
+            };
+            if (j < lines) {
+                line(v, u, std::false_type{}, std::false_type{});
+                flush(u);
+            } else {
+                flush(v);
+            }
+        } else {
+            stage(std::true_type{}, std::false_type{});
+            for (int ks = 1; ks < ksteps;) {
+                if constexpr (LINES) {                    // steps that need no look at where the loads are
+                    int n = min(min(ksteps - ks, ksteps - 1 - iks), total - issued);
+                    ks += max(n, 0);
+                    for (; n > 0; --n) stage(std::false_type{}, std::true_type{});
+                    if (ks == ksteps) break;
+                }
+                stage(std::false_type{}, std::false_type{});
+                ++ks;
+            }
         }
 
         int ln = lane;

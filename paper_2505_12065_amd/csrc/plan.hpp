@@ -273,6 +273,13 @@ inline int wide_thin(int cus, int64_t N, int d, int B) {
     const int64_t tiles = (N + WideThin::BM - 1) / WideThin::BM * ((B + WideThin::BN - 1) / WideThin::BN);
     return d <= 32 || (d <= 256 && tiles > 2 * (int64_t)cus && tiles <= 3 * (int64_t)cus) ? WIDE_SHORT : WIDE_THIN;
 }
+// Whether 256 x 128 and 128 x 64 tiles go by the lines of memory that rows lie in (flat_wide_kernel's BY_LINE: same bits): rows that are no whole
+// number of lines, of corpora that come from memory.  The selects cost what the requests save where the corpus stays in the caches: us, stages
+// of rows / of lines, read again / after others: 80 k x 520, B = 77 30.9 / 31.3, 31.3 / 31.9; 80 k x 776 39.9 / 40.1, 50.7 / 44.8; 123 457 x 776 43.4 / 43.5,
+// 56.4 / 51.3; 640 k x 776 242 / 219, 242 / 220; 300 k x 200, B = 40 32.7 / 31.6, 41.8 / 37.3.  Half lines, which fewer requests divide: 123 457 x 800, B = 77
+// 41.8 / 43.1, 52.4 / 51.5; 160 k x 800 56.9 / 57.3, 70.7 / 68.3; 1 M x 800, B = 128 387 / 365, 399 / 368; 800 k x 160, B = 77 78.2 / 76.1.  Up to a line
+// the stages are mostly first and last ones: 1.5 M x 72, B = 24 63 / 68, 600 k x 120, B = 40 44.5 / 46.6.
+inline bool wide_by_line(int64_t N, int d) { return d > 128 && d % 64 != 0 && N * d * 2 >= (d % 32 != 0 ? 128000000 : 256000000); }
 inline int wide_shape(int cus, int64_t N, int d, int B) {
     auto tiles = [&](int bm, int bn) { return (N + bm - 1) / bm * ((B + bn - 1) / bn); };
     const int64_t cols256 = (B + 255) / 256 * 256, cols128 = (B + 127) / 128 * 128;
@@ -315,7 +322,11 @@ inline double wide_rounds_us(int shape, int cus, int64_t N, int d, int B) {
     return rounds * (a + b * lines / 2 * (1 + share * (full > 1 ? full - 1 : 0)));
 }
 inline int wide_tile(int cus, int64_t N, int d, int B, int k) {
-    const int first = wide_shape(cus, N, d, B);
+    int first = wide_shape(cus, N, d, B);
+    // Lines of memory instead of 512 x 128, us: 600 k x 232, B = 77 93.8 / 85.1; 640 k x 456, B = 77 165 / 146; 1 M x 456, B = 128 271 / 248; 1.5 M x 200,
+    // B = 128 189 / 182; but 4 M x 184, B = 100 412 / 414, and by half lines 2 M x 352, B = 100 344 / 349.
+    const bool tall = !(wide_by_line(N, d) && d % 32 != 0 && d >= 200);
+    if (first == WIDE_TALL && !tall) first = WIDE_MID;
     if (B <= 64 || d <= 64 || first == WIDE_TINY) return first;
     const bool cached = N * d * 2 <= 64000000;
     if (!cached && (first == WIDE_THIN || first == WIDE_SHORT)) return first;
@@ -326,7 +337,7 @@ inline int wide_tile(int cus, int64_t N, int d, int B, int k) {
     const double stays = wide_rounds_us(first, cus, N, d, B);
     double least = (cached ? 0.95 : 0.93) * stays;        // (closer than that the model does not tell them apart)
     for (int shape : {WIDE_LARGE, WIDE_TALL, WIDE_MID, WIDE_SQUARE, WIDE_THIN}) {
-        if (!cached && (shape == WIDE_SQUARE || shape == WIDE_THIN)) continue;
+        if ((!cached && (shape == WIDE_SQUARE || shape == WIDE_THIN)) || (shape == WIDE_TALL && !tall)) continue;
         const double us = wide_rounds_us(shape, cus, N, d, B);
         // (256 x 128 with a half empty last round runs faster in it than the model has it: 15.7 k x 384, B = 839 29.7 / 32.1 by 256 x 256; and the pick of long
         // answers, which the model leaves out, has more to do behind the large tiles: 17.0 k x 128, B = 867, k = 16 24.8 / 28.2 by 512 x 128)

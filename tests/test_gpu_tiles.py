@@ -77,6 +77,38 @@ def test_square_tiles(dtype, N, d, B, k):
     test_line_stages(dtype, N, d, B, k)
 
 
+@pytest.mark.parametrize("dtype,N,d,B,k,offset", [
+    (torch.float16, 83_001, 776, 77, 10, 0),   # 256 x 128, as many lines as steps
+    (torch.bfloat16, 64_257, 1_000, 66, 16, 7),    # ... a line more, one row in the last tile
+    (torch.bfloat16, 530_000, 200, 70, 3, 1),  # ... in the place of 512 x 128; four lines
+    (torch.float16, 131_072, 992, 128, 3, 4),  # ... half lines, whole tiles
+    (torch.float16, 330_001, 200, 40, 4, 3),   # 128 x 64
+    (torch.bfloat16, 480_000, 136, 17, 16, 0),     # ... the shortest rows: a step of one chunk behind two
+    (torch.float16, 300_000, 264, 40, 1, 6),
+])
+def test_stages_of_lines_of_memory(dtype, N, d, B, k, offset):
+    """Rows that begin anywhere in a line (offset: 16-byte chunks) against the same search in pieces small enough to go by the rows' own
+    stages: same bits.  A NaN or an infinity at either end of a row stays its own."""
+    print(f"lines of memory: dtype={dtype} N={N} d={d} B={B} k={k} offset={offset}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(N + d)
+    x = torch.randn(N * d + 64, generator=gen, device=DEV).to(dtype)[8 * offset:8 * offset + N * d].view(N, d)
+    q = torch.randn(B, d, generator=gen, device=DEV).to(dtype)
+    x[3::11, 0] = float("nan")
+    x[5::7, d - 1] = float("nan")
+    x[100::20_011, 0] = float("inf")
+    x[101::30_011, d - 1] = float("-inf")
+    got = ann.ann_flat_search_typed(x, q, k)
+    step = 60_000_000 // (2 * d)
+    ids, sc = [], []
+    for r0 in range(0, N, step):
+        i, s = ann.ann_flat_search_typed(x[r0:r0 + step], q, k)
+        ids.append(i + r0)
+        sc.append(s)
+    ids, sc = torch.cat(ids, 1), torch.cat(sc, 1)
+    best = sc.sort(dim=1, descending=True, stable=True).indices[:, :k]          # (pieces and their rows come in the order of the ids)
+    assert torch.equal(got[0], ids.gather(1, best)) and torch.equal(got[1], sc.gather(1, best))
+
+
 @pytest.mark.parametrize("N,d,B,k,size", [
     (15_656, 512, 1, 1, 1_163),                # maxima do not fit, lists do
     (85_001, 144, 10, 10, 9_789),              # lists do not fit, the corpus in parts does

@@ -41,6 +41,7 @@ extern "C" int in_lds(int64_t N, int d, int elem_bytes, int R, int ef) {
 extern "C" int ahead(int waves) { return frontier_ahead(waves); }
 extern "C" int runs(int cus, int d, int elem_bytes, int B) { return pick_runs(cus, (size_t)d * elem_bytes, 16 * elem_bytes, B); }
 extern "C" int shape(int cus, int64_t N, int d, int B) { return wide_shape(cus, N, d, B); }
+extern "C" int by_line(int64_t N, int d) { return wide_by_line(N, d); }
 extern "C" int tile(int cus, int64_t N, int d, int B, int k) { return wide_tile(cus, N, d, B, k); }
 static int kind(const FlatPlan &pl) { return pl.scores ? 4 : pl.quick ? 5 : pl.wide ? 2 : pl.maxima ? 3 : pl.direct ? 1 : 0; }
 // out: kind (0 lists, 1 direct, 2 matrix cores, 3 streaming with maxima, 4 scores, 5 direct by flat_direct_kernel), queries and rows at a time, maxima of a query,
@@ -85,6 +86,7 @@ def plans(tmp_path_factory):
     L.frontier.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_float, ctypes.c_int, ctypes.c_void_p]
     L.shape.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 2
     L.tile.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 3
+    L.by_line.argtypes = [ctypes.c_int64, ctypes.c_int]
     L.in_lds.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4
     L.flat.argtypes = L.flat_by_fill.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64, ctypes.c_void_p]
     L.static_accepts.argtypes = L.static_kind.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64]
@@ -353,6 +355,21 @@ def test_many_queries_on_large_corpora(plans, N, d, B, k, kind):
 ])
 def test_few_queries_against_the_length_of_rows(plans, N, d, B, kind):
     assert KINDS[flat(plans, N, d, 0, B, 3, 1 << 34)["kind"]] == kind
+
+
+# us, stages of rows / of lines of memory; tile by both rules
+@pytest.mark.parametrize("N,d,B,by_line,first,tile", [
+    (123_457, 776, 77, 1, 2, 2),         # 56.4 / 51.3
+    (80_000, 776, 77, 0, 2, 2),          # from the caches 39.9 / 40.1
+    (160_000, 800, 77, 1, 2, 2),         # half lines, 256 MB
+    (123_457, 800, 77, 0, 2, 2),         # 41.8 / 43.1
+    (1_000_000, 768, 128, 0, 2, 2),      # whole lines
+    (1_500_000, 120, 128, 0, 1, 1),      # less than a line
+    (1_000_000, 456, 128, 1, 1, 2),      # 271 / 248, in the place of 512 x 128
+    (4_000_000, 184, 100, 1, 1, 1),      # 412 / 414
+    (2_000_000, 352, 100, 1, 1, 1)])     # 344 / 349
+def test_lines_of_memory_where_they_were_measured_to_pay(plans, N, d, B, by_line, first, tile):
+    assert (plans.by_line(N, d), plans.shape(CUS, N, d, B), plans.tile(CUS, N, d, B, 3)) == (by_line, first, tile)
 
 
 @pytest.mark.parametrize("N,d,B,k,buffer", [
