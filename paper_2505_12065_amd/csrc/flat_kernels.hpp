@@ -15,8 +15,6 @@
 
 namespace ann {
 
-constexpr int STREAM_BATCH = 4;                       // 16-byte loads per batch; two batches per lane in flight
-
 // Row r of a 16-row MFMA tile is corpus row 16 tile + tile_row(r): lane group g = lane / 16 then receives the
 // scores of corpus rows g, g + 4, g + 8, g + 12 of the tile, so that neighbouring rows (passages of one document,
 // often close to the same query) go to different lanes' lists.
@@ -110,7 +108,8 @@ __device__ __forceinline__ u4 mask_tail(u4 x, bool inside) {
 
 // Corpus rows are the M side of a 16x16 MFMA, queries the N side: a lane ends up with one query (lane % 16)
 // and four rows per tile of 16 rows (see tile_row).  A step is 64 bytes of a row: 32 16-bit or 16 fp32 columns.
-//   FULL: a row is a whole number of 256-byte batches (else the last batch and step are cut to size).
+//   BATCH: 16-byte loads to a batch, of which a lane has two in flight (stream_batch; fp32: an even number).
+//   FULL: a row is a whole number of batches of 64 bytes each load (else the last batch and step are cut to size).
 //   grid: P slabs x G groups of 16 NQG queries, the groups of a slab side by side on one XCD, so that a slab that
 //         several groups read comes from HBM once.  Tile t belongs to wave t % (P NWV) of the grid.
 //   partial [B, P, K] pairs, K = 4, 8, 12 or 16 (>= k), every list sorted, empty slots (-inf, EMPTY_ID) last.
@@ -121,17 +120,18 @@ __device__ __forceinline__ u4 mask_tail(u4 x, bool inside) {
 // Lists of 4 are exact for k <= 4.  For k > 4 a lane may meet more than 4 of the k best rows; the merge then finds 4
 // rows of one lane among the k best and goes over that lane's rows again (flat_merge_lists_kernel).
 //
-// Bound by HBM for up to 64 queries on a large corpus.  Loads come in batches of 4, the next batch always requested
+// Bound by HBM for up to 64 queries on a large corpus.  Loads come in batches, the next one always requested
 // before the products of the one before it, across tiles: without that a row of 12 steps (d = 384) paid four
 // latencies a tile.  Lists of 4 for every k replace lists of 16 (3.5 times the time) and, on large corpora, a
 // sampling pass with candidate arrays (three more launches and global atomics); fp32 runs here too, on the matrix
 // cores, at most 32 queries to a workgroup (more do not raise the rate: eight products of 32 clocks per 1 KB of rows).
 // Registers: two workgroups of 8 waves (or one of 16) per compute unit, except fp32 with two groups of queries (128
 // registers of accumulators), which runs one workgroup and is bound by the products.
-template <class T, int NQG, bool FULL, int NWV, bool MAX>
+template <class T, int NQG, bool FULL, int NWV, bool MAX, int BATCH>
 __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NWV / 4) void flat_stream_kernel(StreamShape sh, Cand *__restrict__ partial, int P, int G,
                                                                int K, int lds_steps, After after, float *__restrict__ maxima, int64_t n,
                                                                StreamOut out) {
+    static_assert(T::bytes == 2 || BATCH % 2 == 0, "fp32 sums go by the parity of a step");
     extern __shared__ __align__(16) unsigned char smem[];
     u4 *qf = reinterpret_cast<u4 *>(smem);            // [NQG][lds_steps][64]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -157,20 +157,20 @@ __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NW
     int64_t ltile = tile;                             // tile and step of the next batch to load
     int lstep = 0;
     if (tile < ntiles) row_ptr(tile);
-    auto load = [&](u4 (&a)[STREAM_BATCH]) {
+    auto load = [&](u4 (&a)[BATCH]) {
 #pragma unroll
-        for (int u = 0; u < STREAM_BATCH; ++u) {
+        for (int u = 0; u < BATCH; ++u) {
             if constexpr (FULL) a[u] = load_chunk(rp + (lstep + u) * 64);
             else a[u] = load_chunk(rp + min(min(lstep + u, steps - 1) * 64, rb - 16 - kofs));
         }
-        lstep += STREAM_BATCH;
+        lstep += BATCH;
         if (lstep >= steps) {
             lstep = 0;
             ltile = next(ltile);
             if (ltile < ntiles) row_ptr(ltile);       // (past the end: the last tile once more, never used)
         }
     };
-    u4 xa[STREAM_BATCH], xb[STREAM_BATCH];
+    u4 xa[BATCH], xb[BATCH];
     if (tile < ntiles) load(xa);
 
     // queries -> LDS, already in B-operand order: fragment (g, s) holds for lane l
@@ -211,9 +211,9 @@ __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NW
 
     int cstep = 0;                                    // step of the batch being multiplied
     // products of one batch; true when it was the last of its tile
-    auto multiply = [&](u4 (&a)[STREAM_BATCH]) -> bool {
+    auto multiply = [&](u4 (&a)[BATCH]) -> bool {
 #pragma unroll
-        for (int u = 0; u < STREAM_BATCH; ++u) {
+        for (int u = 0; u < BATCH; ++u) {
             const int s = cstep + u;
             if (FULL || u == 0 || s < steps) {
                 u4 x = a[u];
@@ -226,12 +226,12 @@ __global__ __launch_bounds__(NWV * 64, STREAM_WG_PER_CU(T::bytes, NQG, NWV) * NW
                     u4 y;
                     if (FULL || NQG > 1 || s < lds_steps) y = qf[(g * lds_steps + s) * WAVE + lane];
                     else y = TileSum<T>::operand(query_chunk(q0 + (lane & 15), s * 64 + kofs));
-                    part[g].step(u, x, y);            // (batches start at even steps)
+                    part[g].step(u, x, y);            // (of fp32, batches start at even steps)
                 }
                 if constexpr (T::bytes == 4) __builtin_amdgcn_sched_barrier(0);   // (one transposed chunk at a time)
             }
         }
-        cstep += STREAM_BATCH;
+        cstep += BATCH;
         if (cstep < steps) return false;
         cstep = 0;
         return true;

@@ -32,6 +32,7 @@ struct StreamPlan {
     int P = 1;                   // slabs of the corpus
     int waves = 8;               // wavefronts per workgroup
     int lds_steps = 1;           // 64-byte steps of a query held in LDS
+    int batch = 4;               // loads of a row that are requested together
     int K = 4;                   // entries of a slab's list: k rounded up to a multiple of 4
     int slots() const { return P * waves; }
 };
@@ -170,6 +171,28 @@ constexpr size_t WIDE_WS_MAX = (size_t)1 << 30;
 constexpr int PART_MIN_B = 256, PART_MIN_B_F32 = 128, PART_MAX_B = 1024;
 constexpr int64_t PART_MIN_ROWS = 8192;          // fewer are not worth a launch: the call does not fit
 
+// The loads of 64 bytes of a row that go together; a lane has two such batches in flight.  What decides is how the batches divide the lines of a
+// row and what the last one loads for nothing, and with several groups of queries, whose products take longer, that requests come in small portions.
+// 16 bits, us, batches of 4 / this:
+//   up to 16 queries, rows that end in a sector of 64 bytes or half a line: 3, and 5 where that is the row: 1 M, B = 1 x 264 109 / 101, x 136 62.5 / 56.7, x 160
+//     70.9 / 61.5, x 776 310 / 292, x 800 287 / 272, x 1000 387 / 369; 100 k x 616, B = 4 38.2 / 36.5; but 1 M x 104 48.3 / 55.7, x 224 84.4 / 86.2 by 3.
+//   more queries, such rows: 5 or 3 where that divides the row: 1 M x 776, B = 48 316 / 300; x 456, B = 32 188 / 180; 3 M x 160, B = 32 212 / 186; 1 M x 264,
+//     B = 48 128 / 121; else 4 (1 M x 616, B = 48 251 / 258 by 3).
+//   more than 32 queries, whole lines of at least 768 bytes: 2: 21 M x 384, B = 64, k = 5 2706 / 2657; 1 M x 384, B = 48 153 / 143, x 768, B = 64 288 / 277, x 1024
+//     361 / 355; 300 k x 576, B = 48 79 / 74.6; shorter 3 M x 256, B = 64 303 / 311.  17 to 32 queries: whole lines of up to 640 bytes: 1 M x 256
+//     103 / 95.7, x 320 127 / 121, 3 M x 256 271 / 258; but 300 k x 768 92.9 / 95.0, 3 M x 512 512 / 523.
+// fp32, up to 16 queries, whole sectors: 2: 1 M x 96, B = 4 80.6 / 73.5; 100 k x 208, B = 12 27.9 / 25.8, x 384 42.2 / 40.7; but 1 M x 300 236 / 256, and more
+// queries 300 k x 256, B = 40 128 / 136.
+inline int stream_batch(int row_bytes, int dtype, int nqg) {
+    if (dtype == ANN_F32) return nqg == 1 && row_bytes % 64 == 0 ? 2 : 4;
+    const int steps = (row_bytes + 63) / 64;
+    if (row_bytes % 128 == 0)
+        return (nqg >= 3 && row_bytes >= 768) || (nqg == 2 && row_bytes <= 640) ? 2 : 4;
+    if (steps % 5 == 0 && (nqg > 1 || steps == 5)) return 5;
+    if (nqg > 1) return steps % 3 == 0 && steps % 4 != 0 ? 3 : 4;
+    return (row_bytes % 64 != 0 && steps >= 9) || (steps + 2) / 3 * 3 <= (steps + 3) / 4 * 4 ? 3 : 4;
+}
+
 // The streaming kernel's geometry.
 // K: see the kernel; unit: rows that go to a wave together.
 inline StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int K, int unit) {
@@ -189,6 +212,7 @@ inline StreamPlan stream_plan(int cus, int64_t N, int d, int dtype, int B, int K
     pl.G = (n16 + nqg - 1) / nqg;
     pl.nqg = (n16 + pl.G - 1) / pl.G;
     pl.waves = stream_waves(elem_bytes(dtype), pl.nqg, pl.lds_steps);
+    pl.batch = stream_batch(d * elem_bytes(dtype), dtype, pl.nqg);
     int occ = (int)(LDS_MAX / stream_lds_bytes(pl.nqg, pl.lds_steps, pl.waves));
     const int most = STREAM_WG_PER_CU(elem_bytes(dtype), pl.nqg, pl.waves);   // measured: more than 2 do not help
     occ = occ < 1 ? 1 : (occ > most ? most : occ);
@@ -491,6 +515,7 @@ inline void lists_plan(FlatPlan &pl, int cus, int64_t N, int d, int dtype, int B
     pl.st = stream_plan(cus, N, d, dtype, B, (k + 3) & ~3, 16);
     if (pl.direct) {
         pl.st.P = 1;
+        pl.st.batch = 4;
         return;
     }
     // lists that do not fit: fewer slabs, down to a quarter of those that fill the chip

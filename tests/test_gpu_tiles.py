@@ -77,6 +77,26 @@ def test_square_tiles(dtype, N, d, B, k):
     test_line_stages(dtype, N, d, B, k)
 
 
+@pytest.mark.parametrize("dtype,N,d,B,k", [
+    (torch.float16, 70_001, 264, 16, 3),       # up to 16 queries, batches of 3: a step of 16 bytes, one row in the last tile
+    (torch.bfloat16, 70_001, 1_000, 3, 10),    # ... of 33 steps, one more than there are
+    (torch.float16, 140_003, 160, 5, 4),       # ... of 5, half lines
+    (torch.bfloat16, 140_003, 136, 7, 16),     # ... a step of 16 bytes
+    (torch.float16, 200_001, 776, 40, 10),     # more queries, batches of 5: eight waves
+    (torch.bfloat16, 200_001, 776, 64, 3),     # ... 16 waves
+    (torch.float16, 200_000, 456, 17, 16),     # ... two groups of queries
+    (torch.float16, 530_001, 264, 33, 3),      # ... of 3
+    (torch.bfloat16, 70_001, 768, 40, 4),      # ... of 2, whole rows
+    (torch.float16, 150_000, 1_024, 64, 10),   # ... 16 waves
+    (torch.bfloat16, 600_001, 192, 17, 5),     # ... two groups, large corpora
+    (torch.float32, 60_001, 80, 9, 4),         # fp32, of 2: half a batch at the end
+    (torch.float32, 50_000, 96, 16, 10),       # ... whole rows
+    (torch.float32, 40_001, 2_400, 3, 1),      # ... queries longer than the LDS holds
+])
+def test_batches_of_the_streaming_kernel(dtype, N, d, B, k):
+    test_line_stages(dtype, N, d, B, k)
+
+
 @pytest.mark.parametrize("dtype,N,d,B,k,offset", [
     (torch.float16, 83_001, 776, 77, 10, 0),   # 256 x 128, as many lines as steps
     (torch.bfloat16, 64_257, 1_000, 66, 16, 7),    # ... a line more, one row in the last tile

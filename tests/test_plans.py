@@ -41,6 +41,10 @@ extern "C" int in_lds(int64_t N, int d, int elem_bytes, int R, int ef) {
 extern "C" int ahead(int waves) { return frontier_ahead(waves); }
 extern "C" int runs(int cus, int d, int elem_bytes, int B) { return pick_runs(cus, (size_t)d * elem_bytes, 16 * elem_bytes, B); }
 extern "C" int shape(int cus, int64_t N, int d, int B) { return wide_shape(cus, N, d, B); }
+extern "C" int batch(int cus, int64_t N, int d, int dtype, int B, int k) {
+    const FlatPlan pl = flat_plan(cus, N, d, dtype, B, k, WIDE_WS_MAX);
+    return pl.wide || pl.scores || pl.quick ? 0 : pl.st.batch;
+}
 extern "C" int by_line(int64_t N, int d) { return wide_by_line(N, d); }
 extern "C" int tile(int cus, int64_t N, int d, int B, int k) { return wide_tile(cus, N, d, B, k); }
 static int kind(const FlatPlan &pl) { return pl.scores ? 4 : pl.quick ? 5 : pl.wide ? 2 : pl.maxima ? 3 : pl.direct ? 1 : 0; }
@@ -86,6 +90,7 @@ def plans(tmp_path_factory):
     L.frontier.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_float, ctypes.c_int, ctypes.c_void_p]
     L.shape.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 2
     L.tile.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 3
+    L.batch.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4
     L.by_line.argtypes = [ctypes.c_int64, ctypes.c_int]
     L.in_lds.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4
     L.flat.argtypes = L.flat_by_fill.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64, ctypes.c_void_p]
@@ -355,6 +360,30 @@ def test_many_queries_on_large_corpora(plans, N, d, B, k, kind):
 ])
 def test_few_queries_against_the_length_of_rows(plans, N, d, B, kind):
     assert KINDS[flat(plans, N, d, 0, B, 3, 1 << 34)["kind"]] == kind
+
+
+# us, batches of 4 / this; 0: not the streaming kernel
+@pytest.mark.parametrize("dtype,N,d,B,k,batch", [
+    (0, 1_000_000, 264, 1, 3, 3),        # 109 / 101
+    (0, 1_000_000, 136, 1, 3, 5),        # 62.5 / 57
+    (0, 1_000_000, 104, 1, 3, 4),        # 48.3 / 55.7 by 3
+    (0, 1_000_000, 224, 1, 3, 4),        # 84.4 / 86.2 by 3
+    (0, 1_000_000, 768, 1, 3, 4),        # 253 / 260 by 3, 268 by 2
+    (0, 1_000_000, 776, 48, 3, 5),       # 316 / 300
+    (0, 1_000_000, 616, 48, 3, 5),       # 251 / 246
+    (0, 1_000_000, 520, 48, 3, 4),       # 225 / 223 by 3
+    (0, 21_000_000, 384, 64, 5, 2),      # 2706 / 2657
+    (0, 3_000_000, 256, 64, 3, 4),       # 303 / 311 by 2
+    (0, 1_000_000, 256, 32, 3, 2),       # 103 / 95.7
+    (2, 1_000_000, 96, 4, 3, 2),         # 80.6 / 73.5
+    (2, 1_000_000, 300, 4, 3, 4),        # 236 / 256 by 2
+    (0, 128, 768, 64, 4, 4),             # one slab
+    # the shapes of test_batches_of_the_streaming_kernel reach what they are there for
+    (0, 70_001, 264, 16, 3, 3), (1, 70_001, 1_000, 3, 10, 3), (0, 140_003, 160, 5, 4, 5), (1, 140_003, 136, 7, 16, 5), (0, 200_001, 776, 40, 10, 5),
+    (1, 200_001, 776, 64, 3, 5), (0, 200_000, 456, 17, 16, 5), (0, 530_001, 264, 33, 3, 3), (1, 70_001, 768, 40, 4, 2), (0, 150_000, 1_024, 64, 10, 2),
+    (1, 600_001, 192, 17, 5, 2), (2, 60_001, 80, 9, 4, 2), (2, 50_000, 96, 16, 10, 2), (2, 40_001, 2_400, 3, 1, 2)])
+def test_batches_where_they_were_measured_to_pay(plans, dtype, N, d, B, k, batch):
+    assert plans.batch(CUS, N, d, dtype, B, k) == batch
 
 
 # us, stages of rows / of lines of memory; tile by both rules
