@@ -387,25 +387,33 @@ inline int wide_tile(int cus, int64_t N, int d, int B, int k) {
 //   81 k x 160, B = 10 19.1 / 13.2; 97 k x 160, B = 14 20.3 / 14.4; 72 k x 240, B = 6 19.3 / 16.6; 211 k x 96, B = 6 23.8 / 20.2; but 100 k x 248,
 //   B = 2 18.1 / 18.9; 112 k x 256, B = 14 18.2 / 19.2; 180 k x 224, B = 12 25.5 / 26.5; 454 k x 128, B = 14 29.7 / 31.1.
 //   up to 32 Ki rows: 20 k x 768, B = 16 / 24 16.2 / 18.9, 22.0 / 19.3; x 384, B = 24 16.4 / 16.5; 32 k x 768, B = 48 26 / 24.
-//   beyond, by groups of 16 queries against d: 64 k x 128, B = 16 / 24 13.3 / 13.2, 16.8 / 13.2; 64 k x 768, B = 32 / 48 31 / 33, 36 / 33;
-//   128 k x 256, B = 16 / 24 20.6 / 23.5, 24.8 / 23.7; 300 k x 128, B = 16 / 24 23 / 27, 28 / 27; 300 k x 256, B = 32 / 48 41 / 43, 47 / 44;
-//   1 M x 128, B = 32 / 48 62 / 63, 85 / 68; 1 M x 256, B = 64 125 / 121; 1 M x 768, B = 64 290 / 320.
-//   beyond 4 Mi rows, where lists seldom change any more: 17.2 M x 232, B = 59, k = 5 1623 / 2185 (2234 in the parts of 8 MiB); 21 M x 256,
-//   B = 64 1841 / 2571; 4.3 M x 248, B = 64 451 / 570; 6.0 M x 200, B = 61 587 / 691; 15.9 M x 120, B = 37 841 / 1020; 9.8 M x 120, B = 64
-//   602 / 675, but 6.6 M x 112, B = 62 502 / 438, x 80, B = 47 392 / 316; 9.4 M x 72, B = 39 516 / 413.
-//   from 1.25 Mi rows of over 192 elements (B = 64): 1.5 M x 256 166 / 178, 2.2 M 226 / 264, 4 M 389 / 485; x 224, B = 60 183 / 175, 245 / 255,
-//   403 / 468; but x 192, B = 52 172 / 137, 234 / 203, 384 / 365; x 136, B = 64 163 / 128, 222 / 194, 352 / 335.
+//   up to 128 Ki rows, by queries against d: 64 k x 128, B = 16 / 24 13.3 / 13.2, 16.8 / 13.2; 64 k x 768, B = 32 / 48 31 / 33, 36 / 33; 128 k x 256,
+//   B = 16 / 24 20.6 / 23.5, 24.8 / 23.7.
+//   beyond, by groups of 16 queries, whose lists and whose share of the products each cost the streaming kernel the same again, against d; the
+//   line falls as corpora grow, since lists change less and less.  Two, three and four groups: 300 k x 96, B = 20 28.5 / 21.3, x 224 1 / 0.90, x 256 1 / 1.02; x 320,
+//   B = 40 1 / 0.94, x 384 1 / 1.00; x 512, B = 56 1 / 0.97; 1 M x 128, B = 24 64.7 / 59.8, x 192, B = 32 77.1 / 83.8; x 224, B = 48 1 / 0.97, x 256 110.6 / 117.2; x 320, B = 64
+//   162 / 148, x 384 163 / 171; 2 M x 96, B = 32 1 / 0.96, x 128 1 / 1.11; x 160, B = 40 1 / 0.98, x 200 1 / 1.06; x 224, B = 64 1 / 0.93, x 256 1 / 1.04; 3.5 M x 96,
+//   B = 32 1 / 1.13; x 128, B = 40 1 / 0.93, x 160 1 / 1.06; x 192, B = 64 1 / 0.91, x 224 1 / 1.04; 3 M x 128, B = 32 149 / 183; 15.9 M x 120, B = 37 841 / 1020; 17.2 M x
+//   232, B = 59, k = 5 1623 / 2185; 6.6 M x 112, B = 62 502 / 438; longer answers 949 k x 320, B = 53, k = 5 142 / 148; 1.5 M x 256, B = 63, k = 16 179 / 192.
 inline bool many_queries(int64_t N, int d, int B) { return B * (N <= 128 * 1024 ? 16 : N <= 512 * 1024 ? 8 : 4) >= d; }
-inline bool lists_settle(int64_t N, int d, int B) { return (N > 4 * 1024 * 1024 || (N > 1280 * 1024 && d > 192)) && 2 * B < d; }
+inline bool queries_apart(int d, int B) {                 // 16 bits: they do not fit the LDS together
+    const int groups = (B + 15) / 16, steps = (d * 2 + 63) / 64;
+    return groups > 1 && groups * steps > STREAM_LDS_STEPS;
+}
+inline bool wide_beats_lists(int64_t N, int d, int B, int k) {
+    const int groups = (B + 15) / 16;
+    const double share = k > 4 && N > 512 * 1024 ? 0.88 : 1;                     // (more groups of rows to score again, from memory)
+    if (N > 1280 * 1024 && d >= 256) return false;                                // (1.5 M x 256, B = 64 166 / 178)
+    return d <= (groups <= 2 ? 155 : groups == 3 ? 235 : 325) * share * pow(1e6 / (double)N, 0.4);
+}
 inline bool use_wide(int64_t N, int d, int dtype, int B, int k) {
     if (dtype == ANN_F32) return false;
     if (B >= WIDE_MIN_B) return true;
     if (N <= 16 * 1024) return k > 4 || d >= 384 || (N > 6000 && B > 32);
-    const int groups = (B + 15) / 16, steps = (d * 2 + 63) / 64;
-    if (d <= 64 || (groups > 1 && groups * steps > STREAM_LDS_STEPS)) return true;
+    if (d <= 64 || queries_apart(d, B)) return true;
     if (N <= 32 * 1024) return B > 32 || (B > 16 && d >= 768);
     if (B <= 16) return N <= 128 * 1024 ? d <= 240 : N <= 512 * 1024 && d <= 96;
-    return many_queries(N, d, B) && !lists_settle(N, d, B);
+    return N <= 128 * 1024 ? many_queries(N, d, B) : wide_beats_lists(N, d, B, k);
 }
 
 // fp32 keeps lists for up to 16 queries (HBM-bound on large corpora) and wherever picking costs more than the lists: the rows
@@ -590,6 +598,8 @@ inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, si
     pl.rows = N;
     pl.wide = !first.wide;
     plan();
+    // (beyond the line by queries a buffer too small for lists has always been refused)
+    if (first.wide && pl.ws_bytes > limit && B > 16 && N > 128 * 1024 && !in_parts && !many_queries(N, d, B) && d > 64 && !queries_apart(d, B)) return pl;
     if (pl.ws_bytes > limit || (fits && lists_us(pl, cus, N, d, dtype, B, k) >= parts_us(first, N, d, B, k))) return first;
     return pl;
 }

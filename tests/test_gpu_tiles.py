@@ -85,7 +85,7 @@ def test_square_tiles(dtype, N, d, B, k):
     (torch.float16, 200_001, 776, 40, 10),     # more queries, batches of 5: eight waves
     (torch.bfloat16, 200_001, 776, 64, 3),     # ... 16 waves
     (torch.float16, 200_000, 456, 17, 16),     # ... two groups of queries
-    (torch.float16, 530_001, 264, 33, 3),      # ... of 3
+    (torch.float16, 1_000_001, 264, 33, 3),    # ... of 3
     (torch.bfloat16, 70_001, 768, 40, 4),      # ... of 2, whole rows
     (torch.float16, 150_000, 1_024, 64, 10),   # ... 16 waves
     (torch.bfloat16, 600_001, 192, 17, 5),     # ... two groups, large corpora

@@ -362,6 +362,36 @@ def test_few_queries_against_the_length_of_rows(plans, N, d, B, kind):
     assert KINDS[flat(plans, N, d, 0, B, 3, 1 << 34)["kind"]] == kind
 
 
+# us, lists / matrix cores
+@pytest.mark.parametrize("N,d,B,k,kind", [
+    (300_000, 96, 20, 3, "wide"),        # 28.5 / 21.3
+    (300_000, 288, 32, 3, "lists"),      # 1 / 1.07
+    (138_238, 464, 44, 5, "wide"),       # 44.8 / 35.1
+    (163_627, 512, 60, 1, "wide"),       # 49.4 / 43.5
+    (1_000_000, 128, 24, 3, "wide"),     # 64.7 / 59.8
+    (1_000_000, 192, 32, 3, "lists"),    # 77.1 / 83.8
+    (1_000_000, 256, 48, 3, "lists"),    # 110.6 / 117.2
+    (1_000_000, 320, 64, 3, "wide"),     # 162 / 148
+    (1_000_000, 384, 64, 3, "lists"),    # 163 / 171
+    (949_486, 320, 53, 5, "lists"),      # 142 / 148
+    (1_528_200, 256, 63, 16, "lists"),   # 179 / 192
+    (3_000_000, 128, 32, 3, "lists"),    # 149 / 183
+    (4_426_861, 88, 41, 5, "wide")])     # 289 / 221
+def test_groups_of_queries_against_the_length_of_rows(plans, N, d, B, k, kind):
+    """The same kernel in the static workspace, so that both entry points give the same bits."""
+    assert KINDS[flat(plans, N, d, 0, B, k, 1 << 30)["kind"]] == kind
+    assert KINDS[plans.static_kind(CUS, N, d, 0, B, k, STATIC)] == kind
+
+
+@pytest.mark.parametrize("N,d,B,k", [(1_000_000, 320, 64, 3), (1_000_000, 224, 48, 3)])
+def test_a_buffer_too_small_for_lists_is_refused(plans, N, d, B, k):
+    """... where parts on the matrix cores would fit, but the line by queries leaves the call to lists; of a size that those need it is taken."""
+    assert KINDS[flat(plans, N, d, 0, B, k, 1 << 30)["kind"]] == "wide"
+    assert flat(plans, N, d, 0, B, k, 20_000)["bytes"] > 20_000
+    p = flat(plans, N, d, 0, B, k, 600_000)
+    assert KINDS[p["kind"]] == "lists" and p["rows"] == N
+
+
 # us, batches of 4 / this; 0: not the streaming kernel
 @pytest.mark.parametrize("dtype,N,d,B,k,batch", [
     (0, 1_000_000, 264, 1, 3, 3),        # 109 / 101
@@ -380,7 +410,7 @@ def test_few_queries_against_the_length_of_rows(plans, N, d, B, kind):
     (0, 128, 768, 64, 4, 4),             # one slab
     # the shapes of test_batches_of_the_streaming_kernel reach what they are there for
     (0, 70_001, 264, 16, 3, 3), (1, 70_001, 1_000, 3, 10, 3), (0, 140_003, 160, 5, 4, 5), (1, 140_003, 136, 7, 16, 5), (0, 200_001, 776, 40, 10, 5),
-    (1, 200_001, 776, 64, 3, 5), (0, 200_000, 456, 17, 16, 5), (0, 530_001, 264, 33, 3, 3), (1, 70_001, 768, 40, 4, 2), (0, 150_000, 1_024, 64, 10, 2),
+    (1, 200_001, 776, 64, 3, 5), (0, 200_000, 456, 17, 16, 5), (0, 1_000_001, 264, 33, 3, 3), (1, 70_001, 768, 40, 4, 2), (0, 150_000, 1_024, 64, 10, 2),
     (1, 600_001, 192, 17, 5, 2), (2, 60_001, 80, 9, 4, 2), (2, 50_000, 96, 16, 10, 2), (2, 40_001, 2_400, 3, 1, 2)])
 def test_batches_where_they_were_measured_to_pay(plans, dtype, N, d, B, k, batch):
     assert plans.batch(CUS, N, d, dtype, B, k) == batch
