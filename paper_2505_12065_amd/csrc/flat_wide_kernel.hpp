@@ -59,6 +59,8 @@ __device__ __forceinline__ void bare_barrier() {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 }
+// ... and that a wave comes to with its LDS reads in registers
+__device__ __forceinline__ void barrier_after_reads() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 static __device__ __align__(16) unsigned char zero_row_end[16];          // what lies behind the end of a row
 
@@ -196,7 +198,11 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
         else static_for<NST - 2>([&](auto rc) {
             if (newer == decltype(rc)::value) wait_vmcnt<decltype(rc)::value * LPW>();
         });
-        bare_barrier();                                   // ... for every wave; the buffer of stage it - 1 is free
+        // ... for every wave.  And the buffer of stage it - 1 is free, which the next loads go to: no wave reads it any more.  Its products
+        // see to that, which need what was read; BY_LINE they come a read later, so the reads are waited for (a tile's first line: its
+        // second one is read before any product).
+        if constexpr (BY_LINE) barrier_after_reads();
+        else bare_barrier();
         if constexpr (!LINES) issue();
         // Operand row r = lane % 32 of a 32-row block pair, chunk 2 kh + lane / 32.  All operand reads of the stage
         // are issued before the first MFMA, so the LDS pipeline always has several 1 KB reads of this wave in flight.
