@@ -277,7 +277,9 @@ int64_t ann_flat_workspace_bytes(int64_t N, int32_t d, int32_t dtype, int32_t B,
  * search that does not fit `bytes` at once takes the corpus in parts, or fewer slabs, or (up to 64
  * queries of 16 bits) the kernel that needs less, if its own needs parts that take longer; one that would need parts of fewer than 8192 rows, or
  * less than a quarter of its slabs, and a graph search that needs more than `bytes`, fail with
- * ANN_ERR_NOMEM instead of growing anything.  A flat search captured into a graph while the library's
+ * ANN_ERR_NOMEM instead of growing anything.  (17 to 64 queries of 16 bits over more than 128 Ki rows of more than 4 times as
+ * many elements, up to 512 Ki rows 8 times, whose lists are one pass: less than a quarter of the slabs of lists, though group maxima may be what
+ * runs and need less.  ann_flat_workspace_bytes is always enough.)  A flat search captured into a graph while the library's
  * own buffer would have to grow does likewise with the buffer as it is.
  *   workspace  device pointer, 256-byte aligned, valid until it is replaced (and as long as graphs
  *              captured with it are replayed); NULL: back to the library-owned buffers.  Not freed by the library.  Calls that use it must not overlap. */

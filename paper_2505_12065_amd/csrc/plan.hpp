@@ -400,6 +400,11 @@ inline bool queries_apart(int d, int B) {                 // 16 bits: they do no
     const int groups = (B + 15) / 16, steps = (d * 2 + 63) / 64;
     return groups > 1 && groups * steps > STREAM_LDS_STEPS;
 }
+// 16-bit calls that the line by queries leaves to lists, whichever kernel the line by groups of queries gives them: callers go by the error that a
+// buffer too small for lists gives (ann_set_workspace), so it stays where it was.
+inline bool lists_must_fit(int64_t N, int d, int B) {
+    return B > 16 && B < WIDE_MIN_B && N > 128 * 1024 && d > 64 && !queries_apart(d, B) && !many_queries(N, d, B);
+}
 inline bool wide_beats_lists(int64_t N, int d, int B, int k) {
     const int groups = (B + 15) / 16;
     const double share = k > 4 && N > 512 * 1024 ? 0.88 : 1;                     // (more groups of rows to score again, from memory)
@@ -581,6 +586,13 @@ inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, si
     pl.quick = pl.direct && direct_quick(cus, N, row_bytes, dtype, B);
     pl.maxima = !pl.direct && dtype == ANN_F32 && use_f32_maxima(N, d, B, k);
     pl.wide = !pl.direct && use_wide(N, d, dtype, B, k);
+    if (pl.wide && !in_parts && lists_must_fit(N, d, B)) {
+        FlatPlan lists{};
+        lists.part = B;
+        lists.rows = N;
+        lists_plan(lists, cus, N, d, dtype, B, k, limit);
+        if (lists.ws_bytes > limit) return lists;
+    }
     auto plan = [&] {
         if (pl.wide || pl.maxima) maxima_plan(pl, cus, N, d, dtype, B, k, limit);
         else lists_plan(pl, cus, N, d, dtype, B, k, limit);
@@ -598,8 +610,6 @@ inline FlatPlan flat_plan(int cus, int64_t N, int d, int dtype, int B, int k, si
     pl.rows = N;
     pl.wide = !first.wide;
     plan();
-    // (beyond the line by queries a buffer too small for lists has always been refused)
-    if (first.wide && pl.ws_bytes > limit && B > 16 && N > 128 * 1024 && !in_parts && !many_queries(N, d, B) && d > 64 && !queries_apart(d, B)) return pl;
     if (pl.ws_bytes > limit || (fits && lists_us(pl, cus, N, d, dtype, B, k) >= parts_us(first, N, d, B, k))) return first;
     return pl;
 }

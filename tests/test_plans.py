@@ -392,6 +392,18 @@ def test_a_buffer_too_small_for_lists_is_refused(plans, N, d, B, k):
     assert KINDS[p["kind"]] == "lists" and p["rows"] == N
 
 
+@pytest.mark.parametrize("N,d,B,k,buffer,slabs", [
+    (156_898, 312, 17, 14, 217_662, 409), (138_557, 576, 50, 13, 565_586, 361), (195_451, 600, 54, 14, 766_163, 509)])
+def test_a_buffer_too_small_for_lists_is_refused_where_maxima_would_fit(plans, N, d, B, k, buffer, slabs):
+    """... at once: the line of what is refused is the one of lists, a quarter of their slabs, for both kernels."""
+    asked = flat(plans, N, d, 0, B, k, 1 << 30)
+    assert KINDS[asked["kind"]] == "wide" and flat(plans, N, d, 0, B, k, asked["bytes"])["bytes"] == asked["bytes"]
+    assert flat(plans, N, d, 0, B, k, buffer)["bytes"] > buffer
+    least = (slabs + 3) // 4 * B * 16 * 8                                # (lists of 16 pairs)
+    assert buffer < least and flat(plans, N, d, 0, B, k, least)["bytes"] <= least
+    assert flat(plans, N, d, 0, B, k, least - 1)["bytes"] > least - 1
+
+
 # us, batches of 4 / this; 0: not the streaming kernel
 @pytest.mark.parametrize("dtype,N,d,B,k,batch", [
     (0, 1_000_000, 264, 1, 3, 3),        # 109 / 101
