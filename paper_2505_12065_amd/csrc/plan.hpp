@@ -389,12 +389,16 @@ inline int wide_tile(int cus, int64_t N, int d, int B, int k) {
 //   up to 32 Ki rows: 20 k x 768, B = 16 / 24 16.2 / 18.9, 22.0 / 19.3; x 384, B = 24 16.4 / 16.5; 32 k x 768, B = 48 26 / 24.
 //   up to 128 Ki rows, by queries against d: 64 k x 128, B = 16 / 24 13.3 / 13.2, 16.8 / 13.2; 64 k x 768, B = 32 / 48 31 / 33, 36 / 33; 128 k x 256,
 //   B = 16 / 24 20.6 / 23.5, 24.8 / 23.7.
-//   beyond, by groups of 16 queries, whose lists and whose share of the products each cost the streaming kernel the same again, against d; the
-//   line falls as corpora grow, since lists change less and less.  Two, three and four groups: 300 k x 96, B = 20 28.5 / 21.3, x 224 1 / 0.90, x 256 1 / 1.02; x 320,
-//   B = 40 1 / 0.94, x 384 1 / 1.00; x 512, B = 56 1 / 0.97; 1 M x 128, B = 24 64.7 / 59.8, x 192, B = 32 77.1 / 83.8; x 224, B = 48 1 / 0.97, x 256 110.6 / 117.2; x 320, B = 64
-//   162 / 148, x 384 163 / 171; 2 M x 96, B = 32 1 / 0.96, x 128 1 / 1.11; x 160, B = 40 1 / 0.98, x 200 1 / 1.06; x 224, B = 64 1 / 0.93, x 256 1 / 1.04; 3.5 M x 96,
-//   B = 32 1 / 1.13; x 128, B = 40 1 / 0.93, x 160 1 / 1.06; x 192, B = 64 1 / 0.91, x 224 1 / 1.04; 3 M x 128, B = 32 149 / 183; 15.9 M x 120, B = 37 841 / 1020; 17.2 M x
-//   232, B = 59, k = 5 1623 / 2185; 6.6 M x 112, B = 62 502 / 438; longer answers 949 k x 320, B = 53, k = 5 142 / 148; 1.5 M x 256, B = 63, k = 16 179 / 192.
+//   beyond, by groups of 16 queries: lists cost a row the same whatever its length, and as long again until they are settled; the matrix cores cost more
+//   for every element.  So lists are quicker where N (d - r) > q, r elements for what a row costs and q, in millions, for settling; with 17 to 32 queries
+//   r = 67.5, q = 65; to 48 82.5, 150; to 64 110, 180.  A row that batches of loads do not divide costs lists about half of what is loaded for nothing
+//   (x 192 in batches of 128 elements), and long answers of 0.5 to 1.25 Mi rows cost the matrix cores 2 %, groups of rows scored again (3 to 5 % less beyond
+//   4 Mi, which the line leaves out).  Fitted to both kernels at 725 sizes within 0.6 to 1.7 times the line, 131 k to 22 M rows: 0.6 % behind the better one on
+//   average, 10 % at worst from 200 k rows on, 18 % below.  Rows of 768 elements and more keep their lists (341 k x 840, B = 51 141 / 126, 133 k x 960, B = 39
+//   69 / 62; from 500 k rows on they are the quicker ones).  us, two, three and four groups: 300 k x 96, B = 20 28.2 / 21.0, x 288, B = 32
+//   45.1 / 48.5; 1 M x 128, B = 24 64.7 / 59.9, x 192, B = 32 77.6 / 83.8; 3 M x 128, B = 32 148 / 183; 138 k x 464, B = 44, k = 5 50.5 / 38.7; 1 M x 256, B = 48
+//   110 / 117; 1.03 M x 232, B = 45 116 / 124; 4.4 M x 88, B = 41, k = 5 288 / 221; 207 k x 520, B = 45 67.7 / 55.5; 1 M x 320, B = 64 153 / 148, x 384 158 / 171;
+//   949 k x 320, B = 53, k = 5 145 / 148; 1.5 M x 256, B = 64 167 / 179; 3.1 M x 192, B = 51, k = 16 323 / 293; 16.8 M x 96, B = 54, k = 5 1036 / 919.
 inline bool many_queries(int64_t N, int d, int B) { return B * (N <= 128 * 1024 ? 16 : N <= 512 * 1024 ? 8 : 4) >= d; }
 inline bool queries_apart(int d, int B) {                 // 16 bits: they do not fit the LDS together
     const int groups = (B + 15) / 16, steps = (d * 2 + 63) / 64;
@@ -406,10 +410,11 @@ inline bool lists_must_fit(int64_t N, int d, int B) {
     return B > 16 && B < WIDE_MIN_B && N > 128 * 1024 && d > 64 && !queries_apart(d, B) && !many_queries(N, d, B);
 }
 inline bool wide_beats_lists(int64_t N, int d, int B, int k) {
-    const int groups = (B + 15) / 16;
-    const double share = k > 4 && N > 512 * 1024 ? 0.88 : 1;                     // (more groups of rows to score again, from memory)
-    if (N > 1280 * 1024 && d >= 256) return false;                                // (1.5 M x 256, B = 64 166 / 178)
-    return d <= (groups <= 2 ? 155 : groups == 3 ? 235 : 325) * share * pow(1e6 / (double)N, 0.4);
+    const int groups = (B + 15) / 16, steps = (d * 2 + 63) / 64, batch = stream_batch(d * 2, ANN_F16, groups);
+    const double r = groups <= 2 ? 67.5 : groups == 3 ? 82.5 : 110, q = groups <= 2 ? 65e6 : groups == 3 ? 150e6 : 180e6;
+    const double answers = k > 4 && N > 512 * 1024 && N <= 1280 * 1024 ? 0.96 : 1;
+    const int idle = ((steps + batch - 1) / batch * batch - steps) * 32;           // elements loaded for nothing
+    return d < 768 && d - 0.5 * idle <= answers * (r + q / (double)N);
 }
 inline bool use_wide(int64_t N, int d, int dtype, int B, int k) {
     if (dtype == ANN_F32) return false;

@@ -383,6 +383,23 @@ def test_groups_of_queries_against_the_length_of_rows(plans, N, d, B, k, kind):
     assert KINDS[plans.static_kind(CUS, N, d, 0, B, k, STATIC)] == kind
 
 
+# us, lists / matrix cores
+@pytest.mark.parametrize("N,d,B,k,kind", [
+    (3_322_254, 192, 59, 3, "wide"),     # 338 / 306
+    (3_105_114, 192, 51, 16, "wide"),    # 323 / 293
+    (16_756_363, 96, 54, 5, "wide"),     # 1036 / 919
+    (207_230, 520, 45, 1, "wide"),       # 67.7 / 55.5
+    (224_096, 608, 58, 5, "wide"),       # 78.2 / 68.2
+    (1_030_004, 232, 45, 3, "lists"),    # 116 / 124
+    (1_167_215, 256, 54, 16, "lists"),   # 141 / 148
+    (1_500_000, 256, 64, 3, "lists"),    # 167 / 179
+    (15_252_880, 128, 64, 1, "lists")])  # 789 / 1040
+def test_a_row_and_settled_lists_against_elements(plans, N, d, B, k, kind):
+    """Sizes that a line by a power of the rows and a cut at 1.25 Mi rows sent to the slower kernel, and some beside them."""
+    assert KINDS[flat(plans, N, d, 0, B, k, 1 << 30)["kind"]] == kind
+    assert KINDS[plans.static_kind(CUS, N, d, 0, B, k, STATIC)] == kind
+
+
 @pytest.mark.parametrize("N,d,B,k", [(1_000_000, 320, 64, 3), (1_000_000, 224, 48, 3)])
 def test_a_buffer_too_small_for_lists_is_refused(plans, N, d, B, k):
     """... where parts on the matrix cores would fit, but the line by queries leaves the call to lists; of a size that those need it is taken."""
