@@ -119,7 +119,10 @@ __global__ __launch_bounds__(C::THREADS, C::PER_CU * C::WAVES / 4) void flat_wid
             if (blk < C::A_BLK) {
                 int64_t row = tile * BM + blk * RPB + lane / CPR;
                 row = row < N ? row : N - 1;
-                if constexpr (BY_LINE) ch = ((ch + lead(row)) & 7) - lead(row);
+                if constexpr (BY_LINE) {
+                    asm volatile("" : "+v"(ch));          // (no register is left for what a ragged tile would find ready made)
+                    ch = ((ch + lead(row)) & 7) - lead(row);
+                }
                 loff[e] = (uint32_t)(row - tile * BM) * (uint32_t)rb + ch * 16;
             } else {
                 int q = n0 + (blk - C::A_BLK) * RPB + lane / CPR;

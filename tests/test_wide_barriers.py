@@ -1,6 +1,6 @@
 """The LDS stages of the matrix-core kernel, by the assembly that the compiler makes of it: a barrier there waits for no memory operation, and
 behind it loads go to a buffer that other waves have read.  So no wave may come to it with LDS reads outstanding; that a load takes longer
-than a read hides a missing wait from any test of results."""
+than a read hides a missing wait from any test of results.  And what the kernel keeps in scratch memory."""
 import re
 import subprocess
 
@@ -65,6 +65,12 @@ def test_no_reads_outstanding_at_a_barrier(kernels, tile, by_line):
     at, barriers, reads, loads = outstanding(kernels[tile, by_line])
     assert barriers and reads and loads and len(at) == barriers          # (all barriers are reached)
     assert at == [0] * barriers
+
+
+@pytest.mark.parametrize("tile,by_line", [(t, "false") for t in TILES] + [(t, "true") for t in BY_LINE])
+def test_no_register_in_scratch_memory(kernels, tile, by_line):
+    """A wait for one that comes back is a wait for the stage loads that are on their way."""
+    assert "scratch_" not in kernels[tile, by_line]
 
 
 def test_an_outstanding_read_is_seen():
