@@ -18,7 +18,7 @@ template <class T, class C>
 hipError_t launch(const WidePlan &pl, const void *X, int64_t N, int d, const void *Q, int B, float *maxima, After after,
                   hipStream_t stream) {
     if constexpr (C::SB == 128 && (C::WAVES == 8 || C::STAGES == 3))      // (the tiles that corpora beyond the caches get)
-        if (pl.gs_log > 0 && wide_by_line(N, d)) return launch_one<T, C, false, true>(pl, X, N, d, Q, B, maxima, after, stream);
+        if (pl.gs_log > 0 && wide_by_line(N, d, pl.NT)) return launch_one<T, C, false, true>(pl, X, N, d, Q, B, maxima, after, stream);
     return pl.gs_log == 0 ? launch_one<T, C, true, false>(pl, X, N, d, Q, B, maxima, after, stream)
                           : launch_one<T, C, false, false>(pl, X, N, d, Q, B, maxima, after, stream);
 }

@@ -297,13 +297,27 @@ inline int wide_thin(int cus, int64_t N, int d, int B) {
     const int64_t tiles = (N + WideThin::BM - 1) / WideThin::BM * ((B + WideThin::BN - 1) / WideThin::BN);
     return d <= 32 || (d <= 256 && tiles > 2 * (int64_t)cus && tiles <= 3 * (int64_t)cus) ? WIDE_SHORT : WIDE_THIN;
 }
+// Stages of a tile by lines, in chunks of 16 bytes: rows begin at multiples of `least` in a line, so 8 - least is the most that comes before them.
+inline int wide_lines(int d) {
+    const int nch = d / 8, least = (nch | 8) & -(nch | 8);
+    return (nch + 8 - least + 7) / 8;
+}
 // Whether 256 x 128 and 128 x 64 tiles go by the lines of memory that rows lie in (flat_wide_kernel's BY_LINE: same bits): rows that are no whole
 // number of lines, of corpora that come from memory.  The selects cost what the requests save where the corpus stays in the caches: us, stages
 // of rows / of lines, read again / after others: 80 k x 520, B = 77 30.9 / 31.3, 31.3 / 31.9; 80 k x 776 39.9 / 40.1, 50.7 / 44.8; 123 457 x 776 43.4 / 43.5,
 // 56.4 / 51.3; 640 k x 776 242 / 219, 242 / 220; 300 k x 200, B = 40 32.7 / 31.6, 41.8 / 37.3.  Half lines, which fewer requests divide: 123 457 x 800, B = 77
 // 41.8 / 43.1, 52.4 / 51.5; 160 k x 800 56.9 / 57.3, 70.7 / 68.3; 1 M x 800, B = 128 387 / 365, 399 / 368; 800 k x 160, B = 77 78.2 / 76.1.  Up to a line
 // the stages are mostly first and last ones: 1.5 M x 72, B = 24 63 / 68, 600 k x 120, B = 40 44.5 / 46.6.
-inline bool wide_by_line(int64_t N, int d) { return d > 128 && d % 64 != 0 && N * d * 2 >= (d % 32 != 0 ? 128000000 : 256000000); }
+// Corpora of less than 256 MiB, the cache in front of the memory, only where that costs nothing when they are read again, as by one call after
+// another: no stage more than by rows and one tile of queries, read again 0.985 times as long, after others 0.90 (98 sizes).  With a stage more, read
+// again 1.024 times (141 881 x 488, B = 170 54.2 / 59.4, 287 599 x 240, B = 78 39.0 / 42.1), with more tiles, whose rows come from the caches but once, 1.03 to
+// 1.05 (136 205 x 688, B = 210 76.6 / 81.6).  From 256 MiB on all gain, read again or not: 0.92.
+constexpr int64_t WIDE_BEYOND_CACHES = 1 << 28;
+inline bool wide_by_line(int64_t N, int d, int col_tiles) {
+    if (d <= 128 || d % 64 == 0) return false;
+    if (N * d * 2 >= WIDE_BEYOND_CACHES) return true;
+    return N * d * 2 >= 128000000 && d % 32 != 0 && col_tiles == 1 && wide_lines(d) == (d + 63) / 64;
+}
 inline int wide_shape(int cus, int64_t N, int d, int B) {
     auto tiles = [&](int bm, int bn) { return (N + bm - 1) / bm * ((B + bn - 1) / bn); };
     const int64_t cols256 = (B + 255) / 256 * 256, cols128 = (B + 127) / 128 * 128;
@@ -348,8 +362,11 @@ inline double wide_rounds_us(int shape, int cus, int64_t N, int d, int B) {
 inline int wide_tile(int cus, int64_t N, int d, int B, int k) {
     int first = wide_shape(cus, N, d, B);
     // Lines of memory instead of 512 x 128, us: 600 k x 232, B = 77 93.8 / 85.1; 640 k x 456, B = 77 165 / 146; 1 M x 456, B = 128 271 / 248; 1.5 M x 200,
-    // B = 128 189 / 182; but 4 M x 184, B = 100 412 / 414, and by half lines 2 M x 352, B = 100 344 / 349.
-    const bool tall = !(wide_by_line(N, d) && d % 32 != 0 && d >= 200);
+    // B = 128 189 / 182; but 4 M x 184, B = 100 412 / 414, by half lines 2 M x 352, B = 100 344 / 349, and 216, of whose lines a third is not the row,
+    // 2.5 M, B = 127 1 / 1.014, 2.2 M, B = 99 1 / 1.024 (800 k, B = 77 1 / 0.96; 232, 240 and 248 2.5 M, B = 127 0.95, 1.002, 0.98).  Corpora of less than 256 MiB,
+    // read again: 247 898 x 280, B = 108 38.8 / 42.3, 360 486 x 208, B = 81 45.4 / 48.0.
+    const bool apart = d % 32 != 0 && d >= 200 && 10 * (8 * wide_lines(d) - d / 8) <= 24 * wide_lines(d);
+    const bool tall = !(apart && N * d * 2 >= WIDE_BEYOND_CACHES);
     if (first == WIDE_TALL && !tall) first = WIDE_MID;
     if (B <= 64 || d <= 64 || first == WIDE_TINY) return first;
     const bool cached = N * d * 2 <= 64000000;

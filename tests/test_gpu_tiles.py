@@ -99,9 +99,9 @@ def test_batches_of_the_streaming_kernel(dtype, N, d, B, k):
 
 @pytest.mark.parametrize("dtype,N,d,B,k,offset", [
     (torch.float16, 83_001, 776, 77, 10, 0),   # 256 x 128, as many lines as steps
-    (torch.bfloat16, 64_257, 1_000, 66, 16, 7),    # ... a line more, one row in the last tile
-    (torch.bfloat16, 530_000, 200, 70, 3, 1),  # ... in the place of 512 x 128; four lines
-    (torch.float16, 131_072, 992, 128, 3, 4),  # ... half lines, whole tiles
+    (torch.bfloat16, 134_401, 1_000, 66, 16, 7),   # ... a line more, one row in the last tile
+    (torch.bfloat16, 680_000, 200, 70, 3, 1),  # ... in the place of 512 x 128; four lines
+    (torch.float16, 135_424, 992, 128, 3, 4),  # ... half lines, whole tiles
     (torch.float16, 330_001, 200, 40, 4, 3),   # 128 x 64
     (torch.bfloat16, 480_000, 136, 17, 16, 0),     # ... the shortest rows: a step of one chunk behind two
     (torch.float16, 300_000, 264, 40, 1, 6),

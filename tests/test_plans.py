@@ -45,7 +45,7 @@ extern "C" int batch(int cus, int64_t N, int d, int dtype, int B, int k) {
     const FlatPlan pl = flat_plan(cus, N, d, dtype, B, k, WIDE_WS_MAX);
     return pl.wide || pl.scores || pl.quick ? 0 : pl.st.batch;
 }
-extern "C" int by_line(int64_t N, int d) { return wide_by_line(N, d); }
+extern "C" int by_line(int64_t N, int d, int col_tiles) { return wide_by_line(N, d, col_tiles); }
 extern "C" int tile(int cus, int64_t N, int d, int B, int k) { return wide_tile(cus, N, d, B, k); }
 static int kind(const FlatPlan &pl) { return pl.scores ? 4 : pl.quick ? 5 : pl.wide ? 2 : pl.maxima ? 3 : pl.direct ? 1 : 0; }
 // out: kind (0 lists, 1 direct, 2 matrix cores, 3 streaming with maxima, 4 scores, 5 direct by flat_direct_kernel), queries and rows at a time, maxima of a query,
@@ -91,7 +91,7 @@ def plans(tmp_path_factory):
     L.shape.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 2
     L.tile.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 3
     L.batch.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4
-    L.by_line.argtypes = [ctypes.c_int64, ctypes.c_int]
+    L.by_line.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 2
     L.in_lds.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4
     L.flat.argtypes = L.flat_by_fill.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64, ctypes.c_void_p]
     L.static_accepts.argtypes = L.static_kind.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.c_int64]
@@ -445,12 +445,25 @@ def test_batches_where_they_were_measured_to_pay(plans, dtype, N, d, B, k, batch
     assert plans.batch(CUS, N, d, dtype, B, k) == batch
 
 
+MID, THIN = 2, 3                                      # 256 x 128, 128 x 64
+
+
+def col_tiles(B, tile):
+    return (B + 127) // 128 if tile == MID else (B + 63) // 64
+
+
 # us, stages of rows / of lines of memory; tile by both rules
 @pytest.mark.parametrize("N,d,B,by_line,first,tile", [
     (123_457, 776, 77, 1, 2, 2),         # 56.4 / 51.3
     (80_000, 776, 77, 0, 2, 2),          # from the caches 39.9 / 40.1
-    (160_000, 800, 77, 1, 2, 2),         # half lines, 256 MB
+    (168_000, 800, 77, 1, 2, 2),         # half lines, 256 MiB
     (123_457, 800, 77, 0, 2, 2),         # 41.8 / 43.1
+    (141_881, 488, 170, 0, 0, 2),        # read again 54.2 / 59.4: two tiles of queries, a stage more
+    (136_000, 776, 170, 0, 0, 2),        # ... two tiles of queries
+    (130_000, 504, 77, 0, 2, 2),         # ... a stage more, 1 / 1.024
+    (247_898, 280, 108, 0, 2, 1),        # ... 38.8 / 42.3
+    (360_486, 208, 81, 1, 2, 1),         # read again 45.4 / 48.0 in the place of 512 x 128
+    (2_195_041, 216, 99, 1, 1, 1),       # 1 / 1.024, a third of the lines not the row
     (1_000_000, 768, 128, 0, 2, 2),      # whole lines
     (1_500_000, 120, 128, 0, 1, 1),      # less than a line
     (1_000_000, 456, 128, 1, 1, 2),      # 271 / 248, in the place of 512 x 128
