@@ -179,15 +179,21 @@ constexpr int64_t PART_MIN_ROWS = 8192;          // fewer are not worth a launch
 //   more queries, such rows: 5 or 3 where that divides the row: 1 M x 776, B = 48 316 / 300; x 456, B = 32 188 / 180; 3 M x 160, B = 32 212 / 186; 1 M x 264,
 //     B = 48 128 / 121; else 4 (1 M x 616, B = 48 251 / 258 by 3).
 //   more than 32 queries, whole lines of at least 768 bytes: 2: 21 M x 384, B = 64, k = 5 2706 / 2657; 1 M x 384, B = 48 153 / 143, x 768, B = 64 288 / 277, x 1024
-//     361 / 355; 300 k x 576, B = 48 79 / 74.6; shorter 3 M x 256, B = 64 303 / 311.  17 to 32 queries: whole lines of up to 640 bytes: 1 M x 256
-//     103 / 95.7, x 320 127 / 121, 3 M x 256 271 / 258; but 300 k x 768 92.9 / 95.0, 3 M x 512 512 / 523.
-// fp32, up to 16 queries, whole sectors: 2: 1 M x 96, B = 4 80.6 / 73.5; 100 k x 208, B = 12 27.9 / 25.8, x 384 42.2 / 40.7; but 1 M x 300 236 / 256, and more
-// queries 300 k x 256, B = 40 128 / 136.
+//     361 / 355; 300 k x 576, B = 48 79 / 74.6; shorter 3 M x 256, B = 64 303 / 311.  17 to 32 queries: whole lines of 384 to 640 bytes: 1 M x 256
+//     103 / 95.7, x 320 127 / 121, 3 M x 256 271 / 258; but 300 k x 768 92.9 / 95.0, 3 M x 512 512 / 523, 1.6 M x 128 86 / 91.
+// fp32, up to 16 queries, whole sectors of 64 bytes, of which batches of 4 load idle ones or split a line between two tiles: 2 where the row is
+//   2 or 6 or 10 ... of them (1 M x 96, B = 4 80.6 / 73.5; 100 k x 208, B = 12 27.9 / 25.8; 270 sizes up to x 1024 0.96), an odd number up to 13 (x 80
+//     0.94, x 208 0.94; but 3 M x 240 1 / 1.02, 561 k x 752, B = 10 304 / 316), and whole batches of 4 of 8 to 32 sectors, for their smaller portions (x 128 0.945; but
+//     131 k x 1024, B = 4 110 / 121, 3.2 M x 64, B = 13 1 / 1.02).  Not 1 M x 300 236 / 256, nor more queries (300 k x 256, B = 40 128 / 136).
 inline int stream_batch(int row_bytes, int dtype, int nqg) {
-    if (dtype == ANN_F32) return nqg == 1 && row_bytes % 64 == 0 ? 2 : 4;
     const int steps = (row_bytes + 63) / 64;
+    if (dtype == ANN_F32) {
+        if (nqg > 1 || row_bytes % 64 != 0) return 4;
+        const bool pays = steps % 4 == 2 || (steps % 2 == 1 ? steps <= 13 : steps >= 8 && steps <= 32);
+        return pays ? 2 : 4;
+    }
     if (row_bytes % 128 == 0)
-        return (nqg >= 3 && row_bytes >= 768) || (nqg == 2 && row_bytes <= 640) ? 2 : 4;
+        return (nqg >= 3 && row_bytes >= 768) || (nqg == 2 && row_bytes >= 384 && row_bytes <= 640) ? 2 : 4;
     if (steps % 5 == 0 && (nqg > 1 || steps == 5)) return 5;
     if (nqg > 1) return steps % 3 == 0 && steps % 4 != 0 ? 3 : 4;
     return (row_bytes % 64 != 0 && steps >= 9) || (steps + 2) / 3 * 3 <= (steps + 3) / 4 * 4 ? 3 : 4;

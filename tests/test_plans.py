@@ -434,8 +434,16 @@ def test_a_buffer_too_small_for_lists_is_refused_where_maxima_would_fit(plans, N
     (0, 21_000_000, 384, 64, 5, 2),      # 2706 / 2657
     (0, 3_000_000, 256, 64, 3, 4),       # 303 / 311 by 2
     (0, 1_000_000, 256, 32, 3, 2),       # 103 / 95.7
+    (0, 3_600_000, 128, 18, 1, 4),       # 1 / 1.01 by 2 (1.6 M 86 / 91)
     (2, 1_000_000, 96, 4, 3, 2),         # 80.6 / 73.5
     (2, 1_000_000, 300, 4, 3, 4),        # 236 / 256 by 2
+    (2, 200_000, 128, 5, 3, 2),          # 1 / 0.924
+    (2, 131_004, 1_024, 4, 5, 4),        # 110 / 121 by 2
+    (2, 3_165_301, 64, 13, 3, 4),        # 1 / 1.024 by 2
+    (2, 250_000, 208, 4, 3, 2),          # 1 / 0.924
+    (2, 2_935_657, 240, 6, 3, 4),        # 1 / 1.023 by 2
+    (2, 561_370, 752, 10, 5, 4),         # 304 / 316 by 2
+    (2, 400_000, 992, 3, 3, 2),          # 1 / 0.99
     (0, 128, 768, 64, 4, 4),             # one slab
     # the shapes of test_batches_of_the_streaming_kernel reach what they are there for
     (0, 70_001, 264, 16, 3, 3), (1, 70_001, 1_000, 3, 10, 3), (0, 140_003, 160, 5, 4, 5), (1, 140_003, 136, 7, 16, 5), (0, 200_001, 776, 40, 10, 5),
