@@ -108,7 +108,7 @@ def test_batches_of_the_streaming_kernel(dtype, N, d, B, k):
 ])
 def test_stages_of_lines_of_memory(dtype, N, d, B, k, offset):
     """Rows that begin anywhere in a line (offset: 16-byte chunks) against the same search in pieces small enough to go by the rows' own
-    stages: same bits.  A NaN or an infinity at either end of a row stays its own."""
+    stages, two pages of each: same bits.  A NaN or an infinity at either end of a row stays its own."""
     print(f"lines of memory: dtype={dtype} N={N} d={d} B={B} k={k} offset={offset}", flush=True)
     gen = torch.Generator(device=DEV).manual_seed(N + d)
     x = torch.randn(N * d + 64, generator=gen, device=DEV).to(dtype)[8 * offset:8 * offset + N * d].view(N, d)
@@ -117,16 +117,43 @@ def test_stages_of_lines_of_memory(dtype, N, d, B, k, offset):
     x[5::7, d - 1] = float("nan")
     x[100::20_011, 0] = float("inf")
     x[101::30_011, d - 1] = float("-inf")
-    got = ann.ann_flat_search_typed(x, q, k)
+    got = two_pages(x, q, k)
     step = 60_000_000 // (2 * d)
     ids, sc = [], []
     for r0 in range(0, N, step):
-        i, s = ann.ann_flat_search_typed(x[r0:r0 + step], q, k)
+        i, s = two_pages(x[r0:r0 + step], q, k)
         ids.append(i + r0)
         sc.append(s)
     ids, sc = torch.cat(ids, 1), torch.cat(sc, 1)
-    best = sc.sort(dim=1, descending=True, stable=True).indices[:, :k]          # (pieces and their rows come in the order of the ids)
+    best = sc.sort(dim=1, descending=True, stable=True).indices[:, :2 * k]      # (pieces and their rows come in the order of the ids)
     assert torch.equal(got[0], ids.gather(1, best)) and torch.equal(got[1], sc.gather(1, best))
+
+
+def two_pages(x, q, k):
+    first = ann.ann_flat_search_typed(x, q, k)
+    second = ann.ann_flat_search_typed(x, q, k, after=(first[1][:, -1].contiguous(), first[0][:, -1].contiguous()))
+    return torch.cat([first[0], second[0]], 1), torch.cat([first[1], second[1]], 1)
+
+
+@pytest.mark.parametrize("dtype,N,d,B,k,size", [
+    (torch.float16, 62_553, 2_056, 33, 9, 140_257),    # 128 x 64, two parts by lines and a short one by rows
+    (torch.bfloat16, 42_905, 3_856, 24, 7, 54_955),
+])
+def test_parts_of_lines_of_memory(dtype, N, d, B, k, size):
+    """Two pages in a caller's buffer that holds the maxima of a part of the corpus only, against the same in the library's."""
+    print(f"lines of memory in parts: dtype={dtype} N={N} d={d} B={B} k={k} bytes={size}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(N + d)
+    x = torch.randn(N, d, generator=gen, device=DEV).to(dtype)
+    q = torch.randn(B, d, generator=gen, device=DEV).to(dtype)
+    want = two_pages(x, q, k)
+    buf = torch.empty(size, dtype=torch.uint8, device=DEV)
+    try:
+        ann.ann_set_workspace(buf)
+        got = two_pages(x, q, k)
+        torch.cuda.synchronize()
+    finally:
+        ann.ann_set_workspace(None)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
 
 
 @pytest.mark.parametrize("N,d,B,k,size", [

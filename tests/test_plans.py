@@ -478,7 +478,26 @@ def col_tiles(B, tile):
     (4_000_000, 184, 100, 1, 1, 1),      # 412 / 414
     (2_000_000, 352, 100, 1, 1, 1)])     # 344 / 349
 def test_lines_of_memory_where_they_were_measured_to_pay(plans, N, d, B, by_line, first, tile):
-    assert (plans.by_line(N, d), plans.shape(CUS, N, d, B), plans.tile(CUS, N, d, B, 3)) == (by_line, first, tile)
+    assert (plans.by_line(N, d, col_tiles(B, MID)), plans.shape(CUS, N, d, B), plans.tile(CUS, N, d, B, 3)) == (by_line, first, tile)
+
+
+@pytest.mark.parametrize("N,d,B,k,tile", [
+    (83_001, 776, 77, 10, MID), (134_401, 1_000, 66, 16, MID), (680_000, 200, 70, 3, MID), (135_424, 992, 128, 3, MID),
+    (330_001, 200, 40, 4, THIN), (480_000, 136, 17, 16, THIN), (300_000, 264, 40, 1, THIN)])
+def test_the_tests_of_lines_of_memory_reach_them(plans, N, d, B, k, tile):
+    """The shapes of test_stages_of_lines_of_memory go by lines, in groups of rows, and the pieces that they are compared with do not."""
+    p = flat(plans, N, d, 0, B, k, 1 << 30)
+    assert (KINDS[p["kind"]], p["shape"], p["rows"], p["part"]) == ("wide", tile, N, B) and p["gs_log"] > 0
+    assert plans.by_line(N, d, col_tiles(B, tile)) and not plans.by_line(60_000_000 // (2 * d), d, 1)
+
+
+@pytest.mark.parametrize("N,d,B,k,size", [(62_553, 2_056, 33, 9, 140_257), (42_905, 3_856, 24, 7, 54_955)])
+def test_the_tests_of_parts_by_lines_of_memory_reach_them(plans, N, d, B, k, size):
+    """... of test_parts_of_lines_of_memory: more than one part by lines, and the whole in other groups of rows."""
+    whole, p = flat(plans, N, d, 0, B, k, 1 << 30), flat(plans, N, d, 0, B, k, size)
+    assert KINDS[p["kind"]] == "wide" and p["bytes"] <= size and p["shape"] == THIN and p["gs_log"] > 0
+    assert 2 * p["rows"] <= N and plans.by_line(p["rows"], d, col_tiles(B, THIN))
+    assert KINDS[whole["kind"]] == "wide" and whole["rows"] == N and whole["gs_log"] != p["gs_log"]
 
 
 @pytest.mark.parametrize("N,d,B,k,buffer", [
