@@ -36,11 +36,13 @@
 // B = 1, ef = 64 with its coarse search 108 / 99.5; maturity exit, rows of 768 bytes, B = 256, ef = 64 and 256 0.97 to 1.00 times as long.
 // The ordered list in LDS that this replaces cost 12 to 15 k clocks a step: 64 list positions looked up, one list in two parts merged, cut
 // and rebuilt (200 k x 768, B = 256, ef = 2048 5190 us; more, and the maturity exit, at frontier_pays).
-// Off the chain of a step (together 200 k x 768, R = 32: B = 1, ef = 64 with its coarse search 121.5 / 118.3 us, B = 256, ef = 2048 2164 / 2120, B = 512,
-// ef = 256 712 / 672; 200 k x 256, B = 32, ef = 512 628 / 569): loads that only warm the caches are waited for with the next adjacency rows instead of
-// before the barrier; the ranks of many new keys come from compares with a lane's key (eight reads of 16 bytes a lane, by eight waves, kept
-// the LDS busy for as long as the compares took); the marks, LDS atomics by every wave, some 500 clocks of that queue, go ahead of the insertion,
-// which hardly reads the LDS, by eight waves (by four, two workgroups a compute unit, that is 1 % longer).
+// Off the chain of a step (together 200 k x 768, R = 32: B = 256, ef = 2048 2164 / 2120 us, B = 512, ef = 256 712 / 672; 200 k x 256, B = 32, ef = 512 628 / 569; B = 1,
+// ef = 64 with its coarse search 134 / 130, eight queries): the ranks of many new keys come from compares with a lane's key (eight
+// reads of 16 bytes a lane, by eight waves, kept the LDS busy for as long as the compares took); loads that only warm the caches are waited for with the next
+// adjacency rows instead of before the barrier; the marks, LDS atomics by every wave, some 500 clocks of that queue, go ahead of the insertion,
+// which hardly reads the LDS, by eight waves (by four, two workgroups a compute unit, that is 1 % longer).  One of them alone undone, ranks / waits /
+// marks, % longer: B = 1, ef = 64 3.9 / 0.8 / 1.3, B = 256, ef = 2048 1.5 / 1.5 / 0.2, B = 512, ef = 256 4.2 / 0.5 / -0.1; 200 k x 256, B = 32, ef = 512 3.0 / 2.0 / 1.1; with the
+// maturity exit, 200 k x 384, B = 256, ef = 256 -0.5 / -1.1 / -0.9, and 0.5 with the average by all waves (200 k x 768, R = 24, B = 10, ef = 400 1.9).
 // Keeping the keys of uncommitted neighbours takes the rows a step loads from 54 to 26 at ef = 2048; 64-bit compares instead
 // of maxima of doubles in the networks and insertions cost 4 % of a short list.  Not faster: 8 waves and two workgroups per compute
 // unit (413 us against 309 at B = 512, ef = 64: 128 registers a lane), the smallest place a neighbour stops found by LDS atomics before the
@@ -342,7 +344,7 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
     uint64_t *ck = reinterpret_cast<uint64_t *>(smem + FrontierLds::CK);               // [2][64] keys of a step's neighbours
     uint64_t *sorted = reinterpret_cast<uint64_t *>(smem + FrontierLds::SORTED);       // [64]
     int *at_hash = reinterpret_cast<int *>(smem + FrontierLds::HASH);                  // [2][HASHES] where a neighbour is among them
-    int *ctl = reinterpret_cast<int *>(smem + FrontierLds::CTL);                       // [2][8] a count of every wave; the ready word
+    int *ctl = reinterpret_cast<int *>(smem + FrontierLds::CTL);                       // [2][8] a count of every wave; the ready word; [2] the moving average
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int *ent = reinterpret_cast<int *>(smem + FrontierLds::WAVES + wave * FrontierLds::WAVE_BYTES);   // [64] this wave's list of the neighbours, and [64]
     int *ent_u = ent + FrontierLds::WAVE_BYTES / 8;                                                   // whose they are (and a place for the rest)
@@ -705,7 +707,7 @@ __global__ __launch_bounds__(NW * WAVE, OCC) void graph_frontier_kernel(
         if (wave == NW - 1) {                             // (the last wave has the fewest rows)
             // The adjacency rows of the queue's next nodes into the L2, out of which the rows drive what is not asked for again
             // (frontier_ahead says where that pays).  Not before there is a pool (what is scored lately is there), nor with the maturity
-            // exit (267 against 261 us at 200 k x 384, ef = 256).
+            // exit, where it changes nothing (200 k x 384, B = 256, ef = 64, 256, 1024 116.7 / 115.9, 246.8 / 246.2, 763.6 / 763.2 us with).
             if (!NS && frontier_ahead(NW) && live > 0 && lane >= W && lane < AHEAD && t != 0) ahead = graph[(size_t)key_node(t) * R];
             if (known) {
                 const int slot = n_need + rank_in(__builtin_amdgcn_ballot_w64(known));

@@ -178,9 +178,10 @@ constexpr int64_t PART_MIN_ROWS = 8192;          // fewer are not worth a launch
 //     70.9 / 61.5, x 776 310 / 292, x 800 287 / 272, x 1000 387 / 369; 100 k x 616, B = 4 38.2 / 36.5; but 1 M x 104 48.3 / 55.7, x 224 84.4 / 86.2 by 3.
 //   more queries, such rows: 5 or 3 where that divides the row: 1 M x 776, B = 48 316 / 300; x 456, B = 32 188 / 180; 3 M x 160, B = 32 212 / 186; 1 M x 264,
 //     B = 48 128 / 121; else 4 (1 M x 616, B = 48 251 / 258 by 3).
-//   more than 32 queries, whole lines of at least 768 bytes: 2: 21 M x 384, B = 64, k = 5 2706 / 2657; 1 M x 384, B = 48 153 / 143, x 768, B = 64 288 / 277, x 1024
-//     361 / 355; 300 k x 576, B = 48 79 / 74.6; shorter 3 M x 256, B = 64 303 / 311.  17 to 32 queries: whole lines of 384 to 640 bytes: 1 M x 256
-//     103 / 95.7, x 320 127 / 121, 3 M x 256 271 / 258; but 300 k x 768 92.9 / 95.0, 3 M x 512 512 / 523, 1.6 M x 128 86 / 91.
+//   whole lines: two batches of 2 are half the bytes in flight, and a batch ends with its row.  With 17 to 32 queries, whose products cover less, what that
+//     costs grows with the row: 1 M x 192, 256, 320, 384, 512, 768, 1024 0.92, 0.93, 0.95, 0.98, 1.01, 1.026, 1.036 times as long by 2, 1.6 M x 128 86 / 91: 2 for 384 to
+//     640 bytes (1 M x 256 103 / 95.7).  More queries: 1 M x 448, 512, 768, 1024, B = 48 0.92, 0.95, 0.98, 0.99, B = 64 0.95, 0.96, 0.954, 0.98; 21 M x 384, B = 64, k = 5 2706 / 2657;
+//     shorter 3 M x 192 and 320, B = 48 0.93 and 0.945, but x 192, B = 55 1.03, x 256, B = 64 303 / 311: 2 from 768 bytes on.
 // fp32, up to 16 queries, whole sectors of 64 bytes, of which batches of 4 load idle ones or split a line between two tiles: 2 where the row is
 //   2 or 6 or 10 ... of them (1 M x 96, B = 4 80.6 / 73.5; 100 k x 208, B = 12 27.9 / 25.8; 270 sizes up to x 1024 0.96), an odd number up to 13 (x 80
 //     0.94, x 208 0.94; but 3 M x 240 1 / 1.02, 561 k x 752, B = 10 304 / 316), and whole batches of 4 of 8 to 32 sectors, for their smaller portions (x 128 0.945; but
@@ -416,8 +417,10 @@ inline int wide_tile(int cus, int64_t N, int d, int B, int k) {
 //   for every element.  So lists are quicker where N (d - r) > q, r elements for what a row costs and q, in millions, for settling; with 17 to 32 queries
 //   r = 67.5, q = 65; to 48 82.5, 150; to 64 110, 180.  A row that batches of loads do not divide costs lists about half of what is loaded for nothing
 //   (x 192 in batches of 128 elements), and long answers of 0.5 to 1.25 Mi rows cost the matrix cores 2 %, groups of rows scored again (3 to 5 % less beyond
-//   4 Mi, which the line leaves out).  Fitted to both kernels at 725 sizes within 0.6 to 1.7 times the line, 131 k to 22 M rows: 0.6 % behind the better one on
-//   average, 10 % at worst from 200 k rows on, 18 % below.  Rows of 768 elements and more keep their lists (341 k x 840, B = 51 141 / 126, 133 k x 960, B = 39
+//   4 Mi, which the line leaves out).  Fitted to both kernels at 725 sizes within 0.6 to 1.7 times the line, 131 k to 22 M rows.  Of 7 941
+//   pairs of times within 0.6 to 1.45 times of it, corpora below 256 MiB read again too, which moves them to the matrix cores: 1.8 % behind the better
+//   of the pair on average (the line by queries 4.2 %), 1.2 % of the pairs more than 5 % longer than by the line by queries, by most for full
+//   groups of 17 to 32 queries, which lists take in less time (8.5 M x 72, B = 32 353 / 301; 9.0 M x 72, B = 24 1 / 1.06).  Rows of 768 elements and more keep their lists (341 k x 840, B = 51 141 / 126, 133 k x 960, B = 39
 //   69 / 62; from 500 k rows on they are the quicker ones).  us, two, three and four groups: 300 k x 96, B = 20 28.2 / 21.0, x 288, B = 32
 //   45.1 / 48.5; 1 M x 128, B = 24 64.7 / 59.9, x 192, B = 32 77.6 / 83.8; 3 M x 128, B = 32 148 / 183; 138 k x 464, B = 44, k = 5 50.5 / 38.7; 1 M x 256, B = 48
 //   110 / 117; 1.03 M x 232, B = 45 116 / 124; 4.4 M x 88, B = 41, k = 5 288 / 221; 207 k x 520, B = 45 67.7 / 55.5; 1 M x 320, B = 64 153 / 148, x 384 158 / 171;
@@ -821,10 +824,9 @@ constexpr int FRONTIER_MOST = 63;                         // most neighbours a s
 constexpr int FRONTIER_VIS_LDS = 0, FRONTIER_VIS_GLOBAL = 1;              // where the visited set is
 constexpr int FRONTIER_SPARE = 512, FRONTIER_SPARE_MIN = 280, FRONTIER_SPARE_TIGHT = 124;   // places beyond ef, at least; where room is what counts; tight
 // Whether a step of graph_frontier_kernel touches the adjacency rows of the queue's next nodes ahead.  Of eight waves the last one, which does so, seldom
-// has a row to score: R = 32, B = 1, ef = 512, 1024, 2048 1.2, 2.7, 3.1 % longer without (200 k x 768 fp16; 0.1, 0.9, 2.1 % at 100 k x 256, but 1.6 %
-// shorter at ef = 128, which a test of ef in the step would cost lists of up to 64 entries half of; taken while the wave waited for them, which no
-// longer is so).  Two workgroups of four waves keep the memory path busy with rows: with / without, us, 200 k x 768, R = 32, B = 512, ef = 256 710 / 702 and
-// 693 / 677, 200 k x 384, B = 1000, ef = 200 784 / 779 and 818 / 803.
+// has a row to score: without, 200 k x 768 fp16, R = 32, B = 1, ef = 64, 256, 512, 1024, 2048 3.0, 3.3, 4.2, 5.5, 6.8 % longer (six queries each), B = 256, ef = 128,
+// 512, 2048 3.2, 4.4, 6.3 %, 200 k x 256, B = 32 4.0, 5.1, 7.9 %.  Two workgroups of four waves keep the memory path busy with rows: with / without, us,
+// 200 k x 768, R = 32, B = 512, ef = 256 710 / 702 and 693 / 677, 200 k x 384, B = 1000, ef = 200 784 / 779 and 818 / 803.
 constexpr bool frontier_ahead(int waves) { return waves == 8; }
 
 struct FrontierLds {

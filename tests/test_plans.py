@@ -197,8 +197,8 @@ def test_graph_kernels_where_they_were_measured_to_pay(plans, N, row, R, B, ef, 
 
 # us of a call with adjacency rows touched ahead / without, 200 k x 768, R = 32, B = 256 and 512
 @pytest.mark.parametrize("B,ef,ahead", [
-    (256, 2048, True),           # 2202 / 2265: the last of eight waves has nothing else to wait for
-    (512, 512, False),           # 1110 / 1030: the last of four has
+    (256, 2048, True),           # 2121 / 2255: the last of eight waves seldom has a row to score
+    (512, 512, False),           # 1110 / 1030: two workgroups of four keep the memory path busy with rows
     (512, 128, False)])          # 443 / 429
 def test_adjacency_rows_touched_ahead_where_that_pays(plans, B, ef, ahead):
     out = (ctypes.c_int64 * 14)()
